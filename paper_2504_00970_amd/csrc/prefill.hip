@@ -1,6 +1,7 @@
 // Prefill kernels: sentence segmentation (Sec. 4.1, Alg. 1 prefilling phase) and per-bucket mean key
 // vectors (Eq. 1).  gfx950, wave64.
 #include "skv_internal.h"
+#include "skv_device.h"
 
 namespace skv {
 
@@ -173,7 +174,37 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float f) {
     return sign | code;
 }
 
-template <int EB, int SVB>     // SVB: bytes per stored element of the table (4 = fp32, 2 = bf16, 1 = E4M3; rounded to nearest even)
+// One lane's EPL means (sums / n) of a bucket to element `o` of the table.  SVB: bytes per stored element (4 = fp32, 2 = bf16,
+// 1 = E4M3; rounded to nearest even).
+template <int EPL, int SVB, bool STREAM>
+__device__ __forceinline__ void store_means(char* __restrict__ semvec, int64_t o, const float* acc, float n) {
+#pragma unroll
+    for (int i = 0; i < EPL; i += 4) {
+        const float m[4] = {acc[i] / n, acc[i + 1] / n, acc[i + 2] / n, acc[i + 3] / n};
+        if (SVB == 4) {
+            const uint4 v = make_uint4(__float_as_uint(m[0]), __float_as_uint(m[1]), __float_as_uint(m[2]), __float_as_uint(m[3]));
+            if (STREAM) st_stream(semvec + (o + i) * 4, v);
+            else *reinterpret_cast<uint4*>(semvec + (o + i) * 4) = v;
+        } else if (SVB == 1) {
+            *reinterpret_cast<uint32_t*>(semvec + (o + i)) = f32_to_e4m3(m[0]) | (f32_to_e4m3(m[1]) << 8) |
+                                                             (f32_to_e4m3(m[2]) << 16) | (f32_to_e4m3(m[3]) << 24);
+        } else {
+            uint32_t rb[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t u = __float_as_uint(m[k]);
+                u += 0x7fffu + ((u >> 16) & 1u);               // round to nearest even bf16 (means are finite)
+                rb[k] = u >> 16;
+            }
+            *reinterpret_cast<uint2*>(semvec + (o + i) * 2) = make_uint2(rb[0] | (rb[1] << 16), rb[2] | (rb[3] << 16));
+        }
+    }
+}
+
+// Bound by HBM: the pool once in, the table once out.  A wave per bucket, one-shot waves with all the rows of a bucket of
+// average length requested at once.  32 layers x 8 heads x 32768 tokens in bf16 (2.36 GB): 431 us with plain accesses and 4
+// waves per block, 404 with non-temporal loads and stores, 383-395 with 8 waves per block (contiguous 40 KB per block).
+template <int EB, int SVB>
 __global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(const char* __restrict__ K, int32_t T,
                                                                               const int32_t* __restrict__ sent_off_all,
                                                                               int32_t off_layer_stride, int32_t Hkv,
@@ -199,7 +230,7 @@ __global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(co
         for (int u = 0; u < kUnroll; ++u) {
             const int32_t x = x0 + u * R::RPW;
             // clamped address + masked value keeps the kUnroll loads independent of the bounds test
-            const uint4 t = *reinterpret_cast<const uint4*>(base + (int64_t)min(x, e - 1) * (kHeadDim * EB));
+            const uint4 t = ld_stream(base + (int64_t)min(x, e - 1) * (kHeadDim * EB));
             v[u] = (x < e) ? t : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
@@ -217,50 +248,79 @@ __global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(co
     }
     if (r == 0) {
         const float n = (e > b) ? (float)(e - b) : 1.f;      // a bucket without tokens yields zeros
-        const int64_t o = (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL;      // element index of the lane's first output
-#pragma unroll
-        for (int i = 0; i < R::EPL; i += 4) {
-            const float m[4] = {acc[i] / n, acc[i + 1] / n, acc[i + 2] / n, acc[i + 3] / n};
-            if (SVB == 4) {
-                *reinterpret_cast<float4*>(semvec + (o + i) * 4) = make_float4(m[0], m[1], m[2], m[3]);
-            } else if (SVB == 1) {
-                *reinterpret_cast<uint32_t*>(semvec + (o + i)) = f32_to_e4m3(m[0]) | (f32_to_e4m3(m[1]) << 8) |
-                                                                 (f32_to_e4m3(m[2]) << 16) | (f32_to_e4m3(m[3]) << 24);
-            } else {
-                uint32_t rb[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    uint32_t u = __float_as_uint(m[k]);
-                    u += 0x7fffu + ((u >> 16) & 1u);               // round to nearest even bf16 (means are finite)
-                    rb[k] = u >> 16;
-                }
-                *reinterpret_cast<uint2*>(semvec + (o + i) * 2) = make_uint2(rb[0] | (rb[1] << 16), rb[2] | (rb[3] << 16));
-            }
-        }
+        store_means<R::EPL, SVB, true>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
     }
 }
 
-template <int EB>
-static void launch_semvec_eb(Ctx* c, dim3 grid, dim3 block, const void* K_pool, int32_t T, const int32_t* sent_off,
-                             int32_t off_layer_stride, int32_t S, void* semvec) {
-    if (c->d.semvec_dtype == SKV_BF16)
-        hipLaunchKernelGGL((semvec_kernel<EB, 2>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
-                           c->d.n_kv_heads, S, (char*)semvec);
-    else if (c->d.semvec_dtype == SKV_FP8_E4M3)
-        hipLaunchKernelGGL((semvec_kernel<EB, 1>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
+// Short buckets (a retained pool keeps a few tokens of each): the row's LPR lanes own a bucket, RPW buckets per wave, and walk
+// its rows; no sum across lanes, and the table's rows are stored RPW at a time.  A wave per bucket is bound by the number of
+// waves here: 32 x 8 x 4096 retained tokens in 1654 buckets (485 MB), 161-169 us with a wave per bucket, 90 us with this.
+template <int EB, int SVB>
+__global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_short_kernel(const char* __restrict__ K, int32_t T,
+                                                                                    const int32_t* __restrict__ sent_off_all,
+                                                                                    int32_t off_layer_stride, int32_t Hkv,
+                                                                                    int32_t S, char* __restrict__ semvec) {
+    using R = Row<EB>;
+    constexpr int kUnroll = 4;
+    const int lane = threadIdx.x & 63, cc = lane % R::LPR;
+    const int32_t s = (blockIdx.x * kSemvecWavesPerBlock + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
+    if (s >= S) return;
+    const int64_t lh = blockIdx.y;
+    const int32_t* sent_off = sent_off_all + (int64_t)(blockIdx.y / Hkv) * off_layer_stride;   // the layer's table
+    const int32_t b = max(sent_off[s], 0), e = min(sent_off[s + 1], T);   // never read outside the pool
+    const char* base = K + (lh * T) * (int64_t)(kHeadDim * EB) + (int64_t)cc * 16;
+    float acc[R::EPL];
+#pragma unroll
+    for (int i = 0; i < R::EPL; ++i) acc[i] = 0.f;
+    for (int32_t x0 = b; x0 < e; x0 += kUnroll) {
+        uint4 v[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const uint4 t = *reinterpret_cast<const uint4*>(base + (int64_t)min(x0 + u, e - 1) * (kHeadDim * EB));
+            v[u] = (x0 + u < e) ? t : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            float f[R::EPL];
+            R::unpack(v[u], f);
+#pragma unroll
+            for (int i = 0; i < R::EPL; ++i) acc[i] += f[i];
+        }
+    }
+    const float n = (e > b) ? (float)(e - b) : 1.f;          // a bucket without tokens yields zeros
+    store_means<R::EPL, SVB, false>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
+}
+
+template <int EB, int SVB>
+static void launch_semvec_t(Ctx* c, const void* K_pool, int32_t T, const int32_t* sent_off, int32_t off_layer_stride, int32_t S,
+                            void* semvec) {
+    // By the bytes of a bucket's rows: 16 layers x 8 heads x 32768 tokens in buckets of n tokens, wave per bucket against several
+    // per wave, us: bf16 pool, fp32 table, n = 6: 323 / 248, 8: 255 / 242, 10: 221 / 233, 24: 186 / 222; fp32 pool, n = 2:
+    // 738 / 530, 4: 460 / 490, 8: 378 / 464.  Smaller tables move the line up a little (E4M3, n = 10: 225 / 202).
+    const bool is_short = (int64_t)T * (kHeadDim * EB) < kSemvecShortBytes * (int64_t)S;
+    const int per_block = kSemvecWavesPerBlock * (is_short ? Row<EB>::RPW : 1);
+    const dim3 grid((S + per_block - 1) / per_block, c->d.n_layers * c->d.n_kv_heads), block(kSemvecWavesPerBlock * kWave);
+    if (is_short)
+        hipLaunchKernelGGL((semvec_short_kernel<EB, SVB>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
                            c->d.n_kv_heads, S, (char*)semvec);
     else
-        hipLaunchKernelGGL((semvec_kernel<EB, 4>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
+        hipLaunchKernelGGL((semvec_kernel<EB, SVB>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
                            c->d.n_kv_heads, S, (char*)semvec);
+}
+
+template <int EB>
+static void launch_semvec_eb(Ctx* c, const void* K_pool, int32_t T, const int32_t* sent_off, int32_t off_layer_stride, int32_t S,
+                             void* semvec) {
+    if (c->d.semvec_dtype == SKV_BF16) launch_semvec_t<EB, 2>(c, K_pool, T, sent_off, off_layer_stride, S, semvec);
+    else if (c->d.semvec_dtype == SKV_FP8_E4M3) launch_semvec_t<EB, 1>(c, K_pool, T, sent_off, off_layer_stride, S, semvec);
+    else launch_semvec_t<EB, 4>(c, K_pool, T, sent_off, off_layer_stride, S, semvec);
 }
 
 hipError_t launch_semvec(Ctx* c, const void* K_pool, int32_t T, const int32_t* sent_off, int32_t off_layer_stride, int32_t S,
                          void* semvec) {
     if (S == 0) return hipSuccess;
-    const dim3 grid((S + kSemvecWavesPerBlock - 1) / kSemvecWavesPerBlock, c->d.n_layers * c->d.n_kv_heads);
-    const dim3 block(kSemvecWavesPerBlock * kWave);
-    if (c->d.kv_dtype == SKV_BF16) launch_semvec_eb<2>(c, grid, block, K_pool, T, sent_off, off_layer_stride, S, semvec);
-    else launch_semvec_eb<4>(c, grid, block, K_pool, T, sent_off, off_layer_stride, S, semvec);
+    if (c->d.kv_dtype == SKV_BF16) launch_semvec_eb<2>(c, K_pool, T, sent_off, off_layer_stride, S, semvec);
+    else launch_semvec_eb<4>(c, K_pool, T, sent_off, off_layer_stride, S, semvec);
     return hipGetLastError();
 }
 

@@ -16,7 +16,8 @@ constexpr int kSegThreads = 256;
 constexpr int kSegTokPerThread = 4;
 constexpr int kSegTokPerBlock = kSegThreads * kSegTokPerThread;      // 1024 tokens per block
 
-constexpr int kSemvecWavesPerBlock = 4;                               // one wave per (layer*head, bucket)
+constexpr int kSemvecWavesPerBlock = 8;
+constexpr int kSemvecShortBytes = 2304;       // mean bytes of a bucket's rows below which a wave takes several buckets
 
 constexpr int kScoreRowsPerWave = 8;          // buckets per wave (32 per block)
 constexpr int kScoreWavesPerBlock = 4;
