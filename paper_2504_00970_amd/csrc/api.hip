@@ -47,6 +47,27 @@ inline int elt_bytes(const Ctx& c) { return c.d.kv_dtype == SKV_BF16 ? 2 : 4; }
 inline int sv_bytes(const Ctx& c) { return c.d.semvec_dtype == SKV_BF16 ? 2 : c.d.semvec_dtype == SKV_FP8_E4M3 ? 1 : 4; }
 
 
+// ---- skv_segment's wait for the number of sentences ---------------------------------------------------------------------
+constexpr unsigned int kNoCount = 0xffffffffu;
+
+// The kernel stores the count after it has written all its results back, and it starts after everything queued before
+// it: once the word is there, the stream's work up to this call is done.  Polling a word of host memory costs about a
+// microsecond where a copy and a stream synchronisation cost 15.  The stream is asked every few thousand reads, so that a
+// launch that failed ends the wait: -1 unless the word arrived.
+int32_t wait_for_count(Ctx& c) {
+    for (;;) {
+        for (int i = 0; i < 4096; ++i) {
+            const unsigned int v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
+            if (v != kNoCount) return (int32_t)v;
+        }
+        const hipError_t e = hipStreamQuery(c.stream);
+        if (e == hipErrorNotReady) continue;
+        const unsigned int v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess && v != kNoCount ? (int32_t)v : -1;
+    }
+}
+
 // ---- workspace: one block of device memory, carved the same way whether skv_create allocated it or it is the static
 // scratch array of skv_decode_step_noalloc ---------------------------------------------------------------------------
 constexpr int kWsParts = 14;
@@ -81,7 +102,7 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     sz[9] = round256(BH * sizeof(int32_t));                                        // f_n_sel
     sz[10] = round256(BH * sizeof(int32_t));                                       // f_n_tok
     sz[11] = round256(BH * d.max_budget * sizeof(int32_t));                        // f_tok_idx
-    sz[12] = 256;                                                                  // err_dev
+    sz[12] = 256;                                                                  // err_dev, seg_arrive
     sz[13] = 0;
     size_t total = 0;
     for (int i = 0; i < kWsParts; ++i) total += sz[i];
@@ -104,7 +125,8 @@ void carve_workspace(Ctx& c, char* base, const size_t sz[kWsParts], int32_t scor
     c.f_n_sel = reinterpret_cast<int32_t*>(p); p += sz[9];
     c.f_n_tok = reinterpret_cast<int32_t*>(p); p += sz[10];
     c.f_tok_idx = reinterpret_cast<int32_t*>(p); p += sz[11];
-    c.err_dev = reinterpret_cast<unsigned int*>(p); p += sz[12];
+    c.err_dev = reinterpret_cast<unsigned int*>(p);
+    c.seg_arrive = reinterpret_cast<unsigned long long*>(p + 128); p += sz[12];
 }
 
 void fill_context(Ctx& c, const skv_desc& d, hipStream_t stream, int dev) {
@@ -192,16 +214,19 @@ int skv_create(skv_ctx** out, const skv_desc* desc, void* hip_stream) {
     if (e != hipSuccess) { (void)hipFree(c.ws); delete ctx; return hip_status(e); }
     c.ws_bytes = total;
     carve_workspace(c, c.ws, sz, score_stride);
-    // a word of pinned host memory the kernels can reach: a block of the single-launch step that gives up waiting sets
-    // it, and the next skv_decode_step on this context reports it
+    // two lines of pinned host memory the kernels can reach: a block of the single-launch step that gives up waiting sets
+    // the first word, and the next skv_decode_step on this context reports it; the segmentation stores the number of
+    // sentences in the second line for a skv_segment that waits for it
     void* eh = nullptr;
-    e = hipHostMalloc(&eh, sizeof(unsigned int), hipHostMallocMapped);
+    e = hipHostMalloc(&eh, 32 * sizeof(unsigned int), hipHostMallocMapped);
     if (e == hipSuccess) {
         void* ed = nullptr;
         *static_cast<unsigned int*>(eh) = 0u;
         if (hipHostGetDevicePointer(&ed, eh, 0) == hipSuccess) {
             c.err_host = static_cast<unsigned int*>(eh);
             c.err_host_dev = static_cast<unsigned int*>(ed);
+            c.n_sent_host = c.err_host + 16;
+            c.n_sent_host_dev = c.err_host_dev + 16;
         } else {
             (void)hipGetLastError();
             (void)hipHostFree(eh);
@@ -268,8 +293,17 @@ int skv_segment(skv_ctx* ctx, const int32_t* tok, int32_t T, const uint32_t* ter
     if (T > ctx->c.d.max_tokens) return SKV_ECAPACITY;
     int rc = check_ctx(ctx);
     if (rc != SKV_OK) return rc;
-    rc = hip_status(skv::launch_segment(&ctx->c, tok, T, term_bitmap, vocab, seg_id, sent_off, sent_len, n_sent_dev));
+    Ctx& c = ctx->c;
+    const bool report = n_sent_host && skv::segment_reports(&c, T, vocab);
+    if (report) __atomic_store_n(c.n_sent_host, kNoCount, __ATOMIC_RELAXED);
+    rc = hip_status(skv::launch_segment(&c, tok, T, term_bitmap, vocab, seg_id, sent_off, sent_len, n_sent_dev, report));
     if (rc != SKV_OK || !n_sent_host) return rc;
+    if (report) {
+        const int32_t n = wait_for_count(c);
+        if (n < 0) return SKV_EHIP;
+        *n_sent_host = n;
+        return n > c.d.max_sentences ? SKV_ECAPACITY : SKV_OK;
+    }
     hipError_t e = hipMemcpyAsync(n_sent_host, n_sent_dev, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->c.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->c.stream);
     if (e != hipSuccess) return SKV_EHIP;

@@ -140,8 +140,123 @@ __global__ __launch_bounds__(kSegThreads) void seg_scan_kernel(const int32_t* __
     }
 }
 
+// The same in ONE launch, for prompts of up to kSegOneMaxTok tokens: a block of 1024 threads owns 4096 tokens, keeps the
+// terminator bitmap in LDS and counts the terminators of all tokens before its own by itself, which is cheaper than a second
+// launch (4 tokens per thread and preceding block, from L2).  Bound by latency: two dependent memory round trips and a block
+// scan.  REPORT: the block that finishes last also stores S to pinned host memory, after every block has written its
+// results back to the level the host and all XCDs share, so that the host can poll the word instead of copying it and
+// waiting for the stream.
+template <bool REPORT>
+__global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* __restrict__ tok, int32_t T,
+                                                                const uint32_t* __restrict__ bitmap, int32_t vocab,
+                                                                int32_t* __restrict__ seg_id, int32_t* __restrict__ sent_off,
+                                                                int32_t* __restrict__ sent_len, int32_t cap_sent,
+                                                                int32_t* __restrict__ n_sent, unsigned long long* arrive,
+                                                                unsigned int* host_word) {
+    extern __shared__ uint32_t sm_bits[];                       // [words]
+    __shared__ uint32_t sm_cnt[kBlockWaves], sm_last[kBlockWaves], sm_pre[2][kBlockWaves];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int words = (vocab + 31) >> 5;
+    const int32_t block0 = blockIdx.x * kSegOneBlockTok, i0 = block0 + 4 * tid;
+    int32_t t[4];
+    if (i0 + 4 <= T) {
+        const int4 v = *reinterpret_cast<const int4*>(tok + i0);
+        t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = i0 + k < T ? tok[i0 + k] : -1;
+    }
+    for (int i = tid; i < words; i += kBlockThreads) sm_bits[i] = bitmap[i];
+    __syncthreads();
+    auto is_term = [&](int32_t id) -> bool {
+        return (uint32_t)id < (uint32_t)vocab && ((sm_bits[(uint32_t)id >> 5] >> (id & 31)) & 1u);
+    };
+    // terminators before the block: number, and 1 + position of the last one (0: none)
+    uint32_t pre_cnt = 0, pre_last = 0;
+    for (int32_t j = 4 * tid; j < block0; j += kSegOneBlockTok) {
+        const int4 v = *reinterpret_cast<const int4*>(tok + j);
+        const int32_t p[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (is_term(p[k])) { pre_cnt += 1; pre_last = (uint32_t)(j + k + 1); }
+    }
+    uint32_t cnt = 0, last = 0, flags = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (is_term(t[k])) { flags |= 1u << k; cnt += 1; last = (uint32_t)(i0 + k + 1); }
+    const uint32_t inc = wave_scan_u32(cnt), inl = wave_scan_max_u32(last);
+    const uint32_t pc = wave_scan_u32(pre_cnt), pl = wave_scan_max_u32(pre_last);
+    if (lane == 63) { sm_cnt[w] = inc; sm_last[w] = inl; sm_pre[0][w] = pc; sm_pre[1][w] = pl; }
+    __syncthreads();
+    uint32_t seg = 0, start = 0;
+#pragma unroll
+    for (int i = 0; i < kBlockWaves; ++i) {
+        seg += sm_pre[0][i] + (i < w ? sm_cnt[i] : 0u);
+        start = max(start, max(sm_pre[1][i], i < w ? sm_last[i] : 0u));
+    }
+    seg += inc - cnt;
+    const uint32_t before = (uint32_t)__shfl_up((int)inl, 1);
+    if (lane > 0) start = max(start, before);
+    int32_t id[4];
+    uint32_t total = 0;                                          // S, in the thread that closes the prompt
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int32_t i = i0 + k;
+        id[k] = (int32_t)seg;
+        if (i < T && (((flags >> k) & 1u) || i == T - 1)) {
+            if ((int32_t)seg < cap_sent) { sent_off[seg] = (int32_t)start; sent_len[seg] = i + 1 - (int32_t)start; }
+            if (i == T - 1) {
+                total = seg + 1;
+                *n_sent = (int32_t)total;
+                if ((int32_t)total <= cap_sent) sent_off[total] = T;
+            }
+            start = (uint32_t)(i + 1);
+            seg += 1;
+        }
+    }
+    if (i0 + 4 <= T) {
+        *reinterpret_cast<int4*>(seg_id + i0) = make_int4(id[0], id[1], id[2], id[3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i0 + k < T) seg_id[i0 + k] = id[k];
+    }
+    if (REPORT) {
+        __shared__ uint32_t sm_total;
+        if (tid == 0) sm_total = 0u;
+        __syncthreads();
+        if (total != 0u) sm_total = total;
+        __threadfence_system();
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned long long mine = (1ull << 32) | (unsigned long long)sm_total;
+            const unsigned long long all = mine + __hip_atomic_fetch_add(arrive, mine, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM);
+            if ((uint32_t)(all >> 32) == gridDim.x) {
+                __hip_atomic_store(arrive, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next call
+                __hip_atomic_store(host_word, (uint32_t)all, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+    }
+}
+
+// One launch while the prompt and the bitmap fit it (an empty prompt takes the two-launch form's early exit).
+static bool segment_in_one(int32_t T, int32_t vocab) { return T > 0 && T <= kSegOneMaxTok && (vocab - 1) / 32 < kSegOneMaxWords; }
+
+bool segment_reports(const Ctx* c, int32_t T, int32_t vocab) { return c->n_sent_host && segment_in_one(T, vocab); }
+
 hipError_t launch_segment(Ctx* c, const int32_t* tok, int32_t T, const uint32_t* bitmap, int32_t vocab,
-                          int32_t* seg_id, int32_t* sent_off, int32_t* sent_len, int32_t* n_sent_dev) {
+                          int32_t* seg_id, int32_t* sent_off, int32_t* sent_len, int32_t* n_sent_dev, bool report) {
+    if (segment_in_one(T, vocab)) {
+        const dim3 grid((T + kSegOneBlockTok - 1) / kSegOneBlockTok), block(kBlockThreads);
+        const size_t lds = (size_t)((vocab - 1) / 32 + 1) * sizeof(uint32_t);
+        if (report)
+            hipLaunchKernelGGL(seg_one_kernel<true>, grid, block, lds, c->stream, tok, T, bitmap, vocab, seg_id, sent_off, sent_len,
+                               c->d.max_sentences, n_sent_dev, c->seg_arrive, c->n_sent_host_dev);
+        else
+            hipLaunchKernelGGL(seg_one_kernel<false>, grid, block, lds, c->stream, tok, T, bitmap, vocab, seg_id, sent_off, sent_len,
+                               c->d.max_sentences, n_sent_dev, nullptr, nullptr);
+        return hipGetLastError();
+    }
     const int nb = (T + kSegTokPerBlock - 1) / kSegTokPerBlock;
     if (nb > 0) {
         hipLaunchKernelGGL(seg_count_kernel, dim3(nb), dim3(kSegThreads), 0, c->stream, tok, T, bitmap, vocab,

@@ -15,6 +15,9 @@ constexpr int kWave = 64;
 constexpr int kSegThreads = 256;
 constexpr int kSegTokPerThread = 4;
 constexpr int kSegTokPerBlock = kSegThreads * kSegTokPerThread;      // 1024 tokens per block
+constexpr int kSegOneBlockTok = 4096;         // single-launch segmentation: 1024 threads x 4 tokens per block
+constexpr int kSegOneMaxTok = 131072;         // prompts it takes
+constexpr int kSegOneMaxWords = 15360;        // terminator bitmap words it keeps in LDS (vocabularies up to 491520)
 
 constexpr int kSemvecWavesPerBlock = 8;
 constexpr int kSemvecShortBytes = 2304;       // mean bytes of a bucket's rows below which a wave takes several buckets
@@ -72,6 +75,9 @@ struct Ctx {
     unsigned int* err_dev;       // [1] set by a block of the single-launch step that gave up waiting
     unsigned int* err_host;      // the same flag in pinned host memory (host address; null: none)
     unsigned int* err_host_dev;  // device address of err_host
+    unsigned long long* seg_arrive;  // [1] blocks of the segmentation that are done (high word) and S (low word); zero between calls
+    unsigned int* n_sent_host;   // S of the last segmentation in pinned host memory (host address; null: none)
+    unsigned int* n_sent_host_dev;   // its device address
     int wait_limit;              // polling rounds before a waiting block gives up
     bool single_launch;          // skv_decode_step may take the single-launch form
 };
@@ -89,8 +95,11 @@ struct SeqView {
 };
 
 // ---- launchers (defined in prefill.hip / decode.hip); each returns the hipError_t of its launch -----
+// report: every result is written back and S then stored to n_sent_host, for a host that polls it (only where
+// segment_reports says that the launch can do it)
+bool segment_reports(const Ctx* c, int32_t T, int32_t vocab);
 hipError_t launch_segment(Ctx* c, const int32_t* tok, int32_t T, const uint32_t* bitmap, int32_t vocab,
-                          int32_t* seg_id, int32_t* sent_off, int32_t* sent_len, int32_t* n_sent_dev);
+                          int32_t* seg_id, int32_t* sent_off, int32_t* sent_len, int32_t* n_sent_dev, bool report);
 // off_layer_stride: 0 = one offset table for all layers, else the distance (in entries) between the layers' tables
 hipError_t launch_semvec(Ctx* c, const void* K_pool, int32_t T, const int32_t* sent_off, int32_t off_layer_stride, int32_t S,
                          void* semvec);
