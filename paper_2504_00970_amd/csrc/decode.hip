@@ -219,7 +219,7 @@ __device__ __forceinline__ void score_wave_f32(const char* __restrict__ q_grp, c
 #pragma unroll
     for (int i = 0; i < kIter; ++i) {
         const int32_t s = min(row0 + 2 * i, n_sent - 1);
-        x[i] = *reinterpret_cast<const float4*>(base + (int64_t)s * kHeadDim);
+        x[i] = __builtin_bit_cast(float4, ld_stream(base + (int64_t)s * kHeadDim));
     }
     float p[kIter];
 #pragma unroll
@@ -270,7 +270,7 @@ __device__ __forceinline__ void score_wave_bf16(const char* __restrict__ q_grp, 
 #pragma unroll
     for (int i = 0; i < kIter; ++i) {                       // clamped addresses: all loads issued back to back
         const int32_t s = min(row0 + 4 * i, n_sent - 1);
-        x[i] = *reinterpret_cast<const uint4*>(base + (int64_t)s * (kHeadDim * 2));
+        x[i] = ld_stream(base + (int64_t)s * (kHeadDim * 2));
     }
     float p[kIter];
 #pragma unroll
@@ -333,7 +333,7 @@ __device__ __forceinline__ void score_wave_e4m3(const char* __restrict__ q_grp, 
 #pragma unroll
     for (int i = 0; i < kIter; ++i) {                       // clamped addresses: all loads issued back to back
         const int32_t s = min(row0 + 8 * i, n_sent - 1);
-        x[i] = *reinterpret_cast<const uint4*>(base + (int64_t)s * kHeadDim);
+        x[i] = ld_stream(base + (int64_t)s * kHeadDim);
     }
     float p[kIter];
 #pragma unroll
@@ -1057,6 +1057,13 @@ __device__ __forceinline__ void demand_step_args(const AttArgs& a) {
                  "s"(a.score_stride), "s"(a.step_part), "s"(a.wait_limit), "s"(a.err_dev), "s"(a.err_host));
 }
 
+// 16 bytes of a K/V row.  POOL: rows straight from the pool are read once (non-temporal: 32 layers of one 32K sequence 456 ->
+// 445 us with the keys' loads, 461 -> 456 with the values' and the mean keys'); rows of K_sel/V_sel have just been written.
+template <bool POOL>
+__device__ __forceinline__ uint4 ld_row(const char* p) {
+    return POOL ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
+}
+
 // CHUNK = retrieved tokens per block: 64 for the latency-bound single-sequence step (most blocks in
 // flight), 256 for batches (fewer partials and arrivals per head, more loads in flight per block).
 template <int EB, int G, int MODE, int CHUNK>
@@ -1315,11 +1322,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 }
                 uint4 kA[4], vR[4];
 #pragma unroll
-                for (int s2 = 0; s2 < 4; ++s2) kA[s2] = *reinterpret_cast<const uint4*>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
+                for (int s2 = 0; s2 < 4; ++s2) kA[s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int32_t rowV = __shfl(rowK, 4 * i + qd);     // lane 4i+qd (< 16) holds the row of token 4i+qd
-                    vR[i] = *reinterpret_cast<const uint4*>(Vh + (int64_t)rowV * kRowBytes + 16 * t16);
+                    vR[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV * kRowBytes + 16 * t16);
                 }
                 const unsigned long long vm = __ballot(liveK);        // bit t (t < 16): token t of the tile is real
                 SKV_T(5);
@@ -1425,8 +1432,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             uint4 kraw[kIter], vraw[kIter];
 #pragma unroll
             for (int i = 0; i < kIter; ++i) {
-                kraw[i] = *reinterpret_cast<const uint4*>(Kh + (int64_t)rowi[i] * kRowBytes + cc * 16);
-                vraw[i] = *reinterpret_cast<const uint4*>(Vh + (int64_t)rowi[i] * kRowBytes + cc * 16);
+                kraw[i] = ld_row<MODE != kDirect>(Kh + (int64_t)rowi[i] * kRowBytes + cc * 16);
+                vraw[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowi[i] * kRowBytes + cc * 16);
             }
             SKV_T(5);
 
@@ -1798,7 +1805,10 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
     // rows of a tile: lanes with the same t16 hold the row of the tile's token t16 (-1: not real)
     auto rows_of = [&](int tile) { return ss.row[16 * tile + t16]; };
     auto issue = [&](int32_t rowt, uint4* k, uint4* v) {
-        // 32-bit byte offsets from the (head, sequence) base: the host only uses this kernel below 2^24 tokens
+        // 32-bit byte offsets from the (head, sequence) base: the host only uses this kernel below 2^24 tokens.
+        // Value rows are requested whole by one instruction and go non-temporal; a key instruction takes 64 bytes of each of
+        // 16 rows, so two of them share every 128-byte line, which must stay until the second (non-temporal key loads:
+        // 6 sequences in 512-token blocks 720 -> 790 us for 32 layers).
         const int32_t rc = max(rowt, 0);
         const uint32_t offK = (uint32_t)rc * kRowBytes + 16u * qd;
 #pragma unroll
@@ -1806,7 +1816,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) {
             const uint32_t offV = (uint32_t)__shfl(rc, 4 * ii + qd) * kRowBytes + 16u * t16;
-            v[ii] = *reinterpret_cast<const uint4*>(Vh + offV);
+            v[ii] = ld_stream(Vh + offV);
         }
     };
     int tile = w;                                                 // wave-uniform

@@ -549,11 +549,11 @@ __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char
     uint4 val[kIter];
 #pragma unroll
     for (int i = 0; i < kIter; ++i)
-        val[i] = *reinterpret_cast<const uint4*>(src + (int64_t)min(max(x[i], 0), T - 1) * kRowBytes + cc * 16);
+        val[i] = ld_stream(src + (int64_t)min(max(x[i], 0), T - 1) * kRowBytes + cc * 16);
 #pragma unroll
     for (int i = 0; i < kIter; ++i) {
         const int32_t j = j0 + i * kRowsPerIter + r;
-        if (j < n && x[i] >= 0 && x[i] < T) *reinterpret_cast<uint4*>(dst + (int64_t)j * kRowBytes + cc * 16) = val[i];
+        if (j < n && x[i] >= 0 && x[i] < T) st_stream(dst + (int64_t)j * kRowBytes + cc * 16, val[i]);
     }
 }
 
