@@ -103,7 +103,7 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     sz[10] = round256(BH * sizeof(int32_t));                                       // f_n_tok
     sz[11] = round256(BH * d.max_budget * sizeof(int32_t));                        // f_tok_idx
     sz[12] = 256;                                                                  // err_dev, seg_arrive
-    sz[13] = 0;
+    sz[13] = fixed_tagged ? 0 : round256((size_t)skv::importance_counters(d) * sizeof(unsigned int));    // imp_arrive
     size_t total = 0;
     for (int i = 0; i < kWsParts; ++i) total += sz[i];
     return total;
@@ -127,6 +127,7 @@ void carve_workspace(Ctx& c, char* base, const size_t sz[kWsParts], int32_t scor
     c.f_tok_idx = reinterpret_cast<int32_t*>(p); p += sz[11];
     c.err_dev = reinterpret_cast<unsigned int*>(p);
     c.seg_arrive = reinterpret_cast<unsigned long long*>(p + 128); p += sz[12];
+    c.imp_arrive = reinterpret_cast<unsigned int*>(p); p += sz[13];
 }
 
 void fill_context(Ctx& c, const skv_desc& d, hipStream_t stream, int dev) {

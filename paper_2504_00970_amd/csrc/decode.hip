@@ -120,30 +120,6 @@ hipError_t launch_query_update(Ctx* c, int32_t B, const void* q_t, const int32_t
     return hipGetLastError();
 }
 
-// Stores that other blocks of the same launch read (possibly on another XCD, each with its own L2): device-scope
-// relaxed atomic accesses go through to the level all XCDs share, so no L2 write-back / invalidate is needed around
-// the arrival counters that publish them.
-__device__ __forceinline__ void st_agent(float* p, float v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(int32_t* p, int32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(unsigned int* p, unsigned int v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_agent(const float* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int32_t ld_agent(const int32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned int ld_agent(const unsigned int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long ld_agent64(const float* p) {       // two consecutive floats
-    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // A float and the tag of the launch that produced it, in one 64-bit word written and read with single relaxed
 // device-scope atomic accesses.  A reader that finds the tag it expects holds the value that belongs to it: nothing has
 // to be ordered against any other location (per-location coherence of atomics is all that is used), so there is no
@@ -157,23 +133,6 @@ __device__ __forceinline__ unsigned long long ld_tagged(const unsigned long long
 }
 __device__ __forceinline__ uint32_t tag_of(unsigned long long w) { return (uint32_t)(w >> 32); }
 __device__ __forceinline__ float val_of(unsigned long long w) { return __uint_as_float((uint32_t)w); }
-
-// Barrier behind which another thread of the block publishes what this block has stored (an arrival counter).  The
-// workgroup barrier by itself does not wait for a wave's outstanding global stores (the waves of a block share their CU's
-// cache, so the compiler leaves the store counter alone at workgroup scope): each wave waits for its own first.
-// ASSUMPTION (of the kernels that publish with a counter: skv_attend, the two- and three-launch forms of
-// skv_decode_step): a device-scope relaxed atomic store that has left the store counter (vmcnt == 0) has reached the
-// level all XCDs share, so a device-scope relaxed load issued by any block after it observed the later counter
-// increment returns the stored value.  The language's memory model does not promise this for relaxed accesses to
-// different locations; it is how write-through stores and the store counter behave on this chip, and it is guarded by
-// test_repeated_launches_reproduce_their_results.  The single-launch step does not rely on it: there every word
-// carries its own validity tag (st_tagged).
-__device__ __forceinline__ void block_sync_after_stores() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-}
-__device__ __forceinline__ float lo_f(unsigned long long v) { return __uint_as_float((uint32_t)v); }
-__device__ __forceinline__ float hi_f(unsigned long long v) { return __uint_as_float((uint32_t)(v >> 32)); }
 
 // ------------------------------------------------------------------------------------------------
 // Scores.  score[h][s] = sum_g q[hG+g] . semvec[h][s]  =  (sum_g q[hG+g]) . semvec[h][s].

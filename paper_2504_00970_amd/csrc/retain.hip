@@ -9,69 +9,79 @@ namespace skv {
 
 // ------------------------------------------------------------------------------------------------
 // Importance.  For one layer and KV head h the window's R = G*N query rows (row = g*N + n: query head
-// h*G+g, window token n, contiguous in q_obs) meet all T keys: S^T = K Q^T / sqrt(D) on
-// v_mfma_f32_16x16x32_bf16, keys as A fragments straight from 16-byte row loads (lane (t, qd): key t of
-// the tile, dims 32s+8qd..+7), query rows as B fragments from an LDS copy.  fp32 inputs are split
+// h*G+g, window token n, contiguous in q_obs) meet all T keys on v_mfma_f32_32x32x16_bf16.  fp32 inputs are split
 // exactly into three bf16 terms -- see Frag -- so that the products keep fp32 accuracy.
 //   pass 1 (stats):   per row, max and sum of exp2 over the keys visible to it (positions <= Tp + n), per block
-//                     of kKeysPerBlock keys; the partials are combined per row by importance_combine_kernel;
+//                     of keys; the block of the (layer, head) that arrives last combines the partials per row;
 //   pass 2 (colsum):  per KV head, the column sums of exp2(s - m_row) / l_row over the head's rows, for the Tp
-//                     prefix keys; importance_sum_heads_kernel adds the heads in ascending order (deterministic).
-// A wave owns 16*KT keys per sweep and walks the row tiles; a block makes kImpSubs sweeps, the next sweep's key
-// fragments being requested before the current sweep is computed (bf16: two register buffers of 32 VGPRs).
-// Each pass covers all layers in one launch (grid z = layer).
+//                     prefix keys; the head whose block arrives last for a range of keys adds the heads in ascending
+//                     order (deterministic).
+// Each pass covers all layers in one launch (grid z = layer).  Its one read of the keys takes 300 us for 32 layers x 8 heads x 32768 keys (a
+// second read within reach of the memory-side cache is no faster, 7.1 TB/s either way), its matrix instructions and
+// exp2 take 260-310 us by themselves at the clock (1.6-2.1 GHz) that the power limit leaves, and the two overlap: 350-400 us a pass.
+//   * The keys go to LDS by asynchronous whole-row non-temporal loads, a ring of stages; the query fragments stay in registers: a wave
+//     owns a row tile and a key tile of every stage.
+//   * Tiles of 32 x 32: a matrix instruction keeps the vector pipe from issuing for 8 cycles, of 32 that it runs (of 16 in the
+//     16 x 16 form).  Next to it a wave issues little more than exp2, fma and add of every logit.
+//   * One key tile's sums are taken while the matrix cores work on the next.
+// Window of 32 tokens, 4 query heads per KV head, 32K tokens: 912-940 us -> 800 us; 1.1K tokens: 55 -> 45; fp32, 8K tokens: 1250 -> 845, 8
+// query heads: 2920 -> 1540.  (Before: fragments straight from memory by 64-byte pieces of 16 rows per load instruction at 5 TB/s,
+// queries from LDS and for fp32 split again for every tile, four launches.)
 // ------------------------------------------------------------------------------------------------
-constexpr int kImpThreads = 256;
-constexpr int kImpWaves = kImpThreads / kWave;
-constexpr int kImpSubs = 4;                                    // sweeps of a block
-template <int EB> struct Imp {
-    static constexpr int KT = EB == 2 ? 2 : 1;                 // 16-key tiles per wave and sweep
-    static constexpr int NB = EB == 2 ? 2 : 1;                 // register buffers of key fragments
-    static constexpr int kKeysPerWave = 16 * KT;
-    static constexpr int kKeysPerSub = kImpWaves * kKeysPerWave;
-    static constexpr int kKeysPerBlock = kKeysPerSub * kImpSubs;
+template <int EB, int RT> struct Imp {                          // RT: 32-row tiles of the window's rows
+    static constexpr int RS = RT;                              // waves that share the rows, a tile each
+    static constexpr int NW = EB == 2 ? (RT == 1 ? 2 : RT == 8 ? 8 : 4) : (RT == 1 ? 4 : 8);     // waves of a block
+    static constexpr int KSP = NW / RS;                        // 32-key tiles of a stage, one for each wave of a row tile
+    static constexpr int kThreads = NW * kWave, kRows = 32 * RT;
+    static constexpr int kStageKeys = 32 * KSP, kStageBytes = kStageKeys * kHeadDim * EB;
+    static constexpr int kPerCu = EB == 4 ? 1 : RT == 8 ? 2 : 3;     // blocks on a compute unit
+    static constexpr int kRingBytes = EB == 4 ? 128 * 1024 : RT == 8 ? 72 * 1024 : 48 * 1024;
+    static constexpr int NB = kRingBytes / kStageBytes;        // stages in the ring
+    static constexpr int kLoads = kStageBytes / (NW * kWave * 16);   // load instructions of a wave per stage
+    static constexpr int kWavesPerSimd = (kPerCu * NW + 3) / 4;
+    static_assert(RS * KSP == NW && NB >= 2 && kLoads >= 1 && NB * kLoads < 64, "every wave has its rows, keys and loads");
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ f32x4 mfma_bf16(const uint4& a, const uint4& b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+__device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-// 2^x for x <= 0 (a probability): the bare instruction; results below the normal range flush to zero
+// 2^x: the bare instruction; results below the normal range flush to zero
 __device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// 8 consecutive elements of a row as bf16 fragments.  bf16 storage: one 16-byte load.  fp32 storage: each value
+// the upper halves of two words in one
+__device__ __forceinline__ uint32_t high_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+
+// 8 consecutive elements of a row as bf16 fragments.  bf16 storage: 16 bytes as they are.  fp32 storage: each value
 // is split exactly into three bf16 terms by truncation (8 + 8 + 8 mantissa bits: x = a + b + c), and x*y is evaluated
 // as aa' + ab' + ba' + ac' + bb' + ca' by six MFMAs; the dropped terms are below 2^-23 of the product.
 template <int EB> struct Frag;
 template <> struct Frag<2> {
     uint4 t0;
-    __device__ __forceinline__ void load(const char* row, int elem) { t0 = *reinterpret_cast<const uint4*>(row + elem * 2); }
+    __device__ __forceinline__ void set(const uint4& lo, const uint4&) { t0 = lo; }
 };
 template <> struct Frag<4> {
     uint4 t0, t1, t2;
-    __device__ __forceinline__ void load(const char* row, int elem) {
-        const uint4 lo4 = *reinterpret_cast<const uint4*>(row + elem * 4);
-        const uint4 hi4 = *reinterpret_cast<const uint4*>(row + elem * 4 + 16);
+    __device__ __forceinline__ void set(const uint4& lo4, const uint4& hi4) {
         const uint32_t x[8] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
         uint32_t a[8], b[8], c[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            a[i] = x[i] & 0xffff0000u;
-            const float r1 = __uint_as_float(x[i]) - __uint_as_float(a[i]);          // exact
-            b[i] = __float_as_uint(r1) & 0xffff0000u;
-            const float r2 = r1 - __uint_as_float(b[i]);                             // exact, at most 8 significant bits
-            c[i] = __float_as_uint(r2) & 0xffff0000u;
+            a[i] = x[i];
+            const float r1 = __uint_as_float(x[i]) - __uint_as_float(x[i] & 0xffff0000u);          // exact
+            b[i] = __float_as_uint(r1);
+            c[i] = __float_as_uint(r1 - __uint_as_float(b[i] & 0xffff0000u));                      // exact, at most 8 significant bits
         }
-        t0 = make_uint4((a[0] >> 16) | a[1], (a[2] >> 16) | a[3], (a[4] >> 16) | a[5], (a[6] >> 16) | a[7]);
-        t1 = make_uint4((b[0] >> 16) | b[1], (b[2] >> 16) | b[3], (b[4] >> 16) | b[5], (b[6] >> 16) | b[7]);
-        t2 = make_uint4((c[0] >> 16) | c[1], (c[2] >> 16) | c[3], (c[4] >> 16) | c[5], (c[6] >> 16) | c[7]);
+        t0 = make_uint4(high_halves(a[0], a[1]), high_halves(a[2], a[3]), high_halves(a[4], a[5]), high_halves(a[6], a[7]));
+        t1 = make_uint4(high_halves(b[0], b[1]), high_halves(b[2], b[3]), high_halves(b[4], b[5]), high_halves(b[6], b[7]));
+        t2 = make_uint4(high_halves(c[0], c[1]), high_halves(c[2], c[3]), high_halves(c[4], c[5]), high_halves(c[6], c[7]));
     }
 };
 
 template <int EB>
-__device__ __forceinline__ f32x4 frag_mma(const Frag<EB>& k, const Frag<EB>& q, f32x4 c) {
+__device__ __forceinline__ f32x16 frag_mma(const Frag<EB>& k, const Frag<EB>& q, f32x16 c) {
     if constexpr (EB == 4) {                                  // small terms first
         c = mfma_bf16(k.t2, q.t0, c);
         c = mfma_bf16(k.t1, q.t1, c);
@@ -82,260 +92,383 @@ __device__ __forceinline__ f32x4 frag_mma(const Frag<EB>& k, const Frag<EB>& q, 
     return mfma_bf16(k.t0, q.t0, c);
 }
 
-// Query rows of KV head h -> LDS as fragments' source (rows >= R are zero).  Row pitch padded by 16 bytes.
-// All loads are issued before the first LDS write, on clamped addresses (a predicated load in a loop costs one
-// full memory latency per iteration).
-template <int EB, int ROWS>
-__device__ __forceinline__ void stage_queries(const char* __restrict__ q_head /* [R][D] */, int R, char* sm_q) {
-    constexpr int kRowBytes = kHeadDim * EB, kPitch = kRowBytes + 16, kPieces = kRowBytes / 16;
-    constexpr int kIter = (ROWS * kPieces + kImpThreads - 1) / kImpThreads;
-    uint4 t[kIter];
-#pragma unroll
-    for (int it = 0; it < kIter; ++it) {
-        const int i = threadIdx.x + it * kImpThreads, row = i / kPieces, piece = i % kPieces;
-        t[it] = *reinterpret_cast<const uint4*>(q_head + (int64_t)min(row, R - 1) * kRowBytes + piece * 16);
-    }
-#pragma unroll
-    for (int it = 0; it < kIter; ++it) {
-        const int i = threadIdx.x + it * kImpThreads, row = i / kPieces, piece = i % kPieces;
-        if (i < ROWS * kPieces) *reinterpret_cast<uint4*>(sm_q + row * kPitch + piece * 16) = row < R ? t[it] : make_uint4(0, 0, 0, 0);
-    }
-}
-
-// Key fragments of one sweep of a wave: keys key0 + 16 kt + t16 (clamped to the last valid row: never out of bounds).
+// Query fragments of a wave's row tile: lane (r, g) = (lane % 32, lane / 32), step d holds dims 16d+8g .. +7 of row row0 + r (rows
+// >= R are zero).
 template <int EB>
-__device__ __forceinline__ void load_keys(Frag<EB> (&kf)[Imp<EB>::KT][4], const char* Kh, int32_t key0, int32_t last, int t16, int qd) {
+__device__ __forceinline__ void load_queries(Frag<EB> (&qf)[8], const char* __restrict__ q_head /* [R][D] */, int R, int row0) {
+    const int lane = threadIdx.x & 63, row = row0 + (lane & 31);
+    const char* src = q_head + (int64_t)min(row, R - 1) * (kHeadDim * EB) + 8 * EB * (lane >> 5);
+    const uint32_t live = row < R ? ~0u : 0u;
 #pragma unroll
-    for (int kt = 0; kt < Imp<EB>::KT; ++kt) {
-        const char* row = Kh + (int64_t)min(key0 + 16 * kt + t16, last) * (kHeadDim * EB);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) kf[kt][s].load(row, 32 * s + 8 * qd);
+    for (int d = 0; d < 8; ++d) {
+        uint4 lo = *reinterpret_cast<const uint4*>(src + 16 * EB * d);
+        uint4 hi = EB == 4 ? *reinterpret_cast<const uint4*>(src + 16 * EB * d + 16) : make_uint4(0, 0, 0, 0);
+        lo = make_uint4(lo.x & live, lo.y & live, lo.z & live, lo.w & live);
+        hi = make_uint4(hi.x & live, hi.y & live, hi.z & live, hi.w & live);
+        qf[d].set(lo, hi);
     }
 }
 
-// pass 1.  grid (ceil(T / Imp<EB>::kKeysPerBlock), Hkv, L); part [L][Hkv][chunks][RT*16][2] = (max in log2 units, sum).
+// this lane's key fragment of step d for key row `row` of a stage
+template <int EB>
+__device__ __forceinline__ void stage_frag(Frag<EB>& f, const char* stage, int row, int d, int g) {
+    const char* base = stage + row * (kHeadDim * EB);
+    if constexpr (EB == 2) {
+        const uint4 lo = *reinterpret_cast<const uint4*>(base + 16 * ((2 * d + g) ^ (row & 15)));
+        f.set(lo, lo);
+    } else {
+        f.set(*reinterpret_cast<const uint4*>(base + 16 * ((4 * d + 2 * g) ^ (row & 15))),
+              *reinterpret_cast<const uint4*>(base + 16 * ((4 * d + 2 * g + 1) ^ (row & 15))));
+    }
+}
+
+// The ring of stages of one head's keys base0 .. of a block.  A wave requests its share of a stage's rows (its own tile where it has all
+// rows of the window), each instruction whole rows.  The 16-byte piece p of row r lands at piece p ^ (r % 16), so that fragment reads
+// (two pieces of 32 rows) spread over the banks.
 template <int EB, int RT>
-__global__ __launch_bounds__(kImpThreads) void importance_stats_kernel(const char* __restrict__ q_obs, const char* __restrict__ K_pool,
-                                                                     int32_t T, int32_t N, int32_t G, float* __restrict__ part) {
-    constexpr int kRowBytes = kHeadDim * EB, kPitch = kRowBytes + 16;
-    constexpr int kRows = RT * 16;
-    constexpr int KT = Imp<EB>::KT, NB = Imp<EB>::NB;
+struct KeyRing {
+    using P = Imp<EB, RT>;
+    static constexpr int kRowBytes = kHeadDim * EB, kPieces = kRowBytes / 16, kRows = kWave / kPieces;      // rows per instruction
+    const char* Kh;
+    char* ring;
+    int32_t base0, last;      // keys past `last` are replaced by it: never out of bounds
+    int n, slot, ahead;
+    int row;                  // stage row of this lane's first load, its byte offset in the stage
+    uint32_t off[P::kLoads];
+
+    __device__ __forceinline__ KeyRing(const char* Kh_, char* ring_, int32_t base0_, int32_t last_, int n_)
+        : Kh(Kh_), ring(ring_), base0(base0_), last(last_), n(n_) {
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        row = kRows * P::kLoads * w + lane / kPieces;
+#pragma unroll
+        for (int i = 0; i < P::kLoads; ++i) {
+            const int r = row + kRows * i;
+            off[i] = (uint32_t)(r * kRowBytes + 16 * ((lane % kPieces) ^ (r & 15)));
+        }
+        restart();
+    }
+    __device__ __forceinline__ void restart() {
+        slot = 0;
+        ahead = P::NB - 1;
+        for (int s = 0; s < P::NB - 1 && s < n; ++s) request(s, s);
+    }
+    __device__ __forceinline__ void request(int s, int to) {
+        const int32_t key0 = base0 + s * P::kStageKeys;
+        const char* src = Kh + (int64_t)key0 * kRowBytes;               // wave-uniform
+        char* dst = ring + to * P::kStageBytes + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (P::kLoads * 1024);
+        if (key0 + P::kStageKeys - 1 <= last) {
+#pragma unroll
+            for (int i = 0; i < P::kLoads; ++i) load_lds_stream(src, off[i], dst + 1024 * i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < P::kLoads; ++i) {
+                const int r = row + kRows * i, beyond = max(r - (last - key0), 0);
+                load_lds_stream(src, off[i] - (uint32_t)(beyond * kRowBytes), dst + 1024 * i);
+            }
+        }
+    }
+    // Stage s, in turn: landed, and one more requested into the place of the stage before it.  Where a wave has all rows it reads only
+    // keys that it requested itself and asks for the next before it waits; otherwise the block meets here.
+    __device__ __forceinline__ const char* next(int s) {
+        auto more = [&]() { request(s + P::NB - 1, ahead); };
+        if constexpr (P::RS == 1) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (s + P::NB - 1 < n) { more(); wait_loads<(P::NB - 1) * P::kLoads>(); }
+            else wait_loads<0>();
+        } else {
+            if (s + P::NB - 2 < n) wait_loads<(P::NB - 2) * P::kLoads>();
+            else wait_loads<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (s + P::NB - 1 < n) more();
+        }
+        const char* stage = ring + slot * P::kStageBytes;
+        slot = slot + 1 == P::NB ? 0 : slot + 1;
+        ahead = ahead + 1 == P::NB ? 0 : ahead + 1;
+        return stage;
+    }
+};
+
+// A 32-key tile against a wave's row tile.  KEYS_A: keys as the A operand (element i of a lane: key 8 (i / 4) + 4 g + i % 4, row r), else
+// the queries (that row, key r).
+template <int EB, bool KEYS_A>
+__device__ __forceinline__ void tile_logits(f32x16& acc, const Frag<EB> (&qf)[8], const char* stage, int row, int g) {
+    f32x16 c = {};
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        Frag<EB> kf;
+        stage_frag<EB>(kf, stage, row, d, g);
+        c = KEYS_A ? frag_mma<EB>(kf, qf[d], c) : frag_mma<EB>(qf[d], kf, c);
+    }
+    acc = c;
+}
+__device__ __forceinline__ int tile_pos(int i, int g) { return 8 * (i >> 2) + 4 * g + (i & 3); }
+
+// pass 1.  grid (chunks of kpb keys, Hkv, L); part [L][Hkv][chunks][rows] (reference in log2 units, sum); rowstat
+// [L][Hkv][rows] the logarithm to base 2 of the sum over all keys (+infinity for rows >= R).
+template <int EB, int RT>
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSimd)) void importance_stats_kernel(
+    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb, float2* part,
+    float* __restrict__ rowstat, unsigned int* arrive) {
+    using P = Imp<EB, RT>;
+    constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
-    extern __shared__ __attribute__((aligned(16))) char sm_dyn[];
-    char* sm_q = sm_dyn;                                              // [kRows][kPitch]
-    __shared__ float sm_m[kImpWaves][kRows], sm_l[kImpWaves][kRows];
+    extern __shared__ __attribute__((aligned(16))) char sm_ring[];
+    __shared__ float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
+    __shared__ int sm_last;
 
     const int h = blockIdx.y, chunk = blockIdx.x, nchunks = gridDim.x;
     const int64_t lh = (int64_t)blockIdx.z * gridDim.y + h;              // (layer, KV head)
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, t16 = lane & 15, qd = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, g = lane >> 5;
+    const int rs = w / P::KSP, ks = w % P::KSP;
     const int R = G * N, Tp = T - N;
     const char* Kh = K_pool + lh * T * kRowBytes;
-    const char* q_layer = q_obs + (int64_t)blockIdx.z * gridDim.y * R * kRowBytes;
-    const int32_t wave_key0 = chunk * Imp<EB>::kKeysPerBlock + Imp<EB>::kKeysPerWave * w;
-    Frag<EB> kf[NB][KT][4];
-    if (NB == 2) load_keys<EB>(kf[0], Kh, wave_key0, T - 1, t16, qd);
-    stage_queries<EB, kRows>(q_layer + (int64_t)h * R * kRowBytes, R, sm_q);
+    const int32_t base0 = chunk * kpb, n = (min(kpb, T - base0) + P::kStageKeys - 1) / P::kStageKeys;
+    KeyRing<EB, RT> keys(Kh, sm_ring, base0, T - 1, n);                  // before the queries: both are on their way together
+    Frag<EB> qf[8];
+    load_queries<EB>(qf, q_obs + lh * R * kRowBytes, R, 32 * rs);
     const float scale = kLog2e * rsqrtf((float)kHeadDim);
 
-    // Running statistics are kept per LANE (a lane sees the keys 4qd..4qd+3 of every tile of its row), in raw logit
-    // units for the max: the four lanes of a row meet only once, after the last sweep.
-    float m_run[RT], l_run[RT];
+    // Sums are kept per LANE (a lane sees half of the keys of every tile of its row) relative to a reference in raw logit
+    // units; the two lanes of a row meet once, after the last stage.  While every key of a stage is visible to every row, the
+    // reference stays what it is after the row's first tile: any reference gives the same sum, and a running maximum
+    // would take a third of the instructions.  Should a sum leave the range of a float that way (logits 2^100 apart), the block
+    // starts over with a running maximum, which the stages at the end of the prompt take in any case.
+    float m_run, l_run;
+    auto add_tile = [&](const f32x16& x) {
+        const float ms = m_run * scale;
+        float sum[2] = {0.f, 0.f};
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) { m_run[rt] = -INFINITY; l_run[rt] = 0.f; }
-    __syncthreads();
-
+        for (int i = 0; i < 16; ++i) sum[i & 1] += exp2_neg(x[i] * scale - ms);
+        l_run += sum[0] + sum[1];
+    };
+    auto add_tile_exact = [&](f32x16& x, int32_t key0) {
+        const int32_t limit = min(Tp + (32 * rs + r) % N, T - 1);        // last position visible to this lane's row
+        float mt = m_run;
 #pragma unroll
-    for (int sub = 0; sub < kImpSubs; ++sub) {
-        const int32_t key0 = wave_key0 + sub * Imp<EB>::kKeysPerSub;
-        const int cur = NB == 2 ? (sub & 1) : 0;
-        if (NB == 2) { if (sub + 1 < kImpSubs) load_keys<EB>(kf[cur ^ 1], Kh, key0 + Imp<EB>::kKeysPerSub, T - 1, t16, qd); }
-        else load_keys<EB>(kf[0], Kh, key0, T - 1, t16, qd);
-        if (key0 >= T) continue;                                      // wave-uniform: nothing of this sweep exists
-        const bool open = key0 + Imp<EB>::kKeysPerWave <= Tp;         // wave-uniform: every key visible to every row
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            Frag<EB> qf[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) qf[s].load(sm_q + (16 * rt + t16) * kPitch, 32 * s + 8 * qd);
-            float sv[KT][4];
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < 4; ++s) acc = frag_mma<EB>(kf[cur][kt][s], qf[s], acc);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sv[kt][j] = acc[j];
-            }
-            if (!open) {                                              // the sweep touches the window or the end of the prompt
-                const int32_t limit = min(Tp + (16 * rt + t16) % N, T - 1);   // last position visible to this lane's row
-#pragma unroll
-                for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (key0 + 16 * kt + 4 * qd + j > limit) sv[kt][j] = -INFINITY;
-            }
-            float mt = m_run[rt];
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) mt = fmaxf(mt, sv[kt][j]);
-            if (open || mt > -INFINITY) {                             // per-lane code only: divergence is harmless
-                const float ms = mt * scale;
-                float sum = 0.f;
-#pragma unroll
-                for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sum += exp2_neg(sv[kt][j] * scale - ms);     // exp2(-inf) = 0
-                l_run[rt] = l_run[rt] * exp2_neg(m_run[rt] * scale - ms) + sum;
-                m_run[rt] = mt;
-            }
+        for (int i = 0; i < 16; ++i) {
+            if (key0 + tile_pos(i, g) > limit) x[i] = -INFINITY;
+            mt = fmaxf(mt, x[i]);
         }
-    }
-    // the four lanes of a row (qd = 0..3), then the block's waves
+        const float ms = mt > -INFINITY ? mt * scale : 0.f;              // (nothing visible yet: every term is exp2(-inf) = 0)
+        float sum = 0.f;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        float m = m_run[rt];
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        float l = m_run[rt] > -INFINITY ? l_run[rt] * exp2_neg((m_run[rt] - m) * scale) : 0.f;
-        l += __shfl_xor(l, 16);
+        for (int i = 0; i < 16; ++i) sum += exp2_neg(x[i] * scale - ms);
+        l_run = l_run * exp2_neg(m_run * scale - ms) + sum;
+        m_run = mt;
+    };
+    const int row0 = 32 * ks + r;                                        // this lane's key row in a stage
+    int n_open = min(max((Tp - base0) / P::kStageKeys, 0), n);           // stages whose keys are all visible to all rows
+    for (;;) {
+        m_run = -INFINITY;
+        l_run = 0.f;
+        if (n_open > 0) {
+            // the sums of a tile are taken while the matrix cores work on the next one
+            f32x16 acc[2];
+            tile_logits<EB, true>(acc[0], qf, keys.next(0), row0, g);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m_run = fmaxf(m_run, acc[0][i]);
+            for (int s = 1; s < n_open; s += 2) {
+                tile_logits<EB, true>(acc[1], qf, keys.next(s), row0, g);
+                add_tile(acc[0]);
+                if (s + 1 < n_open) {
+                    tile_logits<EB, true>(acc[0], qf, keys.next(s + 1), row0, g);
+                    add_tile(acc[1]);
+                }
+            }
+            if (n_open & 1) add_tile(acc[0]);
+            else add_tile(acc[1]);
+        }
+#pragma unroll 1
+        for (int s = n_open; s < n; ++s) {
+            f32x16 x;
+            tile_logits<EB, true>(x, qf, keys.next(s), row0, g);
+            add_tile_exact(x, base0 + s * P::kStageKeys + 32 * ks);
+        }
+        if (n_open == 0 || !__syncthreads_or(!(l_run < 1e30f))) break;
+        n_open = 0;
+        keys.restart();
+    }
+    // the two lanes of a row, then the block's waves
+    {
+        const float m = fmaxf(m_run, __shfl_xor(m_run, 32));
+        float l = m_run > -INFINITY ? l_run * exp2f((m_run - m) * scale) : 0.f;
         l += __shfl_xor(l, 32);
-        if (qd == 0) { sm_m[w][16 * rt + t16] = m * scale; sm_l[w][16 * rt + t16] = l; }
+        if (g == 0) { sm_m[ks][32 * rs + r] = m * scale; sm_l[ks][32 * rs + r] = l; }
     }
     __syncthreads();
-    for (int row = tid; row < kRows; row += kImpThreads) {
+    if (tid < kRows) {
         float m = -INFINITY;
 #pragma unroll
-        for (int ww = 0; ww < kImpWaves; ++ww) m = fmaxf(m, sm_m[ww][row]);
+        for (int k = 0; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][tid]);
         float l = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < kImpWaves; ++ww)
-            if (sm_m[ww][row] > -INFINITY) l += sm_l[ww][row] * exp2_neg(sm_m[ww][row] - m);
-        float* dst = part + ((lh * nchunks + chunk) * kRows + row) * 2;
-        dst[0] = m;
-        dst[1] = l;
+        for (int k = 0; k < P::KSP; ++k)
+            if (sm_m[k][tid] > -INFINITY) l += sm_l[k][tid] * exp2f(sm_m[k][tid] - m);
+        if (l > 0.f) {                                                   // 1 <= l < 2, whatever the reference was
+            const int e = ilogbf(l);
+            l = ldexpf(l, -e);
+            m += (float)e;
+        }
+        st_agent64(part + (lh * nchunks + chunk) * kRows + tid, m, l);
     }
-}
-
-// Combines the per-chunk partials: rowstat [L * Hkv][rows][2] = (max, 1 / sum).  One wave per row, the chunks
-// spread over its lanes.  grid (ceil(L * Hkv * rows / 4)); `Hkv` below counts (layer, head) pairs.
-__global__ __launch_bounds__(kImpThreads) void importance_combine_kernel(const float* __restrict__ part, int32_t nchunks, int32_t rows,
-                                                                       int32_t Hkv, float* __restrict__ rowstat) {
-    const int lane = threadIdx.x & 63;
-    const int item = blockIdx.x * kImpWaves + (threadIdx.x >> 6);     // (head, row)
-    if (item >= Hkv * rows) return;
-    const int h = item / rows, row = item % rows;
+    // ---- the last block of the (layer, head): combined statistics ------------------------------------------------
+    block_sync_after_stores();
+    if (tid == 0) sm_last = __hip_atomic_fetch_add(&arrive[lh], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(nchunks - 1);
+    __syncthreads();
+    if (!sm_last) return;
+    constexpr int kGroups = P::kThreads / kRows;                         // chunks grp, grp + kGroups, ... by thread (grp, row)
+    const int row = tid % kRows, grp = tid / kRows;
     float M = -INFINITY, L = 0.f;
-    for (int c = lane; c < nchunks; c += kWave) {
-        const float2 p = *reinterpret_cast<const float2*>(part + (((int64_t)h * nchunks + c) * rows + row) * 2);
-        if (p.x > -INFINITY) {
-            const float nm = fmaxf(M, p.x);
-            L = L * exp2_neg(M - nm) + p.y * exp2_neg(p.x - nm);
-            M = nm;
+    constexpr int kU = 8;                                                // loads in flight
+    for (int c = grp; c < nchunks; c += kU * kGroups) {
+        unsigned long long v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = ld_agent64(&part[(lh * nchunks + min(c + u * kGroups, nchunks - 1)) * kRows + row].x);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const float pm = c + u * kGroups < nchunks ? lo_f(v[u]) : -INFINITY;
+            if (pm > -INFINITY) {
+                const float nm = fmaxf(M, pm);
+                L = L * exp2_neg(M - nm) + hi_f(v[u]) * exp2_neg(pm - nm);
+                M = nm;
+            }
         }
     }
-    float Mw = M;
+    float* sm_g = reinterpret_cast<float*>(sm_ring);                     // the ring is no longer read
+    sm_g[tid] = M;
+    sm_g[P::kThreads + tid] = L;
+    __syncthreads();
+    if (tid < kRows) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) Mw = fmaxf(Mw, __shfl_xor(Mw, o));
-    float Lw = M > -INFINITY ? L * exp2_neg(M - Mw) : 0.f;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) Lw += __shfl_xor(Lw, o);
-    if (lane == 0) {
-        float* dst = rowstat + ((int64_t)h * rows + row) * 2;
-        dst[0] = Mw;
-        dst[1] = Lw > 0.f ? 1.f / Lw : 0.f;
+        for (int g = 1; g < kGroups; ++g) {
+            const float m2 = sm_g[g * kRows + row], l2 = sm_g[P::kThreads + g * kRows + row];
+            if (m2 > -INFINITY) {
+                const float nm = fmaxf(M, m2);
+                L = L * exp2_neg(M - nm) + l2 * exp2_neg(m2 - nm);
+                M = nm;
+            }
+        }
+        rowstat[lh * kRows + row] = row < R && L > 0.f ? M + log2f(L) : INFINITY;
     }
+    if (tid == 0) __hip_atomic_store(&arrive[lh], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
 }
 
-// pass 2.  grid (ceil(Tp / Imp<EB>::kKeysPerBlock), Hkv, L); alpha_h [L][Hkv][Tp].
+// pass 2.  grid (chunks of kpb of the Tp prefix keys, Hkv, L); alpha_h [L][Hkv][Tp], alpha [L][Tp].  Here the queries are the A operand: a
+// lane gets half of the rows of one key, and the sum over the rows is in-lane but for one exchange.
 template <int EB, int RT>
-__global__ __launch_bounds__(kImpThreads) void importance_colsum_kernel(const char* __restrict__ q_obs, const char* __restrict__ K_pool,
-                                                                      int32_t T, int32_t N, int32_t G,
-                                                                      const float* __restrict__ rowstat, float* __restrict__ alpha_h) {
-    constexpr int kRowBytes = kHeadDim * EB, kPitch = kRowBytes + 16;
-    constexpr int kRows = RT * 16;
-    constexpr int KT = Imp<EB>::KT, NB = Imp<EB>::NB;
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSimd)) void importance_colsum_kernel(
+    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb,
+    const float* __restrict__ rowstat, float* alpha_h, float* __restrict__ alpha, unsigned int* arrive) {
+    using P = Imp<EB, RT>;
+    constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
-    extern __shared__ __attribute__((aligned(16))) char sm_dyn[];
-    char* sm_q = sm_dyn;
-    __shared__ float2 sm_stat[kRows];
+    extern __shared__ __attribute__((aligned(16))) char sm_ring[];
+    __shared__ float sm_col[2][P::RS][P::kStageKeys];
+    __shared__ int sm_last;
 
-    const int h = blockIdx.y;
-    const int64_t lh = (int64_t)blockIdx.z * gridDim.y + h;              // (layer, KV head)
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, t16 = lane & 15, qd = lane >> 4;
+    const int h = blockIdx.y, Hkv = gridDim.y;
+    const int64_t lh = (int64_t)blockIdx.z * Hkv + h;                    // (layer, KV head)
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, g = lane >> 5;
+    const int rs = w / P::KSP, ks = w % P::KSP;
     const int R = G * N, Tp = T - N;
     const char* Kh = K_pool + lh * T * kRowBytes;
-    const char* q_layer = q_obs + (int64_t)blockIdx.z * gridDim.y * R * kRowBytes;
-    const int32_t wave_key0 = blockIdx.x * Imp<EB>::kKeysPerBlock + Imp<EB>::kKeysPerWave * w;
-    Frag<EB> kf[NB][KT][4];
-    if (NB == 2) load_keys<EB>(kf[0], Kh, wave_key0, Tp - 1, t16, qd);
-    stage_queries<EB, kRows>(q_layer + (int64_t)h * R * kRowBytes, R, sm_q);
-    for (int row = tid; row < kRows; row += kImpThreads)       // rows >= R: 1 / sum = 0, so they add nothing
-        sm_stat[row] = row < R ? *reinterpret_cast<const float2*>(rowstat + (lh * kRows + row) * 2) : make_float2(0.f, 0.f);
+    const int32_t base0 = blockIdx.x * kpb, cnt = min(kpb, Tp - base0), n = (cnt + P::kStageKeys - 1) / P::kStageKeys;
+    KeyRing<EB, RT> keys(Kh, sm_ring, base0, Tp - 1, n);
+    Frag<EB> qf[8];
+    load_queries<EB>(qf, q_obs + lh * R * kRowBytes, R, 32 * rs);
+    float c[16];                                                         // this lane's rows of the tile
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[i] = rowstat[lh * kRows + 32 * rs + tile_pos(i, g)];
     const float scale = kLog2e * rsqrtf((float)kHeadDim);
-    __syncthreads();
-
+    const int row0 = 32 * ks + r;                                        // this lane's key in a stage
+    float* dst = alpha_h + lh * Tp + base0;
+    // sums over the wave's rows of its tile of stage s; with the rows on several waves they meet in LDS, and `put` adds and stores them
+    // a barrier later
+    auto sum_tile = [&](const f32x16& x, int s) {
+        float p[2] = {0.f, 0.f};
 #pragma unroll
-    for (int sub = 0; sub < kImpSubs; ++sub) {
-        const int32_t key0 = wave_key0 + sub * Imp<EB>::kKeysPerSub;
-        const int cur = NB == 2 ? (sub & 1) : 0;
-        if (NB == 2) { if (sub + 1 < kImpSubs) load_keys<EB>(kf[cur ^ 1], Kh, key0 + Imp<EB>::kKeysPerSub, Tp - 1, t16, qd); }
-        else load_keys<EB>(kf[0], Kh, key0, Tp - 1, t16, qd);
-        if (key0 >= Tp) continue;                                     // wave-uniform
-        float ps[KT][4];
+        for (int i = 0; i < 16; ++i) p[i & 1] += exp2_neg(x[i] * scale - c[i]);      // prefix keys: at most 1
+        const float v = sum_halves(p[0] + p[1]);
+        if constexpr (P::RS == 1) {
+            if (g == 0 && s * P::kStageKeys + row0 < cnt) st_agent(dst + s * P::kStageKeys + row0, v);
+        } else {
+            if (g == 0) sm_col[s & 1][rs][row0] = v;
+        }
+    };
+    auto put = [&](int s) {
+        if constexpr (P::RS > 1) {
+            if (tid < P::kStageKeys) {
+                float v = sm_col[s & 1][0][tid];
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) ps[kt][j] = 0.f;
-#pragma unroll 2
-        for (int rt = 0; rt < RT; ++rt) {
-            Frag<EB> qf[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) qf[s].load(sm_q + (16 * rt + t16) * kPitch, 32 * s + 8 * qd);
-            const float2 st = sm_stat[16 * rt + t16];
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < 4; ++s) acc = frag_mma<EB>(kf[cur][kt][s], qf[s], acc);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) ps[kt][j] += exp2_neg(acc[j] * scale - st.x) * st.y;   // prefix keys: s <= row max
+                for (int k = 1; k < P::RS; ++k) v += sm_col[s & 1][k][tid];
+                if (s * P::kStageKeys + tid < cnt) st_agent(dst + s * P::kStageKeys + tid, v);
             }
         }
-        // sum over the 16 rows of the tile layout (the lanes of a DPP row); lane t16 == 0 stores its four keys
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float v = ps[kt][j];
-                v = dpp_add<0xB1>(v);
-                v = dpp_add<0x4E>(v);
-                v = dpp_add<0x124>(v);
-                v = dpp_add<0x128>(v);
-                const int32_t key = key0 + 16 * kt + 4 * qd + j;
-                if (t16 == 0 && key < Tp) alpha_h[lh * Tp + key] = v;
-            }
+    };
+
+    // the sums of a tile are taken while the matrix cores work on the next one
+    f32x16 acc[2];
+    tile_logits<EB, false>(acc[0], qf, keys.next(0), row0, g);
+    for (int s = 1; s < n; s += 2) {
+        const char* stage = keys.next(s);
+        if (s > 1) put(s - 2);
+        tile_logits<EB, false>(acc[1], qf, stage, row0, g);
+        sum_tile(acc[0], s - 1);
+        if (s + 1 < n) {
+            stage = keys.next(s + 1);
+            put(s - 1);
+            tile_logits<EB, false>(acc[0], qf, stage, row0, g);
+            sum_tile(acc[1], s);
+        }
     }
+    if (n & 1) sum_tile(acc[0], n - 1);
+    else sum_tile(acc[1], n - 1);
+    __syncthreads();
+    if (n > 1) put(n - 2);
+    put(n - 1);
+    // ---- the last of the heads' blocks for these keys: their sum in ascending order ---------------------------------
+    block_sync_after_stores();
+    unsigned int* mine = arrive + (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+    if (tid == 0) sm_last = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(Hkv - 1);
+    __syncthreads();
+    if (!sm_last) return;
+    const float* src = alpha_h + (int64_t)blockIdx.z * Hkv * Tp + base0;
+    for (int i = tid; i < cnt; i += P::kThreads) {
+        float v = 0.f;
+        for (int hh = 0; hh < Hkv; hh += 8) {
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = ld_agent(src + (int64_t)min(hh + u, Hkv - 1) * Tp + i);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (hh + u < Hkv) v += x[u];
+        }
+        alpha[(int64_t)blockIdx.z * Tp + base0 + i] = v;
+    }
+    if (tid == 0) __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);            // for the next call
 }
 
-// alpha[l][i] = sum over the KV heads, in ascending order, of alpha_h[l][h][i].  grid (ceil(Tp / 256), L).
-__global__ __launch_bounds__(kImpThreads) void importance_sum_heads_kernel(const float* __restrict__ alpha_h, int32_t Tp, int32_t Hkv,
-                                                                         float* __restrict__ alpha) {
-    const int32_t i = blockIdx.x * kImpThreads + threadIdx.x;
-    const int64_t l = blockIdx.y;
-    if (i >= Tp) return;
-    float v = 0.f;
-    for (int h = 0; h < Hkv; ++h) v += alpha_h[(l * Hkv + h) * Tp + i];
-    alpha[l * Tp + i] = v;
+// Keys per block, in units of 128: the number that gives the least rounds x (units + 2), two units being about what a block's
+// start and end take.
+constexpr int kImpUnit = 128;
+static int importance_keys_per_block(const Ctx* c, int32_t T) {
+    const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, resident = (int64_t)c->n_cu * (c->d.kv_dtype == SKV_BF16 ? 3 : 1);
+    const int64_t units = (T + kImpUnit - 1) / kImpUnit;
+    int64_t best = 0, best_cost = 0;
+    for (int64_t per = 1; per <= 256 && per <= units; ++per) {
+        const int64_t rounds = (heads * ((units + per - 1) / per) + resident - 1) / resident, cost = rounds * (per + 2);
+        if (best == 0 || cost < best_cost) { best = per; best_cost = cost; }
+    }
+    return kImpUnit * (int)best;
 }
 
 template <int EB, int RT>
-static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float* part,
+static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
                                        float* rowstat, float* alpha_h) {
-    const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, rows = RT * 16;
-    const int nchunks = (T + Imp<EB>::kKeysPerBlock - 1) / Imp<EB>::kKeysPerBlock;
-    const size_t lds = (size_t)rows * (kHeadDim * EB + 16);
-    static bool raised = false;                                        // dynamic LDS above 64 KB needs the opt-in once
+    using P = Imp<EB, RT>;
+    const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, Tp = T - N, kpb = importance_keys_per_block(c, T);
+    constexpr size_t lds = P::kRingBytes;
+    static bool raised = false;                                        // LDS above 64 KB needs the opt-in once
     if (!raised) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&importance_stats_kernel<EB, RT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -345,48 +478,48 @@ static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_
         if (e != hipSuccess) return e;
         raised = true;
     }
-    const int Tp = T - N;
-    hipLaunchKernelGGL((importance_stats_kernel<EB, RT>), dim3(nchunks, Hkv, L), dim3(kImpThreads), lds, c->stream, q_obs, K_pool, T, N, G,
-                       part);
-    hipLaunchKernelGGL(importance_combine_kernel, dim3((L * Hkv * rows + kImpWaves - 1) / kImpWaves), dim3(kImpThreads), 0, c->stream,
-                       part, nchunks, rows, L * Hkv, rowstat);
-    hipLaunchKernelGGL((importance_colsum_kernel<EB, RT>), dim3((Tp + Imp<EB>::kKeysPerBlock - 1) / Imp<EB>::kKeysPerBlock, Hkv, L),
-                       dim3(kImpThreads), lds, c->stream, q_obs, K_pool, T, N, G, rowstat, alpha_h);
-    hipLaunchKernelGGL(importance_sum_heads_kernel, dim3((Tp + kImpThreads - 1) / kImpThreads, L), dim3(kImpThreads), 0, c->stream,
-                       alpha_h, Tp, Hkv, alpha);
+    hipLaunchKernelGGL((importance_stats_kernel<EB, RT>), dim3((T + kpb - 1) / kpb, Hkv, L), dim3(P::kThreads), lds, c->stream, q_obs,
+                       K_pool, T, N, G, kpb, part, rowstat, c->imp_arrive);
+    hipLaunchKernelGGL((importance_colsum_kernel<EB, RT>), dim3((Tp + kpb - 1) / kpb, Hkv, L), dim3(P::kThreads), lds, c->stream, q_obs,
+                       K_pool, T, N, G, kpb, rowstat, alpha_h, alpha, c->imp_arrive + (int64_t)L * Hkv);
     return hipGetLastError();
 }
 
 template <int EB>
-static hipError_t launch_importance_eb(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float* part,
+static hipError_t launch_importance_eb(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
                                        float* rowstat, float* alpha_h) {
     const int R = c->G * N;
-    if (R <= 32) return launch_importance_rt<EB, 2>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
-    if (R <= 64) return launch_importance_rt<EB, 4>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
-    if (R <= 128) return launch_importance_rt<EB, 8>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
-    if (R <= 256) return launch_importance_rt<EB, 16>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
+    if (R <= 32) return launch_importance_rt<EB, 1>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
+    if (R <= 64) return launch_importance_rt<EB, 2>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
+    if (R <= 128) return launch_importance_rt<EB, 4>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
+    if (R <= 256) return launch_importance_rt<EB, 8>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
     return hipErrorInvalidValue;
 }
 
-static int importance_rows(int rows) { return (rows <= 32 ? 2 : rows <= 64 ? 4 : rows <= 128 ? 8 : 16) * 16; }
+static int importance_rows(int rows) { return rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 128 ? 128 : 256; }
 
 static int64_t importance_chunks(const Ctx* c, int32_t T) {
-    const int per = c->d.kv_dtype == SKV_BF16 ? Imp<2>::kKeysPerBlock : Imp<4>::kKeysPerBlock;
+    const int per = importance_keys_per_block(c, T);
     return (T + per - 1) / per;
 }
 
-// work = part [L][Hkv][chunks][rows][2] | rowstat [L][Hkv][rows][2] | alpha_h [L][Hkv][Tp], floats
-int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N) {
-    const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
-    return (LH * importance_chunks(c, T) * rows * 2 + LH * rows * 2 + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
+// arrival counters of both passes: one per (layer, head), one per (layer, block of keys), at most max_tokens / 64 of them
+int64_t importance_counters(const skv_desc& d) {
+    return (int64_t)d.n_layers * (d.n_kv_heads + (d.max_tokens + kImpUnit - 1) / kImpUnit);
 }
 
-// Four launches cover all layers: statistics, their combination, column sums per head, the ordered sum over heads.
+// work = part [L][Hkv][chunks][rows][2] | rowstat [L][Hkv][rows] | alpha_h [L][Hkv][Tp], floats
+int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N) {
+    const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
+    return (LH * importance_chunks(c, T) * rows * 2 + LH * rows + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
+}
+
+// Two launches cover all layers: the rows' statistics, and the column sums with them.
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work) {
     const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
-    float* part = (float*)work;
-    float* rowstat = part + LH * importance_chunks(c, T) * rows * 2;
-    float* alpha_h = rowstat + LH * rows * 2;
+    float2* part = (float2*)work;
+    float* rowstat = (float*)(part + LH * importance_chunks(c, T) * rows);
+    float* alpha_h = rowstat + LH * rows;
     return c->d.kv_dtype == SKV_BF16
                ? launch_importance_eb<2>(c, (const char*)q_obs, (const char*)K_pool, T, N, alpha, part, rowstat, alpha_h)
                : launch_importance_eb<4>(c, (const char*)q_obs, (const char*)K_pool, T, N, alpha, part, rowstat, alpha_h);

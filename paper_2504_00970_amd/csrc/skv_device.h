@@ -15,6 +15,12 @@ __device__ __forceinline__ float dpp_add(float x) {
     return x + __int_as_float(moved);
 }
 
+// sum over the lanes l and l ^ 32, in both
+__device__ __forceinline__ float sum_halves(float x) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
 // 16 bytes that this launch reads or writes once (K/V rows, mean keys): the non-temporal forms.  Measured on one-shot reads of
 // a 2.15 GB key pool (a wave requests 4 KB and ends): 6.45 TB/s with plain loads, 7.15 TB/s with these.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -26,6 +32,66 @@ __device__ __forceinline__ void st_stream(void* p, const uint4& v) {
     const u32x4_t t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
 }
+
+// 16 bytes per lane from global memory at base + off straight to LDS at `lds` + 16 * lane (base and lds wave-uniform), non-temporal: one-shot
+// reads of the same pool run at 7.1 TB/s with these, 6.2 with plain loads.  Asynchronous: counted by vmcnt, and only the
+// kernel's own waits (wait_loads) order it against reads of the destination.  Written out because the compiler, where it
+// knows that LDS is written, waits for everything outstanding before the next LDS read.
+__device__ __forceinline__ void load_lds_stream(const char* base, uint32_t off, char* lds) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(off),
+                 "s"(base)
+                 : "memory");
+}
+// waits until at most N of the wave's vector memory instructions are outstanding
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// Stores that other blocks of the same launch read (possibly on another XCD, each with its own L2): device-scope
+// relaxed atomic accesses go through to the level all XCDs share, so no L2 write-back / invalidate is needed around
+// the arrival counters that publish them.
+__device__ __forceinline__ void st_agent(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(int32_t* p, int32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(unsigned int* p, unsigned int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float ld_agent(const float* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int32_t ld_agent(const int32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned int ld_agent(const unsigned int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long ld_agent64(const float* p) {       // two consecutive floats
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent64(float2* p, float x, float y) {                 // two floats in one store
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), ((unsigned long long)__float_as_uint(y) << 32) | __float_as_uint(x),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Barrier behind which another thread of the block publishes what this block has stored (an arrival counter).  The
+// workgroup barrier by itself does not wait for a wave's outstanding global stores (the waves of a block share their CU's
+// cache, so the compiler leaves the store counter alone at workgroup scope): each wave waits for its own first.
+// ASSUMPTION (of the kernels that publish with a counter: skv_attend, the two- and three-launch forms of
+// skv_decode_step): a device-scope relaxed atomic store that has left the store counter (vmcnt == 0) has reached the
+// level all XCDs share, so a device-scope relaxed load issued by any block after it observed the later counter
+// increment returns the stored value.  The language's memory model does not promise this for relaxed accesses to
+// different locations; it is how write-through stores and the store counter behave on this chip, and it is guarded by
+// test_repeated_launches_reproduce_their_results.  The single-launch step does not rely on it: there every word
+// carries its own validity tag (st_tagged).
+__device__ __forceinline__ void block_sync_after_stores() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+__device__ __forceinline__ float lo_f(unsigned long long v) { return __uint_as_float((uint32_t)v); }
+__device__ __forceinline__ float hi_f(unsigned long long v) { return __uint_as_float((uint32_t)(v >> 32)); }
 
 // Order-preserving 32-bit image of a float: larger score <=> larger key.
 __device__ __forceinline__ uint32_t score_key(float f) {

@@ -76,6 +76,7 @@ struct Ctx {
     unsigned int* err_host;      // the same flag in pinned host memory (host address; null: none)
     unsigned int* err_host_dev;  // device address of err_host
     unsigned long long* seg_arrive;  // [1] blocks of the segmentation that are done (high word) and S (low word); zero between calls
+    unsigned int* imp_arrive;    // [importance_counters] arrivals of the importance passes; zero between calls
     unsigned int* n_sent_host;   // S of the last segmentation in pinned host memory (host address; null: none)
     unsigned int* n_sent_host_dev;   // its device address
     int wait_limit;              // polling rounds before a waiting block gives up
@@ -106,6 +107,7 @@ hipError_t launch_semvec(Ctx* c, const void* K_pool, int32_t T, const int32_t* s
 // prefill-side token retention (retain.hip)
 constexpr int kImportanceMaxRows = 256;   // query rows (G * window tokens) per KV head
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N);
+int64_t importance_counters(const skv_desc& d);
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work);
 hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
                          int32_t* n_keep, int32_t* ret_off, int32_t* ret_len);

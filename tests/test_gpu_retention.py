@@ -59,6 +59,21 @@ def test_token_importance_matches_oracle(U, oracle32, dtype, Hq, H, N, T):
         assert np.all(alpha[l] >= 0)
 
 
+@pytest.mark.parametrize("dtype,Hq,N,T", [("bf16", 32, 32, 2000), ("bf16", 64, 32, 1500), ("bf16", 32, 16, 1500), ("bf16", 8, 16, 1500),
+                                          ("f32", 32, 32, 1100)])
+def test_token_importance_with_logits_far_apart(U, oracle32, dtype, Hq, N, T):
+    """Logits further apart than a float's exponent reaches, the first keys the smallest: sums relative to a row's first keys overflow."""
+    _say("importance, logits far apart", dtype, Hq, N, T)
+    wl = gen.CFG3.scaled(n_layers=1, n_q_heads=Hq, n_kv_heads=8, n_tokens=T, dtype=dtype, len_dist=("uniform", 5, 30))
+    lens = gen.sentence_lengths(wl.len_dist, T, seed=3)
+    K = gen.kv_layer(lens, 8, 128, wl.torch_dtype, 3, 0)[0][None].to(U.DEV) * 8
+    K[:, :, :64] *= 0.01
+    q_obs = gen.queries(Hq, N, 128, wl.torch_dtype, seed=4, device=U.DEV).view(1, Hq, N, 128) * 8
+    alpha = _gpu_importance(U, U.make_ctx(wl, T, len(lens), 16), q_obs, K, T, N).cpu().numpy()
+    ref = oracle32.token_importance(U.np_of(q_obs[0]), U.np_of(K[0]))
+    assert np.all(np.abs(alpha[0] - ref) <= 1e-3 * ref + 1e-6 * ref.max())     # exponents of several hundred carry fewer fraction bits
+
+
 FULL_IMP_CASES = [("bf16", 32, 8, 32, 32768), ("f32", 32, 8, 32, 32768), ("bf16", 8, 2, 32, 40100), ("f32", 4, 1, 32, 70001)]
 
 
