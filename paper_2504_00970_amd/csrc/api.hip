@@ -499,7 +499,7 @@ static int decode_step_launch(Ctx& c, int32_t layer, int32_t B, const void* q_sc
     }
     e = skv::launch_score(&c, q_score, sv, v, c.f_score);
     if (e != hipSuccess) return hip_status(e);
-    const bool can_stream = c.d.kv_dtype == SKV_BF16 && T_total < (1 << 24);
+    const bool can_stream = skv::can_stream(&c, T_total);
     const int wide_blocks = pairs * ((c.budget_cap + skv::kAttChunkWide - 1) / skv::kAttChunkWide);
     if (can_stream ? wide_blocks > c.n_cu : pairs >= skv::kWideChunkMinHeads) {
         if (can_stream)

@@ -898,44 +898,20 @@ hipError_t launch_gather(Ctx* c, const void* K_layer, const void* V_layer, int32
 }
 
 // ------------------------------------------------------------------------------------------------
-// Attention (Eq. 3), split-K flash decoding.  A 1024-thread block (split, sequence*KV head) handles
-// kAttChunk = 64 consecutive retrieved tokens for the G query heads of its KV head.
-//   FUSED == false: rows come from K_sel/V_sel and n_tok from memory (skv_attend).
-//   FUSED == true : the block first runs the selection for its (sequence, head) from the scores
-//                   (redundantly with the other splits: the scores are a few KB in L2, and it saves a
-//                   launch plus a round trip through tok_idx), keeps the pool rows of its own 64 tokens
-//                   in LDS and reads K/V straight from the pool (skv_decode_step).
-// Lane mapping: a wave covers RPW consecutive rows; lane = chunk * RPW + row, chunk being the 16-byte
-// piece of the row.  The wave's loads still cover whole rows (coalesced), the P.V sum over a wave's
-// rows is a DPP quad exchange (no LDS), and the q.k sum over chunks is DPP row rotations plus two
-// cross-row shuffles.
-//   1. every K and V chunk is requested up front on clamped addresses (no load waits for a bounds test);
-//   2. logits for the G heads -> LDS;   3. one wave per query head: max, exp2, sum over the 64 logits;
-//   4. P.V in registers, reduced over the wave's rows by DPP and over the 16 waves through LDS;
-//   5. the un-normalised partial (m, l, acc) goes to the workspace with write-through stores; the last
+// Attention (Eq. 3), split-K flash decoding.  A 1024-thread block (split, sequence * KV head) handles CHUNK consecutive retrieved
+// tokens for the G query heads of its KV head, a wave for every 16 of them (Tile, below).
+//   kDirect   : rows come from K_sel/V_sel and n_tok from memory (skv_attend).
+//   kIndirect : rows of the pool through tok_idx, n_tok from memory.
+//   kFused, kStep : the block first runs the selection for its (sequence, head) from the scores (redundantly with the other splits: the
+//               scores are a few KB in L2, and it saves a launch plus a round trip through tok_idx) and reads
+//               K/V straight from the pool (skv_decode_step).
+//   1. every K and V piece is requested up front on clamped addresses (no load waits for a bounds test);
+//   2. per wave: logits, max, weights, P V;   3. one barrier, then the block's sums relative to its common max;
+//   4. the un-normalised partial (m, l, acc) goes to the workspace with write-through stores; the last
 //      block to arrive for the (sequence, KV head) -- a device-scope counter, no spinning -- merges the
-//      partials with one round of independent loads and an online-softmax merge.
+//      partials with one round of independent loads and an online-softmax merge (kStep: see there).  A split that is
+//      the only one writes the result.
 // ------------------------------------------------------------------------------------------------
-
-// Split-K partials travel between blocks inside one kernel through st_agent / ld_agent64 (see above).
-
-// sum over the RPW rows of a wave (lane bits below log2 RPW); every lane gets the total
-template <int RPW>
-__device__ __forceinline__ float sum_rows(float x) {
-    x = dpp_add<0xB1>(x);
-    if (RPW == 4) x = dpp_add<0x4E>(x);
-    return x;
-}
-// sum over the LPR chunks of a row (the remaining lane bits); every lane gets the total
-template <int RPW>
-__device__ __forceinline__ float sum_chunks(float x) {
-    if (RPW == 2) x = dpp_add<0x4E>(x);
-    x = dpp_add<0x124>(x);
-    x = dpp_add<0x128>(x);
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
-    return x;
-}
 
 // ds_read_b64_tr_b16 (gfx950): within each group of 16 lanes, lane i receives element i % 4 of the 8-byte pieces that
 // lanes i / 4, i / 4 + 4, i / 4 + 8 and i / 4 + 12 of the group point at, in that order.  With lane s of the group
@@ -947,12 +923,95 @@ __device__ __forceinline__ bf16x4_t lds_read_tr16(const char* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((bf16x4_t __attribute__((address_space(3)))*)(p));
 }
 
-// q.K^T step on 32 dims: v_mfma_f32_16x16x32_bf16 with a 16-byte row chunk (8 consecutive dims) per lane on both sides
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f32x4_t mfma_qk32(const uint4& k, const uint4& q, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k), __builtin_bit_cast(bf16x8_t, q), c, 0, 0, 0);
+// 2^x for x <= 0 (a weight): the bare instruction; results below the normal range flush to zero
+__device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
+// over the four lanes t16, t16 + 16, t16 + 32, t16 + 48 of a tile column; every lane gets the result
+__device__ __forceinline__ float max_quads(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
+__device__ __forceinline__ float sum_quads(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// A wave's tile of 16 tokens on the matrix cores.  With t16 = lane % 16 and qd = lane / 16:
+//  * S^T = K Q^T: the A fragment is a 16-byte piece (at byte 64 s + 16 qd, s < kPieces) of token t16's key, the B fragment the same dims
+//    of head t16's query (heads >= G are zero).  The order of the dims inside the contraction is free as long as A and B agree,
+//    so a piece loaded from a row is one 32-deep step of v_mfma_f32_16x16x32_bf16, or four 4-deep steps of
+//    v_mfma_f32_16x16x4_f32, one for each of its floats.  The accumulator holds logit(token 4 qd + j, head t16), j = 0..3.
+//  * O = P V: that accumulator layout IS the A fragment layout of P (head t16, tokens 4 qd + j), for bf16 of one
+//    v_mfma_f32_16x16x16_bf16, for fp32 of four 4-deep steps, step j on the tokens 4 qd + j.  The B fragments V[token 4 qd + j][16 dt + t16]
+//    are read from a wave-private LDS copy of the 16 value rows, laid out so that the four token groups of a read fall into
+//    different banks (bf16: 16 bytes between rows; fp32: 64-byte groups exchanged, no gaps, for rows that come by load_lds_stream).
+//  * bf16 weights are rounded to bf16 (nearest even) and the normaliser sums the rounded weights; fp32 ones are used as they are.
+// fp32 through the vector pipe (rows over lanes, sums of the logits over 32 lanes by exchanges) took 3.7 us from the loads to
+// the logits of 128 tokens and 1.7 to the partial result, budget 512, 4 heads; see launch_step for what it takes now.
+template <int EB> struct Tile {
+    static constexpr int kPieces = kHeadDim * EB / 64;                // key pieces of a lane
+    static constexpr int LPR = kHeadDim * EB / 16, RPL = kWave / LPR; // lanes of a value row, value rows of a load
+    static constexpr int kLoads = 16 / RPL;                           // value loads of a lane: rows RPL i + lane / LPR
+    static constexpr int kPitch = kHeadDim * EB + (EB == 2 ? 16 : 0); // bytes of a value row in LDS
+    // place of 16-byte piece `piece` of value row `row` in the tile
+    __device__ static __forceinline__ int place(int row, int piece) { return row * kPitch + 16 * (EB == 2 ? piece : piece ^ (4 * (row >> 2))); }
+
+    // query(s): this lane's piece s of the queries
+    template <typename Query>
+    __device__ static __forceinline__ f32x4_t logits(const uint4 (&k)[kPieces], Query query) {
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (EB == 2) {
+#pragma unroll
+            for (int s = 0; s < kPieces; ++s)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k[s]), __builtin_bit_cast(bf16x8_t, query(s)), acc, 0, 0, 0);
+        } else {
+            f32x4_t acc2 = {0.f, 0.f, 0.f, 0.f};                      // two chains: a step's latency is longer than its issue
+#pragma unroll
+            for (int s = 0; s < kPieces; ++s) {
+                const uint4 q = query(s);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[s].x), __uint_as_float(q.x), acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[s].y), __uint_as_float(q.y), acc2, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[s].z), __uint_as_float(q.z), acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[s].w), __uint_as_float(q.w), acc2, 0, 0, 0);
+            }
+            acc += acc2;
+        }
+        return acc;
+    }
+    // weights as P V takes them; the return value is what the normaliser sums
+    __device__ static __forceinline__ float weight(float& p) {
+        if constexpr (EB == 2) {
+            uint32_t u = __float_as_uint(p);
+            u += 0x7fffu + ((u >> 16) & 1u);
+            p = __uint_as_float(u & 0xffff0000u);
+        }
+        return p;
+    }
+    // o[dt] += P V of the tile at `v` (16 rows of pitch kPitch); element j of o[dt]: head 4 qd + j, dim 16 dt + t16
+    __device__ static __forceinline__ void output(const float (&p)[4], const char* v, int lane, f32x4_t (&o)[kHeadDim / 16]) {
+        const int t16 = lane & 15, qd = lane >> 4;
+        if constexpr (EB == 2) {
+            const bf16x4_t pa = {(short)(__float_as_uint(p[0]) >> 16), (short)(__float_as_uint(p[1]) >> 16), (short)(__float_as_uint(p[2]) >> 16),
+                                 (short)(__float_as_uint(p[3]) >> 16)};
+            // B fragments by the LDS transpose read: this lane points at dims 4 (t16 % 4) .. + 3 of value row 4 qd + t16 / 4
+            const char* vtr = v + (4 * qd + (t16 >> 2)) * kPitch + 8 * (t16 & 3);
+#pragma unroll
+            for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, lds_read_tr16(vtr + 32 * dt), o[dt], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int dt = 0; dt < kHeadDim / 16; ++dt) {
+                const char* col = v + 4 * qd * kPitch + 64 * (dt ^ qd) + 4 * t16;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[j], *reinterpret_cast<const float*>(col + j * kPitch), o[dt], 0, 0, 0);
+            }
+        }
+    }
+};
 
 // Tag of a launch of the single-launch step for one pair: the pair's epoch after this launch (1 .. 2^26 - 1, never 0, so
 // zero-filled memory never looks valid) above the pair's number.  A word of memory carries a pair's current tag only if
@@ -962,6 +1021,15 @@ __device__ __forceinline__ uint32_t step_tag(uint32_t epoch, int pair) {
     uint32_t e = (epoch + 1u) & ((1u << (32 - kStepPairBits)) - 1u);
     if (e == 0u) e = 1u;
     return (e << kStepPairBits) | (uint32_t)pair;
+}
+
+constexpr int max_of(int a, int b) { return a > b ? a : b; }
+
+// orders a wave's LDS accesses before it against those after it (other lanes of the wave wrote or will write the same words)
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 struct AttArgs {
@@ -1027,45 +1095,37 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
 // flight), 256 for batches (fewer partials and arrivals per head, more loads in flight per block).
 template <int EB, int G, int MODE, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
-    using R = Row<EB>;
-    constexpr int kRowsPerIter = kBlockWaves * R::RPW;        // 64 (bf16) or 32 (fp32)
-    constexpr int kIter = CHUNK / kRowsPerIter;
+    using X = Tile<EB>;
     constexpr int kRowBytes = kHeadDim * EB;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-    constexpr int GH = G > 4 ? 4 : G, NH = G / GH;           // heads are processed GH at a time (register budget)
-    constexpr int kTPL = CHUNK / kWave;                       // logits per lane in the softmax
-    constexpr bool kMfma = (EB == 2);                         // bf16 runs on the matrix cores
-    constexpr int kTiles = CHUNK / 16;                        // 16-token MFMA tiles, one per wave
-    constexpr int kRedWaves = kMfma ? kTiles : kBlockWaves;   // waves that leave partial sums in sm_red
-    static_assert(kTiles <= kBlockWaves, "one tile per wave");
+    constexpr int kTiles = CHUNK / 16;                        // 16-token tiles, one per wave
+    static_assert(kTiles <= kBlockWaves && CHUNK % kWave == 0, "one tile per wave");
     constexpr int kOut = G * kHeadDim;                        // outputs of the block
     constexpr int kCol2 = kOut / 2;                           // float pairs over the G heads
     constexpr int kGroups = kBlockThreads / kCol2;            // split groups of the merge: 16, 8, 4, 2 for G = 1, 2, 4, 8
-    static_assert(kIter >= 1 && kGroups >= 1 && CHUNK % kWave == 0, "block shape");
 
-    __shared__ float sm_logit[G][CHUNK];
-    // Wave partial sums of P.V (wave ww, head g, dim d at sm_red_flat[ww * kRedStride + g * 128 + d], on the MFMA path at
-    // [ww * kRedStride + d * G + g]); later the
-    // merge scratch.  On the MFMA path each wave's partial sums reuse its own value tile.
-    constexpr int kVPitch = 2 * kHeadDim + 16;                // bytes per value row in LDS; +16 spreads row groups over banks
-    constexpr int kRedStride = kMfma ? 16 * kVPitch / 4 : G * kHeadDim;
-    constexpr int kRedFloats = (kRedWaves * kRedStride > 4 * kBlockThreads) ? kRedWaves * kRedStride : 4 * kBlockThreads;
-    static_assert(!kMfma || G * kHeadDim <= kRedStride, "a wave's partial sums fit in its value tile");
-    __shared__ __attribute__((aligned(16))) float sm_red_flat[kRedFloats];
+    // One region of LDS, used in turn by the selection (SelectShared, and the pair's scores on their way to the owning threads), by the
+    // waves' value tiles and, in each wave's own tile, its partial sums (dim d, head g at [d * G + g]), and by the merge.
+    constexpr bool kSel = MODE == kFused || MODE == kStep;    // the block runs the selection itself
+    constexpr int kTileBytes = 16 * X::kPitch;
+    static_assert(G * kHeadDim * 4 <= kTileBytes, "a wave's partial sums fit in its value tile");
+    constexpr int kSelBytes = kSel ? (int)((sizeof(SelectShared) + 15) / 16 * 16) : 0;
+    constexpr int kKeyBytes = MODE == kStep ? kSelKreg * kBlockThreads * 4 : 0;
+    constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), MODE == kStep ? 0 : 16 * kBlockThreads);
+    __shared__ __attribute__((aligned(16))) char sm[kShBytes];
+    __shared__ __attribute__((aligned(16))) float sm_wmax[16][kTiles], sm_wsum[16][kTiles];     // per head and wave
     __shared__ int sm_last;
     __shared__ int32_t sm_row[CHUNK];
-    // kStep: the pair's scores on their way to the owning threads; later the merging block's scratch
-    __shared__ uint32_t sm_keys[MODE == kStep ? kSelKreg * kBlockThreads : 1];
+    __shared__ float sm_merge[MODE == kStep ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
 
     // kStep: a one-dimensional grid, pair fastest, so that the hardware's round-robin of consecutive blocks over the XCDs
     // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
-    constexpr bool kSel = MODE == kFused || MODE == kStep;        // the block runs the selection itself
     const int n_pairs = a.v.B * a.Hkv;
     const int bh = MODE == kStep ? (int)(blockIdx.x % (unsigned)n_pairs) : (int)blockIdx.y;
     const int split = MODE == kStep ? (int)(blockIdx.x / (unsigned)n_pairs) : (int)blockIdx.x;
     const int b = bh / a.Hkv, h = bh % a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r = lane % R::RPW, cc = lane / R::RPW;
+    const int t16 = lane & 15, qd = lane >> 4;
     const int Hq = a.Hkv * G;
     const int64_t qhead0 = (int64_t)b * Hq + (int64_t)h * G;      // first query head of the group
     demand_args(a);
@@ -1082,22 +1142,19 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     const int slot = split * (CHUNK / kWave);                     // partial slot (slots are counted in 64-token units)
     SKV_T(0);
 
-    // bf16: the query fragments of the tile waves are requested first of all; they are in registers long before the
-    // key rows arrive, so the logits wait for the keys only (lane (t16, qd): head t16, dims 32 s + 8 qd .. + 7)
-    uint4 qB[kMfma ? 4 : 1];
-    if constexpr (kMfma) {
-        if (w < kTiles) {
-            const int t16 = lane & 15, qd = lane >> 4;
+    // The query fragments of the tile waves are requested first of all; they are in registers long before the
+    // key rows arrive, so the logits wait for the keys only (lane (t16, qd): head t16)
+    uint4 qB[X::kPieces];
+    if (w < kTiles) {
 #pragma unroll
-            for (int s2 = 0; s2 < 4; ++s2)
-                qB[s2] = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + min(t16, G - 1)) * kHeadDim) * EB + 64 * s2 + 16 * qd);
-        }
+        for (int s2 = 0; s2 < X::kPieces; ++s2)
+            qB[s2] = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + min(t16, G - 1)) * kHeadDim) * EB + 64 * s2 + 16 * qd);
     }
 
     int32_t n;                                                    // retrieved tokens of this (sequence, head)
     bool step_ok = true;                                          // kStep: every wait of this block ended in time
     if constexpr (kSel) {
-        __shared__ SelectShared sel_sh;
+        SelectShared& sel_sh = *reinterpret_cast<SelectShared*>(sm);
         const int32_t budget = min(sq.budget, a.budget_cap);
         if constexpr (MODE == kStep) {
             // ---- 0. scores of this block's share of the pair's buckets, published to the pair's other blocks ---------
@@ -1135,7 +1192,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         if (tid < CHUNK) sm_row[tid] = -1;
         int32_t nsel, ntok;
         // Each selected bucket that reaches into this block's positions marks, in every 64-position piece it touches,
-        // where it starts there and which pool row that is; one wave per piece then fills the positions in between.
+        // where it starts there and which pool row that is; the waves then fill the positions in between.
         auto mark = [&](int32_t, int32_t o, int32_t ln, int32_t, int32_t tok_pos) {
 #pragma unroll
             for (int pc = 0; pc < CHUNK / kWave; ++pc) {
@@ -1148,6 +1205,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         const int32_t* off = a.sent_off + sq.sent_base + (a.v.cu_sent ? b : 0);
         if constexpr (MODE == kStep) {                            // the scores are being written by the pair's blocks
             const float* tsc = reinterpret_cast<const float*>(a.step_score + (int64_t)bh * a.score_stride);
+            uint32_t* sm_keys = reinterpret_cast<uint32_t*>(sm + kSelBytes);
             if (sq.n_sent <= 2 * kBlockThreads)
                 select_block<2, false, true>(tsc, len, off, sq.n_sent, budget, sel_sh, mark, &nsel, &ntok, tag, a.wait_limit, &step_ok, sm_keys);
             else
@@ -1159,18 +1217,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         }
         n = ntok;
         if (split == 0 && tid == 0 && a.n_tok_out) a.n_tok_out[bh] = n;
-        __syncthreads();                                          // bucket starts are marked
-        if (w < CHUNK / kWave) {
-            const int32_t v = sm_row[w * kWave + lane];
-            // position of the last bucket start at or before this lane (-1: none): running maximum of lane + 1 over the starts
-            const int32_t hp = (int32_t)wave_scan_max_u32(v >= 0 ? (uint32_t)lane + 1u : 0u) - 1;
-            const int32_t base = __shfl(v, max(hp, 0));
-            const int32_t row = hp >= 0 ? base + (lane - hp) : -1;
-            sm_row[w * kWave + lane] = row;
-            const int32_t pos = j0 + w * kWave + lane;
-            if (a.tok_idx_out && pos < n) a.tok_idx_out[(int64_t)bh * a.idx_stride + pos] = row;
-        }
-        __syncthreads();                                          // sm_row complete
+        __syncthreads();                                          // bucket starts are marked; the selection's LDS is free
     } else {
         n = min(ld_const(a.n_tok, bh), MODE == kDirect ? a.row_stride : a.idx_stride);
     }
@@ -1190,9 +1237,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         if constexpr (MODE == kStep) {
             const int n_cand = min(1 << a.lg_parts, max(G, (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
             if (n_cand <= first) return true;                     // block-uniform: the usual case, the budget is filled
-            // the flag lives in the first word of the space the scores came through (thread 0, the only reader of that
+            // the flag lives in the first word of the merge's scratch (thread 0, the only reader of that
             // word in the merge, is past its reads when it clears it)
-            volatile uint32_t* missing = sm_keys;
+            volatile uint32_t* missing = reinterpret_cast<uint32_t*>(sm_merge);
             if (tid == 0) *missing = 0u;
             __syncthreads();
             if (tid >= first && tid < n_cand) {
@@ -1250,257 +1297,125 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             Vh = a.Vb + ((int64_t)h * a.v.T_total + sq.tok_base) * kRowBytes;
         }
         const float scale = kLog2e * rsqrtf((float)kHeadDim);
-        if constexpr (kMfma) {
-            // ---- bf16: q.K^T (v_mfma_f32_16x16x32_bf16) and P.V (v_mfma_f32_16x16x16_bf16) on the matrix cores ----
-            // Wave w owns the 16 tokens [16w, 16w+16) of the chunk.  With t = lane % 16 and qd = lane / 16:
-            //  * S^T = K Q^T: A fragment = 8 consecutive dims of token t's key, B fragment = the same 8 dims of head t's
-            //    query (heads >= G are zero).  The dimension order inside the contraction is free as long as A and B agree,
-            //    so one 16-byte load of a row (dims 32s+8qd .. +7) is one 32-deep MFMA step; four loads cover the row.
-            //    The accumulator holds logit(token 4qd+j, head t), j = 0..3.
-            //  * O = P V: that accumulator layout IS the A-fragment layout (head t, tokens 4qd+j); the B fragment
-            //    V[token 4qd+j][16dt + t] is read from a wave-private LDS copy of the 16 value rows (padded pitch).
-            typedef short bf16x4 __attribute__((ext_vector_type(4)));
-            typedef float f32x4 __attribute__((ext_vector_type(4)));
-            char* sm_v = reinterpret_cast<char*>(sm_red_flat) + (size_t)w * 16 * kVPitch;       // this wave's value tile
-            __shared__ float sm_wmax[kTiles][16], sm_wsum[kTiles][16];
-            const int t16 = lane & 15, qd = lane >> 4;
-            const bool tile = w < kTiles;
-            float sj[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-            bool lv[4] = {false, false, false, false};
-            if (tile) {
-                const int jj = 16 * w + t16;
-                bool liveK = jj < cnt;
-                const int jc = min(jj, cnt - 1);
-                int32_t rowK;
-                if (MODE == kDirect) {
-                    rowK = jc;
+        if (w < kTiles) {
+            char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
+            // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
+            // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
+            const int jj = 16 * w + t16;
+            bool liveK = jj < cnt;
+            int32_t rowK, rowV[X::kLoads];
+            if constexpr (MODE == kDirect) {
+                rowK = min(jj, cnt - 1);
+#pragma unroll
+                for (int i = 0; i < X::kLoads; ++i) rowV[i] = min(16 * w + X::RPL * i + lane / X::LPR, cnt - 1);
+            } else {
+                int32_t x, base = 0;                                  // x: row of the position this lane looked up, the tile's from lane `base` on
+                if constexpr (kSel) {
+                    // the wave fills its tile's 64-position piece in registers: the last bucket start at or before each position
+                    base = 16 * (w & 3);
+                    const int32_t v = sm_row[(w >> 2) * kWave + lane];
+                    const int32_t hp = (int32_t)wave_scan_max_u32(v >= 0 ? (uint32_t)lane + 1u : 0u) - 1;       // -1: none
+                    const int32_t start = __shfl(v, max(hp, 0));
+                    x = hp >= 0 ? start + (lane - hp) : -1;
+                    const int32_t pos = (w >> 2) * kWave + lane;
+                    if ((w & 3) == 0 && a.tok_idx_out && j0 + pos < n) a.tok_idx_out[(int64_t)bh * a.idx_stride + j0 + pos] = x;
                 } else {
-                    const int32_t x = kSel ? sm_row[jc] : a.tok_idx[(int64_t)bh * a.idx_stride + j0 + jc];
-                    liveK = liveK && x >= 0 && x < sq.n_tok_ctx;
-                    rowK = min(max(x, 0), max(sq.n_tok_ctx - 1, 0));
+                    x = a.tok_idx[(int64_t)bh * a.idx_stride + j0 + min(jj, cnt - 1)];
                 }
-                uint4 kA[4], vR[4];
+                const bool in = x >= 0 && x < sq.n_tok_ctx;
+                const unsigned long long ok = __ballot(in) >> base;   // bit t < 16: token t of the tile lies in the sequence
+                liveK = liveK && ((ok >> t16) & 1u);
+                x = min(max(x, 0), max(sq.n_tok_ctx - 1, 0));
+                const int last = base + min(cnt - 1 - 16 * w, 15);    // (negative for a wave past the end: clamped below)
+                rowK = __shfl(x, max(min(base + t16, last), 0));
 #pragma unroll
-                for (int s2 = 0; s2 < 4; ++s2) kA[s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int32_t rowV = __shfl(rowK, 4 * i + qd);     // lane 4i+qd (< 16) holds the row of token 4i+qd
-                    vR[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV * kRowBytes + 16 * t16);
-                }
-                const unsigned long long vm = __ballot(liveK);        // bit t (t < 16): token t of the tile is real
-                SKV_T(5);
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s2 = 0; s2 < 4; ++s2) {
-                    uint4 qq = qB[s2];
-                    if (t16 >= G) qq = make_uint4(0, 0, 0, 0);
-                    acc = mfma_qk32(kA[s2], qq, acc);
-                }
-                float mw = -INFINITY;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    lv[j] = (vm >> (4 * qd + j)) & 1ull;
-                    sj[j] = lv[j] ? acc[j] * scale : -INFINITY;
-                    mw = fmaxf(mw, sj[j]);
-                }
-                mw = fmaxf(mw, __shfl_xor(mw, 16));
-                mw = fmaxf(mw, __shfl_xor(mw, 32));
-                if (qd == 0) sm_wmax[w][t16] = mw;
-                // the tile's value rows go to LDS (rows of masked tokens as zeros)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bool lr = (vm >> (4 * i + qd)) & 1ull;
-                    *reinterpret_cast<uint4*>(sm_v + (4 * i + qd) * kVPitch + 16 * t16) = lr ? vR[i] : make_uint4(0, 0, 0, 0);
-                }
+                for (int i = 0; i < X::kLoads; ++i) rowV[i] = __shfl(x, max(min(base + X::RPL * i + lane / X::LPR, last), 0));
             }
-            __syncthreads();
+            uint4 kA[X::kPieces], vR[X::kLoads];
+#pragma unroll
+            for (int s2 = 0; s2 < X::kPieces; ++s2) kA[s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
+#pragma unroll
+            for (int i = 0; i < X::kLoads; ++i) vR[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
+            const unsigned long long vm = __ballot(liveK);            // bit t (t < 16): token t of the tile is real
+#pragma unroll
+            for (int s2 = 0; s2 < X::kPieces; ++s2)
+                if (t16 >= G) qB[s2] = make_uint4(0, 0, 0, 0);
+            SKV_T(5);
+            const f32x4_t acc = X::logits(kA, [&](int s2) { return qB[s2]; });
+            float p[4], mw = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                p[j] = ((vm >> (4 * qd + j)) & 1ull) ? acc[j] * scale : -INFINITY;
+                mw = fmaxf(mw, p[j]);
+            }
+            mw = max_quads(mw);
+            // the tile's value rows go to LDS (rows of masked tokens as zeros)
+#pragma unroll
+            for (int i = 0; i < X::kLoads; ++i) {
+                const int row = X::RPL * i + lane / X::LPR;
+                *reinterpret_cast<uint4*>(sm_v + X::place(row, lane % X::LPR)) = ((vm >> row) & 1ull) ? vR[i] : make_uint4(0, 0, 0, 0);
+            }
             SKV_T(6);
-            if (tile) {
-                float mb = -INFINITY;
+            float lw = 0.f;
 #pragma unroll
-                for (int ww = 0; ww < kTiles; ++ww) mb = fmaxf(mb, sm_wmax[ww][t16]);
-                unsigned short pb[4];
-                float lw = 0.f;
+            for (int j = 0; j < 4; ++j) {
+                p[j] = mw > -INFINITY ? exp2_neg(p[j] - mw) : 0.f;    // masked: exp2(-inf) = 0
+                lw += X::weight(p[j]);
+            }
+            lw = sum_quads(lw);
+            if (qd == 0) { sm_wmax[t16][w] = mw; sm_wsum[t16][w] = lw; }
+            f32x4_t o[kHeadDim / 16];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float p = (lv[j] && mb > -INFINITY) ? exp2f(sj[j] - mb) : 0.f;
-                    uint32_t u = __float_as_uint(p);
-                    u += 0x7fffu + ((u >> 16) & 1u);                  // round to nearest even bf16
-                    pb[j] = (unsigned short)(u >> 16);
-                    lw += __uint_as_float((uint32_t)pb[j] << 16);     // the normaliser sums the rounded weights
-                }
-                lw += __shfl_xor(lw, 16);
-                lw += __shfl_xor(lw, 32);
-                if (qd == 0) sm_wsum[w][t16] = lw;
-                const bf16x4 pa = {(short)pb[0], (short)pb[1], (short)pb[2], (short)pb[3]};
-                // B fragments by the LDS transpose read: this lane points at dims 4 (t16 % 4) .. + 3 of value row 4 qd + t16 / 4
-                const char* vtr = sm_v + (4 * qd + (t16 >> 2)) * kVPitch + 8 * (t16 & 3);
-                f32x4 o[kHeadDim / 16];
+            for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            wave_lds_sync();                                          // the tile is the wave's own: order only
+            X::output(p, sm_v, lane, o);
+            wave_lds_sync();
+            // the value tile has been consumed: its space takes the wave's partial sums, head fastest (dim d, head g at
+            // red[d * G + g]), so that a lane stores its heads of one dim with a single instruction
+            float* red = reinterpret_cast<float*>(sm_v);
+            if (4 * qd < G) {
 #pragma unroll
                 for (int dt = 0; dt < kHeadDim / 16; ++dt) {
-                    const bf16x4 vb = lds_read_tr16(vtr + 32 * dt);
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, zero, 0, 0, 0);
-                }
-                // the value tile has been consumed: its space takes the wave's partial sums, head fastest (dim d, head g at
-                // red[d * G + g]), so that a lane stores its heads of one dim with a single instruction
-                float* red = sm_red_flat + w * kRedStride;
-                if (4 * qd < G) {
-#pragma unroll
-                    for (int dt = 0; dt < kHeadDim / 16; ++dt) {
-                        float* dst = red + (16 * dt + t16) * G + 4 * qd;
-                        if constexpr (G >= 4) *reinterpret_cast<float4*>(dst) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
-                        else if constexpr (G == 2) *reinterpret_cast<float2*>(dst) = make_float2(o[dt][0], o[dt][1]);
-                        else dst[0] = o[dt][0];
-                    }
-                }
-            }
-            __syncthreads();
-            if (tid < G) {                                            // block max and normaliser of head tid
-                float mb = -INFINITY, lb = 0.f;
-#pragma unroll
-                for (int ww = 0; ww < kTiles; ++ww) { mb = fmaxf(mb, sm_wmax[ww][tid]); lb += sm_wsum[ww][tid]; }
-                if constexpr (MODE == kStep) {
-                    unsigned long long* dst = my_part + tid * kStepPartWords + kHeadDim;
-                    st_tagged(dst, mb, part_tag);
-                    st_tagged(dst + 1, lb, part_tag);
-                } else {
-                    float* dst = a.ml + (((qhead0 + tid) * a.max_splits) + slot) * 2;
-                    st_agent(dst, mb);
-                    st_agent(dst + 1, lb);
-                }
-            }
-        } else {
-            // Rows past the chunk's end (and positions outside the sequence) are clamped to a valid row, loaded
-            // anyway and masked afterwards, so that all loads are in flight together.
-            int32_t rowi[kIter];
-            bool live[kIter];
-#pragma unroll
-            for (int i = 0; i < kIter; ++i) {
-                const int jj = i * kRowsPerIter + w * R::RPW + r;
-                live[i] = jj < cnt;
-                const int jc = min(jj, cnt - 1);
-                if (MODE == kDirect) {
-                    rowi[i] = jc;
-                } else {
-                    const int32_t x = kSel ? sm_row[jc] : a.tok_idx[(int64_t)bh * a.idx_stride + j0 + jc];
-                    live[i] = live[i] && x >= 0 && x < sq.n_tok_ctx;
-                    rowi[i] = min(max(x, 0), max(sq.n_tok_ctx - 1, 0));
-                }
-            }
-            uint4 kraw[kIter], vraw[kIter];
-#pragma unroll
-            for (int i = 0; i < kIter; ++i) {
-                kraw[i] = ld_row<MODE != kDirect>(Kh + (int64_t)rowi[i] * kRowBytes + cc * 16);
-                vraw[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowi[i] * kRowBytes + cc * 16);
-            }
-            SKV_T(5);
-
-            // ---- 2. logits ---------------------------------------------------------------------------------
-#pragma unroll
-            for (int hh = 0; hh < NH; ++hh) {
-                float qf[GH][R::EPL];
-#pragma unroll
-                for (int g = 0; g < GH; ++g) {
-                    const uint4 t = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + hh * GH + g) * kHeadDim) * EB + cc * 16);
-                    R::unpack(t, qf[g]);
-                }
-#pragma unroll
-                for (int i = 0; i < kIter; ++i) {
-                    float kf[R::EPL];
-                    R::unpack(kraw[i], kf);
-#pragma unroll
-                    for (int g = 0; g < GH; ++g) {
-                        float acc = 0.f;
-#pragma unroll
-                        for (int e = 0; e < R::EPL; ++e) acc += qf[g][e] * kf[e];
-                        acc = sum_chunks<R::RPW>(acc);
-                        if (cc == 0) sm_logit[hh * GH + g][i * kRowsPerIter + w * R::RPW + r] = live[i] ? acc * scale : -INFINITY;
-                    }
-                }
-            }
-            __syncthreads();
-            SKV_T(6);
-
-            // ---- 3. softmax over the chunk, one wave per query head --------------------------------------------
-            if (w < G) {
-                const int g = w;
-                float x[kTPL];
-                float m = -INFINITY;
-#pragma unroll
-                for (int t = 0; t < kTPL; ++t) { x[t] = sm_logit[g][t * kWave + lane]; m = fmaxf(m, x[t]); }
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-                float l = 0.f;
-#pragma unroll
-                for (int t = 0; t < kTPL; ++t) {
-                    const float p = (m == -INFINITY) ? 0.f : exp2f(x[t] - m);
-                    sm_logit[g][t * kWave + lane] = p;
-                    l += p;
-                }
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
-                if (lane == 0) {
-                    if constexpr (MODE == kStep) {
-                        unsigned long long* dst = my_part + g * kStepPartWords + kHeadDim;
-                        st_tagged(dst, m, part_tag);
-                        st_tagged(dst + 1, l, part_tag);
-                    } else {
-                        float* dst = a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2;
-                        st_agent(dst, m);
-                        st_agent(dst + 1, l);
-                    }
-                }
-            }
-            __syncthreads();
-
-            // ---- 4. P.V -------------------------------------------------------------------------------------
-#pragma unroll
-            for (int hh = 0; hh < NH; ++hh) {
-                float acc[GH][R::EPL];
-#pragma unroll
-                for (int g = 0; g < GH; ++g)
-#pragma unroll
-                    for (int e = 0; e < R::EPL; ++e) acc[g][e] = 0.f;
-#pragma unroll
-                for (int i = 0; i < kIter; ++i) {
-                    const int jj = i * kRowsPerIter + w * R::RPW + r;
-                    float vf[R::EPL];
-                    R::unpack(vraw[i], vf);
-                    if (!live[i]) {                                      // masked rows hold a clamped (foreign) row
-#pragma unroll
-                        for (int e = 0; e < R::EPL; ++e) vf[e] = 0.f;
-                    }
-#pragma unroll
-                    for (int g = 0; g < GH; ++g) {
-                        const float p = sm_logit[hh * GH + g][jj];
-#pragma unroll
-                        for (int e = 0; e < R::EPL; ++e) acc[g][e] += p * vf[e];
-                    }
-                }
-#pragma unroll
-                for (int g = 0; g < GH; ++g)
-#pragma unroll
-                    for (int e = 0; e < R::EPL; ++e) acc[g][e] = sum_rows<R::RPW>(acc[g][e]);
-                if (r == 0) {
-#pragma unroll
-                    for (int g = 0; g < GH; ++g)
-#pragma unroll
-                        for (int e = 0; e < R::EPL; e += 4)
-                            *reinterpret_cast<float4*>(&sm_red_flat[w * kRedStride + (hh * GH + g) * kHeadDim + cc * R::EPL + e]) =
-                                make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
+                    float* dst = red + (16 * dt + t16) * G + 4 * qd;
+                    if constexpr (G >= 4) *reinterpret_cast<float4*>(dst) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
+                    else if constexpr (G == 2) *reinterpret_cast<float2*>(dst) = make_float2(o[dt][0], o[dt][1]);
+                    else dst[0] = o[dt][0];
                 }
             }
         }
-        if constexpr (!kMfma) __syncthreads();                    // (the matrix-core path met after its partial sums already)
+        __syncthreads();
+        // the waves' sums, each relative to its own max, meet: head g, dim d of the block
         for (int i = tid; i < kOut; i += kBlockThreads) {
             const int g = i / kHeadDim, d = i % kHeadDim;
-            const int src = kMfma ? d * G + g : i;                     // the MFMA path leaves its sums head fastest
-            float o = sm_red_flat[src];
+            float mw[kTiles], lw[kTiles];
 #pragma unroll
-            for (int ww = 1; ww < kRedWaves; ++ww) o += sm_red_flat[ww * kRedStride + src];
-            if constexpr (MODE == kStep) st_tagged(my_part + g * kStepPartWords + d, o, part_tag);
-            else st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, o);
+            for (int k = 0; k < kTiles; k += 4) {
+                const float4 t = *reinterpret_cast<const float4*>(&sm_wmax[g][k]), u = *reinterpret_cast<const float4*>(&sm_wsum[g][k]);
+                mw[k] = t.x; mw[k + 1] = t.y; mw[k + 2] = t.z; mw[k + 3] = t.w;
+                lw[k] = u.x; lw[k + 1] = u.y; lw[k + 2] = u.z; lw[k + 3] = u.w;
+            }
+            float mb = -INFINITY;
+#pragma unroll
+            for (int k = 0; k < kTiles; ++k) mb = fmaxf(mb, mw[k]);
+            float o = 0.f, lb = 0.f;
+#pragma unroll
+            for (int k = 0; k < kTiles; ++k) {
+                const float c = mb > -INFINITY ? exp2_neg(mw[k] - mb) : 0.f;
+                o += c * reinterpret_cast<const float*>(sm + k * kTileBytes)[d * G + g];
+                lb += c * lw[k];
+            }
+            if constexpr (MODE == kStep) {
+                unsigned long long* dst = my_part + g * kStepPartWords;
+                st_tagged(dst + d, o, part_tag);
+                if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
+            } else if (nsplit == 1) {                                 // the only block: its sums are the result
+                const bool empty = !(lb > 0.f);                       // every retrieved position was out of range
+                a.out[qhead0 * kHeadDim + i] = empty ? 0.f : o / lb;
+                if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
+            } else {
+                st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, o);
+                if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
+            }
         }
         SKV_T(7);
     }
@@ -1542,7 +1457,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     const float ms = val_of(mv[u]);
                     if (ms > -INFINITY) {
                         const float nm = fmaxf(M, ms);
-                        const float ca = exp2f(M - nm), cb = exp2f(ms - nm);  // M == -inf gives ca == 0
+                        const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);  // M == -inf gives ca == 0
                         L = L * ca + val_of(lv[u]) * cb;
                         o = o * ca + val_of(pv[u]) * cb;
                         M = nm;
@@ -1551,9 +1466,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
         }
         SKV_T(10);
-        // (o, M, L) per thread: 3 x 1024 floats in the space the scores came through; a thread whose wait ran out leaves
-        // NaN as its maximum
-        float* scratch = reinterpret_cast<float*>(sm_keys);
+        // (o, M, L) per thread: 3 x 1024 floats; a thread whose wait ran out leaves NaN as its maximum
+        float* scratch = sm_merge;
         scratch[tid] = o; scratch[kBlockThreads + tid] = ok ? M : __builtin_nanf(""); scratch[2 * kBlockThreads + tid] = L;
         __syncthreads();
         SKV_T(11);
@@ -1573,7 +1487,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
                 if (mg[gg] > -INFINITY) {
-                    const float c = exp2f(mg[gg] - Mx);
+                    const float c = exp2_neg(mg[gg] - Mx);
                     Ls += c * lg[gg];
                     os += c * og[gg];
                 }
@@ -1599,6 +1513,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         return;
     }
 
+    if (nsplit == 1) return;
     // ---- 5. last arrival combines ------------------------------------------------------------------
     // Every wave waits for its own write-through partial stores, then the barrier: only after both does thread 0
     // issue the device-scope increment, so whoever reads nsplit - 1 knows every partial is there.
@@ -1612,7 +1527,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     if (!sm_last) return;
     // A thread owns one pair of output floats and every kGroups-th split: one batch of independent 8-byte
     // loads, merged online (running max M, normaliser L, outputs) in registers; groups merge through LDS.
-    float4* scratch = reinterpret_cast<float4*>(sm_red_flat);               // (o0, o1, M, L) per thread
+    float4* scratch = reinterpret_cast<float4*>(sm);                        // (o0, o1, M, L) per thread
     {
         const int col = tid % kCol2, grp = tid / kCol2;
         const int g = col / (kHeadDim / 2);
@@ -1633,7 +1548,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 const float ms = (s0 + u * kGroups < nsplit) ? lo_f(mv[u]) : -INFINITY;
                 if (ms > -INFINITY) {
                     const float nm = fmaxf(M, ms);
-                    const float ca = exp2f(M - nm), cb = exp2f(ms - nm);      // M == -inf gives ca == 0
+                    const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);      // M == -inf gives ca == 0
                     L = L * ca + hi_f(mv[u]) * cb;
                     o0 = o0 * ca + lo_f(pv[u]) * cb;
                     o1 = o1 * ca + hi_f(pv[u]) * cb;
@@ -1642,7 +1557,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
         }
         SKV_T(10);
-        __syncthreads();                                     // sm_red (partial sums) no longer read by anyone
+        __syncthreads();                                     // the partial sums are no longer read by anyone
         scratch[grp * kCol2 + col] = make_float4(o0, o1, M, L);
     }
     __syncthreads();
@@ -1656,7 +1571,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         for (int grp = 0; grp < kGroups; ++grp) {
             const float4 t = scratch[grp * kCol2 + tid];
             if (t.z > -INFINITY) {
-                const float c = exp2f(t.z - M);
+                const float c = exp2_neg(t.z - M);
                 L += c * t.w; o0 += c * t.x; o1 += c * t.y;
             }
         }
@@ -1692,46 +1607,44 @@ constexpr int kStreamChunk = kStreamWaves * kStreamTiles * 16;    // 1024 tokens
 static_assert(kStreamChunk == kBlockThreads, "the usual block: one retrieved position per thread");
 
 constexpr int kStreamMaxChunk = 2 * kStreamChunk;                 // the largest block: two positions per thread
-constexpr int kStreamVPitch = 2 * kHeadDim + 16;                  // bytes per value row in LDS; +16 spreads row groups over banks
 
-struct StreamShared {
-    __attribute__((aligned(16))) char v[kStreamWaves][16 * kStreamVPitch];   // value tile, later the wave's partial sums
-    __attribute__((aligned(16))) unsigned short q[16][kHeadDim];             // the group's queries, rows >= G zero
+template <int EB, int CHUNK> struct StreamShared {
+    __attribute__((aligned(16))) char v[kStreamWaves][16 * Tile<EB>::kPitch];    // the selection's, then value tiles, then the waves' partial sums
+    __attribute__((aligned(16))) char q[16][kHeadDim * EB];                      // the group's queries, rows >= G zero
     float wmax[kStreamWaves][16], wsum[kStreamWaves][16];
-    int32_t row[kStreamMaxChunk];                                            // pool row of every position of the block (-1: none)
+    int32_t row[max_of(CHUNK, kBlockThreads)];                                   // pool row of every position of the block (-1: none)
     int next_tile;
     int last;
 };
 
-// queries of the group -> LDS (16 bytes per thread: 16 rows x 256 bytes); a barrier must follow before they are read
-template <int G>
-__device__ __forceinline__ void stream_load_queries(const AttArgs& a, StreamShared& ss, int64_t qhead0) {
+// queries of the group -> LDS (16 rows, 16 bytes per thread); a barrier must follow before they are read
+template <int EB, int G, int CHUNK>
+__device__ __forceinline__ void stream_load_queries(const AttArgs& a, StreamShared<EB, CHUNK>& ss, int64_t qhead0) {
+    constexpr int LPR = Tile<EB>::LPR;
     const int tid = threadIdx.x;
-    if (tid < 256) {
-        const int row = tid >> 4, piece = tid & 15;
+    if (tid < 16 * LPR) {
+        const int row = tid / LPR, piece = tid % LPR;
         uint4 t = make_uint4(0, 0, 0, 0);
-        if (row < G) t = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + row) * kHeadDim) * 2 + 16 * piece);
-        *reinterpret_cast<uint4*>(&ss.q[row][8 * piece]) = t;
+        if (row < G) t = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + row) * kHeadDim) * EB + 16 * piece);
+        *reinterpret_cast<uint4*>(&ss.q[row][16 * piece]) = t;
     }
 }
 
 // Attention of one block of CHUNK (512, 1024 or 2048) positions once the selection is known: n = retrieved tokens of the
 // (sequence, head); ss.row holds the pool row of position split * CHUNK + i at i (-1: no such token) for i < CHUNK.
 // The queries are on their way to ss.q.  Every thread of the block calls this.
-template <int G, int CHUNK>
-__device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss, int bh, int b, int h, int split, const Seq& sq,
+template <int EB, int G, int CHUNK>
+__device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB, CHUNK>& ss, int bh, int b, int h, int split, const Seq& sq,
                                               int32_t n) {
 
     constexpr int NW = kStreamWaves;
     constexpr int kThreads = kBlockThreads;
-    constexpr int kRowBytes = kHeadDim * 2;
-    constexpr int kVPitch = kStreamVPitch;
+    using X = Tile<EB>;
+    constexpr int kRowBytes = kHeadDim * EB;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
     constexpr int kOut = G * kHeadDim, kCol2 = kOut / 2;
     constexpr int kColsPerThread = (kCol2 + kThreads - 1) / kThreads;
-    typedef short bf16x4 __attribute__((ext_vector_type(4)));
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    static_assert(G * kHeadDim * 4 <= 16 * kVPitch, "a wave's partial sums fit in its value tile");
+    static_assert(G * kHeadDim * 4 <= 16 * X::kPitch, "a wave's partial sums fit in its value tile");
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int t16 = lane & 15, qd = lane >> 4;
     const int64_t qhead0 = (int64_t)b * (a.Hkv * G) + (int64_t)h * G;
@@ -1748,10 +1661,11 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
     if (split >= nsplit) return;
     const int32_t cnt = min(CHUNK, n - j0);
 
-    // The block's positions are walked in 16-token tiles handed out dynamically: a wave starts with tile w and takes the
+    // The block's positions are walked in 16-token tiles.  bf16: handed out dynamically, a wave starts with tile w and takes the
     // next free one from an LDS counter whenever it finishes one, so the waves that memory serves first do more tiles
     // and all 16 keep loads in flight until the block's last tile (with four fixed tiles per wave the slowest wave ran
-    // about 5 us behind the first).  Rows of unreal positions are stored as -1.
+    // about 5 us behind the first).  fp32: every 16th tile, so that a result is the same in every call.  Rows of unreal positions are
+    // stored as -1.
     if (tid == 0) ss.next_tile = NW;
     const int ntiles = (cnt + 15) / 16;
     const char* Kh = a.Kb + ((int64_t)h * a.v.T_total + sq.tok_base) * kRowBytes;
@@ -1760,81 +1674,79 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
     __syncthreads();                                              // rows and the tile counter are in LDS
     SKV_T(4);
 
-    uint4 kA[4], vR[4];
+    uint4 kA[X::kPieces], vR[EB == 2 ? X::kLoads : 1];
+    char* vt_b = ss.v[w];
     // rows of a tile: lanes with the same t16 hold the row of the tile's token t16 (-1: not real)
     auto rows_of = [&](int tile) { return ss.row[16 * tile + t16]; };
-    auto issue = [&](int32_t rowt, uint4* k, uint4* v) {
-        // 32-bit byte offsets from the (head, sequence) base: the host only uses this kernel below 2^24 tokens.
-        // Value rows are requested whole by one instruction and go non-temporal; a key instruction takes 64 bytes of each of
-        // 16 rows, so two of them share every 128-byte line, which must stay until the second (non-temporal key loads:
-        // 6 sequences in 512-token blocks 720 -> 790 us for 32 layers).
+    // Requests on 32-bit byte offsets from the (head, sequence) base: the host only uses this kernel for pools of less than 4 GB a head.
+    // Value rows are requested whole and go non-temporal; a key instruction takes 64 bytes of each of
+    // 16 rows, so two of them share every 128-byte line, which must stay until the second (non-temporal key loads:
+    // 6 sequences in 512-token blocks 720 -> 790 us for 32 layers).
+    auto issue_keys = [&](int32_t rowt, int ln) {
+        const uint32_t offK = (uint32_t)max(rowt, 0) * kRowBytes + 16u * (ln >> 4);
+#pragma unroll
+        for (int s2 = 0; s2 < X::kPieces; ++s2) kA[s2] = *reinterpret_cast<const uint4*>(Kh + (offK + 64u * s2));
+    };
+    // bf16: to registers, as early as the keys; fp32: straight to the value tile (registers would spill), once that is free
+    auto issue_values = [&](int32_t rowt, int ln) {
         const int32_t rc = max(rowt, 0);
-        const uint32_t offK = (uint32_t)rc * kRowBytes + 16u * qd;
 #pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) k[s2] = *reinterpret_cast<const uint4*>(Kh + (offK + 64u * s2));
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const uint32_t offV = (uint32_t)__shfl(rc, 4 * ii + qd) * kRowBytes + 16u * t16;
-            v[ii] = ld_stream(Vh + offV);
+        for (int ii = 0; ii < X::kLoads; ++ii) {
+            const uint32_t offV = (uint32_t)__shfl(rc, X::RPL * ii + ln / X::LPR) * kRowBytes;
+            if constexpr (EB == 2) vR[ii] = ld_stream(Vh + (offV + 16u * (ln % X::LPR)));
+            else load_lds_stream(Vh, offV + 16u * ((ln % X::LPR) ^ (4 * ((X::RPL * ii) >> 2))), vt_b + 1024 * ii);
         }
     };
     int tile = w;                                                 // wave-uniform
     int32_t row_cur = tile < ntiles ? rows_of(tile) : -1;
-    if (tile < ntiles) issue(row_cur, kA, vR);
+    if (tile < ntiles) { issue_keys(row_cur, lane); issue_values(row_cur, lane); }
     SKV_T(5);
 
     float m_run = -INFINITY, l_run = 0.f;                         // per head t16; l_run covers this lane's tokens only
-    f32x4 o[kHeadDim / 16];
+    f32x4_t o[kHeadDim / 16];
 #pragma unroll
-    for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    char* vt_b = ss.v[w];
-    // B fragments of P.V by the LDS transpose read: this lane's address is the 4-dim piece (dims 4 (t16 % 4) .. + 3 of
-    // the 16-dim group) of value row 4 qd + t16 / 4
-    const char* vtr = vt_b + (4 * qd + (t16 >> 2)) * kVPitch + 8 * (t16 & 3);
+    for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     while (tile < ntiles) {
+        // fp32: addresses that depend on the lane are formed anew for every tile (kept across the loop they would be spilled)
+        int ln = lane;
+        if constexpr (EB == 4) asm volatile("" : "+v"(ln));
         // the wave's next tile, asked for early so that its rows are known when this tile's registers come free
-        int nxt = 0;
-        if (lane == 0) nxt = atomicAdd(&ss.next_tile, 1);
-        nxt = __builtin_amdgcn_readfirstlane(nxt);
-        const unsigned int tm = (unsigned int)__ballot(row_cur >= 0) & 0xffffu;   // bit t: token t of the tile is real
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) {
-            const uint4 qq = *reinterpret_cast<const uint4*>(&ss.q[t16][32 * s2 + 8 * qd]);
-            acc = mfma_qk32(kA[s2], qq, acc);
+        int nxt = tile + NW;
+        if constexpr (EB == 2) {
+            if (lane == 0) nxt = atomicAdd(&ss.next_tile, 1);
+            nxt = __builtin_amdgcn_readfirstlane(nxt);
         }
-        // the tile's value rows go to the wave's LDS tile (rows of masked tokens as zeros) ...
+        const unsigned int tm = (unsigned int)__ballot(row_cur >= 0) & 0xffffu;   // bit t: token t of the tile is real
+        const f32x4_t acc = X::logits(kA, [&](int s2) { return *reinterpret_cast<const uint4*>(&ss.q[ln & 15][64 * s2 + 16 * (ln >> 4)]); });
+        if constexpr (EB == 2) {
+            // the tile's value rows go to the wave's LDS tile (rows of masked tokens as zeros) ...
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const bool lr = (tm >> (4 * ii + qd)) & 1u;
-            *reinterpret_cast<uint4*>(vt_b + (4 * ii + qd) * kVPitch + 16 * t16) = lr ? vR[ii] : make_uint4(0, 0, 0, 0);
+            for (int ii = 0; ii < X::kLoads; ++ii) {
+                const int row = X::RPL * ii + lane / X::LPR;
+                *reinterpret_cast<uint4*>(vt_b + X::place(row, lane % X::LPR)) = ((tm >> row) & 1u) ? vR[ii] : make_uint4(0, 0, 0, 0);
+            }
         }
         // ... which frees the row registers for the next tile: its loads fly during this tile's softmax and P.V
         row_cur = nxt < ntiles ? rows_of(nxt) : -1;
-        if (nxt < ntiles) issue(row_cur, kA, vR);
+        if (nxt < ntiles) {
+            issue_keys(row_cur, ln);
+            if constexpr (EB == 2) issue_values(row_cur, ln);
+        }
         tile = nxt;
-        float sj[4], mt = -INFINITY;
-        bool lv[4];
+        float p[4], mt = -INFINITY;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            lv[j] = (tm >> (4 * qd + j)) & 1u;
-            sj[j] = lv[j] ? acc[j] * scale : -INFINITY;
-            mt = fmaxf(mt, sj[j]);
+            p[j] = ((tm >> (4 * qd + j)) & 1u) ? acc[j] * scale : -INFINITY;
+            mt = fmaxf(mt, p[j]);
         }
-        mt = fmaxf(mt, __shfl_xor(mt, 16));
-        mt = fmaxf(mt, __shfl_xor(mt, 32));
-        const float m_new = fmaxf(m_run, mt);
-        const float alpha = (m_new > -INFINITY) ? exp2f(m_run - m_new) : 1.f;   // m_run == -inf gives 0
-        unsigned short pb[4];
+        const float m_new = fmaxf(m_run, max_quads(mt));
+        const float alpha = (m_new > -INFINITY) ? exp2_neg(m_run - m_new) : 1.f;   // m_run == -inf gives 0
         float lw = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float p = lv[j] ? exp2f(sj[j] - m_new) : 0.f;
-            uint32_t u = __float_as_uint(p);
-            u += 0x7fffu + ((u >> 16) & 1u);                      // round to nearest even bf16
-            pb[j] = (unsigned short)(u >> 16);
-            lw += __uint_as_float((uint32_t)pb[j] << 16);         // the normaliser sums the rounded weights
+            p[j] = m_new > -INFINITY ? exp2_neg(p[j] - m_new) : 0.f;  // masked: exp2(-inf) = 0
+            lw += X::weight(p[j]);
         }
         l_run = l_run * alpha + lw;
         m_run = m_new;
@@ -1846,30 +1758,34 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
         for (int dt = 0; dt < kHeadDim / 16; ++dt)
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[dt][j] *= ar[j];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");    // the tile is private to the wave: order only
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const bf16x4 pa = {(short)pb[0], (short)pb[1], (short)pb[2], (short)pb[3]};
-#pragma unroll
-        for (int dt = 0; dt < kHeadDim / 16; ++dt) {
-            const bf16x4 vb = lds_read_tr16(vtr + 32 * dt);
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, o[dt], 0, 0, 0);
+        if constexpr (EB == 4) {
+            // this tile's values have landed (the next tile's keys, requested after them, may be outstanding); rows of masked tokens as zeros
+            if (nxt < ntiles) wait_loads<X::kPieces>();
+            else wait_loads<0>();
+            if (tm != 0xffffu) {
+#pragma unroll 1
+                for (int row = 0; row < 16; ++row)
+                    if (!((tm >> row) & 1u) && ln < X::LPR) *reinterpret_cast<uint4*>(vt_b + X::place(row, ln)) = make_uint4(0, 0, 0, 0);
+            }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");    // reads of this tile precede the next tile's writes
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_sync();                                          // the tile is private to the wave: order only
+        X::output(p, vt_b, ln, o);
+        wave_lds_sync();                                          // reads of this tile precede the next tile's writes
+        if constexpr (EB == 4) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (nxt < ntiles) issue_values(row_cur, ln);
+        }
     }
     SKV_T(6);
 
     // ---- the block's waves combine: common max per head, partial sums through the value tiles ------------------
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = sum_quads(l_run);
     if (qd == 0) ss.wmax[w][t16] = m_run;
     __syncthreads();
     float mb = -INFINITY;
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) mb = fmaxf(mb, ss.wmax[ww][t16]);
-    const float cw = (m_run > -INFINITY) ? exp2f(m_run - mb) : 0.f;
+    const float cw = (m_run > -INFINITY) ? exp2_neg(m_run - mb) : 0.f;
     if (qd == 0) ss.wsum[w][t16] = l_run * cw;
     {
         float cr[4];
@@ -1952,7 +1868,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
                 const float ms = (s0 + u < nsplit) ? lo_f(mv[u]) : -INFINITY;
                 if (ms > -INFINITY) {
                     const float nm = fmaxf(M, ms);
-                    const float ca = exp2f(M - nm), cb = exp2f(ms - nm);
+                    const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);
                     L = L * ca + hi_f(mv[u]) * cb;
                     o0 = o0 * ca + lo_f(pv[u]) * cb;
                     o1 = o1 * ca + hi_f(pv[u]) * cb;
@@ -1969,10 +1885,10 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared& ss
     SKV_T(9);
 }
 
-template <int G, int CHUNK>
+template <int EB, int G, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_attend_stream_kernel(AttArgs a) {
     static_assert(CHUNK % kWave == 0 && CHUNK <= kStreamMaxChunk, "the row table holds kStreamMaxChunk positions");
-    __shared__ StreamShared ss;
+    __shared__ StreamShared<EB, CHUNK> ss;
     const int bh = blockIdx.y, b = bh / a.Hkv, h = bh % a.Hkv, split = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     demand_args(a);
@@ -1982,10 +1898,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
 
     int32_t n;                    // retrieved tokens of this (sequence, head)
     {
-        __shared__ SelectShared sel_sh;
+        static_assert(sizeof(SelectShared) <= sizeof(ss.v), "the selection works in the value tiles' space");
+        SelectShared& sel_sh = *reinterpret_cast<SelectShared*>(ss.v);
         const int32_t budget = min(sq.budget, a.budget_cap);
         if (split > 0 && j0 >= budget) return;                    // n <= budget: nothing for this split
-        stream_load_queries<G>(a, ss, (int64_t)b * (a.Hkv * G) + (int64_t)h * G);
+        stream_load_queries<EB, G, CHUNK>(a, ss, (int64_t)b * (a.Hkv * G) + (int64_t)h * G);
         for (int p = tid; p < (CHUNK > kBlockThreads ? CHUNK : kBlockThreads); p += kBlockThreads)
             ss.row[p] = -1;                                       // bucket-start marks first, the rows of all positions later
         // A selected bucket that reaches into this block's positions marks, in every 64-position piece it touches,
@@ -2018,19 +1935,19 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
             ss.row[pc * kWave + lane] = (pos < n && xi >= 0 && xi < sq.n_tok_ctx) ? xi : -1;
         }
     }
-    stream_attend<G, CHUNK>(a, ss, bh, b, h, split, sq, n);
+    stream_attend<EB, G, CHUNK>(a, ss, bh, b, h, split, sq, n);
 }
 
-template <int CHUNK>
+template <int EB, int CHUNK>
 static hipError_t launch_select_attend_stream_g(Ctx* c, const AttArgs& a) {
     int n_splits = (c->budget_cap + CHUNK - 1) / CHUNK;
     if (n_splits < 1) n_splits = 1;       // block 0 still writes the empty-selection result
     const dim3 grid(n_splits, a.v.B * c->d.n_kv_heads), block(kBlockThreads);
     switch (c->G) {
-        case 1: hipLaunchKernelGGL((select_attend_stream_kernel<1, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 2: hipLaunchKernelGGL((select_attend_stream_kernel<2, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 4: hipLaunchKernelGGL((select_attend_stream_kernel<4, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 8: hipLaunchKernelGGL((select_attend_stream_kernel<8, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 1: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 1, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 2: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 2, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 4: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 4, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 8: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 8, CHUNK>), grid, block, 0, c->stream, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2089,12 +2006,13 @@ hipError_t launch_attend_indirect(Ctx* c, const void* q, const void* K_layer, co
                                      : launch_attend_g<4, kIndirect, kAttChunkWide>(c, a, n_splits);
 }
 
-// Batch form of the fused step (bf16 pools below 2^24 tokens, addressed with 32-bit byte offsets inside a
-// (head, sequence) slab): 1024-token blocks that select, then stream.
+// Batch form of the fused step: blocks that select, then stream.  Rows are addressed with 32-bit byte offsets inside a (head, sequence)
+// slab.
+bool can_stream(const Ctx* c, int32_t T_total) { return T_total < (c->d.kv_dtype == SKV_BF16 ? 1 << 24 : 1 << 23); }
 hipError_t launch_select_attend_stream(Ctx* c, const void* q, const void* K_layer, const void* V_layer, const float* score,
                                        const int32_t* sent_off, const int32_t* sent_len, const SeqView& v, float* out,
                                        float* lse, int32_t* tok_idx_out, int32_t* n_tok_out) {
-    if (c->d.kv_dtype != SKV_BF16 || v.T_total >= (1 << 24)) return hipErrorInvalidValue;
+    if (!can_stream(c, v.T_total)) return hipErrorInvalidValue;
     AttArgs a = att_common(c, q, K_layer, V_layer, v, out, lse);
     a.score = score; a.sent_off = sent_off; a.sent_len = sent_len;
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
@@ -2105,11 +2023,12 @@ hipError_t launch_select_attend_stream(Ctx* c, const void* q, const void* K_laye
     // about 5/3 of a 1024-token round (32 sequences: 94.7 -> 87.0 us, 64: 180.2 -> 166.3; 48: 137.8 either way).
     const int pairs = v.B * c->d.n_kv_heads;
     const int blocks = pairs * ((c->budget_cap + kStreamChunk - 1) / kStreamChunk);
-    if (2 * blocks <= c->n_cu) return launch_select_attend_stream_g<kStreamChunk / 2>(c, a);
+    const bool bf16 = c->d.kv_dtype == SKV_BF16;
+    if (2 * blocks <= c->n_cu) return bf16 ? launch_select_attend_stream_g<2, kStreamChunk / 2>(c, a) : launch_select_attend_stream_g<4, kStreamChunk / 2>(c, a);
     const int big_blocks = pairs * ((c->budget_cap + kStreamMaxChunk - 1) / kStreamMaxChunk);
     const int rounds = (blocks + c->n_cu - 1) / c->n_cu, big_rounds = (big_blocks + c->n_cu - 1) / c->n_cu;
-    if (5 * big_rounds < 3 * rounds) return launch_select_attend_stream_g<kStreamMaxChunk>(c, a);
-    return launch_select_attend_stream_g<kStreamChunk>(c, a);
+    if (5 * big_rounds < 3 * rounds) return bf16 ? launch_select_attend_stream_g<2, kStreamMaxChunk>(c, a) : launch_select_attend_stream_g<4, kStreamMaxChunk>(c, a);
+    return bf16 ? launch_select_attend_stream_g<2, kStreamChunk>(c, a) : launch_select_attend_stream_g<4, kStreamChunk>(c, a);
 }
 
 hipError_t launch_select_attend(Ctx* c, const void* q, const void* K_layer, const void* V_layer, const float* score,
@@ -2125,13 +2044,14 @@ hipError_t launch_select_attend(Ctx* c, const void* q, const void* K_layer, cons
     // (4 sequences of 32K, 8 heads, budget 2048: 25.9 us in 128-token blocks, 17 in 256-token blocks).
     const int pairs = v.B * c->d.n_kv_heads;
     auto blocks = [&](int chunk) { return pairs * ((c->budget_cap + chunk - 1) / chunk); };
-    if (c->d.kv_dtype == SKV_BF16 && blocks(kAttChunkMid) > c->n_cu) {
+    if (blocks(kAttChunkMid) > c->n_cu) {
         const int n_splits = (c->budget_cap + kAttChunkWide - 1) / kAttChunkWide;
-        return launch_attend_g<2, kFused, kAttChunkWide>(c, a, n_splits);
+        return c->d.kv_dtype == SKV_BF16 ? launch_attend_g<2, kFused, kAttChunkWide>(c, a, n_splits)
+                                         : launch_attend_g<4, kFused, kAttChunkWide>(c, a, n_splits);
     }
     // Every split block of a head repeats the selection; with thousands of buckets per sequence that repetition
     // (bucket loads from L2, histogram passes) outweighs the shorter K/V phase of 64-token blocks.
-    if (v.S_total / (v.B > 0 ? v.B : 1) > kMidChunkMinSentences || (c->d.kv_dtype == SKV_BF16 && blocks(kAttChunk) > c->n_cu)) {
+    if (v.S_total / (v.B > 0 ? v.B : 1) > kMidChunkMinSentences || blocks(kAttChunk) > c->n_cu) {
         const int n_splits = (c->budget_cap + kAttChunkMid - 1) / kAttChunkMid;
         return c->d.kv_dtype == SKV_BF16 ? launch_attend_g<2, kFused, kAttChunkMid>(c, a, n_splits)
                                          : launch_attend_g<4, kFused, kAttChunkMid>(c, a, n_splits);

@@ -138,7 +138,8 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
                        const void* V_layer, const int32_t* sent_off, const int32_t* sent_len, const SeqView& v, float* out,
                        float* lse, int32_t* tok_idx_out, int32_t* n_tok_out, bool* launched);
 
-// The same for batches with bf16 pools of fewer than 2^24 tokens: 1024-token blocks, streaming attention.
+// The same for batches: streaming attention, for pools of fewer than 2^24 (bf16) or 2^23 (fp32) tokens.
+bool can_stream(const Ctx* c, int32_t T_total);
 hipError_t launch_select_attend_stream(Ctx* c, const void* q, const void* K_layer, const void* V_layer, const float* score,
                                        const int32_t* sent_off, const int32_t* sent_len, const SeqView& v, float* out,
                                        float* lse, int32_t* tok_idx_out, int32_t* n_tok_out);
