@@ -1059,6 +1059,7 @@ struct AttArgs {
     const char* semvec;       // the layer's table [Hkv][S_total][D]
     int32_t sv_bytes;         // bytes per element of the table: 4, 2 or 1
     int32_t lg_parts;         // log2 of the blocks per pair
+    int32_t lg_merge;         // log2 of the blocks that merge one query head
     unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
     unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
     int32_t score_stride;
@@ -1080,7 +1081,7 @@ __device__ __forceinline__ void demand_args(const AttArgs& a) {
                  "s"(a.Hkv), "s"(a.max_splits), "s"(a.part), "s"(a.ml), "s"(a.counter), "s"(a.out), "s"(a.lse));
 }
 __device__ __forceinline__ void demand_step_args(const AttArgs& a) {
-    asm volatile("" ::"s"(a.q_score), "s"(a.semvec), "s"(a.sv_bytes), "s"(a.lg_parts), "s"(a.step_epoch), "s"(a.step_score),
+    asm volatile("" ::"s"(a.q_score), "s"(a.semvec), "s"(a.sv_bytes), "s"(a.lg_parts), "s"(a.lg_merge), "s"(a.step_epoch), "s"(a.step_score),
                  "s"(a.score_stride), "s"(a.step_part), "s"(a.wait_limit), "s"(a.err_dev), "s"(a.err_host));
 }
 
@@ -1185,7 +1186,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             else score_rows(std::integral_constant<int, 16>{});
             SKV_T(12);
             // Blocks that neither attend (no position of theirs can hold a token: n <= budget) nor merge are done.
-            if (split >= G && j0 >= budget) return;
+            if (split >= (G << a.lg_merge) && j0 >= budget) return;
         } else {
             if (split > 0 && j0 >= budget) return;                // n <= budget: nothing for this split
         }
@@ -1235,7 +1236,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // every thread of the block calls this
     auto others_were_here = [&](int first) -> bool {
         if constexpr (MODE == kStep) {
-            const int n_cand = min(1 << a.lg_parts, max(G, (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
+            const int n_cand = min(1 << a.lg_parts, max(G << a.lg_merge, (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
             if (n_cand <= first) return true;                     // block-uniform: the usual case, the budget is filled
             // the flag lives in the first word of the merge's scratch (thread 0, the only reader of that
             // word in the merge, is past its reads when it clears it)
@@ -1270,11 +1271,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         return;
     }
     const int nsplit = (n + CHUNK - 1) / CHUNK;
-    // kStep: block g < G merges query head g of the group, whether or not it holds retrieved tokens itself
+    // kStep: the first G << lg_merge blocks merge, whether or not they hold retrieved tokens themselves
     const bool has_work = split < nsplit;
     if (!has_work) {
         presence();
-        if (!(MODE == kStep && split < G)) return;
+        if (!(MODE == kStep && split < (G << a.lg_merge))) return;
     }
     unsigned long long* my_part = nullptr;
     uint32_t part_tag = 0;
@@ -1421,29 +1422,30 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     }
 
     if constexpr (MODE == kStep) {
-        // ---- 5'. per-head merge without an arrival counter -------------------------------------------------------
-        // Block g < G of the pair merges query head g.  Thread (grp, col) -- a group is two whole waves, so a wave's
-        // loads of a partial row are contiguous -- reads dim `col` of the partials of the splits grp, grp + 8, ...
+        // ---- 5'. merge without an arrival counter ---------------------------------------------------------------
+        // Block m < G << lg_merge of the pair merges 128 >> lg_merge dims of query head m >> lg_merge.  Thread (grp, col) -- consecutive
+        // lanes on consecutive words of a partial row -- reads dim `col` of the partials of the splits grp, grp + groups, ...
         // (value and tag in one word) and their (max, normaliser) words, again and again until all carry the launch tag
         // (bounded; no barrier, no sleep: a wave leaves as soon as its own words are there), folds them into a running
-        // (max, normaliser, output), and the eight groups meet once in LDS.  No block waits for a store
+        // (max, normaliser, output), and the groups meet once in LDS.  No block waits for a store
         // acknowledgement and nothing is counted.
-        if (split >= G) return;
-        constexpr int kGroups8 = kBlockThreads / kHeadDim;               // 8 split groups of 128 threads
-        const int g = split, col = tid % kHeadDim, grp = tid / kHeadDim;
+        if (split >= (G << a.lg_merge)) return;
+        const int lg_dims = 7 - a.lg_merge, dims = 1 << lg_dims, groups = kBlockThreads >> lg_dims;       // 8 groups of 128 dims .. 32 of 32
+        const int g = split >> a.lg_merge, d0 = (split & ((1 << a.lg_merge) - 1)) << lg_dims;
+        const int col = tid & (dims - 1), grp = tid >> lg_dims;
         float M = -INFINITY, L = 0.f, o = 0.f;
         bool ok = step_ok;
-        for (int base = 0; base < nsplit && ok; base += 4 * kGroups8) {
-            unsigned long long pv[4] = {0, 0, 0, 0}, mv[4] = {0, 0, 0, 0}, lv[4] = {0, 0, 0, 0};
+        for (int base = 0; base < nsplit && ok; base += 2 * groups) {
+            unsigned long long pv[2] = {0, 0}, mv[2] = {0, 0}, lv[2] = {0, 0};
             bool mine = false;
             for (int32_t round = 0; !mine && round < a.wait_limit; ++round) {
                 mine = true;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int sp = base + grp + u * kGroups8;             // wave-uniform
+                for (int u = 0; u < 2; ++u) {
+                    const int sp = base + grp + u * groups;
                     if (sp < nsplit) {
                         const unsigned long long* src = a.step_part + ((int64_t)(sp * n_pairs + bh) * G + g) * kStepPartWords;
-                        pv[u] = ld_tagged(src + col);
+                        pv[u] = ld_tagged(src + d0 + col);
                         mv[u] = ld_tagged(src + kHeadDim);
                         lv[u] = ld_tagged(src + kHeadDim + 1);
                         mine = mine && tag_of(pv[u]) == tag && tag_of(mv[u]) == tag && tag_of(lv[u]) == tag;
@@ -1452,8 +1454,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
             ok = mine;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (ok && base + grp + u * kGroups8 < nsplit) {
+            for (int u = 0; u < 2; ++u) {
+                if (ok && base + grp + u * groups < nsplit) {
                     const float ms = val_of(mv[u]);
                     if (ms > -INFINITY) {
                         const float nm = fmaxf(M, ms);
@@ -1471,18 +1473,23 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         scratch[tid] = o; scratch[kBlockThreads + tid] = ok ? M : __builtin_nanf(""); scratch[2 * kBlockThreads + tid] = L;
         __syncthreads();
         SKV_T(11);
+        // 128 threads: 1 << lg_merge of them for a dim, eight groups each
         bool bad = false;
         if (tid < kHeadDim) {
+            constexpr int kGroups8 = 8;
+            const int dim = tid >> a.lg_merge, first = (tid & ((1 << a.lg_merge) - 1)) * kGroups8;
             float mg[kGroups8], lg[kGroups8], og[kGroups8];
             float Mx = -INFINITY;
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
-                og[gg] = scratch[gg * kHeadDim + tid];
-                mg[gg] = scratch[kBlockThreads + gg * kHeadDim + tid];
-                lg[gg] = scratch[2 * kBlockThreads + gg * kHeadDim + tid];
+                const int at = ((first + gg) << lg_dims) + dim;
+                og[gg] = scratch[at];
+                mg[gg] = scratch[kBlockThreads + at];
+                lg[gg] = scratch[2 * kBlockThreads + at];
                 bad = bad || mg[gg] != mg[gg];
                 Mx = fmaxf(Mx, mg[gg]);
             }
+            for (int k = 1; k < (1 << a.lg_merge); k <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, k));
             float Ls = 0.f, os = 0.f;
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
@@ -1492,12 +1499,19 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     os += c * og[gg];
                 }
             }
-            const bool empty = !(Ls > 0.f);                               // every retrieved position was out of range
-            float res = empty ? 0.f : os / Ls;
-            if (bad) res = __builtin_nanf("");                            // a wait of this launch ran out
-            a.out[(qhead0 + g) * kHeadDim + tid] = res;
-            if (a.lse && tid == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (Mx + log2f(Ls)) * kLn2;
-            if (bad) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
+            for (int k = 1; k < (1 << a.lg_merge); k <<= 1) {
+                Ls += __shfl_xor(Ls, k);
+                os += __shfl_xor(os, k);
+                bad = bad || __shfl_xor(bad ? 1 : 0, k) != 0;
+            }
+            if (dim * (1 << a.lg_merge) == tid) {                         // the first of the dim's threads
+                const bool empty = !(Ls > 0.f);                           // every retrieved position was out of range
+                float res = empty ? 0.f : os / Ls;
+                if (bad) res = __builtin_nanf("");                        // a wait of this launch ran out
+                a.out[(qhead0 + g) * kHeadDim + d0 + dim] = res;
+                if (a.lse && d0 + dim == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (Mx + log2f(Ls)) * kLn2;
+                if (bad) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
+            }
         }
         // Block 0 ends the pair's launch by advancing its epoch: its threads have seen the partial of every attending
         // block (the barrier above) and now make sure of the word of every other block that ran the selection; all of
@@ -2115,8 +2129,11 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     int lg = 0;
     while ((pairs << (lg + 1)) <= max_blocks) ++lg;
     const int parts = 1 << lg;
-    // attention blocks of 128 tokens, or of 256 when a pair has too few blocks for 128 (three or four sequences of 8 heads)
-    int chunk = kAttChunkMid;
+    // Attention blocks of 64 tokens, or of 128 or 256 when a pair has too few blocks: the K/V rows of a block pass its compute unit's
+    // 64 bytes a cycle and its four SIMDs, one 16-token tile each.  One sequence, us per layer in 128- / 64-token blocks: bf16
+    // budget 512: 10.9 / 10.0, 1000: 11.5 / 10.8, 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0.
+    int chunk = kAttChunk;
+    if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkMid;
     if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkWide;
     const int att_parts = (c->budget_cap + chunk - 1) / chunk;
     if (att_parts > parts || c->G > parts) return hipSuccess;                    // attention blocks or mergers do not fit
@@ -2125,12 +2142,19 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
     a.q_score = (const char*)q_score; a.semvec = (const char*)semvec_layer;
     a.sv_bytes = c->d.semvec_dtype == SKV_BF16 ? kTableBf16 : c->d.semvec_dtype == SKV_FP8_E4M3 ? kTableE4m3 : kTableF32;
-    a.lg_parts = lg; a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
+    // Up to four blocks merge a head, 32 dims each, so that a thread has one word of a partial row to wait for instead of four (one sequence,
+    // budget 2048, per layer: 12.8 -> 12.55 us, fp32 14.9 -> 14.5), as long as they all attend themselves: a block that runs the
+    // selection only to merge costs more than it saves (budget 512, 8 query heads per KV head: 10.5 -> 12.0 with 32 of them).
+    int lg_merge = 0;
+    while (lg_merge < 2 && (c->G << (lg_merge + 1)) <= att_parts) ++lg_merge;
+    a.lg_parts = lg; a.lg_merge = lg_merge; a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
     a.step_part = c->step_part; a.wait_limit = c->wait_limit;
     a.err_dev = c->err_dev; a.err_host = c->err_host_dev;
     if (chunk == kAttChunkWide)
         return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunkWide>(c, a, pairs * parts, launched)
                                          : launch_step_g<4, kAttChunkWide>(c, a, pairs * parts, launched);
+    if (chunk == kAttChunk) return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunk>(c, a, pairs * parts, launched)
+                                     : launch_step_g<4, kAttChunk>(c, a, pairs * parts, launched);
     return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunkMid>(c, a, pairs * parts, launched)
                                      : launch_step_g<4, kAttChunkMid>(c, a, pairs * parts, launched);
 }

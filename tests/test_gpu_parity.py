@@ -489,6 +489,14 @@ def test_fused_batch_2048_token_blocks(U, oracle32, budget, Hq):
     _fused_case(U, oracle32, wl, seed=31, layers=[0])
 
 
+@pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
+def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
+    """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20), a last tile of one token and of sixteen, a
+    second block of one token, contexts shorter than the budget."""
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(900, 4500), budgets=(budget,), dtype="f32")
+    _fused_case(U, oracle32, wl, seed=33, layers=[0])
+
+
 def test_fused_batch_of_hundreds_of_short_sequences(U, oracle32):
     """600 sequences of 0..60 tokens (4800 (sequence, head) pairs): the sequence lookup of the score kernel bisects seven
     levels deep before its eight-entry step, most waves span several sequences, the attention grid has thousands of rows."""
