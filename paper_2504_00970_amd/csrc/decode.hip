@@ -1032,6 +1032,49 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A wave leaves its sums of P V (element j of o[dt]: head 4 qd + j, dim 16 dt + t16) in the space of its value tile, head fastest (dim d,
+// head g at [d * G + g]), so that a lane stores its heads of one dim with a single instruction.
+template <int G>
+__device__ __forceinline__ void leave_sums(char* tile, const f32x4_t (&o)[kHeadDim / 16]) {
+    const int lane = threadIdx.x & 63, t16 = lane & 15, qd = lane >> 4;
+    if (4 * qd < G) {
+#pragma unroll
+        for (int dt = 0; dt < kHeadDim / 16; ++dt) {
+            float* dst = reinterpret_cast<float*>(tile) + (16 * dt + t16) * G + 4 * qd;
+            if constexpr (G >= 4) *reinterpret_cast<float4*>(dst) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
+            else if constexpr (G == 2) *reinterpret_cast<float2*>(dst) = make_float2(o[dt][0], o[dt][1]);
+            else dst[0] = o[dt][0];
+        }
+    }
+}
+// A barrier later: the block's output relative to its common max, from the sums that NT waves left `stride` bytes apart, each relative to
+// the wave's own max.  put(g, d, sum, max, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
+// streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).
+template <int G, int NT, bool HEAD_FAST, typename Put>
+__device__ __forceinline__ void block_sums(const char* tiles, int stride, const float (&wmax)[16][NT], const float (&wsum)[16][NT], Put put) {
+    for (int i = threadIdx.x; i < G * kHeadDim; i += kBlockThreads) {
+        const int g = HEAD_FAST ? i % G : i / kHeadDim, d = HEAD_FAST ? i / G : i % kHeadDim;
+        float mw[NT], lw[NT];
+#pragma unroll
+        for (int k = 0; k < NT; k += 4) {
+            const float4 t = *reinterpret_cast<const float4*>(&wmax[g][k]), u = *reinterpret_cast<const float4*>(&wsum[g][k]);
+            mw[k] = t.x; mw[k + 1] = t.y; mw[k + 2] = t.z; mw[k + 3] = t.w;
+            lw[k] = u.x; lw[k + 1] = u.y; lw[k + 2] = u.z; lw[k + 3] = u.w;
+        }
+        float mb = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) mb = fmaxf(mb, mw[k]);
+        float o = 0.f, lb = 0.f;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            const float c = mb > -INFINITY ? exp2_neg(mw[k] - mb) : 0.f;
+            o += c * reinterpret_cast<const float*>(tiles + k * stride)[d * G + g];
+            lb += c * lw[k];
+        }
+        put(g, d, o, mb, lb);
+    }
+}
+
 struct AttArgs {
     const char* q;            // [B][Hq][D]
     const char* Kb;           // kDirect: K_sel [B*Hkv][row_stride][D]; else the layer's pool [Hkv][T_total][D]
@@ -1371,53 +1414,23 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             wave_lds_sync();                                          // the tile is the wave's own: order only
             X::output(p, sm_v, lane, o);
             wave_lds_sync();
-            // the value tile has been consumed: its space takes the wave's partial sums, head fastest (dim d, head g at
-            // red[d * G + g]), so that a lane stores its heads of one dim with a single instruction
-            float* red = reinterpret_cast<float*>(sm_v);
-            if (4 * qd < G) {
-#pragma unroll
-                for (int dt = 0; dt < kHeadDim / 16; ++dt) {
-                    float* dst = red + (16 * dt + t16) * G + 4 * qd;
-                    if constexpr (G >= 4) *reinterpret_cast<float4*>(dst) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
-                    else if constexpr (G == 2) *reinterpret_cast<float2*>(dst) = make_float2(o[dt][0], o[dt][1]);
-                    else dst[0] = o[dt][0];
-                }
-            }
+            leave_sums<G>(sm_v, o);
         }
         __syncthreads();
-        // the waves' sums, each relative to its own max, meet: head g, dim d of the block
-        for (int i = tid; i < kOut; i += kBlockThreads) {
-            const int g = i / kHeadDim, d = i % kHeadDim;
-            float mw[kTiles], lw[kTiles];
-#pragma unroll
-            for (int k = 0; k < kTiles; k += 4) {
-                const float4 t = *reinterpret_cast<const float4*>(&sm_wmax[g][k]), u = *reinterpret_cast<const float4*>(&sm_wsum[g][k]);
-                mw[k] = t.x; mw[k + 1] = t.y; mw[k + 2] = t.z; mw[k + 3] = t.w;
-                lw[k] = u.x; lw[k + 1] = u.y; lw[k + 2] = u.z; lw[k + 3] = u.w;
-            }
-            float mb = -INFINITY;
-#pragma unroll
-            for (int k = 0; k < kTiles; ++k) mb = fmaxf(mb, mw[k]);
-            float o = 0.f, lb = 0.f;
-#pragma unroll
-            for (int k = 0; k < kTiles; ++k) {
-                const float c = mb > -INFINITY ? exp2_neg(mw[k] - mb) : 0.f;
-                o += c * reinterpret_cast<const float*>(sm + k * kTileBytes)[d * G + g];
-                lb += c * lw[k];
-            }
+        block_sums<G, kTiles, false>(sm, kTileBytes, sm_wmax, sm_wsum, [&](int g, int d, float sum, float mb, float lb) {
             if constexpr (MODE == kStep) {
                 unsigned long long* dst = my_part + g * kStepPartWords;
-                st_tagged(dst + d, o, part_tag);
+                st_tagged(dst + d, sum, part_tag);
                 if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
             } else if (nsplit == 1) {                                 // the only block: its sums are the result
                 const bool empty = !(lb > 0.f);                       // every retrieved position was out of range
-                a.out[qhead0 * kHeadDim + i] = empty ? 0.f : o / lb;
+                a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
                 if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
             } else {
-                st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, o);
+                st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
                 if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
             }
-        }
+        });
         SKV_T(7);
     }
 
@@ -1625,7 +1638,7 @@ constexpr int kStreamMaxChunk = 2 * kStreamChunk;                 // the largest
 template <int EB, int CHUNK> struct StreamShared {
     __attribute__((aligned(16))) char v[kStreamWaves][16 * Tile<EB>::kPitch];    // the selection's, then value tiles, then the waves' partial sums
     __attribute__((aligned(16))) char q[16][kHeadDim * EB];                      // the group's queries, rows >= G zero
-    float wmax[kStreamWaves][16], wsum[kStreamWaves][16];
+    __attribute__((aligned(16))) float wmax[16][kStreamWaves], wsum[16][kStreamWaves];   // per head and wave
     int32_t row[max_of(CHUNK, kBlockThreads)];                                   // pool row of every position of the block (-1: none)
     int next_tile;
     int last;
@@ -1792,63 +1805,22 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
     }
     SKV_T(6);
 
-    // ---- the block's waves combine: common max per head, partial sums through the value tiles ------------------
+    // ---- the block's waves combine -------------------------------------------------------------------------------
     l_run = sum_quads(l_run);
-    if (qd == 0) ss.wmax[w][t16] = m_run;
+    if (qd == 0) { ss.wmax[t16][w] = m_run; ss.wsum[t16][w] = l_run; }
+    leave_sums<G>(vt_b, o);
     __syncthreads();
-    float mb = -INFINITY;
-#pragma unroll
-    for (int ww = 0; ww < NW; ++ww) mb = fmaxf(mb, ss.wmax[ww][t16]);
-    const float cw = (m_run > -INFINITY) ? exp2_neg(m_run - mb) : 0.f;
-    if (qd == 0) ss.wsum[w][t16] = l_run * cw;
-    {
-        float cr[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cr[j] = __shfl(cw, 4 * qd + j);
-        float* red = reinterpret_cast<float*>(vt_b);
-#pragma unroll
-        for (int dt = 0; dt < kHeadDim / 16; ++dt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (4 * qd + j < G) red[(4 * qd + j) * kHeadDim + 16 * dt + t16] = o[dt][j] * cr[j];
-    }
-    __syncthreads();
-    if (nsplit == 1) {
-        // the only block of this (sequence, head): its combined sums are the result, no partials, no arrival, no merge
-        for (int i = tid; i < kOut; i += kThreads) {
-            const int g = i / kHeadDim;
-            float sum = 0.f, lb = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) {
-                sum += reinterpret_cast<const float*>(ss.v[ww])[i];
-                lb += ss.wsum[ww][g];
-            }
+    block_sums<G, NW, true>(ss.v[0], sizeof(ss.v[0]), ss.wmax, ss.wsum, [&](int g, int d, float sum, float mb, float lb) {
+        if (nsplit == 1) {                                        // the only block of this (sequence, head): no partials, no arrival, no merge
             const bool empty = !(lb > 0.f);                       // every retrieved position was out of range
-            a.out[qhead0 * kHeadDim + i] = empty ? 0.f : sum / lb;
-            if (a.lse && (i % kHeadDim) == 0) {
-                float mh = -INFINITY;
-#pragma unroll
-                for (int ww = 0; ww < NW; ++ww) mh = fmaxf(mh, ss.wmax[ww][g]);
-                a.lse[qhead0 + g] = empty ? -INFINITY : (mh + log2f(lb)) * kLn2;
-            }
+            a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
+            if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
+        } else {
+            st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
+            if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
         }
-        return;
-    }
-    if (tid < G) {
-        float lb = 0.f, mh = -INFINITY;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) { lb += ss.wsum[ww][tid]; mh = fmaxf(mh, ss.wmax[ww][tid]); }
-        float* dst = a.ml + (((qhead0 + tid) * a.max_splits) + slot) * 2;
-        st_agent(dst, mh);
-        st_agent(dst + 1, lb);
-    }
-    for (int i = tid; i < kOut; i += kThreads) {
-        const int g = i / kHeadDim, d = i % kHeadDim;
-        float sum = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) sum += reinterpret_cast<const float*>(ss.v[ww])[i];
-        st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
-    }
+    });
+    if (nsplit == 1) return;
     SKV_T(7);
 
     // ---- last arrival combines (same protocol as attend_kernel) ------------------------------------------------
