@@ -1186,14 +1186,16 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     const int slot = split * (CHUNK / kWave);                     // partial slot (slots are counted in 64-token units)
     SKV_T(0);
 
-    // The query fragments of the tile waves are requested first of all; they are in registers long before the
-    // key rows arrive, so the logits wait for the keys only (lane (t16, qd): head t16)
+    // The query fragments of the tile waves (lane (t16, qd): head t16).  bf16: requested first of all; they are in registers long before the
+    // key rows arrive, so the logits wait for the keys only.  fp32, twice the registers: just ahead of the keys (kept across the
+    // selection, a few registers would be spilled, which costs the single-launch step a tenth).
     uint4 qB[X::kPieces];
-    if (w < kTiles) {
+    auto request_queries = [&]() {
 #pragma unroll
         for (int s2 = 0; s2 < X::kPieces; ++s2)
             qB[s2] = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + min(t16, G - 1)) * kHeadDim) * EB + 64 * s2 + 16 * qd);
-    }
+    };
+    if (EB == 2 && w < kTiles) request_queries();
 
     int32_t n;                                                    // retrieved tokens of this (sequence, head)
     bool step_ok = true;                                          // kStep: every wait of this block ended in time
@@ -1343,6 +1345,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         const float scale = kLog2e * rsqrtf((float)kHeadDim);
         if (w < kTiles) {
             char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
+            if constexpr (EB == 4) request_queries();
             // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
             // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
             const int jj = 16 * w + t16;
