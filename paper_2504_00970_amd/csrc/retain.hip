@@ -5,6 +5,8 @@
 #include "skv_internal.h"
 #include "skv_device.h"
 
+#include <type_traits>
+
 namespace skv {
 
 // ------------------------------------------------------------------------------------------------
@@ -531,6 +533,9 @@ hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int3
 // the kept positions in ascending order, then the retained buckets: kept tokens of one bucket are
 // consecutive in keep_idx (positions ascend, bucket ids do not decrease), so ret_off[s] is the index of
 // the first kept token whose bucket id is >= s.
+// Bound by latency and by what one compute unit can load and count.  A wave owns consecutive tokens, a lane every 64th of them:
+// whole lines per load, and ranks within a wave by ballots.  (A thread with 32 consecutive tokens made every load
+// instruction touch 64 lines: 32 layers of 32768 tokens 47 us.)
 // ------------------------------------------------------------------------------------------------
 struct RetainShared {
     uint32_t hist[2048];
@@ -538,13 +543,14 @@ struct RetainShared {
     int32_t res[3][4];
 };
 
+template <int kRetainKreg>
 __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k,
                                                                const int32_t* __restrict__ seg_id, int32_t S,
                                                                int32_t* __restrict__ keep_all, int32_t keep_stride,
                                                                int32_t* __restrict__ n_keep, int32_t* __restrict__ ret_off_all,
                                                                int32_t* __restrict__ ret_len_all) {
     __shared__ RetainShared sh;
-    const int l = blockIdx.x, tid = threadIdx.x;
+    const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const float* alpha = alpha_all + (int64_t)l * Tp;
     int32_t* keep = keep_all + (int64_t)l * keep_stride;
     int32_t* ret_off = ret_off_all + (int64_t)l * (S + 1);
@@ -557,27 +563,33 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
         return;
     }
     const int kpt = (Tp + kBlockThreads - 1) / kBlockThreads;
-    const int32_t i0 = tid * kpt, i1 = min(i0 + kpt, Tp);
+    const int32_t i0 = w * kpt * kWave + lane;                         // this lane's tokens: i0, i0 + 64, ..., kpt of them
 
-    // Up to kRetainKreg tokens per thread (prompts up to 32K) keep their keys in registers: one batch of loads on
-    // clamped addresses instead of a dependent load per token in each of the six sweeps below.
-    constexpr int kRetainKreg = 32;
+    // Up to kRetainKreg tokens per thread keep their keys in registers: one batch of loads on
+    // clamped addresses instead of a load per token in each of the sweeps below.
     const bool in_regs = kpt <= kRetainKreg;                           // block-uniform
     uint32_t rk[kRetainKreg];
     if (in_regs) {
 #pragma unroll
-        for (int j = 0; j < kRetainKreg; ++j) rk[j] = __float_as_uint(alpha[min(i0 + j, Tp - 1)]);
+        for (int j = 0; j < kRetainKreg; ++j) rk[j] = __float_as_uint(alpha[min(i0 + j * kWave, Tp - 1)]);
 #pragma unroll
         for (int j = 0; j < kRetainKreg; ++j) rk[j] = score_key(__uint_as_float(rk[j]));
     }
-    // fn(i, key) for every token the thread owns, in position order
+    // fn(i, key, exists) for the 64 tokens of every step of the wave, in position order
     auto for_keys = [&](auto&& fn) {
         if (in_regs) {
 #pragma unroll
             for (int j = 0; j < kRetainKreg; ++j)
-                if (i0 + j < i1) fn(i0 + j, rk[j]);
+                if (j < kpt) fn(i0 + j * kWave, rk[j], i0 + j * kWave < Tp);
         } else {
-            for (int32_t i = i0; i < i1; ++i) fn(i, score_key(alpha[i]));
+            for (int j = 0; j < kpt; j += 8) {
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = alpha[min(i0 + (j + u) * kWave, Tp - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (j + u < kpt) fn(i0 + (j + u) * kWave, score_key(x[u]), i0 + (j + u) * kWave < Tp);
+            }
         }
     };
 
@@ -591,8 +603,8 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
         for (int i = tid; i < 2048; i += kBlockThreads) sh.hist[i] = 0;
         if (tid == 0) sh.res[pass][0] = -1;
         __syncthreads();
-        for_keys([&](int32_t, uint32_t key) {
-            if (pass == 0 || (key >> shift) == prefix) atomicAdd(&sh.hist[(key >> nshift) & (nbins - 1)], 1u);
+        for_keys([&](int32_t, uint32_t key, bool exists) {
+            if (exists && (pass == 0 || (key >> shift) == prefix)) atomicAdd(&sh.hist[(key >> nshift) & (nbins - 1)], 1u);
         });
         __syncthreads();
         // thread order == descending digit order: thread t owns digits nbins-1-2t and nbins-2-2t
@@ -613,36 +625,55 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
     const uint32_t take_equal = (uint32_t)need - above;
 
     // ---- compaction in position order ------------------------------------------------------------------
-    uint32_t my_eq = 0;
-    for_keys([&](int32_t, uint32_t key) { my_eq += key == prefix ? 1u : 0u; });
-    uint32_t tot;
-    uint32_t eq_before = block_scan_u32(my_eq, sh.wave_tot[3], &tot) - my_eq;
-    uint32_t my_cnt = 0;
-    {
-        uint32_t e = eq_before;
-        for_keys([&](int32_t, uint32_t key) {
-            if (key > prefix) my_cnt += 1;
-            else if (key == prefix) { if (e < take_equal) my_cnt += 1; e += 1; }
-        });
-    }
-    uint32_t pos = block_scan_u32(my_cnt, sh.wave_tot[4], &tot) - my_cnt;
-    {
-        uint32_t e = eq_before;
-        for_keys([&](int32_t i, uint32_t key) {
-            bool kept = key > prefix;
-            if (key == prefix) { kept = e < take_equal; e += 1; }
-            if (kept) keep[pos++] = i;
-        });
-    }
+    // counts of the wave, exclusive over the waves before it; every lane holds them
+    auto before_wave = [&](uint32_t mine, uint32_t* slot) -> uint32_t {
+        uint32_t tot;
+        const uint32_t own = lane == 0 ? mine : 0u;
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(block_scan_u32(own, slot, &tot) - own));
+    };
+    auto lower = [&](unsigned long long m) { return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
+    uint32_t my_gt = 0, my_eq = 0;
+    for_keys([&](int32_t, uint32_t key, bool exists) {
+        my_gt += (uint32_t)__popcll(__ballot(exists && key > prefix));
+        my_eq += (uint32_t)__popcll(__ballot(exists && key == prefix));
+    });
+    uint32_t eq = before_wave(my_eq, sh.wave_tot[3]);                  // equal ones before the wave, later before the step
+    const uint32_t eq_kept = min(eq + my_eq, take_equal) - min(eq, take_equal);
+    uint32_t pos = before_wave(my_gt + eq_kept, sh.wave_tot[4]);
+    for_keys([&](int32_t i, uint32_t key, bool exists) {
+        const unsigned long long m_eq = __ballot(exists && key == prefix);
+        const bool kept = exists && (key > prefix || (key == prefix && eq + lower(m_eq) < take_equal));
+        const unsigned long long m = __ballot(kept);
+        if (kept) keep[pos + lower(m)] = i;
+        eq += (uint32_t)__popcll(m_eq);
+        pos += (uint32_t)__popcll(m);
+    });
     __syncthreads();                                                   // keep[0 .. need) is written (block-visible)
 
     // ---- buckets of the retained tokens ------------------------------------------------------------------
-    for (int32_t j = tid; j < need; j += kBlockThreads) {
-        const int32_t s_cur = min(max(seg_id[keep[j]], 0), S - 1);
-        const int32_t s_prev = j > 0 ? min(max(seg_id[keep[j - 1]], 0), S - 1) : -1;
-        for (int32_t s = s_prev + 1; s <= s_cur; ++s) ret_off[s] = j;
-        if (j == need - 1)
-            for (int32_t s = s_cur + 1; s <= S; ++s) ret_off[s] = need;
+    constexpr int kU = 4;                                              // kept tokens of a thread whose loads are out together
+    for (int32_t j0 = tid; j0 < need; j0 += kU * kBlockThreads) {
+        int32_t s_cur[kU], s_prev[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = min(j0 + u * kBlockThreads, need - 1);
+            s_cur[u] = keep[j];
+            s_prev[u] = keep[max(j - 1, 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            s_cur[u] = seg_id[s_cur[u]];
+            s_prev[u] = seg_id[s_prev[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = j0 + u * kBlockThreads;
+            if (j >= need) break;
+            const int32_t cur = min(max(s_cur[u], 0), S - 1), prev = j > 0 ? min(max(s_prev[u], 0), S - 1) : -1;
+            for (int32_t s = prev + 1; s <= cur; ++s) ret_off[s] = j;
+            if (j == need - 1)
+                for (int32_t s = cur + 1; s <= S; ++s) ret_off[s] = need;
+        }
     }
     __syncthreads();
     for (int s = tid; s < S; s += kBlockThreads) ret_len[s] = ret_off[s + 1] - ret_off[s];
@@ -650,8 +681,11 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
 
 hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
                          int32_t* n_keep, int32_t* ret_off, int32_t* ret_len) {
-    hipLaunchKernelGGL(retain_kernel, dim3(c->d.n_layers), dim3(kBlockThreads), 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx,
-                       max(k, 1), n_keep, ret_off, ret_len);
+    const dim3 grid(c->d.n_layers), block(kBlockThreads);
+    if (Tp <= 4 * kBlockThreads)
+        hipLaunchKernelGGL(retain_kernel<4>, grid, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len);
+    else                                                               // prompts up to 32K in registers
+        hipLaunchKernelGGL(retain_kernel<32>, grid, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len);
     return hipGetLastError();
 }
 
@@ -659,7 +693,7 @@ hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, cons
 // Pool compaction: K_ret/V_ret [L][Hkv][k][D] = rows keep_idx[l][0 .. n_keep[l]) of K/V [L][Hkv][T][D].
 // Same branch-free copy as the decode-side gather; the kept positions are shared by the heads of a layer.
 // ------------------------------------------------------------------------------------------------
-template <int EB>
+template <int EB, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char* __restrict__ Kp, const char* __restrict__ Vp, int32_t T,
                                                                      const int32_t* __restrict__ keep_all, int32_t k,
                                                                      const int32_t* __restrict__ n_keep, int32_t Hkv,
@@ -681,25 +715,42 @@ __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char
     for (int i = 0; i < kIter; ++i) x[i] = keep[min(j0 + i * kRowsPerIter + r, n - 1)];
     uint4 val[kIter];
 #pragma unroll
-    for (int i = 0; i < kIter; ++i)
-        val[i] = ld_stream(src + (int64_t)min(max(x[i], 0), T - 1) * kRowBytes + cc * 16);
+    for (int i = 0; i < kIter; ++i) {
+        const char* p = src + (int64_t)min(max(x[i], 0), T - 1) * kRowBytes + cc * 16;
+        val[i] = STREAM ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
+    }
 #pragma unroll
     for (int i = 0; i < kIter; ++i) {
         const int32_t j = j0 + i * kRowsPerIter + r;
-        if (j < n && x[i] >= 0 && x[i] < T) st_stream(dst + (int64_t)j * kRowBytes + cc * 16, val[i]);
+        char* p = dst + (int64_t)j * kRowBytes + cc * 16;
+        if (j < n && x[i] >= 0 && x[i] < T) {
+            if (STREAM) st_stream(p, val[i]);
+            else *reinterpret_cast<uint4*>(p) = val[i];
+        }
     }
 }
 
+// Non-temporal rows from this many bytes of output on (a smaller retained pool is read again from the caches): 32 layers x 8 heads, the whole
+// retention with plain / non-temporal rows, us: 34 MB 27.5 / 30.5, 67 MB 46.8 / 47.4, 134 MB 83.7 / 77.2, 537 MB 320 / 296.
+constexpr int64_t kCompactStreamBytes = 96ll << 20;
 hipError_t launch_compact_pool(Ctx* c, const void* K_pool, const void* V_pool, int32_t T, const int32_t* keep_idx, int32_t k,
                                const int32_t* n_keep, void* K_ret, void* V_ret) {
     if (k == 0) return hipSuccess;
     const dim3 grid((k + kGatherRowsPerBlock - 1) / kGatherRowsPerBlock, c->d.n_layers * c->d.n_kv_heads, 2), block(kGatherThreads);
-    if (c->d.kv_dtype == SKV_BF16)
-        hipLaunchKernelGGL(compact_pool_kernel<2>, grid, block, 0, c->stream, (const char*)K_pool, (const char*)V_pool, T, keep_idx, k,
-                           n_keep, c->d.n_kv_heads, (char*)K_ret, (char*)V_ret);
-    else
-        hipLaunchKernelGGL(compact_pool_kernel<4>, grid, block, 0, c->stream, (const char*)K_pool, (const char*)V_pool, T, keep_idx, k,
-                           n_keep, c->d.n_kv_heads, (char*)K_ret, (char*)V_ret);
+    const int64_t bytes = 2ll * c->d.n_layers * c->d.n_kv_heads * k * kHeadDim * (c->d.kv_dtype == SKV_BF16 ? 2 : 4);
+    auto launch = [&](auto eb, auto stream) {
+        hipLaunchKernelGGL((compact_pool_kernel<decltype(eb)::value, decltype(stream)::value>), grid, block, 0, c->stream, (const char*)K_pool,
+                           (const char*)V_pool, T, keep_idx, k, n_keep, c->d.n_kv_heads, (char*)K_ret, (char*)V_ret);
+    };
+    using std::integral_constant;
+    const bool streams = bytes > kCompactStreamBytes;
+    if (c->d.kv_dtype == SKV_BF16) {
+        if (streams) launch(integral_constant<int, 2>{}, std::true_type{});
+        else launch(integral_constant<int, 2>{}, std::false_type{});
+    } else {
+        if (streams) launch(integral_constant<int, 4>{}, std::true_type{});
+        else launch(integral_constant<int, 4>{}, std::false_type{});
+    }
     return hipGetLastError();
 }
 
