@@ -1,9 +1,10 @@
-"""Builds libsentencekv.so (gfx950) in-tree with hipcc."""
+"""Builds libsentencekv.so (gfx950) in-tree with hipcc, and the module that calls it from Python with the host compiler."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -12,6 +13,7 @@ LIB = os.path.join(HERE, "libsentencekv.so")
 # profiling build (-DSKV_PHASE_STAMPS): the decode kernels record the wall clock at marked places, see csrc/skv_stamps.h;
 # built by `python -m paper_2504_00970_amd._build --stamps`, loaded by `bench.py --phase-stamps`
 LIB_STAMPS = os.path.join(HERE, "libsentencekv_stamps.so")
+CALLS = os.path.join(HERE, "_calls.so")
 SOURCES = ["api.hip", "prefill.hip", "decode.hip", "retain.hip"]
 HEADERS = [os.path.join(CSRC, "skv_internal.h"), os.path.join(CSRC, "skv_device.h"), os.path.join(CSRC, "skv_stamps.h"),
            os.path.join(INCLUDE, "sentencekv.h")]
@@ -33,10 +35,19 @@ def stale(lib: str = "") -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _calls_command() -> list:
+    import torch
+    t = os.path.dirname(torch.__file__)
+    return [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-I{INCLUDE}", "-isystem", f"{t}/include",
+            "-isystem", f"{t}/include/torch/csrc/api/include", "-isystem", sysconfig.get_paths()["include"],
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", os.path.join(CSRC, "calls.cpp"), "-o", CALLS + ".tmp",
+            f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{t}/lib"]
+
+
 def build(force: bool = True, verbose: bool = False, stamps: bool = False) -> str:
-    """Compile the library: one hipcc process per source file, side by side, then one link.  With force=False an
-    up-to-date library is kept.  stamps=True builds the profiling variant (LIB_STAMPS) instead."""
-    if not force and not stamps and not stale():
+    """Compile the library and the call module: one compiler process per source file, side by side, then one link.  With
+    force=False up-to-date ones are kept.  stamps=True builds the profiling variant of the library (LIB_STAMPS) instead."""
+    if not force and not stamps and not stale() and os.path.exists(CALLS):
         return LIB
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     objdir = os.path.join(HERE, "_build", "stamps" if stamps else "lib")
@@ -50,13 +61,21 @@ def build(force: bool = True, verbose: bool = False, stamps: bool = False) -> st
         if verbose:
             print(" ".join(cmd), flush=True)
         jobs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    calls = []
+    if not stamps:
+        cmd = _calls_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        calls = [("calls.cpp", CALLS, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     failed = []
-    for src, _, proc in jobs:
+    for src, _, proc in jobs + calls:
         out, _ = proc.communicate()
         if proc.returncode != 0:
             failed.append(f"{src}:\n{out}")
     if failed:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(failed))
+        raise RuntimeError("compilation failed:\n" + "\n".join(failed))
+    if calls:
+        os.replace(CALLS + ".tmp", CALLS)
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[obj for _, obj, _ in jobs], "-o", lib + ".tmp"]
     if verbose:
         print(" ".join(link), flush=True)

@@ -1,8 +1,9 @@
-"""Thin ctypes binding of libsentencekv (see include/sentencekv.h).
+"""Thin Python binding of libsentencekv (see include/sentencekv.h).
 
-Argument marshalling only: every function here forwards raw device pointers of caller-allocated
+Argument marshalling only: every function here forwards the device pointers of caller-allocated
 torch tensors to the C entry point of the same name and raises on a non-zero status.  Nothing is
 computed in Python and there is no fallback: if the HIP library is missing or fails, calls raise.
+The calls of a serving loop go through a native module (csrc/calls.cpp), set-up calls through ctypes.
 """
 from __future__ import annotations
 
@@ -31,6 +32,7 @@ class _Desc(ctypes.Structure):
 
 
 _LIB = None
+_CALLS = None
 _vp, _i32, _int, _i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int, ctypes.c_int64
 
 _SIGNATURES = {
@@ -68,11 +70,14 @@ def lib_path() -> str:
 
 
 def _lib():
-    """Load the built library; build it first only if no library is there at all."""
-    global _LIB
+    """Load the built library and the module that calls it; build them first only if they are not there at all."""
+    global _LIB, _CALLS
     if _LIB is None:
-        if not os.path.exists(_build.LIB):
+        if not os.path.exists(_build.LIB) or not os.path.exists(_build.CALLS):
             _build.build(force=True)
+        from . import _calls
+        _calls.load(_build.LIB)
+        _CALLS = _calls
         lib = ctypes.CDLL(_build.LIB)
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(lib, name)
@@ -132,11 +137,12 @@ class Context:
             stream = torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
         _check(lib.skv_create(ctypes.byref(h), ctypes.byref(d), _vp(stream)), "skv_create")
         self._h = h
+        self._handle = h.value
 
     def close(self) -> None:
         if getattr(self, "_h", None):
             _lib().skv_destroy(self._h)
-            self._h = None
+            self._h = self._handle = None
 
     def __del__(self):
         try:
@@ -164,66 +170,66 @@ class Context:
                 T: Optional[int] = None) -> Optional[int]:
         host = ctypes.c_int32(-1)
         T = tok.shape[0] if T is None else T
-        rc = _lib().skv_segment(self._h, _p(tok), T, _p(term_bitmap), vocab, _p(seg_id), _p(sent_off),
-                                _p(sent_len), _p(n_sent_dev), ctypes.addressof(host) if sync else None)
+        rc = _CALLS.skv_segment(self._handle, tok, T, term_bitmap, vocab, seg_id, sent_off,
+                                sent_len, n_sent_dev, ctypes.addressof(host) if sync else None)
         _check(rc, "skv_segment")
         return int(host.value) if sync else None
 
     def build_semvec(self, K_pool, sent_off, S: int, semvec) -> None:
         T = K_pool.shape[2]
-        _check(_lib().skv_build_semvec(self._h, _p(K_pool), T, _p(sent_off), S, _p(semvec)), "skv_build_semvec")
+        _check(_CALLS.skv_build_semvec(self._handle, K_pool, T, sent_off, S, semvec), "skv_build_semvec")
 
     def build_semvec_layers(self, K_pool, sent_off, S: int, semvec) -> None:
         T = K_pool.shape[2]
-        _check(_lib().skv_build_semvec_layers(self._h, _p(K_pool), T, _p(sent_off), S, _p(semvec)), "skv_build_semvec_layers")
+        _check(_CALLS.skv_build_semvec_layers(self._handle, K_pool, T, sent_off, S, semvec), "skv_build_semvec_layers")
 
     # ---- prefill-side token retention (Sec. 4.1) ---------------------------------------------------------
     def token_importance_work_bytes(self, T: int, N: int) -> int:
         return int(_lib().skv_token_importance_work_bytes(self._h, T, N))
 
     def token_importance(self, q_obs, K_pool, T: int, N: int, alpha, work) -> None:
-        _check(_lib().skv_token_importance(self._h, _p(q_obs), _p(K_pool), T, N, _p(alpha), _p(work),
+        _check(_CALLS.skv_token_importance(self._handle, q_obs, K_pool, T, N, alpha, work,
                                            work.numel() * work.element_size()), "skv_token_importance")
 
     def retain(self, alpha, Tp: int, k: int, seg_id, S: int, keep_idx, n_keep, ret_off, ret_len) -> None:
-        _check(_lib().skv_retain(self._h, _p(alpha), Tp, k, _p(seg_id), S, _p(keep_idx), _p(n_keep), _p(ret_off),
-                                 _p(ret_len)), "skv_retain")
+        _check(_CALLS.skv_retain(self._handle, alpha, Tp, k, seg_id, S, keep_idx, n_keep, ret_off,
+                                 ret_len), "skv_retain")
 
     def compact_pool(self, K_pool, V_pool, T: int, keep_idx, k: int, n_keep, K_ret, V_ret) -> None:
-        _check(_lib().skv_compact_pool(self._h, _p(K_pool), _p(V_pool), T, _p(keep_idx), k, _p(n_keep), _p(K_ret),
-                                       _p(V_ret)), "skv_compact_pool")
+        _check(_CALLS.skv_compact_pool(self._handle, K_pool, V_pool, T, keep_idx, k, n_keep, K_ret,
+                                       V_ret), "skv_compact_pool")
 
     # ---- sentence query cache (Eq. 2) ----------------------------------------------------------------
     def query_update(self, B: int, q_t, tok_t, term_bitmap, vocab: int, q_sum, q_cnt, q_bar) -> None:
-        _check(_lib().skv_query_update(self._h, B, _p(q_t), _p(tok_t), _p(term_bitmap), vocab, _p(q_sum), _p(q_cnt),
-                                       _p(q_bar)), "skv_query_update")
+        _check(_CALLS.skv_query_update(self._handle, B, q_t, tok_t, term_bitmap, vocab, q_sum, q_cnt,
+                                       q_bar), "skv_query_update")
 
     # ---- (2)-(5) decode, one layer, one sequence ---------------------------------------------------
     def score(self, layer: int, q_score, semvec, S: int, score) -> None:
-        _check(_lib().skv_score(self._h, layer, _p(q_score), _p(semvec), S, _p(score)), "skv_score")
+        _check(_CALLS.skv_score(self._handle, layer, q_score, semvec, S, score), "skv_score")
 
     def select(self, score, sent_off, sent_len, S: int, budget: int, sel_sent, n_sel, tok_idx, n_tok) -> None:
-        _check(_lib().skv_select(self._h, _p(score), _p(sent_off), _p(sent_len), S, budget, _p(sel_sent), _p(n_sel),
-                                 _p(tok_idx), _p(n_tok)), "skv_select")
+        _check(_CALLS.skv_select(self._handle, score, sent_off, sent_len, S, budget, sel_sent, n_sel,
+                                 tok_idx, n_tok), "skv_select")
 
     def gather(self, layer: int, K_pool, V_pool, T: int, tok_idx, n_tok, budget: int, K_sel, V_sel,
                pool_in_host: bool = False) -> None:
-        _check(_lib().skv_gather(self._h, layer, _p(K_pool), _p(V_pool), T, int(pool_in_host), _p(tok_idx), _p(n_tok),
-                                 budget, _p(K_sel), _p(V_sel)), "skv_gather")
+        _check(_CALLS.skv_gather(self._handle, layer, K_pool, V_pool, T, int(pool_in_host), tok_idx, n_tok,
+                                 budget, K_sel, V_sel), "skv_gather")
 
     def attend(self, q_attn, K_sel, V_sel, n_tok, budget: int, out, lse=None) -> None:
-        _check(_lib().skv_attend(self._h, _p(q_attn), _p(K_sel), _p(V_sel), _p(n_tok), budget, _p(out), _p(lse)),
+        _check(_CALLS.skv_attend(self._handle, q_attn, K_sel, V_sel, n_tok, budget, out, lse),
                "skv_attend")
 
     # ---- fused, ragged batch -----------------------------------------------------------------------
     def decode_step(self, layer: int, B: int, q_score, q_attn, K_pool, V_pool, T_total: int, semvec, S_total: int,
                     cu_tok, cu_sent, sent_off, sent_len, budget, out, lse=None, tok_idx_out=None, n_tok_out=None) -> None:
-        _check(_lib().skv_decode_step(self._h, layer, B, _p(q_score), _p(q_attn), _p(K_pool), _p(V_pool), T_total,
-                                      _p(semvec), S_total, _p(cu_tok), _p(cu_sent), _p(sent_off), _p(sent_len),
-                                      _p(budget), _p(out), _p(lse), _p(tok_idx_out), _p(n_tok_out)), "skv_decode_step")
+        _check(_CALLS.skv_decode_step(self._handle, layer, B, q_score, q_attn, K_pool, V_pool, T_total,
+                                      semvec, S_total, cu_tok, cu_sent, sent_off, sent_len,
+                                      budget, out, lse, tok_idx_out, n_tok_out), "skv_decode_step")
 
     def merge_lse(self, n_heads: int, out_a, lse_a, out_b, lse_b, out, lse=None) -> None:
-        _check(_lib().skv_merge_lse(self._h, n_heads, _p(out_a), _p(lse_a), _p(out_b), _p(lse_b), _p(out), _p(lse)),
+        _check(_CALLS.skv_merge_lse(self._handle, n_heads, out_a, lse_a, out_b, lse_b, out, lse),
                "skv_merge_lse")
 
 

@@ -242,11 +242,16 @@ int skv_create(skv_ctx** out, const skv_desc* desc, void* hip_stream) {
 
 void skv_destroy(skv_ctx* ctx) {
     if (!ctx) return;
+    // a context may be given back by a garbage collector while this thread records some other stream into a graph: freeing memory
+    // then must not invalidate that recording
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     if (ctx->c.ws) {
         (void)hipStreamSynchronize(ctx->c.stream);
         (void)hipFree(ctx->c.ws);
     }
     if (ctx->c.err_host) (void)hipHostFree(ctx->c.err_host);
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
     delete ctx;
 }
 

@@ -1972,10 +1972,12 @@ hipError_t launch_attend(Ctx* c, const void* q, const void* K_sel, const void* V
                          const int32_t* n_tok, int32_t budget, const SeqView& v, float* out, float* lse) {
     AttArgs a = att_common(c, q, K_sel, V_sel, v, out, lse);
     a.n_tok = n_tok; a.row_stride = row_stride;
-    // Few (sequence, head) pairs: 128-token blocks.  The merging block's uncached reads of the partials cost about
+    // bf16, 129 to 256 tokens: one block, which writes the result itself (fp32 tiles keep the matrix cores of a compute unit busy too long for that: 16
+    // tiles 0.9 us behind 8).  Else, for few (sequence, head) pairs, 128-token blocks.  The merging block's uncached reads of the partials cost about
     // 0.1 us per split, more than a 64-token block saves on its K/V rows (budget 2048: 11.0 us with 64-token blocks,
     // 9.2 with 128, 10.8 with 256; from a budget of 4096 on 256-token blocks are ahead).
-    const bool wide = wide_chunks(c, v) || budget >= 4096;
+    const bool wide = wide_chunks(c, v) || budget >= 4096 ||
+                      (c->d.kv_dtype == SKV_BF16 && budget > kAttChunkMid && budget <= kAttChunkWide);
     const int chunk = wide ? kAttChunkWide : kAttChunkMid;
     int n_splits = (budget + chunk - 1) / chunk;
     if (n_splits < 1) n_splits = 1;       // block 0 still writes the empty-selection result
