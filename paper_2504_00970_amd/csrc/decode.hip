@@ -576,21 +576,27 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             // The words are read with consecutive lanes on consecutive words (thread t: words t, t + 1024, ...: whole
             // cache lines per wave instruction; a thread's own consecutive buckets would cost kpt times the memory
             // requests), and the keys reach their owners through LDS.
+            // A wave asks again only for those of its instructions that found a word missing.
             uint32_t kk[KREG];
+            unsigned int open = (1u << min(kpt, KREG)) - 1u;       // wave-uniform: instructions still to be asked
 #pragma unroll
             for (int i = 0; i < KREG; ++i) kk[i] = 0u;
-            for (int32_t round = 0; !mine && round < wait_limit; ++round) {
-                mine = true;
+            for (int32_t round = 0; open != 0u && round < wait_limit; ++round) {
+                unsigned long long wd[KREG];
 #pragma unroll
                 for (int i = 0; i < KREG; ++i) {
-                    if (i < kpt) {
-                        const int32_t sidx = min(i * kBlockThreads + tid, S - 1);
-                        const unsigned long long wd = ld_tagged(tw + sidx);
-                        kk[i] = (uint32_t)wd;
-                        mine = mine && tag_of(wd) == tag;
+                    wd[i] = 0ull;
+                    if ((open >> i) & 1u) wd[i] = ld_tagged(tw + min(i * kBlockThreads + tid, S - 1));
+                }
+#pragma unroll
+                for (int i = 0; i < KREG; ++i) {
+                    if ((open >> i) & 1u) {
+                        kk[i] = (uint32_t)wd[i];
+                        if (__all(tag_of(wd[i]) == tag)) open &= ~(1u << i);
                     }
                 }
             }
+            mine = open == 0u;
 #pragma unroll
             for (int i = 0; i < KREG; ++i) {
                 if (i < kpt) {
