@@ -1081,6 +1081,9 @@ __device__ __forceinline__ void block_sums(const char* tiles, int stride, const 
     }
 }
 
+// kStep: blocks of a pair that merge
+__device__ __forceinline__ int merging_blocks(int G, int lg_merge) { return lg_merge >= 0 ? G << lg_merge : G >> -lg_merge; }
+
 struct AttArgs {
     const char* q;            // [B][Hq][D]
     const char* Kb;           // kDirect: K_sel [B*Hkv][row_stride][D]; else the layer's pool [Hkv][T_total][D]
@@ -1108,7 +1111,7 @@ struct AttArgs {
     const char* semvec;       // the layer's table [Hkv][S_total][D]
     int32_t sv_bytes;         // bytes per element of the table: 4, 2 or 1
     int32_t lg_parts;         // log2 of the blocks per pair
-    int32_t lg_merge;         // log2 of the blocks that merge one query head
+    int32_t lg_merge;         // log2 of the blocks that merge one query head; -1: a block merges two heads
     unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
     unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
     int32_t score_stride;
@@ -1237,7 +1240,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             else score_rows(std::integral_constant<int, 16>{});
             SKV_T(12);
             // Blocks that neither attend (no position of theirs can hold a token: n <= budget) nor merge are done.
-            if (split >= (G << a.lg_merge) && j0 >= budget) return;
+            if (split >= merging_blocks(G, a.lg_merge) && j0 >= budget) return;
         } else {
             if (split > 0 && j0 >= budget) return;                // n <= budget: nothing for this split
         }
@@ -1287,7 +1290,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // every thread of the block calls this
     auto others_were_here = [&](int first) -> bool {
         if constexpr (MODE == kStep) {
-            const int n_cand = min(1 << a.lg_parts, max(G << a.lg_merge, (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
+            const int n_cand = min(1 << a.lg_parts, max(merging_blocks(G, a.lg_merge), (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
             if (n_cand <= first) return true;                     // block-uniform: the usual case, the budget is filled
             // the flag lives in the first word of the merge's scratch (thread 0, the only reader of that
             // word in the merge, is past its reads when it clears it)
@@ -1322,11 +1325,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         return;
     }
     const int nsplit = (n + CHUNK - 1) / CHUNK;
-    // kStep: the first G << lg_merge blocks merge, whether or not they hold retrieved tokens themselves
+    // kStep: the first merging_blocks() blocks merge, whether or not they hold retrieved tokens themselves
     const bool has_work = split < nsplit;
     if (!has_work) {
         presence();
-        if (!(MODE == kStep && split < (G << a.lg_merge))) return;
+        if (!(MODE == kStep && split < merging_blocks(G, a.lg_merge))) return;
     }
     unsigned long long* my_part = nullptr;
     uint32_t part_tag = 0;
@@ -1445,16 +1448,17 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 
     if constexpr (MODE == kStep) {
         // ---- 5'. merge without an arrival counter ---------------------------------------------------------------
-        // Block m < G << lg_merge of the pair merges 128 >> lg_merge dims of query head m >> lg_merge.  Thread (grp, col) -- consecutive
+        // Block m of the pair merges 128 >> lg_merge dims of query head m >> lg_merge, or two heads.  Thread (grp, col) -- consecutive
         // lanes on consecutive words of a partial row -- reads dim `col` of the partials of the splits grp, grp + groups, ...
         // (value and tag in one word) and their (max, normaliser) words, again and again until all carry the launch tag
         // (bounded; no barrier, no sleep: a wave leaves as soon as its own words are there), folds them into a running
         // (max, normaliser, output), and the groups meet once in LDS.  No block waits for a store
         // acknowledgement and nothing is counted.
-        if (split >= (G << a.lg_merge)) return;
-        const int lg_dims = 7 - a.lg_merge, dims = 1 << lg_dims, groups = kBlockThreads >> lg_dims;       // 8 groups of 128 dims .. 32 of 32
-        const int g = split >> a.lg_merge, d0 = (split & ((1 << a.lg_merge) - 1)) << lg_dims;
-        const int col = tid & (dims - 1), grp = tid >> lg_dims;
+        if (split >= merging_blocks(G, a.lg_merge)) return;
+        const int lg_dims = 7 - a.lg_merge, groups = kBlockThreads >> lg_dims;                            // 4 groups of 256 dims .. 32 of 32
+        // column `col` of the block's 1 << lg_dims: dim (at % 128) of query head (at / 128)
+        auto at_of = [&](int col) { return (split << lg_dims) + col; };
+        const int at = at_of(tid & ((1 << lg_dims) - 1)), grp = tid >> lg_dims, g = at / kHeadDim;
         float M = -INFINITY, L = 0.f, o = 0.f;
         bool ok = step_ok;
         for (int base = 0; base < nsplit && ok; base += 2 * groups) {
@@ -1467,7 +1471,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     const int sp = base + grp + u * groups;
                     if (sp < nsplit) {
                         const unsigned long long* src = a.step_part + ((int64_t)(sp * n_pairs + bh) * G + g) * kStepPartWords;
-                        pv[u] = ld_tagged(src + d0 + col);
+                        pv[u] = ld_tagged(src + at % kHeadDim);
                         mv[u] = ld_tagged(src + kHeadDim);
                         lv[u] = ld_tagged(src + kHeadDim + 1);
                         mine = mine && tag_of(pv[u]) == tag && tag_of(mv[u]) == tag && tag_of(lv[u]) == tag;
@@ -1495,23 +1499,24 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         scratch[tid] = o; scratch[kBlockThreads + tid] = ok ? M : __builtin_nanf(""); scratch[2 * kBlockThreads + tid] = L;
         __syncthreads();
         SKV_T(11);
-        // 128 threads: 1 << lg_merge of them for a dim, eight groups each
+        // `share` threads for a column, eight groups (or all four) each
+        const int lg_share = max(a.lg_merge, 0), share = 1 << lg_share;
         bool bad = false;
-        if (tid < kHeadDim) {
+        if (tid < (share << lg_dims)) {
             constexpr int kGroups8 = 8;
-            const int dim = tid >> a.lg_merge, first = (tid & ((1 << a.lg_merge) - 1)) * kGroups8;
+            const int col = tid >> lg_share, first = (tid & (share - 1)) * kGroups8;
             float mg[kGroups8], lg[kGroups8], og[kGroups8];
             float Mx = -INFINITY;
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
-                const int at = ((first + gg) << lg_dims) + dim;
-                og[gg] = scratch[at];
-                mg[gg] = scratch[kBlockThreads + at];
-                lg[gg] = scratch[2 * kBlockThreads + at];
+                const int i = (min(first + gg, groups - 1) << lg_dims) + col;
+                og[gg] = scratch[i];
+                mg[gg] = first + gg < groups ? scratch[kBlockThreads + i] : -INFINITY;
+                lg[gg] = scratch[2 * kBlockThreads + i];
                 bad = bad || mg[gg] != mg[gg];
                 Mx = fmaxf(Mx, mg[gg]);
             }
-            for (int k = 1; k < (1 << a.lg_merge); k <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, k));
+            for (int k = 1; k < share; k <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, k));
             float Ls = 0.f, os = 0.f;
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
@@ -1521,17 +1526,18 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     os += c * og[gg];
                 }
             }
-            for (int k = 1; k < (1 << a.lg_merge); k <<= 1) {
+            for (int k = 1; k < share; k <<= 1) {
                 Ls += __shfl_xor(Ls, k);
                 os += __shfl_xor(os, k);
                 bad = bad || __shfl_xor(bad ? 1 : 0, k) != 0;
             }
-            if (dim * (1 << a.lg_merge) == tid) {                         // the first of the dim's threads
+            if (first == 0) {                                             // the first of the column's threads
+                const int to = at_of(col);
                 const bool empty = !(Ls > 0.f);                           // every retrieved position was out of range
                 float res = empty ? 0.f : os / Ls;
                 if (bad) res = __builtin_nanf("");                        // a wait of this launch ran out
-                a.out[(qhead0 + g) * kHeadDim + d0 + dim] = res;
-                if (a.lse && d0 + dim == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (Mx + log2f(Ls)) * kLn2;
+                a.out[qhead0 * kHeadDim + to] = res;
+                if (a.lse && to % kHeadDim == 0) a.lse[qhead0 + to / kHeadDim] = empty ? -INFINITY : (Mx + log2f(Ls)) * kLn2;
                 if (bad) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
             }
         }
@@ -2119,7 +2125,7 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkMid;
     if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkWide;
     const int att_parts = (c->budget_cap + chunk - 1) / chunk;
-    if (att_parts > parts || c->G > parts) return hipSuccess;                    // attention blocks or mergers do not fit
+    if (att_parts > parts || c->G > 2 * parts) return hipSuccess;                // attention blocks or mergers do not fit
     AttArgs a = att_common(c, q_attn, K_layer, V_layer, v, out, lse);
     a.sent_off = sent_off; a.sent_len = sent_len;
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
@@ -2130,6 +2136,9 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     // selection only to merge costs more than it saves (budget 512, 8 query heads per KV head: 10.5 -> 12.0 with 32 of them).
     int lg_merge = 0;
     while (lg_merge < 2 && (c->G << (lg_merge + 1)) <= att_parts) ++lg_merge;
+    // two heads per merging block where a pair has fewer blocks that attend than heads: 8 query heads per KV head, 16 layers, 5 to 8
+    // sequences 319 -> 278 us and 347 -> 304 (which had to take two launches), one sequence at a budget of 200 178 -> 173
+    if (c->G > att_parts && c->G > 1 && (c->G > parts || c->G <= 2 * att_parts)) lg_merge = -1;
     a.lg_parts = lg; a.lg_merge = lg_merge; a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
     a.step_part = c->step_part; a.wait_limit = c->wait_limit;
     a.err_dev = c->err_dev; a.err_host = c->err_host_dev;

@@ -489,6 +489,14 @@ def test_fused_batch_2048_token_blocks(U, oracle32, budget, Hq):
     _fused_case(U, oracle32, wl, seed=31, layers=[0])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,budget", [(1, 100), (5, 700), (8, 1000), (8, 1)])
+def test_fused_single_launch_two_heads_per_merging_block(U, oracle32, B, budget, dtype):
+    """8 query heads per KV head and fewer than eight blocks that attend: a merging block takes two heads."""
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=64, batch=B, t_range=(700, 2500), budgets=(budget,), dtype=dtype)
+    _fused_case(U, oracle32, wl, seed=35, layers=[0])
+
+
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
     """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20), a last tile of one token and of sixteen, a
