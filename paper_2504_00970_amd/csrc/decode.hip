@@ -1151,8 +1151,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     using X = Tile<EB>;
     constexpr int kRowBytes = kHeadDim * EB;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
-    constexpr int kTiles = CHUNK / 16;                        // 16-token tiles, one per wave
-    static_assert(kTiles <= kBlockWaves && CHUNK % kWave == 0, "one tile per wave");
+    constexpr int kTiles = CHUNK / 16 < kBlockWaves ? CHUNK / 16 : kBlockWaves;    // waves with 16-token tiles
+    constexpr int kPasses = CHUNK / 16 / kTiles;              // tiles of such a wave: w, w + 16
+    static_assert(kTiles * kPasses * 16 == CHUNK && CHUNK % kWave == 0 && kPasses <= (EB == 2 ? 2 : 1), "the rows of a wave's tiles are in registers together");
     constexpr int kOut = G * kHeadDim;                        // outputs of the block
     constexpr int kCol2 = kOut / 2;                           // float pairs over the G heads
     constexpr int kGroups = kBlockThreads / kCol2;            // split groups of the merge: 16, 8, 4, 2 for G = 1, 2, 4, 8
@@ -1355,77 +1356,87 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         if (w < kTiles) {
             char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
             if constexpr (EB == 4) request_queries();
-            // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
-            // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
-            const int jj = 16 * w + t16;
-            bool liveK = jj < cnt;
-            int32_t rowK, rowV[X::kLoads];
-            if constexpr (MODE == kDirect) {
-                rowK = min(jj, cnt - 1);
+            uint4 kA[kPasses][X::kPieces], vR[kPasses][X::kLoads];
+            unsigned long long vm[kPasses];                           // bit t (t < 16): token t of the tile is real
 #pragma unroll
-                for (int i = 0; i < X::kLoads; ++i) rowV[i] = min(16 * w + X::RPL * i + lane / X::LPR, cnt - 1);
-            } else {
-                int32_t x, base = 0;                                  // x: row of the position this lane looked up, the tile's from lane `base` on
-                if constexpr (kSel) {
-                    // the wave fills its tile's 64-position piece in registers: the last bucket start at or before each position
-                    base = 16 * (w & 3);
-                    const int32_t v = sm_row[(w >> 2) * kWave + lane];
-                    const int32_t hp = (int32_t)wave_scan_max_u32(v >= 0 ? (uint32_t)lane + 1u : 0u) - 1;       // -1: none
-                    const int32_t start = __shfl(v, max(hp, 0));
-                    x = hp >= 0 ? start + (lane - hp) : -1;
-                    const int32_t pos = (w >> 2) * kWave + lane;
-                    if ((w & 3) == 0 && a.tok_idx_out && j0 + pos < n) a.tok_idx_out[(int64_t)bh * a.idx_stride + j0 + pos] = x;
+            for (int ps = 0; ps < kPasses; ++ps) {
+                // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
+                // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
+                const int tile = w + kTiles * ps, jj = 16 * tile + t16;
+                bool liveK = jj < cnt;
+                int32_t rowK, rowV[X::kLoads];
+                if constexpr (MODE == kDirect) {
+                    rowK = min(jj, cnt - 1);
+#pragma unroll
+                    for (int i = 0; i < X::kLoads; ++i) rowV[i] = min(16 * tile + X::RPL * i + lane / X::LPR, cnt - 1);
                 } else {
-                    x = a.tok_idx[(int64_t)bh * a.idx_stride + j0 + min(jj, cnt - 1)];
+                    int32_t x, base = 0;                              // x: row of the position this lane looked up, the tile's from lane `base` on
+                    if constexpr (kSel) {
+                        // the wave fills its tile's 64-position piece in registers: the last bucket start at or before each position
+                        base = 16 * (tile & 3);
+                        const int32_t v = sm_row[(tile >> 2) * kWave + lane];
+                        const int32_t hp = (int32_t)wave_scan_max_u32(v >= 0 ? (uint32_t)lane + 1u : 0u) - 1;   // -1: none
+                        const int32_t start = __shfl(v, max(hp, 0));
+                        x = hp >= 0 ? start + (lane - hp) : -1;
+                        const int32_t pos = (tile >> 2) * kWave + lane;
+                        if ((tile & 3) == 0 && a.tok_idx_out && j0 + pos < n) a.tok_idx_out[(int64_t)bh * a.idx_stride + j0 + pos] = x;
+                    } else {
+                        x = a.tok_idx[(int64_t)bh * a.idx_stride + j0 + min(jj, cnt - 1)];
+                    }
+                    const bool in = x >= 0 && x < sq.n_tok_ctx;
+                    const unsigned long long ok = __ballot(in) >> base;   // bit t < 16: token t of the tile lies in the sequence
+                    liveK = liveK && ((ok >> t16) & 1u);
+                    x = min(max(x, 0), max(sq.n_tok_ctx - 1, 0));
+                    const int last = base + min(cnt - 1 - 16 * tile, 15);     // (negative for a tile past the end: clamped below)
+                    rowK = __shfl(x, max(min(base + t16, last), 0));
+#pragma unroll
+                    for (int i = 0; i < X::kLoads; ++i) rowV[i] = __shfl(x, max(min(base + X::RPL * i + lane / X::LPR, last), 0));
                 }
-                const bool in = x >= 0 && x < sq.n_tok_ctx;
-                const unsigned long long ok = __ballot(in) >> base;   // bit t < 16: token t of the tile lies in the sequence
-                liveK = liveK && ((ok >> t16) & 1u);
-                x = min(max(x, 0), max(sq.n_tok_ctx - 1, 0));
-                const int last = base + min(cnt - 1 - 16 * w, 15);    // (negative for a wave past the end: clamped below)
-                rowK = __shfl(x, max(min(base + t16, last), 0));
 #pragma unroll
-                for (int i = 0; i < X::kLoads; ++i) rowV[i] = __shfl(x, max(min(base + X::RPL * i + lane / X::LPR, last), 0));
+                for (int s2 = 0; s2 < X::kPieces; ++s2) kA[ps][s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
+#pragma unroll
+                for (int i = 0; i < X::kLoads; ++i) vR[ps][i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
+                vm[ps] = __ballot(liveK);
             }
-            uint4 kA[X::kPieces], vR[X::kLoads];
-#pragma unroll
-            for (int s2 = 0; s2 < X::kPieces; ++s2) kA[s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
-#pragma unroll
-            for (int i = 0; i < X::kLoads; ++i) vR[i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
-            const unsigned long long vm = __ballot(liveK);            // bit t (t < 16): token t of the tile is real
 #pragma unroll
             for (int s2 = 0; s2 < X::kPieces; ++s2)
                 if (t16 >= G) qB[s2] = make_uint4(0, 0, 0, 0);
             SKV_T(5);
-            const f32x4_t acc = X::logits(kA, [&](int s2) { return qB[s2]; });
-            float p[4], mw = -INFINITY;
+            float p[kPasses][4], mw = -INFINITY;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                p[j] = ((vm >> (4 * qd + j)) & 1ull) ? acc[j] * scale : -INFINITY;
-                mw = fmaxf(mw, p[j]);
+            for (int ps = 0; ps < kPasses; ++ps) {
+                const f32x4_t acc = X::logits(kA[ps], [&](int s2) { return qB[s2]; });
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    p[ps][j] = ((vm[ps] >> (4 * qd + j)) & 1ull) ? acc[j] * scale : -INFINITY;
+                    mw = fmaxf(mw, p[ps][j]);
+                }
             }
             mw = max_quads(mw);
-            // the tile's value rows go to LDS (rows of masked tokens as zeros)
-#pragma unroll
-            for (int i = 0; i < X::kLoads; ++i) {
-                const int row = X::RPL * i + lane / X::LPR;
-                *reinterpret_cast<uint4*>(sm_v + X::place(row, lane % X::LPR)) = ((vm >> row) & 1ull) ? vR[i] : make_uint4(0, 0, 0, 0);
-            }
-            SKV_T(6);
-            float lw = 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                p[j] = mw > -INFINITY ? exp2_neg(p[j] - mw) : 0.f;    // masked: exp2(-inf) = 0
-                lw += X::weight(p[j]);
-            }
-            lw = sum_quads(lw);
-            if (qd == 0) { sm_wmax[t16][w] = mw; sm_wsum[t16][w] = lw; }
             f32x4_t o[kHeadDim / 16];
 #pragma unroll
             for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            wave_lds_sync();                                          // the tile is the wave's own: order only
-            X::output(p, sm_v, lane, o);
-            wave_lds_sync();
+            float lw = 0.f;
+#pragma unroll
+            for (int ps = 0; ps < kPasses; ++ps) {
+                // the tile's value rows go to LDS (rows of masked tokens as zeros)
+#pragma unroll
+                for (int i = 0; i < X::kLoads; ++i) {
+                    const int row = X::RPL * i + lane / X::LPR;
+                    *reinterpret_cast<uint4*>(sm_v + X::place(row, lane % X::LPR)) = ((vm[ps] >> row) & 1ull) ? vR[ps][i] : make_uint4(0, 0, 0, 0);
+                }
+                SKV_T(6);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    p[ps][j] = mw > -INFINITY ? exp2_neg(p[ps][j] - mw) : 0.f;    // masked: exp2(-inf) = 0
+                    lw += X::weight(p[ps][j]);
+                }
+                wave_lds_sync();                                      // the tile is the wave's own: order only
+                X::output(p[ps], sm_v, lane, o);
+                wave_lds_sync();
+            }
+            lw = sum_quads(lw);
+            if (qd == 0) { sm_wmax[t16][w] = mw; sm_wsum[t16][w] = lw; }
             leave_sums<G>(sm_v, o);
         }
         __syncthreads();
@@ -2118,19 +2129,29 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     int lg = 0;
     while ((pairs << (lg + 1)) <= max_blocks) ++lg;
     const int parts = 1 << lg;
+    const int sv_bytes = c->d.semvec_dtype == SKV_BF16 ? kTableBf16 : c->d.semvec_dtype == SKV_FP8_E4M3 ? kTableE4m3 : kTableF32;
     // Attention blocks of 64 tokens, or of 128 or 256 when a pair has too few blocks: the K/V rows of a block pass its compute unit's
     // 64 bytes a cycle and its four SIMDs, one 16-token tile each.  One sequence, us per layer in 128- / 64-token blocks: bf16
     // budget 512: 10.9 / 10.0, 1000: 11.5 / 10.8, 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0.
     int chunk = kAttChunk;
     if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkMid;
     if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkWide;
+    // 512 tokens, bf16 only, where at least three quarters of the blocks attend and the mean-key rows take at most half the bytes of the
+    // retrieved ones: every attending block waits for all the scores of its pair, and the two-launch form spreads the rows over all compute
+    // units.  Us per 16 layers, two launches / one, 32 query heads: 8 sequences, budget 2048, rows 0.2 of the bytes: 410 / 374;
+    // 6 sequences, budget 1500, 0.2: 350 / 329, 0.3: 349 / 337, 0.6: 369 / 368; past the line: 8 sequences, budget 1100, 0.8: 414 / 450;
+    // 4 sequences, budget 2500, five blocks of eight: 390 / 396.
+    if (c->d.kv_dtype == SKV_BF16 && (c->budget_cap + chunk - 1) / chunk > parts) {
+        const int wide = 2 * kAttChunkWide, n = (c->budget_cap + wide - 1) / wide;
+        if (4 * n >= 3 * parts && (int64_t)v.S_total * sv_bytes <= (int64_t)v.B * c->budget_cap * 2) chunk = wide;
+    }
     const int att_parts = (c->budget_cap + chunk - 1) / chunk;
     if (att_parts > parts || c->G > 2 * parts) return hipSuccess;                // attention blocks or mergers do not fit
     AttArgs a = att_common(c, q_attn, K_layer, V_layer, v, out, lse);
     a.sent_off = sent_off; a.sent_len = sent_len;
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
     a.q_score = (const char*)q_score; a.semvec = (const char*)semvec_layer;
-    a.sv_bytes = c->d.semvec_dtype == SKV_BF16 ? kTableBf16 : c->d.semvec_dtype == SKV_FP8_E4M3 ? kTableE4m3 : kTableF32;
+    a.sv_bytes = sv_bytes;
     // Up to four blocks merge a head, 32 dims each, so that a thread has one word of a partial row to wait for instead of four (one sequence,
     // budget 2048, per layer: 12.8 -> 12.55 us, fp32 14.9 -> 14.5), as long as they all attend themselves: a block that runs the
     // selection only to merge costs more than it saves (budget 512, 8 query heads per KV head: 10.5 -> 12.0 with 32 of them).
@@ -2142,6 +2163,7 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     a.lg_parts = lg; a.lg_merge = lg_merge; a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
     a.step_part = c->step_part; a.wait_limit = c->wait_limit;
     a.err_dev = c->err_dev; a.err_host = c->err_host_dev;
+    if (chunk == 2 * kAttChunkWide) return launch_step_g<2, 2 * kAttChunkWide>(c, a, pairs * parts, launched);
     if (chunk == kAttChunkWide)
         return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunkWide>(c, a, pairs * parts, launched)
                                          : launch_step_g<4, kAttChunkWide>(c, a, pairs * parts, launched);

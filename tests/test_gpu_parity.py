@@ -497,6 +497,14 @@ def test_fused_single_launch_two_heads_per_merging_block(U, oracle32, B, budget,
     _fused_case(U, oracle32, wl, seed=35, layers=[0])
 
 
+@pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (5, 1281, 8), (8, 1297, 64), (7, 2048, 32), (2, 8192, 16), (4, 3073, 64)])
+def test_fused_single_launch_two_tiles_per_wave(U, oracle32, B, budget, Hq):
+    """bf16 blocks of 512 tokens, a wave's second tile 256 tokens behind its first: a last block of one token, of 257 (one token in the
+    second tiles) and of 273, full blocks, contexts shorter than the budget."""
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(900, 4500), budgets=(budget,), dtype="bf16")
+    _fused_case(U, oracle32, wl, seed=36, layers=[0])
+
+
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
     """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20), a last tile of one token and of sixteen, a
