@@ -13,11 +13,15 @@ namespace skv {
 // Importance.  For one layer and KV head h the window's R = G*N query rows (row = g*N + n: query head
 // h*G+g, window token n, contiguous in q_obs) meet all T keys on v_mfma_f32_32x32x16_bf16.  fp32 inputs are split
 // exactly into three bf16 terms -- see Frag -- so that the products keep fp32 accuracy.
-//   pass 1 (stats):   per row, max and sum of exp2 over the keys visible to it (positions <= Tp + n), per block
-//                     of keys; the block of the (layer, head) that arrives last combines the partials per row;
-//   pass 2 (colsum):  per KV head, the column sums of exp2(s - m_row) / l_row over the head's rows, for the Tp
+//   pass 1 (stats):   per row, a whole reference r near the largest logit s (log2 units) and the sum of exp2(s - r) over the
+//                     keys visible to it (positions <= Tp + n), per block of keys; the block of the (layer, head) that
+//                     arrives last combines the partials per row;
+//   pass 2 (colsum):  per KV head, the column sums of exp2(s - r_row) * (1 / sum_row) over the head's rows, for the Tp
 //                     prefix keys; the head whose block arrives last for a range of keys adds the heads in ascending
 //                     order (deterministic).
+// References are whole numbers so that sums change from one to another by exact powers of two, and reference and sum stay apart up
+// to the last multiplication: s - r is then rounded once, at the size of the result.  (Their logarithm in one float, r + log2(sum), has only the
+// fraction bits that the logit's magnitude leaves: from exact logits of 166 to 423, a relative error of 1e-5 instead of 4.6e-7.)
 // Each pass covers all layers in one launch (grid z = layer).  Its one read of the keys takes 300 us for 32 layers x 8 heads x 32768 keys (a
 // second read within reach of the memory-side cache is no faster, 7.1 TB/s either way), its matrix instructions and
 // exp2 take 260-310 us by themselves at the clock (1.6-2.1 GHz) that the power limit leaves, and the two overlap: 350-400 us a pass.
@@ -147,9 +151,6 @@ struct KeyRing {
             const int r = row + kRows * i;
             off[i] = (uint32_t)(r * kRowBytes + 16 * ((lane % kPieces) ^ (r & 15)));
         }
-        restart();
-    }
-    __device__ __forceinline__ void restart() {
         slot = 0;
         ahead = P::NB - 1;
         for (int s = 0; s < P::NB - 1 && s < n; ++s) request(s, s);
@@ -205,12 +206,20 @@ __device__ __forceinline__ void tile_logits(f32x16& acc, const Frag<EB> (&qf)[8]
 }
 __device__ __forceinline__ int tile_pos(int i, int g) { return 8 * (i >> 2) + 4 * g + (i & 3); }
 
-// pass 1.  grid (chunks of kpb keys, Hkv, L); part [L][Hkv][chunks][rows] (reference in log2 units, sum); rowstat
-// [L][Hkv][rows] the logarithm to base 2 of the sum over all keys (+infinity for rows >= R).
+// The waves that the ring leaves room for, no more: with fewer registers the compiler reads one key fragment at a time.
+#define SKV_IMP_WAVES __attribute__((amdgpu_waves_per_eu(Imp<EB, RT>::kWavesPerSimd, Imp<EB, RT>::kWavesPerSimd)))
+
+// sum * 2^(from - to) for whole from <= to (from == -infinity: a sum of nothing, or of NaN)
+__device__ __forceinline__ float move_reference(float sum, float from, float to) {
+    return from > -INFINITY ? ldexpf(sum, (int)fmaxf(from - to, -512.f)) : 0.f * sum;
+}
+
+// pass 1.  grid (chunks of kpb keys, Hkv, L); part [L][Hkv][chunks][rows] (reference, sum); rowstat [L][Hkv][rows] (reference,
+// 1 / sum) over all keys with 1 <= sum < 2 ((+infinity, 0) for rows >= R).
 template <int EB, int RT>
-__global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSimd)) void importance_stats_kernel(
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_stats_kernel(
     const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb, float2* part,
-    float* __restrict__ rowstat, unsigned int* arrive) {
+    float2* __restrict__ rowstat, unsigned int* arrive) {
     using P = Imp<EB, RT>;
     constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
@@ -230,72 +239,91 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
     load_queries<EB>(qf, q_obs + lh * R * kRowBytes, R, 32 * rs);
     const float scale = kLog2e * rsqrtf((float)kHeadDim);
 
-    // Sums are kept per LANE (a lane sees half of the keys of every tile of its row) relative to a reference in raw logit
-    // units; the two lanes of a row meet once, after the last stage.  While every key of a stage is visible to every row, the
-    // reference stays what it is after the row's first tile: any reference gives the same sum, and a running maximum
-    // would take a third of the instructions.  Should a sum leave the range of a float that way (logits 2^100 apart), the block
-    // starts over with a running maximum, which the stages at the end of the prompt take in any case.
-    float m_run, l_run;
-    auto add_tile = [&](const f32x16& x) {
-        const float ms = m_run * scale;
+    // Sums are kept per LANE (a lane sees half of the keys of every tile of its row); the two lanes of a row meet once, after the last
+    // stage.  While every key of a stage is visible to every row, the reference stays what it is until a tile's sum reaches
+    // kFar: any reference near the largest logit gives the same sum, and a running maximum would take a third of the
+    // instructions.  It is set kAbove over the largest logit, so that a later one seldom is too far above (a tile's keys are mostly of one
+    // sentence and have like logits: with 0 and 32 for the two, every third tile of a wave had a row to move, 418 us
+    // instead of 374 for the pass); both together keep the arguments of exp2 that matter within -8 .. 8.
+    constexpr float kFar = 256.f, kAbove = 4.f;
+    float ref = -INFINITY, l_run = 0.f;
+    auto add_relative = [&](const f32x16& x, float m) {                  // reference: the largest logit so far, `m` among them
+        const float to = fmaxf(ref, rintf(m * scale) + kAbove), base = to > -INFINITY ? to : 0.f;   // (nothing visible yet: every term is exp2(-inf) = 0)
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += exp2_neg(fmaf(x[i], scale, -base));
+        l_run = move_reference(l_run, ref, base) + sum;
+        ref = to;
+    };
+    auto sum_tile = [&](const f32x16& x) {
         float sum[2] = {0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sum[i & 1] += exp2_neg(x[i] * scale - ms);
-        l_run += sum[0] + sum[1];
+        for (int i = 0; i < 16; ++i) sum[i & 1] += exp2_neg(fmaf(x[i], scale, -ref));
+        float both = sum[0] + sum[1];
+        asm volatile("" : "+v"(both));                                   // here, next to the matrix instructions, not behind the next barrier
+        return both;
     };
-    auto add_tile_exact = [&](f32x16& x, int32_t key0) {
+    auto settle = [&](const f32x16& x, float sum) {                      // adds sum_tile's result, if need be to another reference
+        if (sum < kFar) {
+            l_run += sum;
+        } else {                                                         // the row's first tile, and rarely a later one
+            float m = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m = fmaxf(m, x[i]);
+            add_relative(x, m);
+        }
+    };
+    auto add_tile_masked = [&](f32x16& x, int32_t key0) {
         const int32_t limit = min(Tp + (32 * rs + r) % N, T - 1);        // last position visible to this lane's row
-        float mt = m_run;
+        float m = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             if (key0 + tile_pos(i, g) > limit) x[i] = -INFINITY;
-            mt = fmaxf(mt, x[i]);
+            m = fmaxf(m, x[i]);
         }
-        const float ms = mt > -INFINITY ? mt * scale : 0.f;              // (nothing visible yet: every term is exp2(-inf) = 0)
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sum += exp2_neg(x[i] * scale - ms);
-        l_run = l_run * exp2_neg(m_run * scale - ms) + sum;
-        m_run = mt;
+        add_relative(x, m);
     };
     const int row0 = 32 * ks + r;                                        // this lane's key row in a stage
-    int n_open = min(max((Tp - base0) / P::kStageKeys, 0), n);           // stages whose keys are all visible to all rows
-    for (;;) {
-        m_run = -INFINITY;
-        l_run = 0.f;
-        if (n_open > 0) {
-            // the sums of a tile are taken while the matrix cores work on the next one
-            f32x16 acc[2];
-            tile_logits<EB, true>(acc[0], qf, keys.next(0), row0, g);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) m_run = fmaxf(m_run, acc[0][i]);
-            for (int s = 1; s < n_open; s += 2) {
-                tile_logits<EB, true>(acc[1], qf, keys.next(s), row0, g);
-                add_tile(acc[0]);
-                if (s + 1 < n_open) {
-                    tile_logits<EB, true>(acc[0], qf, keys.next(s + 1), row0, g);
-                    add_tile(acc[1]);
-                }
-            }
-            if (n_open & 1) add_tile(acc[0]);
-            else add_tile(acc[1]);
+    const int n_open = min(max((Tp - base0) / P::kStageKeys, 0), n);     // stages whose keys are all visible to all rows
+    if (n_open > 0) {
+        // the sums of a tile are taken while the matrix cores work on the next one, and settled a barrier later (a branch in between
+        // would keep the two apart)
+        f32x16 acc[2];
+        float sum = 0.f;
+        tile_logits<EB, true>(acc[0], qf, keys.next(0), row0, g);
+        int s = 1;
+        for (; s + 1 < n_open; s += 2) {
+            const char* stage = keys.next(s);
+            settle(acc[1], sum);
+            tile_logits<EB, true>(acc[1], qf, stage, row0, g);
+            sum = sum_tile(acc[0]);
+            stage = keys.next(s + 1);
+            settle(acc[0], sum);
+            tile_logits<EB, true>(acc[0], qf, stage, row0, g);
+            sum = sum_tile(acc[1]);
         }
+        if (s < n_open) {
+            const char* stage = keys.next(s);
+            settle(acc[1], sum);
+            tile_logits<EB, true>(acc[1], qf, stage, row0, g);
+            settle(acc[0], sum_tile(acc[0]));
+            sum = sum_tile(acc[1]);
+        }
+        settle(acc[1], sum);
+        if (n_open & 1) settle(acc[0], sum_tile(acc[0]));
+    }
 #pragma unroll 1
-        for (int s = n_open; s < n; ++s) {
-            f32x16 x;
-            tile_logits<EB, true>(x, qf, keys.next(s), row0, g);
-            add_tile_exact(x, base0 + s * P::kStageKeys + 32 * ks);
-        }
-        if (n_open == 0 || !__syncthreads_or(!(l_run < 1e30f))) break;
-        n_open = 0;
-        keys.restart();
+    for (int s = n_open; s < n; ++s) {
+        f32x16 x;
+        tile_logits<EB, true>(x, qf, keys.next(s), row0, g);
+        add_tile_masked(x, base0 + s * P::kStageKeys + 32 * ks);
     }
     // the two lanes of a row, then the block's waves
     {
-        const float m = fmaxf(m_run, __shfl_xor(m_run, 32));
-        float l = m_run > -INFINITY ? l_run * exp2f((m_run - m) * scale) : 0.f;
+        const float m = fmaxf(ref, __shfl_xor(ref, 32));
+        float l = move_reference(l_run, ref, m);
         l += __shfl_xor(l, 32);
-        if (g == 0) { sm_m[ks][32 * rs + r] = m * scale; sm_l[ks][32 * rs + r] = l; }
+        if (g == 0) { sm_m[ks][32 * rs + r] = m; sm_l[ks][32 * rs + r] = l; }
     }
     __syncthreads();
     if (tid < kRows) {
@@ -304,13 +332,7 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
         for (int k = 0; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][tid]);
         float l = 0.f;
 #pragma unroll
-        for (int k = 0; k < P::KSP; ++k)
-            if (sm_m[k][tid] > -INFINITY) l += sm_l[k][tid] * exp2f(sm_m[k][tid] - m);
-        if (l > 0.f) {                                                   // 1 <= l < 2, whatever the reference was
-            const int e = ilogbf(l);
-            l = ldexpf(l, -e);
-            m += (float)e;
-        }
+        for (int k = 0; k < P::KSP; ++k) l += move_reference(sm_l[k][tid], sm_m[k][tid], m);
         st_agent64(part + (lh * nchunks + chunk) * kRows + tid, m, l);
     }
     // ---- the last block of the (layer, head): combined statistics ------------------------------------------------
@@ -329,11 +351,9 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const float pm = c + u * kGroups < nchunks ? lo_f(v[u]) : -INFINITY;
-            if (pm > -INFINITY) {
-                const float nm = fmaxf(M, pm);
-                L = L * exp2_neg(M - nm) + hi_f(v[u]) * exp2_neg(pm - nm);
-                M = nm;
-            }
+            const float nm = fmaxf(M, pm);
+            L = move_reference(L, M, nm) + move_reference(hi_f(v[u]), pm, nm);
+            M = nm;
         }
     }
     float* sm_g = reinterpret_cast<float*>(sm_ring);                     // the ring is no longer read
@@ -343,14 +363,13 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
     if (tid < kRows) {
 #pragma unroll
         for (int g = 1; g < kGroups; ++g) {
-            const float m2 = sm_g[g * kRows + row], l2 = sm_g[P::kThreads + g * kRows + row];
-            if (m2 > -INFINITY) {
-                const float nm = fmaxf(M, m2);
-                L = L * exp2_neg(M - nm) + l2 * exp2_neg(m2 - nm);
-                M = nm;
-            }
+            const float m2 = sm_g[g * kRows + row], l2 = sm_g[P::kThreads + g * kRows + row], nm = fmaxf(M, m2);
+            L = move_reference(L, M, nm) + move_reference(l2, m2, nm);
+            M = nm;
         }
-        rowstat[lh * kRows + row] = row < R && L > 0.f ? M + log2f(L) : INFINITY;
+        const bool adds = row < R && L > 0.f;
+        const int e = adds ? ilogbf(L) : 0;
+        rowstat[lh * kRows + row] = adds ? make_float2(M + (float)e, 1.f / ldexpf(L, -e)) : make_float2(INFINITY, 0.f);
     }
     if (tid == 0) __hip_atomic_store(&arrive[lh], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
 }
@@ -358,9 +377,9 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
 // pass 2.  grid (chunks of kpb of the Tp prefix keys, Hkv, L); alpha_h [L][Hkv][Tp], alpha [L][Tp].  Here the queries are the A operand: a
 // lane gets half of the rows of one key, and the sum over the rows is in-lane but for one exchange.
 template <int EB, int RT>
-__global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSimd)) void importance_colsum_kernel(
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_colsum_kernel(
     const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb,
-    const float* __restrict__ rowstat, float* alpha_h, float* __restrict__ alpha, unsigned int* arrive) {
+    const float2* __restrict__ rowstat, float* alpha_h, float* __restrict__ alpha, unsigned int* arrive) {
     using P = Imp<EB, RT>;
     constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
@@ -378,9 +397,9 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
     KeyRing<EB, RT> keys(Kh, sm_ring, base0, Tp - 1, n);
     Frag<EB> qf[8];
     load_queries<EB>(qf, q_obs + lh * R * kRowBytes, R, 32 * rs);
-    float c[16];                                                         // this lane's rows of the tile
+    float2 st[16];                                                       // this lane's rows of the tile
 #pragma unroll
-    for (int i = 0; i < 16; ++i) c[i] = rowstat[lh * kRows + 32 * rs + tile_pos(i, g)];
+    for (int i = 0; i < 16; ++i) st[i] = rowstat[lh * kRows + 32 * rs + tile_pos(i, g)];
     const float scale = kLog2e * rsqrtf((float)kHeadDim);
     const int row0 = 32 * ks + r;                                        // this lane's key in a stage
     float* dst = alpha_h + lh * Tp + base0;
@@ -389,7 +408,7 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads), (Imp<EB, RT>::kWavesPerSim
     auto sum_tile = [&](const f32x16& x, int s) {
         float p[2] = {0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 16; ++i) p[i & 1] += exp2_neg(x[i] * scale - c[i]);      // prefix keys: at most 1
+        for (int i = 0; i < 16; ++i) p[i & 1] = fmaf(exp2_neg(fmaf(x[i], scale, -st[i].x)), st[i].y, p[i & 1]);      // prefix keys: at most 1
         const float v = sum_halves(p[0] + p[1]);
         if constexpr (P::RS == 1) {
             if (g == 0 && s * P::kStageKeys + row0 < cnt) st_agent(dst + s * P::kStageKeys + row0, v);
@@ -466,7 +485,7 @@ static int importance_keys_per_block(const Ctx* c, int32_t T) {
 
 template <int EB, int RT>
 static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
-                                       float* rowstat, float* alpha_h) {
+                                       float2* rowstat, float* alpha_h) {
     using P = Imp<EB, RT>;
     const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, Tp = T - N, kpb = importance_keys_per_block(c, T);
     constexpr size_t lds = P::kRingBytes;
@@ -489,7 +508,7 @@ static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_
 
 template <int EB>
 static hipError_t launch_importance_eb(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
-                                       float* rowstat, float* alpha_h) {
+                                       float2* rowstat, float* alpha_h) {
     const int R = c->G * N;
     if (R <= 32) return launch_importance_rt<EB, 1>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
     if (R <= 64) return launch_importance_rt<EB, 2>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
@@ -510,18 +529,18 @@ int64_t importance_counters(const skv_desc& d) {
     return (int64_t)d.n_layers * (d.n_kv_heads + (d.max_tokens + kImpUnit - 1) / kImpUnit);
 }
 
-// work = part [L][Hkv][chunks][rows][2] | rowstat [L][Hkv][rows] | alpha_h [L][Hkv][Tp], floats
+// work = part [L][Hkv][chunks][rows][2] | rowstat [L][Hkv][rows][2] | alpha_h [L][Hkv][Tp], floats
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N) {
     const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
-    return (LH * importance_chunks(c, T) * rows * 2 + LH * rows + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
+    return (LH * importance_chunks(c, T) * rows * 2 + LH * rows * 2 + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
 }
 
 // Two launches cover all layers: the rows' statistics, and the column sums with them.
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work) {
     const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
     float2* part = (float2*)work;
-    float* rowstat = (float*)(part + LH * importance_chunks(c, T) * rows);
-    float* alpha_h = rowstat + LH * rows;
+    float2* rowstat = part + LH * importance_chunks(c, T) * rows;
+    float* alpha_h = (float*)(rowstat + LH * rows);
     return c->d.kv_dtype == SKV_BF16
                ? launch_importance_eb<2>(c, (const char*)q_obs, (const char*)K_pool, T, N, alpha, part, rowstat, alpha_h)
                : launch_importance_eb<4>(c, (const char*)q_obs, (const char*)K_pool, T, N, alpha, part, rowstat, alpha_h);

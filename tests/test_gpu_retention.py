@@ -7,6 +7,8 @@ the oracle's rule applied to the GPU's own importance bit for bit, and may diffe
 in tokens whose oracle importance is within 5e-4 relative of the cut ("documented tie"); offsets, lengths and compacted
 rows bit-exact; decode on the retained pool to the usual attention tolerance.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -72,6 +74,42 @@ def test_token_importance_with_logits_far_apart(U, oracle32, dtype, Hq, N, T):
     alpha = _gpu_importance(U, U.make_ctx(wl, T, len(lens), 16), q_obs, K, T, N).cpu().numpy()
     ref = oracle32.token_importance(U.np_of(q_obs[0]), U.np_of(K[0]))
     assert np.all(np.abs(alpha[0] - ref) <= 1e-3 * ref + 1e-6 * ref.max())     # exponents of several hundred carry fewer fraction bits
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hq,N", [(8, 1), (8, 32), (16, 32), (32, 32), (64, 32)])          # 1 row, then 32 to 256 rows per KV head
+def test_token_importance_precision_at_large_logits(U, dtype, Hq, N):
+    """Logits that both sides form without rounding (two products of small whole numbers), 166 to 423 above zero in log2 units, within
+    6 of each other: what is left is the softmax's own arithmetic, held against float64.  Bound, relative: the argument of exp2,
+    at most 2^3, is rounded once (2^-22 * ln 2 = 1.7e-7), exp2 and 1 / sum to a unit each (1.8e-7), log2(e) / sqrt(D) is a
+    float (2^-24 * 6 * ln 2 = 2.5e-7 over the spread), sums add a few 2^-24 (2e-7): below 1e-6."""
+    T, H, D = 2900, 8, 128
+    bases = [100, 100.5, 101, 111.5, 213, 255]                                              # a layer each
+    L = len(bases)
+    rng = np.random.default_rng(5)
+    K = torch.zeros(L, H, T, D, dtype=torch.float32)
+    v = rng.integers(0, 48, size=(L, H, T))
+    K[..., 1] = torch.as_tensor(v, dtype=torch.float32)
+    K[..., 0] = 13.0
+    q = torch.zeros(L, Hq, N, D, dtype=torch.float32)
+    q[..., 1] = 1.0
+    for l, b in enumerate(bases):
+        q[l, ..., 0] = b
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    assert torch.equal(q.to(tt).float(), q) and torch.equal(K.to(tt).float(), K)
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype=dtype)
+    _say("importance precision", dtype, Hq, N)
+    got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q.to(tt).to(U.DEV), K.to(tt).to(U.DEV), T, N).cpu().numpy().astype(np.float64)
+    worst = 0.0
+    for l in range(L):
+        want = np.zeros(T - N)
+        for h in range(H):
+            e = np.exp((v[l, h] - 47) / math.sqrt(D))                                       # the common part drops out
+            z = np.cumsum(e)[T - N:]                                                        # window query n sees the keys 0 .. Tp + n
+            want += (Hq // H) * e[:T - N] * (1.0 / z).sum()
+        worst = max(worst, float(np.abs(got[l] / want - 1).max()))
+    _say(f"  largest relative error {worst:.2e}")
+    assert worst <= 1e-6
 
 
 FULL_IMP_CASES = [("bf16", 32, 8, 32, 32768), ("f32", 32, 8, 32, 32768), ("bf16", 8, 2, 32, 40100), ("f32", 4, 1, 32, 70001)]
