@@ -218,7 +218,8 @@ int skv_gather(skv_ctx* ctx, int32_t layer, const void* K_pool, const void* V_po
                const int32_t* tok_idx, const int32_t* n_tok, int32_t budget, void* K_sel, void* V_sel);
 
 /* (5) Eq. 3: out[j] = softmax(q_attn[j] K_sel[h]^T / sqrt(D)) V_sel[h] over the first n_tok[h] rows,
- * h = j / G; lse[j] = log sum_i exp(logit_i) (natural log).  n_tok[h] == 0 gives out = 0 and lse = -inf.
+ * h = j / G; lse[j] = log sum_i exp(logit_i) (natural log).  n_tok[h] == 0 gives out = 0 and lse = -inf.  A NaN among a
+ * head's logits (or an infinite logit) gives NaN in its out and lse, here, in skv_decode_step and through skv_merge_lse.
  * Arithmetic: logits, maxima, normalisers and all sums are fp32.  With fp32 K/V the softmax weights stay fp32.  With
  * bf16 K/V the products run on the matrix cores: the weights exp(logit - max) are rounded to bf16 (nearest even)
  * before P.V, and the normaliser sums those rounded weights, so out is exactly the weighted mean the rounded weights

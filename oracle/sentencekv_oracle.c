@@ -431,8 +431,8 @@ void skvo_merge_lse(const float* out_a, const float* lse_a, const float* out_b, 
                     int32_t D, float* out, float* lse) {
     for (int32_t j = 0; j < n_heads; ++j) {
         real la = (real)lse_a[j], lb = (real)lse_b[j];
-        real m = la > lb ? la : lb;
-        if (!(m > -INFINITY)) {                       /* both sides empty */
+        real m = la != la || lb != lb ? (real)NAN : la > lb ? la : lb;
+        if (m == -INFINITY) {                         /* both sides empty (NaN is not an empty side) */
             for (int32_t d = 0; d < D; ++d) out[(int64_t)j * D + d] = 0.0f;
             lse[j] = -INFINITY;
             continue;

@@ -957,6 +957,7 @@ __device__ __forceinline__ float sum_quads(float x) {
 //    are read from a wave-private LDS copy of the 16 value rows, laid out so that the four token groups of a read fall into
 //    different banks (bf16: 16 bytes between rows; fp32: 64-byte groups exchanged, no gaps, for rows that come by load_lds_stream).
 //  * bf16 weights are rounded to bf16 (nearest even) and the normaliser sums the rounded weights; fp32 ones are used as they are.
+//  * A NaN among a head's live logits makes its normaliser NaN, and with it out and lse, through every sum and merge below.
 // fp32 through the vector pipe (rows over lanes, sums of the logits over 32 lanes by exchanges) took 3.7 us from the loads to
 // the logits of 128 tokens and 1.7 to the partial result, budget 512, 4 heads; see launch_step for what it takes now.
 template <int EB> struct Tile {
@@ -994,7 +995,7 @@ template <int EB> struct Tile {
         if constexpr (EB == 2) {
             uint32_t u = __float_as_uint(p);
             u += 0x7fffu + ((u >> 16) & 1u);
-            p = __uint_as_float(u & 0xffff0000u);
+            p = p == p ? __uint_as_float(u & 0xffff0000u) : p;            // (the carry could leave a NaN's bits as a number)
         }
         return p;
     }
@@ -1077,6 +1078,7 @@ __device__ __forceinline__ void block_sums(const char* tiles, int stride, const 
             o += c * reinterpret_cast<const float*>(tiles + k * stride)[d * G + g];
             lb += c * lw[k];
         }
+        if (lb != lb) mb = 0.f;                                       // NaN, perhaps with no other logit: merges pass over a max of -infinity
         put(g, d, o, mb, lb);
     }
 }
@@ -1413,6 +1415,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 }
             }
             mw = max_quads(mw);
+            const float ref = mw > -INFINITY ? mw : 0.f;              // (no live token, or logits of NaN only: those weights are NaN)
             f32x4_t o[kHeadDim / 16];
 #pragma unroll
             for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1428,7 +1431,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 SKV_T(6);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    p[ps][j] = mw > -INFINITY ? exp2_neg(p[ps][j] - mw) : 0.f;    // masked: exp2(-inf) = 0
+                    p[ps][j] = exp2_neg(p[ps][j] - ref);              // masked: exp2(-inf) = 0
                     lw += X::weight(p[ps][j]);
                 }
                 wave_lds_sync();                                      // the tile is the wave's own: order only
@@ -1446,7 +1449,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 st_tagged(dst + d, sum, part_tag);
                 if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
             } else if (nsplit == 1) {                                 // the only block: its sums are the result
-                const bool empty = !(lb > 0.f);                       // every retrieved position was out of range
+                const bool empty = lb == 0.f;                       // every retrieved position was out of range
                 a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
                 if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
             } else {
@@ -1544,7 +1547,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
             if (first == 0) {                                             // the first of the column's threads
                 const int to = at_of(col);
-                const bool empty = !(Ls > 0.f);                           // every retrieved position was out of range
+                const bool empty = Ls == 0.f;                           // every retrieved position was out of range
                 float res = empty ? 0.f : os / Ls;
                 if (bad) res = __builtin_nanf("");                        // a wait of this launch ran out
                 a.out[qhead0 * kHeadDim + to] = res;
@@ -1628,7 +1631,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 L += c * t.w; o0 += c * t.x; o1 += c * t.y;
             }
         }
-        const bool empty = !(L > 0.f);                       // every retrieved position was out of range
+        const bool empty = L == 0.f;                       // every retrieved position was out of range
         const float inv = empty ? 0.f : 1.f / L;
         reinterpret_cast<float2*>(a.out + qhead0 * kHeadDim)[tid] = make_float2(o0 * inv, o1 * inv);
         if (a.lse && (tid % (kHeadDim / 2)) == 0)
@@ -1795,10 +1798,11 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
         }
         const float m_new = fmaxf(m_run, max_quads(mt));
         const float alpha = (m_new > -INFINITY) ? exp2_neg(m_run - m_new) : 1.f;   // m_run == -inf gives 0
+        const float ref = m_new > -INFINITY ? m_new : 0.f;        // (no live token yet, or logits of NaN only: those weights are NaN)
         float lw = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            p[j] = m_new > -INFINITY ? exp2_neg(p[j] - m_new) : 0.f;  // masked: exp2(-inf) = 0
+            p[j] = exp2_neg(p[j] - ref);                              // masked: exp2(-inf) = 0
             lw += X::weight(p[j]);
         }
         l_run = l_run * alpha + lw;
@@ -1838,7 +1842,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
     __syncthreads();
     block_sums<G, NW, true>(ss.v[0], sizeof(ss.v[0]), ss.wmax, ss.wsum, [&](int g, int d, float sum, float mb, float lb) {
         if (nsplit == 1) {                                        // the only block of this (sequence, head): no partials, no arrival, no merge
-            const bool empty = !(lb > 0.f);                       // every retrieved position was out of range
+            const bool empty = lb == 0.f;                       // every retrieved position was out of range
             a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
             if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
         } else {
@@ -1888,7 +1892,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
                 }
             }
         }
-        const bool empty = !(L > 0.f);                            // every retrieved position was out of range
+        const bool empty = L == 0.f;                            // every retrieved position was out of range
         const float inv = empty ? 0.f : 1.f / L;
         reinterpret_cast<float2*>(a.out + qhead0 * kHeadDim)[col] = make_float2(o0 * inv, o1 * inv);
         if (a.lse && (col % (kHeadDim / 2)) == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (M + log2f(L)) * kLn2;
@@ -2187,7 +2191,7 @@ __global__ __launch_bounds__(256) void merge_lse_kernel(const float* __restrict_
     const float m = fmaxf(la, lb);
     float2 r = make_float2(0.f, 0.f);
     float l = -INFINITY;
-    if (m > -INFINITY) {
+    if (m > -INFINITY || la != la || lb != lb) {                       // (NaN is not an empty side)
         const float za = expf(la - m), zb = expf(lb - m);              // an empty side has lse = -inf: weight 0
         const float inv = 1.f / (za + zb);
         const float2 a = reinterpret_cast<const float2*>(out_a)[i], b = reinterpret_cast<const float2*>(out_b)[i];

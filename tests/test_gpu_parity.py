@@ -703,6 +703,123 @@ def test_single_launch_can_be_turned_off(U, oracle32, B, dtype):
         assert torch.equal(a, b)
 
 
+# ----------------------------------------------------------------------------- values that are not finite
+
+def _same_as_oracle(got, ref, tol, what):
+    """NaN and infinities at the same places, finite values within the attention tolerance."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), what
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref)), what
+    fin = np.isfinite(ref)
+    assert not fin.any() or np.abs(got[fin] - ref[fin]).max() <= tol, what
+
+
+def _planted(kind, q, K, V, head, row):
+    """q [Hq][D], K, V [H][T][D] with one value made not finite: a query, a retrieved key (all of it, or one infinite element), a value."""
+    q, K, V = q.clone(), K.clone(), V.clone()
+    if kind == "query":
+        q[head * (q.shape[0] // K.shape[0]), 5] = float("nan")
+    elif kind == "all queries":
+        q[:] = float("nan")
+    elif kind == "key":
+        K[head, row] = float("nan")
+    elif kind == "infinite key":
+        K[head, row] = 0.0
+        K[head, row, 3] = float("inf")
+    else:
+        V[head, row, 7] = float("nan")
+    return q, K, V
+
+
+NOT_FINITE = ["query", "all queries", "key", "infinite key", "value"]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("budget", [17, 129, 257, 1025])
+def test_attend_carries_values_that_are_not_finite(U, oracle32, dtype, budget):
+    """The last of `budget` rows is alone in its 16-token tile, and from 257 rows on in its block: NaN there, as anywhere, is NaN in
+    the heads that see it, an infinite logit too."""
+    wl = gen.CFG0.scaled(dtype=dtype)
+    H, Hq, D = 8, 32, 128
+    g = torch.Generator().manual_seed(3)
+    q, K, V = (torch.randn(*s, generator=g).to(wl.torch_dtype) for s in ((Hq, D), (H, budget, D), (H, budget, D)))
+    n_tok = np.full(H, budget, dtype=np.int32)
+    n_tok[5:] = [0, 1, 16]
+    ctx = U.make_ctx(wl, 4096, 64, budget)
+    out, lse = torch.zeros(Hq, D, device=U.DEV), torch.zeros(Hq, device=U.DEV)
+    for kind in NOT_FINITE:
+        for row in (budget - 1, 3):
+            _say("attend, not finite:", dtype, budget, kind, "row", row)
+            qp, Kp, Vp = _planted(kind, q, K, V, 2, row)
+            ctx.attend(qp.to(U.DEV), Kp.to(U.DEV), Vp.to(U.DEV), U.i32(n_tok), budget, out, lse)
+            torch.cuda.synchronize()
+            out_ref, lse_ref = oracle32.attend(U.np_of(qp), U.np_of(Kp), U.np_of(Vp), n_tok)
+            _same_as_oracle(out.cpu().numpy(), out_ref, ATT_TOL[dtype], (kind, row))
+            _same_as_oracle(lse.cpu().numpy(), lse_ref, ATT_TOL[dtype], (kind, row))
+
+
+@pytest.mark.parametrize("B,dtype,Hq,budget,capacity", [
+    (1, "bf16", 32, 1025, 0), (1, "f32", 32, 513, 0), (1, "bf16", 64, 100, 0),          # one launch: 64-token blocks, mergers of two heads
+    (3, "f32", 8, 1025, 0), (8, "bf16", 32, 1025, 0),                                   # of 256 tokens, of 512 (two tiles a wave)
+    (9, "bf16", 16, 65, 0), (9, "f32", 32, 257, 0), (9, "bf16", 32, 513, 0),            # two launches: blocks of 64, 128, 256 tokens
+    (9, "bf16", 32, 1009, 0), (9, "f32", 64, 257, STREAM_CAPACITY), (20, "bf16", 8, 1281, 0)])    # streaming: 512, 1024, 2048
+def test_fused_step_carries_values_that_are_not_finite(U, oracle32, B, dtype, Hq, budget, capacity):
+    """Buckets of one token, so that every head retrieves `budget` of them: the last one is alone in its tile.  The scores come from
+    finite queries and keys; what attention then meets is planted in one KV head of the first sequence, the others keep their results."""
+    H, D, T = 8, 128, 1000 if budget <= 600 else 1500 if budget <= 1025 else 1700
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(T, T), budgets=(budget,), dtype=dtype, len_dist=("fixed", 1))
+    inp = gen.ragged_inputs(wl, seed=19, device=U.DEV, resident_layers=1)
+    T_total, S_total = int(inp.cu_tok[-1]), int(inp.cu_sent[-1])
+    cap = max(budget, capacity)
+    ctx = U.make_ctx(wl, T_total, S_total, cap, batch=B, sv_dtype="fp8")
+    sv = torch.zeros(1, H, S_total, D, dtype=torch.uint8, device=U.DEV)
+    ctx.build_semvec(inp.K, U.i32(gen.offsets_of(inp.sent_len)), S_total, sv)
+    d = [U.i32(x) for x in (inp.cu_tok, inp.cu_sent, inp.sent_off, inp.sent_len, inp.budget)]
+    out, lse = torch.zeros(B, Hq, D, device=U.DEV), torch.zeros(B, Hq, device=U.DEV)
+    tok_idx, n_tok = U.empty_i32(B, H, cap, fill=-1), U.empty_i32(B, H, fill=-1)
+
+    def step(q, K, V):
+        ctx.decode_step(0, B, inp.q[0], q, K, V, T_total, sv, S_total, *d, out, lse, tok_idx, n_tok)
+        torch.cuda.synchronize()
+        return out.cpu().numpy(), lse.cpu().numpy()
+
+    o_fin, l_fin = step(inp.q[0], inp.K, inp.V)
+    assert bool((n_tok == budget).all())
+    ti = tok_idx[0, :, :budget].cpu().numpy().copy()
+    nt = np.full(H, budget, dtype=np.int32)
+    for kind in NOT_FINITE:
+        for at in (budget - 1, 3):
+            _say("fused step, not finite:", B, dtype, Hq, budget, capacity, kind, "at", at)
+            q0, K, V = _planted(kind, inp.q[0, 0], inp.K[0], inp.V[0], 2, int(ti[2, at]))
+            q = inp.q[0].clone()
+            q[0] = q0
+            o, l = step(q, K[None], V[None])
+            assert np.array_equal(tok_idx[0, :, :budget].cpu().numpy(), ti)
+            pick = torch.as_tensor(ti, device=U.DEV, dtype=torch.long)[..., None].expand(-1, -1, D)
+            Ks, Vs = (U.np_of(torch.gather(X[:, :T], 1, pick)) for X in (K, V))
+            o_ref, l_ref = oracle32.attend(U.np_of(q0), Ks, Vs, nt)
+            _same_as_oracle(o[0], o_ref, ATT_TOL[dtype], (kind, at))
+            _same_as_oracle(l[0], l_ref, ATT_TOL[dtype], (kind, at))
+            assert np.abs(o[1:] - o_fin[1:]).max(initial=0.0) <= ATT_TOL[dtype] and np.abs(l[1:] - l_fin[1:]).max(initial=0.0) <= ATT_TOL[dtype]
+
+
+def test_merge_carries_nan(U, oracle32):
+    """NaN as a side's lse is not an empty side, whatever the other side is; an empty side's output is ignored all the same."""
+    nan, inf = float("nan"), float("inf")
+    la = np.array([nan, nan, nan, 0.5, -inf, -inf, 1.0, -inf], dtype=np.float32)
+    lb = np.array([0.5, -inf, nan, nan, nan, 2.0, -inf, -inf], dtype=np.float32)
+    rng = np.random.default_rng(2)
+    oa, ob = (rng.standard_normal((8, 128)).astype(np.float32) for _ in range(2))
+    oa[5], ob[6] = nan, nan
+    ctx = U.make_ctx(gen.CFG0, 64, 8, 16)
+    out, lse = torch.zeros(8, 128, device=U.DEV), torch.zeros(8, device=U.DEV)
+    ctx.merge_lse(8, *(torch.as_tensor(x).to(U.DEV) for x in (oa, la, ob, lb)), out, lse)
+    torch.cuda.synchronize()
+    ref, l_ref = oracle32.merge_lse(oa, la, ob, lb)
+    _same_as_oracle(out.cpu().numpy(), ref, 1e-6, "out")
+    _same_as_oracle(lse.cpu().numpy(), l_ref, 1e-6, "lse")
+    assert np.isnan(ref[:5]).all() and np.isnan(l_ref[:5]).all() and np.isfinite(ref[5:]).all()
+
+
 # ----------------------------------------------------------------------------- local window merge, equal chunks
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
