@@ -931,8 +931,23 @@ __device__ __forceinline__ bf16x4_t lds_read_tr16(const char* p) {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-// 2^x for x <= 0 (a weight): the bare instruction; results below the normal range flush to zero
-__device__ __forceinline__ float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
+// A wave's weights are relative to its largest logit (log2 units), so that its largest weight is 1, which bf16 holds exactly: relative to a rounded
+// maximum the error of out is 1.2 to 8 times as large (logits of standard deviation 0.5 to 8).  Where sums of waves and blocks meet they are
+// relative to whole numbers: they then move from one reference to another by an exact power of two, which costs no more than a
+// bare exp2 and reaches below the normal range of a float.
+// 2^d for whole d <= 0; 0 for -infinity and for NaN (the difference of two references of nothing)
+__device__ __forceinline__ float pow2_whole(float d) { return ldexpf(1.f, (int)fmaxf(d, -512.f)); }
+// x <- 2^(x - ref), four weights of a lane (-infinity: 0).  The bare instruction flushes results below the normal range to zero; a wave
+// that has such arguments (masked ones count) takes the full function: in every wave that one costs 2-3 % of the step of one sequence.
+__device__ __forceinline__ void exp2_weights(float (&x)[4], float ref) {
+    if (__any(fminf(fminf(x[0], x[1]), fminf(x[2], x[3])) < ref - 126.f)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = exp2f(x[j] - ref);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = __builtin_amdgcn_exp2f(x[j] - ref);
+    }
+}
 // over the four lanes t16, t16 + 16, t16 + 32, t16 + 48 of a tile column; every lane gets the result
 __device__ __forceinline__ float max_quads(float x) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -1054,19 +1069,31 @@ __device__ __forceinline__ void leave_sums(char* tile, const f32x4_t (&o)[kHeadD
         }
     }
 }
-// A barrier later: the block's output relative to its common max, from the sums that NT waves left `stride` bytes apart, each relative to
-// the wave's own max.  put(g, d, sum, max, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
+// What a wave leaves of its softmax for the block: its largest logit m as 2^m = factor * 2^reference, and the sum of its weights.
+template <int NT> struct WaveSums {
+    __attribute__((aligned(16))) float reference[16][NT], factor[16][NT], sum[16][NT];      // per head and wave
+    // `base`: m, or 0 where there is no logit to speak of (m == -infinity)
+    __device__ __forceinline__ void leave(int head, int w, float m, float base, float l) {
+        reference[head][w] = rintf(m);
+        factor[head][w] = __builtin_amdgcn_exp2f(base - rintf(base));
+        sum[head][w] = l;
+    }
+};
+// A barrier later: the block's output relative to its common reference, from the sums that NT waves left `stride` bytes apart, each relative to
+// the wave's own max.  put(g, d, sum, reference, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
 // streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).
 template <int G, int NT, bool HEAD_FAST, typename Put>
-__device__ __forceinline__ void block_sums(const char* tiles, int stride, const float (&wmax)[16][NT], const float (&wsum)[16][NT], Put put) {
+__device__ __forceinline__ void block_sums(const char* tiles, int stride, const WaveSums<NT>& ws, Put put) {
     for (int i = threadIdx.x; i < G * kHeadDim; i += kBlockThreads) {
         const int g = HEAD_FAST ? i % G : i / kHeadDim, d = HEAD_FAST ? i / G : i % kHeadDim;
-        float mw[NT], lw[NT];
+        float mw[NT], fw[NT], lw[NT];
 #pragma unroll
         for (int k = 0; k < NT; k += 4) {
-            const float4 t = *reinterpret_cast<const float4*>(&wmax[g][k]), u = *reinterpret_cast<const float4*>(&wsum[g][k]);
+            const float4 t = *reinterpret_cast<const float4*>(&ws.reference[g][k]), u = *reinterpret_cast<const float4*>(&ws.factor[g][k]),
+                         v = *reinterpret_cast<const float4*>(&ws.sum[g][k]);
             mw[k] = t.x; mw[k + 1] = t.y; mw[k + 2] = t.z; mw[k + 3] = t.w;
-            lw[k] = u.x; lw[k + 1] = u.y; lw[k + 2] = u.z; lw[k + 3] = u.w;
+            fw[k] = u.x; fw[k + 1] = u.y; fw[k + 2] = u.z; fw[k + 3] = u.w;
+            lw[k] = v.x; lw[k + 1] = v.y; lw[k + 2] = v.z; lw[k + 3] = v.w;
         }
         float mb = -INFINITY;
 #pragma unroll
@@ -1074,11 +1101,11 @@ __device__ __forceinline__ void block_sums(const char* tiles, int stride, const 
         float o = 0.f, lb = 0.f;
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
-            const float c = mb > -INFINITY ? exp2_neg(mw[k] - mb) : 0.f;
+            const float c = fw[k] * pow2_whole(mw[k] - mb);
             o += c * reinterpret_cast<const float*>(tiles + k * stride)[d * G + g];
             lb += c * lw[k];
         }
-        if (lb != lb) mb = 0.f;                                       // NaN, perhaps with no other logit: merges pass over a max of -infinity
+        if (lb != lb) mb = 0.f;                                       // NaN, perhaps with no other logit: merges pass over a reference of -infinity
         put(g, d, o, mb, lb);
     }
 }
@@ -1169,7 +1196,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     constexpr int kKeyBytes = MODE == kStep ? kSelKreg * kBlockThreads * 4 : 0;
     constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), MODE == kStep ? 0 : 16 * kBlockThreads);
     __shared__ __attribute__((aligned(16))) char sm[kShBytes];
-    __shared__ __attribute__((aligned(16))) float sm_wmax[16][kTiles], sm_wsum[16][kTiles];     // per head and wave
+    __shared__ WaveSums<kTiles> sm_waves;
     __shared__ int sm_last;
     __shared__ int32_t sm_row[CHUNK];
     __shared__ float sm_merge[MODE == kStep ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
@@ -1429,21 +1456,19 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     *reinterpret_cast<uint4*>(sm_v + X::place(row, lane % X::LPR)) = ((vm[ps] >> row) & 1ull) ? vR[ps][i] : make_uint4(0, 0, 0, 0);
                 }
                 SKV_T(6);
+                exp2_weights(p[ps], ref);                             // masked: 2^-inf = 0
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    p[ps][j] = exp2_neg(p[ps][j] - ref);              // masked: exp2(-inf) = 0
-                    lw += X::weight(p[ps][j]);
-                }
+                for (int j = 0; j < 4; ++j) lw += X::weight(p[ps][j]);
                 wave_lds_sync();                                      // the tile is the wave's own: order only
                 X::output(p[ps], sm_v, lane, o);
                 wave_lds_sync();
             }
             lw = sum_quads(lw);
-            if (qd == 0) { sm_wmax[t16][w] = mw; sm_wsum[t16][w] = lw; }
+            if (qd == 0) sm_waves.leave(t16, w, mw, ref, lw);
             leave_sums<G>(sm_v, o);
         }
         __syncthreads();
-        block_sums<G, kTiles, false>(sm, kTileBytes, sm_wmax, sm_wsum, [&](int g, int d, float sum, float mb, float lb) {
+        block_sums<G, kTiles, false>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
             if constexpr (MODE == kStep) {
                 unsigned long long* dst = my_part + g * kStepPartWords;
                 st_tagged(dst + d, sum, part_tag);
@@ -1496,14 +1521,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 if (ok && base + grp + u * groups < nsplit) {
-                    const float ms = val_of(mv[u]);
-                    if (ms > -INFINITY) {
-                        const float nm = fmaxf(M, ms);
-                        const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);  // M == -inf gives ca == 0
-                        L = L * ca + val_of(lv[u]) * cb;
-                        o = o * ca + val_of(pv[u]) * cb;
-                        M = nm;
-                    }
+                    const float ms = val_of(mv[u]), ls = val_of(lv[u]), ps = val_of(pv[u]);
+                    const float nm = fmaxf(M, ms), ca = pow2_whole(M - nm), cb = pow2_whole(ms - nm);     // M == -inf gives ca == 0
+                    L = L * ca + ls * cb;
+                    o = o * ca + ps * cb;
+                    M = nm;
                 }
             }
         }
@@ -1534,11 +1556,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             float Ls = 0.f, os = 0.f;
 #pragma unroll
             for (int gg = 0; gg < kGroups8; ++gg) {
-                if (mg[gg] > -INFINITY) {
-                    const float c = exp2_neg(mg[gg] - Mx);
-                    Ls += c * lg[gg];
-                    os += c * og[gg];
-                }
+                const float c = pow2_whole(mg[gg] - Mx);
+                Ls += c * lg[gg];
+                os += c * og[gg];
             }
             for (int k = 1; k < share; k <<= 1) {
                 Ls += __shfl_xor(Ls, k);
@@ -1602,14 +1622,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const float ms = (s0 + u * kGroups < nsplit) ? lo_f(mv[u]) : -INFINITY;
-                if (ms > -INFINITY) {
-                    const float nm = fmaxf(M, ms);
-                    const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);      // M == -inf gives ca == 0
-                    L = L * ca + hi_f(mv[u]) * cb;
-                    o0 = o0 * ca + lo_f(pv[u]) * cb;
-                    o1 = o1 * ca + hi_f(pv[u]) * cb;
-                    M = nm;
-                }
+                const float nm = fmaxf(M, ms), ca = pow2_whole(M - nm), cb = pow2_whole(ms - nm);      // M == -inf gives ca == 0
+                L = L * ca + hi_f(mv[u]) * cb;
+                o0 = o0 * ca + lo_f(pv[u]) * cb;
+                o1 = o1 * ca + hi_f(pv[u]) * cb;
+                M = nm;
             }
         }
         SKV_T(10);
@@ -1626,10 +1643,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 #pragma unroll
         for (int grp = 0; grp < kGroups; ++grp) {
             const float4 t = scratch[grp * kCol2 + tid];
-            if (t.z > -INFINITY) {
-                const float c = exp2_neg(t.z - M);
-                L += c * t.w; o0 += c * t.x; o1 += c * t.y;
-            }
+            const float c = pow2_whole(t.z - M);
+            L += c * t.w; o0 += c * t.x; o1 += c * t.y;
         }
         const bool empty = L == 0.f;                       // every retrieved position was out of range
         const float inv = empty ? 0.f : 1.f / L;
@@ -1667,7 +1682,7 @@ constexpr int kStreamMaxChunk = 2 * kStreamChunk;                 // the largest
 template <int EB, int CHUNK> struct StreamShared {
     __attribute__((aligned(16))) char v[kStreamWaves][16 * Tile<EB>::kPitch];    // the selection's, then value tiles, then the waves' partial sums
     __attribute__((aligned(16))) char q[16][kHeadDim * EB];                      // the group's queries, rows >= G zero
-    __attribute__((aligned(16))) float wmax[16][kStreamWaves], wsum[16][kStreamWaves];   // per head and wave
+    WaveSums<kStreamWaves> waves;
     int32_t row[max_of(CHUNK, kBlockThreads)];                                   // pool row of every position of the block (-1: none)
     int next_tile;
     int last;
@@ -1797,14 +1812,12 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
             mt = fmaxf(mt, p[j]);
         }
         const float m_new = fmaxf(m_run, max_quads(mt));
-        const float alpha = (m_new > -INFINITY) ? exp2_neg(m_run - m_new) : 1.f;   // m_run == -inf gives 0
+        const float alpha = m_new > -INFINITY ? exp2f(m_run - m_new) : 1.f;   // m_run == -inf gives 0
         const float ref = m_new > -INFINITY ? m_new : 0.f;        // (no live token yet, or logits of NaN only: those weights are NaN)
         float lw = 0.f;
+        exp2_weights(p, ref);                                     // masked: 2^-inf = 0
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            p[j] = exp2_neg(p[j] - ref);                              // masked: exp2(-inf) = 0
-            lw += X::weight(p[j]);
-        }
+        for (int j = 0; j < 4; ++j) lw += X::weight(p[j]);
         l_run = l_run * alpha + lw;
         m_run = m_new;
         // running outputs: row 4qd+j of o is head 4qd+j, whose factor sits in lane 4qd+j
@@ -1837,10 +1850,10 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
 
     // ---- the block's waves combine -------------------------------------------------------------------------------
     l_run = sum_quads(l_run);
-    if (qd == 0) { ss.wmax[t16][w] = m_run; ss.wsum[t16][w] = l_run; }
+    if (qd == 0) ss.waves.leave(t16, w, m_run, m_run > -INFINITY ? m_run : 0.f, l_run);
     leave_sums<G>(vt_b, o);
     __syncthreads();
-    block_sums<G, NW, true>(ss.v[0], sizeof(ss.v[0]), ss.wmax, ss.wsum, [&](int g, int d, float sum, float mb, float lb) {
+    block_sums<G, NW, true>(ss.v[0], sizeof(ss.v[0]), ss.waves, [&](int g, int d, float sum, float mb, float lb) {
         if (nsplit == 1) {                                        // the only block of this (sequence, head): no partials, no arrival, no merge
             const bool empty = lb == 0.f;                       // every retrieved position was out of range
             a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
@@ -1882,14 +1895,11 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const float ms = (s0 + u < nsplit) ? lo_f(mv[u]) : -INFINITY;
-                if (ms > -INFINITY) {
-                    const float nm = fmaxf(M, ms);
-                    const float ca = exp2_neg(M - nm), cb = exp2_neg(ms - nm);
-                    L = L * ca + hi_f(mv[u]) * cb;
-                    o0 = o0 * ca + lo_f(pv[u]) * cb;
-                    o1 = o1 * ca + hi_f(pv[u]) * cb;
-                    M = nm;
-                }
+                const float nm = fmaxf(M, ms), ca = pow2_whole(M - nm), cb = pow2_whole(ms - nm);
+                L = L * ca + hi_f(mv[u]) * cb;
+                o0 = o0 * ca + lo_f(pv[u]) * cb;
+                o1 = o1 * ca + hi_f(pv[u]) * cb;
+                M = nm;
             }
         }
         const bool empty = L == 0.f;                            // every retrieved position was out of range

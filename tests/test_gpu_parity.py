@@ -802,6 +802,54 @@ def test_fused_step_carries_values_that_are_not_finite(U, oracle32, B, dtype, Hq
             assert np.abs(o[1:] - o_fin[1:]).max(initial=0.0) <= ATT_TOL[dtype] and np.abs(l[1:] - l_fin[1:]).max(initial=0.0) <= ATT_TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("budget,at", [(32, 3), (32, 19), (257, 256), (1025, 1024)])     # same tile, another wave's tile, another block
+def test_attend_weights_below_the_normal_range(U, dtype, budget, at):
+    """One row ahead of all others by 2^127.5: its value is zero, so out is the others' 2^-127.5-weighted sum, and it is not flushed.
+    Relative bounds: a float of that size keeps 21 bits (2^-20 here with the sums); the same weight rounded to bf16 keeps 5 (2^-5)."""
+    wl = gen.CFG0.scaled(dtype=dtype)
+    H, Hq, D = 8, 32, 128
+    q, K, V = torch.zeros(Hq, D), torch.zeros(H, budget, D), torch.zeros(H, budget, D)
+    q[:, 0] = 1.0
+    K[:, at, 0] = 1000.0
+    V[:, 0] = 2.0 ** 30
+    q, K, V = (x.to(wl.torch_dtype).to(U.DEV) for x in (q, K, V))
+    out, lse = torch.zeros(Hq, D, device=U.DEV), torch.zeros(Hq, device=U.DEV)
+    _say("attend, small weights", dtype, budget, at)
+    U.make_ctx(wl, 4096, 64, budget).attend(q, K, V, U.i32([budget] * H), budget, out, lse)
+    torch.cuda.synchronize()
+    want = 2.0 ** 30 * math.exp(-1000.0 / math.sqrt(D))
+    err = float((out.cpu().double() / want - 1).abs().max())
+    assert err <= (2.0 ** -5 if dtype == "bf16" else 2.0 ** -13), err
+
+
+@pytest.mark.parametrize("B,dtype,capacity", [(1, "bf16", 0), (1, "f32", 0), (9, "bf16", 0), (9, "f32", 0), (9, "bf16", STREAM_CAPACITY)])
+@pytest.mark.parametrize("at", [3, 700])
+def test_fused_weights_below_the_normal_range(U, B, dtype, capacity, at):
+    """The same through the single launch and the streaming kernel; the budget takes every token, the row ahead of the others comes first or late."""
+    H, Hq, D, T = 8, 32, 128, 1100
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, dtype=dtype)
+    cap = max(T, capacity)
+    ctx = U.make_ctx(wl, B * T, B * 11, cap, batch=B)
+    q, K, V = torch.zeros(B, Hq, D), torch.zeros(1, H, B, T, D), torch.full((1, H, B, T, D), 2.0 ** 30)
+    q[:, :, 0] = 1.0
+    K[..., at, 0] = 1000.0
+    V[..., at, :] = 0.0
+    q, K, V = (x.to(wl.torch_dtype).to(U.DEV) for x in (q, K, V))
+    off = np.arange(0, T + 1, 100)
+    out, lse = torch.zeros(B, Hq, D, device=U.DEV), torch.zeros(B, Hq, device=U.DEV)
+    n_tok = U.empty_i32(B, H, fill=-1)
+    _say("fused, small weights", B, dtype, capacity, at)
+    ctx.decode_step(0, B, q, q, K.view(1, H, B * T, D), V.view(1, H, B * T, D), B * T, torch.zeros(1, H, B * 11, D, device=U.DEV), B * 11,
+                    U.i32(np.arange(B + 1) * T), U.i32(np.arange(B + 1) * 11), U.i32(np.tile(off, B)), U.i32([100] * (11 * B)),
+                    U.i32([T] * B), out, lse, None, n_tok)
+    torch.cuda.synchronize()
+    assert bool((n_tok == T).all())
+    want = (T - 1) * 2.0 ** 30 * math.exp(-1000.0 / math.sqrt(D))
+    err = float((out.cpu().double() / want - 1).abs().max())
+    assert err <= (2.0 ** -5 if dtype == "bf16" else 2.0 ** -13), err
+
+
 def test_merge_carries_nan(U, oracle32):
     """NaN as a side's lse is not an empty side, whatever the other side is; an empty side's output is ignored all the same."""
     nan, inf = float("nan"), float("inf")
