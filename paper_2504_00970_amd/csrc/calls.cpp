@@ -1,5 +1,6 @@
-// Calls of libsentencekv's C entry points from Python without ctypes: a tensor argument is its data pointer, None a null
-// pointer, an integer a pointer value or a number.  ctypes and the Python code around it took 2.4 to 4.8 us per call (an is_contiguous and a
+// Calls of libsentencekv's C entry points from Python without ctypes: a pointer argument is a tensor (its data pointer) or None (a null
+// pointer), a number an integer.  Addresses as integers are taken for the context and for skv_segment's n_sent_host only, so that an
+// argument in another one's place is refused here and does not go to the GPU as an address.  ctypes and the Python code around it took 2.4 to 4.8 us per call (an is_contiguous and a
 // data_ptr call for every tensor, argument objects), more than the kernels of a short context run; this takes 0.3 to 0.7.
 // Host code only.  The entry points are looked up in the library that `load` is given, once.
 #include <Python.h>
@@ -16,10 +17,20 @@
 
 namespace {
 
+bool refuse(PyObject* o, const char* wanted) {
+    PyErr_Format(PyExc_TypeError, "%s expected, got %.100s", wanted, Py_TYPE(o)->tp_name);
+    return false;
+}
+
 // One Python argument as a C one; false with a Python exception set where it cannot be.
-template <typename T>
+template <typename T, bool kAddress>
 bool convert(PyObject* o, T* out) {
-    if constexpr (std::is_pointer_v<T>) {
+    if constexpr (kAddress) {
+        if (o != Py_None && !PyLong_Check(o)) return refuse(o, "an address or None");
+        const unsigned long long v = o == Py_None ? 0 : PyLong_AsUnsignedLongLong(o);
+        if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
+        *out = reinterpret_cast<T>(static_cast<uintptr_t>(v));
+    } else if constexpr (std::is_pointer_v<T>) {
         if (o == Py_None) {
             *out = nullptr;
         } else if (THPVariable_Check(o)) {
@@ -30,11 +41,10 @@ bool convert(PyObject* o, T* out) {
             }
             *out = static_cast<T>(t.data_ptr());
         } else {
-            const unsigned long long v = PyLong_AsUnsignedLongLong(o);
-            if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
-            *out = reinterpret_cast<T>(static_cast<uintptr_t>(v));
+            return refuse(o, "a tensor or None");
         }
     } else {
+        if (THPVariable_Check(o)) return refuse(o, "a number");
         const long long v = PyLong_AsLongLong(o);
         if (v == -1 && PyErr_Occurred()) return false;
         *out = static_cast<T>(v);
@@ -47,11 +57,18 @@ template <typename R, typename... A, R (*F)(A...)>
 struct Call<F> {
     static inline R (*entry)(A...) = nullptr;      // in the loaded library; F only names the signature
 
+    template <size_t I>
+    static constexpr bool takes_address() {
+        if constexpr (std::is_same_v<std::tuple_element_t<I, std::tuple<A...>>, skv_ctx*>) return true;
+        else if constexpr (std::is_same_v<decltype(F), decltype(&skv_segment)>) return F == &skv_segment && I + 1 == sizeof...(A);
+        else return false;
+    }
+
     template <size_t... I>
     static PyObject* run(PyObject* const* args, std::index_sequence<I...>) {
         std::tuple<A...> v{};
         try {
-            if (!(convert(args[I], &std::get<I>(v)) && ...)) return nullptr;
+            if (!(convert<A, takes_address<I>()>(args[I], &std::get<I>(v)) && ...)) return nullptr;
         } catch (const std::exception& e) {        // a tensor without storage
             PyErr_SetString(PyExc_RuntimeError, e.what());
             return nullptr;

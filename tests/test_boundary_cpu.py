@@ -60,6 +60,35 @@ def test_null_context_and_null_out_pointer_are_invalid_arguments():
     lib.skv_destroy(None)      # no-op
 
 
+_NATIVE = [n for n in skv.EXPORTS if n in ("skv_segment", "skv_build_semvec", "skv_build_semvec_layers", "skv_token_importance", "skv_retain",
+                                           "skv_compact_pool", "skv_query_update", "skv_score", "skv_select", "skv_gather", "skv_attend",
+                                           "skv_decode_step", "skv_merge_lse")]
+
+
+@pytest.mark.parametrize("name", _NATIVE)
+def test_python_calls_refuse_arguments_in_each_others_place(name):
+    """An integer is no pointer and a tensor no number (the context is null: nothing is looked at beyond the arguments' types)."""
+    import torch
+    binding._lib()
+    call, kinds = getattr(binding._CALLS, name), binding._SIGNATURES[name][1]
+    args = [None if k is ctypes.c_void_p else 1 for k in kinds]
+    assert call(*args) == skv.SKV_EINVAL
+    for i, k in enumerate(kinds):
+        bad = list(args)
+        address = i == 0 or (name == "skv_segment" and i == len(kinds) - 1)
+        bad[i] = torch.zeros(1, dtype=torch.int32) if address or k is not ctypes.c_void_p else 4096
+        with pytest.raises(TypeError):
+            call(*bad)
+        if not address and k is ctypes.c_void_p:
+            bad[i] = torch.zeros(4, 4).t()
+            with pytest.raises(AssertionError):
+                call(*bad)
+            bad[i] = torch.zeros(4, 4)
+            assert call(*bad) == skv.SKV_EINVAL
+    with pytest.raises(TypeError):
+        call(*args[:-1])
+
+
 def test_product_package_does_not_reach_into_the_oracle():
     pkg = os.path.join(ROOT, "paper_2504_00970_amd")
     for dirpath, _, files in os.walk(pkg):
