@@ -3,11 +3,13 @@
 Argument marshalling only: every function here forwards the device pointers of caller-allocated
 torch tensors to the C entry point of the same name and raises on a non-zero status.  Nothing is
 computed in Python and there is no fallback: if the HIP library is missing or fails, calls raise.
-The calls of a serving loop go through a native module (csrc/calls.cpp), set-up calls through ctypes.
+The calls of a serving loop go through a native module (csrc/calls.cpp), set-up calls through ctypes; where the module
+cannot be built, all of them do.
 """
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -69,28 +71,63 @@ def lib_path() -> str:
     return _build.LIB
 
 
-def _lib():
-    """Load the built library and the module that calls it; build them first only if they are not there at all."""
-    global _LIB, _CALLS
-    if _LIB is None:
-        if not os.path.exists(_build.LIB) or not os.path.exists(_build.CALLS):
-            _build.build(force=True)
-        from . import _calls
-        _calls.load(_build.LIB)
-        _CALLS = _calls
-        lib = ctypes.CDLL(_build.LIB)
-        for name, (res, args) in _SIGNATURES.items():
-            fn = getattr(lib, name)
-            fn.restype, fn.argtypes = res, args
-        _LIB = lib
-    return _LIB
+class _CtypesCalls:
+    """The call module's functions by ctypes, for machines that cannot build it: the same arguments, several times the time per call."""
+
+    def __init__(self, lib):
+        for name, (res, kinds) in _SIGNATURES.items():
+            if res is _int and kinds[0] is _vp:
+                setattr(self, name, self._function(getattr(lib, name), kinds, 9 if name == "skv_segment" else 0))
+
+    @staticmethod
+    def _function(fn, kinds, address):
+        def call(*args):
+            if len(args) != len(kinds):
+                raise TypeError("wrong number of arguments")
+            return fn(*(_address(a) if k is _vp and i in (0, address) else _p(a) if k is _vp else _number(a)
+                        for i, (a, k) in enumerate(zip(args, kinds))))
+        return call
+
+
+def _address(a):
+    if a is None or isinstance(a, int):
+        return a
+    raise TypeError(f"an address or None expected, got {type(a).__name__}")
+
+
+def _number(a):
+    if isinstance(a, torch.Tensor):
+        raise TypeError("a number expected, got a tensor")
+    return operator.index(a)
 
 
 def _p(t: Optional[torch.Tensor]):
     if t is None:
         return None
+    if not isinstance(t, torch.Tensor):
+        raise TypeError(f"a tensor or None expected, got {type(t).__name__}")
     assert t.is_contiguous(), "tensors handed to libsentencekv must be contiguous"
     return t.data_ptr()
+
+
+def _lib():
+    """Load the built library and the module that calls it; build what is not there at all, or does not run with this Python and torch."""
+    global _LIB, _CALLS
+    if _LIB is None:
+        if not os.path.exists(_build.LIB):
+            _build.build(force=True)
+        lib = ctypes.CDLL(_build.LIB)
+        for name, (res, args) in _SIGNATURES.items():
+            fn = getattr(lib, name)
+            fn.restype, fn.argtypes = res, args
+        if _build.calls_fit() or _build.build_calls():
+            from . import _calls
+            _calls.load(_build.LIB)
+            _CALLS = _calls
+        else:
+            _CALLS = _CtypesCalls(lib)
+        _LIB = lib
+    return _LIB
 
 
 def _check(status: int, what: str) -> None:

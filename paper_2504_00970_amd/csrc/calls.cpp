@@ -15,7 +15,14 @@
 
 #include "sentencekv.h"
 
+#ifndef SKV_BUILT_FOR
+#define SKV_BUILT_FOR ""
+#endif
+
 namespace {
+
+// the Python and torch of this build: _build.py looks for it in the file, since the module only runs with them
+__attribute__((used)) const char built_for[] = SKV_BUILT_FOR;
 
 bool refuse(PyObject* o, const char* wanted) {
     PyErr_Format(PyExc_TypeError, "%s expected, got %.100s", wanted, Py_TYPE(o)->tp_name);

@@ -3,11 +3,13 @@ the public header declares, and rejects bad arguments before touching the device
 import ctypes
 import os
 import re
+import shutil
+import sysconfig
 
 import pytest
 
 import paper_2504_00970_amd as skv
-from paper_2504_00970_amd import binding
+from paper_2504_00970_amd import _build, binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -65,12 +67,13 @@ _NATIVE = [n for n in skv.EXPORTS if n in ("skv_segment", "skv_build_semvec", "s
                                            "skv_decode_step", "skv_merge_lse")]
 
 
+@pytest.mark.parametrize("through", ["native", "ctypes"])
 @pytest.mark.parametrize("name", _NATIVE)
-def test_python_calls_refuse_arguments_in_each_others_place(name):
+def test_python_calls_refuse_arguments_in_each_others_place(name, through):
     """An integer is no pointer and a tensor no number (the context is null: nothing is looked at beyond the arguments' types)."""
     import torch
-    binding._lib()
-    call, kinds = getattr(binding._CALLS, name), binding._SIGNATURES[name][1]
+    lib = binding._lib()
+    call, kinds = getattr(binding._CALLS if through == "native" else binding._CtypesCalls(lib), name), binding._SIGNATURES[name][1]
     args = [None if k is ctypes.c_void_p else 1 for k in kinds]
     assert call(*args) == skv.SKV_EINVAL
     for i, k in enumerate(kinds):
@@ -87,6 +90,47 @@ def test_python_calls_refuse_arguments_in_each_others_place(name):
             assert call(*bad) == skv.SKV_EINVAL
     with pytest.raises(TypeError):
         call(*args[:-1])
+
+
+def test_build_notices_what_the_call_module_depends_on(tmp_path, monkeypatch):
+    """An edited calls.cpp or header, another torch, another Python or no module at all: build(force=False) compiles it anew."""
+    binding._lib()
+    assert _build.calls_fit()
+    calls = tmp_path / "_calls.so"
+    shutil.copy(_build.CALLS, calls)
+    monkeypatch.setattr(_build, "CALLS", str(calls))
+    newest = max(os.path.getmtime(p) for p in (os.path.join(_build.CSRC, "calls.cpp"), os.path.join(_build.INCLUDE, "sentencekv.h")))
+    os.utime(calls, (newest + 1, newest + 1))
+    assert not _build.calls_stale()
+    os.utime(calls, (newest - 1, newest - 1))
+    assert _build.calls_stale()
+    os.utime(calls, (newest + 1, newest + 1))
+    with monkeypatch.context() as m:
+        m.setattr("torch.__version__", "0.0.1")
+        assert not _build.calls_fit() and _build.calls_stale()
+    with monkeypatch.context() as m:
+        m.setattr(sysconfig, "get_python_version", lambda: "3.1")
+        assert _build.calls_stale()
+    calls.unlink()
+    assert _build.calls_stale()
+    started = []
+    monkeypatch.setattr(_build, "stale", lambda lib="": False)
+    monkeypatch.setattr(_build, "_start", lambda cmd, verbose: started.append(cmd))
+    monkeypatch.setattr(_build, "_finish_calls", lambda proc: True)
+    _build.build(force=False)
+    assert len(started) == 1 and any("calls.cpp" in part for part in started[0])
+
+
+def test_calls_go_through_ctypes_where_the_module_cannot_be_built(tmp_path, monkeypatch):
+    lib = binding._lib()
+    monkeypatch.setattr(_build, "CALLS", str(tmp_path / "_calls.so"))
+    monkeypatch.setattr(_build, "_host_compiler", lambda: str(tmp_path / "no-compiler"))
+    monkeypatch.setattr(binding, "_LIB", None)
+    monkeypatch.setattr(binding, "_CALLS", None)
+    with pytest.warns(UserWarning, match="ctypes"):
+        assert binding._lib() is not lib
+    assert isinstance(binding._CALLS, binding._CtypesCalls)
+    assert binding._CALLS.skv_attend(None, None, None, None, None, 0, None, None) == skv.SKV_EINVAL
 
 
 def test_product_package_does_not_reach_into_the_oracle():
