@@ -36,13 +36,18 @@ __device__ __forceinline__ void st_stream(void* p, const uint4& v) {
 // 16 bytes per lane from global memory at base + off straight to LDS at `lds` + 16 * lane (base and lds wave-uniform), non-temporal: one-shot
 // reads of the same pool run at 7.1 TB/s with these, 6.2 with plain loads.  Asynchronous: counted by vmcnt, and only the
 // kernel's own waits (wait_loads) order it against reads of the destination.  Written out because the compiler, where it
-// knows that LDS is written, waits for everything outstanding before the next LDS read.
+// knows that LDS is written, waits for everything outstanding before the next LDS read.  m0 (the LDS address) is declared as
+// written: the compiler merges its own writes of m0 between uses, which it must not do across this.  (It warns that m0 is reserved, that
+// is, not saved around the statement: nothing here expects it to be.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_lds_stream(const char* base, uint32_t off, char* lds) {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(off),
                  "s"(base)
-                 : "memory");
+                 : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // waits until at most N of the wave's vector memory instructions are outstanding
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
