@@ -472,8 +472,11 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 // Keys per block, in units of 128: the number that gives the least rounds x (units + 2), two units being about what a block's
 // start and end take.
 constexpr int kImpUnit = 128;
-static int importance_keys_per_block(const Ctx* c, int32_t T) {
-    const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, resident = (int64_t)c->n_cu * (c->d.kv_dtype == SKV_BF16 ? 3 : 1);
+static int importance_rows(int rows) { return rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 128 ? 128 : 256; }
+static int importance_keys_per_block(const Ctx* c, int32_t T, int32_t N) {
+    const int per_cu = c->d.kv_dtype != SKV_BF16 ? Imp<4, 8>::kPerCu : importance_rows(c->G * N) == 256 ? Imp<2, 8>::kPerCu : Imp<2, 4>::kPerCu;
+    static_assert(Imp<4, 1>::kPerCu == Imp<4, 8>::kPerCu && Imp<2, 1>::kPerCu == Imp<2, 4>::kPerCu && Imp<2, 2>::kPerCu == Imp<2, 4>::kPerCu, "by type and 256 rows");
+    const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, resident = (int64_t)c->n_cu * per_cu;
     const int64_t units = (T + kImpUnit - 1) / kImpUnit;
     int64_t best = 0, best_cost = 0;
     for (int64_t per = 1; per <= 256 && per <= units; ++per) {
@@ -487,7 +490,7 @@ template <int EB, int RT>
 static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
                                        float2* rowstat, float* alpha_h) {
     using P = Imp<EB, RT>;
-    const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, Tp = T - N, kpb = importance_keys_per_block(c, T);
+    const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, Tp = T - N, kpb = importance_keys_per_block(c, T, N);
     constexpr size_t lds = P::kRingBytes;
     static bool raised = false;                                        // LDS above 64 KB needs the opt-in once
     if (!raised) {
@@ -517,14 +520,12 @@ static hipError_t launch_importance_eb(Ctx* c, const char* q_obs, const char* K_
     return hipErrorInvalidValue;
 }
 
-static int importance_rows(int rows) { return rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 128 ? 128 : 256; }
-
-static int64_t importance_chunks(const Ctx* c, int32_t T) {
-    const int per = importance_keys_per_block(c, T);
+static int64_t importance_chunks(const Ctx* c, int32_t T, int32_t N) {
+    const int per = importance_keys_per_block(c, T, N);
     return (T + per - 1) / per;
 }
 
-// arrival counters of both passes: one per (layer, head), one per (layer, block of keys), at most max_tokens / 64 of them
+// arrival counters of both passes: one per (layer, head), one per (layer, block of keys): at most a block for every unit of max_tokens
 int64_t importance_counters(const skv_desc& d) {
     return (int64_t)d.n_layers * (d.n_kv_heads + (d.max_tokens + kImpUnit - 1) / kImpUnit);
 }
@@ -532,14 +533,14 @@ int64_t importance_counters(const skv_desc& d) {
 // work = part [L][Hkv][chunks][rows][2] | rowstat [L][Hkv][rows][2] | alpha_h [L][Hkv][Tp], floats
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N) {
     const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
-    return (LH * importance_chunks(c, T) * rows * 2 + LH * rows * 2 + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
+    return (LH * importance_chunks(c, T, N) * rows * 2 + LH * rows * 2 + LH * (int64_t)(T - N)) * (int64_t)sizeof(float);
 }
 
 // Two launches cover all layers: the rows' statistics, and the column sums with them.
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work) {
     const int64_t rows = importance_rows(c->G * N), LH = (int64_t)c->d.n_layers * c->d.n_kv_heads;
     float2* part = (float2*)work;
-    float2* rowstat = part + LH * importance_chunks(c, T) * rows;
+    float2* rowstat = part + LH * importance_chunks(c, T, N) * rows;
     float* alpha_h = (float*)(rowstat + LH * rows);
     return c->d.kv_dtype == SKV_BF16
                ? launch_importance_eb<2>(c, (const char*)q_obs, (const char*)K_pool, T, N, alpha, part, rowstat, alpha_h)

@@ -112,6 +112,22 @@ def test_token_importance_precision_at_large_logits(U, dtype, Hq, N):
     assert worst <= 1e-6
 
 
+@pytest.mark.parametrize("dtype,Hq,N,per_cu", [("bf16", 32, 32, 3), ("bf16", 64, 16, 3), ("bf16", 64, 17, 2), ("bf16", 64, 32, 2), ("f32", 64, 32, 1)])
+def test_token_importance_plans_for_the_blocks_that_fit(U, dtype, Hq, N, per_cu):
+    """The scratch holds the plan: a partial per block of keys, whose length fills the chip's rounds of `per_cu` blocks (what LDS
+    leaves room for: two of the 256-row form, three of the narrower ones, one for fp32) at the least rounds x (units of 128 keys + 2)."""
+    L, H, T = 4, 8, 17000
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype=dtype)
+    got = U.make_ctx(wl, T, 64, 16).token_importance_work_bytes(T, N)
+    resident = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    units = -(-T // 128)
+    chunks = lambda per: -(-units // per)
+    per = min(range(1, min(256, units) + 1), key=lambda p: -(-L * H * chunks(p) // resident) * (p + 2))
+    rows = next(r for r in (32, 64, 128, 256) if Hq // H * N <= r)
+    want = 4 * (L * H * chunks(per) * rows * 2 + L * H * rows * 2 + L * H * (T - N))
+    assert got == -(-want // 256) * 256
+
+
 FULL_IMP_CASES = [("bf16", 32, 8, 32, 32768), ("f32", 32, 8, 32, 32768), ("bf16", 8, 2, 32, 40100), ("f32", 4, 1, 32, 70001)]
 
 
