@@ -317,17 +317,20 @@ __device__ __forceinline__ void store_means(char* __restrict__ semvec, int64_t o
 }
 
 // Bound by HBM: the pool once in, the table once out.  A wave per bucket, one-shot waves with all the rows of a bucket of
-// average length requested at once.  32 layers x 8 heads x 32768 tokens in bf16 (2.36 GB): 431 us with plain accesses and 4
-// waves per block, 404 with non-temporal loads and stores, 383-395 with 8 waves per block (contiguous 40 KB per block).
-template <int EB, int SVB>
-__global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(const char* __restrict__ K, int32_t T,
-                                                                              const int32_t* __restrict__ sent_off_all,
-                                                                              int32_t off_layer_stride, int32_t Hkv,
-                                                                              int32_t S, char* __restrict__ semvec) {
+// average length requested at once.  LARGE: 8 waves per block (contiguous 40 KB) and non-temporal stores, else 4 and plain ones; see the launch.
+// The keys' loads are non-temporal in both: a plain read takes a place in the memory-side cache, whose lines may have to be written
+// back first.  32 layers x 8 heads, us, plain / non-temporal loads, after other work has filled the cache with written lines and
+// after the keys themselves have just been written: 1000 tokens 30.4 / 19.0, 16.4 / 16.4; 3000 79 / 44, 43 / 37; 8192 164 / 115, 136 / 115;
+// 32768 491 / 394, 469 / 394 (only keys that a table was built from just before are read again faster with plain ones: 1531 tokens 26 / 29).
+template <int EB, int SVB, bool LARGE>
+__global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const char* __restrict__ K, int32_t T,
+                                                                         const int32_t* __restrict__ sent_off_all,
+                                                                         int32_t off_layer_stride, int32_t Hkv,
+                                                                         int32_t S, char* __restrict__ semvec) {
     using R = Row<EB>;
     constexpr int kUnroll = 4;
     const int lane = threadIdx.x & 63;
-    const int32_t s = blockIdx.x * kSemvecWavesPerBlock + (threadIdx.x >> 6);
+    const int32_t s = blockIdx.x * (LARGE ? 8 : 4) + (threadIdx.x >> 6);
     if (s >= S) return;                                   // wave-uniform
     const int64_t lh = blockIdx.y;
     const int32_t* sent_off = sent_off_all + (int64_t)(blockIdx.y / Hkv) * off_layer_stride;   // the layer's table
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(co
     }
     if (r == 0) {
         const float n = (e > b) ? (float)(e - b) : 1.f;      // a bucket without tokens yields zeros
-        store_means<R::EPL, SVB, true>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
+        store_means<R::EPL, SVB, LARGE>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
     }
 }
 
@@ -371,14 +374,14 @@ __global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_kernel(co
 // its rows; no sum across lanes, and the table's rows are stored RPW at a time.  A wave per bucket is bound by the number of
 // waves here: 32 x 8 x 4096 retained tokens in 1654 buckets (485 MB), 161-169 us with a wave per bucket, 90 us with this.
 template <int EB, int SVB>
-__global__ __launch_bounds__(kSemvecWavesPerBlock * kWave) void semvec_short_kernel(const char* __restrict__ K, int32_t T,
+__global__ __launch_bounds__(kSemvecShortWaves * kWave) void semvec_short_kernel(const char* __restrict__ K, int32_t T,
                                                                                     const int32_t* __restrict__ sent_off_all,
                                                                                     int32_t off_layer_stride, int32_t Hkv,
                                                                                     int32_t S, char* __restrict__ semvec) {
     using R = Row<EB>;
     constexpr int kUnroll = 4;
     const int lane = threadIdx.x & 63, cc = lane % R::LPR;
-    const int32_t s = (blockIdx.x * kSemvecWavesPerBlock + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
+    const int32_t s = (blockIdx.x * kSemvecShortWaves + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
     if (s >= S) return;
     const int64_t lh = blockIdx.y;
     const int32_t* sent_off = sent_off_all + (int64_t)(blockIdx.y / Hkv) * off_layer_stride;   // the layer's table
@@ -412,14 +415,23 @@ static void launch_semvec_t(Ctx* c, const void* K_pool, int32_t T, const int32_t
     // By the bytes of a bucket's rows: 16 layers x 8 heads x 32768 tokens in buckets of n tokens, wave per bucket against several
     // per wave, us: bf16 pool, fp32 table, n = 6: 323 / 248, 8: 255 / 242, 10: 221 / 233, 24: 186 / 222; fp32 pool, n = 2:
     // 738 / 530, 4: 460 / 490, 8: 378 / 464.  Smaller tables move the line up a little (E4M3, n = 10: 225 / 202).
-    const bool is_short = (int64_t)T * (kHeadDim * EB) < kSemvecShortBytes * (int64_t)S;
-    const int per_block = kSemvecWavesPerBlock * (is_short ? Row<EB>::RPW : 1);
-    const dim3 grid((S + per_block - 1) / per_block, c->d.n_layers * c->d.n_kv_heads), block(kSemvecWavesPerBlock * kWave);
-    if (is_short)
-        hipLaunchKernelGGL((semvec_short_kernel<EB, SVB>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
+    const int LH = c->d.n_layers * c->d.n_kv_heads;
+    const auto grid = [&](int per_block) { return dim3((S + per_block - 1) / per_block, LH); };
+    if ((int64_t)T * (kHeadDim * EB) < kSemvecShortBytes * (int64_t)S) {
+        hipLaunchKernelGGL((semvec_short_kernel<EB, SVB>), grid(kSemvecShortWaves * Row<EB>::RPW), dim3(kSemvecShortWaves * kWave), 0, c->stream,
+                           (const char*)K_pool, T, sent_off, off_layer_stride, c->d.n_kv_heads, S, (char*)semvec);
+        return;
+    }
+    // By the number of table rows (of 512 bytes in fp32).  The scores read the table next, from the memory-side cache while it fits there beside
+    // the keys just read, and a short prompt is spread more evenly in small blocks.  fp32 table, 32 layers x 8 heads, keys not in any cache, us,
+    // table / table and the scores of every layer, small against LARGE: 1531 tokens (15000 rows) 25.6 / 101 against 30.6 / 111,
+    // 8192 (105000) 104 / 183 against 111 / 197, 11000 (142000) 137 / 217 against 139 / 225, 16384 (206000) 201 / 284 against 200 / 286 and, keys
+    // just written, 212 / 298 against 198 / 288, 32768 426 / 528 against 397 / 503.
+    if ((int64_t)LH * S <= kSemvecSmallRows)
+        hipLaunchKernelGGL((semvec_kernel<EB, SVB, false>), grid(4), dim3(4 * kWave), 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
                            c->d.n_kv_heads, S, (char*)semvec);
     else
-        hipLaunchKernelGGL((semvec_kernel<EB, SVB>), grid, block, 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
+        hipLaunchKernelGGL((semvec_kernel<EB, SVB, true>), grid(8), dim3(8 * kWave), 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
                            c->d.n_kv_heads, S, (char*)semvec);
 }
 

@@ -19,7 +19,8 @@ constexpr int kSegOneBlockTok = 4096;         // single-launch segmentation: 102
 constexpr int kSegOneMaxTok = 131072;         // prompts it takes
 constexpr int kSegOneMaxWords = 15360;        // terminator bitmap words it keeps in LDS (vocabularies up to 491520)
 
-constexpr int kSemvecWavesPerBlock = 8;
+constexpr int kSemvecSmallRows = 160 * 1024;   // rows of a table that is built in small blocks with plain stores
+constexpr int kSemvecShortWaves = 8;          // waves of a block that takes several short buckets per wave
 constexpr int kSemvecShortBytes = 2304;       // mean bytes of a bucket's rows below which a wave takes several buckets
 
 constexpr int kScoreRowsPerWave = 8;          // buckets per wave (32 per block)

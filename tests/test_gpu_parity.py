@@ -104,6 +104,31 @@ def test_semvec_matches_oracle(U, oracle32, dtype, dist):
     assert np.array_equal(got[:, :, one], ref[:, :, one])          # length-1 buckets are exact copies
 
 
+@pytest.mark.parametrize("sv_dtype", ["f32", "fp8"])
+@pytest.mark.parametrize("S", [639, 640, 641])
+def test_semvec_at_the_line_between_its_forms(U, oracle32, S, sv_dtype):
+    """32 layers x 8 heads: tables of up to 640 buckets are built in blocks of four waves with plain stores, larger ones in blocks of eight
+    with non-temporal ones; the last block is full, one short and one over."""
+    wl = gen.CFG3.scaled(n_tokens=10 * S, len_dist=("fixed", 10), dtype="bf16")
+    lens = np.full(S, 10, dtype=np.int32)
+    lens[:-1:2] += 5
+    lens[1::2] -= 5
+    lens[-1] += 10 * S - lens.sum()
+    off = gen.offsets_of(lens)
+    g = torch.Generator(device=U.DEV).manual_seed(S)
+    K = torch.empty(wl.n_layers, 8, 10 * S, 128, dtype=torch.bfloat16, device=U.DEV).normal_(generator=g)
+    sv = torch.full((wl.n_layers, 8, S, 128), 9, dtype=U.sv_torch_dtype(sv_dtype), device=U.DEV)
+    _say("semvec", S, sv_dtype)
+    U.make_ctx(wl, 10 * S, S, 16, sv_dtype=sv_dtype).build_semvec(K, U.i32(off), S, sv)
+    torch.cuda.synchronize()
+    for l in (0, 31):
+        ref, got = oracle32.semvec(gen.to_numpy(K[l:l + 1]), off, sv_dtype=sv_dtype)[0], U.np_of(sv[l])
+        if sv_dtype == "f32":
+            assert np.abs(got - ref).max() <= 2.0 ** -22 * float(K.float().abs().max())
+        else:
+            assert U.e4m3_table_close(got, ref, oracle32.e4m3_decode)
+
+
 # ----------------------------------------------------------------------------- decode chain, per stage
 
 def _chain_case(U, oracle32, wl, seed, budget, pool_in_host=False, layers=None, sv_dtype="f32"):
