@@ -32,7 +32,7 @@ def _say(*a):
 
 # ----------------------------------------------------------------------------- segment
 
-SEG_SIZES = [0, 1, 2, 63, 64, 1023, 1024, 1025, 4096, 32768, 100001]
+SEG_SIZES = [0, 1, 2, 63, 64, 1023, 1024, 1025, 4096, 32768, 100001, 131072, 131073, 300001]      # beyond 131072: two launches
 
 
 @pytest.mark.parametrize("T", SEG_SIZES)
@@ -65,6 +65,25 @@ def test_segment_hand_built_streams(U, oracle32, text):
     ctx = U.make_ctx(wl, len(tok), len(tok), 16)
     seg, off, ln, S_host, _ = U.gpu_segment(ctx, tok, bitmap, 64, len(tok))
     assert S_host == S_ref and np.array_equal(seg, seg_ref)
+    assert np.array_equal(off[:S_ref + 1], off_ref) and np.array_equal(ln[:S_ref], len_ref)
+
+
+@pytest.mark.parametrize("T", [1, 5000, 131073])
+@pytest.mark.parametrize("vocab", [31, 32, 491520, 491521, 600001])
+def test_segment_vocabularies(U, oracle32, vocab, T):
+    """A terminator bitmap of up to 491520 ids is kept in LDS by the one-launch form; a larger one, as a longer prompt, takes two launches.
+    Ids outside the vocabulary end nothing."""
+    rng = np.random.default_rng(vocab + T)
+    tok = rng.integers(-3, vocab + 40, size=T).astype(np.int32)
+    ends = rng.random(vocab) < 0.05
+    ends[-1] = True                                                 # the last id, in the last word
+    tok[T // 2] = vocab - 1
+    bitmap = np.packbits(np.concatenate([ends, np.zeros(-vocab % 32, dtype=bool)]), bitorder="little").view(np.uint32)
+    _say("segment vocabulary", vocab, "T", T)
+    seg_ref, off_ref, len_ref, S_ref = oracle32.segment(tok, bitmap, vocab)
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=1), T, S_ref, 16)
+    seg, off, ln, S_host, S_dev = U.gpu_segment(ctx, tok, bitmap, vocab, S_ref)
+    assert S_host == S_ref == S_dev and np.array_equal(seg, seg_ref)
     assert np.array_equal(off[:S_ref + 1], off_ref) and np.array_equal(ln[:S_ref], len_ref)
 
 
@@ -327,17 +346,18 @@ def test_attend_large_logits_do_not_overflow(U, oracle32):
 
 # ----------------------------------------------------------------------------- fused step
 
-# Descriptor max_budget values that steer a bf16 batch of 8 sequences x 8 KV heads (64 pairs, 4 blocks per pair in the
-# single-launch step: budgets up to 1024 run there, in 256-token blocks); beyond that the library picks the attention kernel
-# from block counts, pairs x ceil(max_budget / 256) <= 256 compute units: 256-token fused blocks; else the streaming
-# kernel, in 512-token blocks while pairs x ceil(max_budget / 1024) <= 128, else in 1024-token blocks.
+# Descriptor max_budget values that steer a batch of 8 sequences x 8 KV heads (64 pairs, 4 blocks per pair in the single-launch step: budgets up
+# to 1024 run there, in blocks of 64, 128 or 256 tokens, and in bf16 up to 2048, in 512-token blocks, while the table is small beside the
+# retrieved rows).  Where that form does not take the step, or is turned off, the library picks the attention kernel from block
+# counts: pairs x ceil(max_budget / 256) <= 256 compute units: fused blocks of 64, 128 or 256 tokens; else the streaming
+# kernel, in 512-token blocks while pairs x ceil(max_budget / 1024) <= 128, else in 1024- or 2048-token blocks.
 STREAM_CAPACITY = 9000      # 1024-token streaming blocks
-HALF_CAPACITY = 1500        # 512-token streaming blocks (for 64 pairs; 72 pairs need 1024)
+HALF_CAPACITY = 1500        # 512-token streaming blocks for 64 pairs, with the single launch off
 
 
-def _fused_case(U, oracle32, wl, seed, layers, sv_dtype="f32", seq_tokens=None, budgets=None, capacity=0):
+def _fused_case(U, oracle32, wl, seed, layers, sv_dtype="f32", seq_tokens=None, budgets=None, capacity=0, single_launch=True):
     """One skv_decode_step per layer against the oracle, sequence by sequence.  `capacity` raises the context's
-    max_budget above the budgets in use: the library sizes its grids by it, and a bf16 batch whose 256-token blocks
+    max_budget above the budgets in use: the library sizes its grids by it, and a batch whose 256-token blocks
     (pairs x ceil(max_budget / 256)) outnumber the compute units takes the streaming kernel instead of the fused one,
     so the same inputs reach both kernels."""
     inp = gen.ragged_inputs(wl, seed=seed, device=U.DEV, resident_layers=len(layers), seq_tokens=seq_tokens, budgets=budgets)
@@ -345,6 +365,7 @@ def _fused_case(U, oracle32, wl, seed, layers, sv_dtype="f32", seq_tokens=None, 
     T_total, S_total = int(inp.cu_tok[-1]), int(inp.cu_sent[-1])
     max_budget = max(int(inp.budget.max()), capacity)
     ctx = U.make_ctx(wl.scaled(n_layers=len(layers)), T_total, S_total, max_budget, batch=B, sv_dtype=sv_dtype)
+    ctx.set_single_launch(single_launch)
     Kd, Vd, qd = inp.K.to(U.DEV), inp.V.to(U.DEV), inp.q.to(U.DEV)
     # semantic vectors of the concatenated stream: bucket boundaries are the concatenation of the sequences'
     glob_off = gen.offsets_of(inp.sent_len)
@@ -401,10 +422,9 @@ def _fused_case(U, oracle32, wl, seed, layers, sv_dtype="f32", seq_tokens=None, 
 
 @pytest.mark.parametrize("capacity", [0, 5000, STREAM_CAPACITY, 20000])
 def test_fused_single_sequence_matches_oracle(U, oracle32, capacity):
-    """One sequence through the forms of the step: single launch in 128-token blocks, in 256-token blocks (capacity 5000: 8 heads x
-    40 blocks of 128 tokens no longer fit the chip at once), 512- and 1024-token streaming blocks (capacities 9000 and
-    20000: beyond 32 blocks x 256 tokens per head, and 8 x 36 > 256 blocks of 256 tokens); fp32 runs the single launch on the
-    plain ALUs, and selection + attention through the positions for the large capacities."""
+    """One sequence, bf16 and fp32, through the forms of the step: single launch in 64-token blocks, in 256-token blocks (capacity 5000: 8
+    heads x 40 blocks of 128 tokens no longer fit the chip at once), 512- and 1024-token streaming blocks (capacities 9000 and
+    20000: beyond 32 blocks x 256 tokens per head, and 8 x 36 > 256 blocks of 256 tokens)."""
     wl = gen.CFG1.scaled(n_layers=2, batch=1, t_range=(6000, 6000), budgets=(1024,))
     _fused_case(U, oracle32, wl, seed=2, layers=[0, 1], capacity=capacity)
     wl = gen.CFG0.scaled(n_layers=1, batch=1, t_range=(4096, 4096), budgets=(512,))
@@ -415,7 +435,7 @@ def test_fused_single_sequence_matches_oracle(U, oracle32, capacity):
 @pytest.mark.parametrize("B", [1, 3])
 def test_fused_single_launch_with_idle_blocks(U, oracle32, tokens, budget, B):
     """The single-launch step when the retrieved tokens do not fill the blocks the budget provides: a context smaller than
-    the budget (every bucket is taken: 6 of 16 blocks hold tokens), a selection that ends a block or two short of the
+    the budget (every bucket is taken: 11 of 32 blocks hold tokens), a selection that ends a block or two short of the
     budget's last one, and a budget no bucket fits (nothing retrieved).  The blocks without tokens run the selection too,
     and block 0 of a pair waits for their word before it ends the pair's launch."""
     wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(tokens, tokens), budgets=(budget,), len_dist=("uniform", 2, 300))
@@ -440,9 +460,8 @@ def test_fused_ragged_batch_70b_heads(U, oracle32):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("Hq", [8, 16, 32, 64])
 def test_fused_batch_path_many_heads(U, oracle32, Hq, dtype, capacity):
-    """Nine sequences x 8 KV heads, for every group size: bf16 pools run the selection inside 256-token fused MFMA blocks
-    or, with the larger capacities, inside 512-token and 1024-token streaming MFMA blocks; fp32 pools run select_kernel
-    and 256-token blocks through tok_idx."""
+    """Nine sequences x 8 KV heads, for every group size: the selection inside 256-token fused blocks or, with the larger capacities,
+    inside 512-token and 1024-token streaming blocks."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=9, t_range=(200, 3000), budgets=(700,), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=6, layers=[0], capacity=capacity)
 
@@ -451,8 +470,7 @@ def test_fused_batch_path_many_heads(U, oracle32, Hq, dtype, capacity):
 @pytest.mark.parametrize("budget", [100, 200, 700])
 def test_fused_two_launch_small_blocks(U, oracle32, budget, dtype):
     """More than 64 (sequence, head) pairs with small budgets: too many pairs for the single-launch step, few enough blocks
-    for the two-launch step's fused blocks of 64 tokens (budget 100), 128 tokens (200) and 256 tokens (700) (fp32 pools of
-    64 pairs or more: selection kernel + attention through the positions)."""
+    for the two-launch step's fused blocks of 64 tokens (budget 100), 128 tokens (200) and 256 tokens (700)."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=32, batch=9, t_range=(300, 2500), budgets=(budget,), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=51, layers=[0])
 
@@ -462,9 +480,9 @@ def test_fused_two_launch_small_blocks(U, oracle32, budget, dtype):
 def test_fused_batch_path_two_blocks_per_head(U, oracle32, budget, capacity):
     """Budgets around the 512- and 1024-token blocks of the bf16 streaming kernel: a full block, one token in the next
     block, a block whose last waves have nothing to stream, two full blocks; contexts shorter than the budget too.
-    (Without a capacity budgets up to 1024 run 256-token fused blocks, the others 512-token streaming blocks.)"""
+    (Without a capacity the single launch takes them all, in 128-, 256- and 512-token blocks.)"""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=32, batch=8, t_range=(900, 5000), budgets=(budget,))
-    _fused_case(U, oracle32, wl, seed=8, layers=[0], capacity=capacity)
+    _fused_case(U, oracle32, wl, seed=8, layers=[0], capacity=capacity, single_launch=capacity == 0)
 
 
 @pytest.mark.parametrize("capacity", [0, HALF_CAPACITY, STREAM_CAPACITY])
@@ -472,15 +490,14 @@ def test_fused_batch_path_two_blocks_per_head(U, oracle32, budget, capacity):
 @pytest.mark.parametrize("B", [2, 3, 8])
 def test_fused_batch_with_empty_and_tiny_sequences(U, oracle32, dtype, B, capacity):
     """Sequences without tokens, with one token and with one bucket next to ordinary ones, budgets from 0 to more than the
-    context, in the single-launch step (B = 2: 128-token blocks; B = 3: 256-token blocks; B = 8 without a capacity) and on the
-    batch paths (B = 8 with a capacity: 256-token fused blocks or the streaming kernel; fp32: selection kernel + indirect
-    attention)."""
+    context, in the single-launch step (B = 2: 64- and 128-token blocks; B = 3: 128- and 256-token blocks; B = 8 without a capacity:
+    256-token blocks) and in the streaming kernel (B = 8 with a capacity: 512- and 1024-token blocks; the others with the largest)."""
     toks = [0, 1, 1500, 0, 37, 2300, 5, 0][:B]
     buds = [64, 64, 700, 0, 1000, 0, 3, 9][:B]
     if B == 2:
         toks, buds = [1500, 0], [700, 64]
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=32, batch=B, budgets=(1000,), dtype=dtype)
-    _fused_case(U, oracle32, wl, seed=12, layers=[0], seq_tokens=toks, budgets=buds, capacity=capacity)
+    _fused_case(U, oracle32, wl, seed=12, layers=[0], seq_tokens=toks, budgets=buds, capacity=capacity, single_launch=B < 8 or capacity == 0)
 
 
 @pytest.mark.parametrize("capacity", [0, 2048])
@@ -490,8 +507,8 @@ def test_fused_batch_sequence_boundaries_inside_a_wave(U, oracle32, B, sv_dtype,
     """The score kernel's waves own 8, 16 or 32 consecutive buckets of the concatenated batch (fp32, bf16, E4M3 table)
     and look up the sequences they fall in.  Sequences of a handful of tokens, some without tokens, put several
     boundaries inside one wave; a long sequence in between spans many waves; batch sizes lie on both sides of the
-    lookup's eight-entry step.  (With a capacity of 2048 the two largest batches take the streaming kernel's 2048-token
-    blocks, the others 512-token blocks or the fused kernel.)"""
+    lookup's eight-entry step.  (Up to B = 8 the single launch scores them, each pair its own buckets; from B = 9 on the score kernel, then
+    256-token fused blocks or, for B = 21 and 70 and with the capacity, 1024- and 2048-token streaming blocks.)"""
     rng = np.random.default_rng(100 + B)
     toks = rng.integers(0, 90, size=B)
     toks[rng.integers(0, B, size=max(1, B // 5))] = 0
@@ -507,17 +524,17 @@ def test_fused_batch_sequence_boundaries_inside_a_wave(U, oracle32, B, sv_dtype,
 @pytest.mark.parametrize("budget", [1025, 1500, 2048, 2049, 3000])
 def test_fused_batch_2048_token_blocks(U, oracle32, budget, Hq):
     """20 sequences x 8 KV heads with budgets above 1024: the 1024-token streaming blocks would need two rounds on 256
-    compute units, so the kernel runs 2048-token blocks (two positions per thread), each writing its result directly
-    while one block covers the budget, and through the split-K merge from 2049 tokens on; contexts shorter and longer
-    than the budget."""
+    compute units, so the kernel runs 2048-token blocks (two positions per thread), each writing its result directly; from 2049 tokens on
+    1024-token blocks again (as many rounds, and a split-K merge); contexts shorter and longer than the budget."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=20, t_range=(900, 4500), budgets=(budget,))
     _fused_case(U, oracle32, wl, seed=31, layers=[0])
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("B,budget", [(1, 100), (5, 700), (8, 1000), (8, 1)])
+@pytest.mark.parametrize("B,budget", [(1, 200), (5, 700), (8, 1000), (8, 1), (1, 100)])
 def test_fused_single_launch_two_heads_per_merging_block(U, oracle32, B, budget, dtype):
-    """8 query heads per KV head and fewer than eight blocks that attend: a merging block takes two heads."""
+    """8 query heads per KV head and fewer than eight blocks that attend: a merging block takes two heads.  (One sequence, budget 100: two
+    blocks attend, fewer than half the heads, and eight of the pair's 32 blocks merge a head each.)"""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=64, batch=B, t_range=(700, 2500), budgets=(budget,), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=35, layers=[0])
 
@@ -532,8 +549,8 @@ def test_fused_single_launch_two_tiles_per_wave(U, oracle32, B, budget, Hq):
 
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
-    """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20), a last tile of one token and of sixteen, a
-    second block of one token, contexts shorter than the budget."""
+    """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20 with budget 1500), a last tile of one token and of
+    sixteen, a third block of one token (B = 20, budget 2049: 1024-token blocks), contexts shorter than the budget."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(900, 4500), budgets=(budget,), dtype="f32")
     _fused_case(U, oracle32, wl, seed=33, layers=[0])
 
@@ -553,11 +570,63 @@ def test_fused_batch_of_hundreds_of_short_sequences(U, oracle32):
 @pytest.mark.parametrize("capacity", [0, HALF_CAPACITY, STREAM_CAPACITY])
 @pytest.mark.parametrize("dtype,budget", [("f32", 700), ("bf16", 2), ("bf16", 256), ("bf16", 257), ("bf16", 5000)])
 def test_fused_batch_path_edges(U, oracle32, dtype, budget, capacity):
-    """Batch paths (fp32: the VALU kernel through tok_idx; bf16: 256-token fused blocks, and the streaming kernel with the
-    large capacity or the 5000-token budget) with a budget no bucket fits (empty selections), budgets at and just past
-    one 256-token block, and a budget above every context length (all tokens retrieved)."""
+    """The single launch (no capacity: blocks of 64, 128 and 256 tokens) and the streaming kernel (a capacity, or the 5000-token budget) with a
+    budget no bucket fits (empty selections), budgets at and just past one 256-token block, and a budget above every context
+    length (all tokens retrieved)."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=32, batch=8, t_range=(150, 2500), budgets=(budget,), dtype=dtype)
-    _fused_case(U, oracle32, wl, seed=9, layers=[0], capacity=capacity)
+    _fused_case(U, oracle32, wl, seed=9, layers=[0], capacity=capacity, single_launch=capacity == 0)
+
+
+@pytest.mark.parametrize("dtype,log2_tokens", [("f32", 23), ("bf16", 24)])
+def test_fused_pool_beyond_the_streaming_kernels_addresses(U, oracle32, dtype, log2_tokens):
+    """A pool of 2^23 fp32 (2^24 bf16) tokens is past the streaming kernel's 32-bit row offsets: with 64 pairs or more the selection runs in
+    a launch of its own and attention reads the pool through the positions.  65 sequences of one KV head: one holds nearly
+    all tokens, the ones after it start 4 GB into the pool, some are empty or short.  The reference rows are gathered on the GPU."""
+    B, Hq, D, budget = 65, 4, 128, 700
+    total = (1 << log2_tokens) + 12345
+    toks = np.random.default_rng(4).integers(0, 2000, size=B)
+    toks[[3, 40]] = 0
+    toks[[5, 41]] = 1
+    toks[20] = 0
+    toks[20] = total - toks.sum()
+    rng = np.random.default_rng(log2_tokens)
+    lens = []
+    for t in toks:
+        cut = np.unique(np.concatenate([[0, t], rng.integers(0, t + 1, size=min(int(t), max(int(t) // 30, int(t) if t < 3 else 1), 40000))])) if t else np.zeros(1, int)
+        lens.append(np.diff(cut).astype(np.int32))
+    cu_tok, cu_sent = (np.concatenate([[0], np.cumsum(x)]).astype(np.int32) for x in (toks, [len(x) for x in lens]))
+    S = int(cu_sent[-1])
+    wl = gen.CFG0.scaled(n_layers=1, n_q_heads=Hq, n_kv_heads=1, dtype=dtype)
+    ctx = U.make_ctx(wl, total, S, budget, batch=B)
+    g = torch.Generator(device=U.DEV).manual_seed(9)
+    K, V = (torch.empty(1, 1, total, D, dtype=wl.torch_dtype, device=U.DEV).normal_(generator=g) for _ in range(2))
+    q = torch.empty(B, Hq, D, dtype=wl.torch_dtype, device=U.DEV).normal_(generator=g)
+    sv = torch.empty(1, 1, S, D, device=U.DEV).normal_(generator=g)
+    off = np.concatenate([gen.offsets_of(x) for x in lens]).astype(np.int32)
+    sent_len = np.concatenate(lens)
+    out, lse = torch.full((B, Hq, D), 7.0, device=U.DEV), torch.full((B, Hq), 7.0, device=U.DEV)
+    tok_idx, n_tok = U.empty_i32(B, 1, budget, fill=-1), U.empty_i32(B, 4, fill=-1)[:, :1].contiguous()
+    d = [U.i32(x) for x in (cu_tok, cu_sent, off, sent_len, [budget] * B)]
+    _say("pool of", total, dtype, "tokens,", S, "buckets")
+    ctx.decode_step(0, B, q, q, K, V, total, sv, S, *d, out, lse, tok_idx, n_tok)
+    torch.cuda.synchronize()
+    o, ls, ti, nt = out.cpu().numpy(), lse.cpu().numpy(), tok_idx.cpu().numpy(), n_tok.cpu().numpy()
+    sv_np, ties = sv[0].cpu().numpy(), 0
+    for b in range(B):
+        s0, s1 = cu_sent[b], cu_sent[b + 1]
+        sc_gpu = U.gpu_scores(ctx, 0, q[b], sv, S, 1)[:, s0:s1]
+        ties += U.check_selection(oracle32, oracle32.score(U.np_of(q[b]), sv_np[:, s0:s1]), sc_gpu, off[s0 + b: s1 + b + 1], sent_len[s0:s1],
+                                  budget, ti[b], nt[b], what=f"sequence {b}")
+        rows = torch.as_tensor(np.where(ti[b, 0] < 0, 0, ti[b, 0]).astype(np.int64) + int(cu_tok[b]), device=U.DEV).clamp_(max=total - 1)
+        Ks, Vs = (U.np_of(X[0, :, rows]) for X in (K, V))
+        o_ref, l_ref = oracle32.attend(U.np_of(q[b]), Ks, Vs, nt[b].astype(np.int32))
+        _same_as_oracle(o[b], o_ref, ATT_TOL[dtype], b)
+        _same_as_oracle(ls[b], l_ref, ATT_TOL[dtype], b)
+    assert ties <= U.MAX_TIES_PER_TEST and int(nt.max()) > budget // 2
+    out2 = torch.zeros_like(out)
+    ctx.decode_step(0, B, q, q, K, V, total, sv, S, *d, out2, None, None, None)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2)
 
 
 def test_attend_batch_path_direct_rows(U, oracle32):
@@ -604,7 +673,7 @@ def test_full_size_cfg2_128k_sampled_layers(U, oracle32):
     _fused_case(U, oracle32, wl, seed=1, layers=[0, 1])
     # the same sequence through the streaming kernel (a context sized for budgets up to 20000 takes 1024-token blocks)
     _fused_case(U, oracle32, wl.scaled(n_layers=1), seed=1, layers=[0], capacity=20000)
-    # and with a budget of 8192 tokens: 256-token fused blocks, each full of retrieved tokens
+    # and with a budget of 8192 tokens: the single launch's 256-token blocks, each full of retrieved tokens
     _fused_case(U, oracle32, wl.scaled(n_layers=1, budgets=(8192,)), seed=1, layers=[0])
 
 
@@ -783,7 +852,7 @@ def test_attend_carries_values_that_are_not_finite(U, oracle32, dtype, budget):
 
 
 @pytest.mark.parametrize("B,dtype,Hq,budget,capacity", [
-    (1, "bf16", 32, 1025, 0), (1, "f32", 32, 513, 0), (1, "bf16", 64, 100, 0),          # one launch: 64-token blocks, mergers of two heads
+    (1, "bf16", 32, 1025, 0), (1, "f32", 32, 513, 0), (1, "bf16", 64, 200, 0),          # one launch: 64-token blocks, mergers of two heads
     (3, "f32", 8, 1025, 0), (8, "bf16", 32, 1025, 0),                                   # of 256 tokens, of 512 (two tiles a wave)
     (9, "bf16", 16, 65, 0), (9, "f32", 32, 257, 0), (9, "bf16", 32, 513, 0),            # two launches: blocks of 64, 128, 256 tokens
     (9, "bf16", 32, 1009, 0), (9, "f32", 64, 257, STREAM_CAPACITY), (20, "bf16", 8, 1281, 0)])    # streaming: 512, 1024, 2048
@@ -992,12 +1061,12 @@ def test_e4m3_table_every_code_scores_like_the_oracle(U, oracle32):
 
 @pytest.mark.parametrize("dtype,B", [("bf16", 1), ("f32", 1), ("bf16", 3)])
 def test_fused_many_buckets_per_sequence(U, oracle32, dtype, B):
-    """More than 1024 buckets per sequence: the step runs 128-token split blocks (two 64-position pieces per block,
-    buckets spanning both pieces) and the selection with up to 6 buckets per thread in registers."""
+    """More than 1024 buckets per sequence: the selection with up to 6 buckets per thread in registers, in 64-token blocks and, for three
+    sequences, in 128-token blocks (two 64-position pieces, buckets spanning both)."""
     wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(5800, 6400), budgets=(700,), len_dist=("uniform", 1, 3), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=41, layers=[0])
     wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(9000, 9100), budgets=(130,), len_dist=("uniform", 1, 200), dtype=dtype)
-    _fused_case(U, oracle32, wl, seed=42, layers=[0])          # few, long buckets: S small, 64-token blocks; long spans
+    _fused_case(U, oracle32, wl, seed=42, layers=[0])          # few, long buckets: long spans
     wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(40000, 40100), budgets=(1000,), len_dist=("uniform", 1, 30), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=43, layers=[0])          # S > 2048 with buckets that span the 64-position pieces
     wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(16000, 16500), budgets=(600,), len_dist=("uniform", 1, 3), dtype=dtype)
@@ -1012,7 +1081,7 @@ _LEN_DISTS = [("uniform", 1, 3), ("uniform", 8, 40), ("lognormal", 20, 0.7, 3, 1
 @pytest.mark.parametrize("sweep_seed", [1, 7])
 def test_fused_step_seeded_shape_sweep(U, oracle32, sweep_seed):
     """The fused step over a seeded sample of (batch, group size, pool type, table type, budget, context range, bucket
-    length distribution): every launch path (single launch, fused and streaming blocks of the two-launch step, the fp32 batch path) with
+    length distribution): every launch path (single launch, fused and streaming blocks of the two-launch step) with
     shapes no hand-written case has."""
     rng = np.random.default_rng(sweep_seed)
     for it in range(14):
@@ -1054,7 +1123,7 @@ def test_chain_seeded_shape_sweep(U, oracle32, sweep_seed):
 def test_repeated_launches_reproduce_their_results(U, oracle32, case):
     """The split-K partials and the arrival counter travel between blocks inside one launch: many back-to-back launches
     (nothing but the launches themselves between two checks) must keep reproducing the first result of the same inputs --
-    bit for bit where the summation order is fixed, within the attention tolerance for the bf16 batch kernel, whose waves
+    bit for bit where the summation order is fixed, within the attention tolerance for the bf16 streaming kernel, whose waves
     take their tiles in arrival order.  (A missing wait for the partial stores before the arrival showed up as wrong outputs
     about once in 1600 launches of the full-size batch.)"""
     wl, iters, exact = {

@@ -73,7 +73,9 @@ def test_token_importance_with_logits_far_apart(U, oracle32, dtype, Hq, N, T):
     q_obs = gen.queries(Hq, N, 128, wl.torch_dtype, seed=4, device=U.DEV).view(1, Hq, N, 128) * 8
     alpha = _gpu_importance(U, U.make_ctx(wl, T, len(lens), 16), q_obs, K, T, N).cpu().numpy()
     ref = oracle32.token_importance(U.np_of(q_obs[0]), U.np_of(K[0]))
-    assert np.all(np.abs(alpha[0] - ref) <= 1e-3 * ref + 1e-6 * ref.max())     # exponents of several hundred carry fewer fraction bits
+    # both sides sum 128 products in fp32 in partial sums up to 3500, each rounded by up to 2^-13: about 4e-4 in a logit (128 roundings of
+    # random sign), over sqrt(D) 4e-5 of a probability, four times that at the worst of 10^6; measured 1e-4 (bf16), 1.8e-4 (fp32)
+    assert np.all(np.abs(alpha[0] - ref) <= 4e-4 * ref + 1e-6 * ref.max())
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -133,9 +135,8 @@ FULL_IMP_CASES = [("bf16", 32, 8, 32, 32768), ("f32", 32, 8, 32, 32768), ("bf16"
 
 @pytest.mark.parametrize("dtype,Hq,H,N,T", FULL_IMP_CASES, ids=[f"{c[0]}-Hq{c[1]}-H{c[2]}-N{c[3]}-T{c[4]}" for c in FULL_IMP_CASES])
 def test_token_importance_and_retention_at_benchmark_size(U, oracle32, dtype, Hq, H, N, T):
-    """The size the retention benchmark times (32768 tokens, 32/8 heads, a 32-token window: 64 key chunks of 512 per
-    head) and prompts beyond it, where the per-row combine walks its chunks in several strides of 64 (40100 tokens: 79
-    chunks; 70001: 137) and most sweeps lie wholly before the window (no masking): one layer against the oracle, then
+    """The size the retention benchmark times (32768 tokens, 32/8 heads, a 32-token window) and longer prompts of few heads, whose rows are
+    combined from up to 314 blocks of keys; most stages lie wholly before the window (no masking): one layer against the oracle, then
     the k = 4096 best tokens by the oracle's rule on the GPU's own importance, bit for bit."""
     _say("importance at size", dtype, Hq, H, N, T)
     wl = gen.CFG3.scaled(n_layers=1, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype=dtype)

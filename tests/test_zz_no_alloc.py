@@ -76,7 +76,7 @@ def test_noalloc_step_equals_context_step_two_calls_second_smaller(U):
     _same(a, b, exact=True)
     a, b = _both_ways(U, gen.CFG4.scaled(n_layers=1, batch=3, t_range=(500, 4000), budgets=(512,)), seed=8, sentinel=6.0)
     _same(a, b, exact=True)
-    print("noalloc: batch of 12 on the streaming kernel, fp32 batch of 9 through tok_idx", flush=True)
+    print("noalloc: batch of 12 on the streaming kernel, fp32 batch of 9 in fused blocks", flush=True)
     a, b = _both_ways(U, gen.CFG4.scaled(n_layers=1, n_q_heads=8, batch=12, t_range=(900, 5000), budgets=(1500,)), seed=9,
                       sentinel=7.0)
     _same(a, b, exact=False)
