@@ -115,8 +115,11 @@ int skv_set_single_launch(skv_ctx* ctx, int32_t enable);
  * tok          dev  [T]                      seg_id      dev [T]
  * term_bitmap  dev  [ceil(vocab / 32)]       sent_off    dev [max_sentences + 1]
  * n_sent_dev   dev  [1], receives S          sent_len    dev [max_sentences]
- * n_sent_host  host [1] or NULL.  Non-NULL: the call waits for the stream, stores S there and returns
- *              SKV_ECAPACITY if S > max_sentences.  Buckets beyond max_sentences are never written
+ * n_sent_host  host [1] or NULL.  Non-NULL: the call waits until all results are written, and with them everything that was
+ *              queued on the stream before, stores S there and returns SKV_ECAPACITY if S > max_sentences.  (For prompts of
+ *              up to 131072 tokens over up to 491520 ids the kernel itself reports S to the host: the stream need not be
+ *              idle yet when the call returns, and SKV_EHIP is returned only for a failure that keeps S from arriving; any
+ *              other shows at the next synchronisation.)  Buckets beyond max_sentences are never written
  *              (n_sent_dev still receives the true S).  NULL: fully asynchronous.
  * Errors: SKV_EINVAL (null pointers, T < 0, vocab <= 0), SKV_ECAPACITY (T > max_tokens). */
 int skv_segment(skv_ctx* ctx, const int32_t* tok, int32_t T, const uint32_t* term_bitmap, int32_t vocab,
@@ -221,9 +224,10 @@ int skv_gather(skv_ctx* ctx, int32_t layer, const void* K_pool, const void* V_po
  * h = j / G; lse[j] = log sum_i exp(logit_i) (natural log).  n_tok[h] == 0 gives out = 0 and lse = -inf.  A NaN among a
  * head's logits (or an infinite logit) gives NaN in its out and lse, here, in skv_decode_step and through skv_merge_lse.
  * Arithmetic: logits, maxima, normalisers and all sums are fp32.  With fp32 K/V the softmax weights stay fp32.  With
- * bf16 K/V the products run on the matrix cores: the weights exp(logit - max) are rounded to bf16 (nearest even)
- * before P.V, and the normaliser sums those rounded weights, so out is exactly the weighted mean the rounded weights
- * define (max-abs error against fp32 weights below 2e-2 for unit-variance values; the same holds for skv_decode_step).
+ * bf16 K/V the weights exp(logit - max), max being the largest logit of the tokens that a wave has at hand, are rounded to
+ * bf16 (nearest even) before P.V, and the normaliser sums those rounded weights, so out is exactly the weighted mean the
+ * rounded weights define (max-abs error against fp32 weights below 2e-2 for unit-variance values; the same holds for
+ * skv_decode_step).  Both types run on the matrix cores.
  * q_attn dev [Hq][D] kv_dtype;  K_sel, V_sel dev [Hkv][budget][D];  out dev [Hq][D] fp32;
  * lse dev [Hq] fp32 or NULL. */
 int skv_attend(skv_ctx* ctx, const void* q_attn, const void* K_sel, const void* V_sel, const int32_t* n_tok,
@@ -234,17 +238,21 @@ int skv_attend(skv_ctx* ctx, const void* q_attn, const void* K_sel, const void* 
  * batch of B sequences concatenated along the token axis and the bucket axis.  The retrieved tokens
  * are read straight from the HBM pool (no K_sel/V_sel copy).  Results equal skv_score + skv_select +
  * skv_gather + skv_attend run per sequence: the selection bit for bit, out / lse up to the order of the
- * floating-point sums.
- * Launches per call (P = B * Hkv pairs of sequence and KV head, all sizes from the descriptor's max_budget):
- *   - ONE, when P <= 64 and P * 2^k blocks (2^k the largest power of two with P * 2^k <= 256 compute units) cover the
- *     budget in attention blocks of 128 or 256 tokens (2^k * 256 >= max_budget) and 2^k >= G: the blocks first score the buckets of their pair
- *     between them, pass the scores and later the partial attention results to each other inside the kernel, select
+ * floating-point sums and, in bf16, to which tokens' largest logit a weight is rounded relative to.
+ * Launches per call (P = B * Hkv pairs of sequence and KV head, G query heads each, all sizes from the descriptor's max_budget or
+ * the tighter bound of skv_set_budget_hint):
+ *   - ONE, when P <= 64 and the pair's 2^k blocks (2^k the largest power of two with P * 2^k <= 256 compute units) cover the
+ *     budget in attention blocks of 64, 128 or 256 tokens, in bf16 also of 512 where three quarters of the blocks attend and
+ *     the table takes at most half the bytes of the retrieved rows, and G <= 2 * 2^k: the blocks first score the buckets of
+ *     their pair between them, pass the scores and later the partial attention results to each other inside the kernel, select
  *     and attend.  The waits inside the kernel are bounded, see skv_set_wait_limit;
- *   - TWO otherwise for bf16 pools (scores; selection + attention in 256-token blocks, or in streaming blocks of 512,
+ *   - TWO otherwise (scores; selection + attention in blocks of 64 to 256 tokens, or in streaming blocks of 512,
  *     1024 or 2048 tokens when P * ceil(max_budget / 256) exceeds the compute units);
- *   - THREE for fp32 pools with P >= 64 (scores; selection; attention through the positions).
- * In the streaming kernel the order of the floating-point sums can depend on how the hardware schedules a block's
- * waves, so the last bits of out / lse can differ between two identical calls; all other forms are reproducible.
+ *   - THREE for P >= 64 and pools of 2^23 fp32 or 2^24 bf16 tokens or more where ONE does not apply (scores; selection; attention
+ *     through the positions).
+ * In the streaming kernel on bf16 pools the order of the floating-point sums, and what a weight is rounded relative to, depend on how
+ * the hardware schedules a block's waves, so out / lse can differ between two identical calls (about 1e-3 of out); all
+ * other forms are reproducible.
  * q_score, q_attn  dev [B][Hq][D] kv_dtype (may alias)
  * K_pool, V_pool   dev [L][Hkv][T_total][D]        semvec dev [L][Hkv][S_total][D]
  * cu_tok   dev [B+1]  token offset of each sequence in the pool (cu_tok[0] == 0, cu_tok[B] == T_total)

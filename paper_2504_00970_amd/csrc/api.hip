@@ -495,7 +495,7 @@ static int decode_step_launch(Ctx& c, int32_t layer, int32_t B, const void* q_sc
     const char* Vl = (const char*)V_pool + pool_off;
     const int pairs = B * c.d.n_kv_heads;
     hipError_t e;
-    // Few (sequence, head) pairs: the whole step in one launch, when its attention blocks (128 or 256 tokens) fit the
+    // Few (sequence, head) pairs: the whole step in one launch, when its attention blocks (64 to 512 tokens) fit the
     // chip at once beside each other; launch_step decides.
     if (c.single_launch && pairs <= skv::kStepMaxPairs && S_total > 0) {
         bool launched = false;

@@ -912,8 +912,8 @@ hipError_t launch_gather(Ctx* c, const void* K_layer, const void* V_layer, int32
 //               scores are a few KB in L2, and it saves a launch plus a round trip through tok_idx) and reads
 //               K/V straight from the pool (skv_decode_step).
 //   1. every K and V piece is requested up front on clamped addresses (no load waits for a bounds test);
-//   2. per wave: logits, max, weights, P V;   3. one barrier, then the block's sums relative to its common max;
-//   4. the un-normalised partial (m, l, acc) goes to the workspace with write-through stores; the last
+//   2. per wave: logits, max, weights, P V;   3. one barrier, then the block's sums relative to a common reference;
+//   4. the un-normalised partial (reference, normaliser, sums) goes to the workspace with write-through stores; the last
 //      block to arrive for the (sequence, KV head) -- a device-scope counter, no spinning -- merges the
 //      partials with one round of independent loads and an online-softmax merge (kStep: see there).  A split that is
 //      the only one writes the result.
@@ -1144,7 +1144,7 @@ struct AttArgs {
     unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
     unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
     int32_t score_stride;
-    unsigned long long* step_part;    // [blocks][G][kHeadDim + 2] (value, tag) words: a block's partial sums, then (max, normaliser)
+    unsigned long long* step_part;    // [blocks][G][kHeadDim + 2] (value, tag) words: a block's partial sums, then (reference, normaliser)
     int32_t wait_limit;       // rounds of polling before a block gives up
     unsigned int* err_dev;    // set to 1 by a block that gave up
     unsigned int* err_host;   // the same word in pinned host memory (device address), nullable
@@ -1173,8 +1173,8 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
     return POOL ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
 }
 
-// CHUNK = retrieved tokens per block: 64 for the latency-bound single-sequence step (most blocks in
-// flight), 256 for batches (fewer partials and arrivals per head, more loads in flight per block).
+// CHUNK = retrieved tokens per block, a tile of 16 for each of CHUNK / 16 waves (512: two tiles a wave): the smallest whose blocks all run
+// at once, see launch_step, launch_select_attend and launch_attend.
 template <int EB, int G, int MODE, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     using X = Tile<EB>;
@@ -1307,7 +1307,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         n = min(ld_const(a.n_tok, bh), MODE == kDirect ? a.row_stride : a.idx_stride);
     }
     // kStep: every block of the pair that ran the selection (and so used the epoch it read at its start) tells block 0 so
-    // in the first (max, tag) word of its partial: the attending blocks with their partial, the others as soon as they
+    // in the (reference, tag) word of its partial: the attending blocks with their partial, the others as soon as they
     // know that they hold no retrieved tokens.  Block 0 advances the epoch only after it has seen all of them, so that no
     // block of this launch can read the advanced epoch.
     auto presence = [&]() {
@@ -1489,9 +1489,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         // ---- 5'. merge without an arrival counter ---------------------------------------------------------------
         // Block m of the pair merges 128 >> lg_merge dims of query head m >> lg_merge, or two heads.  Thread (grp, col) -- consecutive
         // lanes on consecutive words of a partial row -- reads dim `col` of the partials of the splits grp, grp + groups, ...
-        // (value and tag in one word) and their (max, normaliser) words, again and again until all carry the launch tag
+        // (value and tag in one word) and their (reference, normaliser) words, again and again until all carry the launch tag
         // (bounded; no barrier, no sleep: a wave leaves as soon as its own words are there), folds them into a running
-        // (max, normaliser, output), and the groups meet once in LDS.  No block waits for a store
+        // (reference, normaliser, output), and the groups meet once in LDS.  No block waits for a store
         // acknowledgement and nothing is counted.
         if (split >= merging_blocks(G, a.lg_merge)) return;
         const int lg_dims = 7 - a.lg_merge, groups = kBlockThreads >> lg_dims;                            // 4 groups of 256 dims .. 32 of 32
@@ -1657,14 +1657,13 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Streaming form of the bf16 attention for batches.  Measured on the 1024-thread kernel above with 16 sequences
-// x 8 heads: all blocks start together, load together (memory saturated for 5 us) and then compute together
+// Streaming form of the attention for batches.  Measured on the 1024-thread kernel above with 16 sequences
+// x 8 heads in bf16: all blocks start together, load together (memory saturated for 5 us) and then compute together
 // (memory idle for 7 us), twice.  Here a wave owns 64 consecutive retrieved tokens and walks them in four 16-token
 // MFMA tiles -- the next tile's K and V rows are requested as soon as the current ones have been consumed (K by the
 // logit MFMAs, V by its copy to LDS) -- carrying a running (max, normaliser, output) per head as in flash decoding;
 // all blocks of the launch are resident at once (16 waves per CU, each with 8 KB in flight).
-// Tile arithmetic is that of the kernel above: S^T = K Q^T with K rows as A fragments, P rounded to bf16 with the
-// normaliser summing the rounded weights, V through a wave-private LDS tile into B fragments.
+// Tile arithmetic is that of the kernel above (Tile).
 // A block is 16 waves and CHUNK = 1024 (or 512, or 2048) retrieved tokens of one (sequence, KV head).  It first runs the
 // selection itself from the scores (as the single-sequence kernel does, redundantly with the head's other blocks) and
 // keeps the pool rows of its positions in LDS: no selection launch, no tok_idx round trip, two partials per 2048-token
@@ -2002,7 +2001,7 @@ static AttArgs att_common(Ctx* c, const void* q, const void* Kbase, const void* 
     return a;
 }
 
-// Batches with many (sequence, head) pairs fill the GPU with 256-token blocks; below that 128-token blocks.
+// Many (sequence, head) pairs fill the GPU with 256-token blocks; below that 128-token blocks.
 static bool wide_chunks(const Ctx* c, const SeqView& v) { return v.B * c->d.n_kv_heads >= kWideChunkMinHeads; }
 
 hipError_t launch_attend(Ctx* c, const void* q, const void* K_sel, const void* V_sel, int32_t row_stride,
@@ -2065,11 +2064,9 @@ hipError_t launch_select_attend(Ctx* c, const void* q, const void* K_layer, cons
     AttArgs a = att_common(c, q, K_layer, V_layer, v, out, lse);
     a.score = score; a.sent_off = sent_off; a.sent_len = sent_len;
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
-    // Every split block of a head repeats the selection; with thousands of buckets per sequence that repetition
-    // (bucket loads from L2, histogram passes) outweighs the shorter K/V phase of 64-token blocks.
-    // bf16: one block per compute unit fits (value tiles + selection histograms in LDS), so the block size is the
+    // One block per compute unit fits (value tiles + selection histograms in LDS), so the block size is the
     // smallest whose blocks all run at once; a second round of blocks costs more than the larger blocks' longer K/V phase
-    // (4 sequences of 32K, 8 heads, budget 2048: 25.9 us in 128-token blocks, 17 in 256-token blocks).
+    // (4 sequences of 32K, 8 heads, budget 2048, bf16: 25.9 us in 128-token blocks, 17 in 256-token blocks).
     const int pairs = v.B * c->d.n_kv_heads;
     auto blocks = [&](int chunk) { return pairs * ((c->budget_cap + chunk - 1) / chunk); };
     if (blocks(kAttChunkMid) > c->n_cu) {

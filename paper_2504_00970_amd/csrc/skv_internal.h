@@ -31,22 +31,23 @@ constexpr int kBlockThreads = 1024;   // select, attention and the fused select+
 constexpr int kGatherRowsPerBlock = 64;
 constexpr int kGatherThreads = 256;
 
-constexpr int kAttChunk = 64;         // tokens per split-K block, single-sequence step
-constexpr int kAttChunkMid = 128;     // tokens per split-K block of the single-sequence step when a sequence has many buckets
-constexpr int kMidChunkMinSentences = 1024;
-constexpr int kAttChunkWide = 256;    // tokens per split-K block when many (sequence, head) pairs fill the GPU
-constexpr int kWideChunkMinHeads = 64;   // (sequences x KV heads) from which the fp32 batch path is used
+constexpr int kAttChunk = 64;         // tokens per split-K block: the smallest (partial slots are counted in it) ...
+constexpr int kAttChunkMid = 128;     // ... and the larger ones, where a pair has too few blocks; the single launch also takes 512 in bf16
+constexpr int kAttChunkWide = 256;
+constexpr int kMidChunkMinSentences = 1024;   // buckets per sequence from which the two-launch form takes no 64-token blocks
+constexpr int kWideChunkMinHeads = 64;   // (sequences x KV heads) from which skv_attend takes 256-token blocks, and a pool that cannot be
+                                         // streamed is attended through the positions
 constexpr int kComputeUnits = 256;       // MI355X; the context takes the device's own count when it can be read
 // single-launch decode step: at most kStepMaxPairs (sequence, head) pairs and kStepMaxBlocks blocks per launch
 constexpr int kStepPairBits = 6;
 constexpr int kStepMaxPairs = 1 << kStepPairBits;
 constexpr int kStepMaxBlocks = 256;
 constexpr int kStepEpochStride = 16;     // 32-bit words between the epoch counters of two pairs (one 64-byte line each)
-constexpr int kStepPartWords = kHeadDim + 2;   // 64-bit words per query head of a block's partial: D sums, max, normaliser
+constexpr int kStepPartWords = kHeadDim + 2;   // 64-bit words per query head of a block's partial: D sums, reference, normaliser
 constexpr int kStepWaitLimit = 200000;   // default bound on the polling rounds of a waiting block (a round is about a microsecond)
-// bf16 decode step: the fused kernel's block size (64, 128, 256 tokens) is the smallest whose blocks, (sequence, KV head)
+// decode step in two launches: the fused kernel's block size (64, 128, 256 tokens) is the smallest whose blocks, (sequence, KV head)
 // pairs x ceil(max_budget / size), all fit the chip at once (one block per compute unit); if even the 256-token blocks do
-// not, the streaming kernel's 512- or 1024-token blocks
+// not, the streaming kernel's 512-, 1024- or 2048-token blocks
 
 struct Ctx {
     skv_desc d;
@@ -61,7 +62,7 @@ struct Ctx {
     size_t ws_bytes;
     unsigned long long* seg_part;  // [ceil(max_tokens / kSegTokPerBlock)] packed (count << 32 | last_end)
     float* att_part;        // [max_batch * Hq][max_splits][D] un-normalised partial outputs
-    float* att_ml;          // [max_batch * Hq][max_splits][2] (running max in log2 units, sum)
+    float* att_ml;          // [max_batch * Hq][max_splits][2] (reference in log2 units, sum)
     unsigned int* att_counter;  // [max_batch * Hkv] arrivals per (sequence, KV head); zero between calls
     float* f_score;         // [Hkv][max_sentences] scores of the fused path
     int32_t* f_sel_sent;    // [max_batch * Hkv][max_sel]     selection of the batch path
@@ -133,7 +134,7 @@ hipError_t launch_select_attend(Ctx* c, const void* q, const void* K_layer, cons
                                 const int32_t* sent_off, const int32_t* sent_len, const SeqView& v, float* out,
                                 float* lse, int32_t* tok_idx_out, int32_t* n_tok_out);
 
-// The whole step in one launch (scores by the blocks of each pair, a per-pair ticket barrier, selection, attention) when
+// The whole step in one launch (scores by the blocks of each pair, passed on as tagged words, selection, attention) when
 // its grid fits the chip at once; *launched is false (and nothing was launched) when the shapes do not allow it.
 hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const void* semvec_layer, const void* K_layer,
                        const void* V_layer, const int32_t* sent_off, const int32_t* sent_len, const SeqView& v, float* out,
