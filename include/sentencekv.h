@@ -117,9 +117,8 @@ int skv_set_single_launch(skv_ctx* ctx, int32_t enable);
  * n_sent_dev   dev  [1], receives S          sent_len    dev [max_sentences]
  * n_sent_host  host [1] or NULL.  Non-NULL: the call waits until all results are written, and with them everything that was
  *              queued on the stream before, stores S there and returns SKV_ECAPACITY if S > max_sentences.  (For prompts of
- *              up to 131072 tokens over up to 491520 ids the kernel itself reports S to the host: the stream need not be
- *              idle yet when the call returns, and SKV_EHIP is returned only for a failure that keeps S from arriving; any
- *              other shows at the next synchronisation.)  Buckets beyond max_sentences are never written
+ *              up to 131072 tokens over up to 491520 ids the kernel itself reports S to the host, and the stream need not be
+ *              idle yet when the call returns.  A failure of that work is returned as SKV_EHIP.)  Buckets beyond max_sentences are never written
  *              (n_sent_dev still receives the true S).  NULL: fully asynchronous.
  * Errors: SKV_EINVAL (null pointers, T < 0, vocab <= 0), SKV_ECAPACITY (T > max_tokens). */
 int skv_segment(skv_ctx* ctx, const int32_t* tok, int32_t T, const uint32_t* term_bitmap, int32_t vocab,

@@ -53,18 +53,19 @@ constexpr unsigned int kNoCount = 0xffffffffu;
 // The kernel stores the count after it has written all its results back, and it starts after everything queued before
 // it: once the word is there, the stream's work up to this call is done.  Polling a word of host memory costs about a
 // microsecond where a copy and a stream synchronisation cost 15.  The stream is asked every few thousand reads, so that a
-// launch that failed ends the wait: -1 unless the word arrived.
+// launch that failed ends the wait, and once more at the end (no measurable time), so that a failure of earlier work is reported as a
+// synchronisation would: -1 then, or if the word does not arrive.
 int32_t wait_for_count(Ctx& c) {
     for (;;) {
-        for (int i = 0; i < 4096; ++i) {
-            const unsigned int v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
-            if (v != kNoCount) return (int32_t)v;
-        }
+        unsigned int v = kNoCount;
+        for (int i = 0; i < 4096 && v == kNoCount; ++i) v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
         const hipError_t e = hipStreamQuery(c.stream);
-        if (e == hipErrorNotReady) continue;
-        const unsigned int v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
-        if (e != hipSuccess) (void)hipGetLastError();
-        return e == hipSuccess && v != kNoCount ? (int32_t)v : -1;
+        if (e != hipSuccess && e != hipErrorNotReady) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        if (e == hipSuccess) v = __atomic_load_n(c.n_sent_host, __ATOMIC_ACQUIRE);
+        if (v != kNoCount || e == hipSuccess) return v != kNoCount ? (int32_t)v : -1;
     }
 }
 
