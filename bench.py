@@ -236,8 +236,7 @@ def run_single_sequence(args, wl, budget):
     # of the layer), so the dominant kernel's launch is the layer: its algorithmic bytes are the step's, its duration
     # the per-layer time of the timed region (launch to launch, HIP events on the launching stream).
     copy_peak = measured_copy_peak(dev)
-    roofline = dict(bound="hbm", kernel="attend_kernel<bf16, G, single-launch step, 128-token blocks>" if wl.dtype == "bf16"
-                    else "attend_kernel<fp32, G, single-launch step, 128-token blocks>",
+    roofline = dict(bound="hbm", kernel="attend_kernel<%s, G, single-launch step>" % ("bf16" if wl.dtype == "bf16" else "fp32"),
                     achieved=round(gbps, 1), peak=HBM_PEAK_GBPS, unit="GB/s", frac=round(gbps / HBM_PEAK_GBPS, 4),
                     traffic=None if sv16 else measured_traffic(wl.name, "decode_step_kernel"),
                     bytes_per_launch=int(bytes_layer["total"]), us_per_launch=round(us_per_layer, 3),
