@@ -152,7 +152,11 @@ int skv_build_semvec_layers(skv_ctx* ctx, const void* K_pool, int32_t T, const i
  * work   dev scratch of at least skv_token_importance_work_bytes(ctx, T, N) bytes (caller-owned; nothing is kept in
  *        it between calls).  G * N <= 256.  Asynchronous.
  * Errors: SKV_EINVAL (null / misaligned pointers, N < 1, N >= T, work too small), SKV_ECAPACITY (T > max_tokens,
- * G * N > 256).  skv_token_importance_work_bytes returns -1 for arguments the call would reject. */
+ * G * N > 256).  skv_token_importance_work_bytes returns -1 for arguments the call would reject.
+ * bf16 prompts whose (layer, head) fits the GPU run as one sweep over the keys whose blocks wait for each other inside the
+ * kernel, at most the polls of skv_set_wait_limit and never more than 8000; where they run out (blocks kept from starting by other work on
+ * the GPU) the same call does the work in two passes that wait for nothing, and nothing fails.  skv_set_single_launch(ctx, 0) always takes the two
+ * passes. */
 int64_t skv_token_importance_work_bytes(const skv_ctx* ctx, int32_t T, int32_t N);
 int skv_token_importance(skv_ctx* ctx, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work,
                          int64_t work_bytes);

@@ -71,7 +71,7 @@ int32_t wait_for_count(Ctx& c) {
 
 // ---- workspace: one block of device memory, carved the same way whether skv_create allocated it or it is the static
 // scratch array of skv_decode_step_noalloc ---------------------------------------------------------------------------
-constexpr int kWsParts = 14;
+constexpr int kWsParts = 16;
 // Fixed sizes of the tagged area (epochs, tagged scores, tagged partials) in the static scratch of
 // skv_decode_step_noalloc: that area must hold tagged words only, whatever descriptor a call brings (a word of some
 // other array could look like a valid tag), so it has the same extent for every descriptor.
@@ -103,8 +103,11 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     sz[9] = round256(BH * sizeof(int32_t));                                        // f_n_sel
     sz[10] = round256(BH * sizeof(int32_t));                                       // f_n_tok
     sz[11] = round256(BH * d.max_budget * sizeof(int32_t));                        // f_tok_idx
-    sz[12] = 256;                                                                  // err_dev, seg_arrive
+    sz[12] = 256;                                                                  // err_dev, seg_arrive, imp_state
     sz[13] = fixed_tagged ? 0 : round256((size_t)skv::importance_counters(d) * sizeof(unsigned int));    // imp_arrive
+    const size_t heads = (size_t)d.n_layers * d.n_kv_heads, stat_heads = heads < (size_t)skv::kSweepStatHeads ? heads : (size_t)skv::kSweepStatHeads;
+    sz[14] = fixed_tagged ? 0 : (size_t)skv::kSweepMaxBlocks * skv::kImportanceMaxRows * sizeof(unsigned long long);       // imp_part
+    sz[15] = fixed_tagged ? 0 : stat_heads * skv::kImportanceMaxRows * sizeof(unsigned long long);                         // imp_stat
     size_t total = 0;
     for (int i = 0; i < kWsParts; ++i) total += sz[i];
     return total;
@@ -127,8 +130,13 @@ void carve_workspace(Ctx& c, char* base, const size_t sz[kWsParts], int32_t scor
     c.f_n_tok = reinterpret_cast<int32_t*>(p); p += sz[10];
     c.f_tok_idx = reinterpret_cast<int32_t*>(p); p += sz[11];
     c.err_dev = reinterpret_cast<unsigned int*>(p);
-    c.seg_arrive = reinterpret_cast<unsigned long long*>(p + 128); p += sz[12];
+    c.seg_arrive = reinterpret_cast<unsigned long long*>(p + 128);
+    c.imp_state = reinterpret_cast<unsigned int*>(p + 192); p += sz[12];
     c.imp_arrive = reinterpret_cast<unsigned int*>(p); p += sz[13];
+    c.imp_part = sz[14] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[14];
+    c.imp_stat = sz[15] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[15];
+    c.imp_part_words = (int64_t)(sz[14] / sizeof(unsigned long long));
+    c.imp_stat_words = (int64_t)(sz[15] / sizeof(unsigned long long));
 }
 
 void fill_context(Ctx& c, const skv_desc& d, hipStream_t stream, int dev) {

@@ -120,20 +120,6 @@ hipError_t launch_query_update(Ctx* c, int32_t B, const void* q_t, const int32_t
     return hipGetLastError();
 }
 
-// A float and the tag of the launch that produced it, in one 64-bit word written and read with single relaxed
-// device-scope atomic accesses.  A reader that finds the tag it expects holds the value that belongs to it: nothing has
-// to be ordered against any other location (per-location coherence of atomics is all that is used), so there is no
-// arrival counter, no wait for store acknowledgements and no cache maintenance between producer and consumer.
-__device__ __forceinline__ void st_tagged(unsigned long long* p, float v, uint32_t tag) {
-    __hip_atomic_store(p, ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long ld_tagged(const unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t tag_of(unsigned long long w) { return (uint32_t)(w >> 32); }
-__device__ __forceinline__ float val_of(unsigned long long w) { return __uint_as_float((uint32_t)w); }
-
 // ------------------------------------------------------------------------------------------------
 // Scores.  score[h][s] = sum_g q[hG+g] . semvec[h][s]  =  (sum_g q[hG+g]) . semvec[h][s].
 // A semantic vector is 512 bytes = 32 lanes x float4; a wave covers 2 buckets per load instruction

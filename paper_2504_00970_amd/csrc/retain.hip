@@ -5,6 +5,7 @@
 #include "skv_internal.h"
 #include "skv_device.h"
 
+#include <atomic>
 #include <type_traits>
 
 namespace skv {
@@ -214,12 +215,32 @@ __device__ __forceinline__ float move_reference(float sum, float from, float to)
     return from > -INFINITY ? ldexpf(sum, (int)fmaxf(from - to, -512.f)) : 0.f * sum;
 }
 
-// pass 1.  grid (chunks of kpb keys, Hkv, L); part [L][Hkv][chunks][rows] (reference, sum); rowstat [L][Hkv][rows] (reference,
-// 1 / sum) over all keys with 1 <= sum < 2 ((+infinity, 0) for rows >= R).
+// alpha[l][i] = sum over the heads of alpha_h[l][h][i] in ascending order; grid (any, Hkv, L)
+__device__ __forceinline__ void add_heads(const float* __restrict__ alpha_h, float* __restrict__ alpha, int32_t Tp) {
+    const int Hkv = gridDim.y, l = blockIdx.z;
+    const float* src = alpha_h + (int64_t)l * Hkv * Tp;
+    const int32_t step = gridDim.x * gridDim.y * blockDim.x;
+    for (int32_t i = (blockIdx.x * gridDim.y + blockIdx.y) * blockDim.x + threadIdx.x; i < Tp; i += step) {
+        float v = 0.f;
+        for (int hh = 0; hh < Hkv; hh += 8) {
+            float y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] = src[(int64_t)min(hh + u, Hkv - 1) * Tp + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (hh + u < Hkv) v += y[u];
+        }
+        alpha[(int64_t)l * Tp + i] = v;
+    }
+}
+
+// pass 1, a block: chunk `chunk` of `nchunks` (kpb keys each) of a (layer, head); part [L][Hkv][chunks][rows] (reference, sum); rowstat
+// [L][Hkv][rows] (reference, 1 / sum) over all keys with 1 <= sum < 2 ((+infinity, 0) for rows >= R), written by the (layer, head)'s last block, which
+// gets true.
 template <int EB, int RT>
-__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_stats_kernel(
-    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb, float2* part,
-    float2* __restrict__ rowstat, unsigned int* arrive) {
+__device__ __forceinline__ bool importance_stats(const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G,
+                                                 int32_t kpb, float2* part, float2* rowstat, unsigned int* arrive, int chunk, int nchunks,
+                                                 int64_t lh) {
     using P = Imp<EB, RT>;
     constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
@@ -227,8 +248,6 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
     __shared__ float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
     __shared__ int sm_last;
 
-    const int h = blockIdx.y, chunk = blockIdx.x, nchunks = gridDim.x;
-    const int64_t lh = (int64_t)blockIdx.z * gridDim.y + h;              // (layer, KV head)
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, g = lane >> 5;
     const int rs = w / P::KSP, ks = w % P::KSP;
     const int R = G * N, Tp = T - N;
@@ -339,11 +358,11 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
     block_sync_after_stores();
     if (tid == 0) sm_last = __hip_atomic_fetch_add(&arrive[lh], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(nchunks - 1);
     __syncthreads();
-    if (!sm_last) return;
+    if (!sm_last) return false;
     constexpr int kGroups = P::kThreads / kRows;                         // chunks grp, grp + kGroups, ... by thread (grp, row)
     const int row = tid % kRows, grp = tid / kRows;
     float M = -INFINITY, L = 0.f;
-    constexpr int kU = 8;                                                // loads in flight
+    constexpr int kU = 12;                                                // loads in flight
     for (int c = grp; c < nchunks; c += kU * kGroups) {
         unsigned long long v[kU];
 #pragma unroll
@@ -372,14 +391,24 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
         rowstat[lh * kRows + row] = adds ? make_float2(M + (float)e, 1.f / ldexpf(L, -e)) : make_float2(INFINITY, 0.f);
     }
     if (tid == 0) __hip_atomic_store(&arrive[lh], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
+    return true;
 }
 
-// pass 2.  grid (chunks of kpb of the Tp prefix keys, Hkv, L); alpha_h [L][Hkv][Tp], alpha [L][Tp].  Here the queries are the A operand: a
-// lane gets half of the rows of one key, and the sum over the rows is in-lane but for one exchange.
+// grid (chunks, Hkv, L)
 template <int EB, int RT>
-__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_colsum_kernel(
-    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb,
-    const float2* __restrict__ rowstat, float* alpha_h, float* __restrict__ alpha, unsigned int* arrive) {
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_stats_kernel(
+    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb, float2* part,
+    float2* __restrict__ rowstat, unsigned int* arrive) {
+    (void)importance_stats<EB, RT>(q_obs, K_pool, T, N, G, kpb, part, rowstat, arrive, blockIdx.x, gridDim.x,
+                                   (int64_t)blockIdx.z * gridDim.y + blockIdx.y);
+}
+
+// pass 2, a block: chunk `chunk` of `nchunks` of the Tp prefix keys (kpb each) of head h; alpha_h [L][Hkv][Tp], alpha [L][Tp].  Here the queries are
+// the A operand: a lane gets half of the rows of one key, and the sum over the rows is in-lane but for one exchange.
+template <int EB, int RT>
+__device__ __forceinline__ void importance_colsum(const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G,
+                                                  int32_t kpb, const float2* rowstat, float* alpha_h, float* __restrict__ alpha,
+                                                  unsigned int* arrive, int chunk, int nchunks, int h, int Hkv, int l) {
     using P = Imp<EB, RT>;
     constexpr int kRowBytes = kHeadDim * EB, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f;
@@ -387,13 +416,12 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
     __shared__ float sm_col[2][P::RS][P::kStageKeys];
     __shared__ int sm_last;
 
-    const int h = blockIdx.y, Hkv = gridDim.y;
-    const int64_t lh = (int64_t)blockIdx.z * Hkv + h;                    // (layer, KV head)
+    const int64_t lh = (int64_t)l * Hkv + h;                             // (layer, KV head)
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, g = lane >> 5;
     const int rs = w / P::KSP, ks = w % P::KSP;
     const int R = G * N, Tp = T - N;
     const char* Kh = K_pool + lh * T * kRowBytes;
-    const int32_t base0 = blockIdx.x * kpb, cnt = min(kpb, Tp - base0), n = (cnt + P::kStageKeys - 1) / P::kStageKeys;
+    const int32_t base0 = chunk * kpb, cnt = min(kpb, Tp - base0), n = (cnt + P::kStageKeys - 1) / P::kStageKeys;
     KeyRing<EB, RT> keys(Kh, sm_ring, base0, Tp - 1, n);
     Frag<EB> qf[8];
     load_queries<EB>(qf, q_obs + lh * R * kRowBytes, R, 32 * rs);
@@ -449,11 +477,11 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
     put(n - 1);
     // ---- the last of the heads' blocks for these keys: their sum in ascending order ---------------------------------
     block_sync_after_stores();
-    unsigned int* mine = arrive + (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+    unsigned int* mine = arrive + (int64_t)l * nchunks + chunk;
     if (tid == 0) sm_last = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(Hkv - 1);
     __syncthreads();
     if (!sm_last) return;
-    const float* src = alpha_h + (int64_t)blockIdx.z * Hkv * Tp + base0;
+    const float* src = alpha_h + (int64_t)l * Hkv * Tp + base0;
     for (int i = tid; i < cnt; i += P::kThreads) {
         float v = 0.f;
         for (int hh = 0; hh < Hkv; hh += 8) {
@@ -464,9 +492,424 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
             for (int u = 0; u < 8; ++u)
                 if (hh + u < Hkv) v += x[u];
         }
-        alpha[(int64_t)blockIdx.z * Tp + base0 + i] = v;
+        alpha[(int64_t)l * Tp + base0 + i] = v;
     }
     if (tid == 0) __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);            // for the next call
+}
+
+// grid (chunks, Hkv, L)
+template <int EB, int RT>
+__global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importance_colsum_kernel(
+    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb,
+    const float2* __restrict__ rowstat, float* alpha_h, float* __restrict__ alpha, unsigned int* arrive) {
+    importance_colsum<EB, RT>(q_obs, K_pool, T, N, G, kpb, rowstat, alpha_h, alpha, arrive, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, blockIdx.z);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Importance in one sweep over the keys, bf16, up to 128 rows.  The two passes read every key, multiply it and take its exp2 twice,
+// because a row's normaliser is known only once all keys have been seen.  Here the exp2 values of a chunk of keys stay in the
+// registers of the block that made them (128 a lane: half of the chip's registers) until the blocks that hold the other chunks of the
+// (layer, head) have published their sums of every row.
+//   Blocks of four waves, two on a compute unit; block b takes the chunks b, b + blocks, ... of the launch, chunks numbered head by head.
+//   Per chunk:  logits of all its keys (matrix cores; the keys of the next chunk are requested as the places in LDS come
+//   free) -> per row the chunk's largest logit, rounded to a whole reference -> exp2 in place, sums of the rows -> published ->
+//   the blocks of the head combine a share of its rows each and publish 1 / sum -> column sums of the values held.
+// The exchange passes tagged words: nothing is cleared, drained or counted.  A block publishes its next chunk only after it has seen
+// every row of the present one combined, so one place per block is enough.  While one block of a compute unit waits for the
+// others, its neighbour computes.  Half of a block's waves request keys, the other half talk to the other blocks: a wave's loads return in
+// order, and a polled word would come only after the keys requested before it.
+// Waiting needs the blocks of a head to be resident together.  A block that has polled `limit` times, or sees that another gave up, marks the
+// launch as failed and ends; the kernel behind the sweep, which otherwise adds up the heads, then does all of the work in two passes.
+// Bound by HBM for 32 rows (32 layers x 8 heads x 32768 keys: 726 us in two passes, 417 here), where a chunk is 1024 keys; a chunk
+// holds 256 keys of 128 rows, and the exchange (two trips through memory, 5.5 us, 6-7 beside the keys) takes as long as a chunk's
+// logits and exp2: 64 rows 713 -> 520 us, 128 rows 821 -> 819 (of 16384 keys 448 -> 413).  Three blocks of 192 keys on a compute unit were slower (912 us: the
+// exchange grows to 9 us), and so were two row tiles a wave (940).
+// ------------------------------------------------------------------------------------------------
+template <int RT> struct Sweep {                               // RT: 32-row tiles of the window's rows
+    static constexpr int NW = 4, KSP = NW / RT;                // waves of a block: a row tile each, KSP beside each other along the keys
+    static constexpr int KT = 8;                               // 32-key tiles of a wave in a chunk, 16 registers each
+    static constexpr int TPS = RT == 4 ? 2 : RT;               // of these, in a stage
+    static constexpr int SC = KT / TPS, NS = RT == 4 ? 4 : 2;  // stages of a chunk, stages that LDS holds
+    static constexpr int kThreads = NW * kWave, kRows = 32 * RT;
+    static constexpr int kStageKeys = 32 * KSP * TPS, kStageBytes = kStageKeys * kHeadDim * 2, kChunkKeys = kStageKeys * SC;
+    static constexpr int kRingBytes = NS * kStageBytes;
+    static constexpr int kLoaders = NW / 2, kPollers = NW - kLoaders;
+    static constexpr int kLoads = kStageBytes / (kLoaders * 1024);     // load instructions of a loader per stage
+    static_assert(RT * KSP == NW && SC % NS == 0 && NS * kLoads < 64, "a stage has one place in LDS, the load counter holds them all");
+};
+
+struct SweepArgs {
+    const char* q_obs;
+    const char* K_pool;
+    float* alpha_h;              // [heads][Tp]
+    unsigned long long* part;    // [blocks][rows] a chunk's sums
+    unsigned long long* stat;    // [stat_heads][rows] 1 / sum of all chunks
+    unsigned int* state;         // number of the heads so far, the last failed launch, the last launch, its blocks that are done
+    int64_t part_words, stat_words;      // all there are
+    int32_t T, N, G, nch, total, stat_heads, limit;
+    int32_t blocks_div, blocks_mod;      // blocks / nch and the remainder
+};
+
+// Reductions of 16 values over the 32 lanes of a half wave: lane a of the half ends with value number a >> 1.  Values and lanes are halved
+// together, step by step (38 instructions; 16 separate reductions take 96).
+struct MaxOp { __device__ static __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
+struct AddOp { __device__ static __forceinline__ float of(float a, float b) { return a + b; } };
+template <int CTRL> __device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false); }
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) { return __int_as_float(dpp_move<CTRL>(__float_as_int(x))); }
+// x of the lane l ^ N, N = 16 or 32
+template <int N> __device__ __forceinline__ int other_half(int x) {
+    const auto s = N == 16 ? __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false)
+                           : __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    return (int)(s[0] ^ s[1] ^ (uint32_t)x);
+}
+template <class Op> __device__ __forceinline__ float reduce_16x32(const float (&v)[16]) {
+    const int a = threadIdx.x & 31;
+    float x[8], y[4], z[2];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 8]), false, false);
+        x[j] = Op::of(__uint_as_float(s[0]), __uint_as_float(s[1]));                 // value j + 8 (a >> 4)
+    }
+    const bool b3 = a & 8, b2 = a & 4, b1 = a & 2;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = Op::of(b3 ? x[j + 4] : x[j], dpp_move<0x140>(b3 ? x[j] : x[j + 4]));    // row_mirror
+#pragma unroll
+    for (int j = 0; j < 2; ++j) z[j] = Op::of(b2 ? y[j + 2] : y[j], dpp_move<0x141>(b2 ? y[j] : y[j + 2]));    // row_half_mirror
+    const float u = Op::of(b1 ? z[1] : z[0], dpp_move<0x4E>(b1 ? z[0] : z[1]));
+    return Op::of(u, dpp_move<0xB1>(u));
+}
+// A number m * 2^x, 1 <= m < 2, and the tag of the (layer, head) it belongs to in one 64-bit word: 24 bits, 17 of the exponent, 23 of m.
+constexpr int kExpBias = 1 << 16, kExpNone = -kExpBias, kExpNan = kExpBias - 1;       // exponents that stand for zero and NaN
+__device__ __forceinline__ unsigned long long tagged_number(float v, int exponent, uint32_t tag) {       // v * 2^exponent, v >= 0
+    const int e = v != v ? kExpNan : v > 0.f ? exponent + __builtin_amdgcn_frexp_expf(v) - 1 : kExpNone;
+    const uint32_t m = __float_as_uint(__builtin_amdgcn_frexp_mantf(v)) & 0x7fffffu;
+    return ((unsigned long long)tag << 40) | ((unsigned long long)(uint32_t)(e + kExpBias) << 23) | m;
+}
+__device__ __forceinline__ uint32_t number_tag(unsigned long long w) { return (uint32_t)(w >> 40); }
+__device__ __forceinline__ int number_exp(unsigned long long w) { return (int)((uint32_t)(w >> 23) & 0x1ffffu) - kExpBias; }
+__device__ __forceinline__ float number_mant(unsigned long long w) {
+    const int e = number_exp(w);
+    return e == kExpNone ? 0.f : e == kExpNan ? NAN : __uint_as_float(0x3f800000u | ((uint32_t)w & 0x7fffffu));
+}
+
+// A block's stages in LDS, across its chunks: stage k of a chunk at place k % NS, filled again (with stage k + NS, of the next chunk at the end) when
+// every wave has read it.
+template <int RT>
+struct SweepStages {
+    using P = Sweep<RT>;
+    static constexpr int kRowBytes = kHeadDim * 2, kPieces = kRowBytes / 16, kRows = kWave / kPieces;      // rows per instruction
+    int loader;               // which of the loading waves, negative: none
+    uint32_t lds;             // where this wave's part of the first stage goes
+    __device__ __forceinline__ SweepStages(char* ring, int loader_) : loader(loader_) {
+        lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + (uint32_t)(loader * P::kLoads * 1024);
+    }
+    // stage k (compile time) of the chunk whose first key is `src`, `keys` of the head's keys from there on; piece p of row r lands at piece p ^ (r % 16)
+    __device__ __forceinline__ void request(const char* src, int keys, int k) const {
+        if (loader < 0) return;
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));                                   // each load's offset made here, not kept in a register of its own
+        const uint32_t first = (uint32_t)((kRows * P::kLoads * loader + lane / kPieces) * kRowBytes + 16 * ((lane % kPieces) ^ (lane / kPieces)));
+        if (keys >= (k + 1) * P::kStageKeys) {
+#pragma unroll
+            for (int i = 0; i < P::kLoads; ++i)
+                load_lds_stream_at(src + k * P::kStageBytes, (first ^ (uint32_t)((kRows * i & 15) * 16)) + (uint32_t)(kRows * i * kRowBytes),
+                                   lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i));
+        } else {                                                         // keys past the last: that one again
+#pragma unroll
+            for (int i = 0; i < P::kLoads; ++i) {
+                const uint32_t piece = (first ^ (uint32_t)((kRows * i & 15) * 16)) & (uint32_t)(kRowBytes - 1);
+                load_lds_stream_at(src, (uint32_t)(min(k * P::kStageKeys + (int)(first / kRowBytes) + kRows * i, keys - 1) * kRowBytes) + piece,
+                                   lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i));
+            }
+        }
+    }
+    // stage k has landed: at most this many stages were requested after it
+    template <int AFTER> __device__ __forceinline__ void landed() const {
+        if (loader >= 0) wait_loads<AFTER * P::kLoads>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+};
+
+// Words of other blocks, asked for until they carry the tag.
+struct Waiter {
+    const unsigned int* failed;
+    unsigned int failed_if;
+    int limit;
+    bool ok;
+    // word u of a lane: base[at(u, lane)], where need(u, lane)
+    template <int U, class At, class Need>
+    __device__ __forceinline__ void get(const unsigned long long* base, At at, Need need, uint32_t tag, unsigned long long (&v)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = 0;
+        for (int n = 0; ok; ++n) {
+            bool all = true;
+            int lane = threadIdx.x & 63;
+            asm volatile("" : "+v"(lane));                               // addresses made in every round, not kept in registers
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = ld_tagged(base + at(u, lane));
+#pragma unroll
+            for (int u = 0; u < U; ++u) all = all && (!need(u, lane) || number_tag(v[u]) == tag);
+            if (__all(all)) return;
+            if (n >= limit || ((n & 31) == 31 && ld_agent(failed) == failed_if)) ok = false;
+        }
+    }
+};
+
+template <int RT>
+__global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_per_eu(kSweepPerCu, kSweepPerCu))) void importance_sweep_kernel(SweepArgs x) {
+    using P = Sweep<RT>;
+    constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows, kU = 8;       // kU: words of a lane asked for together
+    constexpr float kLog2e = 1.4426950408889634f;
+    extern __shared__ __attribute__((aligned(16))) char sm_ring[];
+    __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
+    __shared__ float sm_col[RT][P::kChunkKeys];
+    __shared__ int sm_ok[P::kPollers];
+    float* const sm_f = sm_l[0];                                         // a row's factor in the place of its sum, by the thread that published it
+
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // what depends on the lane is made where it is used: kept for the whole loop it would take registers from the chunk's values
+    int lane_of = threadIdx.x & 63;
+    auto this_lane = [&]() { int l = lane_of; asm volatile("" : "+v"(l)); return l; };
+    const int rs = w / P::KSP, ks = w % P::KSP;
+    const int R = x.G * x.N, Tp = x.T - x.N, nblk = gridDim.x;
+    const int loader = w - P::kPollers;                                  // negative: the wave talks to the other blocks
+    const float scale = kLog2e * rsqrtf((float)kHeadDim);
+    const unsigned int epoch = ld_agent(x.state);
+    int lh = blockIdx.x / x.nch, chunk = blockIdx.x - lh * x.nch;
+    auto chunk_src = [&](int head, int ch) { return x.K_pool + ((int64_t)head * x.T + ch * P::kChunkKeys) * kRowBytes; };
+    const SweepStages<RT> stages(sm_ring, loader);
+#pragma unroll
+    for (int k = 0; k < P::NS; ++k) stages.request(chunk_src(lh, chunk), x.T - chunk * P::kChunkKeys, k);
+    Frag<2> qf[8];
+    auto load_q = [&](int head) {
+        const int lane = this_lane(), r = lane & 31, g = lane >> 5;
+        // rows past the last repeat it: they get a factor of zero
+        const char* q = x.q_obs + ((int64_t)head * R + min(32 * rs + r, R - 1)) * kRowBytes + 16 * g;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) qf[d].t0 = *reinterpret_cast<const uint4*>(q + 32 * d);
+    };
+    load_q(lh);
+
+    for (int left = ((int)x.total - (int)blockIdx.x + nblk - 1) / nblk - 1; left >= 0; --left) {         // chunks after this one
+        const int32_t base0 = chunk * P::kChunkKeys;
+        const uint32_t tag = epoch + 1 + (uint32_t)lh;
+        int lh_next = lh + x.blocks_div, chunk_next = chunk + x.blocks_mod;
+        if (chunk_next >= x.nch) { chunk_next -= x.nch; ++lh_next; }
+        const char *src = chunk_src(lh, chunk), *src_next = chunk_src(lh_next, chunk_next);
+        const int keys = x.T - base0, keys_next = x.T - chunk_next * P::kChunkKeys;
+        f32x16 acc[P::KT];
+        const int lane = this_lane(), tid = lane + w * kWave, r = lane & 31, g = lane >> 5;
+#pragma unroll
+        for (int k = 0; k < P::SC; ++k) {
+            // one stage was requested after each that has been read, but the last of a chunk already behind the barrier after it
+            if (k == 0) stages.template landed<P::NS - 1>();
+            else if (k + P::NS - 2 < P::SC || left > 0) stages.template landed<P::NS - 2>();
+            else stages.template landed<0>();
+            if (k > 0) {
+                if (k - 1 + P::NS < P::SC) stages.request(src, keys, k - 1 + P::NS);
+                else if (left > 0) stages.request(src_next, keys_next, k - 1 + P::NS - P::SC);
+            }
+            const char* stage = sm_ring + k % P::NS * P::kStageBytes;
+            // a fragment of the next tile is read behind the matrix instruction that used its registers
+            Frag<2> kf[8];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) stage_frag<2>(kf[d], stage, 32 * ks + r, d, g);
+#pragma unroll
+            for (int u = 0; u < P::TPS; ++u) {
+                f32x16 c = {};
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    c = frag_mma<2>(qf[d], kf[d], c);
+                    if (u + 1 < P::TPS) stage_frag<2>(kf[d], stage, 32 * (P::KSP * (u + 1) + ks) + r, d, g);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                acc[k * P::TPS + u] = c;
+            }
+        }
+        if (base0 + P::kChunkKeys > Tp) {                                // keys that not every row sees
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int32_t limit = min(Tp + (32 * rs + tile_pos(i, g)) % x.N, x.T - 1) - base0 - 32 * ks - r;
+#pragma unroll
+                for (int k = 0; k < P::KT; ++k)
+                    if (32 * P::KSP * k > limit) acc[k][i] = -INFINITY;
+            }
+        }
+        // whole references, the rows' sums relative to them
+        {
+            float m[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m[i] = acc[0][i];
+#pragma unroll
+            for (int k = 1; k < P::KT; ++k)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) m[i] = fmaxf(m[i], acc[k][i]);
+            const float top = rintf(reduce_16x32<MaxOp>(m) * scale);
+            if ((lane & 1) == 0) sm_m[ks][32 * rs + tile_pos(r >> 1, g)] = top;
+        }
+        if constexpr (P::KSP > 1) __syncthreads();
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the wave's own rows
+        {
+            float ref[16], sum[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                float m = sm_m[0][32 * rs + tile_pos(i, g)];
+#pragma unroll
+                for (int k = 1; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][32 * rs + tile_pos(i, g)]);
+                ref[i] = m > -INFINITY ? m : 0.f;                        // (nothing visible: every term is exp2(-inf) = 0)
+                sum[i] = 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < P::KT; ++k)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    acc[k][i] = exp2_neg(fmaf(acc[k][i], scale, -ref[i]));
+                    sum[i] += acc[k][i];
+                    if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // (a schedule across tiles runs out of registers)
+                }
+            const float l = reduce_16x32<AddOp>(sum);
+            if ((lane & 1) == 0) sm_l[ks][32 * rs + tile_pos(r >> 1, g)] = l;
+        }
+        __syncthreads();
+        if (left > 0) stages.request(src_next, keys_next, P::NS - 1);
+        if (loader < 0) {
+            __builtin_amdgcn_s_setprio(3);
+            // published: the sum of every row
+            Waiter wait{x.state + 1, epoch + 1, x.limit, true};
+            for (int row = tid; row < kRows; row += P::kPollers * kWave) {
+                float m = sm_m[0][row], l = sm_l[0][row];
+#pragma unroll
+                for (int k = 1; k < P::KSP; ++k) { m = fmaxf(m, sm_m[k][row]); l += sm_l[k][row]; }
+                if (l > 0.f && !(fabsf(m) < (float)(kExpBias - 256))) wait.ok = false;       // beyond the words' exponent
+                __hip_atomic_store(x.part + (int64_t)blockIdx.x * kRows + row, tagged_number(l, l > 0.f ? (int)m : 0, tag), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+            wait.ok = __all(wait.ok);
+            // combined: four rows a wave, 16 lanes to a row
+            unsigned long long* stat = x.stat + (int64_t)(lh % x.stat_heads) * kRows;
+            int first = (int)blockIdx.x - chunk;                         // block of the head's first chunk
+            if (first < 0) first += nblk;
+            for (int row0 = 4 * (chunk * P::kPollers + w); row0 < kRows; row0 += 4 * P::kPollers * x.nch) {
+                const int row = row0 + (lane & 3);
+                int X = kExpNone;
+                float L = 0.f;
+                for (int c0 = 0; c0 < x.nch; c0 += 16 * kU) {
+                    unsigned long long v[kU];
+                    auto need = [&](int u, int l) { return c0 + 16 * u + (l >> 2) < x.nch; };
+                    wait.get<kU>(x.part, [&](int u, int l) {
+                        int b = first + min(c0 + 16 * u + (l >> 2), x.nch - 1);
+                        if (b >= nblk) b -= nblk;
+                        return (uint32_t)(b * kRows + row0 + (l & 3));
+                    }, need, tag, v);
+                    int top = X;
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) top = max(top, need(u, lane) ? number_exp(v[u]) : kExpNone);
+                    L = ldexpf(L, max(X - top, -512));
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) L += need(u, lane) ? ldexpf(number_mant(v[u]), max(number_exp(v[u]) - top, -512)) : 0.f;
+                    X = top;
+                }
+                int top = max(X, dpp_move<0x124>(X));                    // row_ror 4, 8: the lanes of the row
+                top = max(top, dpp_move<0x128>(top));
+                top = max(top, other_half<16>(top));
+                top = max(top, other_half<32>(top));
+                L = ldexpf(L, max(X - top, -512));
+                L += dpp_move<0x124>(L);
+                L += dpp_move<0x128>(L);
+                L += __int_as_float(other_half<16>(__float_as_int(L)));
+                L += __int_as_float(other_half<32>(__float_as_int(L)));
+                if (wait.ok && lane < 4)
+                    __hip_atomic_store(stat + row, tagged_number(row < R && L > 0.f ? 1.f / L : 0.f, -top, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            // all rows: the factor that makes this chunk's values probabilities
+            for (int row = tid; row - lane < kRows; row += P::kPollers * kWave) {
+                unsigned long long v[1];
+                wait.get<1>(stat, [&](int, int l) { return (uint32_t)min(row - lane + l, kRows - 1); }, [&](int, int) { return row < kRows; }, tag, v);
+                if (row < kRows) {
+                    float m = sm_m[0][row];
+#pragma unroll
+                    for (int k = 1; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][row]);
+                    sm_f[row] = m > -INFINITY ? ldexpf(number_mant(v[0]), min(max((int)m + number_exp(v[0]), -512), 512)) : 0.f;
+                }
+            }
+            if (lane == 0) sm_ok[w] = wait.ok;
+            __builtin_amdgcn_s_setprio(0);
+        }
+        load_q(left > 0 ? lh_next : lh);                                 // (always: until here no register holds queries)
+        __syncthreads();
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < P::kPollers; ++i) ok = ok && sm_ok[i];
+        if (!ok) {                                                       // the passes that follow do it
+            if (tid == 0) st_agent(x.state + 1, epoch + 1);
+            break;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            float f[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) f[i] = sm_f[32 * rs + tile_pos(i, g)];
+#pragma unroll
+            for (int k = 0; k < P::KT; ++k) {
+                float p[2] = {0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 16; ++i) p[i & 1] = fmaf(acc[k][i], f[i], p[i & 1]);
+                const float v = sum_halves(p[0] + p[1]);
+                if (g == 0) sm_col[rs][32 * (P::KSP * k + ks) + r] = v;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+        if (loader < 0) {
+            float* dst = x.alpha_h + (int64_t)lh * Tp + base0;
+            for (int i = tid; i < P::kChunkKeys && base0 + i < Tp; i += P::kPollers * kWave) {
+                float v = sm_col[0][i];
+#pragma unroll
+                for (int k = 1; k < RT; ++k) v += sm_col[k][i];
+                dst[i] = v;
+            }
+        }
+        lh = lh_next;
+        chunk = chunk_next;
+    }
+    wait_loads<0>();                                                     // nothing lands in LDS after the block's end
+    // The last block to end moves the numbers on.  Before a tag comes again the words are cleared.
+    if (threadIdx.x == 0)
+        sm_ok[0] = __hip_atomic_fetch_add(x.state + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(nblk - 1);
+    __syncthreads();
+    if (!sm_ok[0]) return;
+    const unsigned int heads = (unsigned int)(x.total / x.nch), next = epoch + heads;
+    const bool again = next + heads > kSweepTags;
+    if (threadIdx.x == 0) {
+        st_agent(x.state + 2, epoch + 1);
+        st_agent(x.state + 3, 0u);
+        st_agent(x.state, again ? 0u : next);
+    }
+    if (again) {
+        for (int64_t i = threadIdx.x; i < x.part_words; i += P::kThreads) __hip_atomic_store(x.part + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int64_t i = threadIdx.x; i < x.stat_words; i += P::kThreads) __hip_atomic_store(x.stat + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Behind the sweep, grid (chunks of pass 1, Hkv, L): the heads added up, or, if it failed, all of the work: pass 1, and pass 2 of a (layer, head) by
+// its last block.
+template <int RT>
+__global__ __launch_bounds__((Imp<2, RT>::kThreads)) void importance_finish_kernel(
+    const char* __restrict__ q_obs, const char* __restrict__ K_pool, int32_t T, int32_t N, int32_t G, int32_t kpb, float2* part, float2* rowstat,
+    unsigned int* arrive, float* alpha_h, float* alpha, const unsigned int* state) {
+    if (ld_agent(state + 1) != ld_agent(state + 2)) {
+        add_heads(alpha_h, alpha, T - N);
+        return;
+    }
+    const int h = blockIdx.y, Hkv = gridDim.y, l = blockIdx.z;
+    if (!importance_stats<2, RT>(q_obs, K_pool, T, N, G, kpb, part, rowstat, arrive, blockIdx.x, gridDim.x, (int64_t)l * Hkv + h)) return;
+    block_sync_after_stores();
+    const int n = (T - N + kpb - 1) / kpb;
+    for (int chunk = 0; chunk < n; ++chunk) {
+        importance_colsum<2, RT>(q_obs, K_pool, T, N, G, kpb, rowstat, alpha_h, alpha, arrive + (int64_t)gridDim.z * Hkv, chunk, n, h, Hkv, l);
+        __syncthreads();
+    }
 }
 
 // Keys per block, in units of 128: the number that gives the least rounds x (units + 2), two units being about what a block's
@@ -486,22 +929,74 @@ static int importance_keys_per_block(const Ctx* c, int32_t T, int32_t N) {
     return kImpUnit * (int)best;
 }
 
+// LDS above 64 KB needs the opt-in once per kernel
+template <class F> static hipError_t raise_lds(F kernel, int bytes, std::atomic<bool>& raised) {
+    if (raised.load(std::memory_order_acquire)) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) raised.store(true, std::memory_order_release);
+    return e;
+}
+
+static int sweep_blocks(const Ctx* c) { return min(kSweepPerCu * c->n_cu, kSweepMaxBlocks); }
+
+// Where the sweep is the faster form (us, two passes / one sweep): the chunks of a head fit the chip at once, and the launch has
+// chunks enough (32 layers x 8 heads of 1024 keys, 32 rows, 256 chunks: 33.0 / 29.5; 8 layers, 64 chunks: 19.7 / 26.1; 2048 keys, 128 chunks: 23.3 / 23.2).
+// 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 418, 715 / 573); 128 rows, a chunk of 256 keys a block, from 4096 keys
+// (131 / 121; 3000 keys: 97 / 100) to 64 chunks a head (16384 keys 448 / 413; 24000: 615 / 618, 32768: 821 / 819, 65000, 8 layers: 426 / 436).
+template <int RT>
+static bool importance_sweeps(const Ctx* c, int32_t T) {
+    using P = Sweep<RT>;
+    const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, nch = (T + P::kChunkKeys - 1) / P::kChunkKeys, most = sweep_blocks(c);
+    if (!c->single_launch || !c->imp_part || nch > most || heads > kSweepMostHeads || heads * nch > (1 << 30) || heads * nch < 128) return false;
+    return RT < 4 || (T >= 4096 && nch <= 64);
+}
+
+template <int RT>
+static hipError_t launch_sweep(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part, float2* rowstat,
+                               float* alpha_h) {
+    using P = Sweep<RT>;
+    static std::atomic<bool> raised{false}, raised_finish{false};
+    hipError_t e = raise_lds(&importance_sweep_kernel<RT>, P::kRingBytes, raised);
+    if (e == hipSuccess) e = raise_lds(&importance_finish_kernel<RT>, Imp<2, RT>::kRingBytes, raised_finish);
+    if (e != hipSuccess) return e;
+    const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, kpb = importance_keys_per_block(c, T, N);
+    SweepArgs x;
+    x.q_obs = q_obs;
+    x.K_pool = K_pool;
+    x.alpha_h = alpha_h;
+    x.part = c->imp_part;
+    x.stat = c->imp_stat;
+    x.state = c->imp_state;
+    x.part_words = c->imp_part_words;
+    x.stat_words = c->imp_stat_words;
+    x.T = T;
+    x.N = N;
+    x.G = c->G;
+    x.nch = (T + P::kChunkKeys - 1) / P::kChunkKeys;
+    x.total = L * Hkv * x.nch;
+    x.stat_heads = min(L * Hkv, kSweepStatHeads);
+    x.limit = min(c->wait_limit, kSweepWaitLimit);
+    const int blocks = min(sweep_blocks(c) / x.nch * x.nch, x.total);      // whole heads: else every head's blocks wait for those of the next ones
+    x.blocks_div = blocks / x.nch;
+    x.blocks_mod = blocks % x.nch;
+    hipLaunchKernelGGL((importance_sweep_kernel<RT>), dim3(blocks), dim3(P::kThreads), P::kRingBytes, c->stream, x);
+    hipLaunchKernelGGL((importance_finish_kernel<RT>), dim3((T + kpb - 1) / kpb, Hkv, L), dim3(Imp<2, RT>::kThreads), (Imp<2, RT>::kRingBytes), c->stream,
+                       q_obs, K_pool, T, N, c->G, kpb, part, rowstat, c->imp_arrive, alpha_h, alpha, c->imp_state);
+    return hipGetLastError();
+}
+
 template <int EB, int RT>
 static hipError_t launch_importance_rt(Ctx* c, const char* q_obs, const char* K_pool, int32_t T, int32_t N, float* alpha, float2* part,
                                        float2* rowstat, float* alpha_h) {
     using P = Imp<EB, RT>;
+    if constexpr (EB == 2 && RT <= 4)
+        if (importance_sweeps<RT>(c, T)) return launch_sweep<RT>(c, q_obs, K_pool, T, N, alpha, part, rowstat, alpha_h);
     const int Hkv = c->d.n_kv_heads, L = c->d.n_layers, G = c->G, Tp = T - N, kpb = importance_keys_per_block(c, T, N);
-    constexpr size_t lds = P::kRingBytes;
-    static bool raised = false;                                        // LDS above 64 KB needs the opt-in once
-    if (!raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&importance_stats_kernel<EB, RT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&importance_colsum_kernel<EB, RT>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
+    constexpr int lds = P::kRingBytes;
+    static std::atomic<bool> raised_stats{false}, raised_colsum{false};
+    hipError_t e = raise_lds(&importance_stats_kernel<EB, RT>, lds, raised_stats);
+    if (e == hipSuccess) e = raise_lds(&importance_colsum_kernel<EB, RT>, lds, raised_colsum);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((importance_stats_kernel<EB, RT>), dim3((T + kpb - 1) / kpb, Hkv, L), dim3(P::kThreads), lds, c->stream, q_obs,
                        K_pool, T, N, G, kpb, part, rowstat, c->imp_arrive);
     hipLaunchKernelGGL((importance_colsum_kernel<EB, RT>), dim3((Tp + kpb - 1) / kpb, Hkv, L), dim3(P::kThreads), lds, c->stream, q_obs,
@@ -671,7 +1166,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
     __syncthreads();                                                   // keep[0 .. need) is written (block-visible)
 
     // ---- buckets of the retained tokens ------------------------------------------------------------------
-    constexpr int kU = 4;                                              // kept tokens of a thread whose loads are out together
+    constexpr int kU = 12;                                              // kept tokens of a thread whose loads are out together
     for (int32_t j0 = tid; j0 < need; j0 += kU * kBlockThreads) {
         int32_t s_cur[kU], s_prev[kU];
 #pragma unroll

@@ -41,11 +41,13 @@ __device__ __forceinline__ void st_stream(void* p, const uint4& v) {
 // is, not saved around the statement: nothing here expects it to be.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_lds_stream(const char* base, uint32_t off, char* lds) {
-    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+__device__ __forceinline__ void load_lds_stream_at(const char* base, uint32_t off, uint32_t at /* address in LDS */) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(off),
                  "s"(base)
                  : "memory", "m0");
+}
+__device__ __forceinline__ void load_lds_stream(const char* base, uint32_t off, char* lds) {
+    load_lds_stream_at(base, off, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds);
 }
 #pragma clang diagnostic pop
 // waits until at most N of the wave's vector memory instructions are outstanding
@@ -97,6 +99,20 @@ __device__ __forceinline__ void block_sync_after_stores() {
 }
 __device__ __forceinline__ float lo_f(unsigned long long v) { return __uint_as_float((uint32_t)v); }
 __device__ __forceinline__ float hi_f(unsigned long long v) { return __uint_as_float((uint32_t)(v >> 32)); }
+
+// A float and the tag of the launch that produced it, in one 64-bit word written and read with single relaxed
+// device-scope atomic accesses.  A reader that finds the tag it expects holds the value that belongs to it: nothing has
+// to be ordered against any other location (per-location coherence of atomics is all that is used), so there is no
+// arrival counter, no wait for store acknowledgements and no cache maintenance between producer and consumer.
+__device__ __forceinline__ void st_tagged(unsigned long long* p, float v, uint32_t tag) {
+    __hip_atomic_store(p, ((unsigned long long)tag << 32) | (unsigned long long)__float_as_uint(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long ld_tagged(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t tag_of(unsigned long long w) { return (uint32_t)(w >> 32); }
+__device__ __forceinline__ float val_of(unsigned long long w) { return __uint_as_float((uint32_t)w); }
 
 // Order-preserving 32-bit image of a float: larger score <=> larger key.
 __device__ __forceinline__ uint32_t score_key(float f) {

@@ -79,6 +79,10 @@ struct Ctx {
     unsigned int* err_host_dev;  // device address of err_host
     unsigned long long* seg_arrive;  // [1] blocks of the segmentation that are done (high word) and S (low word); zero between calls
     unsigned int* imp_arrive;    // [importance_counters] arrivals of the importance passes; zero between calls
+    unsigned int* imp_state;     // [4] numbers of the one-sweep importance (SweepArgs::state)
+    unsigned long long* imp_part;    // its tagged words: [kSweepMaxBlocks][kImportanceMaxRows] (null: no sweep)
+    unsigned long long* imp_stat;    // [min(heads, kSweepStatHeads)][kImportanceMaxRows]
+    int64_t imp_part_words, imp_stat_words;
     unsigned int* n_sent_host;   // S of the last segmentation in pinned host memory (host address; null: none)
     unsigned int* n_sent_host_dev;   // its device address
     int wait_limit;              // polling rounds before a waiting block gives up
@@ -108,6 +112,14 @@ hipError_t launch_semvec(Ctx* c, const void* K_pool, int32_t T, const int32_t* s
                          void* semvec);
 // prefill-side token retention (retain.hip)
 constexpr int kImportanceMaxRows = 256;   // query rows (G * window tokens) per KV head
+// one-sweep importance: blocks on a compute unit and in all, (layer, head) pairs that have a place of their own for the combined rows, the largest
+// tag, and the polling rounds (about a microsecond each) before a block leaves the work to the two passes
+constexpr int kSweepPerCu = 2;
+constexpr int kSweepMaxBlocks = kSweepPerCu * kComputeUnits;
+constexpr int kSweepStatHeads = 1024;
+constexpr unsigned int kSweepTags = (1u << 24) - 1;
+constexpr int kSweepMostHeads = 1 << 20;
+constexpr int kSweepWaitLimit = 8000;
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N);
 int64_t importance_counters(const skv_desc& d);
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work);

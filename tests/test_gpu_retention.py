@@ -129,6 +129,78 @@ def test_token_importance_plans_for_the_blocks_that_fit(U, dtype, Hq, N, per_cu)
     want = 4 * (L * H * chunks(per) * rows * 2 + L * H * rows * 2 + L * H * (T - N))
     assert got == -(-want // 256) * 256
 
+SWEEP_CASES = [(8, 32, 1023), (8, 32, 1025), (8, 1, 2), (8, 7, 40), (16, 32, 512), (16, 25, 513), (16, 32, 1057), (32, 32, 4096),
+               (32, 24, 4353), (32, 32, 16384)]
+
+
+def _importance_inputs(U, L, Hq, H, N, T, seed=11):
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype="bf16")
+    g = torch.Generator(device=U.DEV)
+    g.manual_seed(seed)
+    K = torch.empty(L, H, T, 128, dtype=torch.bfloat16, device=U.DEV).normal_(generator=g)
+    q = torch.empty(L, Hq, N, 128, dtype=torch.bfloat16, device=U.DEV).normal_(generator=g)
+    return wl, q, K
+
+
+@pytest.mark.parametrize("limit", [None, 0])
+@pytest.mark.parametrize("Hq,N,T", SWEEP_CASES, ids=[f"rows{c[0] // 8 * c[1]}-N{c[1]}-T{c[2]}" for c in SWEEP_CASES])
+def test_token_importance_in_one_sweep(U, Hq, N, T, limit):
+    """The one-sweep form at the edges of its chunks (1024, 512 or 256 keys), from one chunk to several rounds of them, against the two passes.
+    Both form the same logits bit for bit; arguments of exp2 (up to 2^4 here) are rounded once to 2^-21 on each side, sums of T terms differ in
+    order: 2^-20 * ln 2 + a few 2^-24 of a value, below 2e-6.  With a wait limit of zero every block leaves the work to the passes behind
+    the sweep, which give their very bits."""
+    L, H = 36, 8                                                                            # 288 (layer, head) pairs
+    _say("importance in one sweep", Hq, N, T, limit)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want = _gpu_importance(U, two, q, K, T, N)
+    ctx = U.make_ctx(wl, T, 64, 16)
+    if limit is not None:
+        ctx.set_wait_limit(limit)
+    for _ in range(3):                                                                      # launch numbers move on
+        got = _gpu_importance(U, ctx, q, K, T, N)
+        if limit == 0 and T > 1024:                                                         # (a head in one chunk waits for nobody)
+            assert torch.equal(got, want)
+        rel = ((got - want).abs() / want.abs().clamp_min(1e-30)).max().item()
+        assert rel <= 2e-6, rel
+    if limit == 0:
+        ctx.set_wait_limit(200000)
+        rel = ((_gpu_importance(U, ctx, q, K, T, N) - want).abs() / want.abs().clamp_min(1e-30)).max().item()
+        assert rel <= 2e-6, rel
+
+
+def test_token_importance_sweep_with_infinities_and_nan(U):
+    """A NaN or infinite logit, and keys that every row weighs zero: the places of NaN and the values are those of the two passes."""
+    L, Hq, H, N, T = 4, 16, 8, 32, 5000
+    _say("importance in one sweep, special values")
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    K[0, 1, 700] = float("nan")
+    K[1, 2, 800, 3] = float("inf")
+    K[2, :, 900:1900] = -200.0 * q[2, ::2, 0].float().sign().to(torch.bfloat16)[:, None]
+    q[3, 5] *= 1e30                                                                         # logits beyond the exchange's exponents
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert torch.equal(want.isnan(), got.isnan())
+    ok = ~want.isnan()
+    assert torch.all((got - want).abs()[ok] <= 2e-6 * want[ok] + 1e-30)
+
+
+def test_token_importance_sweep_tags_start_again(U):
+    """2^24 tags, one per (layer, head) and launch: with 2^19 pairs they are used up at the 32nd launch."""
+    L, Hq, H, N, T = 8192, 64, 64, 2, 20
+    _say("importance in one sweep, tags used up")
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want = _gpu_importance(U, two, q, K, T, N)
+    ctx = U.make_ctx(wl, T, 64, 16)
+    first = _gpu_importance(U, ctx, q, K, T, N)
+    assert ((first - want).abs() / want).max().item() <= 2e-6
+    for _ in range(40):
+        assert torch.equal(_gpu_importance(U, ctx, q, K, T, N), first)
+
 
 FULL_IMP_CASES = [("bf16", 32, 8, 32, 32768), ("f32", 32, 8, 32, 32768), ("bf16", 8, 2, 32, 40100), ("f32", 4, 1, 32, 70001)]
 
