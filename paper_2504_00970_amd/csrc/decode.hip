@@ -1125,7 +1125,7 @@ struct AttArgs {
     const char* q_score;      // [B][Hq][D]
     const char* semvec;       // the layer's table [Hkv][S_total][D]
     int32_t sv_bytes;         // bytes per element of the table: 4, 2 or 1
-    int32_t lg_parts;         // log2 of the blocks per pair
+    int32_t lg_parts;         // kStep: log2 of the blocks per pair
     int32_t lg_merge;         // log2 of the blocks that merge one query head; -1: a block merges two heads
     unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
     unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
@@ -1134,9 +1134,12 @@ struct AttArgs {
     int32_t wait_limit;       // rounds of polling before a block gives up
     unsigned int* err_dev;    // set to 1 by a block that gave up
     unsigned int* err_host;   // the same word in pinned host memory (device address), nullable
+    // kStepRagged: blocks per pair, tokens of an attending block (a multiple of 16, at most CHUNK), and 2^32 / each, rounded up
+    int32_t parts, chunk;
+    uint32_t per_part, per_chunk;
 };
 
-enum { kDirect = 0, kFused = 1, kIndirect = 2, kStep = 3 };
+enum { kDirect = 0, kFused = 1, kIndirect = 2, kStep = 3, kStepRagged = 4 };      // kStepRagged: any number of blocks, any share of the budget
 
 // Every argument is demanded at this point, so the kernel-argument loads go out in one batch at the top of the kernel;
 // left alone, the compiler loads each argument before its first use: one dependent round trip per branch, and a
@@ -1147,7 +1150,8 @@ __device__ __forceinline__ void demand_args(const AttArgs& a) {
                  "s"(a.v.cu_sent), "s"(a.v.budget_arr), "s"(a.v.T_total), "s"(a.v.S_total), "s"(a.v.budget), "s"(a.v.B),
                  "s"(a.Hkv), "s"(a.max_splits), "s"(a.part), "s"(a.ml), "s"(a.counter), "s"(a.out), "s"(a.lse));
 }
-__device__ __forceinline__ void demand_step_args(const AttArgs& a) {
+template <bool RAGGED> __device__ __forceinline__ void demand_step_args(const AttArgs& a) {
+    if constexpr (RAGGED) asm volatile("" ::"s"(a.parts), "s"(a.chunk), "s"(a.per_part), "s"(a.per_chunk));
     asm volatile("" ::"s"(a.q_score), "s"(a.semvec), "s"(a.sv_bytes), "s"(a.lg_parts), "s"(a.lg_merge), "s"(a.step_epoch), "s"(a.step_score),
                  "s"(a.score_stride), "s"(a.step_part), "s"(a.wait_limit), "s"(a.err_dev), "s"(a.err_host));
 }
@@ -1159,11 +1163,15 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
     return POOL ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
 }
 
+// ceil(n / d) with `per` = 2^32 / d rounded up; exact while n + d <= 2^32 / d
+__device__ __forceinline__ int32_t ceil_div(int32_t n, int32_t d, uint32_t per) { return (int32_t)__umulhi((uint32_t)(n + d - 1), per); }
+
 // CHUNK = retrieved tokens per block, a tile of 16 for each of CHUNK / 16 waves (512: two tiles a wave): the smallest whose blocks all run
 // at once, see launch_step, launch_select_attend and launch_attend.
 template <int EB, int G, int MODE, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     using X = Tile<EB>;
+    constexpr bool kStepping = MODE == kStep || MODE == kStepRagged;
     constexpr int kRowBytes = kHeadDim * EB;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
     constexpr int kTiles = CHUNK / 16 < kBlockWaves ? CHUNK / 16 : kBlockWaves;    // waves with 16-token tiles
@@ -1175,23 +1183,23 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
 
     // One region of LDS, used in turn by the selection (SelectShared, and the pair's scores on their way to the owning threads), by the
     // waves' value tiles and, in each wave's own tile, its partial sums (dim d, head g at [d * G + g]), and by the merge.
-    constexpr bool kSel = MODE == kFused || MODE == kStep;    // the block runs the selection itself
+    constexpr bool kSel = MODE == kFused || kStepping;    // the block runs the selection itself
     constexpr int kTileBytes = 16 * X::kPitch;
     static_assert(G * kHeadDim * 4 <= kTileBytes, "a wave's partial sums fit in its value tile");
     constexpr int kSelBytes = kSel ? (int)((sizeof(SelectShared) + 15) / 16 * 16) : 0;
-    constexpr int kKeyBytes = MODE == kStep ? kSelKreg * kBlockThreads * 4 : 0;
-    constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), MODE == kStep ? 0 : 16 * kBlockThreads);
+    constexpr int kKeyBytes = kStepping ? kSelKreg * kBlockThreads * 4 : 0;
+    constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), kStepping ? 0 : 16 * kBlockThreads);
     __shared__ __attribute__((aligned(16))) char sm[kShBytes];
     __shared__ WaveSums<kTiles> sm_waves;
     __shared__ int sm_last;
     __shared__ int32_t sm_row[CHUNK];
-    __shared__ float sm_merge[MODE == kStep ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
+    __shared__ float sm_merge[kStepping ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
 
     // kStep: a one-dimensional grid, pair fastest, so that the hardware's round-robin of consecutive blocks over the XCDs
     // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
     const int n_pairs = a.v.B * a.Hkv;
-    const int bh = MODE == kStep ? (int)(blockIdx.x % (unsigned)n_pairs) : (int)blockIdx.y;
-    const int split = MODE == kStep ? (int)(blockIdx.x / (unsigned)n_pairs) : (int)blockIdx.x;
+    const int bh = kStepping ? (int)(blockIdx.x % (unsigned)n_pairs) : (int)blockIdx.y;
+    const int split = kStepping ? (int)(blockIdx.x / (unsigned)n_pairs) : (int)blockIdx.x;
     const int b = bh / a.Hkv, h = bh % a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int t16 = lane & 15, qd = lane >> 4;
@@ -1202,12 +1210,14 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // after it has seen the partial of every attending block, each of which had seen every score of the pair: so every
     // block whose tag matters has read the epoch by then), and the pair's number makes tags of different pairs differ.
     uint32_t tag = 0;
-    if constexpr (MODE == kStep) {
-        demand_step_args(a);
+    if constexpr (kStepping) {
+        demand_step_args<MODE == kStepRagged>(a);
         tag = step_tag(ld_agent(a.step_epoch + bh * kStepEpochStride), bh);
     }
     const Seq sq = seq_of(a.v, b);
-    const int32_t j0 = split * CHUNK;
+    const int32_t chunk = MODE == kStepRagged ? a.chunk : CHUNK;        // tokens of a block
+    auto blocks_of = [&](int32_t tokens) { return MODE == kStepRagged ? ceil_div(tokens, chunk, a.per_chunk) : (tokens + CHUNK - 1) / CHUNK; };
+    const int32_t j0 = split * chunk;
     const int slot = split * (CHUNK / kWave);                     // partial slot (slots are counted in 64-token units)
     SKV_T(0);
 
@@ -1227,14 +1237,14 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     if constexpr (kSel) {
         SelectShared& sel_sh = *reinterpret_cast<SelectShared*>(sm);
         const int32_t budget = min(sq.budget, a.budget_cap);
-        if constexpr (MODE == kStep) {
+        if constexpr (kStepping) {
             // ---- 0. scores of this block's share of the pair's buckets, published to the pair's other blocks ---------
-            // Part `split` of the 2^lg_parts blocks of the pair owns the buckets [split * per, (split + 1) * per); wave
+            // Part `split` of the pair's blocks owns the buckets [split * per, (split + 1) * per); wave
             // w takes RPWV consecutive buckets at a time.  The arithmetic per bucket is that of score_kernel (same
             // lanes, same order), so skv_score returns the very floats that are ranked here.  Each score is stored
             // with the launch tag in one 64-bit word; the blocks that go on read the pair's words until all carry it.
             const int32_t S = sq.n_sent;
-            const int32_t per = (S + (1 << a.lg_parts) - 1) >> a.lg_parts;
+            const int32_t per = MODE == kStep ? (S + (1 << a.lg_parts) - 1) >> a.lg_parts : ceil_div(S, a.parts, a.per_part);
             const int32_t lo = split * per, hi = min(lo + per, S);
             const char* qg = a.q_score + ((qhead0 * kHeadDim) * EB);
             const int64_t row0 = (int64_t)h * a.v.S_total + sq.sent_base;
@@ -1274,7 +1284,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         const float* sc = a.score + (int64_t)h * a.v.S_total + sq.sent_base;
         const int32_t* len = a.sent_len + sq.sent_base;
         const int32_t* off = a.sent_off + sq.sent_base + (a.v.cu_sent ? b : 0);
-        if constexpr (MODE == kStep) {                            // the scores are being written by the pair's blocks
+        if constexpr (kStepping) {                            // the scores are being written by the pair's blocks
             const float* tsc = reinterpret_cast<const float*>(a.step_score + (int64_t)bh * a.score_stride);
             uint32_t* sm_keys = reinterpret_cast<uint32_t*>(sm + kSelBytes);
             if (sq.n_sent <= 2 * kBlockThreads)
@@ -1297,7 +1307,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // know that they hold no retrieved tokens.  Block 0 advances the epoch only after it has seen all of them, so that no
     // block of this launch can read the advanced epoch.
     auto presence = [&]() {
-        if constexpr (MODE == kStep) {
+        if constexpr (kStepping) {
             if (tid == 0)                                         // a block that gave up publishes nothing valid
                 st_tagged(a.step_part + (int64_t)blockIdx.x * G * kStepPartWords + kHeadDim, -INFINITY, step_ok ? tag : 0u);
         }
@@ -1305,8 +1315,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // block 0: the words of blocks first .. (blocks of the pair that run the selection) - 1 carry the tag (bounded wait);
     // every thread of the block calls this
     auto others_were_here = [&](int first) -> bool {
-        if constexpr (MODE == kStep) {
-            const int n_cand = min(1 << a.lg_parts, max(merging_blocks(G, a.lg_merge), (min(sq.budget, a.budget_cap) + CHUNK - 1) / CHUNK));
+        if constexpr (kStepping) {
+            const int n_cand = min(MODE == kStep ? 1 << a.lg_parts : a.parts, max(merging_blocks(G, a.lg_merge), blocks_of(max(min(sq.budget, a.budget_cap), 0))));
             if (n_cand <= first) return true;                     // block-uniform: the usual case, the budget is filled
             // the flag lives in the first word of the merge's scratch (thread 0, the only reader of that
             // word in the merge, is past its reads when it clears it)
@@ -1329,7 +1339,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             step_ok = others_were_here(1) && step_ok;
             for (int i = tid; i < kOut; i += kBlockThreads) a.out[qhead0 * kHeadDim + i] = step_ok ? 0.f : __builtin_nanf("");
             if (a.lse && tid < G) a.lse[qhead0 + tid] = -INFINITY;
-            if constexpr (MODE == kStep) {
+            if constexpr (kStepping) {
                 if (tid == 0) {
                     st_agent(a.step_epoch + bh * kStepEpochStride, tag >> kStepPairBits);     // this launch of the pair is over
                     if (!step_ok) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
@@ -1340,21 +1350,21 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         }
         return;
     }
-    const int nsplit = (n + CHUNK - 1) / CHUNK;
+    const int nsplit = blocks_of(n);
     // kStep: the first merging_blocks() blocks merge, whether or not they hold retrieved tokens themselves
     const bool has_work = split < nsplit;
     if (!has_work) {
         presence();
-        if (!(MODE == kStep && split < merging_blocks(G, a.lg_merge))) return;
+        if (!(kStepping && split < merging_blocks(G, a.lg_merge))) return;
     }
     unsigned long long* my_part = nullptr;
     uint32_t part_tag = 0;
-    if constexpr (MODE == kStep) {
+    if constexpr (kStepping) {
         my_part = a.step_part + (int64_t)blockIdx.x * G * kStepPartWords;
         part_tag = step_ok ? tag : 0u;                            // a block that gave up publishes nothing valid
     }
     if (has_work) {
-        const int32_t cnt = min(CHUNK, n - j0);
+        const int32_t cnt = min(chunk, n - j0);
         SKV_T(4);
 
         // ---- 1. issue every load of the chunk ------------------------------------------------------------
@@ -1378,6 +1388,14 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
                 // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
                 const int tile = w + kTiles * ps, jj = 16 * tile + t16;
+                if (ps > 0 && 16 * tile >= cnt) {                     // (wave-uniform) no second tile
+                    vm[ps] = 0;
+#pragma unroll
+                    for (int s2 = 0; s2 < X::kPieces; ++s2) kA[ps][s2] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < X::kLoads; ++i) vR[ps][i] = make_uint4(0, 0, 0, 0);
+                    continue;
+                }
                 bool liveK = jj < cnt;
                 int32_t rowK, rowV[X::kLoads];
                 if constexpr (MODE == kDirect) {
@@ -1394,7 +1412,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                         const int32_t start = __shfl(v, max(hp, 0));
                         x = hp >= 0 ? start + (lane - hp) : -1;
                         const int32_t pos = (tile >> 2) * kWave + lane;
-                        if ((tile & 3) == 0 && a.tok_idx_out && j0 + pos < n) a.tok_idx_out[(int64_t)bh * a.idx_stride + j0 + pos] = x;
+                        if ((tile & 3) == 0 && a.tok_idx_out && pos < cnt) a.tok_idx_out[(int64_t)bh * a.idx_stride + j0 + pos] = x;
                     } else {
                         x = a.tok_idx[(int64_t)bh * a.idx_stride + j0 + min(jj, cnt - 1)];
                     }
@@ -1455,7 +1473,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         }
         __syncthreads();
         block_sums<G, kTiles, false>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
-            if constexpr (MODE == kStep) {
+            if constexpr (kStepping) {
                 unsigned long long* dst = my_part + g * kStepPartWords;
                 st_tagged(dst + d, sum, part_tag);
                 if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
@@ -1471,7 +1489,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         SKV_T(7);
     }
 
-    if constexpr (MODE == kStep) {
+    if constexpr (kStepping) {
         // ---- 5'. merge without an arrival counter ---------------------------------------------------------------
         // Block m of the pair merges 128 >> lg_merge dims of query head m >> lg_merge, or two heads.  Thread (grp, col) -- consecutive
         // lanes on consecutive words of a partial row -- reads dim `col` of the partials of the splits grp, grp + groups, ...
@@ -2078,12 +2096,12 @@ hipError_t launch_select_attend(Ctx* c, const void* q, const void* K_layer, cons
 // Blocks of the single-launch kernel a compute unit can hold at once (registers, LDS), asked of the runtime once per
 // instantiation: the kernel's waits need every block of the grid resident, so the launcher refuses grids beyond
 // compute units x this number.
-template <int EB, int G, int CHUNK>
+template <int EB, int G, int MODE, int CHUNK>
 static int step_blocks_per_cu() {
     static int cached = -1;
     if (cached < 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, attend_kernel<EB, G, kStep, CHUNK>, kBlockThreads, 0) != hipSuccess) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, attend_kernel<EB, G, MODE, CHUNK>, kBlockThreads, 0) != hipSuccess) {
             (void)hipGetLastError();
             n = 0;
         }
@@ -2092,24 +2110,24 @@ static int step_blocks_per_cu() {
     return cached;
 }
 
-template <int EB, int CHUNK>
+template <int EB, int MODE, int CHUNK>
 static hipError_t launch_step_g(Ctx* c, const AttArgs& a, int n_blocks, bool* launched) {
     const dim3 grid(n_blocks), block(kBlockThreads);
     int per_cu = 0;
     switch (c->G) {
-        case 1: per_cu = step_blocks_per_cu<EB, 1, CHUNK>(); break;
-        case 2: per_cu = step_blocks_per_cu<EB, 2, CHUNK>(); break;
-        case 4: per_cu = step_blocks_per_cu<EB, 4, CHUNK>(); break;
-        case 8: per_cu = step_blocks_per_cu<EB, 8, CHUNK>(); break;
+        case 1: per_cu = step_blocks_per_cu<EB, 1, MODE, CHUNK>(); break;
+        case 2: per_cu = step_blocks_per_cu<EB, 2, MODE, CHUNK>(); break;
+        case 4: per_cu = step_blocks_per_cu<EB, 4, MODE, CHUNK>(); break;
+        case 8: per_cu = step_blocks_per_cu<EB, 8, MODE, CHUNK>(); break;
         default: return hipErrorInvalidValue;
     }
     if (per_cu < 1 || n_blocks > c->n_cu * per_cu) return hipSuccess;       // not every block would be resident: other forms
     *launched = true;
     switch (c->G) {
-        case 1: hipLaunchKernelGGL((attend_kernel<EB, 1, kStep, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 2: hipLaunchKernelGGL((attend_kernel<EB, 2, kStep, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 4: hipLaunchKernelGGL((attend_kernel<EB, 4, kStep, CHUNK>), grid, block, 0, c->stream, a); break;
-        case 8: hipLaunchKernelGGL((attend_kernel<EB, 8, kStep, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 1: hipLaunchKernelGGL((attend_kernel<EB, 1, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 2: hipLaunchKernelGGL((attend_kernel<EB, 2, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 4: hipLaunchKernelGGL((attend_kernel<EB, 4, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
+        case 8: hipLaunchKernelGGL((attend_kernel<EB, 8, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2123,32 +2141,31 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     const int max_blocks = c->n_cu < kStepMaxBlocks ? c->n_cu : kStepMaxBlocks;
     if (pairs < 1 || pairs > kStepMaxPairs || pairs > max_blocks || c->step_score_stride <= 0) return hipSuccess;
     if (v.S_total > c->step_score_stride || (int64_t)pairs * c->step_score_stride > c->step_score_words) return hipSuccess;
-    int lg = 0;
-    while ((pairs << (lg + 1)) <= max_blocks) ++lg;
-    const int parts = 1 << lg;
+    const int parts = max_blocks / pairs;
     const int sv_bytes = c->d.semvec_dtype == SKV_BF16 ? kTableBf16 : c->d.semvec_dtype == SKV_FP8_E4M3 ? kTableE4m3 : kTableF32;
-    // Attention blocks of 64 tokens, or of 128 or 256 when a pair has too few blocks: the K/V rows of a block pass its compute unit's
-    // 64 bytes a cycle and its four SIMDs, one 16-token tile each.  One sequence, us per layer in 128- / 64-token blocks: bf16
-    // budget 512: 10.9 / 10.0, 1000: 11.5 / 10.8, 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0.
-    int chunk = kAttChunk;
-    if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkMid;
-    if ((c->budget_cap + chunk - 1) / chunk > parts) chunk = kAttChunkWide;
-    // 512 tokens, bf16 only, where at least three quarters of the blocks attend and the mean-key rows take at most half the bytes of the
-    // retrieved ones: every attending block waits for all the scores of its pair, and the two-launch form spreads the rows over all compute
-    // units.  Us per 16 layers, two launches / one, 32 query heads: 8 sequences, budget 2048, rows 0.2 of the bytes: 410 / 374;
-    // 6 sequences, budget 1500, 0.2: 350 / 329, 0.3: 349 / 337, 0.6: 369 / 368; past the line: 8 sequences, budget 1100, 0.8: 414 / 450;
-    // 4 sequences, budget 2500, five blocks of eight: 390 / 396.
-    if (c->d.kv_dtype == SKV_BF16 && (c->budget_cap + chunk - 1) / chunk > parts) {
-        const int wide = 2 * kAttChunkWide, n = (c->budget_cap + wide - 1) / wide;
-        if (4 * n >= 3 * parts && (int64_t)v.S_total * sv_bytes <= (int64_t)v.B * c->budget_cap * 2) chunk = wide;
-    }
+    // Attention blocks of 64 or 128 tokens where a pair has a power of two of them and they cover the budget (MODE kStep; constants where the other
+    // form has arguments, 0.5 % of a step).  A block's K/V rows pass its compute unit at 34 bytes a nanosecond, so that small blocks are
+    // faster until there are too many partials to merge: one sequence, us per layer in 128- / 64-token blocks: bf16 budget 512: 10.9 / 10.0, 1000: 11.5 / 10.8,
+    // 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0; budget 2500 in 20 blocks of 128 / 32 of 80: 13.0 / 14.1.
+    // Otherwise (kStepRagged) every block of the pair takes an equal share.  Us per layer, powers of two of blocks of 128, 256 or 512 tokens / this: 3 sequences,
+    // budget 2048, eight blocks / ten: 19.2 / 18.2; 6 sequences, budget 1500, three blocks of four / five: 22.2 / 18.1; 8 sequences, budget 1100, two
+    // launches / four blocks: 22.2 / 18.8; 4 sequences, budget 1100, five of eight / eight: 19.3 / 18.6; budget 2500, two launches / eight: 23.2 / 19.9.
+    const bool even = (parts & (parts - 1)) == 0 && c->budget_cap <= parts * kAttChunkMid;
+    const int chunk = !even ? max((c->budget_cap + 16 * parts - 1) / (16 * parts) * 16, kAttChunk) : c->budget_cap <= parts * kAttChunk ? kAttChunk : kAttChunkMid;
+    const int most = c->d.kv_dtype == SKV_BF16 ? 2 * kAttChunkWide : kAttChunkWide;
+    if (chunk > most || parts < 2 || v.S_total >= (1 << 24)) return hipSuccess;
+    // More than 256 tokens, bf16 only: two tiles a wave.  Every attending block waits for all the scores of its pair, and the two-launch form spreads
+    // the rows over all compute units: where a sequence has more than 1024 buckets on average, the mean-key rows have to take at most half the
+    // bytes of the retrieved ones.  Two launches / one, us per layer: 6 sequences, budget 1500, 960 buckets, 0.64 of the bytes: 24.4 / 21.3; 8 sequences,
+    // budget 1300, 960, 0.74: 25.6 / 23.6; budget 2048, 1310, 0.64: 30.0 / 29.0; past the line: 6 sequences, budget 2048, 2621, 0.64: 27.2 / 28.8;
+    // budget 2048, 1600, 0.78: 27.3 / 27.7; 4 sequences, budget 2600, 2621, 1.0: 28.0 / 28.7.
+    if (chunk > kAttChunkWide && v.S_total > 1024ll * v.B && (int64_t)v.S_total * sv_bytes > (int64_t)v.B * c->budget_cap * 2) return hipSuccess;
     const int att_parts = (c->budget_cap + chunk - 1) / chunk;
-    if (att_parts > parts || c->G > 2 * parts) return hipSuccess;                // attention blocks or mergers do not fit
+    if (c->G > 2 * parts) return hipSuccess;                                     // mergers do not fit
     AttArgs a = att_common(c, q_attn, K_layer, V_layer, v, out, lse);
     a.sent_off = sent_off; a.sent_len = sent_len;
     a.tok_idx_out = tok_idx_out; a.n_tok_out = n_tok_out; a.idx_stride = c->d.max_budget;
     a.q_score = (const char*)q_score; a.semvec = (const char*)semvec_layer;
-    a.sv_bytes = sv_bytes;
     // Up to four blocks merge a head, 32 dims each, so that a thread has one word of a partial row to wait for instead of four (one sequence,
     // budget 2048, per layer: 12.8 -> 12.55 us, fp32 14.9 -> 14.5), as long as they all attend themselves: a block that runs the
     // selection only to merge costs more than it saves (budget 512, 8 query heads per KV head: 10.5 -> 12.0 with 32 of them).
@@ -2157,17 +2174,24 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     // two heads per merging block where a pair has fewer blocks that attend than heads: 8 query heads per KV head, 16 layers, 5 to 8
     // sequences 319 -> 278 us and 347 -> 304 (which had to take two launches), one sequence at a budget of 200 178 -> 173
     if (c->G > att_parts && c->G > 1 && (c->G > parts || c->G <= 2 * att_parts)) lg_merge = -1;
-    a.lg_parts = lg; a.lg_merge = lg_merge; a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
+    auto per = [](int n) { return (uint32_t)(((1ull << 32) + (unsigned long long)n - 1) / (unsigned long long)n); };
+    a.sv_bytes = sv_bytes; a.lg_parts = even ? __builtin_ctz(parts) : 0; a.lg_merge = lg_merge;
+    a.parts = parts; a.chunk = chunk; a.per_part = per(parts); a.per_chunk = per(chunk);
+    a.step_epoch = c->step_epoch; a.step_score = c->step_score; a.score_stride = c->step_score_stride;
     a.step_part = c->step_part; a.wait_limit = c->wait_limit;
     a.err_dev = c->err_dev; a.err_host = c->err_host_dev;
-    if (chunk == 2 * kAttChunkWide) return launch_step_g<2, 2 * kAttChunkWide>(c, a, pairs * parts, launched);
-    if (chunk == kAttChunkWide)
-        return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunkWide>(c, a, pairs * parts, launched)
-                                         : launch_step_g<4, kAttChunkWide>(c, a, pairs * parts, launched);
-    if (chunk == kAttChunk) return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunk>(c, a, pairs * parts, launched)
-                                     : launch_step_g<4, kAttChunk>(c, a, pairs * parts, launched);
-    return c->d.kv_dtype == SKV_BF16 ? launch_step_g<2, kAttChunkMid>(c, a, pairs * parts, launched)
-                                     : launch_step_g<4, kAttChunkMid>(c, a, pairs * parts, launched);
+    const bool bf16 = c->d.kv_dtype == SKV_BF16;
+    const int blocks = pairs * parts;
+    auto go = [&](auto mode, auto cap) {
+        constexpr int M = decltype(mode)::value, C = decltype(cap)::value;
+        return bf16 ? launch_step_g<2, M, C>(c, a, blocks, launched) : launch_step_g<4, M, C>(c, a, blocks, launched);
+    };
+    using std::integral_constant;
+    if (even && chunk == kAttChunk) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunk>{});
+    if (even) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunkMid>{});
+    if (chunk <= kAttChunkMid) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkMid>{});
+    if (chunk <= kAttChunkWide) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkWide>{});
+    return launch_step_g<2, kStepRagged, 2 * kAttChunkWide>(c, a, blocks, launched);
 }
 
 // ------------------------------------------------------------------------------------------------

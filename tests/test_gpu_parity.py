@@ -547,6 +547,19 @@ def test_fused_single_launch_two_tiles_per_wave(U, oracle32, B, budget, Hq):
     _fused_case(U, oracle32, wl, seed=36, layers=[0])
 
 
+@pytest.mark.parametrize("B,budgets,Hq,dtype", [
+    (3, [640, 1, 640], 32, "bf16"), (3, [641, 641, 0], 8, "bf16"), (3, [641, 640, 1], 64, "f32"),     # ten blocks of 64 and of 80 tokens; one token in the last
+    (3, [1281, 900, 1281], 32, "bf16"), (3, [2000, 2000, 2000], 32, "f32"),                           # of 144 and 208
+    (5, [1537, 1537, 100, 0, 1537], 64, "bf16"), (6, [1500] * 6, 32, "bf16"), (6, [1281, 1, 1280, 900, 1281, 320], 16, "f32"),   # six of 272; five of 304, 272
+    (7, [1000] * 7, 8, "f32"), (8, [1100, 1025, 1, 600, 1100, 0, 1100, 275], 32, "bf16"),             # four of 256; of 288
+    (4, [2500, 2500, 2100, 2500], 64, "bf16"), (3, [5000, 4801, 5000], 32, "bf16")])                  # eight of 320; ten of 512
+def test_fused_single_launch_equal_shares(U, oracle32, B, budgets, Hq, dtype):
+    """Blocks of an equal share of the largest budget, any number of them to a pair: shares that end in a block with one token, blocks
+    without any (smaller budgets, contexts shorter than the budget), one and two tiles a wave, mergers of parts of a head to two heads."""
+    wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(700, 5600), budgets=(max(budgets),), dtype=dtype)
+    _fused_case(U, oracle32, wl, seed=37, layers=[0], budgets=budgets, seq_tokens=np.random.default_rng(B).integers(700, 5600, B).tolist())
+
+
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
     """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20 with budget 1500), a last tile of one token and of
