@@ -893,6 +893,7 @@ hipError_t launch_gather(Ctx* c, const void* K_layer, const void* V_layer, int32
 // Attention (Eq. 3), split-K flash decoding.  A 1024-thread block (split, sequence * KV head) handles CHUNK consecutive retrieved
 // tokens for the G query heads of its KV head, a wave for every 16 of them (Tile, below).
 //   kDirect   : rows come from K_sel/V_sel and n_tok from memory (skv_attend).
+//   kDirectDims : as kDirect, all tokens and 32 dims of the output to a block: there is nothing to merge.
 //   kIndirect : rows of the pool through tok_idx, n_tok from memory.
 //   kFused, kStep : the block first runs the selection for its (sequence, head) from the scores (redundantly with the other splits: the
 //               scores are a few KB in L2, and it saves a launch plus a round trip through tok_idx) and reads
@@ -961,11 +962,12 @@ __device__ __forceinline__ float sum_quads(float x) {
 //  * A NaN among a head's live logits makes its normaliser NaN, and with it out and lse, through every sum and merge below.
 // fp32 through the vector pipe (rows over lanes, sums of the logits over 32 lanes by exchanges) took 3.7 us from the loads to
 // the logits of 128 tokens and 1.7 to the partial result, budget 512, 4 heads; see launch_step for what it takes now.
-template <int EB> struct Tile {
+template <int EB, int DIMS = kHeadDim> struct Tile {                // DIMS: dims of the value rows (bf16: 32, or all)
+    static_assert(EB == 2 || DIMS == kHeadDim, "fp32 pieces are exchanged over the whole row");
     static constexpr int kPieces = kHeadDim * EB / 64;                // key pieces of a lane
-    static constexpr int LPR = kHeadDim * EB / 16, RPL = kWave / LPR; // lanes of a value row, value rows of a load
+    static constexpr int LPR = DIMS * EB / 16, RPL = kWave / LPR; // lanes of a value row, value rows of a load
     static constexpr int kLoads = 16 / RPL;                           // value loads of a lane: rows RPL i + lane / LPR
-    static constexpr int kPitch = kHeadDim * EB + (EB == 2 ? 16 : 0); // bytes of a value row in LDS
+    static constexpr int kPitch = DIMS * EB + (EB == 2 ? 16 : 0); // bytes of a value row in LDS
     // place of 16-byte piece `piece` of value row `row` in the tile
     __device__ static __forceinline__ int place(int row, int piece) { return row * kPitch + 16 * (EB == 2 ? piece : piece ^ (4 * (row >> 2))); }
 
@@ -1001,7 +1003,7 @@ template <int EB> struct Tile {
         return p;
     }
     // o[dt] += P V of the tile at `v` (16 rows of pitch kPitch); element j of o[dt]: head 4 qd + j, dim 16 dt + t16
-    __device__ static __forceinline__ void output(const float (&p)[4], const char* v, int lane, f32x4_t (&o)[kHeadDim / 16]) {
+    __device__ static __forceinline__ void output(const float (&p)[4], const char* v, int lane, f32x4_t (&o)[DIMS / 16]) {
         const int t16 = lane & 15, qd = lane >> 4;
         if constexpr (EB == 2) {
             const bf16x4_t pa = {(short)(__float_as_uint(p[0]) >> 16), (short)(__float_as_uint(p[1]) >> 16), (short)(__float_as_uint(p[2]) >> 16),
@@ -1009,10 +1011,10 @@ template <int EB> struct Tile {
             // B fragments by the LDS transpose read: this lane points at dims 4 (t16 % 4) .. + 3 of value row 4 qd + t16 / 4
             const char* vtr = v + (4 * qd + (t16 >> 2)) * kPitch + 8 * (t16 & 3);
 #pragma unroll
-            for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, lds_read_tr16(vtr + 32 * dt), o[dt], 0, 0, 0);
+            for (int dt = 0; dt < DIMS / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, lds_read_tr16(vtr + 32 * dt), o[dt], 0, 0, 0);
         } else {
 #pragma unroll
-            for (int dt = 0; dt < kHeadDim / 16; ++dt) {
+            for (int dt = 0; dt < DIMS / 16; ++dt) {
                 const char* col = v + 4 * qd * kPitch + 64 * (dt ^ qd) + 4 * t16;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[j], *reinterpret_cast<const float*>(col + j * kPitch), o[dt], 0, 0, 0);
@@ -1042,12 +1044,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // A wave leaves its sums of P V (element j of o[dt]: head 4 qd + j, dim 16 dt + t16) in the space of its value tile, head fastest (dim d,
 // head g at [d * G + g]), so that a lane stores its heads of one dim with a single instruction.
-template <int G>
-__device__ __forceinline__ void leave_sums(char* tile, const f32x4_t (&o)[kHeadDim / 16]) {
+template <int G, int NDT>
+__device__ __forceinline__ void leave_sums(char* tile, const f32x4_t (&o)[NDT]) {
     const int lane = threadIdx.x & 63, t16 = lane & 15, qd = lane >> 4;
     if (4 * qd < G) {
 #pragma unroll
-        for (int dt = 0; dt < kHeadDim / 16; ++dt) {
+        for (int dt = 0; dt < NDT; ++dt) {
             float* dst = reinterpret_cast<float*>(tile) + (16 * dt + t16) * G + 4 * qd;
             if constexpr (G >= 4) *reinterpret_cast<float4*>(dst) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
             else if constexpr (G == 2) *reinterpret_cast<float2*>(dst) = make_float2(o[dt][0], o[dt][1]);
@@ -1068,10 +1070,10 @@ template <int NT> struct WaveSums {
 // A barrier later: the block's output relative to its common reference, from the sums that NT waves left `stride` bytes apart, each relative to
 // the wave's own max.  put(g, d, sum, reference, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
 // streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).
-template <int G, int NT, bool HEAD_FAST, typename Put>
+template <int G, int NT, bool HEAD_FAST, int DIMS = kHeadDim, typename Put>
 __device__ __forceinline__ void block_sums(const char* tiles, int stride, const WaveSums<NT>& ws, Put put) {
-    for (int i = threadIdx.x; i < G * kHeadDim; i += kBlockThreads) {
-        const int g = HEAD_FAST ? i % G : i / kHeadDim, d = HEAD_FAST ? i / G : i % kHeadDim;
+    for (int i = threadIdx.x; i < G * DIMS; i += kBlockThreads) {
+        const int g = HEAD_FAST ? i % G : i / DIMS, d = HEAD_FAST ? i / G : i % DIMS;
         float mw[NT], fw[NT], lw[NT];
 #pragma unroll
         for (int k = 0; k < NT; k += 4) {
@@ -1139,7 +1141,7 @@ struct AttArgs {
     uint32_t per_part, per_chunk;
 };
 
-enum { kDirect = 0, kFused = 1, kIndirect = 2, kStep = 3, kStepRagged = 4 };      // kStepRagged: any number of blocks, any share of the budget
+enum { kDirect = 0, kFused = 1, kIndirect = 2, kStep = 3, kStepRagged = 4, kDirectDims = 5 };      // kStepRagged: any number of blocks, any share of the budget
 
 // Every argument is demanded at this point, so the kernel-argument loads go out in one batch at the top of the kernel;
 // left alone, the compiler loads each argument before its first use: one dependent round trip per branch, and a
@@ -1163,6 +1165,7 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
     return POOL ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
 }
 
+constexpr int kDimsPerBlock = 32, kMaxDirectDims = 384;       // kDirectDims: dims of a block, tokens of a call
 // ceil(n / d) with `per` = 2^32 / d rounded up; exact while n + d <= 2^32 / d
 __device__ __forceinline__ int32_t ceil_div(int32_t n, int32_t d, uint32_t per) { return (int32_t)__umulhi((uint32_t)(n + d - 1), per); }
 
@@ -1170,14 +1173,16 @@ __device__ __forceinline__ int32_t ceil_div(int32_t n, int32_t d, uint32_t per) 
 // at once, see launch_step, launch_select_attend and launch_attend.
 template <int EB, int G, int MODE, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
-    using X = Tile<EB>;
+    constexpr int kDims = MODE == kDirectDims ? kDimsPerBlock : kHeadDim;         // dims of the output that a block makes
+    constexpr bool kRowsDirect = MODE == kDirect || MODE == kDirectDims;
+    using X = Tile<EB, kDims>;
     constexpr bool kStepping = MODE == kStep || MODE == kStepRagged;
     constexpr int kRowBytes = kHeadDim * EB;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
     constexpr int kTiles = CHUNK / 16 < kBlockWaves ? CHUNK / 16 : kBlockWaves;    // waves with 16-token tiles
     constexpr int kPasses = CHUNK / 16 / kTiles;              // tiles of such a wave: w, w + 16
     static_assert(kTiles * kPasses * 16 == CHUNK && CHUNK % kWave == 0 && kPasses <= (EB == 2 ? 2 : 1), "the rows of a wave's tiles are in registers together");
-    constexpr int kOut = G * kHeadDim;                        // outputs of the block
+    constexpr int kOut = G * kDims;                        // outputs of the block
     constexpr int kCol2 = kOut / 2;                           // float pairs over the G heads
     constexpr int kGroups = kBlockThreads / kCol2;            // split groups of the merge: 16, 8, 4, 2 for G = 1, 2, 4, 8
 
@@ -1185,7 +1190,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // waves' value tiles and, in each wave's own tile, its partial sums (dim d, head g at [d * G + g]), and by the merge.
     constexpr bool kSel = MODE == kFused || kStepping;    // the block runs the selection itself
     constexpr int kTileBytes = 16 * X::kPitch;
-    static_assert(G * kHeadDim * 4 <= kTileBytes, "a wave's partial sums fit in its value tile");
+    static_assert(kOut * 4 <= kTileBytes, "a wave's partial sums fit in its value tile");
     constexpr int kSelBytes = kSel ? (int)((sizeof(SelectShared) + 15) / 16 * 16) : 0;
     constexpr int kKeyBytes = kStepping ? kSelKreg * kBlockThreads * 4 : 0;
     constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), kStepping ? 0 : 16 * kBlockThreads);
@@ -1199,7 +1204,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
     const int n_pairs = a.v.B * a.Hkv;
     const int bh = kStepping ? (int)(blockIdx.x % (unsigned)n_pairs) : (int)blockIdx.y;
-    const int split = kStepping ? (int)(blockIdx.x / (unsigned)n_pairs) : (int)blockIdx.x;
+    const int split = kStepping ? (int)(blockIdx.x / (unsigned)n_pairs) : MODE == kDirectDims ? 0 : (int)blockIdx.x;
+    const int dim0 = MODE == kDirectDims ? (int)blockIdx.x * kDims : 0;        // first of the block's dims
     const int b = bh / a.Hkv, h = bh % a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int t16 = lane & 15, qd = lane >> 4;
@@ -1300,7 +1306,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         if (split == 0 && tid == 0 && a.n_tok_out) a.n_tok_out[bh] = n;
         __syncthreads();                                          // bucket starts are marked; the selection's LDS is free
     } else {
-        n = min(ld_const(a.n_tok, bh), MODE == kDirect ? a.row_stride : a.idx_stride);
+        n = min(ld_const(a.n_tok, bh), kRowsDirect ? a.row_stride : a.idx_stride);
     }
     // kStep: every block of the pair that ran the selection (and so used the epoch it read at its start) tells block 0 so
     // in the (reference, tag) word of its partial: the attending blocks with their partial, the others as soon as they
@@ -1337,8 +1343,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     if (n <= 0) {
         if (split == 0) {
             step_ok = others_were_here(1) && step_ok;
-            for (int i = tid; i < kOut; i += kBlockThreads) a.out[qhead0 * kHeadDim + i] = step_ok ? 0.f : __builtin_nanf("");
-            if (a.lse && tid < G) a.lse[qhead0 + tid] = -INFINITY;
+            for (int i = tid; i < kOut; i += kBlockThreads)
+                a.out[MODE == kDirectDims ? (qhead0 + i / kDims) * kHeadDim + dim0 + i % kDims : qhead0 * kHeadDim + i] = step_ok ? 0.f : __builtin_nanf("");
+            if (a.lse && tid < G && dim0 == 0) a.lse[qhead0 + tid] = -INFINITY;
             if constexpr (kStepping) {
                 if (tid == 0) {
                     st_agent(a.step_epoch + bh * kStepEpochStride, tag >> kStepPairBits);     // this launch of the pair is over
@@ -1350,7 +1357,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         }
         return;
     }
-    const int nsplit = blocks_of(n);
+    const int nsplit = MODE == kDirectDims ? 1 : blocks_of(n);
     // kStep: the first merging_blocks() blocks merge, whether or not they hold retrieved tokens themselves
     const bool has_work = split < nsplit;
     if (!has_work) {
@@ -1370,9 +1377,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         // ---- 1. issue every load of the chunk ------------------------------------------------------------
         const char* Kh;
         const char* Vh;
-        if (MODE == kDirect) {
+        if (kRowsDirect) {
             Kh = a.Kb + ((int64_t)bh * a.row_stride + j0) * kRowBytes;
-            Vh = a.Vb + ((int64_t)bh * a.row_stride + j0) * kRowBytes;
+            Vh = a.Vb + ((int64_t)bh * a.row_stride + j0) * kRowBytes + dim0 * EB;
         } else {
             Kh = a.Kb + ((int64_t)h * a.v.T_total + sq.tok_base) * kRowBytes;
             Vh = a.Vb + ((int64_t)h * a.v.T_total + sq.tok_base) * kRowBytes;
@@ -1398,7 +1405,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 }
                 bool liveK = jj < cnt;
                 int32_t rowK, rowV[X::kLoads];
-                if constexpr (MODE == kDirect) {
+                if constexpr (kRowsDirect) {
                     rowK = min(jj, cnt - 1);
 #pragma unroll
                     for (int i = 0; i < X::kLoads; ++i) rowV[i] = min(16 * tile + X::RPL * i + lane / X::LPR, cnt - 1);
@@ -1426,9 +1433,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                     for (int i = 0; i < X::kLoads; ++i) rowV[i] = __shfl(x, max(min(base + X::RPL * i + lane / X::LPR, last), 0));
                 }
 #pragma unroll
-                for (int s2 = 0; s2 < X::kPieces; ++s2) kA[ps][s2] = ld_row<MODE != kDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
+                for (int s2 = 0; s2 < X::kPieces; ++s2) kA[ps][s2] = ld_row<!kRowsDirect>(Kh + (int64_t)rowK * kRowBytes + 64 * s2 + 16 * qd);
 #pragma unroll
-                for (int i = 0; i < X::kLoads; ++i) vR[ps][i] = ld_row<MODE != kDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
+                for (int i = 0; i < X::kLoads; ++i) vR[ps][i] = ld_row<!kRowsDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
                 vm[ps] = __ballot(liveK);
             }
 #pragma unroll
@@ -1447,9 +1454,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
             mw = max_quads(mw);
             const float ref = mw > -INFINITY ? mw : 0.f;              // (no live token, or logits of NaN only: those weights are NaN)
-            f32x4_t o[kHeadDim / 16];
+            f32x4_t o[kDims / 16];
 #pragma unroll
-            for (int dt = 0; dt < kHeadDim / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int dt = 0; dt < kDims / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             float lw = 0.f;
 #pragma unroll
             for (int ps = 0; ps < kPasses; ++ps) {
@@ -1472,15 +1479,15 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             leave_sums<G>(sm_v, o);
         }
         __syncthreads();
-        block_sums<G, kTiles, false>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
+        block_sums<G, kTiles, false, kDims>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
             if constexpr (kStepping) {
                 unsigned long long* dst = my_part + g * kStepPartWords;
                 st_tagged(dst + d, sum, part_tag);
                 if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
             } else if (nsplit == 1) {                                 // the only block: its sums are the result
                 const bool empty = lb == 0.f;                       // every retrieved position was out of range
-                a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
-                if (a.lse && d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
+                a.out[(qhead0 + g) * kHeadDim + dim0 + d] = empty ? 0.f : sum / lb;
+                if (a.lse && dim0 + d == 0) a.lse[qhead0 + g] = empty ? -INFINITY : (mb + log2f(lb)) * kLn2;
             } else {
                 st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
                 if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
@@ -2012,7 +2019,19 @@ hipError_t launch_attend(Ctx* c, const void* q, const void* K_sel, const void* V
                          const int32_t* n_tok, int32_t budget, const SeqView& v, float* out, float* lse) {
     AttArgs a = att_common(c, q, K_sel, V_sel, v, out, lse);
     a.n_tok = n_tok; a.row_stride = row_stride;
-    // bf16, 129 to 256 tokens: one block, which writes the result itself (fp32 tiles keep the matrix cores of a compute unit busy too long for that: 16
+    // bf16, up to 384 tokens of few heads: blocks that take all tokens and a quarter of the dims each (kDirectDims), so that nothing is merged and
+    // a compute unit, which gets its rows at about 34 bytes a nanosecond, reads the keys and a quarter of the values.  Us per call, 4 query heads
+    // per KV head, before / now: 64 tokens 3.9 / 3.2, 128: 4.31 / 3.94, 256 (one block) 6.2 / 5.5, 257 (three blocks and a merge) 6.8 / 6.0, 384:
+    // 6.9 / 6.6, 512: 7.1 / 7.6; 8 query heads, 128: 5.2 / 4.2, 257: 7.8 / 6.4; one query head, 64: 3.5 / 3.1, 257: 6.0 / 5.9, 384: 6.1 / 6.5; halves of the
+    // dims, 257 tokens: 6.6.
+    constexpr int parts = kHeadDim / kDimsPerBlock;
+    if (c->d.kv_dtype == SKV_BF16 && budget <= (c->G > 1 ? kMaxDirectDims : kAttChunkWide) && v.B * c->d.n_kv_heads * parts <= c->n_cu) {
+        if (budget <= kAttChunk) return launch_attend_g<2, kDirectDims, kAttChunk>(c, a, parts);
+        if (budget <= kAttChunkMid) return launch_attend_g<2, kDirectDims, kAttChunkMid>(c, a, parts);
+        if (budget <= kAttChunkWide) return launch_attend_g<2, kDirectDims, kAttChunkWide>(c, a, parts);
+        return launch_attend_g<2, kDirectDims, 2 * kAttChunkWide>(c, a, parts);
+    }
+    // Else bf16, 129 to 256 tokens: one block, which writes the result itself (fp32 tiles keep the matrix cores of a compute unit busy too long for that: 16
     // tiles 0.9 us behind 8).  Else, for few (sequence, head) pairs, 128-token blocks.  The merging block's uncached reads of the partials cost about
     // 0.1 us per split, more than a 64-token block saves on its K/V rows (budget 2048: 11.0 us with 64-token blocks,
     // 9.2 with 128, 10.8 with 256; from a budget of 4096 on 256-token blocks are ahead).

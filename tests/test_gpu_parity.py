@@ -840,6 +840,27 @@ def _planted(kind, q, K, V, head, row):
 NOT_FINITE = ["query", "all queries", "key", "infinite key", "value"]
 
 
+@pytest.mark.parametrize("Hq", [8, 16, 32, 64])
+@pytest.mark.parametrize("budget", [1, 16, 17, 64, 65, 128, 129, 256, 257, 272, 273, 384, 385])
+def test_attend_blocks_of_dims(U, oracle32, budget, Hq):
+    """bf16 calls of up to 384 tokens: a block takes all tokens and 32 dims.  Full and shorter token counts, none at all, edges of tiles, of
+    blocks and of the second tiles, and the first size that goes back to blocks of tokens."""
+    wl = gen.CFG0.scaled(dtype="bf16", n_q_heads=Hq)
+    H, D = wl.n_kv_heads, wl.head_dim
+    g = torch.Generator(device=U.DEV)
+    g.manual_seed(budget)
+    q, K, V = (torch.empty(n, D, dtype=torch.bfloat16, device=U.DEV).normal_(generator=g) for n in (Hq, H * budget, H * budget))
+    K, V = K.view(H, budget, D), V.view(H, budget, D)
+    n_tok = np.array([budget, max(budget - 1, 0), 0, 1, max(budget - 16, 0), budget // 2, budget, budget][:H] + [budget] * max(H - 8, 0), dtype=np.int32)
+    out, lse = torch.full((Hq, D), 7.0, device=U.DEV), torch.full((Hq,), 7.0, device=U.DEV)
+    _say("attend, blocks of dims", budget, Hq)
+    U.make_ctx(wl, 4096, 64, max(budget, 64)).attend(q, K, V, U.i32(n_tok), budget, out, lse)
+    torch.cuda.synchronize()
+    o_ref, l_ref = oracle32.attend(U.np_of(q), U.np_of(K), U.np_of(V), n_tok)
+    _same_as_oracle(out.cpu().numpy(), o_ref, ATT_TOL["bf16"], (budget, Hq))
+    _same_as_oracle(lse.cpu().numpy(), l_ref, ATT_TOL["bf16"], (budget, Hq))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("budget", [17, 129, 257, 1025])
 def test_attend_carries_values_that_are_not_finite(U, oracle32, dtype, budget):
