@@ -71,13 +71,16 @@ int32_t wait_for_count(Ctx& c) {
 
 // ---- workspace: one block of device memory, carved the same way whether skv_create allocated it or it is the static
 // scratch array of skv_decode_step_noalloc ---------------------------------------------------------------------------
-constexpr int kWsParts = 16;
+constexpr int kWsParts = 17;
 // Fixed sizes of the tagged area (epochs, tagged scores, tagged partials) in the static scratch of
 // skv_decode_step_noalloc: that area must hold tagged words only, whatever descriptor a call brings (a word of some
 // other array could look like a valid tag), so it has the same extent for every descriptor.
 constexpr size_t kFixedEpochBytes = (size_t)skv::kStepMaxPairs * skv::kStepEpochStride * sizeof(unsigned int);
 constexpr size_t kFixedScoreWords = 128 * 1024;
 constexpr size_t kFixedPartBytes = (size_t)skv::kStepMaxBlocks * 8 * skv::kStepPartWords * sizeof(unsigned long long);
+
+// per layer: list, counts by digit, kept tokens per block, cut, counters
+constexpr size_t kRetainLayerBytes = skv::kRetList * 8 + 2048 * 4 + skv::kRetMaxChunks * 4 + 16 + 16;
 
 // fixed_tagged: the static-scratch form.  *score_stride receives the words per pair of the tagged scores.
 size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fixed_tagged, size_t sz[kWsParts], int32_t* score_stride) {
@@ -108,6 +111,7 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     const size_t heads = (size_t)d.n_layers * d.n_kv_heads, stat_heads = heads < (size_t)skv::kSweepStatHeads ? heads : (size_t)skv::kSweepStatHeads;
     sz[14] = fixed_tagged ? 0 : (size_t)skv::kSweepMaxBlocks * skv::kImportanceMaxRows * sizeof(unsigned long long);       // imp_part
     sz[15] = fixed_tagged ? 0 : stat_heads * skv::kImportanceMaxRows * sizeof(unsigned long long);                         // imp_stat
+    sz[16] = fixed_tagged || d.n_layers > skv::kRetMaxLayers ? 0 : (size_t)d.n_layers * kRetainLayerBytes;                // retention
     size_t total = 0;
     for (int i = 0; i < kWsParts; ++i) total += sz[i];
     return total;
@@ -135,6 +139,15 @@ void carve_workspace(Ctx& c, char* base, const size_t sz[kWsParts], int32_t scor
     c.imp_arrive = reinterpret_cast<unsigned int*>(p); p += sz[13];
     c.imp_part = sz[14] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[14];
     c.imp_stat = sz[15] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[15];
+    if (sz[16]) {
+        const size_t L = (size_t)c.d.n_layers;
+        c.ret_list = reinterpret_cast<unsigned long long*>(p);
+        c.ret_hist = reinterpret_cast<unsigned int*>(c.ret_list + L * skv::kRetList);
+        c.ret_chunk = reinterpret_cast<int32_t*>(c.ret_hist + L * 2048);
+        c.ret_cut = c.ret_chunk + L * skv::kRetMaxChunks;
+        c.ret_count = reinterpret_cast<unsigned int*>(c.ret_cut + 4 * L);
+    }
+    p += sz[16];
     c.imp_part_words = (int64_t)(sz[14] / sizeof(unsigned long long));
     c.imp_stat_words = (int64_t)(sz[15] / sizeof(unsigned long long));
 }

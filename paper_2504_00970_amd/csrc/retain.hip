@@ -1194,9 +1194,272 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
     for (int s = tid; s < S; s += kBlockThreads) ret_len[s] = ret_off[s + 1] - ret_off[s];
 }
 
+// ------------------------------------------------------------------------------------------------
+// Retention of long prompts: the same in three launches of several blocks per layer, 8192 tokens each.  One block per layer reads
+// its tokens' importances five times at what one compute unit gets, from 32769 tokens on from memory.
+//   digit:      counts by the top 11 bits of the key; the layer's last block finds the digit that holds the cut;
+//   candidates: the tokens of that digit go to a list, those above it are counted per block; the layer's last block finds the cut among the
+//               listed ones (more than kRetList of them: among all tokens, as the single block would), the last position kept of those that equal
+//               it, and the kept tokens before every block;
+//   compact:    kept positions, ret_off at the first token of every bucket (the kept tokens before it), ret_len by the layer's last block.
+// Bound by latency: three launches, each with an arrival and the last block's block scans, about 7 us apiece.  Us per call, one block a layer /
+// this: 32 layers x 16500 tokens 21.4 / 20.2 (16384: 20.9, the line), 32768 27.6 / 21.1, 16 x 65536 67.6 / 22.5, 8 x 131072 128 / 24.
+// ------------------------------------------------------------------------------------------------
+constexpr int kRetTok = 8, kRetChunk = kRetTok * kBlockThreads;      // tokens of a thread, of a block
+struct RetainWork {
+    unsigned int* hist;           // [L][2048], zero between calls
+    unsigned long long* list;     // [L][kRetList] (key, position)
+    unsigned int* count;          // [L][4] arrivals, length of the list; zero between calls
+    int32_t* cut;                 // [L][4] digit, tokens above it; then key of the cut, last position kept of those that equal it
+    int32_t* chunk;               // [L][kRetMaxChunks] tokens above the digit, then kept tokens before the block
+};
+
+// this wave's tokens of its block, i0 + 64 j, and their keys (0 past the end)
+struct RetainTokens {
+    int32_t i0;
+    uint32_t key[kRetTok];
+    __device__ __forceinline__ RetainTokens(const float* __restrict__ alpha, int32_t Tp) {
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        i0 = blockIdx.x * kRetChunk + w * (kRetTok * kWave) + lane;
+        float x[kRetTok];
+#pragma unroll
+        for (int j = 0; j < kRetTok; ++j) x[j] = alpha[min(i0 + j * kWave, Tp - 1)];
+#pragma unroll
+        for (int j = 0; j < kRetTok; ++j) key[j] = score_key(x[j]);
+    }
+};
+// true in the block of the layer that arrives last (all of the layer's stores before it are visible to it)
+__device__ __forceinline__ bool retain_last(unsigned int* arrive, int* sm_last) {
+    block_sync_after_stores();
+    if (threadIdx.x == 0) {
+        *sm_last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (*sm_last) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // for the next launch
+    }
+    __syncthreads();
+    return *sm_last != 0;
+}
+// The digit (of nbins <= 2048, counts by `count`) that holds the need-th largest; res = digit, number above it.  Every thread calls it.
+template <typename Count>
+__device__ __forceinline__ void retain_cross(int nbins, uint32_t need, Count count, uint32_t* slot, int32_t* res) {
+    const int d1 = nbins - 1 - 2 * (int)threadIdx.x;
+    const uint32_t c1 = d1 >= 0 ? count(d1) : 0u, c0 = d1 >= 1 ? count(d1 - 1) : 0u;
+    uint32_t total;
+    const uint32_t above1 = block_scan_u32(c1 + c0, slot, &total) - c1 - c0, above0 = above1 + c1;
+    if (c1 > 0 && above1 < need && above0 >= need) { res[0] = d1; res[1] = (int32_t)above1; }
+    if (c0 > 0 && above0 < need && above0 + c0 >= need) { res[0] = d1 - 1; res[1] = (int32_t)above0; }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kBlockThreads) void retain_digit_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
+    __shared__ uint32_t hist[2048], wave_tot[kBlockWaves];
+    __shared__ int32_t res[2];
+    __shared__ int sm_last;
+    const int l = blockIdx.y, tid = threadIdx.x;
+    const RetainTokens t(alpha_all + (int64_t)l * Tp, Tp);
+    for (int i = tid; i < 2048; i += kBlockThreads) hist[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j)
+        if (t.i0 + j * kWave < Tp) atomicAdd(&hist[t.key[j] >> 21], 1u);
+    __syncthreads();
+    unsigned int* all = wk.hist + (int64_t)l * 2048;
+    for (int i = tid; i < 2048; i += kBlockThreads)
+        if (hist[i] != 0) __hip_atomic_fetch_add(all + i, hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!retain_last(wk.count + 4 * l, &sm_last)) return;
+    retain_cross(2048, (uint32_t)min(k, Tp), [&](int d) { return ld_agent(all + d); }, wave_tot, res);
+    if (tid < 2) wk.cut[4 * l + tid] = res[tid];
+    for (int i = tid; i < 2048; i += kBlockThreads) st_agent(all + i, 0u);
+}
+
+__global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
+    __shared__ uint32_t hist[2048], wave_tot[2][kBlockWaves], before[kRetMaxChunks];
+    __shared__ int32_t equal[kRetList];
+    __shared__ int32_t res[2], tie, n_equal;
+    __shared__ uint32_t sm_base;
+    __shared__ int sm_last;
+    const int l = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nchunk = gridDim.x;
+    const float* alpha = alpha_all + (int64_t)l * Tp;
+    const uint32_t digit = (uint32_t)wk.cut[4 * l], above = (uint32_t)wk.cut[4 * l + 1];
+    const RetainTokens t(alpha, Tp);
+    auto lower = [&](unsigned long long m) { return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
+    uint32_t n_above = 0, n_cand = 0;
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j) {
+        const bool exists = t.i0 + j * kWave < Tp;
+        n_above += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> 21) > digit));
+        n_cand += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> 21) == digit));
+    }
+    uint32_t all_above, all_cand;
+    (void)block_scan_u32(lane == 0 ? n_above : 0u, wave_tot[0], &all_above);
+    uint32_t at = block_scan_u32(lane == 0 ? n_cand : 0u, wave_tot[1], &all_cand);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)(at - n_cand));                 // candidates of the block's waves before this one
+    if (tid == 0) {
+        sm_base = __hip_atomic_fetch_add(wk.count + 4 * l + 1, all_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        st_agent(wk.chunk + (int64_t)l * kRetMaxChunks + blockIdx.x, (int32_t)all_above);
+    }
+    __syncthreads();
+    at += sm_base;
+    unsigned long long* list = wk.list + (int64_t)l * kRetList;
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j) {
+        const bool cand = t.i0 + j * kWave < Tp && (t.key[j] >> 21) == digit;
+        const unsigned long long m = __ballot(cand);
+        const uint32_t to = at + lower(m);
+        if (cand && to < (uint32_t)kRetList)
+            __hip_atomic_store(list + to, ((unsigned long long)t.key[j] << 32) | (uint32_t)(t.i0 + j * kWave), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at += (uint32_t)__popcll(m);
+    }
+    if (!retain_last(wk.count + 4 * l, &sm_last)) return;
+
+    // ---- the layer's last block ----------------------------------------------------------------------------
+    const uint32_t listed = ld_agent(wk.count + 4 * l + 1);
+    const bool fits = listed <= (uint32_t)kRetList;
+    uint32_t need = (uint32_t)min(k, Tp) - above;                     // of the candidates, at least one
+    constexpr int kMine = kRetList / kBlockThreads;
+    unsigned long long mine[kMine];
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) mine[j] = __hip_atomic_load(list + j * kBlockThreads + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // fn(key, position) for every candidate: the listed ones, or those among all tokens
+    auto for_candidates = [&](auto&& fn) {
+        if (fits) {
+#pragma unroll
+            for (int j = 0; j < kMine; ++j)
+                if ((uint32_t)(j * kBlockThreads + tid) < listed) fn((uint32_t)(mine[j] >> 32), (int32_t)(uint32_t)mine[j]);
+        } else {
+            for (int32_t i = tid; i < Tp; i += kBlockThreads) {
+                const uint32_t key = score_key(alpha[i]);
+                if ((key >> 21) == digit) fn(key, i);
+            }
+        }
+    };
+    uint32_t prefix = digit;
+    int shift = 21;
+    for (int pass = 0; pass < 2; ++pass) {
+        const int bits = pass == 0 ? 11 : 10;
+        for (int i = tid; i < 2048; i += kBlockThreads) hist[i] = 0;
+        __syncthreads();
+        for_candidates([&](uint32_t key, int32_t) {
+            if ((key >> shift) == prefix) atomicAdd(&hist[(key >> (shift - bits)) & ((1u << bits) - 1u)], 1u);
+        });
+        __syncthreads();
+        retain_cross(1 << bits, need, [&](int d) { return hist[d]; }, wave_tot[pass], res);
+        prefix = (prefix << bits) | (uint32_t)res[0];
+        need -= (uint32_t)res[1];
+        shift -= bits;
+        __syncthreads();
+    }
+    // `need` of the tokens whose key is `prefix` are kept, those of the lowest positions
+    const uint32_t n_eq = hist[prefix & 1023u];
+    if (tid == 0) { tie = Tp; n_equal = 0; }
+    for (int i = tid; i < nchunk; i += kBlockThreads) before[i] = fits ? (uint32_t)ld_agent(wk.chunk + (int64_t)l * kRetMaxChunks + i) : 0u;
+    __syncthreads();
+    if (need < n_eq) {
+        if (n_eq <= (uint32_t)kRetList) {
+            for_candidates([&](uint32_t key, int32_t i) { if (key == prefix) equal[atomicAdd(&n_equal, 1)] = i; });
+            __syncthreads();
+            for (int e = tid; e < (int)n_eq; e += kBlockThreads) {
+                uint32_t rank = 0;
+                for (int o = 0; o < (int)n_eq; ++o) rank += equal[o] < equal[e];
+                if (rank == need - 1) tie = equal[e];
+            }
+        } else {                                                       // a plateau: in position order, 1024 tokens at a time
+            uint32_t seen = 0;
+            for (int32_t g = 0; g < Tp && seen < need; g += kBlockThreads) {
+                const uint32_t eq = g + tid < Tp && score_key(alpha[min(g + tid, Tp - 1)]) == prefix;
+                uint32_t total;
+                const uint32_t rank = seen + block_scan_u32(eq, wave_tot[0], &total);
+                if (eq && rank == need) tie = g + tid;
+                seen += total;
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+    }
+    if (fits) {
+        for_candidates([&](uint32_t key, int32_t i) { if (key > prefix || (key == prefix && i <= tie)) atomicAdd(&before[i / kRetChunk], 1u); });
+    } else {
+        for (int32_t g = 0; g < Tp; g += kBlockThreads) {
+            const int32_t i = g + tid;
+            const uint32_t key = score_key(alpha[min(i, Tp - 1)]);
+            const unsigned long long m = __ballot(i < Tp && (key > prefix || (key == prefix && i <= tie)));
+            if (lane == 0 && m != 0) atomicAdd(&before[(g + w * kWave) / kRetChunk], (uint32_t)__popcll(m));
+        }
+    }
+    __syncthreads();
+    if (w == 0) {                                                      // kRetMaxChunks = 128: two a lane
+        const uint32_t a = 2 * lane < nchunk ? before[2 * lane] : 0u, b = 2 * lane + 1 < nchunk ? before[2 * lane + 1] : 0u;
+        const uint32_t ex = wave_scan_u32(a + b) - a - b;
+        int32_t* dst = wk.chunk + (int64_t)l * kRetMaxChunks + 2 * lane;
+        if (2 * lane < nchunk) dst[0] = (int32_t)ex;
+        if (2 * lane + 1 < nchunk) dst[1] = (int32_t)(ex + a);
+    }
+    if (tid == 0) {
+        wk.cut[4 * l + 2] = (int32_t)prefix;
+        wk.cut[4 * l + 3] = tie;
+        st_agent(wk.count + 4 * l + 1, 0u);                            // for the next call
+    }
+}
+
+__global__ __launch_bounds__(kBlockThreads) void retain_compact_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k,
+                                                                       const int32_t* __restrict__ seg_id, int32_t S, int32_t* __restrict__ keep_all,
+                                                                       int32_t keep_stride, int32_t* __restrict__ n_keep, int32_t* ret_off_all,
+                                                                       int32_t* __restrict__ ret_len_all, RetainWork wk) {
+    __shared__ uint32_t wave_tot[kBlockWaves];
+    __shared__ int sm_last;
+    const int l = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    int32_t* keep = keep_all + (int64_t)l * keep_stride;
+    int32_t* ret_off = ret_off_all + (int64_t)l * (S + 1);
+    const int32_t need = min(k, Tp);
+    const uint32_t cut = (uint32_t)wk.cut[4 * l + 2];
+    const int32_t tie = wk.cut[4 * l + 3];
+    const RetainTokens t(alpha_all + (int64_t)l * Tp, Tp);
+    int32_t cur[kRetTok], prev[kRetTok];
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j) {
+        const int32_t i = min(t.i0 + j * kWave, Tp - 1);
+        cur[j] = seg_id[i];
+        prev[j] = seg_id[max(i - 1, 0)];
+    }
+    unsigned long long kept[kRetTok];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j) {
+        const int32_t i = t.i0 + j * kWave;
+        kept[j] = __ballot(i < Tp && (t.key[j] > cut || (t.key[j] == cut && i <= tie)));
+        mine += (uint32_t)__popcll(kept[j]);
+    }
+    uint32_t total;
+    uint32_t pos = block_scan_u32(lane == 0 ? mine : 0u, wave_tot, &total) - mine;
+    pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)wk.chunk[(int64_t)l * kRetMaxChunks + blockIdx.x];
+#pragma unroll
+    for (int j = 0; j < kRetTok; ++j) {
+        const int32_t i = t.i0 + j * kWave;
+        const uint32_t at = pos + (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept[j], 0u));
+        if ((kept[j] >> lane) & 1ull) keep[at] = i;
+        if (i < Tp) {
+            const int32_t c = min(max(cur[j], 0), S - 1), p = i > 0 ? min(max(prev[j], 0), S - 1) : -1;
+            for (int32_t s = p + 1; s <= c; ++s) st_agent(ret_off + s, (int32_t)at);
+            if (i == Tp - 1)
+                for (int32_t s = c + 1; s <= S; ++s) st_agent(ret_off + s, need);
+        }
+        pos += (uint32_t)__popcll(kept[j]);
+    }
+    if (blockIdx.x == 0 && tid == 0) n_keep[l] = need;
+    if (!retain_last(wk.count + 4 * l, &sm_last)) return;
+    for (int s = tid; s < S; s += kBlockThreads) ret_len_all[(int64_t)l * S + s] = ld_agent(ret_off + s + 1) - ld_agent(ret_off + s);
+}
+
 hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
                          int32_t* n_keep, int32_t* ret_off, int32_t* ret_len) {
     const dim3 grid(c->d.n_layers), block(kBlockThreads);
+    if (k > 0 && c->ret_hist && Tp > kRetainLongTok && (Tp + kRetChunk - 1) / kRetChunk <= kRetMaxChunks) {
+        const RetainWork wk = {c->ret_hist, c->ret_list, c->ret_count, c->ret_cut, c->ret_chunk};
+        const dim3 chunks((Tp + kRetChunk - 1) / kRetChunk, c->d.n_layers);
+        hipLaunchKernelGGL(retain_digit_kernel, chunks, block, 0, c->stream, alpha, Tp, k, wk);
+        hipLaunchKernelGGL(retain_candidates_kernel, chunks, block, 0, c->stream, alpha, Tp, k, wk);
+        hipLaunchKernelGGL(retain_compact_kernel, chunks, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len, wk);
+        return hipGetLastError();
+    }
     if (Tp <= 4 * kBlockThreads)
         hipLaunchKernelGGL(retain_kernel<4>, grid, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len);
     else                                                               // prompts up to 32K in registers

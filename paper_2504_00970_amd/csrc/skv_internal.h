@@ -83,6 +83,10 @@ struct Ctx {
     unsigned long long* imp_part;    // its tagged words: [kSweepMaxBlocks][kImportanceMaxRows] (null: no sweep)
     unsigned long long* imp_stat;    // [min(heads, kSweepStatHeads)][kImportanceMaxRows]
     int64_t imp_part_words, imp_stat_words;
+    unsigned int* ret_hist;      // scratch of the retention of long prompts (RetainWork; null: more than kRetMaxLayers layers)
+    unsigned long long* ret_list;
+    unsigned int* ret_count;
+    int32_t *ret_cut, *ret_chunk;
     unsigned int* n_sent_host;   // S of the last segmentation in pinned host memory (host address; null: none)
     unsigned int* n_sent_host_dev;   // its device address
     int wait_limit;              // polling rounds before a waiting block gives up
@@ -120,6 +124,9 @@ constexpr int kSweepStatHeads = 1024;
 constexpr unsigned int kSweepTags = (1u << 24) - 1;
 constexpr int kSweepMostHeads = 1 << 20;
 constexpr int kSweepWaitLimit = 8000;
+// retention of long prompts by several blocks per layer: tokens from which it is used, layers and blocks per layer it has scratch for, listed tokens
+constexpr int kRetainLongTok = 16384;
+constexpr int kRetMaxLayers = 256, kRetMaxChunks = 128, kRetList = 4096;
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N);
 int64_t importance_counters(const skv_desc& d);
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work);

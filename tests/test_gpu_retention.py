@@ -277,6 +277,34 @@ def test_retain_bit_exact(U, oracle32, Tp):
             assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
 
 
+@pytest.mark.parametrize("Tp", [16384, 16385, 24576, 24577, 131072, 200001])
+def test_retain_long_prompts(U, oracle32, Tp):
+    """Several blocks per layer (from 16385 tokens on), 8192 tokens each.  Layers: spread values; the cut among 4096 and 4097 tokens that share the first
+    11 bits (the list's length and one more), distinct and in groups of equal ones; all tokens equal; all within one digit; mostly NaN.
+    Called twice: the scratch is as the first call found it."""
+    _say("retain, long prompt", Tp)
+    rng = np.random.default_rng(Tp)
+    lens = gen.sentence_lengths(("uniform", 1, 40), Tp + 8, seed=Tp)
+    seg = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    rows = [np.exp(1.5 * rng.standard_normal(Tp))]
+    for n, equal in ((4096, 1), (4097, 1), (4096, 7), (4097, 7)):
+        x = np.full(Tp, 0.25)
+        x[rng.permutation(Tp)[:n]] = 1.0 + (np.arange(n) // equal) * 2.0 ** -23
+        rows.append(x)
+    rows += [np.full(Tp, 3.0), 1.0 + rng.permutation(Tp) * 2.0 ** -21, np.where(rng.random(Tp) < 0.9, np.nan, -rng.random(Tp))]
+    alpha = np.stack(rows).astype(np.float32)
+    L, S = len(rows), len(lens)
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=L), Tp + 8, S, 16)
+    a_dev = torch.from_numpy(alpha).to(U.DEV)
+    for k in (1, 2000, 4095, 4096, 4097, Tp // 3, Tp, 2000):
+        keep, n_keep, off, ln = _gpu_retain(U, ctx, a_dev, k, seg, S)
+        for l in range(L):
+            want_keep, want_off, want_len = oracle32.retain(alpha[l], k, seg, S)
+            assert n_keep[l] == len(want_keep)
+            assert np.array_equal(keep[l, :n_keep[l]], want_keep) and np.all(keep[l, n_keep[l]:] == -9), (k, l)
+            assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
+
+
 @pytest.mark.parametrize("S", [50, 3000, 7000])
 def test_select_ignores_buckets_without_tokens(U, oracle32, S):
     """Zero-length buckets (a retained pool has them) are never listed, in both the register and the re-read path of
