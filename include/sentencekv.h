@@ -244,9 +244,9 @@ int skv_attend(skv_ctx* ctx, const void* q_attn, const void* K_sel, const void* 
  * floating-point sums and, in bf16, to which tokens' largest logit a weight is rounded relative to.
  * Launches per call (P = B * Hkv pairs of sequence and KV head, G query heads each, all sizes from the descriptor's max_budget or
  * the tighter bound of skv_set_budget_hint):
- *   - ONE, when P <= 64 and the pair's 2^k blocks (2^k the largest power of two with P * 2^k <= 256 compute units) cover the
- *     budget in attention blocks of 64, 128 or 256 tokens, in bf16 also of 512 where three quarters of the blocks attend and
- *     the table takes at most half the bytes of the retrieved rows, and G <= 2 * 2^k: the blocks first score the buckets of
+ *   - ONE, when P <= 64 and the pair's floor(256 / P) blocks (256 compute units) cover the budget with equal shares of up to 256
+ *     tokens, in bf16 also of up to 512 where a sequence has at most 1024 buckets on average or the table takes at most half the bytes of
+ *     the retrieved rows, and G <= 2 * floor(256 / P): the blocks first score the buckets of
  *     their pair between them, pass the scores and later the partial attention results to each other inside the kernel, select
  *     and attend.  The waits inside the kernel are bounded, see skv_set_wait_limit;
  *   - TWO otherwise (scores; selection + attention in blocks of 64 to 256 tokens, or in streaming blocks of 512,

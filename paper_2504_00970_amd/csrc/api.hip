@@ -109,9 +109,11 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     sz[12] = 256;                                                                  // err_dev, seg_arrive, imp_state
     sz[13] = fixed_tagged ? 0 : round256((size_t)skv::importance_counters(d) * sizeof(unsigned int));    // imp_arrive
     const size_t heads = (size_t)d.n_layers * d.n_kv_heads, stat_heads = heads < (size_t)skv::kSweepStatHeads ? heads : (size_t)skv::kSweepStatHeads;
-    sz[14] = fixed_tagged ? 0 : (size_t)skv::kSweepMaxBlocks * skv::kImportanceMaxRows * sizeof(unsigned long long);       // imp_part
-    sz[15] = fixed_tagged ? 0 : stat_heads * skv::kImportanceMaxRows * sizeof(unsigned long long);                         // imp_stat
-    sz[16] = fixed_tagged || d.n_layers > skv::kRetMaxLayers ? 0 : (size_t)d.n_layers * kRetainLayerBytes;                // retention
+    // only where the calls that use them can be made: creating a context takes as long as its memory does
+    const bool sweeps = !fixed_tagged && skv::importance_may_sweep(d);
+    sz[14] = sweeps ? (size_t)skv::kSweepMaxBlocks * skv::kSweepMaxRows * sizeof(unsigned long long) : 0;                  // imp_part
+    sz[15] = sweeps ? stat_heads * skv::kSweepMaxRows * sizeof(unsigned long long) : 0;                                    // imp_stat
+    sz[16] = fixed_tagged || d.n_layers > skv::kRetMaxLayers || d.max_tokens <= skv::kRetainLongTok ? 0 : round256((size_t)d.n_layers * kRetainLayerBytes);
     size_t total = 0;
     for (int i = 0; i < kWsParts; ++i) total += sz[i];
     return total;
@@ -138,7 +140,7 @@ void carve_workspace(Ctx& c, char* base, const size_t sz[kWsParts], int32_t scor
     c.imp_state = reinterpret_cast<unsigned int*>(p + 192); p += sz[12];
     c.imp_arrive = reinterpret_cast<unsigned int*>(p); p += sz[13];
     c.imp_part = sz[14] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[14];
-    c.imp_stat = sz[15] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[15];
+    c.imp_stat = sz[14] ? reinterpret_cast<unsigned long long*>(p) : nullptr; p += sz[15];
     if (sz[16]) {
         const size_t L = (size_t)c.d.n_layers;
         c.ret_list = reinterpret_cast<unsigned long long*>(p);

@@ -943,11 +943,17 @@ static int sweep_blocks(const Ctx* c) { return min(kSweepPerCu * c->n_cu, kSweep
 // chunks enough (32 layers x 8 heads of 1024 keys, 32 rows, 256 chunks: 33.0 / 29.5; 8 layers, 64 chunks: 19.7 / 26.1; 2048 keys, 128 chunks: 23.3 / 23.2).
 // 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 418, 715 / 573); 128 rows, a chunk of 256 keys a block, from 4096 keys
 // (131 / 121; 3000 keys: 97 / 100) to 64 chunks a head (16384 keys 448 / 413; 24000: 615 / 618, 32768: 821 / 819, 65000, 8 layers: 426 / 436).
+bool importance_may_sweep(const skv_desc& d) {
+    const int64_t heads = (int64_t)d.n_layers * d.n_kv_heads;
+    static_assert(Sweep<1>::kChunkKeys >= kSweepMinChunk && Sweep<2>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kRows <= kSweepMaxRows, "");
+    return d.kv_dtype == SKV_BF16 && heads <= kSweepMostHeads && heads * ((d.max_tokens + kSweepMinChunk - 1) / kSweepMinChunk) >= kSweepMinChunks;
+}
+
 template <int RT>
 static bool importance_sweeps(const Ctx* c, int32_t T) {
     using P = Sweep<RT>;
     const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, nch = (T + P::kChunkKeys - 1) / P::kChunkKeys, most = sweep_blocks(c);
-    if (!c->single_launch || !c->imp_part || nch > most || heads > kSweepMostHeads || heads * nch > (1 << 30) || heads * nch < 128) return false;
+    if (!c->single_launch || !c->imp_part || nch > most || heads > kSweepMostHeads || heads * nch > (1 << 30) || heads * nch < kSweepMinChunks) return false;
     return RT < 4 || (T >= 4096 && nch <= 64);
 }
 

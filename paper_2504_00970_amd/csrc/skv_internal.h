@@ -80,8 +80,8 @@ struct Ctx {
     unsigned long long* seg_arrive;  // [1] blocks of the segmentation that are done (high word) and S (low word); zero between calls
     unsigned int* imp_arrive;    // [importance_counters] arrivals of the importance passes; zero between calls
     unsigned int* imp_state;     // [4] numbers of the one-sweep importance (SweepArgs::state)
-    unsigned long long* imp_part;    // its tagged words: [kSweepMaxBlocks][kImportanceMaxRows] (null: no sweep)
-    unsigned long long* imp_stat;    // [min(heads, kSweepStatHeads)][kImportanceMaxRows]
+    unsigned long long* imp_part;    // its tagged words: [kSweepMaxBlocks][kSweepMaxRows] (null: no sweep)
+    unsigned long long* imp_stat;    // [min(heads, kSweepStatHeads)][kSweepMaxRows]
     int64_t imp_part_words, imp_stat_words;
     unsigned int* ret_hist;      // scratch of the retention of long prompts (RetainWork; null: more than kRetMaxLayers layers)
     unsigned long long* ret_list;
@@ -120,6 +120,7 @@ constexpr int kImportanceMaxRows = 256;   // query rows (G * window tokens) per 
 // tag, and the polling rounds (about a microsecond each) before a block leaves the work to the two passes
 constexpr int kSweepPerCu = 2;
 constexpr int kSweepMaxBlocks = kSweepPerCu * kComputeUnits;
+constexpr int kSweepMaxRows = 128, kSweepMinChunk = 256, kSweepMinChunks = 128;      // rows, keys of the shortest chunk, chunks of the smallest launch
 constexpr int kSweepStatHeads = 1024;
 constexpr unsigned int kSweepTags = (1u << 24) - 1;
 constexpr int kSweepMostHeads = 1 << 20;
@@ -129,6 +130,7 @@ constexpr int kRetainLongTok = 16384;
 constexpr int kRetMaxLayers = 256, kRetMaxChunks = 128, kRetList = 4096;
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N);
 int64_t importance_counters(const skv_desc& d);
+bool importance_may_sweep(const skv_desc& d);
 hipError_t launch_importance(Ctx* c, const void* q_obs, const void* K_pool, int32_t T, int32_t N, float* alpha, void* work);
 hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
                          int32_t* n_keep, int32_t* ret_off, int32_t* ret_len);
