@@ -1201,22 +1201,25 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
 }
 
 // ------------------------------------------------------------------------------------------------
-// Retention of long prompts: the same in three launches of several blocks per layer, 8192 tokens each.  One block per layer reads
+// Retention of long prompts: the same in four launches of several blocks per layer, 8192 tokens each.  One block per layer reads
 // its tokens' importances five times at what one compute unit gets, from 32769 tokens on from memory.
-//   digit:      counts by the top 11 bits of the key; the layer's last block finds the digit that holds the cut;
+//   digit:      counts by the top 11 bits of the key; the layer's last block finds the digit that holds the cut; once more with the next 11 bits
+//               where too many tokens share that digit;
 //   candidates: the tokens of that digit go to a list, those above it are counted per block; the layer's last block finds the cut among the
 //               listed ones (more than kRetList of them: among all tokens, as the single block would), the last position kept of those that equal
 //               it, and the kept tokens before every block;
 //   compact:    kept positions, ret_off at the first token of every bucket (the kept tokens before it), ret_len by the layer's last block.
-// Bound by latency: three launches, each with an arrival and the last block's block scans, about 7 us apiece.  Us per call, one block a layer /
-// this: 32 layers x 16500 tokens 21.4 / 20.2 (16384: 20.9, the line), 32768 27.6 / 21.1, 16 x 65536 67.6 / 22.5, 8 x 131072 128 / 24.
+// Bound by latency: an arrival and the last block's block scans in each launch, 5 to 8 us apiece (2 where the second digit is not needed).  Us per call, one
+// block a layer / this, importances spread over 2^+-6 and, in brackets, within 10 %: 32 layers x 16500 tokens 21.2 / 22.7 (26.7 / 28.0), 20000 22.5 /
+// 22.6 (29.3 / 28.1), the line, 32768 27.6 / 24.5 (38.9 / 29.6), 16 x 65536 68 / 26 (87 / 32), 8 x 131072 127 / 27 (166 / 31).
 // ------------------------------------------------------------------------------------------------
 constexpr int kRetTok = 8, kRetChunk = kRetTok * kBlockThreads;      // tokens of a thread, of a block
 struct RetainWork {
     unsigned int* hist;           // [L][2048], zero between calls
     unsigned long long* list;     // [L][kRetList] (key, position)
     unsigned int* count;          // [L][4] arrivals, length of the list; zero between calls
-    int32_t* cut;                 // [L][4] digit, tokens above it; then key of the cut, last position kept of those that equal it
+    int32_t* cut;                 // [L][4] leading bits, tokens above them, bits left, tokens that share them; then (2, 3) key of the cut, last position kept of
+                                  // those that equal it
     int32_t* chunk;               // [L][kRetMaxChunks] tokens above the digit, then kept tokens before the block
 };
 
@@ -1244,56 +1247,68 @@ __device__ __forceinline__ bool retain_last(unsigned int* arrive, int* sm_last) 
     __syncthreads();
     return *sm_last != 0;
 }
-// The digit (of nbins <= 2048, counts by `count`) that holds the need-th largest; res = digit, number above it.  Every thread calls it.
+// The digit (of nbins <= 2048, counts by `count`) that holds the need-th largest; res = digit, number above it, its count.  Every thread calls it.
 template <typename Count>
 __device__ __forceinline__ void retain_cross(int nbins, uint32_t need, Count count, uint32_t* slot, int32_t* res) {
     const int d1 = nbins - 1 - 2 * (int)threadIdx.x;
     const uint32_t c1 = d1 >= 0 ? count(d1) : 0u, c0 = d1 >= 1 ? count(d1 - 1) : 0u;
     uint32_t total;
     const uint32_t above1 = block_scan_u32(c1 + c0, slot, &total) - c1 - c0, above0 = above1 + c1;
-    if (c1 > 0 && above1 < need && above0 >= need) { res[0] = d1; res[1] = (int32_t)above1; }
-    if (c0 > 0 && above0 < need && above0 + c0 >= need) { res[0] = d1 - 1; res[1] = (int32_t)above0; }
+    if (c1 > 0 && above1 < need && above0 >= need) { res[0] = d1; res[1] = (int32_t)above1; res[2] = (int32_t)c1; }
+    if (c0 > 0 && above0 < need && above0 + c0 >= need) { res[0] = d1 - 1; res[1] = (int32_t)above0; res[2] = (int32_t)c0; }
     __syncthreads();
 }
 
+// SECOND: the 11 bits behind the first digit, where more tokens share it than the list takes (importances of like tokens: 32768 tokens in three or four
+// digits); else nothing.
+template <bool SECOND>
 __global__ __launch_bounds__(kBlockThreads) void retain_digit_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
     __shared__ uint32_t hist[2048], wave_tot[kBlockWaves];
-    __shared__ int32_t res[2];
+    __shared__ int32_t res[3];
     __shared__ int sm_last;
     const int l = blockIdx.y, tid = threadIdx.x;
+    int32_t* cut = wk.cut + 4 * l;
+    const int32_t digit = SECOND ? ld_agent(cut) : 0, above = SECOND ? ld_agent(cut + 1) : 0;
+    if (SECOND && ld_agent(cut + 3) <= kRetList) return;
     const RetainTokens t(alpha_all + (int64_t)l * Tp, Tp);
     for (int i = tid; i < 2048; i += kBlockThreads) hist[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kRetTok; ++j)
-        if (t.i0 + j * kWave < Tp) atomicAdd(&hist[t.key[j] >> 21], 1u);
+        if (t.i0 + j * kWave < Tp && (!SECOND || (int32_t)(t.key[j] >> 21) == digit)) atomicAdd(&hist[SECOND ? (t.key[j] >> 10) & 2047u : t.key[j] >> 21], 1u);
     __syncthreads();
     unsigned int* all = wk.hist + (int64_t)l * 2048;
     for (int i = tid; i < 2048; i += kBlockThreads)
         if (hist[i] != 0) __hip_atomic_fetch_add(all + i, hist[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!retain_last(wk.count + 4 * l, &sm_last)) return;
-    retain_cross(2048, (uint32_t)min(k, Tp), [&](int d) { return ld_agent(all + d); }, wave_tot, res);
-    if (tid < 2) wk.cut[4 * l + tid] = res[tid];
+    if (!retain_last(wk.count + 4 * l, &sm_last)) return;             // (every block of the layer has read `cut`)
+    retain_cross(2048, (uint32_t)(min(k, Tp) - above), [&](int d) { return ld_agent(all + d); }, wave_tot, res);
+    if (tid == 0) {
+        st_agent(cut, SECOND ? (digit << 11) | res[0] : res[0]);
+        st_agent(cut + 1, above + res[1]);
+        st_agent(cut + 2, SECOND ? 10 : 21);
+        st_agent(cut + 3, res[2]);
+    }
     for (int i = tid; i < 2048; i += kBlockThreads) st_agent(all + i, 0u);
 }
 
 __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
     __shared__ uint32_t hist[2048], wave_tot[2][kBlockWaves], before[kRetMaxChunks];
     __shared__ int32_t equal[kRetList];
-    __shared__ int32_t res[2], tie, n_equal;
+    __shared__ int32_t res[3], tie, n_equal;
     __shared__ uint32_t sm_base;
     __shared__ int sm_last;
     const int l = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nchunk = gridDim.x;
     const float* alpha = alpha_all + (int64_t)l * Tp;
-    const uint32_t digit = (uint32_t)wk.cut[4 * l], above = (uint32_t)wk.cut[4 * l + 1];
+    const uint32_t digit = (uint32_t)ld_agent(wk.cut + 4 * l), above = (uint32_t)ld_agent(wk.cut + 4 * l + 1);
+    const int open = ld_agent(wk.cut + 4 * l + 2);                     // bits of the key behind the digits
     const RetainTokens t(alpha, Tp);
     auto lower = [&](unsigned long long m) { return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
     uint32_t n_above = 0, n_cand = 0;
 #pragma unroll
     for (int j = 0; j < kRetTok; ++j) {
         const bool exists = t.i0 + j * kWave < Tp;
-        n_above += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> 21) > digit));
-        n_cand += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> 21) == digit));
+        n_above += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> open) > digit));
+        n_cand += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> open) == digit));
     }
     uint32_t all_above, all_cand;
     (void)block_scan_u32(lane == 0 ? n_above : 0u, wave_tot[0], &all_above);
@@ -1308,7 +1323,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
     unsigned long long* list = wk.list + (int64_t)l * kRetList;
 #pragma unroll
     for (int j = 0; j < kRetTok; ++j) {
-        const bool cand = t.i0 + j * kWave < Tp && (t.key[j] >> 21) == digit;
+        const bool cand = t.i0 + j * kWave < Tp && (t.key[j] >> open) == digit;
         const unsigned long long m = __ballot(cand);
         const uint32_t to = at + lower(m);
         if (cand && to < (uint32_t)kRetList)
@@ -1334,21 +1349,20 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
         } else {
             for (int32_t i = tid; i < Tp; i += kBlockThreads) {
                 const uint32_t key = score_key(alpha[i]);
-                if ((key >> 21) == digit) fn(key, i);
+                if ((key >> open) == digit) fn(key, i);
             }
         }
     };
     uint32_t prefix = digit;
-    int shift = 21;
-    for (int pass = 0; pass < 2; ++pass) {
-        const int bits = pass == 0 ? 11 : 10;
+    for (int shift = open; shift > 0;) {                               // 11 and 10 bits, or 10
+        const int bits = shift == 21 ? 11 : 10;
         for (int i = tid; i < 2048; i += kBlockThreads) hist[i] = 0;
         __syncthreads();
         for_candidates([&](uint32_t key, int32_t) {
             if ((key >> shift) == prefix) atomicAdd(&hist[(key >> (shift - bits)) & ((1u << bits) - 1u)], 1u);
         });
         __syncthreads();
-        retain_cross(1 << bits, need, [&](int d) { return hist[d]; }, wave_tot[pass], res);
+        retain_cross(1 << bits, need, [&](int d) { return hist[d]; }, wave_tot[shift == 21], res);
         prefix = (prefix << bits) | (uint32_t)res[0];
         need -= (uint32_t)res[1];
         shift -= bits;
@@ -1461,7 +1475,8 @@ hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, cons
     if (k > 0 && c->ret_hist && Tp > kRetainLongTok && (Tp + kRetChunk - 1) / kRetChunk <= kRetMaxChunks) {
         const RetainWork wk = {c->ret_hist, c->ret_list, c->ret_count, c->ret_cut, c->ret_chunk};
         const dim3 chunks((Tp + kRetChunk - 1) / kRetChunk, c->d.n_layers);
-        hipLaunchKernelGGL(retain_digit_kernel, chunks, block, 0, c->stream, alpha, Tp, k, wk);
+        hipLaunchKernelGGL(retain_digit_kernel<false>, chunks, block, 0, c->stream, alpha, Tp, k, wk);
+        hipLaunchKernelGGL(retain_digit_kernel<true>, chunks, block, 0, c->stream, alpha, Tp, k, wk);
         hipLaunchKernelGGL(retain_candidates_kernel, chunks, block, 0, c->stream, alpha, Tp, k, wk);
         hipLaunchKernelGGL(retain_compact_kernel, chunks, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len, wk);
         return hipGetLastError();

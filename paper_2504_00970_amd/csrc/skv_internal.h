@@ -126,7 +126,7 @@ constexpr unsigned int kSweepTags = (1u << 24) - 1;
 constexpr int kSweepMostHeads = 1 << 20;
 constexpr int kSweepWaitLimit = 8000;
 // retention of long prompts by several blocks per layer: tokens from which it is used, layers and blocks per layer it has scratch for, listed tokens
-constexpr int kRetainLongTok = 16384;
+constexpr int kRetainLongTok = 20000;
 constexpr int kRetMaxLayers = 256, kRetMaxChunks = 128, kRetList = 4096;
 int64_t importance_work_bytes(const Ctx* c, int32_t T, int32_t N);
 int64_t importance_counters(const skv_desc& d);

@@ -277,10 +277,10 @@ def test_retain_bit_exact(U, oracle32, Tp):
             assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
 
 
-@pytest.mark.parametrize("Tp", [16384, 16385, 24576, 24577, 131072, 200001])
+@pytest.mark.parametrize("Tp", [20000, 20001, 24576, 24577, 131072, 200001])
 def test_retain_long_prompts(U, oracle32, Tp):
-    """Several blocks per layer (from 16385 tokens on), 8192 tokens each.  Layers: spread values; the cut among 4096 and 4097 tokens that share the first
-    11 bits (the list's length and one more), distinct and in groups of equal ones; all tokens equal; all within one digit; mostly NaN.
+    """Several blocks per layer (from 20001 tokens on), 8192 tokens each.  Layers: spread values; the cut among 4096 and 4097 tokens that share the first
+    11 bits (the list's length, and one more: the second digit), distinct and in groups of equal ones; all tokens equal; all within one digit; mostly NaN.
     Called twice: the scratch is as the first call found it."""
     _say("retain, long prompt", Tp)
     rng = np.random.default_rng(Tp)
