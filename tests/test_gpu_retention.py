@@ -187,6 +187,68 @@ def test_token_importance_sweep_with_infinities_and_nan(U):
     assert torch.all((got - want).abs()[ok] <= 2e-6 * want[ok] + 1e-30)
 
 
+def test_token_importance_sweeps_on_two_streams(U):
+    """Two contexts whose sweeps meet on the GPU: each finds part of the compute units taken, its blocks wait or leave the work to the two passes;
+    the results are those of a sweep alone to the bound of the test above."""
+    L, Hq, H, N, T = 16, 8, 8, 32, 32768
+    _say("importance in one sweep, two streams")
+    work = []
+    for seed in (1, 2):
+        wl, q, K = _importance_inputs(U, L, Hq, H, N, T, seed=seed)
+        ctx = U.make_ctx(wl, T, 64, 16)
+        want = _gpu_importance(U, ctx, q, K, T, N)
+        stream = torch.cuda.Stream()
+        ctx.set_stream(stream.cuda_stream)
+        scratch = torch.empty(ctx.token_importance_work_bytes(T, N), dtype=torch.uint8, device=U.DEV)
+        work.append((ctx, q, K, torch.zeros_like(want), scratch, want, stream))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for ctx, q, K, alpha, scratch, _, _ in work:
+            ctx.token_importance(q, K, T, N, alpha, scratch)
+    torch.cuda.synchronize()
+    for _, _, _, alpha, _, want, _ in work:
+        assert ((alpha - want).abs() / want).max().item() <= 2e-6
+
+
+def test_importance_and_long_retention_in_a_graph(U):
+    """The sweep and the retention of a long prompt recorded into a HIP graph: launch numbers, tags and counters live on the device, so that replays with
+    calls of the same context in between give what direct calls give."""
+    L, Hq, H, N, T, k = 4, 16, 8, 32, 30000, 3000
+    _say("importance and retention in a graph")
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    seg = torch.arange(T, device=U.DEV, dtype=torch.int32) // 20
+    S = int(seg[-1]) + 1
+    ctx = U.make_ctx(wl, T, S, 16)
+    work = torch.empty(ctx.token_importance_work_bytes(T, N), dtype=torch.uint8, device=U.DEV)
+
+    def outputs():
+        return (torch.zeros(L, T - N, device=U.DEV), torch.zeros(L, k, dtype=torch.int32, device=U.DEV), torch.zeros(L, dtype=torch.int32, device=U.DEV),
+                torch.zeros(L, S + 1, dtype=torch.int32, device=U.DEV), torch.zeros(L, S, dtype=torch.int32, device=U.DEV))
+
+    def call(alpha, keep, n_keep, off, ln):
+        ctx.token_importance(q, K, T, N, alpha, work)
+        ctx.retain(alpha, T - N, k, seg, S, keep, n_keep, off, ln)
+
+    want, got = outputs(), outputs()
+    call(*want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+        call(*got)
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    for _ in range(4):
+        for t in got:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        eager = outputs()
+        call(*eager)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(eager, want))
+
+
 def test_token_importance_sweep_tags_start_again(U):
     """2^24 tags, one per (layer, head) and launch: with 2^19 pairs they are used up at the 32nd launch."""
     L, Hq, H, N, T = 8192, 64, 64, 2, 20
