@@ -663,7 +663,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     extern __shared__ __attribute__((aligned(16))) char sm_ring[];
     __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
     __shared__ float sm_col[RT][P::kChunkKeys];
-    __shared__ int sm_ok[P::kPollers];
+    __shared__ int sm_ok[P::kPollers], sm_last;
     float* const sm_f = sm_l[0];                                         // a row's factor in the place of its sum, by the thread that published it
 
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -874,11 +874,12 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         chunk = chunk_next;
     }
     wait_loads<0>();                                                     // nothing lands in LDS after the block's end
-    // The last block to end moves the numbers on.  Before a tag comes again the words are cleared.
+    // The last block to end moves the numbers on.  Before a tag comes again the words are cleared.  (Not in the place of sm_ok: behind the
+    // `break` there is no barrier, and a wave may still be reading that.)
     if (threadIdx.x == 0)
-        sm_ok[0] = __hip_atomic_fetch_add(x.state + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(nblk - 1);
+        sm_last = __hip_atomic_fetch_add(x.state + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned int)(nblk - 1);
     __syncthreads();
-    if (!sm_ok[0]) return;
+    if (!sm_last) return;
     const unsigned int heads = (unsigned int)(x.total / x.nch), next = epoch + heads;
     const bool again = next + heads > kSweepTags;
     if (threadIdx.x == 0) {

@@ -170,6 +170,23 @@ def test_token_importance_in_one_sweep(U, Hq, N, T, limit):
         assert rel <= 2e-6, rel
 
 
+@pytest.mark.parametrize("Hq,N,T", [(8, 32, 9000), (16, 32, 4300), (32, 32, 16384)])
+@pytest.mark.parametrize("limit", [1, 3])
+def test_token_importance_sweep_gives_up_on_the_way(U, Hq, N, T, limit):
+    """So few polls that some blocks give up at one chunk, some at another, and some not at all: the launch ends, its numbers move on, and the result is
+    that of the sweep or of the two passes behind it, call after call; without the limit the sweep runs again."""
+    L, H = 36, 8
+    _say("importance in one sweep, gives up on the way", Hq, N, T, limit)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want = _gpu_importance(U, two, q, K, T, N)
+    ctx = U.make_ctx(wl, T, 64, 16)
+    for polls in (limit, limit, limit, 200000):
+        ctx.set_wait_limit(polls)
+        assert ((_gpu_importance(U, ctx, q, K, T, N) - want).abs() / want.abs().clamp_min(1e-30)).max().item() <= 2e-6
+
+
 def test_token_importance_sweep_with_infinities_and_nan(U):
     """A NaN or infinite logit, and keys that every row weighs zero: the places of NaN and the values are those of the two passes."""
     L, Hq, H, N, T = 4, 16, 8, 32, 5000
