@@ -384,6 +384,36 @@ def test_retain_long_prompts(U, oracle32, Tp):
             assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
 
 
+@pytest.mark.parametrize("Tp", [20001, 70000, 1 << 20])
+def test_retain_long_prompts_many_equal_at_the_cut(U, oracle32, Tp):
+    """Equal importances at the cut, the first and the last token among them: 2 to 4096 of them in the list (up to 128 are compared with each other, more are
+    ranked by the digits of their positions), and 3000 of 5000 tokens that share 22 bits, which the list does not take."""
+    _say("retain, equal importances at the cut", Tp)
+    rng = np.random.default_rng(Tp)
+    rows = []
+    for n in (4096, 3000, 1025, 129, 128, 2):
+        x = np.full(Tp, 0.25)
+        x[rng.permutation(np.arange(1, Tp - 1))[:n - 2]] = 1.0
+        x[[0, Tp - 1]] = 1.0
+        rows.append(x)
+    x = np.full(Tp, 0.25)
+    p = rng.permutation(Tp)
+    x[p[:3000]] = 1.0
+    x[p[3000:5000]] = 1.0 + rng.integers(1, 1024, 2000) * 2.0 ** -23
+    rows.append(x)
+    alpha = np.stack(rows).astype(np.float32)
+    seg = (np.arange(Tp) // 17).astype(np.int32)
+    L, S = len(rows), int(seg[-1]) + 1
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=L), Tp, S, 16)
+    a_dev = torch.from_numpy(alpha).to(U.DEV)
+    for k in (1, 2, 127, 128, 1024, 1025, 2999, 4095, 4999):
+        keep, n_keep, off, ln = _gpu_retain(U, ctx, a_dev, k, seg, S)
+        for l in range(L):
+            want_keep, want_off, want_len = oracle32.retain(alpha[l], k, seg, S)
+            assert n_keep[l] == len(want_keep) and np.array_equal(keep[l, :n_keep[l]], want_keep), (k, l)
+            assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
+
+
 @pytest.mark.parametrize("S", [50, 3000, 7000])
 def test_select_ignores_buckets_without_tokens(U, oracle32, S):
     """Zero-length buckets (a retained pool has them) are never listed, in both the register and the re-read path of
