@@ -1385,7 +1385,17 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             Vh = a.Vb + ((int64_t)h * a.v.T_total + sq.tok_base) * kRowBytes;
         }
         const float scale = kLog2e * rsqrtf((float)kHeadDim);
-        if (w < kTiles) {
+        // Shares of 80 to 112 and 144 to 240 tokens leave waves without a token (wave-uniform): these do nothing but say so.  Us per layer, with their loads and
+        // matrix instructions on zeros / without: 3 sequences, budget 800 (80 tokens) 12.24 / 12.08, 1440 (144) 14.87 / 14.44, 5 sequences, 860 15.3 / 14.8; where
+        // every wave has tokens the question costs 0.3 % (5 sequences, 1500: 17.35 / 17.41).
+        const bool none = MODE == kStepRagged && kPasses == 1 && CHUNK > kAttChunk && 16 * __builtin_amdgcn_readfirstlane(w) >= __builtin_amdgcn_readfirstlane(cnt);
+        if (w < kTiles && none) {
+            f32x4_t o[kDims / 16];
+#pragma unroll
+            for (int dt = 0; dt < kDims / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (qd == 0) sm_waves.leave(t16, w, -INFINITY, 0.f, 0.f);
+            leave_sums<G>(sm + w * kTileBytes, o);
+        } else if (w < kTiles) {
             char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
             if constexpr (EB == 4) request_queries();
             uint4 kA[kPasses][X::kPieces], vR[kPasses][X::kLoads];
@@ -2160,17 +2170,22 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     const int max_blocks = c->n_cu < kStepMaxBlocks ? c->n_cu : kStepMaxBlocks;
     if (pairs < 1 || pairs > kStepMaxPairs || pairs > max_blocks || c->step_score_stride <= 0) return hipSuccess;
     if (v.S_total > c->step_score_stride || (int64_t)pairs * c->step_score_stride > c->step_score_words) return hipSuccess;
-    const int parts = max_blocks / pairs;
+    int parts = max_blocks / pairs, pow2 = 1;
+    while (2 * pow2 <= parts) pow2 *= 2;
+    if (c->budget_cap <= pow2 * kAttChunk) parts = pow2;
     const int sv_bytes = c->d.semvec_dtype == SKV_BF16 ? kTableBf16 : c->d.semvec_dtype == SKV_FP8_E4M3 ? kTableE4m3 : kTableF32;
     // Attention blocks of 64 or 128 tokens where a pair has a power of two of them and they cover the budget (MODE kStep; constants where the other
-    // form has arguments, 0.5 % of a step).  A block's K/V rows pass its compute unit at 34 bytes a nanosecond, so that small blocks are
-    // faster until there are too many partials to merge: one sequence, us per layer in 128- / 64-token blocks: bf16 budget 512: 10.9 / 10.0, 1000: 11.5 / 10.8,
-    // 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0; budget 2500 in 20 blocks of 128 / 32 of 80: 13.0 / 14.1.
+    // form has arguments, 0.5 % of a step; shares of exactly 256 tokens too, 8 sequences, budget 1024: 19.55 / 19.45).  A block's K/V rows pass its compute unit at 34
+    // bytes a nanosecond, so that small blocks are faster until there are too many partials to merge: one sequence, us per layer in 128- / 64-token blocks: bf16 budget 512:
+    // 10.9 / 10.0, 1000: 11.5 / 10.8, 2048: 13.1 / 12.8; fp32 13.6 / 11.9, 14.5 / 12.7, 15.9 / 15.0; budget 2500 in 20 blocks of 128 / 32 of 80: 13.0 / 14.1.
     // Otherwise (kStepRagged) every block of the pair takes an equal share.  Us per layer, powers of two of blocks of 128, 256 or 512 tokens / this: 3 sequences,
     // budget 2048, eight blocks / ten: 19.2 / 18.2; 6 sequences, budget 1500, three blocks of four / five: 22.2 / 18.1; 8 sequences, budget 1100, two
     // launches / four blocks: 22.2 / 18.8; 4 sequences, budget 1100, five of eight / eight: 19.3 / 18.6; budget 2500, two launches / eight: 23.2 / 19.9.
-    const bool even = (parts & (parts - 1)) == 0 && c->budget_cap <= parts * kAttChunkMid;
-    const int chunk = !even ? max((c->budget_cap + 16 * parts - 1) / (16 * parts) * 16, kAttChunk) : c->budget_cap <= parts * kAttChunk ? kAttChunk : kAttChunkMid;
+    // Budgets that a power of two of 64-token blocks covers leave the pair's other blocks out; equal shares of 64 / this: 5 sequences of 8192 tokens, budget 128 11.68 / 11.40,
+    // fp32, 256 14.4 / 14.0, 64 query heads, 256 13.3 / 12.8; 6 sequences, 256 12.1 / 11.85 (of 32768 tokens 17.4 / 17.9); 3 sequences 10.58 / 10.61.
+    const int share = max((c->budget_cap + 16 * parts - 1) / (16 * parts) * 16, kAttChunk);
+    const bool even = parts == pow2 && (c->budget_cap <= parts * kAttChunkMid || share == kAttChunkWide);
+    const int chunk = !even || share == kAttChunkWide ? share : c->budget_cap <= parts * kAttChunk ? kAttChunk : kAttChunkMid;
     const int most = c->d.kv_dtype == SKV_BF16 ? 2 * kAttChunkWide : kAttChunkWide;
     if (chunk > most || parts < 2 || v.S_total >= (1 << 24)) return hipSuccess;
     // More than 256 tokens, bf16 only: two tiles a wave.  Every attending block waits for all the scores of its pair, and the two-launch form spreads
@@ -2207,7 +2222,9 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     };
     using std::integral_constant;
     if (even && chunk == kAttChunk) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunk>{});
-    if (even) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunkMid>{});
+    if (even && chunk == kAttChunkMid) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunkMid>{});
+    if (even) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunkWide>{});
+    if (chunk == kAttChunk) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunk>{});
     if (chunk <= kAttChunkMid) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkMid>{});
     if (chunk <= kAttChunkWide) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkWide>{});
     return launch_step_g<2, kStepRagged, 2 * kAttChunkWide>(c, a, blocks, launched);

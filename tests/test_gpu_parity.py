@@ -551,11 +551,14 @@ def test_fused_single_launch_two_tiles_per_wave(U, oracle32, B, budget, Hq):
     (3, [640, 1, 640], 32, "bf16"), (3, [641, 641, 0], 8, "bf16"), (3, [641, 640, 1], 64, "f32"),     # ten blocks of 64 and of 80 tokens; one token in the last
     (3, [1281, 900, 1281], 32, "bf16"), (3, [2000, 2000, 2000], 32, "f32"),                           # of 144 and 208
     (5, [1537, 1537, 100, 0, 1537], 64, "bf16"), (6, [1500] * 6, 32, "bf16"), (6, [1281, 1, 1280, 900, 1281, 320], 16, "f32"),   # six of 272; five of 304, 272
+    (3, [512, 449, 1], 32, "bf16"), (5, [256, 257, 0, 64, 250], 64, "f32"), (6, [321, 320, 1, 65, 0, 319], 32, "bf16"),               # 8 and 4 blocks of 64; of 80
+    (6, [320, 257, 1, 64, 65, 320], 8, "f32"), (5, [384, 1, 321, 384, 0], 64, "bf16"), (4, [2048, 2048, 1793, 1], 32, "bf16"),       # 5, 6 of 64; 8 of 256
     (7, [1000] * 7, 8, "f32"), (8, [1100, 1025, 1, 600, 1100, 0, 1100, 275], 32, "bf16"),             # four of 256; of 288
     (4, [2500, 2500, 2100, 2500], 64, "bf16"), (3, [5000, 4801, 5000], 32, "bf16")])                  # eight of 320; ten of 512
 def test_fused_single_launch_equal_shares(U, oracle32, B, budgets, Hq, dtype):
     """Blocks of an equal share of the largest budget, any number of them to a pair: shares that end in a block with one token, blocks
-    without any (smaller budgets, contexts shorter than the budget), one and two tiles a wave, mergers of parts of a head to two heads."""
+    without any (smaller budgets, contexts shorter than the budget), waves without a token, one and two tiles a wave, mergers of parts of a head to two
+    heads; and the budgets beside them that a power of two of blocks covers."""
     wl = gen.CFG4.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(700, 5600), budgets=(max(budgets),), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=37, layers=[0], budgets=budgets, seq_tokens=np.random.default_rng(B).integers(700, 5600, B).tolist())
 
