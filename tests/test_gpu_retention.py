@@ -79,13 +79,14 @@ def test_token_importance_with_logits_far_apart(U, oracle32, dtype, Hq, N, T):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("Hq,N", [(8, 1), (8, 32), (16, 32), (32, 32), (64, 32)])          # 1 row, then 32 to 256 rows per KV head
-def test_token_importance_precision_at_large_logits(U, dtype, Hq, N):
+@pytest.mark.parametrize("Hq,N,T", [(8, 1, 2900), (8, 32, 2900), (16, 32, 2900), (32, 32, 2900), (64, 32, 2900),          # 1 row, then 32 to 256 rows per KV head
+                                    (32, 32, 4500)])                                       # 128 rows in one sweep
+def test_token_importance_precision_at_large_logits(U, dtype, Hq, N, T):
     """Logits that both sides form without rounding (two products of small whole numbers), 166 to 423 above zero in log2 units, within
     6 of each other: what is left is the softmax's own arithmetic, held against float64.  Bound, relative: the argument of exp2,
     at most 2^3, is rounded once (2^-22 * ln 2 = 1.7e-7), exp2 and 1 / sum to a unit each (1.8e-7), log2(e) / sqrt(D) is a
     float (2^-24 * 6 * ln 2 = 2.5e-7 over the spread), sums add a few 2^-24 (2e-7): below 1e-6."""
-    T, H, D = 2900, 8, 128
+    H, D = 8, 128
     bases = [100, 100.5, 101, 111.5, 213, 255]                                              # a layer each
     L = len(bases)
     rng = np.random.default_rng(5)
@@ -100,7 +101,7 @@ def test_token_importance_precision_at_large_logits(U, dtype, Hq, N):
     tt = torch.bfloat16 if dtype == "bf16" else torch.float32
     assert torch.equal(q.to(tt).float(), q) and torch.equal(K.to(tt).float(), K)
     wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype=dtype)
-    _say("importance precision", dtype, Hq, N)
+    _say("importance precision", dtype, Hq, N, T)
     got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q.to(tt).to(U.DEV), K.to(tt).to(U.DEV), T, N).cpu().numpy().astype(np.float64)
     worst = 0.0
     for l in range(L):
@@ -148,7 +149,7 @@ def test_token_importance_in_one_sweep(U, Hq, N, T, limit):
     """The one-sweep form at the edges of its chunks (1024, 512 or 256 keys), from one chunk to several rounds of them, against the two passes.
     Both form the same logits bit for bit; arguments of exp2 (up to 2^4 here) are rounded once to 2^-21 on each side, sums of T terms differ in
     order: 2^-20 * ln 2 + a few 2^-24 of a value, below 2e-6.  With a wait limit of zero every block leaves the work to the passes behind
-    the sweep, which give their very bits."""
+    the sweep, which give their very bits; without one the sweep's own result arrives, which among so many values has other bits somewhere."""
     L, H = 36, 8                                                                            # 288 (layer, head) pairs
     _say("importance in one sweep", Hq, N, T, limit)
     wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
@@ -162,6 +163,8 @@ def test_token_importance_in_one_sweep(U, Hq, N, T, limit):
         got = _gpu_importance(U, ctx, q, K, T, N)
         if limit == 0 and T > 1024:                                                         # (a head in one chunk waits for nobody)
             assert torch.equal(got, want)
+        if limit is None and T > 500:
+            assert not torch.equal(got, want)
         rel = ((got - want).abs() / want.abs().clamp_min(1e-30)).max().item()
         assert rel <= 2e-6, rel
     if limit == 0:
@@ -187,21 +190,40 @@ def test_token_importance_sweep_gives_up_on_the_way(U, Hq, N, T, limit):
         assert ((_gpu_importance(U, ctx, q, K, T, N) - want).abs() / want.abs().clamp_min(1e-30)).max().item() <= 2e-6
 
 
-def test_token_importance_sweep_with_infinities_and_nan(U):
-    """A NaN or infinite logit, and keys that every row weighs zero: the places of NaN and the values are those of the two passes."""
-    L, Hq, H, N, T = 4, 16, 8, 32, 5000
-    _say("importance in one sweep, special values")
+@pytest.mark.parametrize("Hq", [8, 16, 32])                                                # chunks of 1024, 512 and 256 keys
+def test_token_importance_sweep_with_infinities_and_nan(U, Hq):
+    """A NaN or infinite logit, and keys that every row weighs zero: the places of NaN and the values are those of the two passes, to the bound above; that not all
+    bits are shows whose result it is, layer by layer."""
+    L, H, N, T = 4, 8, 32, 5000
+    _say("importance in one sweep, special values", Hq)
     wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
     K[0, 1, 700] = float("nan")
     K[1, 2, 800, 3] = float("inf")
-    K[2, :, 900:1900] = -200.0 * q[2, ::2, 0].float().sign().to(torch.bfloat16)[:, None]
-    q[3, 5] *= 1e30                                                                         # logits beyond the exchange's exponents
+    K[2, :, 900:1900] = -200.0 * q[2, ::Hq // H, 0].float().sign().to(torch.bfloat16)[:, None]
+    q[2] = q[2, ::Hq // H, :1].repeat_interleave(Hq // H, 0)                                # (every row of a head is the first)
     two = U.make_ctx(wl, T, 64, 16)
     two.set_single_launch(False)
     want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
     assert torch.equal(want.isnan(), got.isnan())
-    ok = ~want.isnan()
-    assert torch.all((got - want).abs()[ok] <= 2e-6 * want[ok] + 1e-30)
+    assert want[0].isnan().sum() == want[1].isnan().sum() == 1 and not want[2:].isnan().any()
+    assert torch.all(want[2, 900:1900] == 0)
+    for l in range(L):
+        ok = ~want[l].isnan()
+        assert torch.all((got - want)[l].abs()[ok] <= 2e-6 * want[l][ok] + 1e-30)
+        assert not torch.equal(got[l][ok], want[l][ok]), l
+
+
+@pytest.mark.parametrize("Hq", [8, 16, 32])
+def test_token_importance_sweep_beyond_its_exponents(U, Hq):
+    """Logits beyond what the words of the exchange hold, in one layer: the sweep gives up and the two passes do all layers, bit for bit."""
+    L, H, N, T = 4, 8, 32, 5000
+    _say("importance in one sweep, beyond its exponents", Hq)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    q[3, 5] *= 2.0 ** 15                                                                    # logits of some 10^5 in log2 units, words up to 65279
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert torch.equal(got, want) and not want.isnan().any()
 
 
 def test_token_importance_sweeps_on_two_streams(U):
@@ -354,6 +376,30 @@ def test_retain_bit_exact(U, oracle32, Tp):
             assert np.array_equal(keep[l, :n_keep[l]], want_keep), (k, l)
             assert np.all(keep[l, n_keep[l]:] == -9)                                       # nothing written past n_keep
             assert np.array_equal(off[l], want_off) and np.array_equal(ln[l], want_len), (k, l)
+
+
+@pytest.mark.parametrize("Tp", [32768, 32769, 36001])
+def test_retain_long_prompts_of_many_layers(U, oracle32, Tp):
+    """More layers than the form of several blocks has scratch for: one block per layer, which holds 32768 tokens in registers and reads longer
+    prompts again in every sweep."""
+    _say("retain, 257 layers", Tp)
+    L = 257
+    rng = np.random.default_rng(Tp)
+    lens = gen.sentence_lengths(("uniform", 1, 40), Tp + 8, seed=Tp)
+    seg = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    S = len(lens)
+    kinds = np.stack([rng.random(Tp), rng.choice(np.array([0.0, 0.125, 0.5, 2.0]), size=Tp), rng.random(Tp), np.full(Tp, 3.0)]).astype(np.float32)
+    kinds[2, rng.integers(0, Tp, Tp // 50)] = np.nan
+    kinds[2, rng.integers(0, Tp, Tp // 50)] = -0.0
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=L), Tp + 8, S, 16)
+    a_dev = torch.from_numpy(kinds[np.arange(L) % 4]).to(U.DEV)
+    for k in (1, 4096, Tp - Tp // 60, Tp):
+        keep, n_keep, off, ln = _gpu_retain(U, ctx, a_dev, k, seg, S)
+        for kind in range(4):
+            want_keep, want_off, want_len = oracle32.retain(kinds[kind], k, seg, S)
+            assert np.all(n_keep[kind::4] == len(want_keep)) and len(want_keep) == k
+            assert np.all(keep[kind::4] == want_keep), (k, kind)
+            assert np.all(off[kind::4] == want_off) and np.all(ln[kind::4] == want_len), (k, kind)
 
 
 @pytest.mark.parametrize("Tp", [20000, 20001, 24576, 24577, 131072, 200001])
