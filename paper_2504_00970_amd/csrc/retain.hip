@@ -510,7 +510,7 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 // because a row's normaliser is known only once all keys have been seen.  Here the exp2 values of a chunk of keys stay in the
 // registers of the block that made them (128 a lane: half of the chip's registers) until the blocks that hold the other chunks of the
 // (layer, head) have published their sums of every row.
-//   Blocks of four waves, two on a compute unit; block b takes the chunks b, b + blocks, ... of the launch, chunks numbered head by head.
+//   Blocks of four waves, two on a compute unit, as many as some whole heads have chunks: a block takes the same chunk of one head after another.
 //   Per chunk:  logits of all its keys (matrix cores; the keys of the next chunk are requested as the places in LDS come
 //   free) -> per row the chunk's largest logit, rounded to a whole reference -> exp2 in place, sums of the rows -> published ->
 //   the blocks of the head combine a share of its rows each and publish 1 / sum -> column sums of the values held.
@@ -547,7 +547,7 @@ struct SweepArgs {
     unsigned int* state;         // number of the heads so far, the last failed launch, the last launch, its blocks that are done
     int64_t part_words, stat_words;      // all there are
     int32_t T, N, G, nch, total, stat_heads, limit;
-    int32_t blocks_div, blocks_mod;      // blocks / nch and the remainder
+    int32_t heads_at_once;               // the grid is this many times nch blocks
 };
 
 // Reductions of 16 values over the 32 lanes of a half wave: lane a of the half ends with value number a >> 1.  Values and lanes are halved
@@ -693,10 +693,9 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     for (int left = ((int)x.total - (int)blockIdx.x + nblk - 1) / nblk - 1; left >= 0; --left) {         // chunks after this one
         const int32_t base0 = chunk * P::kChunkKeys;
         const uint32_t tag = epoch + 1 + (uint32_t)lh;
-        int lh_next = lh + x.blocks_div, chunk_next = chunk + x.blocks_mod;
-        if (chunk_next >= x.nch) { chunk_next -= x.nch; ++lh_next; }
-        const char *src = chunk_src(lh, chunk), *src_next = chunk_src(lh_next, chunk_next);
-        const int keys = x.T - base0, keys_next = x.T - chunk_next * P::kChunkKeys;
+        const int lh_next = lh + x.heads_at_once;
+        const char *src = chunk_src(lh, chunk), *src_next = chunk_src(lh_next, chunk);
+        const int keys = x.T - base0;
         f32x16 acc[P::KT];
         const int lane = this_lane(), tid = lane + w * kWave, r = lane & 31, g = lane >> 5;
 #pragma unroll
@@ -707,7 +706,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             else stages.template landed<0>();
             if (k > 0) {
                 if (k - 1 + P::NS < P::SC) stages.request(src, keys, k - 1 + P::NS);
-                else if (left > 0) stages.request(src_next, keys_next, k - 1 + P::NS - P::SC);
+                else if (left > 0) stages.request(src_next, keys, k - 1 + P::NS - P::SC);
             }
             const char* stage = sm_ring + k % P::NS * P::kStageBytes;
             // a fragment of the next tile is read behind the matrix instruction that used its registers
@@ -772,7 +771,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             if ((lane & 1) == 0) sm_l[ks][32 * rs + tile_pos(r >> 1, g)] = l;
         }
         __syncthreads();
-        if (left > 0) stages.request(src_next, keys_next, P::NS - 1);
+        if (left > 0) stages.request(src_next, keys, P::NS - 1);
         if (loader < 0) {
             __builtin_amdgcn_s_setprio(3);
             // published: the sum of every row
@@ -788,8 +787,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             wait.ok = __all(wait.ok);
             // combined: four rows a wave, 16 lanes to a row
             unsigned long long* stat = x.stat + (int64_t)(lh % x.stat_heads) * kRows;
-            int first = (int)blockIdx.x - chunk;                         // block of the head's first chunk
-            if (first < 0) first += nblk;
+            const int first = (int)blockIdx.x - chunk;                   // block of the head's first chunk
             for (int row0 = 4 * (chunk * P::kPollers + w); row0 < kRows; row0 += 4 * P::kPollers * x.nch) {
                 const int row = row0 + (lane & 3);
                 int X = kExpNone;
@@ -798,9 +796,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                     unsigned long long v[kU];
                     auto need = [&](int u, int l) { return c0 + 16 * u + (l >> 2) < x.nch; };
                     wait.get<kU>(x.part, [&](int u, int l) {
-                        int b = first + min(c0 + 16 * u + (l >> 2), x.nch - 1);
-                        if (b >= nblk) b -= nblk;
-                        return (uint32_t)(b * kRows + row0 + (l & 3));
+                        return (uint32_t)((first + min(c0 + 16 * u + (l >> 2), x.nch - 1)) * kRows + row0 + (l & 3));
                     }, need, tag, v);
                     int top = X;
 #pragma unroll
@@ -871,7 +867,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             }
         }
         lh = lh_next;
-        chunk = chunk_next;
+        asm volatile("" : "+s"(chunk));                                  // what depends on it is made in every round (made once: 4096 keys of 32 rows 59.4 -> 59.8 us)
     }
     wait_loads<0>();                                                     // nothing lands in LDS after the block's end
     // The last block to end moves the numbers on.  Before a tag comes again the words are cleared.  (Not in the place of sm_ok: behind the
@@ -983,9 +979,8 @@ static hipError_t launch_sweep(Ctx* c, const char* q_obs, const char* K_pool, in
     x.total = L * Hkv * x.nch;
     x.stat_heads = min(L * Hkv, kSweepStatHeads);
     x.limit = min(c->wait_limit, kSweepWaitLimit);
-    const int blocks = min(sweep_blocks(c) / x.nch * x.nch, x.total);      // whole heads: else every head's blocks wait for those of the next ones
-    x.blocks_div = blocks / x.nch;
-    x.blocks_mod = blocks % x.nch;
+    x.heads_at_once = min(sweep_blocks(c) / x.nch, L * Hkv);               // whole heads: else every head's blocks wait for those of the next ones
+    const int blocks = x.heads_at_once * x.nch;
     hipLaunchKernelGGL((importance_sweep_kernel<RT>), dim3(blocks), dim3(P::kThreads), P::kRingBytes, c->stream, x);
     hipLaunchKernelGGL((importance_finish_kernel<RT>), dim3((T + kpb - 1) / kpb, Hkv, L), dim3(Imp<2, RT>::kThreads), (Imp<2, RT>::kRingBytes), c->stream,
                        q_obs, K_pool, T, N, c->G, kpb, part, rowstat, c->imp_arrive, alpha_h, alpha, c->imp_state);
@@ -1510,7 +1505,7 @@ hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, cons
     }
     if (Tp <= 4 * kBlockThreads)
         hipLaunchKernelGGL(retain_kernel<4>, grid, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len);
-    else                                                               // prompts up to 32K in registers
+    else                                                               // up to 32768 tokens in registers; more only for contexts of many layers, and past 2^20
         hipLaunchKernelGGL(retain_kernel<32>, grid, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len);
     return hipGetLastError();
 }

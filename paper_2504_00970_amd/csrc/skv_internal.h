@@ -83,7 +83,7 @@ struct Ctx {
     unsigned long long* imp_part;    // its tagged words: [kSweepMaxBlocks][kSweepMaxRows] (null: no sweep)
     unsigned long long* imp_stat;    // [min(heads, kSweepStatHeads)][kSweepMaxRows]
     int64_t imp_part_words, imp_stat_words;
-    unsigned int* ret_hist;      // scratch of the retention of long prompts (RetainWork; null: more than kRetMaxLayers layers)
+    unsigned int* ret_hist;      // scratch of the retention of long prompts (RetainWork; null: more than kRetMaxLayers layers, or max_tokens up to kRetainLongTok)
     unsigned long long* ret_list;
     unsigned int* ret_count;
     int32_t *ret_cut, *ret_chunk;
