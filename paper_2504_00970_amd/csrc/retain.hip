@@ -51,6 +51,7 @@ template <int EB, int RT> struct Imp {                          // RT: 32-row ti
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -508,34 +509,40 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 // ------------------------------------------------------------------------------------------------
 // Importance in one sweep over the keys, bf16, up to 128 rows.  The two passes read every key, multiply it and take its exp2 twice,
 // because a row's normaliser is known only once all keys have been seen.  Here the exp2 values of a chunk of keys stay in the
-// registers of the block that made them (128 a lane: half of the chip's registers) until the blocks that hold the other chunks of the
+// registers of the block that made them (64 a lane: half of the chip's registers) until the blocks that hold the other chunks of the
 // (layer, head) have published their sums of every row.
-//   Blocks of four waves, two on a compute unit, as many as some whole heads have chunks: a block takes the same chunk of one head after another.
-//   Per chunk:  logits of all its keys (matrix cores; the keys of the next chunk are requested as the places in LDS come
-//   free) -> per row the chunk's largest logit, rounded to a whole reference -> exp2 in place, sums of the rows -> published ->
+//   Blocks of eight waves, two on a compute unit, as many as some whole heads have chunks: a block takes the same chunk of one head after another.
+//   Per chunk:  logits of its keys, tile by tile on the matrix cores (the keys of the next chunk are requested as the places in LDS come free), exp2 of
+//   a tile and the sums of its rows beside the next tile's logits, relative to a whole reference from the wave's first tile -> published ->
 //   the blocks of the head combine a share of its rows each and publish 1 / sum -> column sums of the values held.
+// A chunk whose logits rise too far above those of its first tile (kFar) takes them from memory once more, with its own maxima.
 // The exchange passes tagged words: nothing is cleared, drained or counted.  A block publishes its next chunk only after it has seen
 // every row of the present one combined, so one place per block is enough.  While one block of a compute unit waits for the
-// others, its neighbour computes.  Half of a block's waves request keys, the other half talk to the other blocks: a wave's loads return in
+// others, its neighbour computes.  Some of a block's waves request keys, others talk to the other blocks: a wave's loads return in
 // order, and a polled word would come only after the keys requested before it.
 // Waiting needs the blocks of a head to be resident together.  A block that has polled `limit` times, or sees that another gave up, marks the
 // launch as failed and ends; the kernel behind the sweep, which otherwise adds up the heads, then does all of the work in two passes.
-// Bound by HBM for 32 rows (32 layers x 8 heads x 32768 keys: 726 us in two passes, 417 here), where a chunk is 1024 keys; a chunk
-// holds 256 keys of 128 rows, and the exchange (two trips through memory, 5.5 us, 6-7 beside the keys) takes as long as a chunk's
-// logits and exp2: 64 rows 713 -> 520 us, 128 rows 821 -> 819 (of 16384 keys 448 -> 413).  Three blocks of 192 keys on a compute unit were slower (912 us: the
-// exchange grows to 9 us), and so were two row tiles a wave (940).
+// Bound by HBM for 32 rows (a chunk is 1024 keys, 5.7 TB/s), by the exchange for 128 (256 keys): a block by itself takes 7.5 us for such a chunk, 2.5 until its
+// exp2 values are there, 0.8 until its sums are published, 3.3 for two trips through memory, 0.9 for the column sums; two on a compute unit take 10.6 us each.
+// us, 32 layers x 8 heads, two passes / waves of 32 rows that took the maximum of the whole chunk first, all exp2 after all logits, four waves a block / now:
+// 32768 keys 812 / 815 / 680, 64 rows 713 / 515 / 442, 32 rows 727 / 417 / 382; 4096 keys 131 / 110 / 85, 64 rows 105 / 73 / 62, 32 rows 100 / 61 / 51.
+// What the way there gave, 32768 keys of 128 rows: the chunk that holds the last keys masks its last tile only, the limits from LDS (every block of the head
+// waited 1.5 us for it), and exp2 beside the matrix instructions 815 -> 720; waves of 16 rows, eight a block 730 -> 690; stages of 64 keys for every width
+// (64 rows 490 -> 450).  Not kept: polls one instruction at a time (each waits for its own trip: 840), a row a wave to combine (many writers to a line of the
+// combined words: 830), the next chunk's keys requested together behind the sums or the exchange (770, 790), priorities for all waves behind the
+// logits (the same), heads confined to two of the chip's dies (the same).
 // ------------------------------------------------------------------------------------------------
 template <int RT> struct Sweep {                               // RT: 32-row tiles of the window's rows
-    static constexpr int NW = 4, KSP = NW / RT;                // waves of a block: a row tile each, KSP beside each other along the keys
-    static constexpr int KT = 8;                               // 32-key tiles of a wave in a chunk, 16 registers each
-    static constexpr int TPS = RT == 4 ? 2 : RT;               // of these, in a stage
-    static constexpr int SC = KT / TPS, NS = RT == 4 ? 4 : 2;  // stages of a chunk, stages that LDS holds
+    static constexpr int NW = 8, RS = 2 * RT, KSP = NW / RS;   // waves of a block: 16 rows each, KSP beside each other along the keys
+    static constexpr int KT = 16;                              // 16-key tiles of a wave in a chunk, 4 registers each
+    static constexpr int TPS = RT;                             // of these, in a stage of 64 keys
+    static constexpr int SC = KT / TPS, NS = 4;                // stages of a chunk, stages that LDS holds
     static constexpr int kThreads = NW * kWave, kRows = 32 * RT;
-    static constexpr int kStageKeys = 32 * KSP * TPS, kStageBytes = kStageKeys * kHeadDim * 2, kChunkKeys = kStageKeys * SC;
+    static constexpr int kStageKeys = 16 * KSP * TPS, kStageBytes = kStageKeys * kHeadDim * 2, kChunkKeys = kStageKeys * SC;
     static constexpr int kRingBytes = NS * kStageBytes;
-    static constexpr int kLoaders = NW / 2, kPollers = NW - kLoaders;
+    static constexpr int kPollers = 2, kStorers = 4, kLoaders = 4;     // waves 0, 1; 0 to 3; 4 to 7
     static constexpr int kLoads = kStageBytes / (kLoaders * 1024);     // load instructions of a loader per stage
-    static_assert(RT * KSP == NW && SC % NS == 0 && NS * kLoads < 64, "a stage has one place in LDS, the load counter holds them all");
+    static_assert(RS * KSP == NW && kStorers + kLoaders == NW && SC % NS == 0 && NS * kLoads < 64, "a stage has one place in LDS, the load counter holds them all");
 };
 
 struct SweepArgs {
@@ -550,8 +557,6 @@ struct SweepArgs {
     int32_t heads_at_once;               // the grid is this many times nch blocks
 };
 
-// Reductions of 16 values over the 32 lanes of a half wave: lane a of the half ends with value number a >> 1.  Values and lanes are halved
-// together, step by step (38 instructions; 16 separate reductions take 96).
 struct MaxOp { __device__ static __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
 struct AddOp { __device__ static __forceinline__ float of(float a, float b) { return a + b; } };
 template <int CTRL> __device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false); }
@@ -562,21 +567,18 @@ template <int N> __device__ __forceinline__ int other_half(int x) {
                            : __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
     return (int)(s[0] ^ s[1] ^ (uint32_t)x);
 }
-template <class Op> __device__ __forceinline__ float reduce_16x32(const float (&v)[16]) {
-    const int a = threadIdx.x & 31;
-    float x[8], y[4], z[2];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 8]), false, false);
-        x[j] = Op::of(__uint_as_float(s[0]), __uint_as_float(s[1]));                 // value j + 8 (a >> 4)
-    }
-    const bool b3 = a & 8, b2 = a & 4, b1 = a & 2;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) y[j] = Op::of(b3 ? x[j + 4] : x[j], dpp_move<0x140>(b3 ? x[j] : x[j + 4]));    // row_mirror
-#pragma unroll
-    for (int j = 0; j < 2; ++j) z[j] = Op::of(b2 ? y[j + 2] : y[j], dpp_move<0x141>(b2 ? y[j] : y[j + 2]));    // row_half_mirror
-    const float u = Op::of(b1 ? z[1] : z[0], dpp_move<0x4E>(b1 ? z[0] : z[1]));
-    return Op::of(u, dpp_move<0xB1>(u));
+// over the 16 lanes of a row of lanes, in all of them
+template <class Op> __device__ __forceinline__ float reduce_16(float x) {
+    x = Op::of(x, dpp_move<0x128>(x));                                   // row_ror 8, 4, 2, 1
+    x = Op::of(x, dpp_move<0x124>(x));
+    x = Op::of(x, dpp_move<0x122>(x));
+    return Op::of(x, dpp_move<0x121>(x));
+}
+// a + (a of lane l ^ N) in the lanes without bit N, b + (b of lane l ^ N) in the others; N = 16 or 32
+template <int N> __device__ __forceinline__ float add_swap(float a, float b) {
+    const auto s = N == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)
+                           : __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 // A number m * 2^x, 1 <= m < 2, and the tag of the (layer, head) it belongs to in one 64-bit word: 24 bits, 17 of the exponent, 23 of m.
 constexpr int kExpBias = 1 << 16, kExpNone = -kExpBias, kExpNan = kExpBias - 1;       // exponents that stand for zero and NaN
@@ -599,28 +601,29 @@ struct SweepStages {
     using P = Sweep<RT>;
     static constexpr int kRowBytes = kHeadDim * 2, kPieces = kRowBytes / 16, kRows = kWave / kPieces;      // rows per instruction
     int loader;               // which of the loading waves, negative: none
-    uint32_t lds;             // where this wave's part of the first stage goes
+    uint32_t lds;             // where the ring begins
     __device__ __forceinline__ SweepStages(char* ring, int loader_) : loader(loader_) {
-        lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + (uint32_t)(loader * P::kLoads * 1024);
+        lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
     }
-    // stage k (compile time) of the chunk whose first key is `src`, `keys` of the head's keys from there on; piece p of row r lands at piece p ^ (r % 16)
+    // Stage k (compile time) of the chunk whose first key is `src`, `keys` of the head's keys from there on; a loader takes its share of the rows, four to
+    // an instruction; piece p of row r lands at piece p ^ (r % 16).
     __device__ __forceinline__ void request(const char* src, int keys, int k) const {
+        static_assert(kRows * P::kLoads % 16 == 0, "a loader begins at a multiple of 16 rows");
         if (loader < 0) return;
         int lane = threadIdx.x & 63;
-        asm volatile("" : "+v"(lane));                                   // each load's offset made here, not kept in a register of its own
-        const uint32_t first = (uint32_t)((kRows * P::kLoads * loader + lane / kPieces) * kRowBytes + 16 * ((lane % kPieces) ^ (lane / kPieces)));
+        asm volatile("" : "+v"(lane));                                   // offsets made here, not kept in registers
+        const int row = lane / kPieces, at = loader * P::kLoads * 1024;
+        const uint32_t piece = (uint32_t)(16 * ((lane % kPieces) ^ row));
         if (keys >= (k + 1) * P::kStageKeys) {
+            const uint32_t first = (uint32_t)(row * kRowBytes) + piece;
 #pragma unroll
             for (int i = 0; i < P::kLoads; ++i)
-                load_lds_stream_at(src + k * P::kStageBytes, (first ^ (uint32_t)((kRows * i & 15) * 16)) + (uint32_t)(kRows * i * kRowBytes),
-                                   lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i));
+                load_lds_stream_at(src + (k * P::kStageBytes + 1024 * i) + at, first ^ (uint32_t)(16 * (kRows * i & 15)), lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i + at));
         } else {                                                         // keys past the last: that one again
 #pragma unroll
-            for (int i = 0; i < P::kLoads; ++i) {
-                const uint32_t piece = (first ^ (uint32_t)((kRows * i & 15) * 16)) & (uint32_t)(kRowBytes - 1);
-                load_lds_stream_at(src, (uint32_t)(min(k * P::kStageKeys + (int)(first / kRowBytes) + kRows * i, keys - 1) * kRowBytes) + piece,
-                                   lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i));
-            }
+            for (int i = 0; i < P::kLoads; ++i)
+                load_lds_stream_at(src, (uint32_t)(min(k * P::kStageKeys + kRows * (P::kLoads * loader + i) + row, keys - 1) * kRowBytes) + (piece ^ (uint32_t)(16 * (kRows * i & 15))),
+                                   lds + (uint32_t)(k % P::NS * P::kStageBytes + 1024 * i + at));
         }
     }
     // stage k has landed: at most this many stages were requested after it
@@ -656,15 +659,15 @@ struct Waiter {
 };
 
 template <int RT>
-__global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_per_eu(kSweepPerCu, kSweepPerCu))) void importance_sweep_kernel(SweepArgs x) {
+__global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_per_eu(kSweepPerCu * Sweep<RT>::NW / 4, kSweepPerCu * Sweep<RT>::NW / 4))) void importance_sweep_kernel(SweepArgs x) {
     using P = Sweep<RT>;
-    constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows, kU = 8;       // kU: words of a lane asked for together
-    constexpr float kLog2e = 1.4426950408889634f;
+    constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows;
+    constexpr float kLog2e = 1.4426950408889634f, kAbove = 4.f, kFar = 0x1p24f;
     extern __shared__ __attribute__((aligned(16))) char sm_ring[];
     __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
-    __shared__ float sm_col[RT][P::kChunkKeys];
-    __shared__ int sm_ok[P::kPollers], sm_last;
-    float* const sm_f = sm_l[0];                                         // a row's factor in the place of its sum, by the thread that published it
+    __shared__ float sm_col[P::RS][P::kChunkKeys];
+    __shared__ int sm_ok[P::kPollers], sm_far[2], sm_last;
+    __shared__ __attribute__((aligned(16))) int32_t sm_limit[kRows];     // last key that a row sees
 
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // what depends on the lane is made where it is used: kept for the whole loop it would take registers from the chunk's values
@@ -672,21 +675,25 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     auto this_lane = [&]() { int l = lane_of; asm volatile("" : "+v"(l)); return l; };
     const int rs = w / P::KSP, ks = w % P::KSP;
     const int R = x.G * x.N, Tp = x.T - x.N, nblk = gridDim.x;
-    const int loader = w - P::kPollers;                                  // negative: the wave talks to the other blocks
+    const int loader = w - P::kStorers;                                  // negative: none
     const float scale = kLog2e * rsqrtf((float)kHeadDim);
     const unsigned int epoch = ld_agent(x.state);
     int lh = blockIdx.x / x.nch, chunk = blockIdx.x - lh * x.nch;
     auto chunk_src = [&](int head, int ch) { return x.K_pool + ((int64_t)head * x.T + ch * P::kChunkKeys) * kRowBytes; };
+    if (threadIdx.x < 2) sm_far[threadIdx.x] = 0;
+    for (int row = threadIdx.x; row < kRows; row += P::kThreads) sm_limit[row] = min(Tp + row % x.N, x.T - 1);      // (the first stage's barrier follows)
     const SweepStages<RT> stages(sm_ring, loader);
 #pragma unroll
     for (int k = 0; k < P::NS; ++k) stages.request(chunk_src(lh, chunk), x.T - chunk * P::kChunkKeys, k);
-    Frag<2> qf[8];
+    // Lane (t16, qd) = (lane % 16, lane / 16).  Queries are the A operand of v_mfma_f32_16x16x32_bf16, keys the B operand, the 16 bytes 4 s + qd of a row for
+    // step s; element j of a tile is (row 4 qd + j, key t16).
+    uint4 qf[4];
     auto load_q = [&](int head) {
-        const int lane = this_lane(), r = lane & 31, g = lane >> 5;
+        const int lane = this_lane(), t16 = lane & 15, qd = lane >> 4;
         // rows past the last repeat it: they get a factor of zero
-        const char* q = x.q_obs + ((int64_t)head * R + min(32 * rs + r, R - 1)) * kRowBytes + 16 * g;
+        const char* q = x.q_obs + ((int64_t)head * R + min(16 * rs + t16, R - 1)) * kRowBytes + 16 * qd;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) qf[d].t0 = *reinterpret_cast<const uint4*>(q + 32 * d);
+        for (int st = 0; st < 4; ++st) qf[st] = *reinterpret_cast<const uint4*>(q + 64 * st);
     };
     load_q(lh);
 
@@ -696,8 +703,46 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         const int lh_next = lh + x.heads_at_once;
         const char *src = chunk_src(lh, chunk), *src_next = chunk_src(lh_next, chunk);
         const int keys = x.T - base0;
-        f32x16 acc[P::KT];
-        const int lane = this_lane(), tid = lane + w * kWave, r = lane & 31, g = lane >> 5;
+        f32x4 acc[P::KT];
+        float ref[4], sum[4];
+        const int lane = this_lane(), tid = lane + w * kWave, t16 = lane & 15, qd = lane >> 4;
+        const int row_of = 16 * rs + 4 * qd;                             // row of a tile's first element
+        // keys that a row does not see
+        auto mask_tile = [&](f32x4& v, int t) {
+            const int key = base0 + 16 * (P::KSP * t + ks) + t16;
+            const int4 limit = *reinterpret_cast<const int4*>(sm_limit + row_of);
+            if (key > limit.x) v[0] = -INFINITY;
+            if (key > limit.y) v[1] = -INFINITY;
+            if (key > limit.z) v[2] = -INFINITY;
+            if (key > limit.w) v[3] = -INFINITY;
+        };
+        // whole references, kAbove over the largest logit of the wave's first tile
+        auto set_references = [&]() {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float top = rintf(reduce_16<MaxOp>(acc[0][j]) * scale) + kAbove;
+                ref[j] = top > -INFINITY ? top : 0.f;                    // (nothing visible: any)
+                sum[j] = 0.f;
+            }
+        };
+        // the exp2 values of tile t and its part of the sums, here and not behind a later barrier
+        auto exps = [&](int t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(acc[t][j], scale, -ref[j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[t][j] = exp2_neg(acc[t][j]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum[j] += acc[t][j];
+            asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]));
+        };
+        auto leave_sums = [&]() {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum[j] = reduce_16<AddOp>(sum[j]);
+            if (t16 == 0) {
+                *reinterpret_cast<float4*>(&sm_m[ks][row_of]) = make_float4(ref[0], ref[1], ref[2], ref[3]);
+                *reinterpret_cast<float4*>(&sm_l[ks][row_of]) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+            }
+        };
 #pragma unroll
         for (int k = 0; k < P::SC; ++k) {
             // one stage was requested after each that has been read, but the last of a chunk already behind the barrier after it
@@ -710,123 +755,139 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             }
             const char* stage = sm_ring + k % P::NS * P::kStageBytes;
             // a fragment of the next tile is read behind the matrix instruction that used its registers
-            Frag<2> kf[8];
+            uint4 kf[4];
+            auto key_frag = [&](int u, int st) {
+                const int row = 16 * (P::KSP * u + ks) + t16;
+                kf[st] = *reinterpret_cast<const uint4*>(stage + row * kRowBytes + 16 * ((4 * st + qd) ^ t16));
+            };
 #pragma unroll
-            for (int d = 0; d < 8; ++d) stage_frag<2>(kf[d], stage, 32 * ks + r, d, g);
+            for (int st = 0; st < 4; ++st) key_frag(0, st);
 #pragma unroll
             for (int u = 0; u < P::TPS; ++u) {
-                f32x16 c = {};
+                const int t = k * P::TPS + u;
+                f32x4 c = {};
 #pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    c = frag_mma<2>(qf[d], kf[d], c);
-                    if (u + 1 < P::TPS) stage_frag<2>(kf[d], stage, 32 * (P::KSP * (u + 1) + ks) + r, d, g);
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                for (int st = 0; st < 4; ++st) {
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[st]), __builtin_bit_cast(bf16x8, kf[st]), c, 0, 0, 0);
+                    if (u + 1 < P::TPS) key_frag(u + 1, st);
                 }
-                acc[k * P::TPS + u] = c;
+                if (t == 1) set_references();
+                if (t >= 1) exps(t - 1);
+                acc[t] = c;
+                if (base0 + 16 * P::KSP * (t + 1) > Tp) mask_tile(acc[t], t);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (base0 + P::kChunkKeys > Tp) {                                // keys that not every row sees
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int32_t limit = min(Tp + (32 * rs + tile_pos(i, g)) % x.N, x.T - 1) - base0 - 32 * ks - r;
-#pragma unroll
-                for (int k = 0; k < P::KT; ++k)
-                    if (32 * P::KSP * k > limit) acc[k][i] = -INFINITY;
-            }
-        }
-        // whole references, the rows' sums relative to them
-        {
-            float m[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) m[i] = acc[0][i];
-#pragma unroll
-            for (int k = 1; k < P::KT; ++k)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) m[i] = fmaxf(m[i], acc[k][i]);
-            const float top = rintf(reduce_16x32<MaxOp>(m) * scale);
-            if ((lane & 1) == 0) sm_m[ks][32 * rs + tile_pos(r >> 1, g)] = top;
-        }
-        if constexpr (P::KSP > 1) __syncthreads();
-        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the wave's own rows
-        {
-            float ref[16], sum[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float m = sm_m[0][32 * rs + tile_pos(i, g)];
-#pragma unroll
-                for (int k = 1; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][32 * rs + tile_pos(i, g)]);
-                ref[i] = m > -INFINITY ? m : 0.f;                        // (nothing visible: every term is exp2(-inf) = 0)
-                sum[i] = 0.f;
-            }
-#pragma unroll
-            for (int k = 0; k < P::KT; ++k)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    acc[k][i] = exp2_neg(fmaf(acc[k][i], scale, -ref[i]));
-                    sum[i] += acc[k][i];
-                    if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // (a schedule across tiles runs out of registers)
-                }
-            const float l = reduce_16x32<AddOp>(sum);
-            if ((lane & 1) == 0) sm_l[ks][32 * rs + tile_pos(r >> 1, g)] = l;
-        }
+        exps(P::KT - 1);
+        leave_sums();
+        if (__any(!(sum[0] < kFar && sum[1] < kFar && sum[2] < kFar && sum[3] < kFar)) && lane == 0) sm_far[left & 1] = 1;
+        if (tid == 0) sm_far[~left & 1] = 0;
         __syncthreads();
         if (left > 0) stages.request(src_next, keys, P::NS - 1);
-        if (loader < 0) {
+        if (sm_far[left & 1]) {
+            // Some row's logits rise far above those of its first tile, or are no numbers: all of it once more from memory, with the chunk's own maxima.
+            load_q(lh);
+            const char* mine = src + 16 * qd;
+            auto logits = [&](int t) {
+                const char* key = mine + min(16 * (P::KSP * t + ks) + t16, keys - 1) * kRowBytes;
+                f32x4 c = {};
+#pragma unroll
+                for (int st = 0; st < 4; ++st)
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[st]), __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(key + 64 * st)), c, 0, 0, 0);
+                acc[t] = c;
+                if (base0 + 16 * P::KSP * (t + 1) > Tp) mask_tile(acc[t], t);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            logits(0);
+            float m[4] = {acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+#pragma unroll
+            for (int t = 1; t < P::KT; ++t) {
+                logits(t);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) m[j] = fmaxf(m[j], acc[t][j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float top = rintf(reduce_16<MaxOp>(m[j]) * scale);
+                ref[j] = top > -INFINITY ? top : 0.f;
+                sum[j] = 0.f;
+            }
+#pragma unroll
+            for (int t = 0; t < P::KT; ++t) exps(t);
+            leave_sums();
+            __syncthreads();
+        }
+        if (w < P::kPollers) {
             __builtin_amdgcn_s_setprio(3);
-            // published: the sum of every row
+            // published: the sum of every row; four rows of a chunk side by side, then those of the next chunk
+            unsigned long long* part = x.part + ((int64_t)blockIdx.x - chunk) * kRows;
             Waiter wait{x.state + 1, epoch + 1, x.limit, true};
             for (int row = tid; row < kRows; row += P::kPollers * kWave) {
-                float m = sm_m[0][row], l = sm_l[0][row];
+                float m = sm_m[0][row];
 #pragma unroll
-                for (int k = 1; k < P::KSP; ++k) { m = fmaxf(m, sm_m[k][row]); l += sm_l[k][row]; }
+                for (int k = 1; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][row]);
+                float l = 0.f;
+#pragma unroll
+                for (int k = 0; k < P::KSP; ++k) l += ldexpf(sm_l[k][row], (int)fmaxf(sm_m[k][row] - m, -512.f));
                 if (l > 0.f && !(fabsf(m) < (float)(kExpBias - 256))) wait.ok = false;       // beyond the words' exponent
-                __hip_atomic_store(x.part + (int64_t)blockIdx.x * kRows + row, tagged_number(l, l > 0.f ? (int)m : 0, tag), __ATOMIC_RELAXED,
+                __hip_atomic_store(part + ((row >> 2) * x.nch + chunk) * 4 + (row & 3), tagged_number(l, l > 0.f ? (int)m : 0, tag), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
             wait.ok = __all(wait.ok);
-            // combined: four rows a wave, 16 lanes to a row
+            // combined: four rows a wave, 16 lanes to a row, U words of a lane asked for together
             unsigned long long* stat = x.stat + (int64_t)(lh % x.stat_heads) * kRows;
-            const int first = (int)blockIdx.x - chunk;                   // block of the head's first chunk
-            for (int row0 = 4 * (chunk * P::kPollers + w); row0 < kRows; row0 += 4 * P::kPollers * x.nch) {
-                const int row = row0 + (lane & 3);
-                int X = kExpNone;
-                float L = 0.f;
-                for (int c0 = 0; c0 < x.nch; c0 += 16 * kU) {
-                    unsigned long long v[kU];
-                    auto need = [&](int u, int l) { return c0 + 16 * u + (l >> 2) < x.nch; };
-                    wait.get<kU>(x.part, [&](int u, int l) {
-                        return (uint32_t)((first + min(c0 + 16 * u + (l >> 2), x.nch - 1)) * kRows + row0 + (l & 3));
-                    }, need, tag, v);
-                    int top = X;
+            auto combine = [&](auto words) {
+                constexpr int U = decltype(words)::value;
+                for (int row0 = 4 * (chunk * P::kPollers + w); row0 < kRows; row0 += 4 * P::kPollers * x.nch) {
+                    const int row = row0 + (lane & 3);
+                    int X = kExpNone;
+                    float L = 0.f;
+                    for (int c0 = 0; c0 < x.nch; c0 += 16 * U) {
+                        unsigned long long v[U];
+                        auto need = [&](int u, int l) { return c0 + 16 * u + (l >> 2) < x.nch; };
+                        wait.get<U>(part, [&](int u, int l) { return (uint32_t)(row0 * x.nch + min(c0 + 16 * u + (l >> 2), x.nch - 1) * 4 + (l & 3)); }, need, tag, v);
+                        // Mostly every number is one that a float holds, and so is their sum: its bits are then those of the word, but for the bias.
+                        bool plain = x.nch <= 16 * U;
 #pragma unroll
-                    for (int u = 0; u < kU; ++u) top = max(top, need(u, lane) ? number_exp(v[u]) : kExpNone);
+                        for (int u = 0; u < U; ++u) plain = plain && (uint32_t)(number_exp(v[u]) + 100) <= 200u;
+                        if (__all(plain)) {
+                            X = 0;
+#pragma unroll
+                            for (int u = 0; u < U; ++u) L += need(u, lane) ? __uint_as_float((uint32_t)v[u] + (127u << 23)) : 0.f;
+                        } else {
+                            int top = X;
+#pragma unroll
+                            for (int u = 0; u < U; ++u) top = max(top, need(u, lane) ? number_exp(v[u]) : kExpNone);
+                            L = ldexpf(L, max(X - top, -512));
+#pragma unroll
+                            for (int u = 0; u < U; ++u) L += need(u, lane) ? ldexpf(number_mant(v[u]), max(number_exp(v[u]) - top, -512)) : 0.f;
+                            X = top;
+                        }
+                    }
+                    int top = max(X, dpp_move<0x124>(X));                // row_ror 4, 8: the lanes of the row
+                    top = max(top, dpp_move<0x128>(top));
+                    top = max(top, other_half<16>(top));
+                    top = max(top, other_half<32>(top));
                     L = ldexpf(L, max(X - top, -512));
-#pragma unroll
-                    for (int u = 0; u < kU; ++u) L += need(u, lane) ? ldexpf(number_mant(v[u]), max(number_exp(v[u]) - top, -512)) : 0.f;
-                    X = top;
+                    L += dpp_move<0x124>(L);
+                    L += dpp_move<0x128>(L);
+                    L = sum_rows16(L);
+                    L = sum_halves(L);
+                    if (wait.ok && lane < 4)
+                        __hip_atomic_store(stat + row, tagged_number(row < R && L > 0.f ? 1.f / L : 0.f, -top, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                int top = max(X, dpp_move<0x124>(X));                    // row_ror 4, 8: the lanes of the row
-                top = max(top, dpp_move<0x128>(top));
-                top = max(top, other_half<16>(top));
-                top = max(top, other_half<32>(top));
-                L = ldexpf(L, max(X - top, -512));
-                L += dpp_move<0x124>(L);
-                L += dpp_move<0x128>(L);
-                L += __int_as_float(other_half<16>(__float_as_int(L)));
-                L += __int_as_float(other_half<32>(__float_as_int(L)));
-                if (wait.ok && lane < 4)
-                    __hip_atomic_store(stat + row, tagged_number(row < R && L > 0.f ? 1.f / L : 0.f, -top, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            };
+            if (x.nch <= 16) combine(std::integral_constant<int, 1>{});
+            else if (x.nch <= 64) combine(std::integral_constant<int, 4>{});
+            else combine(std::integral_constant<int, 8>{});
             // all rows: the factor that makes this chunk's values probabilities
             for (int row = tid; row - lane < kRows; row += P::kPollers * kWave) {
                 unsigned long long v[1];
                 wait.get<1>(stat, [&](int, int l) { return (uint32_t)min(row - lane + l, kRows - 1); }, [&](int, int) { return row < kRows; }, tag, v);
                 if (row < kRows) {
-                    float m = sm_m[0][row];
 #pragma unroll
-                    for (int k = 1; k < P::KSP; ++k) m = fmaxf(m, sm_m[k][row]);
-                    sm_f[row] = m > -INFINITY ? ldexpf(number_mant(v[0]), min(max((int)m + number_exp(v[0]), -512), 512)) : 0.f;
+                    for (int k = 0; k < P::KSP; ++k)
+                        sm_l[k][row] = ldexpf(number_mant(v[0]), min(max((int)sm_m[k][row] + number_exp(v[0]), -512), 512));
                 }
             }
             if (lane == 0) sm_ok[w] = wait.ok;
@@ -843,26 +904,25 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         }
         __builtin_amdgcn_sched_barrier(0);
         {
-            float f[16];
+            const float4 f = *reinterpret_cast<const float4*>(&sm_l[ks][row_of]);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) f[i] = sm_f[32 * rs + tile_pos(i, g)];
+            for (int t = 0; t < P::KT; t += 4) {
+                float y[4];
 #pragma unroll
-            for (int k = 0; k < P::KT; ++k) {
-                float p[2] = {0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 16; ++i) p[i & 1] = fmaf(acc[k][i], f[i], p[i & 1]);
-                const float v = sum_halves(p[0] + p[1]);
-                if (g == 0) sm_col[rs][32 * (P::KSP * k + ks) + r] = v;
+                for (int u = 0; u < 4; ++u) y[u] = fmaf(acc[t + u][3], f.w, fmaf(acc[t + u][2], f.z, fmaf(acc[t + u][1], f.y, acc[t + u][0] * f.x)));
+                // the four lanes of a key, for four tiles together: lanes qd end with tile t + qd
+                const float z0 = add_swap<32>(y[0], y[2]), z1 = add_swap<32>(y[1], y[3]);
+                sm_col[rs][16 * (P::KSP * (t + qd) + ks) + t16] = add_swap<16>(z0, z1);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         __syncthreads();
         if (loader < 0) {
             float* dst = x.alpha_h + (int64_t)lh * Tp + base0;
-            for (int i = tid; i < P::kChunkKeys && base0 + i < Tp; i += P::kPollers * kWave) {
+            for (int i = tid; i < P::kChunkKeys && base0 + i < Tp; i += P::kStorers * kWave) {
                 float v = sm_col[0][i];
 #pragma unroll
-                for (int k = 1; k < RT; ++k) v += sm_col[k][i];
+                for (int k = 1; k < P::RS; ++k) v += sm_col[k][i];
                 dst[i] = v;
             }
         }
@@ -936,10 +996,11 @@ template <class F> static hipError_t raise_lds(F kernel, int bytes, std::atomic<
 
 static int sweep_blocks(const Ctx* c) { return min(kSweepPerCu * c->n_cu, kSweepMaxBlocks); }
 
-// Where the sweep is the faster form (us, two passes / one sweep): the chunks of a head fit the chip at once, and the launch has
-// chunks enough (32 layers x 8 heads of 1024 keys, 32 rows, 256 chunks: 33.0 / 29.5; 8 layers, 64 chunks: 19.7 / 26.1; 2048 keys, 128 chunks: 23.3 / 23.2).
-// 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 418, 715 / 573); 128 rows, a chunk of 256 keys a block, from 4096 keys
-// (131 / 121; 3000 keys: 97 / 100) to 64 chunks a head (16384 keys 448 / 413; 24000: 615 / 618, 32768: 821 / 819, 65000, 8 layers: 426 / 436).
+// Where the sweep is the faster form (us, two passes / one sweep): the chunks of a head fit the chip at once, and the launch has chunks enough (96; 64
+// chunks: 512 keys a chunk 14.8 / 15.4, 1024: 17.5 / 16.9, 256: 15.7 / 14.6; 96 chunks of 256 keys 16.8 / 13.9, 20.2 / 16.0 with 192).
+// 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 390, 715 / 538).  128 rows gain up to 128 chunks a head, whose words a wave combines in one round of
+// loads, as long as whole heads fill 84 % of the chip's blocks (16 layers: 28000 keys, 86 %: 359 / 348; 30000, 92 %: 383 / 360; 36000, 83 %, 141 chunks:
+// 452 / 513; 40000, 92 %, 157 chunks: 499 / 538; 65536, 100 %, 256 chunks: 807 / 848; 1024 keys of 32 layers 44 / 34.5, of 8 layers 22.6 / 17.6).
 bool importance_may_sweep(const skv_desc& d) {
     const int64_t heads = (int64_t)d.n_layers * d.n_kv_heads;
     static_assert(Sweep<1>::kChunkKeys >= kSweepMinChunk && Sweep<2>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kRows <= kSweepMaxRows, "");
@@ -951,7 +1012,7 @@ static bool importance_sweeps(const Ctx* c, int32_t T) {
     using P = Sweep<RT>;
     const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, nch = (T + P::kChunkKeys - 1) / P::kChunkKeys, most = sweep_blocks(c);
     if (!c->single_launch || !c->imp_part || nch > most || heads > kSweepMostHeads || heads * nch > (1 << 30) || heads * nch < kSweepMinChunks) return false;
-    return RT < 4 || (T >= 4096 && nch <= 64);
+    return RT < 4 || (nch <= 128 && most / nch * nch * 100 >= 84 * most);
 }
 
 template <int RT>

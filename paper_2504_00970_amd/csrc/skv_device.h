@@ -21,6 +21,12 @@ __device__ __forceinline__ float sum_halves(float x) {
     return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
+// sum over the lanes l and l ^ 16, in both
+__device__ __forceinline__ float sum_rows16(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
 // 16 bytes that this launch reads or writes once (K/V rows, mean keys): the non-temporal forms.  Measured on one-shot reads of
 // a 2.15 GB key pool (a wave requests 4 KB and ends): 6.45 TB/s with plain loads, 7.15 TB/s with these.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));

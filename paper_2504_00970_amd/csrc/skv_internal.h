@@ -120,7 +120,7 @@ constexpr int kImportanceMaxRows = 256;   // query rows (G * window tokens) per 
 // tag, and the polling rounds (about a microsecond each) before a block leaves the work to the two passes
 constexpr int kSweepPerCu = 2;
 constexpr int kSweepMaxBlocks = kSweepPerCu * kComputeUnits;
-constexpr int kSweepMaxRows = 128, kSweepMinChunk = 256, kSweepMinChunks = 128;      // rows, keys of the shortest chunk, chunks of the smallest launch
+constexpr int kSweepMaxRows = 128, kSweepMinChunk = 256, kSweepMinChunks = 96;      // rows, keys of the shortest chunk, chunks of the smallest launch
 constexpr int kSweepStatHeads = 1024;
 constexpr unsigned int kSweepTags = (1u << 24) - 1;
 constexpr int kSweepMostHeads = 1 << 20;

@@ -226,6 +226,43 @@ def test_token_importance_sweep_beyond_its_exponents(U, Hq):
     assert torch.equal(got, want) and not want.isnan().any()
 
 
+# a wave combines 16, 64 or 128 chunks in one round of loads and more in several: 16, 17, 64, 65 and 128 chunks of 256 keys, 137 of 512, 17 of 1024
+@pytest.mark.parametrize("L,Hq,H,N,T", [(6, 4, 1, 32, 4096), (6, 4, 1, 32, 4097), (2, 4, 1, 32, 16384), (2, 4, 1, 32, 16400), (1, 4, 1, 32, 32768),
+                                        (1, 2, 1, 32, 70001), (6, 1, 1, 32, 16500)])
+def test_token_importance_sweep_combines_any_number_of_chunks(U, L, Hq, H, N, T):
+    """Against the two passes, to the bound of test_token_importance_in_one_sweep; other bits show whose result it is."""
+    _say("importance in one sweep, chunks", L, Hq, N, T)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert ((got - want).abs() / want).max().item() <= 2e-6
+    assert not torch.equal(got, want)
+
+
+@pytest.mark.parametrize("Hq", [8, 16, 32])                                                # chunks of 1024, 512 and 256 keys
+@pytest.mark.parametrize("rise", [16, 40, 120, 250])
+def test_token_importance_sweep_of_logits_that_rise(U, Hq, rise):
+    """The first keys of some chunks, the first and the last among them, lie `rise` (log2 units) below the rest: sums relative to a chunk's first keys stay
+    below 2^24 or pass it, or overflow.  Arguments of exp2 below 2^6 (below 2^8: results under 1e-19 of the others, held to 1e-30 in all) are rounded
+    to 2^-19 on each side: 2 * 2^-19 * ln 2 = 2.6e-6 of a value, with sums in another order below 4e-6."""
+    L, H, N, T = 4, 8, 32, 4120
+    _say("importance in one sweep, rising logits", Hq, rise)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    q[..., 0] = 8.0
+    K[..., 0] = 0.0
+    low = -rise / (8 * 1.4426950408889634 / math.sqrt(128))
+    for first in (0, 1024, 2304, 3072, 4096):
+        K[:, ::2, first:first + 20, 0] = low
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert torch.isfinite(got).all()
+    assert torch.all((got - want).abs() <= 4e-6 * want + 1e-30)
+    for l in range(L):
+        assert not torch.equal(got[l], want[l])
+
+
 def test_token_importance_sweeps_on_two_streams(U):
     """Two contexts whose sweeps meet on the GPU: each finds part of the compute units taken, its blocks wait or leave the work to the two passes;
     the results are those of a sweep alone to the bound of the test above."""
