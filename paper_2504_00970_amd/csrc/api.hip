@@ -77,7 +77,7 @@ constexpr int kWsParts = 17;
 // other array could look like a valid tag), so it has the same extent for every descriptor.
 constexpr size_t kFixedEpochBytes = (size_t)skv::kStepMaxPairs * skv::kStepEpochStride * sizeof(unsigned int);
 constexpr size_t kFixedScoreWords = 128 * 1024;
-constexpr size_t kFixedPartBytes = (size_t)skv::kStepMaxBlocks * 8 * skv::kStepPartWords * sizeof(unsigned long long);
+constexpr size_t kFixedPartBytes = (size_t)skv::kStepMaxBlocks * skv::step_part_words(8) * sizeof(unsigned long long);
 
 // per layer: list, counts by digit, kept tokens per block, cut, counters
 constexpr size_t kRetainLayerBytes = skv::kRetList * 8 + 2048 * 4 + skv::kRetMaxChunks * 4 + 16 + 16;
@@ -88,14 +88,16 @@ size_t workspace_layout(const skv_desc& d, int max_splits, int max_sel, bool fix
     const size_t n_seg = (size_t)(d.max_tokens + skv::kSegTokPerBlock - 1) / skv::kSegTokPerBlock;
     const size_t step_pairs = BH < (size_t)skv::kStepMaxPairs ? BH : (size_t)skv::kStepMaxPairs;
     const int G = d.n_q_heads / d.n_kv_heads;
-    *score_stride = d.max_sentences;
+    // a pair's scores begin at a line, where there is room: two pairs' blocks that store to one line others poll wait for each other
+    *score_stride = (d.max_sentences + 15) / 16 * 16;
+    if (fixed_tagged && step_pairs * (size_t)*score_stride > kFixedScoreWords) *score_stride = d.max_sentences;
     sz[0] = kFixedEpochBytes;                                                      // step_epoch
     if (fixed_tagged) {
         sz[1] = kFixedScoreWords * sizeof(unsigned long long);                     // step_score
         sz[2] = kFixedPartBytes;                                                   // step_part
     } else {
-        sz[1] = round256(step_pairs * (size_t)d.max_sentences * sizeof(unsigned long long));
-        sz[2] = round256((size_t)skv::kStepMaxBlocks * G * skv::kStepPartWords * sizeof(unsigned long long));
+        sz[1] = round256(step_pairs * (size_t)*score_stride * sizeof(unsigned long long));
+        sz[2] = round256((size_t)skv::kStepMaxBlocks * skv::step_part_words(G) * sizeof(unsigned long long));
     }
     sz[3] = round256(n_seg * sizeof(unsigned long long));                          // seg_part
     sz[4] = round256(BQ * max_splits * skv::kHeadDim * sizeof(float));             // att_part

@@ -128,15 +128,35 @@ hipError_t launch_query_update(Ctx* c, int32_t B, const void* q_t, const int32_t
 // Blocks are aligned to sequences: block x -> (sequence b, local block) by walking cu_sent.
 // ------------------------------------------------------------------------------------------------
 
+// Scores of the STEP * N buckets from row_w on: p[i] of the lanes (lane / (64 / STEP)) is the score of bucket row_w + lane / (64 / STEP) + STEP i; c: the lane's place
+// among those of its bucket, negative where they hold no sum.  TAGGED: consecutive lanes take consecutive buckets, for one store of whole words of a line.
+template <bool TAGGED, int STEP, int N>
+__device__ __forceinline__ void store_scores(void* __restrict__ out_seq, const float (&p)[N], int c, int32_t row_w, int32_t n_sent, uint32_t tag) {
+    constexpr int kLanes = kWave / STEP, kFirst = STEP == 8 ? 4 : 0;      // lanes of a bucket, the first that holds its sum
+    const int lane = threadIdx.x & 63;
+    if constexpr (TAGGED) {
+        float v = p[0];
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+            float x = p[i];
+            asm volatile("" : "+v"(x));                                  // (selects; else the compiler makes an array in LDS of p)
+            v = c == i ? x : v;
+        }
+        v = __shfl(v, kLanes * (lane & (STEP - 1)) + kFirst + ((lane / STEP) & (N - 1)));
+        const int32_t s = row_w + lane;
+        if (lane < STEP * N && s < n_sent) st_tagged(static_cast<unsigned long long*>(out_seq) + s, v, tag);
+    } else if (c == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int32_t s = row_w + lane / kLanes + STEP * i;
+            if (s < n_sent) static_cast<float*>(out_seq)[s] = p[i];
+        }
+    }
+}
+
 // One wave: the RPWV buckets [row_w, row_w + RPWV) of a sequence.  q_grp = the first query of the head's group,
 // sv_seq / out_seq = the (head, sequence) slices of the table and of the scores.  TAGGED: out_seq holds 64-bit (score, tag)
 // words that other blocks of the same launch read.
-template <bool TAGGED>
-__device__ __forceinline__ void store_score(void* __restrict__ out_seq, int32_t s, float v, uint32_t tag) {
-    if (TAGGED) st_tagged(static_cast<unsigned long long*>(out_seq) + s, v, tag);
-    else static_cast<float*>(out_seq)[s] = v;
-}
-
 template <int EB, int G, int RPWV, bool TAGGED>
 __device__ __forceinline__ void score_wave_f32(const char* __restrict__ q_grp, const float* __restrict__ sv_seq,
                                                int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, uint32_t tag = 0) {
@@ -177,13 +197,7 @@ __device__ __forceinline__ void score_wave_f32(const char* __restrict__ q_grp, c
         p[i] = dpp_add<0x128>(p[i]);
         p[i] += __shfl_xor(p[i], 16);
     }
-    if (c == 0) {
-#pragma unroll
-        for (int i = 0; i < kIter; ++i) {
-            const int32_t s = row0 + 2 * i;
-            if (s < n_sent) store_score<TAGGED>(out_seq, s, p[i], tag);
-        }
-    }
+    store_scores<TAGGED, 2>(out_seq, p, c, row_w, n_sent, tag);
 }
 
 // The same from a bf16 table: a vector is 256 bytes = 16 lanes x 16 bytes (8 dims per lane), a wave load covers
@@ -233,13 +247,7 @@ __device__ __forceinline__ void score_wave_bf16(const char* __restrict__ q_grp, 
         p[i] = dpp_add<0x124>(p[i]);
         p[i] = dpp_add<0x128>(p[i]);
     }
-    if (c == 0) {
-#pragma unroll
-        for (int i = 0; i < kIter; ++i) {
-            const int32_t s = row0 + 4 * i;
-            if (s < n_sent) store_score<TAGGED>(out_seq, s, p[i], tag);
-        }
-    }
+    store_scores<TAGGED, 4>(out_seq, p, c, row_w, n_sent, tag);
 }
 
 // The same from an E4M3 table: a vector is 128 bytes = 8 lanes x 16 bytes (16 dims per lane), a wave load covers 8 buckets,
@@ -300,13 +308,7 @@ __device__ __forceinline__ void score_wave_e4m3(const char* __restrict__ q_grp, 
         p[i] = dpp_add<0x4E>(p[i]);
         p[i] = dpp_add<0x124>(p[i]);                        // row_ror 4: lanes 4..7 of each group of 8 now hold the group's sum
     }
-    if (c == 4) {
-#pragma unroll
-        for (int i = 0; i < kIter; ++i) {
-            const int32_t s = row0 + 8 * i;
-            if (s < n_sent) store_score<TAGGED>(out_seq, s, p[i], tag);
-        }
-    }
+    store_scores<TAGGED, 8>(out_seq, p, c - 4, row_w, n_sent, tag);        // (lanes 4 .. 7 of each group)
 }
 
 constexpr int kScoreRowsPerWave16 = 16;
@@ -1132,7 +1134,7 @@ struct AttArgs {
     unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
     unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
     int32_t score_stride;
-    unsigned long long* step_part;    // [blocks][G][kHeadDim + 2] (value, tag) words: a block's partial sums, then (reference, normaliser)
+    unsigned long long* step_part;    // [blocks][step_part_words(G)] (value, tag) words: a block's sums [G][kHeadDim], then (reference, normaliser) [G]
     int32_t wait_limit;       // rounds of polling before a block gives up
     unsigned int* err_dev;    // set to 1 by a block that gave up
     unsigned int* err_host;   // the same word in pinned host memory (device address), nullable
@@ -1197,6 +1199,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     __shared__ __attribute__((aligned(16))) char sm[kShBytes];
     __shared__ WaveSums<kTiles> sm_waves;
     __shared__ int sm_last;
+    __shared__ float sm_norm[kStepping ? 2 * G : 1];                        // kStep: (reference, normaliser) of the block's heads
     __shared__ int32_t sm_row[CHUNK];
     __shared__ float sm_merge[kStepping ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
 
@@ -1250,26 +1253,39 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             // lanes, same order), so skv_score returns the very floats that are ranked here.  Each score is stored
             // with the launch tag in one 64-bit word; the blocks that go on read the pair's words until all carry it.
             const int32_t S = sq.n_sent;
-            const int32_t per = MODE == kStep ? (S + (1 << a.lg_parts) - 1) >> a.lg_parts : ceil_div(S, a.parts, a.per_part);
+            // From kStepLineRows buckets a block on, shares are whole lines of the exchange (16 words), each written by one store: a line that others poll and that is
+            // written in pieces, by several stores or several blocks, costs its readers a trip through memory for each.  Us per layer, shares as
+            // they come, a store for every two words / this: one sequence of 49152 tokens 13.5 / 12.5, 131072 17.8 / 17.2, two of 32768 15.4 / 14.6, four of
+            // 16384 17.7 / 17.1; 32768 tokens (41 buckets a block, 28 of 32 blocks would score) 11.9 / 12.0, 8192 (11) 10.4 / 10.5.
+            int32_t per = MODE == kStep ? (S + (1 << a.lg_parts) - 1) >> a.lg_parts : ceil_div(S, a.parts, a.per_part);
+            const bool lines = per > kStepLineRows;
+            if (lines) per = (per + 15) & ~15;
             const int32_t lo = split * per, hi = min(lo + per, S);
             const char* qg = a.q_score + ((qhead0 * kHeadDim) * EB);
             const int64_t row0 = (int64_t)h * a.v.S_total + sq.sent_base;
             unsigned long long* sc_out = a.step_score + (int64_t)bh * a.score_stride;
-            auto score_rows = [&](auto rpwv_tag) {
-                constexpr int RPWV = decltype(rpwv_tag)::value;
-                for (int32_t rw = lo + w * RPWV; rw < hi; rw += kBlockWaves * RPWV) {
-                    if (a.sv_bytes == kTableF32)
-                        score_wave_f32<EB, G, RPWV, true>(qg, reinterpret_cast<const float*>(a.semvec) + row0 * kHeadDim, hi, rw, sc_out, tag);
-                    else if (a.sv_bytes == kTableBf16)
-                        score_wave_bf16<EB, G, (RPWV < 4 ? 4 : RPWV), true>(qg, a.semvec + row0 * kHeadDim * 2, hi, rw, sc_out, tag);
-                    else
-                        score_wave_e4m3<EB, G, (RPWV < 8 ? 8 : RPWV), true>(qg, a.semvec + row0 * kHeadDim, hi, rw, sc_out, tag);
-                }
+            // few buckets per block: 4 per wave visit (8 from an E4M3 table; two loads in flight per lane, all 16 waves busy from 64 buckets on);
+            // more: 16 per visit (eight loads in flight per lane), a line of the exchange
+            auto score_rows = [&](auto rows, auto score) {
+                constexpr int R = decltype(rows)::value;
+                for (int32_t rw = lo + w * R; rw < hi; rw += kBlockWaves * R) score(rows, rw);
             };
-            // few buckets per block: 4 per wave visit (two loads in flight per lane, all 16 waves busy from 64 buckets on);
-            // many: 16 per visit (eight loads in flight per lane)
-            if (per <= kBlockWaves * 4) score_rows(std::integral_constant<int, 4>{});
-            else score_rows(std::integral_constant<int, 16>{});
+            auto score_table = [&](auto few, auto score) {
+                if (lines) score_rows(std::integral_constant<int, 16>{}, score);
+                else score_rows(few, score);
+            };
+            if (a.sv_bytes == kTableF32)
+                score_table(std::integral_constant<int, 4>{}, [&](auto rows, int32_t rw) {
+                    score_wave_f32<EB, G, decltype(rows)::value, true>(qg, reinterpret_cast<const float*>(a.semvec) + row0 * kHeadDim, hi, rw, sc_out, tag);
+                });
+            else if (a.sv_bytes == kTableBf16)
+                score_table(std::integral_constant<int, 4>{}, [&](auto rows, int32_t rw) {
+                    score_wave_bf16<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim * 2, hi, rw, sc_out, tag);
+                });
+            else
+                score_table(std::integral_constant<int, 8>{}, [&](auto rows, int32_t rw) {
+                    score_wave_e4m3<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim, hi, rw, sc_out, tag);
+                });
             SKV_T(12);
             // Blocks that neither attend (no position of theirs can hold a token: n <= budget) nor merge are done.
             if (split >= merging_blocks(G, a.lg_merge) && j0 >= budget) return;
@@ -1315,7 +1331,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     auto presence = [&]() {
         if constexpr (kStepping) {
             if (tid == 0)                                         // a block that gave up publishes nothing valid
-                st_tagged(a.step_part + (int64_t)blockIdx.x * G * kStepPartWords + kHeadDim, -INFINITY, step_ok ? tag : 0u);
+                st_tagged(a.step_part + (int64_t)blockIdx.x * step_part_words(G) + G * kHeadDim, -INFINITY, step_ok ? tag : 0u);
         }
     };
     // block 0: the words of blocks first .. (blocks of the pair that run the selection) - 1 carry the tag (bounded wait);
@@ -1330,7 +1346,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             if (tid == 0) *missing = 0u;
             __syncthreads();
             if (tid >= first && tid < n_cand) {
-                const unsigned long long* src = a.step_part + ((int64_t)(tid * n_pairs + bh) * G) * kStepPartWords + kHeadDim;
+                const unsigned long long* src = a.step_part + (int64_t)(tid * n_pairs + bh) * step_part_words(G) + G * kHeadDim;
                 bool there = false;
                 for (int32_t round = 0; !there && round < a.wait_limit; ++round) there = tag_of(ld_tagged(src)) == tag;
                 if (!there) *missing = 1u;
@@ -1367,7 +1383,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     unsigned long long* my_part = nullptr;
     uint32_t part_tag = 0;
     if constexpr (kStepping) {
-        my_part = a.step_part + (int64_t)blockIdx.x * G * kStepPartWords;
+        my_part = a.step_part + (int64_t)blockIdx.x * step_part_words(G);
         part_tag = step_ok ? tag : 0u;                            // a block that gave up publishes nothing valid
     }
     if (has_work) {
@@ -1491,9 +1507,8 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
         __syncthreads();
         block_sums<G, kTiles, false, kDims>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
             if constexpr (kStepping) {
-                unsigned long long* dst = my_part + g * kStepPartWords;
-                st_tagged(dst + d, sum, part_tag);
-                if (d < 2) st_tagged(dst + kHeadDim + d, d == 0 ? mb : lb, part_tag);
+                st_tagged(my_part + g * kHeadDim + d, sum, part_tag);
+                if (d == 0) { sm_norm[2 * g] = mb; sm_norm[2 * g + 1] = lb; }
             } else if (nsplit == 1) {                                 // the only block: its sums are the result
                 const bool empty = lb == 0.f;                       // every retrieved position was out of range
                 a.out[(qhead0 + g) * kHeadDim + dim0 + d] = empty ? 0.f : sum / lb;
@@ -1503,6 +1518,10 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
             }
         });
+        if constexpr (kStepping) {                                // one store: see step_part_words
+            __syncthreads();
+            if (tid < 2 * G) st_tagged(my_part + G * kHeadDim + tid, sm_norm[tid], part_tag);
+        }
         SKV_T(7);
     }
 
@@ -1530,10 +1549,10 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
                 for (int u = 0; u < 2; ++u) {
                     const int sp = base + grp + u * groups;
                     if (sp < nsplit) {
-                        const unsigned long long* src = a.step_part + ((int64_t)(sp * n_pairs + bh) * G + g) * kStepPartWords;
-                        pv[u] = ld_tagged(src + at % kHeadDim);
-                        mv[u] = ld_tagged(src + kHeadDim);
-                        lv[u] = ld_tagged(src + kHeadDim + 1);
+                        const unsigned long long* src = a.step_part + (int64_t)(sp * n_pairs + bh) * step_part_words(G);
+                        pv[u] = ld_tagged(src + at);
+                        mv[u] = ld_tagged(src + G * kHeadDim + 2 * g);
+                        lv[u] = ld_tagged(src + G * kHeadDim + 2 * g + 1);
                         mine = mine && tag_of(pv[u]) == tag && tag_of(mv[u]) == tag && tag_of(lv[u]) == tag;
                     }
                 }

@@ -43,7 +43,12 @@ constexpr int kStepPairBits = 6;
 constexpr int kStepMaxPairs = 1 << kStepPairBits;
 constexpr int kStepMaxBlocks = 256;
 constexpr int kStepEpochStride = 16;     // 32-bit words between the epoch counters of two pairs (one 64-byte line each)
-constexpr int kStepPartWords = kHeadDim + 2;   // 64-bit words per query head of a block's partial: D sums, reference, normaliser
+constexpr int kStepLineRows = 48;        // buckets that a block scores up to which the shares are taken as they come, not in whole lines
+// 64-bit words of a block's partial: D sums of each of its G query heads, then a line with their (reference, normaliser) pairs, written by one store.  (Pairs behind the
+// sums of their head, in lines that held the next head's sums too: one sequence of 32768 tokens 12.4 us per layer, this 11.9; pairs in a line of their own, a store
+// for each: 12.7; the pairs of all blocks side by side: 13.4.)
+constexpr int kStepNormWords = 16;
+constexpr int step_part_words(int G) { return G * kHeadDim + kStepNormWords; }
 constexpr int kStepWaitLimit = 200000;   // default bound on the polling rounds of a waiting block (a round is about a microsecond)
 // decode step in two launches: the fused kernel's block size (64, 128, 256 tokens) is the smallest whose blocks, (sequence, KV head)
 // pairs x ceil(max_budget / size), all fit the chip at once (one block per compute unit); if even the 256-token blocks do
@@ -73,7 +78,7 @@ struct Ctx {
     unsigned long long* step_score;  // [pairs][step_score_stride] (score, tag) words
     int32_t step_score_stride;   // words per pair (max_sentences)
     int64_t step_score_words;    // words in step_score: a launch needs pairs * step_score_stride of them
-    unsigned long long* step_part;   // [kStepMaxBlocks][G][kStepPartWords] (value, tag) words
+    unsigned long long* step_part;   // [kStepMaxBlocks][step_part_words(G)] (value, tag) words
     unsigned int* err_dev;       // [1] set by a block of the single-launch step that gave up waiting
     unsigned int* err_host;      // the same flag in pinned host memory (host address; null: none)
     unsigned int* err_host_dev;  // device address of err_host

@@ -563,6 +563,17 @@ def test_fused_single_launch_equal_shares(U, oracle32, B, budgets, Hq, dtype):
     _fused_case(U, oracle32, wl, seed=37, layers=[0], budgets=budgets, seq_tokens=np.random.default_rng(B).integers(700, 5600, B).tolist())
 
 
+# buckets a block scores of 8 KV heads: 32 blocks a pair with one sequence (48, 49 and 64, the last block with one bucket), 10 with three (one tenth of
+# 480, 481 and 1000; shares of 16 lines), 8 with four
+@pytest.mark.parametrize("B,S,dtype,Hq,sv_dtype", [(1, 1536, "bf16", 32, "f32"), (1, 1537, "bf16", 32, "f32"), (1, 1985, "f32", 16, "bf16"), (1, 1600, "bf16", 64, "fp8"),
+                                                   (3, 480, "bf16", 32, "fp8"), (3, 481, "bf16", 8, "fp8"), (3, 1000, "f32", 32, "f32"), (4, 393, "bf16", 64, "bf16"),
+                                                   (4, 5, "bf16", 32, "fp8")])
+def test_fused_single_launch_shares_of_whole_lines(U, oracle32, B, S, dtype, Hq, sv_dtype):
+    """The single launch's blocks score up to 48 buckets as they come, more in shares of 16, rounded up, so that the last blocks of a pair may have fewer or none."""
+    wl = gen.CFG1.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(3 * S, 3 * S), budgets=(500,), len_dist=("fixed", 3), dtype=dtype)
+    _fused_case(U, oracle32, wl, seed=81, layers=[0], sv_dtype=sv_dtype)
+
+
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
     """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20 with budget 1500), a last tile of one token and of
