@@ -123,6 +123,23 @@ def test_semvec_matches_oracle(U, oracle32, dtype, dist):
     assert np.array_equal(got[:, :, one], ref[:, :, one])          # length-1 buckets are exact copies
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_semvec_on_both_sides_of_the_long_buckets(U, oracle32, dtype):
+    """Buckets of up to 48 rows and of more, whole rounds of loads (16 or 32 rows in bf16, 8 or 16 in fp32) and a row more or less; the bound of the test above."""
+    _say("semvec, long buckets", dtype)
+    lens = np.array([48, 49, 1, 47, 50, 63, 64, 65, 79, 80, 81, 96, 97, 128, 129, 16, 17, 33], dtype=np.int64)
+    wl = gen.CFG3.scaled(n_layers=2, n_kv_heads=2, n_q_heads=8, n_tokens=int(lens.sum()), dtype=dtype)
+    off, S = gen.offsets_of(lens), len(lens)
+    K = torch.stack([gen.kv_layer(lens, 2, 128, wl.torch_dtype, 6, l)[0] for l in range(2)])
+    ref = oracle32.semvec(gen.to_numpy(K), off)
+    sv = torch.full((2, 2, S, 128), 9.0, dtype=torch.float32, device=U.DEV)
+    U.make_ctx(wl, wl.n_tokens, S, 16).build_semvec(K.to(U.DEV), U.i32(off), S, sv)
+    torch.cuda.synchronize()
+    kmax = float(K.float().abs().max())
+    bound = (2.0 * np.maximum(lens - 1, 0) * 2.0 ** -24 * kmax + 2.0 ** -22 * kmax)[None, None, :, None]
+    assert np.all(np.abs(sv.cpu().numpy() - ref) <= bound)
+
+
 @pytest.mark.parametrize("sv_dtype", ["f32", "fp8"])
 @pytest.mark.parametrize("S", [639, 640, 641])
 def test_semvec_at_the_line_between_its_forms(U, oracle32, S, sv_dtype):
