@@ -951,6 +951,12 @@ __device__ __forceinline__ float sum_quads(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// the larger of the lanes l and l ^ 32, in both
+__device__ __forceinline__ float max_halves(float x) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+
 // A wave's tile of 16 tokens on the matrix cores.  With t16 = lane % 16 and qd = lane / 16:
 //  * S^T = K Q^T: the A fragment is a 16-byte piece (at byte 64 s + 16 qd, s < kPieces) of token t16's key, the B fragment the same dims
 //    of head t16's query (heads >= G are zero).  The order of the dims inside the contraction is free as long as A and B agree,
@@ -1071,33 +1077,34 @@ template <int NT> struct WaveSums {
 };
 // A barrier later: the block's output relative to its common reference, from the sums that NT waves left `stride` bytes apart, each relative to
 // the wave's own max.  put(g, d, sum, reference, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
-// streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).
+// streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).  Where 16 waves are added up for
+// at most 512 outputs, the two halves of a wave take half of them each (257 tokens, 128 outputs: 5.92 -> 5.78 us; with 4 lanes an output 5.79, with 8 5.98;
+// 8 waves over two lanes: 512 tokens 7.32 -> 7.45, 4 waves: the step of 7351 tokens 10.40 -> 10.48).
 template <int G, int NT, bool HEAD_FAST, int DIMS = kHeadDim, typename Put>
 __device__ __forceinline__ void block_sums(const char* tiles, int stride, const WaveSums<NT>& ws, Put put) {
-    for (int i = threadIdx.x; i < G * DIMS; i += kBlockThreads) {
-        const int g = HEAD_FAST ? i % G : i / DIMS, d = HEAD_FAST ? i / G : i % DIMS;
-        float mw[NT], fw[NT], lw[NT];
+    constexpr int kOuts = G * DIMS, kLanes = !HEAD_FAST && NT == 16 && 2 * kOuts <= kBlockThreads ? 2 : 1, kWaves = NT / kLanes;
+    static_assert(kWaves * kLanes == NT && kWaves % 4 == 0 && kOuts * kLanes <= kBlockThreads && (kLanes == 1 || kOuts % (kWave / kLanes) == 0), "every output at once, both lanes of each");
+    const int lane = threadIdx.x & 63, i = (int)(threadIdx.x >> 6) * (kWave / kLanes) + lane % (kWave / kLanes), k0 = lane / (kWave / kLanes) * kWaves;
+    if (i >= kOuts) return;
+    const int g = HEAD_FAST ? i % G : i / DIMS, d = HEAD_FAST ? i / G : i % DIMS;
+    float mw[kWaves], fw[kWaves], lw[kWaves];
+    __builtin_memcpy(mw, __builtin_assume_aligned(&ws.reference[g][k0], 16), sizeof(mw));
+    __builtin_memcpy(fw, __builtin_assume_aligned(&ws.factor[g][k0], 16), sizeof(fw));
+    __builtin_memcpy(lw, __builtin_assume_aligned(&ws.sum[g][k0], 16), sizeof(lw));
+    float mb = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < NT; k += 4) {
-            const float4 t = *reinterpret_cast<const float4*>(&ws.reference[g][k]), u = *reinterpret_cast<const float4*>(&ws.factor[g][k]),
-                         v = *reinterpret_cast<const float4*>(&ws.sum[g][k]);
-            mw[k] = t.x; mw[k + 1] = t.y; mw[k + 2] = t.z; mw[k + 3] = t.w;
-            fw[k] = u.x; fw[k + 1] = u.y; fw[k + 2] = u.z; fw[k + 3] = u.w;
-            lw[k] = v.x; lw[k + 1] = v.y; lw[k + 2] = v.z; lw[k + 3] = v.w;
-        }
-        float mb = -INFINITY;
+    for (int k = 0; k < kWaves; ++k) mb = fmaxf(mb, mw[k]);
+    if constexpr (kLanes == 2) mb = max_halves(mb);
+    float o = 0.f, lb = 0.f;
 #pragma unroll
-        for (int k = 0; k < NT; ++k) mb = fmaxf(mb, mw[k]);
-        float o = 0.f, lb = 0.f;
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            const float c = fw[k] * pow2_whole(mw[k] - mb);
-            o += c * reinterpret_cast<const float*>(tiles + k * stride)[d * G + g];
-            lb += c * lw[k];
-        }
-        if (lb != lb) mb = 0.f;                                       // NaN, perhaps with no other logit: merges pass over a reference of -infinity
-        put(g, d, o, mb, lb);
+    for (int k = 0; k < kWaves; ++k) {
+        const float c = fw[k] * pow2_whole(mw[k] - mb);
+        o += c * reinterpret_cast<const float*>(tiles + (k0 + k) * stride)[d * G + g];
+        lb += c * lw[k];
     }
+    if constexpr (kLanes == 2) { o = sum_halves(o); lb = sum_halves(lb); }
+    if (lb != lb) mb = 0.f;                                           // NaN, perhaps with no other logit: merges pass over a reference of -infinity
+    if (k0 == 0) put(g, d, o, mb, lb);
 }
 
 // kStep: blocks of a pair that merge
@@ -1168,6 +1175,11 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
 }
 
 constexpr int kDimsPerBlock = 32, kMaxDirectDims = 384;       // kDirectDims: dims of a block, tokens of a call
+// kDirectDims, blocks of 16 waves: pair fastest in the grid, so that the blocks of a pair find their common keys in one L2, and each begins at another quarter of
+// them.  Us a call, 32 query heads on 8: 257 tokens 6.02 -> 5.92 (5.98 without the quarters); with the two lanes an output of block_sums 200 5.45 -> 4.97, 256 5.70 -> 5.22,
+// 257 6.05 -> 5.78, 384 6.86 -> 6.34; 64 on 8: 256 6.15 -> 5.82; 32 on 32: 256 5.57 -> 5.37.  Fewer waves, heads first: 8 on 8, 64 tokens 3.03 -> 3.15, 128 3.54 -> 3.70; 32
+// on 32, 64 tokens 3.57 -> 3.25.
+template <int MODE, int CHUNK> constexpr bool kPairFirst = MODE == kDirectDims && CHUNK / 16 >= kBlockWaves;
 // ceil(n / d) with `per` = 2^32 / d rounded up; exact while n + d <= 2^32 / d
 __device__ __forceinline__ int32_t ceil_div(int32_t n, int32_t d, uint32_t per) { return (int32_t)__umulhi((uint32_t)(n + d - 1), per); }
 
@@ -1206,9 +1218,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     // kStep: a one-dimensional grid, pair fastest, so that the hardware's round-robin of consecutive blocks over the XCDs
     // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
     const int n_pairs = a.v.B * a.Hkv;
-    const int bh = kStepping ? (int)(blockIdx.x % (unsigned)n_pairs) : (int)blockIdx.y;
+    const int bh = kStepping ? (int)(blockIdx.x % (unsigned)n_pairs) : kPairFirst<MODE, CHUNK> ? (int)blockIdx.x : (int)blockIdx.y;
     const int split = kStepping ? (int)(blockIdx.x / (unsigned)n_pairs) : MODE == kDirectDims ? 0 : (int)blockIdx.x;
-    const int dim0 = MODE == kDirectDims ? (int)blockIdx.x * kDims : 0;        // first of the block's dims
+    const int dim0 = MODE == kDirectDims ? (int)(kPairFirst<MODE, CHUNK> ? blockIdx.y : blockIdx.x) * kDims : 0;        // first of the block's dims
     const int b = bh / a.Hkv, h = bh % a.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int t16 = lane & 15, qd = lane >> 4;
@@ -1420,7 +1432,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             for (int ps = 0; ps < kPasses; ++ps) {
                 // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
                 // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
-                const int tile = w + kTiles * ps, jj = 16 * tile + t16;
+                const int tile = (kPairFirst<MODE, CHUNK> ? (w + (int)blockIdx.y * (kTiles * kDims / kHeadDim)) % kTiles : w) + kTiles * ps, jj = 16 * tile + t16;
                 if (ps > 0 && 16 * tile >= cnt) {                     // (wave-uniform) no second tile
                     vm[ps] = 0;
 #pragma unroll
@@ -2020,7 +2032,8 @@ static hipError_t launch_select_attend_stream_g(Ctx* c, const AttArgs& a) {
 
 template <int EB, int MODE, int CHUNK>
 static hipError_t launch_attend_g(Ctx* c, const AttArgs& a, int32_t n_splits) {
-    const dim3 grid(n_splits, a.v.B * c->d.n_kv_heads), block(kBlockThreads);
+    const int pairs = a.v.B * c->d.n_kv_heads;
+    const dim3 grid = kPairFirst<MODE, CHUNK> ? dim3(pairs, n_splits) : dim3(n_splits, pairs), block(kBlockThreads);
     switch (c->G) {
         case 1: hipLaunchKernelGGL((attend_kernel<EB, 1, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
         case 2: hipLaunchKernelGGL((attend_kernel<EB, 2, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
@@ -2050,8 +2063,8 @@ hipError_t launch_attend(Ctx* c, const void* q, const void* K_sel, const void* V
     a.n_tok = n_tok; a.row_stride = row_stride;
     // bf16, up to 384 tokens of few heads: blocks that take all tokens and a quarter of the dims each (kDirectDims), so that nothing is merged and
     // a compute unit, which gets its rows at about 34 bytes a nanosecond, reads the keys and a quarter of the values.  Us per call, 4 query heads
-    // per KV head, before / now: 64 tokens 3.9 / 3.2, 128: 4.31 / 3.94, 256 (one block) 6.2 / 5.5, 257 (three blocks and a merge) 6.8 / 6.0, 384:
-    // 6.9 / 6.6, 512: 7.1 / 7.6; 8 query heads, 128: 5.2 / 4.2, 257: 7.8 / 6.4; one query head, 64: 3.5 / 3.1, 257: 6.0 / 5.9, 384: 6.1 / 6.5; halves of the
+    // per KV head, before / now: 64 tokens 3.9 / 3.2, 128: 4.31 / 3.94, 256 (one block) 6.2 / 5.2, 257 (three blocks and a merge) 6.8 / 5.8, 384:
+    // 6.9 / 6.3, 512: 7.1 / 7.6; 8 query heads, 128: 5.2 / 4.2, 257: 7.8 / 6.4; one query head, 64: 3.5 / 3.1, 257: 6.0 / 5.9, 384: 6.1 / 6.5; halves of the
     // dims, 257 tokens: 6.6.
     constexpr int parts = kHeadDim / kDimsPerBlock;
     if (c->d.kv_dtype == SKV_BF16 && budget <= (c->G > 1 ? kMaxDirectDims : kAttChunkWide) && v.B * c->d.n_kv_heads * parts <= c->n_cu) {

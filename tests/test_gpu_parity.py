@@ -892,6 +892,28 @@ def test_attend_blocks_of_dims(U, oracle32, budget, Hq):
     _same_as_oracle(lse.cpu().numpy(), l_ref, ATT_TOL["bf16"], (budget, Hq))
 
 
+@pytest.mark.parametrize("H, G", [(1, 8), (3, 4), (5, 2), (13, 1), (16, 8)])
+@pytest.mark.parametrize("budget", [40, 128, 200, 300])
+def test_attend_blocks_of_dims_of_any_number_of_heads(U, H, G, budget):
+    """The grid runs over the KV heads first and a block's waves begin at a tile that depends on its dims: numbers of heads that are no multiple of
+    the chip's dies, 4, 8 and 16 waves, a second tile for some.  Against float64; a weight is rounded to bf16 (2^-9 of it) and the normaliser sums
+    the rounded ones, so an output is off by at most 2^-8 of sum w |v|, and a little for fp32 sums."""
+    wl = gen.CFG0.scaled(dtype="bf16", n_q_heads=H * G, n_kv_heads=H)
+    D = wl.head_dim
+    g = torch.Generator().manual_seed(100 * H + budget)
+    q, K, V = (torch.randn(*n, D, generator=g).to(torch.bfloat16) for n in ((H * G,), (H, budget), (H, budget)))
+    n_tok = [budget - 7 * (h % 5) for h in range(H)]
+    out, lse = torch.full((H * G, D), 7.0, device=U.DEV), torch.full((H * G,), 7.0, device=U.DEV)
+    _say("attend, blocks of dims", H, G, budget)
+    U.make_ctx(wl, 4096, 64, budget).attend(q.to(U.DEV), K.to(U.DEV), V.to(U.DEV), U.i32(n_tok), budget, out, lse)
+    torch.cuda.synchronize()
+    for h, n in enumerate(n_tok):
+        logit = q[h * G:(h + 1) * G].double() @ K[h, :n].double().T / D ** 0.5
+        p, v = torch.softmax(logit, 1), V[h, :n].double()
+        assert ((out[h * G:(h + 1) * G].cpu() - p @ v).abs() <= 2.0 ** -8 * (p @ v.abs()) + 1e-5).all(), h
+        assert ((lse[h * G:(h + 1) * G].cpu() - torch.logsumexp(logit, 1)).abs() <= 2.0 ** -8).all(), h
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("budget", [17, 129, 257, 1025])
 def test_attend_carries_values_that_are_not_finite(U, oracle32, dtype, budget):
