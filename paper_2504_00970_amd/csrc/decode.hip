@@ -1174,7 +1174,7 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
     return POOL ? ld_stream(p) : *reinterpret_cast<const uint4*>(p);
 }
 
-constexpr int kDimsPerBlock = 32, kMaxDirectDims = 384;       // kDirectDims: dims of a block, tokens of a call
+constexpr int kDimsPerBlock = 32, kMaxDirectDims = 416, kMaxDirectDims1 = 320;       // kDirectDims: dims of a block, tokens of a call (of one query head per KV head)
 // kDirectDims, blocks of 16 waves: pair fastest in the grid, so that the blocks of a pair find their common keys in one L2, and each begins at another quarter of
 // them.  Us a call, 32 query heads on 8: 257 tokens 6.02 -> 5.92 (5.98 without the quarters); with the two lanes an output of block_sums 200 5.45 -> 4.97, 256 5.70 -> 5.22,
 // 257 6.05 -> 5.78, 384 6.86 -> 6.34; 64 on 8: 256 6.15 -> 5.82; 32 on 32: 256 5.57 -> 5.37.  Fewer waves, heads first: 8 on 8, 64 tokens 3.03 -> 3.15, 128 3.54 -> 3.70; 32
@@ -2061,13 +2061,14 @@ hipError_t launch_attend(Ctx* c, const void* q, const void* K_sel, const void* V
                          const int32_t* n_tok, int32_t budget, const SeqView& v, float* out, float* lse) {
     AttArgs a = att_common(c, q, K_sel, V_sel, v, out, lse);
     a.n_tok = n_tok; a.row_stride = row_stride;
-    // bf16, up to 384 tokens of few heads: blocks that take all tokens and a quarter of the dims each (kDirectDims), so that nothing is merged and
+    // bf16, up to 416 tokens (one query head per KV head: 320) of few heads: blocks that take all tokens and a quarter of the dims each (kDirectDims), so that nothing is merged and
     // a compute unit, which gets its rows at about 34 bytes a nanosecond, reads the keys and a quarter of the values.  Us per call, 4 query heads
     // per KV head, before / now: 64 tokens 3.9 / 3.2, 128: 4.31 / 3.94, 256 (one block) 6.2 / 5.2, 257 (three blocks and a merge) 6.8 / 5.8, 384:
-    // 6.9 / 6.3, 512: 7.1 / 7.6; 8 query heads, 128: 5.2 / 4.2, 257: 7.8 / 6.4; one query head, 64: 3.5 / 3.1, 257: 6.0 / 5.9, 384: 6.1 / 6.5; halves of the
-    // dims, 257 tokens: 6.6.
+    // 6.9 / 6.3; 8 query heads, 128: 5.2 / 4.2, 257: 7.8 / 6.4; one query head, 64: 3.5 / 3.1; halves of the dims, 257 tokens: 6.6.  Around the lines, blocks of tokens /
+    // of dims, 400 tokens: 32 heads on 8 7.15 / 6.57, 64 on 8 8.06 / 7.17, 12 on 3 6.84 / 6.77; 448: 7.13 / 6.92, 8.00 / 7.54, 6.82 / 6.97; 512: 7.35 / 7.53, 8.19 / 8.23,
+    // 6.88 / 7.47; 8 heads on 8, 32 on 32, 320 tokens: 5.97 / 5.82, 6.69 / 6.30; 352: 6.00 / 6.07, 6.78 / 6.57; 400: 6.14 / 6.46, 6.79 / 6.89.
     constexpr int parts = kHeadDim / kDimsPerBlock;
-    if (c->d.kv_dtype == SKV_BF16 && budget <= (c->G > 1 ? kMaxDirectDims : kAttChunkWide) && v.B * c->d.n_kv_heads * parts <= c->n_cu) {
+    if (c->d.kv_dtype == SKV_BF16 && budget <= (c->G > 1 ? kMaxDirectDims : kMaxDirectDims1) && v.B * c->d.n_kv_heads * parts <= c->n_cu) {
         if (budget <= kAttChunk) return launch_attend_g<2, kDirectDims, kAttChunk>(c, a, parts);
         if (budget <= kAttChunkMid) return launch_attend_g<2, kDirectDims, kAttChunkMid>(c, a, parts);
         if (budget <= kAttChunkWide) return launch_attend_g<2, kDirectDims, kAttChunkWide>(c, a, parts);

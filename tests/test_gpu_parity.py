@@ -874,8 +874,8 @@ NOT_FINITE = ["query", "all queries", "key", "infinite key", "value"]
 @pytest.mark.parametrize("Hq", [8, 16, 32, 64])
 @pytest.mark.parametrize("budget", [1, 16, 17, 64, 65, 128, 129, 256, 257, 272, 273, 384, 385])
 def test_attend_blocks_of_dims(U, oracle32, budget, Hq):
-    """bf16 calls of up to 384 tokens: a block takes all tokens and 32 dims.  Full and shorter token counts, none at all, edges of tiles, of
-    blocks and of the second tiles, and the first size that goes back to blocks of tokens."""
+    """bf16 calls of a few hundred tokens: a block takes all tokens and 32 dims.  Full and shorter token counts, none at all, edges of tiles, of
+    blocks and of the second tiles."""
     wl = gen.CFG0.scaled(dtype="bf16", n_q_heads=Hq)
     H, D = wl.n_kv_heads, wl.head_dim
     g = torch.Generator(device=U.DEV)
@@ -893,10 +893,10 @@ def test_attend_blocks_of_dims(U, oracle32, budget, Hq):
 
 
 @pytest.mark.parametrize("H, G", [(1, 8), (3, 4), (5, 2), (13, 1), (16, 8)])
-@pytest.mark.parametrize("budget", [40, 128, 200, 300])
+@pytest.mark.parametrize("budget", [40, 128, 200, 300, 320, 321, 416, 417])
 def test_attend_blocks_of_dims_of_any_number_of_heads(U, H, G, budget):
     """The grid runs over the KV heads first and a block's waves begin at a tile that depends on its dims: numbers of heads that are no multiple of
-    the chip's dies, 4, 8 and 16 waves, a second tile for some.  Against float64; a weight is rounded to bf16 (2^-9 of it) and the normaliser sums
+    the chip's dies, 4, 8 and 16 waves, a second tile for some, the largest calls (320 tokens with one query head per KV head, else 416) and the next.  Against float64; a weight is rounded to bf16 (2^-9 of it) and the normaliser sums
     the rounded ones, so an output is off by at most 2^-8 of sum w |v|, and a little for fp32 sums."""
     wl = gen.CFG0.scaled(dtype="bf16", n_q_heads=H * G, n_kv_heads=H)
     D = wl.head_dim
