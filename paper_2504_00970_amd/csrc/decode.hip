@@ -951,6 +951,8 @@ __device__ __forceinline__ float sum_quads(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// of the lane l ^ 8
+__device__ __forceinline__ float other_eight(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128 /* row_ror:8 */, 0xf, 0xf, false)); }
 // the larger of the lanes l and l ^ 32, in both
 __device__ __forceinline__ float max_halves(float x) {
     const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -1210,10 +1212,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     constexpr int kShBytes = max_of(max_of(kTiles * kTileBytes, kSelBytes + kKeyBytes), kStepping ? 0 : 16 * kBlockThreads);
     __shared__ __attribute__((aligned(16))) char sm[kShBytes];
     __shared__ WaveSums<kTiles> sm_waves;
-    __shared__ int sm_last;
+    __shared__ int sm_last;                                                 // kStep: set by a thread of the merge whose wait ran out
     __shared__ float sm_norm[kStepping ? 2 * G : 1];                        // kStep: (reference, normaliser) of the block's heads
     __shared__ int32_t sm_row[CHUNK];
-    __shared__ float sm_merge[kStepping ? 3 * kBlockThreads : 1];           // kStep: the merging block's scratch
+    constexpr int kMergeWords = kStepping ? 3 * (kBlockThreads + kWave) : 1;
+    __shared__ float sm_merge[kMergeWords];                                   // kStep: the merging block's scratch
 
     // kStep: a one-dimensional grid, pair fastest, so that the hardware's round-robin of consecutive blocks over the XCDs
     // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
@@ -1305,6 +1308,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             if (split > 0 && j0 >= budget) return;                // n <= budget: nothing for this split
         }
         if (tid < CHUNK) sm_row[tid] = -1;
+        if (kStepping && tid == 0) sm_last = 0;
         int32_t nsel, ntok;
         // Each selected bucket that reaches into this block's positions marks, in every 64-position piece it touches,
         // where it starts there and which pool row that is; the waves then fill the positions in between.
@@ -1582,51 +1586,52 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             }
         }
         SKV_T(10);
-        // (o, M, L) per thread: 3 x 1024 floats; a thread whose wait ran out leaves NaN as its maximum
-        float* scratch = sm_merge;
-        scratch[tid] = o; scratch[kBlockThreads + tid] = ok ? M : __builtin_nanf(""); scratch[2 * kBlockThreads + tid] = L;
-        __syncthreads();
-        SKV_T(11);
-        // `share` threads for a column, eight groups (or all four) each
-        const int lg_share = max(a.lg_merge, 0), share = 1 << lg_share;
-        bool bad = false;
-        if (tid < (share << lg_dims)) {
-            constexpr int kGroups8 = 8;
-            const int col = tid >> lg_share, first = (tid & (share - 1)) * kGroups8;
-            float mg[kGroups8], lg[kGroups8], og[kGroups8];
-            float Mx = -INFINITY;
-#pragma unroll
-            for (int gg = 0; gg < kGroups8; ++gg) {
-                const int i = (min(first + gg, groups - 1) << lg_dims) + col;
-                og[gg] = scratch[i];
-                mg[gg] = first + gg < groups ? scratch[kBlockThreads + i] : -INFINITY;
-                lg[gg] = scratch[2 * kBlockThreads + i];
-                bad = bad || mg[gg] != mg[gg];
-                Mx = fmaxf(Mx, mg[gg]);
+        // The groups meet in LDS, where every column's are taken by lanes of one wave, two groups each, that fold them with exchanges in registers; 32 columns: the
+        // two groups of a wave meet before that.  (LDS rows have a pitch that lets these lanes read from different banks.)  One to four lanes a column, eight groups each,
+        // and exchanges through LDS / this, us per layer: 8192 tokens, budget 1000, 10.82 / 10.48, 32768 (2048) 11.9 / 11.75, 131072 16.9 / 16.5, fp32 32768 14.3 / 14.0.
+        if (!ok) { M = __builtin_nanf(""); sm_last = 1; }                     // a thread whose wait ran out
+        auto finish = [&](auto lg) {
+            constexpr int kCols = 1 << decltype(lg)::value, kHalves = kCols < kWave ? 2 : 1, kRows = kBlockThreads / kCols / kHalves;
+            constexpr int kLanes = kRows / 2, kPitch = kCols + 32 / kLanes, kPlane = kRows * kPitch, kPer = kWave / kLanes;      // lanes of a column; columns of a wave
+            static_assert(3 * kPlane <= kMergeWords && kLanes * kCols <= kBlockThreads, "");
+            if constexpr (kHalves == 2) {
+                const float nm = max_halves(M), c = pow2_whole(M - nm);
+                o = sum_halves(o * c);
+                L = sum_halves(L * c);
+                M = nm;
             }
-            for (int k = 1; k < share; k <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, k));
-            float Ls = 0.f, os = 0.f;
-#pragma unroll
-            for (int gg = 0; gg < kGroups8; ++gg) {
-                const float c = pow2_whole(mg[gg] - Mx);
-                Ls += c * lg[gg];
-                os += c * og[gg];
+            if (kHalves == 1 || lane < kCols) {
+                float* dst = sm_merge + (kHalves == 2 ? w : grp) * kPitch + (tid & (kCols - 1));
+                dst[0] = o; dst[kPlane] = M; dst[2 * kPlane] = L;
             }
-            for (int k = 1; k < share; k <<= 1) {
-                Ls += __shfl_xor(Ls, k);
-                os += __shfl_xor(os, k);
-                bad = bad || __shfl_xor(bad ? 1 : 0, k) != 0;
-            }
-            if (first == 0) {                                             // the first of the column's threads
+            __syncthreads();
+            SKV_T(11);
+            if (w >= kCols / kPer) return;
+            const int col = w * kPer + lane % kPer, part = lane / kPer;
+            const float* src = sm_merge + 2 * part * kPitch + col;
+            const float o0 = src[0], o1 = src[kPitch], m0 = src[kPlane], m1 = src[kPlane + kPitch], l0 = src[2 * kPlane], l1 = src[2 * kPlane + kPitch];
+            float Mx = fmaxf(m0, m1);
+            if constexpr (kLanes == 8) Mx = fmaxf(Mx, other_eight(Mx));
+            if constexpr (kLanes >= 4) Mx = max_quads(Mx);
+            else Mx = max_halves(Mx);
+            const float c0 = pow2_whole(m0 - Mx), c1 = pow2_whole(m1 - Mx);
+            float Ls = c0 * l0 + c1 * l1, os = c0 * o0 + c1 * o1;
+            if constexpr (kLanes == 8) { Ls += other_eight(Ls); os += other_eight(os); }
+            if constexpr (kLanes >= 4) { Ls = sum_quads(Ls); os = sum_quads(os); }
+            else { Ls = sum_halves(Ls); os = sum_halves(os); }
+            const bool bad = sm_last != 0;                                    // a wait of this launch ran out
+            if (part == 0) {
                 const int to = at_of(col);
-                const bool empty = Ls == 0.f;                           // every retrieved position was out of range
-                float res = empty ? 0.f : os / Ls;
-                if (bad) res = __builtin_nanf("");                        // a wait of this launch ran out
-                a.out[qhead0 * kHeadDim + to] = res;
+                const bool empty = Ls == 0.f;                               // every retrieved position was out of range
+                a.out[qhead0 * kHeadDim + to] = bad ? __builtin_nanf("") : empty ? 0.f : os / Ls;
                 if (a.lse && to % kHeadDim == 0) a.lse[qhead0 + to / kHeadDim] = empty ? -INFINITY : (Mx + log2f(Ls)) * kLn2;
-                if (bad) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
             }
-        }
+            if (bad && tid == 0) { st_agent(a.err_dev, 1u); if (a.err_host) st_agent(a.err_host, 1u); }
+        };
+        if (lg_dims == 5) finish(std::integral_constant<int, 5>{});
+        else if (lg_dims == 6) finish(std::integral_constant<int, 6>{});
+        else if (lg_dims == 7) finish(std::integral_constant<int, 7>{});
+        else finish(std::integral_constant<int, 8>{});
         // Block 0 ends the pair's launch by advancing its epoch: its threads have seen the partial of every attending
         // block (the barrier above) and now make sure of the word of every other block that ran the selection; all of
         // them, and through the scores they waited for every scoring block, have read the epoch by then.

@@ -591,6 +591,18 @@ def test_fused_single_launch_shares_of_whole_lines(U, oracle32, B, S, dtype, Hq,
     _fused_case(U, oracle32, wl, seed=81, layers=[0], sv_dtype=sv_dtype)
 
 
+# dims of a query head that a block merges (256: of two heads): 256, 128, 64 and 32, from the fewest to the most partial results of each
+@pytest.mark.parametrize("Hq,budget", [(64, 250), (64, 448), (64, 512), (64, 960), (64, 1024), (64, 1984), (64, 2048), (32, 1024), (32, 2000), (16, 128), (16, 200), (8, 64), (8, 128),
+                                       (8, 200), (8, 2048)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_fused_single_launch_merges_of_every_width(U, oracle32, Hq, budget, dtype):
+    """A column's partial results meet in registers, two to a lane of 2, 4 or 8; a merging block takes 32 to 256 columns.  Some of the blocks hold no token (a short
+    sequence), which leaves groups without a partial result."""
+    for seed, tokens in ((82, 4100), (83, max(budget // 3, 20))):
+        wl = gen.CFG1.scaled(n_layers=1, n_q_heads=Hq, batch=1, t_range=(tokens, tokens), budgets=(budget,), dtype=dtype)
+        _fused_case(U, oracle32, wl, seed=seed, layers=[0])
+
+
 @pytest.mark.parametrize("B,budget,Hq", [(8, 1025, 32), (8, 1040, 8), (12, 1500, 64), (12, 2048, 16), (20, 1500, 32), (20, 2049, 64)])
 def test_fused_batch_streaming_fp32(U, oracle32, B, budget, Hq):
     """fp32 pools in the streaming kernel's 512-, 1024- and 2048-token blocks (B = 8, 12, 20 with budget 1500), a last tile of one token and of
