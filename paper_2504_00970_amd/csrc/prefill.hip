@@ -389,7 +389,10 @@ __global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const c
 
 // Short buckets (a retained pool keeps a few tokens of each): the row's LPR lanes own a bucket, RPW buckets per wave, and walk
 // its rows; no sum across lanes, and the table's rows are stored RPW at a time.  A wave per bucket is bound by the number of
-// waves here: 32 x 8 x 4096 retained tokens in 1654 buckets (485 MB), 161-169 us with a wave per bucket, 90 us with this.
+// waves here: 32 x 8 x 4096 retained tokens in 1654 buckets (485 MB), 161-169 us with a wave per bucket, 90 us with this.  The pool has usually just been written by
+// skv_compact_pool: the last heads are read first, while the memory-side cache still holds them, and with non-temporal loads, which leave the others their
+// places.  Compaction and mean keys, first to last / last to first, us: 16 layers x 8 heads x 16384 retained tokens 526 / 511, smaller pools the same; plain /
+// non-temporal loads there 536 / 511, 32 layers x 6000 tokens 371 / 370, x 4096 297 / 286, x 2048 with an E4M3 table 139 / 133, x 1024 119 / 120.
 template <int EB, int SVB>
 __global__ __launch_bounds__(kSemvecShortWaves * kWave) void semvec_short_kernel(const char* __restrict__ K, int32_t T,
                                                                                     const int32_t* __restrict__ sent_off_all,
@@ -398,10 +401,10 @@ __global__ __launch_bounds__(kSemvecShortWaves * kWave) void semvec_short_kernel
     using R = Row<EB>;
     constexpr int kUnroll = 4;
     const int lane = threadIdx.x & 63, cc = lane % R::LPR;
-    const int32_t s = (blockIdx.x * kSemvecShortWaves + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
+    const int32_t s = ((int32_t)(gridDim.x - 1 - blockIdx.x) * kSemvecShortWaves + (threadIdx.x >> 6)) * R::RPW + lane / R::LPR;
     if (s >= S) return;
-    const int64_t lh = blockIdx.y;
-    const int32_t* sent_off = sent_off_all + (int64_t)(blockIdx.y / Hkv) * off_layer_stride;   // the layer's table
+    const int64_t lh = gridDim.y - 1 - blockIdx.y;
+    const int32_t* sent_off = sent_off_all + (int64_t)((gridDim.y - 1 - blockIdx.y) / Hkv) * off_layer_stride;   // the layer's table
     const int32_t b = max(sent_off[s], 0), e = min(sent_off[s + 1], T);   // never read outside the pool
     const char* base = K + (lh * T) * (int64_t)(kHeadDim * EB) + (int64_t)cc * 16;
     float acc[R::EPL];
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(kSemvecShortWaves * kWave) void semvec_short_kernel
         uint4 v[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const uint4 t = *reinterpret_cast<const uint4*>(base + (int64_t)min(x0 + u, e - 1) * (kHeadDim * EB));
+            const uint4 t = ld_stream(base + (int64_t)min(x0 + u, e - 1) * (kHeadDim * EB));
             v[u] = (x0 + u < e) ? t : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll

@@ -1573,7 +1573,11 @@ hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, cons
 
 // ------------------------------------------------------------------------------------------------
 // Pool compaction: K_ret/V_ret [L][Hkv][k][D] = rows keep_idx[l][0 .. n_keep[l]) of K/V [L][Hkv][T][D].
-// Same branch-free copy as the decode-side gather; the kept positions are shared by the heads of a layer.
+// Same branch-free copy as the decode-side gather; the kept positions are shared by the heads of a layer.  The mean keys of the retained tokens
+// are made of K_ret next: values go first and keys last, with plain stores, so that what fits the 256 MB memory-side cache of K_ret is still there.  Us for retention,
+// compaction and mean keys together, keys first and non-temporal / this (and keys of semvec_short_kernel read last to first, non-temporal), 32 layers x 8 bf16 heads,
+// kept of tokens: 1024 of 8192 87.2 / 81.4, 2048 of 4096 129.6 / 120.7, 1024 of 32768 136 / 120.5, 6000 of 16384 395 / 370, 4096 of 32768 295 / 286; 16 layers,
+// 16384 of 65536 526 / 511, fp32 3000 of 20000 219 / 204; keys first with plain stores 32768 310.
 // ------------------------------------------------------------------------------------------------
 template <int EB, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char* __restrict__ Kp, const char* __restrict__ Vp, int32_t T,
@@ -1588,8 +1592,9 @@ __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char
     const int32_t n = min(n_keep[l], k);
     const int32_t j0 = blockIdx.x * kGatherRowsPerBlock;
     if (j0 >= n || T <= 0) return;
-    const char* src = (blockIdx.z == 0 ? Kp : Vp) + (int64_t)lh * T * kRowBytes;
-    char* dst = (blockIdx.z == 0 ? Kr : Vr) + (int64_t)lh * k * kRowBytes;
+    const bool keys = blockIdx.z != 0;                                 // (dispatched last)
+    const char* src = (keys ? Kp : Vp) + (int64_t)lh * T * kRowBytes;
+    char* dst = (keys ? Kr : Vr) + (int64_t)lh * k * kRowBytes;
     const int32_t* keep = keep_all + (int64_t)l * k;
     const int r = threadIdx.x / R::LPR, cc = threadIdx.x % R::LPR;
     int32_t x[kIter];
@@ -1606,14 +1611,14 @@ __global__ __launch_bounds__(kGatherThreads) void compact_pool_kernel(const char
         const int32_t j = j0 + i * kRowsPerIter + r;
         char* p = dst + (int64_t)j * kRowBytes + cc * 16;
         if (j < n && x[i] >= 0 && x[i] < T) {
-            if (STREAM) st_stream(p, val[i]);
+            if (STREAM && !keys) st_stream(p, val[i]);
             else *reinterpret_cast<uint4*>(p) = val[i];
         }
     }
 }
 
-// Non-temporal rows from this many bytes of output on (a smaller retained pool is read again from the caches): 32 layers x 8 heads, the whole
-// retention with plain / non-temporal rows, us: 34 MB 27.5 / 30.5, 67 MB 46.8 / 47.4, 134 MB 83.7 / 77.2, 537 MB 320 / 296.
+// Non-temporal loads and stores of values from this many bytes of output on (a smaller retained pool is read again from the caches): 32 layers x 8 heads, the whole
+// retention, us, all plain / from here on: 134 MB 90.1 / 81.4, 269 MB 126.0 / 120.7, 537 MB 316 / 286; everywhere / from here on: 67 MB 42.0 / 41.7.
 constexpr int64_t kCompactStreamBytes = 96ll << 20;
 hipError_t launch_compact_pool(Ctx* c, const void* K_pool, const void* V_pool, int32_t T, const int32_t* keep_idx, int32_t k,
                                const int32_t* n_keep, void* K_ret, void* V_ret) {

@@ -528,6 +528,37 @@ def test_select_ignores_buckets_without_tokens(U, oracle32, S):
             assert np.all(lens[g_sel[h, :m]] > 0)
 
 
+@pytest.mark.parametrize("dtype,L,k,S", [("bf16", 1, 1, 1), ("bf16", 3, 333, 97), ("bf16", 4, 6203, 2117), ("f32", 2, 5, 33), ("f32", 3, 4111, 1700)])
+def test_compacted_pool_and_its_mean_keys(U, dtype, L, k, S):
+    """Rows and mean keys of pools below and above the 96 MB from which values are stored past the caches, buckets of a few tokens or none, tables that end
+    within a wave's buckets, a block's or at them: every layer and head at its own place."""
+    _say("compacted pool", dtype, L, k, S)
+    H, D, T = 8, 128, k + 1024
+    rng = np.random.default_rng(k)
+    wl = gen.CFG1.scaled(n_layers=L, n_tokens=T, dtype=dtype)
+    ctx = U.make_ctx(wl, T, S, 1)
+    g = torch.Generator(device=U.DEV)
+    g.manual_seed(k)
+    K, V = (torch.empty(L, H, T, D, dtype=wl.torch_dtype, device=U.DEV).normal_(generator=g) for _ in range(2))
+    keep = np.stack([np.sort(rng.choice(T, k, replace=False)) for _ in range(L)]).astype(np.int32)
+    off = np.sort(np.concatenate([np.zeros((L, 1), int), rng.integers(0, k + 1, (L, S - 1)), np.full((L, 1), k)], 1), 1).astype(np.int32)
+    K_ret, V_ret = (torch.zeros(L, H, k, D, dtype=wl.torch_dtype, device=U.DEV) for _ in range(2))
+    table = torch.full((L, H, S, D), 3.0, device=U.DEV)
+    ctx.compact_pool(K, V, T, U.i32(keep), k, U.i32(np.full(L, k)), K_ret, V_ret)
+    ctx.build_semvec_layers(K_ret, U.i32(off), S, table)
+    torch.cuda.synchronize()
+    for l in range(L):
+        rows = torch.as_tensor(keep[l].astype(np.int64), device=U.DEV)
+        assert torch.equal(K_ret[l], K[l].index_select(1, rows)) and torch.equal(V_ret[l], V[l].index_select(1, rows)), l
+        n = np.diff(off[l])
+        to = torch.as_tensor(np.repeat(np.arange(S), n), device=U.DEV)
+        ref = torch.zeros(H, S, D, dtype=torch.float64, device=U.DEV).index_add_(1, to, K_ret[l].double())
+        size = torch.zeros_like(ref).index_add_(1, to, K_ret[l].double().abs())
+        n = torch.as_tensor(np.maximum(n, 1), device=U.DEV).view(1, S, 1)
+        # n additions and a division in fp32: at most n half units in the last place of the sum of magnitudes
+        assert bool(((table[l].double() - ref / n).abs() <= (n + 1) * 2.0 ** -24 * size / n).all()), l
+
+
 @pytest.mark.parametrize("dtype,T,N,k,budget", [("bf16", 6000, 32, 1024, 512), ("f32", 2500, 16, 600, 256)])
 def test_retention_pipeline_then_decode(U, oracle32, dtype, T, N, k, budget):
     """segment -> importance -> retain -> compact -> mean keys of the retained tokens -> fused decode step on the
