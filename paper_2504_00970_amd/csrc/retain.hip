@@ -1260,7 +1260,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
 }
 
 // ------------------------------------------------------------------------------------------------
-// Retention of long prompts: the same in four launches of several blocks per layer, 8192 tokens each.  One block per layer reads
+// Retention of long prompts: the same in four launches of several blocks per layer, 8192 or 4096 tokens each.  One block per layer reads
 // its tokens' importances five times at what one compute unit gets, from 32769 tokens on from memory.
 //   digit:      counts by the top 11 bits of the key; the layer's last block finds the digit that holds the cut; once more with the next 11 bits
 //               where too many tokens share that digit;
@@ -1269,10 +1269,11 @@ __global__ __launch_bounds__(kBlockThreads) void retain_kernel(const float* __re
 //               it, and the kept tokens before every block;
 //   compact:    kept positions, ret_off at the first token of every bucket (the kept tokens before it), ret_len by the layer's last block.
 // Bound by latency: an arrival and the last block's block scans in each launch, 5 to 8 us apiece (2 where the second digit is not needed).  Us per call, one
-// block a layer / this, importances spread over 2^+-6 and, in brackets, within 10 %: 32 layers x 16500 tokens 21.2 / 22.7 (26.7 / 28.0), 20000 22.5 /
+// block a layer / this with 8192 tokens a block, importances spread over 2^+-6 and, in brackets, within 10 %: 32 layers x 16500 tokens 21.2 / 22.7 (26.7 / 28.0), 20000 22.5 /
 // 22.6 (29.3 / 28.1), the line, 32768 27.6 / 24.5 (38.9 / 29.6), 16 x 65536 68 / 26 (87 / 32), 8 x 131072 127 / 27 (166 / 31).
 // ------------------------------------------------------------------------------------------------
-constexpr int kRetTok = 8, kRetChunk = kRetTok * kBlockThreads;      // tokens of a thread, of a block
+template <int TOK> constexpr int kRetChunk = TOK * kBlockThreads;       // tokens of a block, TOK of each thread
+constexpr int kRetTok = 8, kRetTokFew = 4, kRetFewTok = 65536;          // tokens of a thread, of one of a layer of up to kRetFewTok tokens
 struct RetainWork {
     unsigned int* hist;           // [L][2048], zero between calls
     unsigned long long* list;     // [L][kRetList] (key, position)
@@ -1283,17 +1284,17 @@ struct RetainWork {
 };
 
 // this wave's tokens of its block, i0 + 64 j, and their keys (0 past the end)
-struct RetainTokens {
+template <int TOK> struct RetainTokens {
     int32_t i0;
-    uint32_t key[kRetTok];
+    uint32_t key[TOK];
     __device__ __forceinline__ RetainTokens(const float* __restrict__ alpha, int32_t Tp) {
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        i0 = blockIdx.x * kRetChunk + w * (kRetTok * kWave) + lane;
-        float x[kRetTok];
+        i0 = blockIdx.x * kRetChunk<TOK> + w * (TOK * kWave) + lane;
+        float x[TOK];
 #pragma unroll
-        for (int j = 0; j < kRetTok; ++j) x[j] = alpha[min(i0 + j * kWave, Tp - 1)];
+        for (int j = 0; j < TOK; ++j) x[j] = alpha[min(i0 + j * kWave, Tp - 1)];
 #pragma unroll
-        for (int j = 0; j < kRetTok; ++j) key[j] = score_key(x[j]);
+        for (int j = 0; j < TOK; ++j) key[j] = score_key(x[j]);
     }
 };
 // true in the block of the layer that arrives last (all of the layer's stores before it are visible to it)
@@ -1320,7 +1321,7 @@ __device__ __forceinline__ void retain_cross(int nbins, uint32_t need, Count cou
 
 // SECOND: the 11 bits behind the first digit, where more tokens share it than the list takes (importances of like tokens: 32768 tokens in three or four
 // digits); else nothing.
-template <bool SECOND>
+template <bool SECOND, int TOK>
 __global__ __launch_bounds__(kBlockThreads) void retain_digit_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
     __shared__ uint32_t hist[2048], wave_tot[kBlockWaves];
     __shared__ int32_t res[3];
@@ -1329,11 +1330,11 @@ __global__ __launch_bounds__(kBlockThreads) void retain_digit_kernel(const float
     int32_t* cut = wk.cut + 4 * l;
     const int32_t digit = SECOND ? ld_agent(cut) : 0, above = SECOND ? ld_agent(cut + 1) : 0;
     if (SECOND && ld_agent(cut + 3) <= kRetList) return;
-    const RetainTokens t(alpha_all + (int64_t)l * Tp, Tp);
+    const RetainTokens<TOK> t(alpha_all + (int64_t)l * Tp, Tp);
     for (int i = tid; i < 2048; i += kBlockThreads) hist[i] = 0;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j)
+    for (int j = 0; j < TOK; ++j)
         if (t.i0 + j * kWave < Tp && (!SECOND || (int32_t)(t.key[j] >> 21) == digit)) atomicAdd(&hist[SECOND ? (t.key[j] >> 10) & 2047u : t.key[j] >> 21], 1u);
     __syncthreads();
     unsigned int* all = wk.hist + (int64_t)l * 2048;
@@ -1350,6 +1351,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_digit_kernel(const float
     for (int i = tid; i < 2048; i += kBlockThreads) st_agent(all + i, 0u);
 }
 
+template <int TOK>
 __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k, RetainWork wk) {
     __shared__ uint32_t hist[2048], wave_tot[2][kBlockWaves], before[kRetMaxChunks];
     __shared__ int32_t equal[kRetList];
@@ -1360,11 +1362,11 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
     const float* alpha = alpha_all + (int64_t)l * Tp;
     const uint32_t digit = (uint32_t)ld_agent(wk.cut + 4 * l), above = (uint32_t)ld_agent(wk.cut + 4 * l + 1);
     const int open = ld_agent(wk.cut + 4 * l + 2);                     // bits of the key behind the digits
-    const RetainTokens t(alpha, Tp);
+    const RetainTokens<TOK> t(alpha, Tp);
     auto lower = [&](unsigned long long m) { return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
     uint32_t n_above = 0, n_cand = 0;
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
         const bool exists = t.i0 + j * kWave < Tp;
         n_above += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> open) > digit));
         n_cand += (uint32_t)__popcll(__ballot(exists && (t.key[j] >> open) == digit));
@@ -1381,7 +1383,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
     at += sm_base;
     unsigned long long* list = wk.list + (int64_t)l * kRetList;
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
         const bool cand = t.i0 + j * kWave < Tp && (t.key[j] >> open) == digit;
         const unsigned long long m = __ballot(cand);
         const uint32_t to = at + lower(m);
@@ -1446,7 +1448,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
                     if (rank == need - 1) tie = equal[tid];
                 }
             } else {
-                static_assert((int64_t)kRetMaxChunks * kRetChunk <= 1 << 20, "20 bits of a position");
+                static_assert((int64_t)kRetMaxChunks * kRetChunk<kRetTok> <= 1 << 20, "20 bits of a position");
                 constexpr uint32_t kLast = (1u << 20) - 1u;
                 uint32_t lead = 0, left = need;
 #pragma unroll
@@ -1479,13 +1481,13 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
         __syncthreads();
     }
     if (fits) {
-        for_candidates([&](uint32_t key, int32_t i) { if (key > prefix || (key == prefix && i <= tie)) atomicAdd(&before[i / kRetChunk], 1u); });
+        for_candidates([&](uint32_t key, int32_t i) { if (key > prefix || (key == prefix && i <= tie)) atomicAdd(&before[i / kRetChunk<TOK>], 1u); });
     } else {
         for (int32_t g = 0; g < Tp; g += kBlockThreads) {
             const int32_t i = g + tid;
             const uint32_t key = score_key(alpha[min(i, Tp - 1)]);
             const unsigned long long m = __ballot(i < Tp && (key > prefix || (key == prefix && i <= tie)));
-            if (lane == 0 && m != 0) atomicAdd(&before[(g + w * kWave) / kRetChunk], (uint32_t)__popcll(m));
+            if (lane == 0 && m != 0) atomicAdd(&before[(g + w * kWave) / kRetChunk<TOK>], (uint32_t)__popcll(m));
         }
     }
     __syncthreads();
@@ -1503,6 +1505,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_candidates_kernel(const 
     }
 }
 
+template <int TOK>
 __global__ __launch_bounds__(kBlockThreads) void retain_compact_kernel(const float* __restrict__ alpha_all, int32_t Tp, int32_t k,
                                                                        const int32_t* __restrict__ seg_id, int32_t S, int32_t* __restrict__ keep_all,
                                                                        int32_t keep_stride, int32_t* __restrict__ n_keep, int32_t* ret_off_all,
@@ -1515,18 +1518,18 @@ __global__ __launch_bounds__(kBlockThreads) void retain_compact_kernel(const flo
     const int32_t need = min(k, Tp);
     const uint32_t cut = (uint32_t)wk.cut[4 * l + 2];
     const int32_t tie = wk.cut[4 * l + 3];
-    const RetainTokens t(alpha_all + (int64_t)l * Tp, Tp);
-    int32_t cur[kRetTok], prev[kRetTok];
+    const RetainTokens<TOK> t(alpha_all + (int64_t)l * Tp, Tp);
+    int32_t cur[TOK], prev[TOK];
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
         const int32_t i = min(t.i0 + j * kWave, Tp - 1);
         cur[j] = seg_id[i];
         prev[j] = seg_id[max(i - 1, 0)];
     }
-    unsigned long long kept[kRetTok];
+    unsigned long long kept[TOK];
     uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
         const int32_t i = t.i0 + j * kWave;
         kept[j] = __ballot(i < Tp && (t.key[j] > cut || (t.key[j] == cut && i <= tie)));
         mine += (uint32_t)__popcll(kept[j]);
@@ -1535,7 +1538,7 @@ __global__ __launch_bounds__(kBlockThreads) void retain_compact_kernel(const flo
     uint32_t pos = block_scan_u32(lane == 0 ? mine : 0u, wave_tot, &total) - mine;
     pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)wk.chunk[(int64_t)l * kRetMaxChunks + blockIdx.x];
 #pragma unroll
-    for (int j = 0; j < kRetTok; ++j) {
+    for (int j = 0; j < TOK; ++j) {
         const int32_t i = t.i0 + j * kWave;
         const uint32_t at = pos + (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept[j], 0u));
         if ((kept[j] >> lane) & 1ull) keep[at] = i;
@@ -1552,16 +1555,29 @@ __global__ __launch_bounds__(kBlockThreads) void retain_compact_kernel(const flo
     for (int s = tid; s < S; s += kBlockThreads) ret_len_all[(int64_t)l * S + s] = ld_agent(ret_off + s + 1) - ld_agent(ret_off + s);
 }
 
+template <int TOK>
+static void launch_retain_long(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
+                               int32_t* n_keep, int32_t* ret_off, int32_t* ret_len) {
+    static_assert((kRetFewTok + kRetChunk<kRetTokFew> - 1) / kRetChunk<kRetTokFew> <= kRetMaxChunks, "");
+    const RetainWork wk = {c->ret_hist, c->ret_list, c->ret_count, c->ret_cut, c->ret_chunk};
+    const dim3 chunks((Tp + kRetChunk<TOK> - 1) / kRetChunk<TOK>, c->d.n_layers), block(kBlockThreads);
+    hipLaunchKernelGGL((retain_digit_kernel<false, TOK>), chunks, block, 0, c->stream, alpha, Tp, k, wk);
+    hipLaunchKernelGGL((retain_digit_kernel<true, TOK>), chunks, block, 0, c->stream, alpha, Tp, k, wk);
+    hipLaunchKernelGGL(retain_candidates_kernel<TOK>, chunks, block, 0, c->stream, alpha, Tp, k, wk);
+    hipLaunchKernelGGL(retain_compact_kernel<TOK>, chunks, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len, wk);
+}
+
 hipError_t launch_retain(Ctx* c, const float* alpha, int32_t Tp, int32_t k, const int32_t* seg_id, int32_t S, int32_t* keep_idx,
                          int32_t* n_keep, int32_t* ret_off, int32_t* ret_len) {
     const dim3 grid(c->d.n_layers), block(kBlockThreads);
-    if (k > 0 && c->ret_hist && Tp > kRetainLongTok && (Tp + kRetChunk - 1) / kRetChunk <= kRetMaxChunks) {
-        const RetainWork wk = {c->ret_hist, c->ret_list, c->ret_count, c->ret_cut, c->ret_chunk};
-        const dim3 chunks((Tp + kRetChunk - 1) / kRetChunk, c->d.n_layers);
-        hipLaunchKernelGGL(retain_digit_kernel<false>, chunks, block, 0, c->stream, alpha, Tp, k, wk);
-        hipLaunchKernelGGL(retain_digit_kernel<true>, chunks, block, 0, c->stream, alpha, Tp, k, wk);
-        hipLaunchKernelGGL(retain_candidates_kernel, chunks, block, 0, c->stream, alpha, Tp, k, wk);
-        hipLaunchKernelGGL(retain_compact_kernel, chunks, block, 0, c->stream, alpha, Tp, k, seg_id, S, keep_idx, max(k, 1), n_keep, ret_off, ret_len, wk);
+    if (k > 0 && c->ret_hist && Tp > kRetainLongTok && (Tp + kRetChunk<kRetTok> - 1) / kRetChunk<kRetTok> <= kRetMaxChunks) {
+        // Shorter blocks for few tokens, as long as the chip holds them all at once.  Us per call, 8192 / 4096 tokens a block, importances spread over 2^+-6 and, in
+        // brackets, within 10 %: 32 layers x 20500 tokens 22.3 / 20.2 (30.8 / 26.1), 32768 23.0 / 21.0 (31.6 / 27.3), 2 x 65536 22.0 / 20.1 (30.1 / 25.0), 16 x 65536
+        // 24.4 / 23.8 (32.6 / 30.0), 8 x 131072 25.2 / 25.6 (34.1 / 32.2); more blocks than compute units: 64 x 32768 23.1 / 25.1, 32 x 49152 24.3 / 26.1, 32 x 65536
+        // 24.8 / 28.1.
+        const int few_blocks = (Tp + kRetChunk<kRetTokFew> - 1) / kRetChunk<kRetTokFew> * c->d.n_layers;
+        if (Tp <= kRetFewTok && few_blocks <= c->n_cu) launch_retain_long<kRetTokFew>(c, alpha, Tp, k, seg_id, S, keep_idx, n_keep, ret_off, ret_len);
+        else launch_retain_long<kRetTok>(c, alpha, Tp, k, seg_id, S, keep_idx, n_keep, ret_off, ret_len);
         return hipGetLastError();
     }
     if (Tp <= 4 * kBlockThreads)

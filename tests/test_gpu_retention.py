@@ -439,9 +439,9 @@ def test_retain_long_prompts_of_many_layers(U, oracle32, Tp):
             assert np.all(off[kind::4] == want_off) and np.all(ln[kind::4] == want_len), (k, kind)
 
 
-@pytest.mark.parametrize("Tp", [20000, 20001, 24576, 24577, 131072, 200001])
+@pytest.mark.parametrize("Tp", [20000, 20001, 24576, 24577, 65536, 65537, 131072, 200001])
 def test_retain_long_prompts(U, oracle32, Tp):
-    """Several blocks per layer (from 20001 tokens on), 8192 tokens each.  Layers: spread values; the cut among 4096 and 4097 tokens that share the first
+    """Several blocks per layer (from 20001 tokens on), 4096 tokens each, from 65537 tokens on 8192.  Layers: spread values; the cut among 4096 and 4097 tokens that share the first
     11 bits (the list's length, and one more: the second digit), distinct and in groups of equal ones; all tokens equal; all within one digit; mostly NaN.
     Called twice: the scratch is as the first call found it."""
     _say("retain, long prompt", Tp)
