@@ -663,6 +663,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     using P = Sweep<RT>;
     constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f, kAbove = 4.f, kFar = 0x1p24f;
+    constexpr float kLeast = -4.f * kExpBias;                            // a reference as low as this next to any that a word holds: the values weigh nothing
     extern __shared__ __attribute__((aligned(16))) char sm_ring[];
     __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
     __shared__ float sm_col[P::RS][P::kChunkKeys];
@@ -887,7 +888,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 if (row < kRows) {
 #pragma unroll
                     for (int k = 0; k < P::KSP; ++k)
-                        sm_l[k][row] = ldexpf(number_mant(v[0]), min(max((int)sm_m[k][row] + number_exp(v[0]), -512), 512));
+                        sm_l[k][row] = ldexpf(number_mant(v[0]), min(max((int)fmaxf(sm_m[k][row], kLeast) + number_exp(v[0]), -512), 512));
                 }
             }
             if (lane == 0) sm_ok[w] = wait.ok;

@@ -263,6 +263,30 @@ def test_token_importance_sweep_of_logits_that_rise(U, Hq, rise):
         assert not torch.equal(got[l], want[l])
 
 
+@pytest.mark.parametrize("Hq,keys", [(8, 64), (16, 32)])                                     # keys of a block's four or two waves, 16 each
+def test_token_importance_sweep_of_a_wave_far_below_the_others(U, Hq, keys):
+    """The 16 keys in `keys` that one wave of a block takes lie 2^31 and more (log2 units) below those of its other waves: they weigh nothing, the others what they weigh
+    without them (logits within 6 of zero: the bound of test_token_importance_precision_at_large_logits)."""
+    L, H, N, T, D = 4, 8, 32, 4128, 128
+    _say("importance in one sweep, a wave far below", Hq)
+    v = np.random.default_rng(Hq).integers(0, 48, size=(L, H, T))
+    K = torch.zeros(L, H, T, D)
+    K[..., 1] = torch.as_tensor(v, dtype=torch.float32)
+    far = np.zeros(T, dtype=bool)
+    far[1024:3072] = np.arange(1024, 3072) // 16 % (keys // 16) == 1
+    K[:, :, far, 0] = -2.0 ** 24
+    q = torch.zeros(L, Hq, N, D)
+    q[..., 1] = 1.0
+    q[..., 0] = 2.0 ** 20
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype="bf16")
+    got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q.to(torch.bfloat16).to(U.DEV), K.to(torch.bfloat16).to(U.DEV), T, N).cpu().numpy().astype(np.float64)
+    e = np.where(far, 0.0, np.exp((v - 47) / math.sqrt(D)))
+    z = np.cumsum(e, axis=-1)[..., T - N:]
+    want = (Hq // H * e[..., :T - N] * (1.0 / z).sum(-1, keepdims=True)).sum(1)
+    assert np.all(got[:, far[:T - N]] == 0)
+    assert np.all(np.abs(got - want) <= 1e-6 * want)
+
+
 def test_token_importance_sweeps_on_two_streams(U):
     """Two contexts whose sweeps meet on the GPU: each finds part of the compute units taken, its blocks wait or leave the work to the two passes;
     the results are those of a sweep alone to the bound of the test above."""
