@@ -663,6 +663,9 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     using P = Sweep<RT>;
     constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows;
     constexpr float kLog2e = 1.4426950408889634f, kAbove = 4.f, kFar = 0x1p24f;
+    // Reference of a row that has shown a wave nothing: below every other, so that it is not the largest of a block's waves, and the first finite logit that comes
+    // to it rises far above it.  exp2(-infinity + 3.4e38) = 0.
+    constexpr float kNothing = -3.402823466e38f;
     constexpr float kLeast = -4.f * kExpBias;                            // a reference as low as this next to any that a word holds: the values weigh nothing
     extern __shared__ __attribute__((aligned(16))) char sm_ring[];
     __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
@@ -722,7 +725,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float top = rintf(reduce_16<MaxOp>(acc[0][j]) * scale) + kAbove;
-                ref[j] = top > -INFINITY ? top : 0.f;                    // (nothing visible: any)
+                ref[j] = top > -INFINITY ? top : kNothing;
                 sum[j] = 0.f;
             }
         };
@@ -810,7 +813,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float top = rintf(reduce_16<MaxOp>(m[j]) * scale);
-                ref[j] = top > -INFINITY ? top : 0.f;
+                ref[j] = top > -INFINITY ? top : kNothing;
                 sum[j] = 0.f;
             }
 #pragma unroll

@@ -287,6 +287,66 @@ def test_token_importance_sweep_of_a_wave_far_below_the_others(U, Hq, keys):
     assert np.all(np.abs(got - want) <= 1e-6 * want)
 
 
+# the last chunk holds 1, 16, 17, 40 or 60 keys (of 1024, 512 and 256), or is the only one
+BELOW_ZERO = [(8, t) for t in (40, 1025, 1040, 1041, 1064, 1084, 4136)] + [(16, t) for t in (40, 513, 528, 529, 552, 572)] + [(32, t) for t in (40, 257, 272, 273, 296)]
+
+
+@pytest.mark.parametrize("Hq,T", BELOW_ZERO, ids=[f"rows{4 * hq}-T{t}" for hq, t in BELOW_ZERO])
+def test_token_importance_sweep_of_logits_far_from_zero(U, Hq, T):
+    """A shift of a row's logits leaves its softmax alone, also where parts of a block see none of the last chunk's keys: all logits up to 423 below or
+    above zero in log2 units, a layer each, products and sums exact as in test_token_importance_precision_at_large_logits, the window's own keys up to 2^6 times as
+    heavy as the rest.  The bound of that test, for arguments of exp2 of up to 2^4 (rounded to 2^-21: 3.3e-7) and twice its spread (5e-7): 1.4e-6."""
+    H, N, D = 8, 32, 128
+    bases = [-255, -213, -181, -111.5, -101, -100.5, -90.5, -50, 0, 100.5, 181, 255]
+    L = len(bases)                                                                          # 96 (layer, head) pairs: one chunk each is enough
+    _say("importance in one sweep, logits far from zero", Hq, T)
+    v = np.random.default_rng(T).integers(0, 48, size=(L, H, T))
+    v[:, :, T - N:] += 48
+    K = torch.zeros(L, H, T, D)
+    K[..., 1] = torch.as_tensor(v, dtype=torch.float32)
+    K[..., 0] = 13.0
+    q = torch.zeros(L, Hq, N, D)
+    q[..., 1] = 1.0
+    q[..., 0] = torch.tensor(bases)[:, None, None]
+    K16, q16 = K.to(torch.bfloat16), q.to(torch.bfloat16)
+    assert torch.equal(K16.float(), K) and torch.equal(q16.float(), q)
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype="bf16")
+    got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q16.to(U.DEV), K16.to(U.DEV), T, N).cpu().numpy().astype(np.float64)
+    e = np.exp((v - 95) / math.sqrt(D))                                                     # the common part drops out
+    z = np.cumsum(e, axis=-1)[..., T - N:]                                                  # window query n sees the keys 0 .. Tp + n
+    want = (Hq // H * e[..., :T - N] * (1.0 / z).sum(-1, keepdims=True)).sum(1)
+    worst = np.abs(got / want - 1).max(1)
+    _say("  largest relative error of each layer", *(f"{x:.1e}" for x in worst))
+    assert np.all(worst <= 1.4e-6)
+
+
+@pytest.mark.parametrize("Hq", [8, 16, 32])                                                # chunks of 1024, 512 and 256 keys
+@pytest.mark.parametrize("base", [-255, -100, 0, 100])
+def test_token_importance_sweep_of_chunks_that_begin_with_infinite_keys(U, Hq, base):
+    """Sixteen keys and more whose logits are -infinity, where a block, one of its waves or the window begins: they weigh nothing, and the keys behind them, up to 430
+    from zero in log2 units, what they weigh without them.  The bound of test_token_importance_sweep_of_logits_far_from_zero."""
+    L, H, N, T, D = 4, 8, 32, 4128, 128
+    _say("importance in one sweep, infinite keys first", Hq, base)
+    v = np.random.default_rng(Hq).integers(0, 48, size=(L, H, T))
+    K = torch.zeros(L, H, T, D)
+    K[..., 1] = torch.as_tensor(v, dtype=torch.float32)
+    K[..., 0] = 13.0
+    gone = np.zeros(T, dtype=bool)
+    for first, last in ((0, 16), (1040, 1056), (2096, 2112), (3072, 3136), (4096, 4112)):
+        gone[first:last] = True
+    K[:, :, gone, 2] = -math.inf
+    q = torch.zeros(L, Hq, N, D)
+    q[..., 1:3] = 1.0
+    q[..., 0] = base
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype="bf16")
+    got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q.to(torch.bfloat16).to(U.DEV), K.to(torch.bfloat16).to(U.DEV), T, N).cpu().numpy().astype(np.float64)
+    e = np.where(gone, 0.0, np.exp((v - 47) / math.sqrt(D)))
+    z = np.cumsum(e, axis=-1)[..., T - N:]
+    want = (Hq // H * e[..., :T - N] * (1.0 / z).sum(-1, keepdims=True)).sum(1)
+    assert np.all(got[:, gone[:T - N]] == 0)
+    assert np.all(np.abs(got - want) <= 1.4e-6 * want)
+
+
 def test_token_importance_sweeps_on_two_streams(U):
     """Two contexts whose sweeps meet on the GPU: each finds part of the compute units taken, its blocks wait or leave the work to the two passes;
     the results are those of a sweep alone to the bound of the test above."""
