@@ -833,8 +833,9 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 float l = 0.f;
 #pragma unroll
                 for (int k = 0; k < P::KSP; ++k) l += ldexpf(sm_l[k][row], (int)fmaxf(sm_m[k][row] - m, -512.f));
-                if (l > 0.f && !(fabsf(m) < (float)(kExpBias - 256))) wait.ok = false;       // beyond the words' exponent
-                __hip_atomic_store(part + ((row >> 2) * x.nch + chunk) * 4 + (row & 3), tagged_number(l, l > 0.f ? (int)m : 0, tag), __ATOMIC_RELAXED,
+                const bool fits = l > 0.f && fabsf(m) < (float)(kExpBias - 256);             // within the words' exponents
+                if (l > 0.f && !fits) wait.ok = false;
+                __hip_atomic_store(part + ((row >> 2) * x.nch + chunk) * 4 + (row & 3), tagged_number(l, fits ? (int)m : 0, tag), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
             wait.ok = __all(wait.ok);

@@ -347,6 +347,23 @@ def test_token_importance_sweep_of_chunks_that_begin_with_infinite_keys(U, Hq, b
     assert np.all(np.abs(got - want) <= 1.4e-6 * want)
 
 
+def test_token_importance_sweep_after_one_beyond_its_exponents(U):
+    """A sweep that gave up over logits beyond the exponents of its words leaves words that no later launch takes for its own: here the place of the exponent
+    alone would turn the tags of a first launch, 1 to 256, into those of the second."""
+    L, Hq, H, N, T = 32, 8, 8, 32, 4128
+    _say("importance in one sweep, after one beyond its exponents")
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want = _gpu_importance(U, two, q, K, T, N)
+    ctx = U.make_ctx(wl, T, 64, 16)
+    q_far, K_far = torch.zeros_like(q), torch.zeros_like(K)
+    q_far[..., 0], K_far[..., 0] = 16384, 16064                                             # 2^25 and some thousands in log2 units
+    _gpu_importance(U, ctx, q_far, K_far, T, N)
+    got = _gpu_importance(U, ctx, q, K, T, N)
+    assert ((got - want).abs() / want).max().item() <= 2e-6
+
+
 def test_token_importance_sweeps_on_two_streams(U):
     """Two contexts whose sweeps meet on the GPU: each finds part of the compute units taken, its blocks wait or leave the work to the two passes;
     the results are those of a sweep alone to the bound of the test above."""
