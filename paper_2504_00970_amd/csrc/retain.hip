@@ -515,7 +515,9 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 //   Per chunk:  logits of its keys, tile by tile on the matrix cores (the keys of the next chunk are requested as the places in LDS come free), exp2 of
 //   a tile and the sums of its rows beside the next tile's logits, relative to a whole reference from the wave's first tile -> published ->
 //   the blocks of the head combine a share of its rows each and publish 1 / sum -> column sums of the values held.
-// A chunk whose logits rise too far above those of its first tile (kFar) takes them from memory once more, with its own maxima.
+// A wave whose logits rise far above its references (kFar) in some tile moves them up and the values that it holds down.  (The chunk's logits taken from memory once
+// more instead, with its own maxima, while all blocks of the head wait: with a key in every chunk 45 nats above the others 32768 keys of 128 rows 2680 -> 750 us,
+// 64 rows 1460 -> 451, 32 rows 928 -> 378; every tile 45 nats above the one before it 1180, 592, 392; none far above: the same, 682.)
 // The exchange passes tagged words: nothing is cleared, drained or counted.  A block publishes its next chunk only after it has seen
 // every row of the present one combined, so one place per block is enough.  While one block of a compute unit waits for the
 // others, its neighbour computes.  Some of a block's waves request keys, others talk to the other blocks: a wave's loads return in
@@ -662,7 +664,7 @@ template <int RT>
 __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_per_eu(kSweepPerCu * Sweep<RT>::NW / 4, kSweepPerCu * Sweep<RT>::NW / 4))) void importance_sweep_kernel(SweepArgs x) {
     using P = Sweep<RT>;
     constexpr int kRowBytes = kHeadDim * 2, kRows = P::kRows;
-    constexpr float kLog2e = 1.4426950408889634f, kAbove = 4.f, kFar = 0x1p24f;
+    constexpr float kLog2e = 1.4426950408889634f, kAbove = 4.f, kFar = 24.f;
     // Reference of a row that has shown a wave nothing: below every other, so that it is not the largest of a block's waves, and the first finite logit that comes
     // to it rises far above it.  exp2(-infinity + 3.4e38) = 0.
     constexpr float kNothing = -3.402823466e38f;
@@ -670,7 +672,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     extern __shared__ __attribute__((aligned(16))) char sm_ring[];
     __shared__ __attribute__((aligned(16))) float sm_m[P::KSP][kRows], sm_l[P::KSP][kRows];
     __shared__ float sm_col[P::RS][P::kChunkKeys];
-    __shared__ int sm_ok[P::kPollers], sm_far[2], sm_last;
+    __shared__ int sm_ok[P::kPollers], sm_last;
     __shared__ __attribute__((aligned(16))) int32_t sm_limit[kRows];     // last key that a row sees
 
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -684,7 +686,6 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
     const unsigned int epoch = ld_agent(x.state);
     int lh = blockIdx.x / x.nch, chunk = blockIdx.x - lh * x.nch;
     auto chunk_src = [&](int head, int ch) { return x.K_pool + ((int64_t)head * x.T + ch * P::kChunkKeys) * kRowBytes; };
-    if (threadIdx.x < 2) sm_far[threadIdx.x] = 0;
     for (int row = threadIdx.x; row < kRows; row += P::kThreads) sm_limit[row] = min(Tp + row % x.N, x.T - 1);      // (the first stage's barrier follows)
     const SweepStages<RT> stages(sm_ring, loader);
 #pragma unroll
@@ -729,23 +730,31 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 sum[j] = 0.f;
             }
         };
+        // Some row's logits in tile t rise kFar and more above its reference, which moves up to them; the values in registers move down with it (an exact factor).
+        auto raise_references = [&](int t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float top = fmaxf(rintf(reduce_16<MaxOp>(acc[t][j]) * scale) + kAbove, ref[j]);
+                const float f = exp2_neg(ref[j] < top ? ref[j] - top : 0.f);
+                ref[j] = top;
+                sum[j] *= f;
+#pragma unroll
+                for (int u = 0; u < P::KT; ++u)
+                    if (u < t) acc[u][j] *= f;
+            }
+        };
         // the exp2 values of tile t and its part of the sums, here and not behind a later barrier
         auto exps = [&](int t) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(acc[t][j], scale, -ref[j]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[t][j] = exp2_neg(acc[t][j]);
+            f32x4 v = acc[t];
+            float x0 = fmaf(v[0], scale, -ref[0]), x1 = fmaf(v[1], scale, -ref[1]), x2 = fmaf(v[2], scale, -ref[2]), x3 = fmaf(v[3], scale, -ref[3]);
+            if (t > 0 && __any(fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)) > kFar)) {
+                raise_references(t);
+                x0 = fmaf(v[0], scale, -ref[0]); x1 = fmaf(v[1], scale, -ref[1]); x2 = fmaf(v[2], scale, -ref[2]); x3 = fmaf(v[3], scale, -ref[3]);
+            }
+            acc[t] = f32x4{exp2_neg(x0), exp2_neg(x1), exp2_neg(x2), exp2_neg(x3)};
 #pragma unroll
             for (int j = 0; j < 4; ++j) sum[j] += acc[t][j];
             asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]));
-        };
-        auto leave_sums = [&]() {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) sum[j] = reduce_16<AddOp>(sum[j]);
-            if (t16 == 0) {
-                *reinterpret_cast<float4*>(&sm_m[ks][row_of]) = make_float4(ref[0], ref[1], ref[2], ref[3]);
-                *reinterpret_cast<float4*>(&sm_l[ks][row_of]) = make_float4(sum[0], sum[1], sum[2], sum[3]);
-            }
         };
 #pragma unroll
         for (int k = 0; k < P::SC; ++k) {
@@ -783,44 +792,14 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             }
         }
         exps(P::KT - 1);
-        leave_sums();
-        if (__any(!(sum[0] < kFar && sum[1] < kFar && sum[2] < kFar && sum[3] < kFar)) && lane == 0) sm_far[left & 1] = 1;
-        if (tid == 0) sm_far[~left & 1] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[j] = reduce_16<AddOp>(sum[j]);
+        if (t16 == 0) {
+            *reinterpret_cast<float4*>(&sm_m[ks][row_of]) = make_float4(ref[0], ref[1], ref[2], ref[3]);
+            *reinterpret_cast<float4*>(&sm_l[ks][row_of]) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+        }
         __syncthreads();
         if (left > 0) stages.request(src_next, keys, P::NS - 1);
-        if (sm_far[left & 1]) {
-            // Some row's logits rise far above those of its first tile, or are no numbers: all of it once more from memory, with the chunk's own maxima.
-            load_q(lh);
-            const char* mine = src + 16 * qd;
-            auto logits = [&](int t) {
-                const char* key = mine + min(16 * (P::KSP * t + ks) + t16, keys - 1) * kRowBytes;
-                f32x4 c = {};
-#pragma unroll
-                for (int st = 0; st < 4; ++st)
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[st]), __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(key + 64 * st)), c, 0, 0, 0);
-                acc[t] = c;
-                if (base0 + 16 * P::KSP * (t + 1) > Tp) mask_tile(acc[t], t);
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            logits(0);
-            float m[4] = {acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
-#pragma unroll
-            for (int t = 1; t < P::KT; ++t) {
-                logits(t);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) m[j] = fmaxf(m[j], acc[t][j]);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float top = rintf(reduce_16<MaxOp>(m[j]) * scale);
-                ref[j] = top > -INFINITY ? top : kNothing;
-                sum[j] = 0.f;
-            }
-#pragma unroll
-            for (int t = 0; t < P::KT; ++t) exps(t);
-            leave_sums();
-            __syncthreads();
-        }
         if (w < P::kPollers) {
             __builtin_amdgcn_s_setprio(3);
             // published: the sum of every row; four rows of a chunk side by side, then those of the next chunk

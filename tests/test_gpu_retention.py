@@ -263,6 +263,35 @@ def test_token_importance_sweep_of_logits_that_rise(U, Hq, rise):
         assert not torch.equal(got[l], want[l])
 
 
+@pytest.mark.parametrize("Hq", [8, 16, 32])                                                # a wave takes tiles of 16 keys, 64, 32 and 16 keys apart
+@pytest.mark.parametrize("step", [20, 25, 30, 100])
+def test_token_importance_sweep_of_logits_that_rise_tile_by_tile(U, Hq, step):
+    """Every tile of a wave lies `step` (log2 units) above the one before it, so that references move up never, now and then or each time; in one layer all rows,
+    in one a single row; in the others the steps begin late in the chunk, or are taken in the window's own.  The bound of
+    test_token_importance_sweep_of_logits_that_rise."""
+    L, H, N, T = 4, 8, 32, 4120
+    _say("importance in one sweep, rising tiles", Hq, step)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    apart = 512 // Hq
+    tile = torch.arange(T, device=U.DEV) // apart % 16
+    q[..., 0] = 0.0
+    q[0, ..., 0] = 8.0
+    q[1, ::Hq // H, 5, 0] = 8.0
+    q[2:, ..., 0] = 8.0
+    K[..., 0] = 0.0
+    unit = step / (8 * 1.4426950408889634 / math.sqrt(128))
+    K[0, ..., 0] = K[1, ..., 0] = (tile * unit).to(torch.bfloat16)
+    K[2, ..., 0] = ((tile - 12).clamp_min(0) * unit).to(torch.bfloat16)
+    K[3, :, T - 100:, 0] = (tile[T - 100:] * unit).to(torch.bfloat16)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert torch.isfinite(got).all()
+    for l in range(L):
+        assert torch.all((got - want)[l].abs() <= 4e-6 * want[l] + 1e-30), l
+        assert not torch.equal(got[l], want[l])
+
+
 @pytest.mark.parametrize("Hq,keys", [(8, 64), (16, 32)])                                     # keys of a block's four or two waves, 16 each
 def test_token_importance_sweep_of_a_wave_far_below_the_others(U, Hq, keys):
     """The 16 keys in `keys` that one wave of a block takes lie 2^31 and more (log2 units) below those of its other waves: they weigh nothing, the others what they weigh
