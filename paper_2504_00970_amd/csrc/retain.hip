@@ -737,10 +737,10 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 const float top = fmaxf(rintf(reduce_16<MaxOp>(acc[t][j]) * scale) + kAbove, ref[j]);
                 const float f = exp2_neg(ref[j] < top ? ref[j] - top : 0.f);
                 ref[j] = top;
-                sum[j] *= f;
+                sum[j] = sum[j] == INFINITY ? 0.f : sum[j] * f;            // (of logits that a float does not hold: see below)
 #pragma unroll
                 for (int u = 0; u < P::KT; ++u)
-                    if (u < t) acc[u][j] *= f;
+                    if (u < t) acc[u][j] = acc[u][j] == INFINITY ? 0.f : acc[u][j] * f;
             }
         };
         // the exp2 values of tile t and its part of the sums, here and not behind a later barrier
@@ -794,6 +794,17 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         exps(P::KT - 1);
 #pragma unroll
         for (int j = 0; j < 4; ++j) sum[j] = reduce_16<AddOp>(sum[j]);
+        // Logits that a float does not hold (from 2^31 on) can lie 2^128 above the reference that is rounded from them.  Such a row's values weigh nothing next to
+        // a wave's that the words hold; where there is none, the launch is left to the passes.
+        if (__any(fmaxf(fmaxf(sum[0], sum[1]), fmaxf(sum[2], sum[3])) == INFINITY)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool nothing = sum[j] == INFINITY;
+                sum[j] = nothing ? 0.f : sum[j];
+#pragma unroll
+                for (int t = 0; t < P::KT; ++t) acc[t][j] = nothing ? 0.f : acc[t][j];
+            }
+        }
         if (t16 == 0) {
             *reinterpret_cast<float4*>(&sm_m[ks][row_of]) = make_float4(ref[0], ref[1], ref[2], ref[3]);
             *reinterpret_cast<float4*>(&sm_l[ks][row_of]) = make_float4(sum[0], sum[1], sum[2], sum[3]);
@@ -812,9 +823,9 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 float l = 0.f;
 #pragma unroll
                 for (int k = 0; k < P::KSP; ++k) l += ldexpf(sm_l[k][row], (int)fmaxf(sm_m[k][row] - m, -512.f));
-                const bool fits = l > 0.f && fabsf(m) < (float)(kExpBias - 256);             // within the words' exponents
-                if (l > 0.f && !fits) wait.ok = false;
-                __hip_atomic_store(part + ((row >> 2) * x.nch + chunk) * 4 + (row & 3), tagged_number(l, fits ? (int)m : 0, tag), __ATOMIC_RELAXED,
+                const bool fits = fabsf(m) < (float)(kExpBias - 256);                        // within the words' exponents
+                if (l == l && m > kNothing && !fits) wait.ok = false;
+                __hip_atomic_store(part + ((row >> 2) * x.nch + chunk) * 4 + (row & 3), tagged_number(l, l > 0.f && fits ? (int)m : 0, tag), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
             wait.ok = __all(wait.ok);

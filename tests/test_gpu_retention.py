@@ -316,6 +316,33 @@ def test_token_importance_sweep_of_a_wave_far_below_the_others(U, Hq, keys):
     assert np.all(np.abs(got - want) <= 1e-6 * want)
 
 
+@pytest.mark.parametrize("Hq,keys", [(8, 64), (16, 32)])
+def test_token_importance_sweep_of_a_wave_far_below_in_rounded_logits(U, Hq, keys):
+    """As above, with logits that a float does not hold: rounded at 2^41 they differ by thousands of log2 units from the largest of their tile, rounded otherwise,
+    and are nothing next to the others all the same."""
+    L, H, N, T, D = 4, 8, 32, 4128, 128
+    _say("importance in one sweep, a wave far below, rounded", Hq)
+    rng = np.random.default_rng(Hq)
+    v = rng.integers(0, 48, size=(L, H, T))
+    K = torch.zeros(L, H, T, D)
+    K[..., 1] = torch.as_tensor(v, dtype=torch.float32)
+    far = np.zeros(T, dtype=bool)
+    far[1024:3072] = np.arange(1024, 3072) // 16 % (keys // 16) == 1
+    far[3088:3104] = True                                                                   # the first tile of a wave whose others are not far
+    K[:, :, far, 0] = torch.as_tensor(-2.0 ** 17 * rng.integers(128, 256, size=(L, H, int(far.sum()))), dtype=torch.float32)
+    q = torch.zeros(L, Hq, N, D)
+    q[..., 1] = 1.0
+    q[..., 0] = 2.0 ** 20
+    assert torch.equal(K.to(torch.bfloat16).float(), K)
+    wl = gen.CFG3.scaled(n_layers=L, n_q_heads=Hq, n_kv_heads=H, n_tokens=T, dtype="bf16")
+    got = _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q.to(torch.bfloat16).to(U.DEV), K.to(torch.bfloat16).to(U.DEV), T, N).cpu().numpy().astype(np.float64)
+    e = np.where(far, 0.0, np.exp((v - 47) / math.sqrt(D)))
+    z = np.cumsum(e, axis=-1)[..., T - N:]
+    want = (Hq // H * e[..., :T - N] * (1.0 / z).sum(-1, keepdims=True)).sum(1)
+    assert np.all(got[:, far[:T - N]] == 0)
+    assert np.all(np.abs(got - want) <= 1e-6 * want)
+
+
 # the last chunk holds 1, 16, 17, 40 or 60 keys (of 1024, 512 and 256), or is the only one
 BELOW_ZERO = [(8, t) for t in (40, 1025, 1040, 1041, 1064, 1084, 4136)] + [(16, t) for t in (40, 513, 528, 529, 552, 572)] + [(32, t) for t in (40, 257, 272, 273, 296)]
 
