@@ -269,6 +269,9 @@ __device__ __forceinline__ void score_wave_e4m3(const char* __restrict__ q_grp, 
                 const float4 t = *reinterpret_cast<const float4*>(qrow + 16 * k);
                 qs[4 * k] += t.x; qs[4 * k + 1] += t.y; qs[4 * k + 2] += t.z; qs[4 * k + 3] += t.w;
             }
+            // eight fp32 queries: four at a time, else the single-launch step has no registers for what lives across the scores (8 spilled; one sequence of
+            // 32768 tokens 16.8 -> 15.6 us per layer, seven and one 15.9)
+            if (TAGGED && G == 8 && g == 3) __builtin_amdgcn_sched_barrier(0);
         } else {
 #pragma unroll
             for (int k = 0; k < 2; ++k) {

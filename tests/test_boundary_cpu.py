@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 import shutil
+import struct
 import sysconfig
 
 import pytest
@@ -140,3 +141,37 @@ def test_product_package_does_not_reach_into_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 src = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in src.lower(), f
+
+
+def _kernels(path):
+    """Metadata of the gfx950 kernels in a library: the code objects of its bundles carry it as a note (type 32, msgpack)."""
+    msgpack = pytest.importorskip("msgpack")
+    data, kernels, at = open(path, "rb").read(), [], 0
+    while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        (entries,), p = struct.unpack_from("<Q", data, at + 24), at + 32
+        for _ in range(entries):
+            offset, size, length = struct.unpack_from("<3Q", data, p)
+            name, p = data[p + 24:p + 24 + length], p + 24 + length
+            if b"gfx950" not in name:
+                continue
+            elf = data[at + offset:at + offset + size]
+            headers, = struct.unpack_from("<Q", elf, 0x20)
+            each, n = struct.unpack_from("<2H", elf, 0x36)
+            for i in range(n):
+                kind, _, begin, _, _, length = struct.unpack_from("<2I4Q", elf, headers + i * each)
+                end = begin + length
+                while kind == 4 and begin < end:                                            # PT_NOTE
+                    name_size, desc_size, note = struct.unpack_from("<3I", elf, begin)
+                    begin += 12 + (name_size + 3) // 4 * 4
+                    if note == 32:
+                        kernels += msgpack.unpackb(elf[begin:begin + desc_size])["amdhsa.kernels"]
+                    begin += (desc_size + 3) // 4 * 4
+        at += 24
+    return kernels
+
+
+def test_no_kernel_spills_registers():
+    """A spilled register is a trip through memory in kernels that are bound by such trips, and in those that load keys it waits behind the keys."""
+    kernels = _kernels(_build.build(force=False))
+    assert len(kernels) > 100
+    assert [k[".name"] for k in kernels if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]] == []

@@ -582,7 +582,7 @@ def test_fused_single_launch_equal_shares(U, oracle32, B, budgets, Hq, dtype):
 
 # buckets a block scores of 8 KV heads: 32 blocks a pair with one sequence (48, 49 and 64, the last block with one bucket), 10 with three (one tenth of
 # 480, 481 and 1000; shares of 16 lines), 8 with four
-@pytest.mark.parametrize("B,S,dtype,Hq,sv_dtype", [(1, 1536, "bf16", 32, "f32"), (1, 1537, "bf16", 32, "f32"), (1, 1985, "f32", 16, "bf16"), (1, 1600, "bf16", 64, "fp8"),
+@pytest.mark.parametrize("B,S,dtype,Hq,sv_dtype", [(1, 1536, "bf16", 32, "f32"), (1, 1537, "bf16", 32, "f32"), (1, 1985, "f32", 16, "bf16"), (1, 1600, "bf16", 64, "fp8"), (1, 1600, "f32", 64, "fp8"),
                                                    (3, 480, "bf16", 32, "fp8"), (3, 481, "bf16", 8, "fp8"), (3, 1000, "f32", 32, "f32"), (4, 393, "bf16", 64, "bf16"),
                                                    (4, 5, "bf16", 32, "fp8")])
 def test_fused_single_launch_shares_of_whole_lines(U, oracle32, B, S, dtype, Hq, sv_dtype):
