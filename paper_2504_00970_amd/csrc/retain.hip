@@ -993,9 +993,14 @@ static int sweep_blocks(const Ctx* c) { return min(kSweepPerCu * c->n_cu, kSweep
 
 // Where the sweep is the faster form (us, two passes / one sweep): the chunks of a head fit the chip at once, and the launch has chunks enough (96; 64
 // chunks: 512 keys a chunk 14.8 / 15.4, 1024: 17.5 / 16.9, 256: 15.7 / 14.6; 96 chunks of 256 keys 16.8 / 13.9, 20.2 / 16.0 with 192).
-// 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 390, 715 / 538).  128 rows gain up to 128 chunks a head, whose words a wave combines in one round of
-// loads, as long as whole heads fill 84 % of the chip's blocks (16 layers: 28000 keys, 86 %: 359 / 348; 30000, 92 %: 383 / 360; 36000, 83 %, 141 chunks:
-// 452 / 513; 40000, 92 %, 157 chunks: 499 / 538; 65536, 100 %, 256 chunks: 807 / 848; 1024 keys of 32 layers 44 / 34.5, of 8 layers 22.6 / 17.6).
+// 32 and 64 rows gain at every length (131072 keys, 8 layers: 737 / 390, 715 / 538).  128 rows gain up to 64 chunks a head (1024 keys of 32 layers 44 / 34.5, of 8 layers
+// 22.6 / 17.6; 9465 keys, 32, 16, 8, 4 layers: 250 / 227, 136 / 118, 77 / 63, 48 / 37; 14585 keys, 57 chunks, whole heads fill 89 % of the chip's blocks: 373 / 364,
+// 200 / 185, 112 / 96, 63 / 51), and up to 128, whose words a wave combines in one round of loads, as long as whole heads fill the blocks: 93 % of them in launches of more
+// than 64 heads, where the start and end of the two passes weigh less, 84 % in smaller ones.  16, 8, 4 layers of 8 heads: 18937 keys (74 chunks, 87 %) 254 / 258, 142 / 129,
+// 75 / 72; 20473 (94 %) 270 / 262, 151 / 133, 79 / 73; 22521 (86 %) 296 / 308, 163 / 154, 85 / 81; 23545 (90 %) 305 / 315, 172 / 158, 86 / 82; 26105 (99.6 %) 338 / 325, 181 / 166,
+// 94 / 84; 26361 (103 chunks, 80 %) 339 / 377, 189 / 186, 98 / 95; 27641 (84.4 %) 355 / 382, 190 / 197, 102 / 97; 29689 (91 %) 378 / 393, 210 / 192, 111 / 99; 30713 (94 %) 391 / 391,
+// 210 / 197, 112 / 102; 32761 (100 %) 416 / 392, 226 / 199, 120 / 104; 32 layers, 74 chunks 487 / 495, 80 515 / 507, 85 547 / 507.  Keys without structure draw more power: 20473 keys
+// 250 / 267, 136 / 127, 74 / 68; 26361 323 / 374, 170 / 185, 89 / 91; 32761 397 / 390, 203 / 197, 108 / 99.  More chunks: 40000 keys, 16 layers 499 / 538, 65536 807 / 848.
 bool importance_may_sweep(const skv_desc& d) {
     const int64_t heads = (int64_t)d.n_layers * d.n_kv_heads;
     static_assert(Sweep<1>::kChunkKeys >= kSweepMinChunk && Sweep<2>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kChunkKeys >= kSweepMinChunk && Sweep<4>::kRows <= kSweepMaxRows, "");
@@ -1007,7 +1012,7 @@ static bool importance_sweeps(const Ctx* c, int32_t T) {
     using P = Sweep<RT>;
     const int64_t heads = (int64_t)c->d.n_layers * c->d.n_kv_heads, nch = (T + P::kChunkKeys - 1) / P::kChunkKeys, most = sweep_blocks(c);
     if (!c->single_launch || !c->imp_part || nch > most || heads > kSweepMostHeads || heads * nch > (1 << 30) || heads * nch < kSweepMinChunks) return false;
-    return RT < 4 || (nch <= 128 && most / nch * nch * 100 >= 84 * most);
+    return RT < 4 || nch <= 64 || (nch <= 128 && most / nch * nch * 100 >= (heads > 64 ? 93 : 84) * most);
 }
 
 template <int RT>

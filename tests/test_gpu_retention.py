@@ -240,6 +240,20 @@ def test_token_importance_sweep_combines_any_number_of_chunks(U, L, Hq, H, N, T)
     assert not torch.equal(got, want)
 
 
+# 128 rows, 256 keys a chunk: 57 chunks a head fill 456 of the 512 blocks, 73 and 74 fill 511 and 444, 102 and 103 fill 510 and 412, 129 are too many
+@pytest.mark.parametrize("L,chunks,sweeps", [(9, 57, True), (9, 73, True), (9, 74, False), (8, 74, True), (8, 102, True), (8, 103, False), (1, 128, True), (1, 129, False)])
+def test_token_importance_sweep_where_whole_heads_fill_the_chip(U, L, chunks, sweeps):
+    """Which of the two forms a launch takes, by its bits; the sweep to the bound of test_token_importance_in_one_sweep."""
+    Hq, H, N, T = 32, 8, 32, 256 * chunks
+    _say("importance in one sweep, whole heads", L, chunks)
+    wl, q, K = _importance_inputs(U, L, Hq, H, N, T)
+    two = U.make_ctx(wl, T, 64, 16)
+    two.set_single_launch(False)
+    want, got = _gpu_importance(U, two, q, K, T, N), _gpu_importance(U, U.make_ctx(wl, T, 64, 16), q, K, T, N)
+    assert torch.equal(got, want) == (not sweeps)
+    assert ((got - want).abs() / want).max().item() <= 2e-6
+
+
 @pytest.mark.parametrize("Hq", [8, 16, 32])                                                # chunks of 1024, 512 and 256 keys
 @pytest.mark.parametrize("rise", [16, 40, 120, 250])
 def test_token_importance_sweep_of_logits_that_rise(U, Hq, rise):
