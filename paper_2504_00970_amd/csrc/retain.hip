@@ -517,7 +517,8 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 //   the blocks of the head combine a share of its rows each and publish 1 / sum -> column sums of the values held.
 // A wave whose logits rise far above its references (kFar) in some tile moves them up and the values that it holds down.  (The chunk's logits taken from memory once
 // more instead, with its own maxima, while all blocks of the head wait: with a key in every chunk 45 nats above the others 32768 keys of 128 rows 2680 -> 750 us,
-// 64 rows 1460 -> 451, 32 rows 928 -> 378; every tile 45 nats above the one before it 1180, 592, 392; none far above: the same, 682.)
+// 64 rows 1460 -> 452, 32 rows 928 -> 378; every tile 45 nats above the one before it 1370, 656, 407; none far above: the same.  That code and the masks of the
+// last keys lie behind the kernel's end: between the tiles 705 -> 694, on a box where the form without it takes 699.)
 // The exchange passes tagged words: nothing is cleared, drained or counted.  A block publishes its next chunk only after it has seen
 // every row of the present one combined, so one place per block is enough.  While one block of a compute unit waits for the
 // others, its neighbour computes.  Some of a block's waves request keys, others talk to the other blocks: a wave's loads return in
@@ -712,8 +713,8 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         float ref[4], sum[4];
         const int lane = this_lane(), tid = lane + w * kWave, t16 = lane & 15, qd = lane >> 4;
         const int row_of = 16 * rs + 4 * qd;                             // row of a tile's first element
-        // keys that a row does not see
-        auto mask_tile = [&](f32x4& v, int t) {
+        // keys that a row does not see  (here and below: inlined though it is rarely run, or the tiles would not stay in registers)
+        auto mask_tile = [&](f32x4& v, int t) __attribute__((always_inline)) {
             const int key = base0 + 16 * (P::KSP * t + ks) + t16;
             const int4 limit = *reinterpret_cast<const int4*>(sm_limit + row_of);
             if (key > limit.x) v[0] = -INFINITY;
@@ -731,7 +732,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
             }
         };
         // Some row's logits in tile t rise kFar and more above its reference, which moves up to them; the values in registers move down with it (an exact factor).
-        auto raise_references = [&](int t) {
+        auto raise_references = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float top = fmaxf(rintf(reduce_16<MaxOp>(acc[t][j]) * scale) + kAbove, ref[j]);
@@ -747,7 +748,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         auto exps = [&](int t) {
             f32x4 v = acc[t];
             float x0 = fmaf(v[0], scale, -ref[0]), x1 = fmaf(v[1], scale, -ref[1]), x2 = fmaf(v[2], scale, -ref[2]), x3 = fmaf(v[3], scale, -ref[3]);
-            if (t > 0 && __any(fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)) > kFar)) {
+            if (t > 0 && __builtin_expect(__any(fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)) > kFar), 0)) {
                 raise_references(t);
                 x0 = fmaf(v[0], scale, -ref[0]); x1 = fmaf(v[1], scale, -ref[1]); x2 = fmaf(v[2], scale, -ref[2]); x3 = fmaf(v[3], scale, -ref[3]);
             }
@@ -787,7 +788,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
                 if (t == 1) set_references();
                 if (t >= 1) exps(t - 1);
                 acc[t] = c;
-                if (base0 + 16 * P::KSP * (t + 1) > Tp) mask_tile(acc[t], t);
+                if (__builtin_expect(base0 + 16 * P::KSP * (t + 1) > Tp, 0)) mask_tile(acc[t], t);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -796,7 +797,7 @@ __global__ __launch_bounds__((Sweep<RT>::kThreads)) __attribute__((amdgpu_waves_
         for (int j = 0; j < 4; ++j) sum[j] = reduce_16<AddOp>(sum[j]);
         // Logits that a float does not hold (from 2^31 on) can lie 2^128 above the reference that is rounded from them.  Such a row's values weigh nothing next to
         // a wave's that the words hold; where there is none, the launch is left to the passes.
-        if (__any(fmaxf(fmaxf(sum[0], sum[1]), fmaxf(sum[2], sum[3])) == INFINITY)) {
+        if (__builtin_expect(__any(fmaxf(fmaxf(sum[0], sum[1]), fmaxf(sum[2], sum[3])) == INFINITY), 0)) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool nothing = sum[j] == INFINITY;
