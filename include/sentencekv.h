@@ -158,8 +158,8 @@ int skv_build_semvec_layers(skv_ctx* ctx, const void* K_pool, int32_t T, const i
  * bf16 prompts whose (layer, head) fits the GPU run as one sweep over the keys whose blocks wait for each other inside the
  * kernel, at most the polls of skv_set_wait_limit (about a microsecond each) and never more than 8000; where they run out (blocks kept from starting
  * by other work on the GPU) the same call does the work in two passes that wait for nothing, and nothing fails.  Such a call takes the time of its
- * polls and then 2.5 to 6 times that of a sweep (32 layers x 8 heads x 32768 keys, 32 rows: 414 us in one sweep, 727 in two passes, 1070 in two passes behind a
- * sweep that gave up at once; 8 layers x 131072 keys: 420, 740, 2600).  The two ways round differently, by up to 2e-6 of a value, so that where other
+ * polls and then 2.3 to 6.5 times that of a sweep (32 layers x 8 heads x 32768 keys, 32 rows: 378 us in one sweep, 723 in two passes, 1055 in two passes behind a
+ * sweep that gave up at once; 8 layers x 131072 keys: 400, 749, 2605).  The two ways round differently, by up to 2e-6 of a value, so that where other
  * work shares the GPU alpha need not be the same from call to call, nor skv_retain's choice between tokens at its cut.  Each way by itself
  * repeats its bits; a caller who needs that of every call takes skv_set_single_launch(ctx, 0), which always means the two passes. */
 int64_t skv_token_importance_work_bytes(const skv_ctx* ctx, int32_t T, int32_t N);
