@@ -518,7 +518,7 @@ __global__ __launch_bounds__((Imp<EB, RT>::kThreads)) SKV_IMP_WAVES void importa
 // A wave whose logits rise far above its references (kFar) in some tile moves them up and the values that it holds down.  (The chunk's logits taken from memory once
 // more instead, with its own maxima, while all blocks of the head wait: with a key in every chunk 45 nats above the others 32768 keys of 128 rows 2680 -> 750 us,
 // 64 rows 1460 -> 452, 32 rows 928 -> 378; every tile 45 nats above the one before it 1370, 656, 407; none far above: the same.  That code and the masks of the
-// last keys lie behind the kernel's end: between the tiles 705 -> 694, on a box where the form without it takes 699.)
+// last keys lie behind the kernel's end: between the tiles 705, there 694, where the form without it took 699.)
 // The exchange passes tagged words: nothing is cleared, drained or counted.  A block publishes its next chunk only after it has seen
 // every row of the present one combined, so one place per block is enough.  While one block of a compute unit waits for the
 // others, its neighbour computes.  Some of a block's waves request keys, others talk to the other blocks: a wave's loads return in
