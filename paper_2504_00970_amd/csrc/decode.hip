@@ -43,21 +43,26 @@ __device__ __forceinline__ int32_t ld_const(const int32_t* p, int64_t i) {
 
 __device__ __forceinline__ Seq seq_of(const SeqView& v, int b) {
     Seq s;
-    if (v.cu_sent) {
-        s.sent_base = ld_const(v.cu_sent, b);
-        s.n_sent = ld_const(v.cu_sent, b + 1) - s.sent_base;
-    } else {
-        s.sent_base = 0;
-        s.n_sent = v.S_total;
-    }
-    if (v.cu_tok) {
-        s.tok_base = ld_const(v.cu_tok, b);
-        s.n_tok_ctx = ld_const(v.cu_tok, b + 1) - s.tok_base;
-    } else {
-        s.tok_base = 0;
-        s.n_tok_ctx = v.T_total;
-    }
+    s.sent_base = v.cu_sent ? ld_const(v.cu_sent, b) : 0;
+    s.n_sent = v.cu_sent ? ld_const(v.cu_sent, b + 1) - s.sent_base : v.S_total;
+    s.tok_base = v.cu_tok ? ld_const(v.cu_tok, b) : 0;
+    s.n_tok_ctx = v.cu_tok ? ld_const(v.cu_tok, b + 1) - s.tok_base : v.T_total;
     s.budget = v.budget_arr ? ld_const(v.budget_arr, b) : v.budget;
+    return s;
+}
+// The same for the decode step, which has budgets, and both boundary arrays or neither: one round of loads at most, and nobody waits for the budget yet.
+__device__ __forceinline__ Seq seq_of_step(const SeqView& v, int b) {
+    Seq s;
+    s.budget = ld_const(v.budget_arr, b);
+    if (v.cu_sent) {
+        const int32_t s0 = ld_const(v.cu_sent, b), s1 = ld_const(v.cu_sent, b + 1), t0 = ld_const(v.cu_tok, b), t1 = ld_const(v.cu_tok, b + 1);
+        asm volatile("" ::"s"(s0), "s"(s1), "s"(t0), "s"(t1));
+        s.sent_base = s0; s.n_sent = s1 - s0;
+        s.tok_base = t0; s.n_tok_ctx = t1 - t0;
+    } else {
+        s.sent_base = 0; s.n_sent = v.S_total;
+        s.tok_base = 0; s.n_tok_ctx = v.T_total;
+    }
     return s;
 }
 
@@ -128,10 +133,32 @@ hipError_t launch_query_update(Ctx* c, int32_t B, const void* q_t, const int32_t
 // Blocks are aligned to sequences: block x -> (sequence b, local block) by walking cu_sent.
 // ------------------------------------------------------------------------------------------------
 
+// Tag of a launch of the single-launch step for one pair: the pair's epoch after this launch (1 .. 2^26 - 1, never 0, so
+// zero-filled memory never looks valid) above the pair's number.  A word of memory carries a pair's current tag only if
+// a block of that pair wrote it in this launch: other pairs differ in the low bits, earlier launches in the epoch (which
+// repeats after 2^26 - 1 launches of the pair).
+__device__ __forceinline__ uint32_t step_tag(uint32_t epoch, int pair) {
+    uint32_t e = (epoch + 1u) & ((1u << (32 - kStepPairBits)) - 1u);
+    if (e == 0u) e = 1u;
+    return (e << kStepPairBits) | (uint32_t)pair;
+}
+
+// What a block knows of its pair when it begins: the epoch, on its way from memory, and the pair's number.  The tag is formed where it is needed: formed
+// at the top, the wait for the epoch comes before the request for the mean keys.
+struct StepState {
+    unsigned int epoch;
+    int pair;
+    __device__ __forceinline__ uint32_t tag() const {
+        unsigned int e = epoch;
+        asm volatile("" : "+v"(e));
+        return step_tag(e, pair);
+    }
+};
+
 // Scores of the STEP * N buckets from row_w on: p[i] of the lanes (lane / (64 / STEP)) is the score of bucket row_w + lane / (64 / STEP) + STEP i; c: the lane's place
 // among those of its bucket, negative where they hold no sum.  TAGGED: consecutive lanes take consecutive buckets, for one store of whole words of a line.
 template <bool TAGGED, int STEP, int N>
-__device__ __forceinline__ void store_scores(void* __restrict__ out_seq, const float (&p)[N], int c, int32_t row_w, int32_t n_sent, uint32_t tag) {
+__device__ __forceinline__ void store_scores(void* __restrict__ out_seq, const float (&p)[N], int c, int32_t row_w, int32_t n_sent, const StepState& st) {
     constexpr int kLanes = kWave / STEP, kFirst = STEP == 8 ? 4 : 0;      // lanes of a bucket, the first that holds its sum
     const int lane = threadIdx.x & 63;
     if constexpr (TAGGED) {
@@ -144,6 +171,7 @@ __device__ __forceinline__ void store_scores(void* __restrict__ out_seq, const f
         }
         v = __shfl(v, kLanes * (lane & (STEP - 1)) + kFirst + ((lane / STEP) & (N - 1)));
         const int32_t s = row_w + lane;
+        const uint32_t tag = st.tag();
         if (lane < STEP * N && s < n_sent) st_tagged(static_cast<unsigned long long*>(out_seq) + s, v, tag);
     } else if (c == 0) {
 #pragma unroll
@@ -159,7 +187,7 @@ __device__ __forceinline__ void store_scores(void* __restrict__ out_seq, const f
 // words that other blocks of the same launch read.
 template <int EB, int G, int RPWV, bool TAGGED>
 __device__ __forceinline__ void score_wave_f32(const char* __restrict__ q_grp, const float* __restrict__ sv_seq,
-                                               int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, uint32_t tag = 0) {
+                                               int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, const StepState& st = {}) {
     const int lane = threadIdx.x & 63;
     const int c = lane & 31, half = lane >> 5;
     float qs[4] = {0.f, 0.f, 0.f, 0.f};
@@ -197,14 +225,14 @@ __device__ __forceinline__ void score_wave_f32(const char* __restrict__ q_grp, c
         p[i] = dpp_add<0x128>(p[i]);
         p[i] += __shfl_xor(p[i], 16);
     }
-    store_scores<TAGGED, 2>(out_seq, p, c, row_w, n_sent, tag);
+    store_scores<TAGGED, 2>(out_seq, p, c, row_w, n_sent, st);
 }
 
 // The same from a bf16 table: a vector is 256 bytes = 16 lanes x 16 bytes (8 dims per lane), a wave load covers
 // 4 buckets, RPWV / 4 loads in flight; the sum over a bucket's 16 lanes stays inside a DPP row.
 template <int EB, int G, int RPWV, bool TAGGED>
 __device__ __forceinline__ void score_wave_bf16(const char* __restrict__ q_grp, const char* __restrict__ sv_seq,
-                                                int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, uint32_t tag = 0) {
+                                                int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, const StepState& st = {}) {
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, sub = lane >> 4;
     float qs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -247,14 +275,14 @@ __device__ __forceinline__ void score_wave_bf16(const char* __restrict__ q_grp, 
         p[i] = dpp_add<0x124>(p[i]);
         p[i] = dpp_add<0x128>(p[i]);
     }
-    store_scores<TAGGED, 4>(out_seq, p, c, row_w, n_sent, tag);
+    store_scores<TAGGED, 4>(out_seq, p, c, row_w, n_sent, st);
 }
 
 // The same from an E4M3 table: a vector is 128 bytes = 8 lanes x 16 bytes (16 dims per lane), a wave load covers 8 buckets,
 // RPWV / 8 loads in flight; the sum over a bucket's 8 lanes is two quad exchanges and a rotation by 4.
 template <int EB, int G, int RPWV, bool TAGGED>
 __device__ __forceinline__ void score_wave_e4m3(const char* __restrict__ q_grp, const char* __restrict__ sv_seq,
-                                                int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, uint32_t tag = 0) {
+                                                int32_t n_sent, int32_t row_w, void* __restrict__ out_seq, const StepState& st = {}) {
     const int lane = threadIdx.x & 63;
     const int c = lane & 7, sub = lane >> 3;
     float qs[16];
@@ -311,7 +339,7 @@ __device__ __forceinline__ void score_wave_e4m3(const char* __restrict__ q_grp, 
         p[i] = dpp_add<0x4E>(p[i]);
         p[i] = dpp_add<0x124>(p[i]);                        // row_ror 4: lanes 4..7 of each group of 8 now hold the group's sum
     }
-    store_scores<TAGGED, 8>(out_seq, p, c - 4, row_w, n_sent, tag);        // (lanes 4 .. 7 of each group)
+    store_scores<TAGGED, 8>(out_seq, p, c - 4, row_w, n_sent, st);        // (lanes 4 .. 7 of each group)
 }
 
 constexpr int kScoreRowsPerWave16 = 16;
@@ -325,25 +353,21 @@ enum { kTableF32 = 4, kTableBf16 = 2, kTableE4m3 = 1 };       // bytes per eleme
 // of cu_sent down to eight candidates (dependent scalar loads), then eight consecutive boundaries in one scalar load,
 // which also gives the end of the first run; log2(B / 8) + 1 round trips, whatever the batch size.
 
-// The RPWV buckets [r0, r0 + RPWV) of the concatenated bucket axis, head h, by one wave.  TAGGED: `out` holds 64-bit
-// (score, tag) words, tags[pair] being the launch tag of (sequence, head) pair b * Hkv + h.
-template <int EB, int G, int SVB, int RPWV, bool TAGGED>
+// The RPWV buckets [r0, r0 + RPWV) of the concatenated bucket axis, head h, by one wave.
+template <int EB, int G, int SVB, int RPWV>
 __device__ __forceinline__ void score_group(const char* __restrict__ q, const char* __restrict__ semvec, const SeqView& v,
-                                            int32_t Hq, int h, int32_t r0, void* __restrict__ out,
-                                            const uint32_t* tags = nullptr) {
+                                            int32_t Hq, int h, int32_t r0, float* __restrict__ out) {
     const int32_t r1 = min(r0 + RPWV, v.S_total);
     auto run = [&](int b, int32_t first, int32_t n) {      // buckets [first, first + n) of the batch axis, sequence b
         const char* qg = q + ((int64_t)(b * Hq + h * G) * kHeadDim) * EB;
         const int64_t row = (int64_t)h * v.S_total + first;
-        void* dst = TAGGED ? static_cast<void*>(static_cast<unsigned long long*>(out) + row)
-                           : static_cast<void*>(static_cast<float*>(out) + row);
-        const uint32_t tag = TAGGED ? tags[b * (Hq / G) + h] : 0u;
+        float* dst = out + row;
         if (SVB == kTableF32)
-            score_wave_f32<EB, G, RPWV, TAGGED>(qg, reinterpret_cast<const float*>(semvec) + row * kHeadDim, n, 0, dst, tag);
+            score_wave_f32<EB, G, RPWV, false>(qg, reinterpret_cast<const float*>(semvec) + row * kHeadDim, n, 0, dst);
         else if (SVB == kTableBf16)
-            score_wave_bf16<EB, G, RPWV, TAGGED>(qg, semvec + row * kHeadDim * 2, n, 0, dst, tag);
+            score_wave_bf16<EB, G, RPWV, false>(qg, semvec + row * kHeadDim * 2, n, 0, dst);
         else
-            score_wave_e4m3<EB, G, RPWV, TAGGED>(qg, semvec + row * kHeadDim, n, 0, dst, tag);
+            score_wave_e4m3<EB, G, RPWV, false>(qg, semvec + row * kHeadDim, n, 0, dst);
     };
     if (!v.cu_sent) {                                      // one sequence
         run(0, r0, r1 - r0);
@@ -397,7 +421,7 @@ __global__ __launch_bounds__(kScoreWavesPerBlock * kWave) void score_kernel(cons
     asm volatile("" ::"s"(q), "s"(semvec), "s"(v.cu_sent), "s"(v.S_total), "s"(v.B), "s"(Hq), "s"(score));
     const int32_t r0 = (blockIdx.x * kScoreWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * RPWV;
     if (r0 >= v.S_total) return;
-    score_group<EB, G, SVB, RPWV, false>(q, semvec, v, Hq, blockIdx.y, r0, score);
+    score_group<EB, G, SVB, RPWV>(q, semvec, v, Hq, blockIdx.y, r0, score);
 }
 
 template <int EB, int G>
@@ -1036,16 +1060,6 @@ template <int EB, int DIMS = kHeadDim> struct Tile {                // DIMS: dim
     }
 };
 
-// Tag of a launch of the single-launch step for one pair: the pair's epoch after this launch (1 .. 2^26 - 1, never 0, so
-// zero-filled memory never looks valid) above the pair's number.  A word of memory carries a pair's current tag only if
-// a block of that pair wrote it in this launch: other pairs differ in the low bits, earlier launches in the epoch (which
-// repeats after 2^26 - 1 launches of the pair).
-__device__ __forceinline__ uint32_t step_tag(uint32_t epoch, int pair) {
-    uint32_t e = (epoch + 1u) & ((1u << (32 - kStepPairBits)) - 1u);
-    if (e == 0u) e = 1u;
-    return (e << kStepPairBits) | (uint32_t)pair;
-}
-
 constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
 // orders a wave's LDS accesses before it against those after it (other lanes of the wave wrote or will write the same words)
@@ -1115,61 +1129,81 @@ __device__ __forceinline__ void block_sums(const char* tiles, int stride, const 
 // kStep: blocks of a pair that merge
 __device__ __forceinline__ int merging_blocks(int G, int lg_merge) { return lg_merge >= 0 ? G << lg_merge : G >> -lg_merge; }
 
+// In the order in which the single-launch step needs them: what it takes to ask for the mean keys in the first two lines.
 struct AttArgs {
+    // kStep: the blocks of a (sequence, head) pair first score the pair's buckets between them
+    const char* q_score;      // [B][Hq][D]
+    const char* semvec;       // the layer's table [Hkv][S_total][D]
+    unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
+    unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
     const char* q;            // [B][Hq][D]
-    const char* Kb;           // kDirect: K_sel [B*Hkv][row_stride][D]; else the layer's pool [Hkv][T_total][D]
-    const char* Vb;
-    const int32_t* n_tok;     // kDirect, kIndirect: [B*Hkv]
-    const int32_t* tok_idx;   // kIndirect: [B*Hkv][idx_stride] positions local to the sequence
-    int32_t row_stride;       // kDirect
-    const float* score;       // kFused: [Hkv][S_total]
-    const int32_t* sent_off;  // kFused
-    const int32_t* sent_len;  // kFused
-    int32_t* tok_idx_out;     // kFused, nullable: [B*Hkv][idx_stride]
-    int32_t* n_tok_out;       // kFused, nullable: [B*Hkv]
-    int32_t idx_stride;       // kFused, kIndirect: max_budget (positions per pair in tok_idx / tok_idx_out)
-    int32_t budget_cap;       // budgets are clamped to this (the context's budget hint, at most max_budget)
+    float* out;
     SeqView v;
     int32_t Hkv;
+    int32_t sv_bytes;         // bytes per element of the table: 4, 2 or 1
+    int32_t score_stride;
+    int32_t lg_parts;         // kStep: log2 of the blocks per pair
+    int32_t parts;            // kStepRagged: blocks per pair, and 2^32 / that, rounded up
+    uint32_t per_part;
+    int32_t chunk;            // kStepRagged: tokens of an attending block (a multiple of 16, at most CHUNK), and 2^32 / that, rounded up
+    uint32_t per_chunk;
+    int32_t lg_merge;         // log2 of the blocks that merge one query head; -1: a block merges two heads
+    int32_t budget_cap;       // budgets are clamped to this (the context's budget hint, at most max_budget)
+    const int32_t* sent_off;  // kFused
+    const int32_t* sent_len;  // kFused
+    int32_t* n_tok_out;       // kFused, nullable: [B*Hkv]
+    const char* Kb;           // kDirect: K_sel [B*Hkv][row_stride][D]; else the layer's pool [Hkv][T_total][D]
+    const char* Vb;
+    int32_t* tok_idx_out;     // kFused, nullable: [B*Hkv][idx_stride]
+    unsigned long long* step_part;    // [blocks][step_part_words(G)] (value, tag) words: a block's sums [G][kHeadDim], then (reference, normaliser) [G]
+    float* lse;
+    int32_t idx_stride;       // kFused, kIndirect: max_budget (positions per pair in tok_idx / tok_idx_out)
+    int32_t wait_limit;       // rounds of polling before a block gives up
+    unsigned int* err_dev;    // set to 1 by a block that gave up
+    unsigned int* err_host;   // the same word in pinned host memory (device address), nullable
+    // the other forms
+    const int32_t* n_tok;     // kDirect, kIndirect: [B*Hkv]
+    const int32_t* tok_idx;   // kIndirect: [B*Hkv][idx_stride] positions local to the sequence
+    const float* score;       // kFused: [Hkv][S_total]
+    int32_t row_stride;       // kDirect
     int32_t max_splits;       // partial slots per query head (counted in 64-token chunks)
     float* part;
     float* ml;
     unsigned int* counter;
-    float* out;
-    float* lse;
-    // kStep: the blocks of a (sequence, head) pair first score the pair's buckets between them
-    const char* q_score;      // [B][Hq][D]
-    const char* semvec;       // the layer's table [Hkv][S_total][D]
-    int32_t sv_bytes;         // bytes per element of the table: 4, 2 or 1
-    int32_t lg_parts;         // kStep: log2 of the blocks per pair
-    int32_t lg_merge;         // log2 of the blocks that merge one query head; -1: a block merges two heads
-    unsigned int* step_epoch; // [pairs][kStepEpochStride]: launches of the single-launch step each pair has been through
-    unsigned long long* step_score;   // [pairs][score_stride] (score, tag) words
-    int32_t score_stride;
-    unsigned long long* step_part;    // [blocks][step_part_words(G)] (value, tag) words: a block's sums [G][kHeadDim], then (reference, normaliser) [G]
-    int32_t wait_limit;       // rounds of polling before a block gives up
-    unsigned int* err_dev;    // set to 1 by a block that gave up
-    unsigned int* err_host;   // the same word in pinned host memory (device address), nullable
-    // kStepRagged: blocks per pair, tokens of an attending block (a multiple of 16, at most CHUNK), and 2^32 / each, rounded up
-    int32_t parts, chunk;
-    uint32_t per_part, per_chunk;
 };
 
 enum { kDirect = 0, kFused = 1, kIndirect = 2, kStep = 3, kStepRagged = 4, kDirectDims = 5 };      // kStepRagged: any number of blocks, any share of the budget
 
-// Every argument is demanded at this point, so the kernel-argument loads go out in one batch at the top of the kernel;
-// left alone, the compiler loads each argument before its first use: one dependent round trip per branch, and a
-// scalar-cache miss for each new 64-byte line of the argument block.
-__device__ __forceinline__ void demand_args(const AttArgs& a) {
-    asm volatile("" ::"s"(a.q), "s"(a.Kb), "s"(a.Vb), "s"(a.n_tok), "s"(a.tok_idx), "s"(a.row_stride), "s"(a.score),
-                 "s"(a.sent_off), "s"(a.sent_len), "s"(a.tok_idx_out), "s"(a.n_tok_out), "s"(a.idx_stride), "s"(a.budget_cap), "s"(a.v.cu_tok),
-                 "s"(a.v.cu_sent), "s"(a.v.budget_arr), "s"(a.v.T_total), "s"(a.v.S_total), "s"(a.v.budget), "s"(a.v.B),
-                 "s"(a.Hkv), "s"(a.max_splits), "s"(a.part), "s"(a.ml), "s"(a.counter), "s"(a.out), "s"(a.lse));
+// Arguments are demanded together, so that their loads go out in one batch; left alone, the compiler loads each argument before its first use: one
+// dependent round trip per branch, and a scalar-cache miss for each new 64-byte line of the argument block.
+__device__ __forceinline__ void demand_seq_args(const AttArgs& a) {
+    asm volatile("" ::"s"(a.v.cu_tok), "s"(a.v.cu_sent), "s"(a.v.budget_arr), "s"(a.v.T_total), "s"(a.v.S_total), "s"(a.v.budget), "s"(a.Hkv), "s"(a.q), "s"(a.out));
 }
-template <bool RAGGED> __device__ __forceinline__ void demand_step_args(const AttArgs& a) {
-    if constexpr (RAGGED) asm volatile("" ::"s"(a.parts), "s"(a.chunk), "s"(a.per_part), "s"(a.per_chunk));
-    asm volatile("" ::"s"(a.q_score), "s"(a.semvec), "s"(a.sv_bytes), "s"(a.lg_parts), "s"(a.lg_merge), "s"(a.step_epoch), "s"(a.step_score),
-                 "s"(a.score_stride), "s"(a.step_part), "s"(a.wait_limit), "s"(a.err_dev), "s"(a.err_host));
+template <int MODE> __device__ __forceinline__ void demand_args(const AttArgs& a) {
+    if constexpr (MODE != kDirect && MODE != kDirectDims) demand_seq_args(a);
+    if constexpr (MODE == kFused)
+        asm volatile("" ::"s"(a.score), "s"(a.sent_off), "s"(a.sent_len), "s"(a.tok_idx_out), "s"(a.n_tok_out), "s"(a.idx_stride), "s"(a.budget_cap));
+    else
+        asm volatile("" ::"s"(a.q), "s"(a.n_tok), "s"(a.tok_idx), "s"(a.row_stride), "s"(a.idx_stride), "s"(a.Hkv), "s"(a.out));
+    asm volatile("" ::"s"(a.Kb), "s"(a.Vb), "s"(a.lse), "s"(a.max_splits), "s"(a.part), "s"(a.ml), "s"(a.counter));
+}
+// kStep, first: what the scores need, and a word of each line of the rest, which is on its way to the scalar cache then
+template <bool RAGGED> __device__ __forceinline__ void demand_score_args(const AttArgs& a) {
+    demand_seq_args(a);
+    if constexpr (RAGGED) asm volatile("" ::"s"(a.parts), "s"(a.per_part), "s"(a.chunk));
+    else asm volatile("" ::"s"(a.lg_parts));
+    asm volatile("" ::"s"(a.q_score), "s"(a.semvec), "s"(a.step_epoch), "s"(a.step_score), "s"(a.score_stride), "s"(a.sv_bytes), "s"(a.lg_merge), "s"(a.budget_cap),
+                 "s"(a.idx_stride));
+}
+// ... and after the scores, while others may still be at theirs, all the rest.  They are read through a pointer formed there, else the compiler asks for them with
+// the first ones, has no registers for them and waits for them to move them away.
+__device__ __forceinline__ void load_attend_args(AttArgs& a) {
+    const AttArgs __attribute__((address_space(4))) * p = (const AttArgs __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    a.sent_off = p->sent_off; a.sent_len = p->sent_len; a.n_tok_out = p->n_tok_out; a.Kb = p->Kb; a.Vb = p->Vb; a.tok_idx_out = p->tok_idx_out;
+    a.step_part = p->step_part; a.lse = p->lse; a.idx_stride = p->idx_stride; a.wait_limit = p->wait_limit; a.err_dev = p->err_dev; a.err_host = p->err_host;
+    asm volatile("" ::"s"(a.sent_off), "s"(a.sent_len), "s"(a.n_tok_out), "s"(a.Kb), "s"(a.Vb), "s"(a.tok_idx_out), "s"(a.step_part), "s"(a.lse), "s"(a.idx_stride),
+                 "s"(a.wait_limit), "s"(a.err_dev), "s"(a.err_host));
 }
 
 // 16 bytes of a K/V row.  POOL: rows straight from the pool are read once (non-temporal: 32 layers of one 32K sequence 456 ->
@@ -1184,14 +1218,15 @@ constexpr int kDimsPerBlock = 32, kMaxDirectDims = 416, kMaxDirectDims1 = 320;  
 // them.  Us a call, 32 query heads on 8: 257 tokens 6.02 -> 5.92 (5.98 without the quarters); with the two lanes an output of block_sums 200 5.45 -> 4.97, 256 5.70 -> 5.22,
 // 257 6.05 -> 5.78, 384 6.86 -> 6.34; 64 on 8: 256 6.15 -> 5.82; 32 on 32: 256 5.57 -> 5.37.  Fewer waves, heads first: 8 on 8, 64 tokens 3.03 -> 3.15, 128 3.54 -> 3.70; 32
 // on 32, 64 tokens 3.57 -> 3.25.
-template <int MODE, int CHUNK> constexpr bool kPairFirst = MODE == kDirectDims && CHUNK / 16 >= kBlockWaves;
+template <int MODE, int CHUNK> constexpr bool kPairFirst = MODE == kStep || MODE == kStepRagged || (MODE == kDirectDims && CHUNK / 16 >= kBlockWaves);
 // ceil(n / d) with `per` = 2^32 / d rounded up; exact while n + d <= 2^32 / d
 __device__ __forceinline__ int32_t ceil_div(int32_t n, int32_t d, uint32_t per) { return (int32_t)__umulhi((uint32_t)(n + d - 1), per); }
 
 // CHUNK = retrieved tokens per block, a tile of 16 for each of CHUNK / 16 waves (512: two tiles a wave): the smallest whose blocks all run
 // at once, see launch_step, launch_select_attend and launch_attend.
 template <int EB, int G, int MODE, int CHUNK>
-__global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
+__global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
+    AttArgs a = args;
     constexpr int kDims = MODE == kDirectDims ? kDimsPerBlock : kHeadDim;         // dims of the output that a block makes
     constexpr bool kRowsDirect = MODE == kDirect || MODE == kDirectDims;
     using X = Tile<EB, kDims>;
@@ -1221,27 +1256,32 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     constexpr int kMergeWords = kStepping ? 3 * (kBlockThreads + kWave) : 1;
     __shared__ float sm_merge[kMergeWords];                                   // kStep: the merging block's scratch
 
-    // kStep: a one-dimensional grid, pair fastest, so that the hardware's round-robin of consecutive blocks over the XCDs
-    // keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs
-    const int n_pairs = a.v.B * a.Hkv;
-    const int bh = kStepping ? (int)(blockIdx.x % (unsigned)n_pairs) : kPairFirst<MODE, CHUNK> ? (int)blockIdx.x : (int)blockIdx.y;
-    const int split = kStepping ? (int)(blockIdx.x / (unsigned)n_pairs) : MODE == kDirectDims ? 0 : (int)blockIdx.x;
-    const int dim0 = MODE == kDirectDims ? (int)(kPairFirst<MODE, CHUNK> ? blockIdx.y : blockIdx.x) * kDims : 0;        // first of the block's dims
-    const int b = bh / a.Hkv, h = bh % a.Hkv;
+    // Heads, sequences and splits are the dimensions of the grid (nothing has to be divided); where head and sequence are fastest (kPairFirst), the hardware's
+    // round-robin of consecutive blocks over the XCDs keeps the blocks of a pair together whenever the number of pairs is a multiple of the number of XCDs.
+    constexpr bool kFirst = kPairFirst<MODE, CHUNK>;
+    const int h = (int)(kFirst ? blockIdx.x : blockIdx.y), b = (int)(kFirst ? blockIdx.y : blockIdx.z), part = (int)(kFirst ? blockIdx.z : blockIdx.x);
+    const int split = MODE == kDirectDims ? 0 : part;
+    const int dim0 = MODE == kDirectDims ? part * kDims : 0;        // first of the block's dims
+    const int bh = b * a.Hkv + h;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int t16 = lane & 15, qd = lane >> 4;
-    const int Hq = a.Hkv * G;
-    const int64_t qhead0 = (int64_t)b * Hq + (int64_t)h * G;      // first query head of the group
-    demand_args(a);
+    const int n_pairs = a.v.B * a.Hkv;
+    const int64_t qhead0 = (int64_t)bh * G;                       // first query head of the group
+    if constexpr (kStepping) demand_score_args<MODE == kStepRagged>(a);
+    else demand_args<MODE>(a);
+    // What the block does before it asks for its first mean keys is on the way of every launch.  Us per layer, grids of one dimension (two divisions), the sequence's
+    // numbers one after the other, all arguments at once (there is no room for them: their waits came first too) and the tag formed here / this: 4096 tokens, fp32
+    // 10.4 / 9.9, 32768 11.7 / 11.25, 131072 16.45 / 16.4, 6 sequences of 1900 to 21001 18.0 / 17.35, 3 of 8192 15.9 / 15.6.
     // kStep: the tag of this launch for this pair.  Every launch of the pair ends with its epoch advanced by one (block 0,
     // after it has seen the partial of every attending block, each of which had seen every score of the pair: so every
     // block whose tag matters has read the epoch by then), and the pair's number makes tags of different pairs differ.
     uint32_t tag = 0;
+    StepState state = {};
     if constexpr (kStepping) {
-        demand_step_args<MODE == kStepRagged>(a);
-        tag = step_tag(ld_agent(a.step_epoch + bh * kStepEpochStride), bh);
+        state = {ld_agent(a.step_epoch + bh * kStepEpochStride), bh};
     }
-    const Seq sq = seq_of(a.v, b);
+    Seq sq = {};
+    if constexpr (!kRowsDirect) sq = seq_of_step(a.v, b);
     const int32_t chunk = MODE == kStepRagged ? a.chunk : CHUNK;        // tokens of a block
     auto blocks_of = [&](int32_t tokens) { return MODE == kStepRagged ? ceil_div(tokens, chunk, a.per_chunk) : (tokens + CHUNK - 1) / CHUNK; };
     const int32_t j0 = split * chunk;
@@ -1294,19 +1334,21 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             };
             if (a.sv_bytes == kTableF32)
                 score_table(std::integral_constant<int, 4>{}, [&](auto rows, int32_t rw) {
-                    score_wave_f32<EB, G, decltype(rows)::value, true>(qg, reinterpret_cast<const float*>(a.semvec) + row0 * kHeadDim, hi, rw, sc_out, tag);
+                    score_wave_f32<EB, G, decltype(rows)::value, true>(qg, reinterpret_cast<const float*>(a.semvec) + row0 * kHeadDim, hi, rw, sc_out, state);
                 });
             else if (a.sv_bytes == kTableBf16)
                 score_table(std::integral_constant<int, 4>{}, [&](auto rows, int32_t rw) {
-                    score_wave_bf16<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim * 2, hi, rw, sc_out, tag);
+                    score_wave_bf16<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim * 2, hi, rw, sc_out, state);
                 });
             else
                 score_table(std::integral_constant<int, 8>{}, [&](auto rows, int32_t rw) {
-                    score_wave_e4m3<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim, hi, rw, sc_out, tag);
+                    score_wave_e4m3<EB, G, decltype(rows)::value, true>(qg, a.semvec + row0 * kHeadDim, hi, rw, sc_out, state);
                 });
             SKV_T(12);
+            tag = state.tag();
             // Blocks that neither attend (no position of theirs can hold a token: n <= budget) nor merge are done.
             if (split >= merging_blocks(G, a.lg_merge) && j0 >= budget) return;
+            load_attend_args(a);
         } else {
             if (split > 0 && j0 >= budget) return;                // n <= budget: nothing for this split
         }
@@ -1350,7 +1392,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     auto presence = [&]() {
         if constexpr (kStepping) {
             if (tid == 0)                                         // a block that gave up publishes nothing valid
-                st_tagged(a.step_part + (int64_t)blockIdx.x * step_part_words(G) + G * kHeadDim, -INFINITY, step_ok ? tag : 0u);
+                st_tagged(a.step_part + (int64_t)(split * n_pairs + bh) * step_part_words(G) + G * kHeadDim, -INFINITY, step_ok ? tag : 0u);
         }
     };
     // block 0: the words of blocks first .. (blocks of the pair that run the selection) - 1 carry the tag (bounded wait);
@@ -1402,7 +1444,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
     unsigned long long* my_part = nullptr;
     uint32_t part_tag = 0;
     if constexpr (kStepping) {
-        my_part = a.step_part + (int64_t)blockIdx.x * step_part_words(G);
+        my_part = a.step_part + (int64_t)(split * n_pairs + bh) * step_part_words(G);
         part_tag = step_ok ? tag : 0u;                            // a block that gave up publishes nothing valid
     }
     if (has_work) {
@@ -1439,7 +1481,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs a) {
             for (int ps = 0; ps < kPasses; ++ps) {
                 // Pool row of the tile's token t16 (K) and of the tokens whose value row this lane loads; rows past the chunk's end (and
                 // positions outside the sequence) are clamped to a valid row, loaded anyway and masked afterwards.
-                const int tile = (kPairFirst<MODE, CHUNK> ? (w + (int)blockIdx.y * (kTiles * kDims / kHeadDim)) % kTiles : w) + kTiles * ps, jj = 16 * tile + t16;
+                const int tile = (MODE == kDirectDims && kFirst ? (w + part * (kTiles * kDims / kHeadDim)) % kTiles : w) + kTiles * ps, jj = 16 * tile + t16;
                 if (ps > 0 && 16 * tile >= cnt) {                     // (wave-uniform) no second tile
                     vm[ps] = 0;
 #pragma unroll
@@ -1974,10 +2016,10 @@ template <int EB, int G, int CHUNK>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_attend_stream_kernel(AttArgs a) {
     static_assert(CHUNK % kWave == 0 && CHUNK <= kStreamMaxChunk, "the row table holds kStreamMaxChunk positions");
     __shared__ StreamShared<EB, CHUNK> ss;
-    const int bh = blockIdx.y, b = bh / a.Hkv, h = bh % a.Hkv, split = blockIdx.x;
+    const int h = blockIdx.y, b = blockIdx.z, bh = b * a.Hkv + h, split = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
-    demand_args(a);
-    const Seq sq = seq_of(a.v, b);
+    demand_args<kFused>(a);
+    const Seq sq = seq_of_step(a.v, b);
     const int32_t j0 = split * CHUNK;
     SKV_T(0);
 
@@ -2027,7 +2069,7 @@ template <int EB, int CHUNK>
 static hipError_t launch_select_attend_stream_g(Ctx* c, const AttArgs& a) {
     int n_splits = (c->budget_cap + CHUNK - 1) / CHUNK;
     if (n_splits < 1) n_splits = 1;       // block 0 still writes the empty-selection result
-    const dim3 grid(n_splits, a.v.B * c->d.n_kv_heads), block(kBlockThreads);
+    const dim3 grid(n_splits, c->d.n_kv_heads, a.v.B), block(kBlockThreads);
     switch (c->G) {
         case 1: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 1, CHUNK>), grid, block, 0, c->stream, a); break;
         case 2: hipLaunchKernelGGL((select_attend_stream_kernel<EB, 2, CHUNK>), grid, block, 0, c->stream, a); break;
@@ -2040,8 +2082,8 @@ static hipError_t launch_select_attend_stream_g(Ctx* c, const AttArgs& a) {
 
 template <int EB, int MODE, int CHUNK>
 static hipError_t launch_attend_g(Ctx* c, const AttArgs& a, int32_t n_splits) {
-    const int pairs = a.v.B * c->d.n_kv_heads;
-    const dim3 grid = kPairFirst<MODE, CHUNK> ? dim3(pairs, n_splits) : dim3(n_splits, pairs), block(kBlockThreads);
+    const int H = c->d.n_kv_heads, B = a.v.B;
+    const dim3 grid = kPairFirst<MODE, CHUNK> ? dim3(H, B, n_splits) : dim3(n_splits, H, B), block(kBlockThreads);
     switch (c->G) {
         case 1: hipLaunchKernelGGL((attend_kernel<EB, 1, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
         case 2: hipLaunchKernelGGL((attend_kernel<EB, 2, MODE, CHUNK>), grid, block, 0, c->stream, a); break;
@@ -2181,8 +2223,9 @@ static int step_blocks_per_cu() {
 }
 
 template <int EB, int MODE, int CHUNK>
-static hipError_t launch_step_g(Ctx* c, const AttArgs& a, int n_blocks, bool* launched) {
-    const dim3 grid(n_blocks), block(kBlockThreads);
+static hipError_t launch_step_g(Ctx* c, const AttArgs& a, int parts, bool* launched) {
+    const dim3 grid(c->d.n_kv_heads, a.v.B, parts), block(kBlockThreads);
+    const int n_blocks = c->d.n_kv_heads * a.v.B * parts;
     int per_cu = 0;
     switch (c->G) {
         case 1: per_cu = step_blocks_per_cu<EB, 1, MODE, CHUNK>(); break;
@@ -2256,10 +2299,9 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     a.step_part = c->step_part; a.wait_limit = c->wait_limit;
     a.err_dev = c->err_dev; a.err_host = c->err_host_dev;
     const bool bf16 = c->d.kv_dtype == SKV_BF16;
-    const int blocks = pairs * parts;
     auto go = [&](auto mode, auto cap) {
         constexpr int M = decltype(mode)::value, C = decltype(cap)::value;
-        return bf16 ? launch_step_g<2, M, C>(c, a, blocks, launched) : launch_step_g<4, M, C>(c, a, blocks, launched);
+        return bf16 ? launch_step_g<2, M, C>(c, a, parts, launched) : launch_step_g<4, M, C>(c, a, parts, launched);
     };
     using std::integral_constant;
     if (even && chunk == kAttChunk) return go(integral_constant<int, kStep>{}, integral_constant<int, kAttChunk>{});
@@ -2268,7 +2310,7 @@ hipError_t launch_step(Ctx* c, const void* q_score, const void* q_attn, const vo
     if (chunk == kAttChunk) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunk>{});
     if (chunk <= kAttChunkMid) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkMid>{});
     if (chunk <= kAttChunkWide) return go(integral_constant<int, kStepRagged>{}, integral_constant<int, kAttChunkWide>{});
-    return launch_step_g<2, kStepRagged, 2 * kAttChunkWide>(c, a, blocks, launched);
+    return launch_step_g<2, kStepRagged, 2 * kAttChunkWide>(c, a, parts, launched);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -13,7 +13,7 @@ extern __device__ unsigned long long g_stamps[kStampBlocks * kStampSlots];
 #define SKV_T(k)                                                                                       \
     do {                                                                                               \
         if (threadIdx.x == 0) {                                                                        \
-            const unsigned skv_blk = blockIdx.y * gridDim.x + blockIdx.x;                              \
+            const unsigned skv_blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;                          \
             if (skv_blk < skv::kStampBlocks) skv::g_stamps[skv_blk * skv::kStampSlots + (k)] = wall_clock64(); \
         }                                                                                              \
     } while (0)
