@@ -470,12 +470,14 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 // increasing, so the retrieved set is {i : (total length ranked before i) + len_i <= budget}.  The
 // first bucket that overflows (the "cut") is found without sorting, by a length-weighted radix select
 // on an order-preserving 32-bit image of the score: 11 + 11 + 10 bit digits, most significant first.
-// Per pass: LDS atomics build a histogram of (count, total length) per digit; thread t owns digits
-// 2047-2t and 2046-2t, so a block-wide prefix sum in thread order (DPP wave scan + 16 wave totals) is
-// the running total from the top digit down, and exactly one thread sees the budget crossed inside
-// its two digits.  The three histograms are zeroed up front.  The search stops as soon as the crossing
-// digit holds a single bucket (typically after two passes); buckets with exactly the cut's score are
-// resolved in id order by a scan.
+// Per pass: LDS atomics build a histogram of (count, total length) per digit and the total lengths of
+// groups of 32 digits; after the one barrier of the pass every wave finds the crossing digit by itself: a lane
+// per group, from the top one down, a scan and the lane that sees the budget crossed, then a lane per digit
+// of that group.  (The block finding it together, thread t with digits 2047-2t and 2046-2t, a block scan
+// and the crossing thread telling the others, takes two more barriers and trips to LDS a pass: keys in
+// registers to cut known 1.1 us, this way 0.7; a layer of the single-launch step of 32768 tokens 11.3 -> 11.1 us.)  The three
+// histograms are zeroed up front.  The search stops as soon as the crossing digit holds a single bucket
+// (typically after one pass); buckets with exactly the cut's score are resolved in id order by a scan.
 //
 // The routine is written for few instructions per wave (a wave issues one instruction every 4+
 // cycles, so instruction count is latency) and 32-bit arithmetic throughout (token totals < 2^31):
@@ -487,12 +489,13 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 
 constexpr int kSelKreg = 6;                                   // 1024 threads x 6 buckets in registers: S <= 6144
 constexpr int kBins = 2048;                                   // 11-bit digits (the last pass uses 1024)
+constexpr int kGroupBins = kBins / kWave;                     // digits of a group: 64 groups, a lane each
 
 struct SelectShared {
     unsigned long long hist[3][kBins];                        // packed (count << 32 | total length) per digit
-    uint32_t wave_tot[6][kBlockWaves];                        // one slot per block scan
-    int32_t res[3][4];                                        // per pass: crossing digit (-1: none), carry, count
-    int32_t poll[3];                                          // tagged scores: [0] set by a thread whose wait ran out
+    uint32_t group[3][kWave];                                 // total length per group of 32 digits
+    uint32_t wave_tot[3][kBlockWaves];                        // one slot per block scan
+    int32_t gave_up;                                          // tagged scores: set by a thread whose wait ran out
     __attribute__((aligned(16))) uint32_t wmax[kBlockWaves];  // largest key per wave
 };
 
@@ -521,7 +524,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
 
     uint32_t rkey[KREG];
     int32_t rlen[KREG], roff[KREG];
-    static_assert(KREG % 2 == 0, "the register-held buckets are loaded in pairs");
+    static_assert(KREG <= 2 || KREG % 2 == 0, "the register-held buckets are loaded in pairs");
 #pragma unroll
     for (int i = 0; i < KREG; ++i) { rkey[i] = 0; rlen[i] = 0; roff[i] = 0; }
     if (KREG > 2 && S >= 2) {
@@ -559,10 +562,10 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         unsigned long long* h = &sh.hist[0][0];
 #pragma unroll
         for (int i = 0; i < 3 * kBins / kBlockThreads; ++i) h[i * kBlockThreads + tid] = 0;
-        if (tid < 3) sh.res[tid][0] = -1;
+        if (tid < 3 * kWave) (&sh.group[0][0])[tid] = 0;
     };
     zero_hist();
-    if (tid == 0) sh.poll[0] = 0;
+    if (tid == 0) sh.gave_up = 0;
     // The largest key of the block (over all buckets read, with or without tokens: an upper bound of the keys that take
     // part is all that is needed): a wave's maximum goes to LDS ahead of a barrier that is there anyway.
     uint32_t my_max = 0;
@@ -615,7 +618,8 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
 #pragma unroll
             for (int i = 0; i < KREG; ++i) {
                 if (i < kpt) {
-                    key_lds[i * kBlockThreads + tid] = kk[i];
+                    if constexpr (KREG == 1) rkey[i] = kk[i];          // a thread's word is its bucket's
+                    else key_lds[i * kBlockThreads + tid] = kk[i];
                     my_max = max(my_max, score_key(__uint_as_float(kk[i])));
                 }
             }
@@ -640,10 +644,10 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             for (int i = 0; i < KREG; ++i) my_max = max(my_max, score_key(__uint_as_float(rkey[i])));
         }
         share_max();
-        if (!mine) sh.poll[0] = 1;
+        if (!mine) sh.gave_up = 1;
         __syncthreads();
-        if (sh.poll[0] != 0 && ok_out) *ok_out = false;
-        if (strided) {
+        if (sh.gave_up != 0 && ok_out) *ok_out = false;
+        if (KREG > 1 && strided) {
 #pragma unroll
             for (int i = 0; i < KREG; ++i)
                 if (i < kpt) rkey[i] = key_lds[s0 + i];    // s0 + i < kpt * 1024 <= KREG * 1024
@@ -654,15 +658,14 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             if (s0 + i >= S) rlen[i] = 0;                  // slots past the end take part in nothing
         }
     }
-    uint32_t kmax = 0;
-    {
-        const uint4* wm4 = reinterpret_cast<const uint4*>(sh.wmax);
-#pragma unroll
-        for (int q4 = 0; q4 < kBlockWaves / 4; ++q4) {
-            const uint4 t = wm4[q4];
-            kmax = max(max(kmax, max(t.x, t.y)), max(t.z, t.w));
-        }
-    }
+    // the 16 waves' maxima, one a lane of every row of 16
+    static_assert(kBlockWaves == 16, "a wave's maximum per lane of a DPP row");
+    uint32_t kmax = sh.wmax[tid & (kBlockWaves - 1)];
+    kmax = dpp_max_u32<0x128, 0xf>(kmax);                      // row_ror 8, 4, 2, 1
+    kmax = dpp_max_u32<0x124, 0xf>(kmax);
+    kmax = dpp_max_u32<0x122, 0xf>(kmax);
+    kmax = dpp_max_u32<0x121, 0xf>(kmax);
+    kmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmax);
     SKV_T(1);
 
     // ---- weighted radix select of the cut ----------------------------------------------------------
@@ -690,38 +693,39 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         for (int pass = 0; pass < 3; ++pass) {
             const int bits = pass < 2 ? 11 : (near ? 2 : 10), nbins = 1 << bits, nshift = shift - bits;
             unsigned long long* H = sh.hist[pass];
+            auto count = [&](uint32_t k, int32_t ln) {
+                const uint32_t digit = (k >> nshift) & (nbins - 1);
+                atomicAdd(&H[digit], (1ull << 32) | (unsigned long long)(uint32_t)ln);
+                atomicAdd(&sh.group[pass][digit / kGroupBins], (uint32_t)ln);
+            };
 #pragma unroll
-            for (int i = 0; i < KREG; ++i) {
-                if (i < kpt && rlen[i] > 0 && (shift == 32 || (rkey[i] >> shift) == prefix))
-                    atomicAdd(&H[(rkey[i] >> nshift) & (nbins - 1)], (1ull << 32) | (unsigned long long)(uint32_t)rlen[i]);
-            }
+            for (int i = 0; i < KREG; ++i)
+                if (i < kpt && rlen[i] > 0 && (shift == 32 || (rkey[i] >> shift) == prefix)) count(rkey[i], rlen[i]);
             for (int i = KREG; i < kpt; ++i) {
                 if (s0 + i < S && len[s0 + i] > 0) {           // a bucket without tokens takes part in nothing
                     const uint32_t k = to_rank(score_key(ldsc(s0 + i)));
-                    if (shift == 32 || (k >> shift) == prefix)
-                        atomicAdd(&H[(k >> nshift) & (nbins - 1)], (1ull << 32) | (unsigned long long)(uint32_t)len[s0 + i]);
+                    if (shift == 32 || (k >> shift) == prefix) count(k, len[s0 + i]);
                 }
             }
             __syncthreads();
-            // thread order == descending digit order: thread t owns digits nbins-1-2t and nbins-2-2t
-            const int d1 = nbins - 1 - 2 * tid;
-            const unsigned long long v1 = d1 >= 0 ? H[d1] : 0ull, v0 = d1 >= 1 ? H[d1 - 1] : 0ull;
-            const uint32_t l1 = (uint32_t)v1, l0 = (uint32_t)v0;
-            uint32_t total;
-            const uint32_t incl = block_scan_u32(l1 + l0, sh.wave_tot[pass], &total);
-            const uint32_t above1 = (uint32_t)carry + incl - l1 - l0, above0 = above1 + l1;
-            if (l1 > 0 && above1 <= (uint32_t)budget && above1 + l1 > (uint32_t)budget) {
-                sh.res[pass][0] = d1; sh.res[pass][1] = (int32_t)above1; sh.res[pass][2] = (int32_t)(v1 >> 32);
-            }
-            if (l0 > 0 && above0 <= (uint32_t)budget && above0 + l0 > (uint32_t)budget) {
-                sh.res[pass][0] = d1 - 1; sh.res[pass][1] = (int32_t)above0; sh.res[pass][2] = (int32_t)(v0 >> 32);
-            }
-            __syncthreads();
-            const int digit = sh.res[pass][0];
-            if (digit < 0) { found_none = true; break; }           // the buckets of this attempt all fit (only possible in pass 0)
+            // The lane whose digits, `own` tokens of them, take the running total past the budget (none: -1); carry: the total above it.
+            const int lane = tid & (kWave - 1);
+            auto crossing = [&](uint32_t own) -> int {
+                const uint32_t above = (uint32_t)carry + wave_scan_u32(own) - own;
+                const unsigned long long at = __ballot(above <= (uint32_t)budget && above + own > (uint32_t)budget);
+                if (at == 0ull) return -1;
+                const int l = __builtin_ctzll(at);
+                carry = __builtin_amdgcn_readlane((int)above, l);
+                return l;
+            };
+            const int grp = crossing(sh.group[pass][kWave - 1 - lane]);
+            if (grp < 0) { found_none = true; break; }             // the buckets of this attempt all fit (only possible in pass 0)
+            const int top = (kWave - 1 - grp) * kGroupBins + kGroupBins - 1;                  // the group's highest digit
+            const unsigned long long v = lane < kGroupBins ? H[top - lane] : 0ull;
+            const int sub = crossing((uint32_t)v);
+            const int digit = top - sub;
+            cut_cnt = __builtin_amdgcn_readlane((int)(v >> 32), sub);
             prefix = (shift == 32) ? (uint32_t)digit : ((prefix << bits) | (uint32_t)digit);
-            carry = sh.res[pass][1];
-            cut_cnt = sh.res[pass][2];
             shift = nshift;
             if (cut_cnt == 1) break;                               // the cut is unique: it is the bucket that overflows
         }
@@ -731,7 +735,8 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         near = false;
 #pragma unroll
         for (int i = 0; i < KREG; ++i) rkey[i] = kmax - ~rkey[i];  // back to the plain keys
-        zero_hist();                                               // (every thread is past its reads of the first attempt)
+        __syncthreads();                                           // every wave is past its reads of the first attempt
+        zero_hist();
         __syncthreads();
     }
     const bool ties = !select_all && cut_cnt > 1;              // then shift == 0: several buckets share the cut's score
@@ -751,7 +756,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         uint32_t mine = 0;
         for_items([&](int, int32_t, uint32_t k, int32_t ln, int32_t) { if (k == prefix) mine += (uint32_t)ln; });
         uint32_t tot;
-        tie_run = block_scan_u32(mine, sh.wave_tot[3], &tot) - mine;
+        tie_run = block_scan_u32(mine, sh.wave_tot[0], &tot) - mine;
     }
     auto chosen = [&](uint32_t k, int32_t ln, uint32_t& tie_acc) -> bool {
         if (select_all) return true;
@@ -775,9 +780,9 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             if (s0 + i < S && len[s0 + i] > 0 && chosen(to_rank(score_key(ldsc(s0 + i))), len[s0 + i], t)) { my_tok += (uint32_t)len[s0 + i]; my_cnt += 1; }
     }
     uint32_t tot_tok, tot_cnt = 0;
-    uint32_t pos_tok = block_scan_u32(my_tok, sh.wave_tot[4], &tot_tok) - my_tok;
+    uint32_t pos_tok = block_scan_u32(my_tok, sh.wave_tot[1], &tot_tok) - my_tok;
     uint32_t pos_cnt = 0;
-    if (COUNT) pos_cnt = block_scan_u32(my_cnt, sh.wave_tot[5], &tot_cnt) - my_cnt;
+    if (COUNT) pos_cnt = block_scan_u32(my_cnt, sh.wave_tot[2], &tot_cnt) - my_cnt;
     if (my_cnt != 0) {
 #pragma unroll
         for (int i = 0; i < KREG; ++i) {
@@ -1370,7 +1375,11 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
         if constexpr (kStepping) {                            // the scores are being written by the pair's blocks
             const float* tsc = reinterpret_cast<const float*>(a.step_score + (int64_t)bh * a.score_stride);
             uint32_t* sm_keys = reinterpret_cast<uint32_t*>(sm + kSelBytes);
-            if (sq.n_sent <= 2 * kBlockThreads)
+            // at most one bucket a thread: no keys through LDS, a third of the walks.  With the search above, us per layer: 4096 tokens, fp32, 10.1 -> 9.45, 6 sequences
+            // of 1900 to 21001 tokens 17.2 -> 16.3
+            if (sq.n_sent <= kBlockThreads)
+                select_block<1, false, true>(tsc, len, off, sq.n_sent, budget, sel_sh, mark, &nsel, &ntok, tag, a.wait_limit, &step_ok);
+            else if (sq.n_sent <= 2 * kBlockThreads)
                 select_block<2, false, true>(tsc, len, off, sq.n_sent, budget, sel_sh, mark, &nsel, &ntok, tag, a.wait_limit, &step_ok, sm_keys);
             else
                 select_block<kSelKreg, false, true>(tsc, len, off, sq.n_sent, budget, sel_sh, mark, &nsel, &ntok, tag, a.wait_limit, &step_ok, sm_keys);

@@ -319,6 +319,19 @@ def test_select_hand_made_scores(U, oracle32):
         _check_select(U, oracle32, wide, lens, int(rng.integers(1, 1500)))
 
 
+def test_select_cut_at_the_edges_of_digits_and_their_groups(U, oracle32):
+    """The search ranks by the distance below the best key, in steps of 2^13 (a digit) and 2^18 (a group of digits) up to 2^24, beyond that by
+    the key itself: the cut in the first and last digit of groups, in the first and last group and on both sides of 2^24, for every budget."""
+    edges = [k << 13 for k in (1, 31, 32, 33, 64, 2016, 2047, 2048)] + [1 << 25, 1 << 29]
+    below = sorted({0, 2} | {e + d for e in edges for d in (-1, 0, 1)})
+    rng = np.random.default_rng(5)
+    order = rng.permutation(len(below))
+    score = (np.uint32(0x7f000000) - np.asarray(below, dtype=np.uint32)[order]).view(np.float32)[None, :]
+    lens = rng.integers(1, 4, size=len(below))
+    for budget in range(1, int(lens.sum()) + 2):
+        _check_select(U, oracle32, score, lens, budget)
+
+
 # ----------------------------------------------------------------------------- attention edge cases
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -589,6 +602,13 @@ def test_fused_single_launch_shares_of_whole_lines(U, oracle32, B, S, dtype, Hq,
     """The single launch's blocks score up to 48 buckets as they come, more in shares of 16, rounded up, so that the last blocks of a pair may have fewer or none."""
     wl = gen.CFG1.scaled(n_layers=1, n_q_heads=Hq, batch=B, t_range=(3 * S, 3 * S), budgets=(500,), len_dist=("fixed", 3), dtype=dtype)
     _fused_case(U, oracle32, wl, seed=81, layers=[0], sv_dtype=sv_dtype)
+
+
+@pytest.mark.parametrize("B,S", [(1, 1023), (1, 1024), (1, 1025), (3, 1024), (1, 2048), (1, 2049)])
+def test_fused_single_launch_buckets_per_thread(U, oracle32, B, S):
+    """The selection on both sides of one and of two buckets a thread."""
+    wl = gen.CFG1.scaled(n_layers=1, batch=B, t_range=(2 * S, 2 * S), budgets=(300,), len_dist=("fixed", 2))
+    _fused_case(U, oracle32, wl, seed=82, layers=[0])
 
 
 # dims of a query head that a block merges (256: of two heads): 256, 128, 64 and 32, from the fewest to the most partial results of each
