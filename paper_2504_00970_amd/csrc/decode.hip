@@ -983,6 +983,10 @@ __device__ __forceinline__ float sum_quads(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// of lane (t + 16 - N) % 16 of the row of 16
+template <int N> __device__ __forceinline__ float of_row_turned(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N /* row_ror */, 0xf, 0xf, false));
+}
 // of the lane l ^ 8
 __device__ __forceinline__ float other_eight(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128 /* row_ror:8 */, 0xf, 0xf, false)); }
 // the larger of the lanes l and l ^ 32, in both
@@ -1099,36 +1103,78 @@ template <int NT> struct WaveSums {
         sum[head][w] = l;
     }
 };
+// lane N of the lane's row of 16
+template <int N> __device__ __forceinline__ float of_row(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + N /* row_newbcast */, 0xf, 0xf, false));
+}
 // A barrier later: the block's output relative to its common reference, from the sums that NT waves left `stride` bytes apart, each relative to
-// the wave's own max.  put(g, d, sum, reference, normaliser) for every head and dim: consecutive threads on consecutive heads as the sums lie (the
-// streaming kernel's 16 waves: 64 sequences 1-2 % faster), or on consecutive dims as the result lies (tagged words: 2 % faster).  Where 16 waves are added up for
-// at most 512 outputs, the two halves of a wave take half of them each (257 tokens, 128 outputs: 5.92 -> 5.78 us; with 4 lanes an output 5.79, with 8 5.98;
-// 8 waves over two lanes: 512 tokens 7.32 -> 7.45, 4 waves: the step of 7351 tokens 10.40 -> 10.48).
-template <int G, int NT, bool HEAD_FAST, int DIMS = kHeadDim, typename Put>
-__device__ __forceinline__ void block_sums(const char* tiles, int stride, const WaveSums<NT>& ws, Put put) {
-    constexpr int kOuts = G * DIMS, kLanes = !HEAD_FAST && NT == 16 && 2 * kOuts <= kBlockThreads ? 2 : 1, kWaves = NT / kLanes;
-    static_assert(kWaves * kLanes == NT && kWaves % 4 == 0 && kOuts * kLanes <= kBlockThreads && (kLanes == 1 || kOuts % (kWave / kLanes) == 0), "every output at once, both lanes of each");
-    const int lane = threadIdx.x & 63, i = (int)(threadIdx.x >> 6) * (kWave / kLanes) + lane % (kWave / kLanes), k0 = lane / (kWave / kLanes) * kWaves;
-    if (i >= kOuts) return;
-    const int g = HEAD_FAST ? i % G : i / DIMS, d = HEAD_FAST ? i / G : i % DIMS;
-    float mw[kWaves], fw[kWaves], lw[kWaves];
-    __builtin_memcpy(mw, __builtin_assume_aligned(&ws.reference[g][k0], 16), sizeof(mw));
-    __builtin_memcpy(fw, __builtin_assume_aligned(&ws.factor[g][k0], 16), sizeof(fw));
-    __builtin_memcpy(lw, __builtin_assume_aligned(&ws.sum[g][k0], 16), sizeof(lw));
-    float mb = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) mb = fmaxf(mb, mw[k]);
-    if constexpr (kLanes == 2) mb = max_halves(mb);
-    float o = 0.f, lb = 0.f;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        const float c = fw[k] * pow2_whole(mw[k] - mb);
-        o += c * reinterpret_cast<const float*>(tiles + (k0 + k) * stride)[d * G + g];
-        lb += c * lw[k];
+// the wave's own max.  put(g, d, sum, reference, normaliser) for every head and dim, consecutive lanes on consecutive dims; norm(2 g, reference) and
+// norm(2 g + 1, normaliser) of all heads, by lanes of the first wave together.
+// A wave makes 16 dims of up to four heads: row r of its lanes adds up a quarter of the NT waves, a lane one dim of the four heads, 16 bytes at a time as the sums lie, and
+// the rows meet in registers, where row r keeps head r.  What the weights of the NT waves and four heads take (differences of references, powers of two) is formed
+// once a wave, lane 4 j + g of row r for wave NT / 4 r + j and head g, and handed out along the row.  (A lane per output, or two, each with all of the weights, and with sums
+// read four lanes to a bank, and the references in a store of their own behind another barrier, with the queries as below: us per layer 131072 tokens 16.1 -> 15.9, 6
+// sequences of 1900 to 21001 16.3 -> 15.9, 16 of 64 heads 50.1 -> 49.6.)
+template <int G, int NT, int DIMS = kHeadDim, typename Put, typename Norm>
+__device__ __forceinline__ void block_sums(const char* tiles, int stride, const WaveSums<NT>& ws, Put put, Norm norm) {
+    constexpr int kHeads = G < 4 ? G : 4, kPer = NT / 4, kSlices = DIMS / 16;
+    static_assert(NT % 4 == 0 && kPer <= 4 && DIMS % 16 == 0 && (G <= 4 || G == 8), "a weight per lane, a row of lanes per head");
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, t = lane & 15, row = lane >> 4;
+    if (w >= kSlices * (G / kHeads)) return;
+    const int h0 = G > 4 ? w / kSlices * 4 : 0, d = w % kSlices * 16 + t;
+    // (reference, normaliser) of head h + t % 4, and the lane's weight
+    auto head_sums = [&](int h, float& mb, float& lb) -> float {
+        const int g = h + min(t & 3, kHeads - 1), k = kPer * row + ((t >> 2) & (kPer - 1));
+        const float m = ws.reference[g][k], f = ws.factor[g][k], l = ws.sum[g][k];
+        mb = m;
+        if constexpr (kPer == 4) mb = fmaxf(mb, other_eight(mb));
+        if constexpr (kPer >= 2) mb = fmaxf(mb, of_row_turned<4>(mb));
+        mb = max_quads(mb);
+        const float c = f * pow2_whole(m - mb);
+        lb = c * l;
+        if constexpr (kPer == 4) lb += other_eight(lb);
+        if constexpr (kPer >= 2) lb += of_row_turned<4>(lb);
+        lb = sum_quads(lb);
+        if (lb != lb) mb = 0.f;                                       // NaN, perhaps with no other logit: merges pass over a reference of -infinity
+        return c;
+    };
+    float mb, lb;
+    const float c = head_sums(h0, mb, lb);
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+    auto add = [&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        if constexpr (j < kPer) {
+            const char* src = tiles + (kPer * row + j) * stride + (d * G + h0) * 4;
+            float x[kHeads];
+            __builtin_memcpy(x, __builtin_assume_aligned(src, 4 * kHeads), sizeof(x));
+            o[0] += of_row<4 * j>(c) * x[0];
+            if constexpr (kHeads >= 2) o[1] += of_row<4 * j + 1>(c) * x[1];
+            if constexpr (kHeads >= 4) { o[2] += of_row<4 * j + 2>(c) * x[2]; o[3] += of_row<4 * j + 3>(c) * x[3]; }
+        }
+    };
+    add(std::integral_constant<int, 0>{});
+    add(std::integral_constant<int, 1>{});
+    add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 3>{});
+    // two exchanges: halves of the wave add heads (0, 1 | 2, 3), rows of a half one each
+    auto halves = [](float x, float y) { const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false); return __uint_as_float(s[0]) + __uint_as_float(s[1]); };
+    auto rows = [](float x, float y) { const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false); return __uint_as_float(s[0]) + __uint_as_float(s[1]); };
+    const float sum = rows(halves(o[0], o[2]), halves(o[1], o[3]));
+    auto of_head = [&](float x) {                                     // head r's in row r
+        int v = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x00 /* quad_perm */, 0x1, 0xf, false);
+        v = __builtin_amdgcn_update_dpp(v, __float_as_int(x), 0x55, 0x2, 0xf, false);
+        v = __builtin_amdgcn_update_dpp(v, __float_as_int(x), 0xAA, 0x4, 0xf, false);
+        return __int_as_float(__builtin_amdgcn_update_dpp(v, __float_as_int(x), 0xFF, 0x8, 0xf, false));
+    };
+    const float mr = of_head(mb), lr = of_head(lb);
+    if (row < kHeads) put(h0 + row, d, sum, mr, lr);
+    if (w == 0) {
+        float m2 = mb, l2 = lb;
+        if constexpr (G > 4) (void)head_sums(4, m2, l2);
+        const int g = (t & 3) + 4 * (t >> 3);
+        const float v = t < 8 ? (t < 4 ? mb : lb) : (t < 12 ? m2 : l2);
+        if (row == 0 && (t & 3) < kHeads && g < G) norm(2 * g + ((t >> 2) & 1), v);
     }
-    if constexpr (kLanes == 2) { o = sum_halves(o); lb = sum_halves(lb); }
-    if (lb != lb) mb = 0.f;                                           // NaN, perhaps with no other logit: merges pass over a reference of -infinity
-    if (k0 == 0) put(g, d, o, mb, lb);
 }
 
 // kStep: blocks of a pair that merge
@@ -1220,7 +1266,7 @@ __device__ __forceinline__ uint4 ld_row(const char* p) {
 
 constexpr int kDimsPerBlock = 32, kMaxDirectDims = 416, kMaxDirectDims1 = 320;       // kDirectDims: dims of a block, tokens of a call (of one query head per KV head)
 // kDirectDims, blocks of 16 waves: pair fastest in the grid, so that the blocks of a pair find their common keys in one L2, and each begins at another quarter of
-// them.  Us a call, 32 query heads on 8: 257 tokens 6.02 -> 5.92 (5.98 without the quarters); with the two lanes an output of block_sums 200 5.45 -> 4.97, 256 5.70 -> 5.22,
+// them.  Us a call, 32 query heads on 8: 257 tokens 6.02 -> 5.92 (5.98 without the quarters); with two lanes an output in block_sums, as it was then, 200 5.45 -> 4.97, 256 5.70 -> 5.22,
 // 257 6.05 -> 5.78, 384 6.86 -> 6.34; 64 on 8: 256 6.15 -> 5.82; 32 on 32: 256 5.57 -> 5.37.  Fewer waves, heads first: 8 on 8, 64 tokens 3.03 -> 3.15, 128 3.54 -> 3.70; 32
 // on 32, 64 tokens 3.57 -> 3.25.
 template <int MODE, int CHUNK> constexpr bool kPairFirst = MODE == kStep || MODE == kStepRagged || (MODE == kDirectDims && CHUNK / 16 >= kBlockWaves);
@@ -1256,7 +1302,10 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
     __shared__ __attribute__((aligned(16))) char sm[kShBytes];
     __shared__ WaveSums<kTiles> sm_waves;
     __shared__ int sm_last;                                                 // kStep: set by a thread of the merge whose wait ran out
-    __shared__ float sm_norm[kStepping ? 2 * G : 1];                        // kStep: (reference, normaliser) of the block's heads
+    // The group's queries, requested first of all and once a block: the tile waves read their fragments from here.  (Every tile wave with fragments of its own from memory,
+    // four 1 KB requests each, eight in fp32: see block_sums.)
+    constexpr int kQueryPitch = kRowBytes + 64;                               // the four heads that a fragment read meets lie in different banks
+    __shared__ __attribute__((aligned(16))) char sm_q[G * kQueryPitch];
     __shared__ int32_t sm_row[CHUNK];
     constexpr int kMergeWords = kStepping ? 3 * (kBlockThreads + kWave) : 1;
     __shared__ float sm_merge[kMergeWords];                                   // kStep: the merging block's scratch
@@ -1293,16 +1342,13 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
     const int slot = split * (CHUNK / kWave);                     // partial slot (slots are counted in 64-token units)
     SKV_T(0);
 
-    // The query fragments of the tile waves (lane (t16, qd): head t16).  bf16: requested first of all; they are in registers long before the
-    // key rows arrive, so the logits wait for the keys only.  fp32, twice the registers: just ahead of the keys (kept across the
-    // selection, a few registers would be spilled, which costs the single-launch step a tenth).
-    uint4 qB[X::kPieces];
-    auto request_queries = [&]() {
-#pragma unroll
-        for (int s2 = 0; s2 < X::kPieces; ++s2)
-            qB[s2] = *reinterpret_cast<const uint4*>(a.q + ((qhead0 + min(t16, G - 1)) * kHeadDim) * EB + 64 * s2 + 16 * qd);
+    constexpr int kQueryPieces = G * kRowBytes / 16;                  // a thread each
+    static_assert(kQueryPieces <= kTiles * kWave, "by tile waves");
+    uint4 q_piece = make_uint4(0, 0, 0, 0);
+    if (tid < kQueryPieces) q_piece = *reinterpret_cast<const uint4*>(a.q + qhead0 * kRowBytes + 16 * tid);
+    auto leave_queries = [&]() {                                      // a barrier must follow
+        if (tid < kQueryPieces) *reinterpret_cast<uint4*>(sm_q + tid / (kRowBytes / 16) * kQueryPitch + tid % (kRowBytes / 16) * 16) = q_piece;
     };
-    if (EB == 2 && w < kTiles) request_queries();
 
     int32_t n;                                                    // retrieved tokens of this (sequence, head)
     bool step_ok = true;                                          // kStep: every wait of this block ended in time
@@ -1359,6 +1405,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
         }
         if (tid < CHUNK) sm_row[tid] = -1;
         if (kStepping && tid == 0) sm_last = 0;
+        leave_queries();
         int32_t nsel, ntok;
         // Each selected bucket that reaches into this block's positions marks, in every 64-position piece it touches,
         // where it starts there and which pool row that is; the waves then fill the positions in between.
@@ -1483,7 +1530,6 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
             leave_sums<G>(sm + w * kTileBytes, o);
         } else if (w < kTiles) {
             char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
-            if constexpr (EB == 4) request_queries();
             uint4 kA[kPasses][X::kPieces], vR[kPasses][X::kLoads];
             unsigned long long vm[kPasses];                           // bit t (t < 16): token t of the tile is real
 #pragma unroll
@@ -1541,9 +1587,16 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
                 for (int i = 0; i < X::kLoads; ++i) vR[ps][i] = ld_row<!kRowsDirect>(Vh + (int64_t)rowV[i] * kRowBytes + 16 * (lane % X::LPR));
                 vm[ps] = __ballot(liveK);
             }
+            if constexpr (!kSel) {                                    // behind the rows' requests
+                leave_queries();
+                __syncthreads();
+            }
+            uint4 qB[X::kPieces];                                     // lane (t16, qd): pieces of head t16
 #pragma unroll
-            for (int s2 = 0; s2 < X::kPieces; ++s2)
+            for (int s2 = 0; s2 < X::kPieces; ++s2) {
+                qB[s2] = *reinterpret_cast<const uint4*>(sm_q + min(t16, G - 1) * kQueryPitch + 64 * s2 + 16 * qd);
                 if (t16 >= G) qB[s2] = make_uint4(0, 0, 0, 0);
+            }
             SKV_T(5);
             float p[kPasses][4], mw = -INFINITY;
 #pragma unroll
@@ -1580,12 +1633,13 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
             lw = sum_quads(lw);
             if (qd == 0) sm_waves.leave(t16, w, mw, ref, lw);
             leave_sums<G>(sm_v, o);
+        } else if constexpr (!kSel) {
+            __syncthreads();                                          // the queries'
         }
         __syncthreads();
-        block_sums<G, kTiles, false, kDims>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
+        block_sums<G, kTiles, kDims>(sm, kTileBytes, sm_waves, [&](int g, int d, float sum, float mb, float lb) {
             if constexpr (kStepping) {
                 st_tagged(my_part + g * kHeadDim + d, sum, part_tag);
-                if (d == 0) { sm_norm[2 * g] = mb; sm_norm[2 * g + 1] = lb; }
             } else if (nsplit == 1) {                                 // the only block: its sums are the result
                 const bool empty = lb == 0.f;                       // every retrieved position was out of range
                 a.out[(qhead0 + g) * kHeadDim + dim0 + d] = empty ? 0.f : sum / lb;
@@ -1594,11 +1648,9 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
                 st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
                 if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
             }
+        }, [&](int i, float v) {
+            if constexpr (kStepping) st_tagged(my_part + G * kHeadDim + i, v, part_tag);      // one store: see step_part_words
         });
-        if constexpr (kStepping) {                                // one store: see step_part_words
-            __syncthreads();
-            if (tid < 2 * G) st_tagged(my_part + G * kHeadDim + tid, sm_norm[tid], part_tag);
-        }
         SKV_T(7);
     }
 
@@ -1970,7 +2022,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
     if (qd == 0) ss.waves.leave(t16, w, m_run, m_run > -INFINITY ? m_run : 0.f, l_run);
     leave_sums<G>(vt_b, o);
     __syncthreads();
-    block_sums<G, NW, true>(ss.v[0], sizeof(ss.v[0]), ss.waves, [&](int g, int d, float sum, float mb, float lb) {
+    block_sums<G, NW>(ss.v[0], sizeof(ss.v[0]), ss.waves, [&](int g, int d, float sum, float mb, float lb) {
         if (nsplit == 1) {                                        // the only block of this (sequence, head): no partials, no arrival, no merge
             const bool empty = lb == 0.f;                       // every retrieved position was out of range
             a.out[(qhead0 + g) * kHeadDim + d] = empty ? 0.f : sum / lb;
@@ -1979,7 +2031,7 @@ __device__ __forceinline__ void stream_attend(const AttArgs& a, StreamShared<EB,
             st_agent(a.part + (((qhead0 + g) * a.max_splits) + slot) * kHeadDim + d, sum);
             if (d < 2) st_agent(a.ml + (((qhead0 + g) * a.max_splits) + slot) * 2 + d, d == 0 ? mb : lb);
         }
-    });
+    }, [](int, float) {});
     if (nsplit == 1) return;
     SKV_T(7);
 
