@@ -299,31 +299,39 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float f) {
     return sign | code;
 }
 
+// nearest bf16 of a finite float, ties to even
+__device__ __forceinline__ uint32_t f32_to_bf16(float f) {
+    const uint32_t u = __float_as_uint(f);
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+
 // One lane's EPL means (sums / n) of a bucket to element `o` of the table.  SVB: bytes per stored element (4 = fp32, 2 = bf16,
 // 1 = E4M3; rounded to nearest even).
-template <int EPL, int SVB, bool STREAM>
+template <int EPL, int SVB>
 __device__ __forceinline__ void store_means(char* __restrict__ semvec, int64_t o, const float* acc, float n) {
 #pragma unroll
     for (int i = 0; i < EPL; i += 4) {
         const float m[4] = {acc[i] / n, acc[i + 1] / n, acc[i + 2] / n, acc[i + 3] / n};
-        if (SVB == 4) {
-            const uint4 v = make_uint4(__float_as_uint(m[0]), __float_as_uint(m[1]), __float_as_uint(m[2]), __float_as_uint(m[3]));
-            if (STREAM) st_stream(semvec + (o + i) * 4, v);
-            else *reinterpret_cast<uint4*>(semvec + (o + i) * 4) = v;
-        } else if (SVB == 1) {
+        if (SVB == 4)
+            *reinterpret_cast<uint4*>(semvec + (o + i) * 4) = make_uint4(__float_as_uint(m[0]), __float_as_uint(m[1]), __float_as_uint(m[2]), __float_as_uint(m[3]));
+        else if (SVB == 1)
             *reinterpret_cast<uint32_t*>(semvec + (o + i)) = f32_to_e4m3(m[0]) | (f32_to_e4m3(m[1]) << 8) |
                                                              (f32_to_e4m3(m[2]) << 16) | (f32_to_e4m3(m[3]) << 24);
-        } else {
-            uint32_t rb[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                uint32_t u = __float_as_uint(m[k]);
-                u += 0x7fffu + ((u >> 16) & 1u);               // round to nearest even bf16 (means are finite)
-                rb[k] = u >> 16;
-            }
-            *reinterpret_cast<uint2*>(semvec + (o + i) * 2) = make_uint2(rb[0] | (rb[1] << 16), rb[2] | (rb[3] << 16));
-        }
+        else
+            *reinterpret_cast<uint2*>(semvec + (o + i) * 2) = make_uint2(f32_to_bf16(m[0]) | (f32_to_bf16(m[1]) << 16), f32_to_bf16(m[2]) | (f32_to_bf16(m[3]) << 16));
     }
+}
+// Two of them.
+template <int SVB, bool STREAM>
+__device__ __forceinline__ void store_pair(char* __restrict__ semvec, int64_t o, float m0, float m1) {
+    auto put = [&](auto v) {
+        auto* p = reinterpret_cast<decltype(v)*>(semvec + o * SVB);
+        if (STREAM) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
+    if (SVB == 4) put((unsigned long long)__float_as_uint(m0) | ((unsigned long long)__float_as_uint(m1) << 32));
+    else if (SVB == 2) put((uint32_t)(f32_to_bf16(m0) | (f32_to_bf16(m1) << 16)));
+    else put((uint16_t)(f32_to_e4m3(m0) | (f32_to_e4m3(m1) << 8)));
 }
 
 // Bound by HBM: the pool once in, the table once out.  A wave per bucket, one-shot waves with all the rows of a bucket of
@@ -376,15 +384,33 @@ __global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const c
     };
     if (e - b > 48) add_rows(std::integral_constant<int, 8>{});
     else add_rows(std::integral_constant<int, 4>{});
+    // The sums over the wave's rows, half of the elements left to each side of an exchange: every lane divides and stores two, and the vector leaves in one
+    // whole piece.  Before, 16 (fp32: 32) lanes held all sums and stored eight (four) each, an fp32 vector in two pieces with gaps, reduced ones with plain stores
+    // in large tables too, where a piece goes past the caches now like everything else there.  32 layers x 8 heads, us, before / now: 32768 tokens, table in fp32
+    // 388 / 378, bf16 403 / 361, E4M3 379 / 347; 16384, E4M3 204 / 180; table and the scores of every layer: 494 / 483, 487 / 449, 467 / 445; 283 / 274.  Up to 8192
+    // tokens the same within 1 %.  Not kept: loads counted out by the bucket's length instead of masked, and 52 registers instead of more, 32768 tokens 388 / 405;
+    // 24 or 16 waves on a compute unit 407, 475.
+    float h[4];
+    if constexpr (R::RPW == 4) {
 #pragma unroll
-    for (int off = R::LPR; off < 64; off <<= 1) {
+        for (int i = 0; i < 4; ++i) {
+            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i]), __float_as_uint(acc[i + 4]), false, false);
+            h[i] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        }
+    } else {
+        static_assert(R::RPW == 2 && R::EPL == 4);
 #pragma unroll
-        for (int i = 0; i < R::EPL; ++i) acc[i] += __shfl_xor(acc[i], off);
+        for (int i = 0; i < 4; ++i) h[i] = acc[i];
     }
-    if (r == 0) {
-        const float n = (e > b) ? (float)(e - b) : 1.f;      // a bucket without tokens yields zeros
-        store_means<R::EPL, SVB, LARGE>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
+    float m[2];
+    const float n = (e > b) ? (float)(e - b) : 1.f;          // a bucket without tokens yields zeros
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(h[i]), __float_as_uint(h[i + 2]), false, false);
+        m[i] = (__uint_as_float(x[0]) + __uint_as_float(x[1])) / n;
     }
+    const int first = cc * R::EPL + (R::RPW == 4 ? (r & 1) * 4 + (r >> 1) * 2 : r * 2);
+    store_pair<SVB, LARGE>(semvec, (lh * S + s) * (int64_t)kHeadDim + first, m[0], m[1]);
 }
 
 // Short buckets (a retained pool keeps a few tokens of each): the row's LPR lanes own a bucket, RPW buckets per wave, and walk
@@ -426,7 +452,7 @@ __global__ __launch_bounds__(kSemvecShortWaves * kWave) void semvec_short_kernel
         }
     }
     const float n = (e > b) ? (float)(e - b) : 1.f;          // a bucket without tokens yields zeros
-    store_means<R::EPL, SVB, false>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
+    store_means<R::EPL, SVB>(semvec, (lh * S + s) * (int64_t)kHeadDim + cc * R::EPL, acc, n);
 }
 
 template <int EB, int SVB>

@@ -165,6 +165,32 @@ def test_semvec_at_the_line_between_its_forms(U, oracle32, S, sv_dtype):
             assert U.e4m3_table_close(got, ref, oracle32.e4m3_decode)
 
 
+@pytest.mark.parametrize("dtype, sv_dtype", [("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16"), ("f32", "fp8")])
+def test_large_tables_of_the_other_types(U, oracle32, dtype, sv_dtype):
+    """The types that the test above leaves out, in a table one bucket past its line: buckets of 5 to 15 rows (2 to 8 of an fp32 pool), as there."""
+    S, n = 641, 10 if dtype == "bf16" else 5
+    wl = gen.CFG3.scaled(n_tokens=n * S, len_dist=("fixed", n), dtype=dtype)
+    lens = np.full(S, n, dtype=np.int32)
+    lens[:-1:2] += n // 2 + n % 2
+    lens[1::2] -= n // 2 + n % 2
+    off = gen.offsets_of(lens)
+    g = torch.Generator(device=U.DEV).manual_seed(S)
+    K = torch.empty(wl.n_layers, 8, n * S, 128, dtype=wl.torch_dtype, device=U.DEV).normal_(generator=g)
+    sv = torch.full((wl.n_layers, 8, S, 128), 9, dtype=U.sv_torch_dtype(sv_dtype), device=U.DEV)
+    _say("semvec", dtype, sv_dtype)
+    U.make_ctx(wl, n * S, S, 16, sv_dtype=sv_dtype).build_semvec(K, U.i32(off), S, sv)
+    torch.cuda.synchronize()
+    for l in (0, 31):
+        ref, got = oracle32.semvec(gen.to_numpy(K[l:l + 1]), off, sv_dtype=sv_dtype)[0], U.np_of(sv[l])
+        if sv_dtype == "f32":
+            # sums of up to 15 rows and a division, as bounded above
+            assert np.abs(got - ref).max() <= (2 * 14 * 2.0 ** -24 + 2.0 ** -22) * float(K.abs().max())
+        elif sv_dtype == "bf16":
+            assert U.bf16_table_close(got, ref)
+        else:
+            assert U.e4m3_table_close(got, ref, oracle32.e4m3_decode)
+
+
 # ----------------------------------------------------------------------------- decode chain, per stage
 
 def _chain_case(U, oracle32, wl, seed, budget, pool_in_host=False, layers=None, sv_dtype="f32"):
