@@ -145,9 +145,11 @@ __global__ __launch_bounds__(kSegThreads) void seg_scan_kernel(const int32_t* __
 // The same in ONE launch, for prompts of up to kSegOneMaxTok tokens: a block of 1024 threads owns 4096 tokens, keeps the
 // terminator bitmap in LDS and counts the terminators of all tokens before its own by itself, which is cheaper than a second
 // launch (4 tokens per thread and preceding block, from L2).  Bound by latency: two dependent memory round trips and a block
-// scan.  REPORT: the block that finishes last also stores S to pinned host memory, after every block has written its
-// results back to the level the host and all XCDs share, so that the host can poll the word instead of copying it and
-// waiting for the stream.
+// scan.  REPORT: the block that finishes last also stores S to pinned host memory, when the results of every block are where the
+// host and all XCDs see them, so that the host can poll the word instead of copying it and waiting for the stream.  They are written
+// there store by store; a release at system scope writes back an XCD's whole L2, with what earlier work left in it.  Us a call as the host sees it, with ordinary
+// stores, a release by a wave of every block, and words and blocks read one after the other / now: 1531 tokens 19.7 / 16.2, 8192 19.9 / 15.3, 32768 19.7 / 17.0, 131072
+// 27.2 / 23.8, behind a kernel that wrote 64 MB 31.6 / 25.6.
 template <bool REPORT>
 __global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* __restrict__ tok, int32_t T,
                                                                 const uint32_t* __restrict__ bitmap, int32_t vocab,
@@ -168,19 +170,38 @@ __global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* _
 #pragma unroll
         for (int k = 0; k < 4; ++k) t[k] = i0 + k < T ? tok[i0 + k] : -1;
     }
-    for (int i = tid; i < words; i += kBlockThreads) sm_bits[i] = bitmap[i];
+    for (int i = tid; i < words; i += 4 * kBlockThreads) {      // four at a time: 16 KB of bitmap in one round trip
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = bitmap[min(i + u * kBlockThreads, words - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * kBlockThreads < words) sm_bits[i + u * kBlockThreads] = v[u];
+    }
     __syncthreads();
+    // REPORT: results are written through to memory (every store on its own, system scope), so that a wave that has waited for its stores has nothing left in the L2.
+    auto put = [](int32_t* p, int32_t v) {
+        if (REPORT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        else *p = v;
+    };
     auto is_term = [&](int32_t id) -> bool {
         return (uint32_t)id < (uint32_t)vocab && ((sm_bits[(uint32_t)id >> 5] >> (id & 31)) & 1u);
     };
     // terminators before the block: number, and 1 + position of the last one (0: none)
     uint32_t pre_cnt = 0, pre_last = 0;
-    for (int32_t j = 4 * tid; j < block0; j += kSegOneBlockTok) {
-        const int4 v = *reinterpret_cast<const int4*>(tok + j);
-        const int32_t p[4] = {v.x, v.y, v.z, v.w};
+    for (int32_t first = 0; first < (int32_t)blockIdx.x; first += 4) {
+        int4 v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (is_term(p[k])) { pre_cnt += 1; pre_last = (uint32_t)(j + k + 1); }
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const int4*>(tok + min(first + u, (int32_t)blockIdx.x - 1) * kSegOneBlockTok + 4 * tid);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t p[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            if (first + u < (int32_t)blockIdx.x) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (is_term(p[k])) { pre_cnt += 1; pre_last = (uint32_t)((first + u) * kSegOneBlockTok + 4 * tid + k + 1); }
+            }
+        }
     }
     uint32_t cnt = 0, last = 0, flags = 0;
 #pragma unroll
@@ -206,45 +227,46 @@ __global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* _
         const int32_t i = i0 + k;
         id[k] = (int32_t)seg;
         if (i < T && (((flags >> k) & 1u) || i == T - 1)) {
-            if ((int32_t)seg < cap_sent) { sent_off[seg] = (int32_t)start; sent_len[seg] = i + 1 - (int32_t)start; }
+            if ((int32_t)seg < cap_sent) { put(sent_off + seg, (int32_t)start); put(sent_len + seg, i + 1 - (int32_t)start); }
             if (i == T - 1) {
                 total = seg + 1;
-                *n_sent = (int32_t)total;
-                if ((int32_t)total <= cap_sent) sent_off[total] = T;
+                put(n_sent, (int32_t)total);
+                if ((int32_t)total <= cap_sent) put(sent_off + total, T);
             }
             start = (uint32_t)(i + 1);
             seg += 1;
         }
     }
     if (i0 + 4 <= T) {
-        *reinterpret_cast<int4*>(seg_id + i0) = make_int4(id[0], id[1], id[2], id[3]);
+        if (REPORT) {
+#pragma unroll
+            for (int k = 0; k < 4; k += 2)
+                __hip_atomic_store(reinterpret_cast<unsigned long long*>(seg_id + i0 + k), ((unsigned long long)(uint32_t)id[k + 1] << 32) | (uint32_t)id[k],
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        } else {
+            *reinterpret_cast<int4*>(seg_id + i0) = make_int4(id[0], id[1], id[2], id[3]);
+        }
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (i0 + k < T) seg_id[i0 + k] = id[k];
+            if (i0 + k < T) put(seg_id + i0 + k, id[k]);
     }
     if (REPORT) {
         __shared__ uint32_t sm_total;
         if (tid == 0) sm_total = 0u;
         __syncthreads();
         if (total != 0u) sm_total = total;
-        // One wave makes the block's results visible to the host: the release at system scope writes back the XCD's whole L2, with what earlier work left
-        // there (every wave's own, another in the arrival's order and one in the host word's: a prompt of 1531 tokens with its mean keys 42.1
-        // us, this 37.5).
-        block_sync_after_stores();
+        block_sync_after_stores();                              // every wave's results are in memory
         if (tid == 0) {
             const unsigned long long mine = (1ull << 32) | (unsigned long long)sm_total;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-            if (gridDim.x == 1) {
-                __hip_atomic_store(host_word, (uint32_t)mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            } else {
-                const unsigned long long all = mine + __hip_atomic_fetch_add(arrive, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((uint32_t)(all >> 32) == gridDim.x) {
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                    __hip_atomic_store(arrive, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next call
-                    __hip_atomic_store(host_word, (uint32_t)all, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-                }
+            unsigned long long all = mine;
+            if (gridDim.x > 1) {
+                all += __hip_atomic_fetch_add(arrive, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((uint32_t)(all >> 32) != gridDim.x) return;
+                __hip_atomic_store(arrive, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);     // for the next call, which the word below may start
+                wait_loads<0>();
             }
+            __hip_atomic_store(host_word, (uint32_t)all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }

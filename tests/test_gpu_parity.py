@@ -87,6 +87,31 @@ def test_segment_vocabularies(U, oracle32, vocab, T):
     assert np.array_equal(off[:S_ref + 1], off_ref) and np.array_equal(ln[:S_ref], len_ref)
 
 
+@pytest.mark.parametrize("blocks, extra", [(1, 3), (4, 1), (5, 0), (5, 3), (9, 2)])
+def test_segment_blocks_are_whole_when_the_call_returns(U, oracle32, blocks, extra):
+    """Blocks of 4096 tokens read those before them four at a time, the bitmap 4096 words at a time (4100 here).  When the call returns, another stream
+    finds all of its results."""
+    T, vocab = 4096 * blocks + extra, 131200
+    rng = np.random.default_rng(T)
+    tok, ends = rng.integers(0, vocab, size=T).astype(np.int32), rng.random(vocab) < 0.05
+    bitmap = np.packbits(ends, bitorder="little").view(np.uint32)
+    _say("segment", T)
+    seg_ref, off_ref, len_ref, S_ref = oracle32.segment(tok, bitmap, vocab)
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=1), T, S_ref, 16)
+    d_tok, d_bm = U.i32(tok), torch.as_tensor(bitmap.view(np.int32)).to(U.DEV)
+    other = torch.cuda.Stream()
+    for _ in range(3):
+        seg, off, ln, n = U.empty_i32(T, fill=-7), U.empty_i32(S_ref + 1, fill=-7), U.empty_i32(S_ref, fill=-7), U.empty_i32(4, fill=-7)
+        torch.cuda.synchronize()
+        S = ctx.segment(d_tok, d_bm, vocab, seg, off, ln, n)
+        with torch.cuda.stream(other):
+            seen = [x.clone() for x in (seg, off, ln, n)]
+        other.synchronize()
+        got = [x.cpu().numpy() for x in seen]
+        assert S == S_ref == got[3][0]
+        assert np.array_equal(got[0], seg_ref) and np.array_equal(got[1], off_ref) and np.array_equal(got[2], len_ref)
+
+
 def test_segment_reports_capacity_overflow(U, oracle32):
     import paper_2504_00970_amd as skv
     tok = np.array([7] * 50, dtype=np.int32)
