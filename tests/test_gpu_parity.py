@@ -216,6 +216,21 @@ def test_large_tables_of_the_other_types(U, oracle32, dtype, sv_dtype):
             assert U.e4m3_table_close(got, ref, oracle32.e4m3_decode)
 
 
+@pytest.mark.parametrize("S", [165, 169, 171, 341, 512, 685])
+def test_semvec_blocks_dealt_in_groups(U, oracle32, S):
+    """3 layers x 2 heads of ceil(S / 4) blocks each: 252 (no group of 256), 258 (two past the first), 516, 768 (three groups) and 1032 of them; one float per
+    bucket tells whose rows it is made of."""
+    wl = gen.CFG3.scaled(n_layers=3, n_kv_heads=2, n_q_heads=8, n_tokens=10 * S, dtype="f32", len_dist=("fixed", 10))
+    off = np.arange(S + 1, dtype=np.int32) * 10
+    whose = torch.arange(6 * S, dtype=torch.float32, device=U.DEV).reshape(3, 2, S)
+    K = whose.repeat_interleave(10, dim=2)[..., None].expand(-1, -1, -1, 128).contiguous()
+    sv = torch.full((3, 2, S, 128), -1.0, device=U.DEV)
+    _say("semvec", S)
+    U.make_ctx(wl, 10 * S, S, 16).build_semvec(K, U.i32(off), S, sv)
+    torch.cuda.synchronize()
+    assert torch.equal(sv, whose[..., None].expand(-1, -1, -1, 128))      # sums of ten equal whole numbers below 2^17 and their quotients are exact
+
+
 # ----------------------------------------------------------------------------- decode chain, per stage
 
 def _chain_case(U, oracle32, wl, seed, budget, pool_in_host=False, layers=None, sv_dtype="f32"):
