@@ -356,7 +356,6 @@ __device__ __forceinline__ void store_pair(char* __restrict__ semvec, int64_t o,
     else put((uint16_t)(f32_to_e4m3(m0) | (f32_to_e4m3(m1) << 8)));
 }
 
-constexpr uint32_t kXcdRun = 32;               // neighbouring blocks of an XCD (a power of two)
 // Bound by HBM: the pool once in, the table once out.  A wave per bucket, one-shot waves with all the rows of a bucket of
 // average length requested at once.  LARGE: 8 waves per block (contiguous 40 KB) and non-temporal stores, else 4 and plain ones; see the launch.
 // The keys' loads are non-temporal in both: a plain read takes a place in the memory-side cache, whose lines may have to be written
@@ -370,11 +369,9 @@ __global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const c
                                                                          int32_t S, char* __restrict__ semvec) {
     using R = Row<EB>;
     const int lane = threadIdx.x & 63;
-    // The hardware deals consecutive blocks to the XCDs in turn; of 8 * kXcdRun of them each XCD takes kXcdRun that are neighbours in the pool (blocks past the last
-    // whole group as they come).  Us, blocks as they come / runs of 32, 32 layers x 8 heads: 32768 tokens in lognormal lengths, fp32 table 416 / 370, E4M3 375 / 344,
-    // geometric lengths 380 / 376 (4 blocks 381, 16 379, 64 380, 256 375; a whole eighth of the grid 425), 8192 tokens, lognormal, fp32 109.5 / 105, E4M3 95 / 90, 1531 the same.
-    const uint32_t id = blockIdx.x + gridDim.x * blockIdx.y, group = id / (8 * kXcdRun) * (8 * kXcdRun);
-    const uint32_t at = group + 8 * kXcdRun <= gridDim.x * gridDim.y ? group + (id & 7) * kXcdRun + ((id >> 3) & (kXcdRun - 1)) : id;
+    // Blocks in runs of an XCD.  Us, blocks as they come / runs of 32, 32 layers x 8 heads: 32768 tokens in lognormal lengths, fp32 table 416 / 370, E4M3 375 / 344,
+    // geometric lengths 380 / 376 (runs of 4 381, 16 379, 64 380, 256 375, an eighth of the grid 425), 8192 tokens, lognormal, fp32 109.5 / 105, E4M3 95 / 90, 1531 the same.
+    const uint32_t at = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
     const uint32_t by = at / gridDim.x, bx = at - by * gridDim.x;
     const int32_t s = bx * (LARGE ? 8 : 4) + (threadIdx.x >> 6);
     if (s >= S) return;                                   // wave-uniform

@@ -27,6 +27,14 @@ __device__ __forceinline__ float sum_rows16(float x) {
     return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
+// Block `id` of n in the order in which an XCD takes neighbours: the hardware deals consecutive blocks to the eight XCDs in turn, and of 8 * kXcdRun of them each
+// XCD takes kXcdRun in a row here (blocks past the last whole group as they come).
+constexpr uint32_t kXcdRun = 32;               // a power of two
+__device__ __forceinline__ uint32_t xcd_run(uint32_t id, uint32_t n) {
+    const uint32_t group = id / (8 * kXcdRun) * (8 * kXcdRun);
+    return group + 8 * kXcdRun <= n ? group + (id & 7) * kXcdRun + ((id >> 3) & (kXcdRun - 1)) : id;
+}
+
 // 16 bytes that this launch reads or writes once (K/V rows, mean keys): the non-temporal forms.  Measured on one-shot reads of
 // a 2.15 GB key pool (a wave requests 4 KB and ends): 6.45 TB/s with plain loads, 7.15 TB/s with these.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
