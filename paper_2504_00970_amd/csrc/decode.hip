@@ -476,7 +476,15 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 // per group, from the top one down, a scan and the lane that sees the budget crossed, then a lane per digit
 // of that group.  (The block finding it together, thread t with digits 2047-2t and 2046-2t, a block scan
 // and the crossing thread telling the others, takes two more barriers and trips to LDS a pass: keys in
-// registers to cut known 1.1 us, this way 0.7; a layer of the single-launch step of 32768 tokens 11.3 -> 11.1 us.)  The three
+// registers to cut known 1.1 us, this way 0.7; a layer of the single-launch step of 32768 tokens 11.3 -> 11.1 us.)
+// Scores close to each other, as keys with a large common part give them, fall into a few groups (one spans 3 % of the best
+// score), and the lanes of a wave that add to one word do so one after the other: a group has a counter for every eighth lane.
+// Us, the block scan / one counter a group / eight, scores 3 %, 1 % and 0.3 % apart (standard deviation over mean): a layer of the
+// single-launch step of 131072 tokens, 5461 buckets, 16.9, 17.0, 17.6 / 17.5, 19.0, 21.1 / 16.6, 16.9, 17.3 (normal scores 16.2 / 15.6 / 15.75); skv_select of 1400
+// buckets 6.2, 6.2, 6.4 / 6.2, 6.6, 7.2 / 6.1, 6.2, 6.3 (5.85 / 5.5 / 5.55), of 5200 8.2, 8.3, 8.4 / 9.0, 10.6, 12.4 / 8.2, 8.5, 8.7 (8.0 / 7.65 / 7.75).  So skv_select of more than
+// 2048 buckets takes the groups' totals from the histogram, a wave four groups, with a barrier more: 8.2, 8.3, 8.45 (7.9); the steps, whose blocks have more to do, would lose
+// by that (131072 tokens, normal scores 15.75 -> 16.0).  Not kept: four counters a group (131072 tokens 16.8, 17.2, 17.8), sixteen (17.1, 17.3, 17.8), neighbouring
+// buckets of a thread added up first (18.1).  The three
 // histograms are zeroed up front.  The search stops as soon as the crossing digit holds a single bucket
 // (typically after one pass); buckets with exactly the cut's score are resolved in id order by a scan.
 //
@@ -491,10 +499,11 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 constexpr int kSelKreg = 6;                                   // 1024 threads x 6 buckets in registers: S <= 6144
 constexpr int kBins = 2048;                                   // 11-bit digits (the last pass uses 1024)
 constexpr int kGroupBins = kBins / kWave;                     // digits of a group: 64 groups, a lane each
+constexpr int kGroupCounters = 8;                             // counters of a group: lane l adds to l % 8
 
 struct SelectShared {
-    unsigned long long hist[3][kBins];                        // packed (count << 32 | total length) per digit
-    uint32_t group[3][kWave];                                 // total length per group of 32 digits
+    __attribute__((aligned(16))) unsigned long long hist[3][kBins];           // packed (count << 32 | total length) per digit
+    __attribute__((aligned(16))) uint32_t group[3][kWave][kGroupCounters];    // total length per group of 32 digits, in parts (from the histogram: the first 64 words)
     uint32_t wave_tot[3][kBlockWaves];                        // one slot per block scan
     int32_t gave_up;                                          // tagged scores: set by a thread whose wait ran out
     __attribute__((aligned(16))) uint32_t wmax[kBlockWaves];  // largest key per wave
@@ -513,6 +522,8 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
                                              SelectShared& sh, Emit emit, int32_t* n_sel_out, int32_t* n_tok_out,
                                              uint32_t tag = 0, int32_t wait_limit = 0, bool* ok_out = nullptr,
                                              uint32_t* __restrict__ key_lds = nullptr /* TAGGED: KREG * kBlockThreads words */) {
+    constexpr bool kByHist = COUNT && KREG > 2;                // the groups' totals: from the histogram, else counted beside it
+    static_assert(sizeof(sh.group) / 16 <= kBlockThreads, "zeroed by a store each");
     const int tid = threadIdx.x;
     *n_sel_out = 0;
     *n_tok_out = 0;
@@ -563,7 +574,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         unsigned long long* h = &sh.hist[0][0];
 #pragma unroll
         for (int i = 0; i < 3 * kBins / kBlockThreads; ++i) h[i * kBlockThreads + tid] = 0;
-        if (tid < 3 * kWave) (&sh.group[0][0])[tid] = 0;
+        if (!kByHist && tid < (int)(sizeof(sh.group) / 16)) reinterpret_cast<uint4*>(sh.group)[tid] = make_uint4(0, 0, 0, 0);
     };
     zero_hist();
     if (tid == 0) sh.gave_up = 0;
@@ -697,7 +708,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             auto count = [&](uint32_t k, int32_t ln) {
                 const uint32_t digit = (k >> nshift) & (nbins - 1);
                 atomicAdd(&H[digit], (1ull << 32) | (unsigned long long)(uint32_t)ln);
-                atomicAdd(&sh.group[pass][digit / kGroupBins], (uint32_t)ln);
+                if (!kByHist) atomicAdd(&sh.group[pass][digit / kGroupBins][tid % kGroupCounters], (uint32_t)ln);
             };
 #pragma unroll
             for (int i = 0; i < KREG; ++i)
@@ -709,6 +720,17 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
                 }
             }
             __syncthreads();
+            if constexpr (kByHist) {                               // 16 lanes a group, two digits each
+                static_assert(2 * kBlockThreads == kBins && kGroupBins == 32);
+                const uint4 two = *reinterpret_cast<const uint4*>(H + 2 * tid);
+                uint32_t sum = two.x + two.z;
+                sum = dpp_add_u32<0x128, 0xf>(sum);                // row_ror 8, 4, 2, 1
+                sum = dpp_add_u32<0x124, 0xf>(sum);
+                sum = dpp_add_u32<0x122, 0xf>(sum);
+                sum = dpp_add_u32<0x121, 0xf>(sum);
+                if (tid % 16 == 0) (&sh.group[pass][0][0])[tid / 16] = sum;
+                __syncthreads();
+            }
             // The lane whose digits, `own` tokens of them, take the running total past the budget (none: -1); carry: the total above it.
             const int lane = tid & (kWave - 1);
             auto crossing = [&](uint32_t own) -> int {
@@ -719,7 +741,16 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
                 carry = __builtin_amdgcn_readlane((int)above, l);
                 return l;
             };
-            const int grp = crossing(sh.group[pass][kWave - 1 - lane]);
+            uint32_t in_group = 0;
+            if constexpr (kByHist) {
+                in_group = (&sh.group[pass][0][0])[kWave - 1 - lane];
+            } else {
+                uint32_t x[kGroupCounters];
+                __builtin_memcpy(x, __builtin_assume_aligned(sh.group[pass][kWave - 1 - lane], 16), sizeof(x));
+#pragma unroll
+                for (int c = 0; c < kGroupCounters; ++c) in_group += x[c];
+            }
+            const int grp = crossing(in_group);
             if (grp < 0) { found_none = true; break; }             // the buckets of this attempt all fit (only possible in pass 0)
             const int top = (kWave - 1 - grp) * kGroupBins + kGroupBins - 1;                  // the group's highest digit
             const unsigned long long v = lane < kGroupBins ? H[top - lane] : 0ull;

@@ -398,6 +398,20 @@ def test_select_cut_at_the_edges_of_digits_and_their_groups(U, oracle32):
         _check_select(U, oracle32, score, lens, budget)
 
 
+@pytest.mark.parametrize("S", [1025, 2048, 2049, 6200])
+def test_select_scores_close_together(U, oracle32, S):
+    """Scores within 3 %, 0.1 % and a few steps of each other fall into a few groups of digits, or one; up to 2048 buckets the groups' totals are counted beside the
+    histogram, beyond that they come from it."""
+    rng = np.random.default_rng(S)
+    lens = rng.integers(1, 40, size=S)
+    for spread in (3e-2, 1e-3, 3e-7):
+        score = (100.0 * (1.0 + spread * rng.standard_normal((2, S)))).astype(np.float32)
+        edge = np.sort(score[0])[::-1].view(np.uint32)[0] - (np.arange(70, dtype=np.uint32) << 13)       # a bucket in every one of the first digits, and in two groups
+        score[1, :70] = edge.view(np.float32)
+        for budget in (1, 300, 2048, int(lens.sum()) - 1, int(lens.sum())):
+            _check_select(U, oracle32, score, lens, budget)
+
+
 # ----------------------------------------------------------------------------- attention edge cases
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
