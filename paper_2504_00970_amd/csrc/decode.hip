@@ -1376,9 +1376,20 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
 
     constexpr int kQueryPieces = G * kRowBytes / 16;                  // a thread each
     static_assert(kQueryPieces <= kTiles * kWave, "by tile waves");
-    // Direct blocks with a second tile in some waves: every wave has its own fragments from memory (behind that branch the barrier of the queries would wait for rows
-    // as well).  Us per call, once a block / own: 32 query heads on 8, 257 tokens 6.03 / 5.57, 400 7.06 / 6.60; 64 on 8, 257 6.11 / 5.87.
-    constexpr bool kOwnQueries = kRowsDirect && kPasses > 1;
+    // Where no selection lies between the request and the rows, the queries' way through LDS is a barrier behind the rows' requests.  Every wave has its own fragments from memory
+    // there, bf16 ones requested first of all, fp32 ones, twice the registers, just ahead of the keys; but for eight heads in bf16 and blocks of dims with a tile a wave,
+    // where a wave would ask for as much as for its keys, and positions (kIndirect).  Us per call, once a block / own: 32 query heads on 8, 257 tokens 6.03 / 5.57, 400 7.06 /
+    // 6.48, 1000 7.62 / 7.52, 2048 8.49 / 8.28, 4096 10.3 / 10.0, fp32, 257 9.8 / 9.4, 2048 11.5 / 11.1, 4096 16.7 / 14.6; 64 on 8 fp32, 4096 18.2 / 16.6; bf16, 500 7.27 / 7.40,
+    // 1000 7.73 / 7.81, 2048 9.84 / 9.78; 24 on 3, 448 7.08 / 7.20; 64 sequences through positions 88.9 / 89.3, fp32 74.9 / 68.7.  (bf16 ones just ahead of the keys: 1000 7.70,
+    // 2048 8.55.)
+    constexpr bool kOwnQueries = !kSel && (EB == 4 || (MODE == kDirect && G < 8) || (MODE == kDirectDims && kPasses > 1));
+    uint4 qB[X::kPieces];                                             // lane (t16, qd): pieces of head t16
+    auto own_queries = [&]() {
+#pragma unroll
+        for (int s2 = 0; s2 < X::kPieces; ++s2)
+            qB[s2] = *reinterpret_cast<const uint4*>(a.q + (qhead0 + min(t16, G - 1)) * kRowBytes + 64 * s2 + 16 * qd);
+    };
+    if constexpr (kOwnQueries && EB == 2) { if (w < kTiles) own_queries(); }
     uint4 q_piece = make_uint4(0, 0, 0, 0);
     if (!kOwnQueries && tid < kQueryPieces) q_piece = *reinterpret_cast<const uint4*>(a.q + qhead0 * kRowBytes + 16 * tid);
     auto leave_queries = [&]() {                                      // a barrier must follow
@@ -1565,12 +1576,7 @@ __global__ __launch_bounds__(kBlockThreads) void attend_kernel(AttArgs args) {
             leave_sums<G>(sm + w * kTileBytes, o);
         } else if (w < kTiles) {
             char* sm_v = sm + w * kTileBytes;                         // this wave's value tile
-            uint4 qB[X::kPieces];                                     // lane (t16, qd): pieces of head t16
-            if constexpr (kOwnQueries) {
-#pragma unroll
-                for (int s2 = 0; s2 < X::kPieces; ++s2)
-                    qB[s2] = *reinterpret_cast<const uint4*>(a.q + (qhead0 + min(t16, G - 1)) * kRowBytes + 64 * s2 + 16 * qd);
-            }
+            if constexpr (kOwnQueries && EB == 4) own_queries();
             uint4 kA[kPasses][X::kPieces], vR[kPasses][X::kLoads];
             unsigned long long vm[kPasses];                           // bit t (t < 16): token t of the tile is real
 #pragma unroll

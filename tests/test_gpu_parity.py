@@ -1027,6 +1027,26 @@ def test_attend_blocks_of_dims_of_any_number_of_heads(U, H, G, budget):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("budget", [130, 450, 4100])
+def test_attend_blocks_of_tokens(U, oracle32, dtype, G, budget):
+    """Blocks of 128 and 256 tokens, for every number of heads on a KV head: the queries reach a wave from memory or, eight bf16 heads, through LDS.  (bf16, 130 tokens:
+    blocks of dims, with one tile a wave.)"""
+    wl = gen.CFG0.scaled(dtype=dtype, n_q_heads=8 * G)
+    D = wl.head_dim
+    g = torch.Generator().manual_seed(budget + G)
+    q, K, V = (torch.randn(*n, D, generator=g).to(wl.torch_dtype) for n in ((8 * G,), (8, budget), (8, budget)))
+    n_tok = np.array([budget, budget - 1, 0, 1, 127, 129, budget - 16, budget // 2], dtype=np.int32)
+    out, lse = torch.full((8 * G, D), 7.0, device=U.DEV), torch.full((8 * G,), 7.0, device=U.DEV)
+    _say("attend, blocks of tokens", dtype, G, budget)
+    U.make_ctx(wl, 4096, 64, budget).attend(q.to(U.DEV), K.to(U.DEV), V.to(U.DEV), U.i32(n_tok), budget, out, lse)
+    torch.cuda.synchronize()
+    o_ref, l_ref = oracle32.attend(U.np_of(q), U.np_of(K), U.np_of(V), n_tok)
+    _same_as_oracle(out.cpu().numpy(), o_ref, ATT_TOL[dtype], (G, budget))
+    _same_as_oracle(lse.cpu().numpy(), l_ref, ATT_TOL[dtype], (G, budget))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("budget", [17, 129, 257, 1025])
 def test_attend_carries_values_that_are_not_finite(U, oracle32, dtype, budget):
     """The last of `budget` rows is alone in its 16-token tile, and from 257 rows on in its block: NaN there, as anywhere, is NaN in
