@@ -147,9 +147,9 @@ __global__ __launch_bounds__(kSegThreads) void seg_scan_kernel(const int32_t* __
 // launch (4 tokens per thread and preceding block, from L2).  Bound by latency: two dependent memory round trips and a block
 // scan.  REPORT: the block that finishes last also stores S to pinned host memory, when the results of every block are where the
 // host and all XCDs see them, so that the host can poll the word instead of copying it and waiting for the stream.  They are written
-// there store by store; a release at system scope writes back an XCD's whole L2, with what earlier work left in it.  Us a call as the host sees it, with ordinary
-// stores, a release by a wave of every block, and words and blocks read one after the other / now: 1531 tokens 19.7 / 16.2, 8192 19.9 / 15.3, 32768 19.7 / 17.0, 131072
-// 27.2 / 23.8, behind a kernel that wrote 64 MB 31.6 / 25.6.
+// there store by store; a release at system scope goes through an XCD's whole L2.  Us a call as the host sees it, with ordinary stores, a release by a wave of every
+// block, and words and blocks read one after the other / now, both in turn in one program (medians): 1531 tokens 16.4 / 16.7, 8192 16.9 / 16.8, 32768 19.3 / 18.9, 131072
+// 27.2 / 24.2; behind a kernel that writes 64 MB 19.1 / 18.8, 20.4 / 19.8, 24.2 / 23.0, 38.6 / 32.5.
 template <bool REPORT>
 __global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* __restrict__ tok, int32_t T,
                                                                 const uint32_t* __restrict__ bitmap, int32_t vocab,
@@ -187,22 +187,27 @@ __global__ __launch_bounds__(kBlockThreads) void seg_one_kernel(const int32_t* _
     auto is_term = [&](int32_t id) -> bool {
         return (uint32_t)id < (uint32_t)vocab && ((sm_bits[(uint32_t)id >> 5] >> (id & 31)) & 1u);
     };
-    // terminators before the block: number, and 1 + position of the last one (0: none)
+    // Terminators before the block: number, and 1 + position of the last one (0: none).  Four preceding blocks at a time, what is left over one by one.  Us of kernel, one
+    // by one / four at a time with the last four made up / this: 8192 tokens 4.4 / 4.7 / 4.4, 32768 7.2 / 7.05 / 6.95, 131072 18.2 / 16.8 / 15.5.  (The rest together, a form for
+    // each number: 1531 tokens 3.5 -> 3.65, by the size of the code.)
     uint32_t pre_cnt = 0, pre_last = 0;
-    for (int32_t first = 0; first < (int32_t)blockIdx.x; first += 4) {
-        int4 v[4];
+    auto count_before = [&](int32_t first, auto blocks) {
+        constexpr int N = decltype(blocks)::value;
+        int4 v[N];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const int4*>(tok + min(first + u, (int32_t)blockIdx.x - 1) * kSegOneBlockTok + 4 * tid);
+        for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const int4*>(tok + (first + u) * kSegOneBlockTok + 4 * tid);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < N; ++u) {
             const int32_t p[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            if (first + u < (int32_t)blockIdx.x) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (is_term(p[k])) { pre_cnt += 1; pre_last = (uint32_t)((first + u) * kSegOneBlockTok + 4 * tid + k + 1); }
-            }
+            for (int k = 0; k < 4; ++k)
+                if (is_term(p[k])) { pre_cnt += 1; pre_last = (uint32_t)((first + u) * kSegOneBlockTok + 4 * tid + k + 1); }
         }
-    }
+    };
+    int32_t first = 0;
+    for (; first + 4 <= (int32_t)blockIdx.x; first += 4) count_before(first, std::integral_constant<int, 4>{});
+#pragma unroll 1
+    for (; first < (int32_t)blockIdx.x; ++first) count_before(first, std::integral_constant<int, 1>{});
     uint32_t cnt = 0, last = 0, flags = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
