@@ -371,13 +371,17 @@ template <int EB, int SVB, bool LARGE>
 __global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const char* __restrict__ K, int32_t T,
                                                                          const int32_t* __restrict__ sent_off_all,
                                                                          int32_t off_layer_stride, int32_t Hkv,
-                                                                         int32_t S, char* __restrict__ semvec) {
+                                                                         int32_t S, char* __restrict__ semvec, bool runs) {
     using R = Row<EB>;
     const int lane = threadIdx.x & 63;
-    // Blocks in runs of an XCD.  Us, blocks as they come / runs of 32, 32 layers x 8 heads: 32768 tokens in lognormal lengths, fp32 table 416 / 370, E4M3 375 / 344,
+    // runs: blocks in runs of an XCD, see the launch.  Us, blocks as they come / runs of 32, 32 layers x 8 heads: 32768 tokens in lognormal lengths, fp32 table 416 / 370, E4M3 375 / 344,
     // geometric lengths 380 / 376 (runs of 4 381, 16 379, 64 380, 256 375, an eighth of the grid 425), 8192 tokens, lognormal, fp32 109.5 / 105, E4M3 95 / 90, 1531 the same.
-    const uint32_t at = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-    const uint32_t by = at / gridDim.x, bx = at - by * gridDim.x;
+    uint32_t bx = blockIdx.x, by = blockIdx.y;
+    if (runs) {
+        const uint32_t at = xcd_run(bx + gridDim.x * by, gridDim.x * gridDim.y);
+        by = at / gridDim.x;
+        bx = at - by * gridDim.x;
+    }
     const int32_t s = bx * (LARGE ? 8 : 4) + (threadIdx.x >> 6);
     if (s >= S) return;                                   // wave-uniform
     const int64_t lh = by;
@@ -504,12 +508,19 @@ static void launch_semvec_t(Ctx* c, const void* K_pool, int32_t T, const int32_t
     // table / table and the scores of every layer, small against LARGE: 1531 tokens (15000 rows) 25.6 / 101 against 30.6 / 111,
     // 8192 (105000) 104 / 183 against 111 / 197, 11000 (142000) 137 / 217 against 139 / 225, 16384 (206000) 201 / 284 against 200 / 286 and, keys
     // just written, 212 / 298 against 198 / 288, 32768 426 / 528 against 397 / 503.
-    if ((int64_t)LH * S <= kSemvecSmallRows)
+    // Blocks are dealt in runs where a head has 6000 tokens and more, a launch 4096 blocks and a bucket fewer than 128 tokens on average.  fp32 table, 8 heads, us, as they
+    // come / in runs: 32 layers of 2048 tokens 26.5 / 27.05, 4 of 4096 10.2 / 10.5; one of 32768 (2736 blocks) 15.0 / 15.5, 32 heads of 8192 (3296) 14.5 / 14.8, 8 layers of 8192 in buckets of 12 tokens (10900) 31.0 / 29.95, of 20 the same, 2 layers of
+    // 32768 (5500) 28.05 / 27.5; 16 layers of 32768 in buckets of 50 tokens 214 / 193, 100 192.8 / 187.9, 200 188.1 / 189.1, 500 192.7 / 201, 2000 223.5 / 229.7,
+    // fp32 keys, 100 371 / 365, 200 362.5 / 362.5, 500 370 / 380.
+    const bool small = (int64_t)LH * S <= kSemvecSmallRows;
+    const int64_t blocks = ((int64_t)S + (small ? 4 : 8) - 1) / (small ? 4 : 8) * LH;
+    const bool runs = T >= kSemvecRunTokens && blocks >= kSemvecRunBlocks && T < kSemvecRunBucket * (int64_t)S;
+    if (small)
         hipLaunchKernelGGL((semvec_kernel<EB, SVB, false>), grid(4), dim3(4 * kWave), 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
-                           c->d.n_kv_heads, S, (char*)semvec);
+                           c->d.n_kv_heads, S, (char*)semvec, runs);
     else
         hipLaunchKernelGGL((semvec_kernel<EB, SVB, true>), grid(8), dim3(8 * kWave), 0, c->stream, (const char*)K_pool, T, sent_off, off_layer_stride,
-                           c->d.n_kv_heads, S, (char*)semvec);
+                           c->d.n_kv_heads, S, (char*)semvec, runs);
 }
 
 template <int EB>

@@ -20,6 +20,7 @@ constexpr int kSegOneMaxTok = 131072;         // prompts it takes
 constexpr int kSegOneMaxWords = 15360;        // terminator bitmap words it keeps in LDS (vocabularies up to 491520)
 
 constexpr int kSemvecSmallRows = 160 * 1024;   // rows of a table that is built in small blocks with plain stores
+constexpr int kSemvecRunTokens = 6000, kSemvecRunBlocks = 4096, kSemvecRunBucket = 128;   // tokens of a head, blocks, tokens of a bucket: the line of runs
 constexpr int kSemvecShortWaves = 8;          // waves of a block that takes several short buckets per wave
 constexpr int kSemvecShortBytes = 2304;       // mean bytes of a bucket's rows below which a wave takes several buckets
 

@@ -216,10 +216,10 @@ def test_large_tables_of_the_other_types(U, oracle32, dtype, sv_dtype):
             assert U.e4m3_table_close(got, ref, oracle32.e4m3_decode)
 
 
-@pytest.mark.parametrize("S", [165, 169, 171, 341, 512, 685])
+@pytest.mark.parametrize("S", [165, 169, 171, 341, 512, 685, 2728, 2729, 2816, 2818, 3413])
 def test_semvec_blocks_dealt_in_groups(U, oracle32, S):
-    """3 layers x 2 heads of ceil(S / 4) blocks each: 252 (no group of 256), 258 (two past the first), 516, 768 (three groups) and 1032 of them; one float per
-    bucket tells whose rows it is made of."""
+    """3 layers x 2 heads of ceil(S / 4) blocks each: 252 to 1032 and 4092 of them, which take their buckets as they come, and, in groups of 256, 4098 (sixteen groups and
+    two past them), 4224 (half a group), 4230 and 5124 (twenty groups and four); one float per bucket tells whose rows it is made of."""
     wl = gen.CFG3.scaled(n_layers=3, n_kv_heads=2, n_q_heads=8, n_tokens=10 * S, dtype="f32", len_dist=("fixed", 10))
     off = np.arange(S + 1, dtype=np.int32) * 10
     whose = torch.arange(6 * S, dtype=torch.float32, device=U.DEV).reshape(3, 2, S)
@@ -228,7 +228,7 @@ def test_semvec_blocks_dealt_in_groups(U, oracle32, S):
     _say("semvec", S)
     U.make_ctx(wl, 10 * S, S, 16).build_semvec(K, U.i32(off), S, sv)
     torch.cuda.synchronize()
-    assert torch.equal(sv, whose[..., None].expand(-1, -1, -1, 128))      # sums of ten equal whole numbers below 2^17 and their quotients are exact
+    assert torch.equal(sv, whose[..., None].expand(-1, -1, -1, 128))      # sums of ten equal whole numbers below 2^18 and their quotients are exact
 
 
 # ----------------------------------------------------------------------------- decode chain, per stage
