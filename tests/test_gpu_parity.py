@@ -231,6 +231,30 @@ def test_semvec_blocks_dealt_in_groups(U, oracle32, S):
     assert torch.equal(sv, whose[..., None].expand(-1, -1, -1, 128))      # sums of ten equal whole numbers below 2^18 and their quotients are exact
 
 
+@pytest.mark.parametrize("sv_dtype, rows", [("f32", 32), ("bf16", 64), ("fp8", 128)])
+@pytest.mark.parametrize("blocks, extra", [(254, 1), (255, 0), (255, 5), (256, 3), (512, 1)])
+def test_score_blocks_dealt_in_groups(U, sv_dtype, rows, blocks, extra):
+    """255 blocks a head (no group of 256), the last one short and whole, 256, 257 and 513 with a short last one: a bucket's vector spells its number in digits of base 16, exact in every type,
+    and the query weighs them, so that a score says which bucket it is of."""
+    H, G, D, S = 3, 4, 128, rows * blocks + extra
+    number = torch.arange(H * S, device=U.DEV).reshape(H, S)
+    table = torch.zeros(1, H, S, D, device=U.DEV)
+    q = torch.zeros(H * G, D, device=U.DEV)
+    for i in range(5):
+        table[0, :, :, 27 * i + 3] = ((number >> (4 * i)) & 15).float()           # dims of different lanes
+        q[:, 27 * i + 3] = 16.0 ** i / G                                          # the group's heads add up to a digit's weight
+    if sv_dtype == "fp8":
+        table = table.cpu().to(torch.float8_e4m3fn).view(torch.uint8).to(U.DEV)
+    elif sv_dtype == "bf16":
+        table = table.to(torch.bfloat16)
+    wl = gen.CFG3.scaled(n_layers=1, n_kv_heads=H, n_q_heads=H * G)
+    score = torch.full((H, S), -777.0, device=U.DEV)
+    _say("score", sv_dtype, S)
+    U.make_ctx(wl, S, S, 16, sv_dtype=sv_dtype).score(0, q.to(wl.torch_dtype), table, S, score)
+    torch.cuda.synchronize()
+    assert torch.equal(score, number.float())                        # whole numbers below 2^18: every sum is exact
+
+
 # ----------------------------------------------------------------------------- decode chain, per stage
 
 def _chain_case(U, oracle32, wl, seed, budget, pool_in_host=False, layers=None, sv_dtype="f32"):
