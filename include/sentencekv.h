@@ -118,7 +118,7 @@ int skv_set_single_launch(skv_ctx* ctx, int32_t enable);
  * term_bitmap  dev  [ceil(vocab / 32)]       sent_off    dev [max_sentences + 1]
  * n_sent_dev   dev  [1], receives S          sent_len    dev [max_sentences]
  * n_sent_host  host [1] or NULL.  Non-NULL: the call waits until all results are written, and with them everything that was
- *              queued on the stream before, stores S there and returns SKV_ECAPACITY if S > max_sentences.  (For prompts of
+ *              queued on the stream before, so that other streams, copies and the host may read both, stores S there and returns SKV_ECAPACITY if S > max_sentences.  (For prompts of
  *              up to 131072 tokens over up to 491520 ids the kernel itself reports S to the host, and the stream need not be
  *              idle yet when the call returns.  A failure of that work is returned as SKV_EHIP.)  Buckets beyond max_sentences are never written
  *              (n_sent_dev still receives the true S).  NULL: fully asynchronous.

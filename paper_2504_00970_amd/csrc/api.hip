@@ -50,8 +50,10 @@ inline int sv_bytes(const Ctx& c) { return c.d.semvec_dtype == SKV_BF16 ? 2 : c.
 // ---- skv_segment's wait for the number of sentences ---------------------------------------------------------------------
 constexpr unsigned int kNoCount = 0xffffffffu;
 
-// The kernel stores the count after it has written all its results back, and it starts after everything queued before
-// it: once the word is there, the stream's work up to this call is done.  Polling a word of host memory costs about a
+// The kernel stores the count when all its results are written through to memory, and it starts after everything queued before
+// it has ended: once the word is there, the stream's work up to this call is done.  What earlier kernels have stored is in memory by then without this kernel's
+// doing: the runtime ends a kernel with a release at device scope, since the blocks of the next one run on other XCDs, whose L2s do not see each other's lines, and stores to
+// coherent host memory go past the L2s; copies signal their own end (pinned by test_segment_returns_behind_earlier_work).  Polling a word of host memory costs about a
 // microsecond where a copy and a stream synchronisation cost 15.  The stream is asked every few thousand reads, so that a
 // launch that failed ends the wait, and once more at the end (no measurable time), so that a failure of earlier work is reported as a
 // synchronisation would: -1 then, or if the word does not arrive.

@@ -105,7 +105,10 @@ __device__ __forceinline__ void st_agent64(float2* p, float x, float y) {       
 // level all XCDs share, so a device-scope relaxed load issued by any block after it observed the later counter
 // increment returns the stored value.  The language's memory model does not promise this for relaxed accesses to
 // different locations; it is how write-through stores and the store counter behave on this chip, and it is guarded by
-// test_repeated_launches_reproduce_their_results.  The single-launch step does not rely on it: there every word
+// test_repeated_launches_reproduce_their_results.  The segmentation that reports its count relies on the same at system
+// scope: its relaxed system-scope stores, once they have left the store counter, are in the memory that the host, copies and
+// kernels of other streams read, so that whoever sees the count in host memory (stored relaxed, behind an arrival counter at
+// device scope) finds them; guarded by test_segment_returns_behind_earlier_work.  The single-launch step does not rely on it: there every word
 // carries its own validity tag (st_tagged).
 __device__ __forceinline__ void block_sync_after_stores() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

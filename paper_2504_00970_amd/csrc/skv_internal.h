@@ -112,8 +112,8 @@ struct SeqView {
 };
 
 // ---- launchers (defined in prefill.hip / decode.hip); each returns the hipError_t of its launch -----
-// report: every result is written back and S then stored to n_sent_host, for a host that polls it (only where
-// segment_reports says that the launch can do it)
+// report: every result is written through to memory and S then stored to n_sent_host, for a host that polls it (only
+// where segment_reports says that the launch can do it)
 bool segment_reports(const Ctx* c, int32_t T, int32_t vocab);
 hipError_t launch_segment(Ctx* c, const int32_t* tok, int32_t T, const uint32_t* bitmap, int32_t vocab,
                           int32_t* seg_id, int32_t* sent_off, int32_t* sent_len, int32_t* n_sent_dev, bool report);

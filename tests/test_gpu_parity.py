@@ -112,6 +112,40 @@ def test_segment_blocks_are_whole_when_the_call_returns(U, oracle32, blocks, ext
         assert np.array_equal(got[0], seg_ref) and np.array_equal(got[1], off_ref) and np.array_equal(got[2], len_ref)
 
 
+@pytest.mark.parametrize("T", [1531, 40000])
+def test_segment_returns_behind_earlier_work(U, oracle32, T):
+    """A call that returns the number of sentences has waited for its own results and for everything queued before it: another stream, a copy to the host
+    by that stream and the host itself find all of it, call after call, without the stream of the call being waited for."""
+    vocab = 131200
+    rng = np.random.default_rng(T)
+    bitmap = np.packbits(rng.random(vocab) < 0.05, bitorder="little").view(np.uint32)
+    toks = [rng.integers(0, vocab, size=T).astype(np.int32) for _ in range(2)]
+    refs = [oracle32.segment(t, bitmap, vocab) for t in toks]
+    ctx = U.make_ctx(gen.CFG3.scaled(n_layers=1), T, max(r[3] for r in refs), 16)
+    d_tok, d_bm = [U.i32(t) for t in toks], torch.as_tensor(bitmap.view(np.int32)).to(U.DEV)
+    want = [[U.i32(r[0]), U.i32(r[1][:r[3] + 1]), U.i32(r[2][:r[3]])] for r in refs]
+    cap = max(r[3] for r in refs)
+    seg, off, ln, n = U.empty_i32(T, fill=-7), U.empty_i32(cap + 1, fill=-7), U.empty_i32(cap, fill=-7), U.empty_i32(4, fill=-7)
+    written = U.empty_i32(1 << 23, fill=-7)                            # 32 MB, as much as the second-level caches hold
+    by_call, by_copy = (torch.empty(1 << 20, dtype=torch.int32, pin_memory=True) for _ in range(2))
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    _say("segment behind earlier work", T)
+    for i in range(200):
+        k = i % 2
+        written.fill_(i)
+        by_call.copy_(written[-(1 << 20):], non_blocking=True)
+        S = ctx.segment(d_tok[k], d_bm, vocab, seg, off, ln, n)
+        host = int(by_call.min()), int(by_call.max())
+        with torch.cuda.stream(other):
+            by_copy.copy_(written[:1 << 20], non_blocking=True)
+            wrong = [(written != i).sum(), (seg != want[k][0]).sum(), (off[:S + 1] != want[k][1]).sum(), (ln[:S] != want[k][2]).sum(), (n[:1] != S).sum()]
+            wrong = torch.stack(wrong).cpu().tolist()
+        other.synchronize()
+        assert S == refs[k][3] and host == (i, i), i
+        assert not any(wrong) and bool((by_copy == i).all()), (i, wrong)
+
+
 def test_segment_reports_capacity_overflow(U, oracle32):
     import paper_2504_00970_amd as skv
     tok = np.array([7] * 50, dtype=np.int32)
