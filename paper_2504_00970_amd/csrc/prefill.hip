@@ -423,7 +423,8 @@ __global__ __launch_bounds__((LARGE ? 8 : 4) * kWave) void semvec_kernel(const c
     // whole piece.  Before, 16 (fp32: 32) lanes held all sums and stored eight (four) each, an fp32 vector in two pieces with gaps, reduced ones with plain stores
     // in large tables too, where a piece goes past the caches now like everything else there.  32 layers x 8 heads, us, before / now: 32768 tokens, table in fp32
     // 388 / 378, bf16 403 / 361, E4M3 379 / 347; 16384, E4M3 204 / 180; table and the scores of every layer: 494 / 483, 487 / 449, 467 / 445; 283 / 274.  Up to 8192
-    // tokens the same within 1 %.  Not kept: loads counted out by the bucket's length instead of masked, and 52 registers instead of more, 32768 tokens 388 / 405;
+    // tokens the same within 1 %.  What carries it is the one piece past the caches (an fp32 table of 205056 KiB was written as 253048): with plain stores 16 layers of 32768 tokens
+    // take 185 -> 199, bf16 177 -> 195, with shuffles for the swaps or 32 lanes of 16 bytes for the 64 of 8 the same as this.  Not kept: loads counted out by the bucket's length instead of masked, and 52 registers instead of more, 32768 tokens 388 / 405;
     // 24 or 16 waves on a compute unit 407, 475.
     float h[4];
     if constexpr (R::RPW == 4) {
