@@ -472,20 +472,19 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 // first bucket that overflows (the "cut") is found without sorting, by a length-weighted radix select
 // on an order-preserving 32-bit image of the score: 11 + 11 + 10 bit digits, most significant first.
 // Per pass: LDS atomics build a histogram of (count, total length) per digit and the total lengths of
-// groups of 32 digits; after the one barrier of the pass every wave finds the crossing digit by itself: a lane
+// groups of 64 digits; after the one barrier of the pass every wave finds the crossing digit by itself: two lanes
 // per group, from the top one down, a scan and the lane that sees the budget crossed, then a lane per digit
 // of that group.  (The block finding it together, thread t with digits 2047-2t and 2046-2t, a block scan
 // and the crossing thread telling the others, takes two more barriers and trips to LDS a pass: keys in
 // registers to cut known 1.1 us, this way 0.7; a layer of the single-launch step of 32768 tokens 11.3 -> 11.1 us.)
-// Scores close to each other, as keys with a large common part give them, fall into a few groups (one spans 3 % of the best
-// score), and the lanes of a wave that add to one word do so one after the other: a group has four counters, eight beyond 2048 buckets, for the lanes in turn.
-// Us, the block scan / one counter a group / this, scores 3 %, 1 % and 0.3 % apart (standard deviation over mean), then normal scores: a layer of the single-launch
-// step of 131072 tokens, 5461 buckets, 16.6, 16.7, 17.3; 16.1 / 17.4, 18.8, 20.8; 15.6 / 16.5, 16.7, 17.2; 15.8, of 32768 tokens 12.0, 12.05, 12.1; 11.35 / 11.4, 11.6, 12.25;
-// 10.55 / 11.25, 11.3, 11.5; 10.6; skv_select of 1400 buckets 6.25, 6.3, 6.4; 5.8 / 6.25, 6.7, 7.2; 5.45 / 6.05, 6.2, 6.3; 5.5, of 5200 8.2, 8.3, 8.45; 8.0 / 9.0, 10.6, 12.4; 7.6 /
-// 8.2, 8.2, 8.4; 7.9.  The last one, skv_select of more than 2048 buckets, takes the groups' totals from the histogram, a wave four groups, with a barrier more (eight
-// counters: 8.2, 8.5, 8.7; 7.75); the steps, whose blocks have more to do, would lose by that (131072 tokens, normal scores 15.75 -> 16.0).  Not kept: four counters there
-// (16.8, 17.2, 17.8), sixteen (17.1, 17.3, 17.8), eight up to 2048 buckets (32768 tokens, normal scores 10.65), neighbouring buckets of a thread added up first (131072
-// tokens 18.1).  The three
+// Scores close to each other, as keys with a large common part give them, fall into a few groups (one spans 6 % of the best
+// score), and the lanes of a wave that add to one word do so one after the other: a group has eight counters, for the lanes in turn, read 16 bytes a lane.
+// Us, the block scan / 64 groups of one counter each / this, scores 3 %, 1 % and 0.3 % apart (standard deviation over mean), then normal scores: a layer of the single-launch
+// step of 131072 tokens, 5461 buckets, 16.6, 16.7, 17.3; 16.1 / 17.4, 18.7, 20.9; 15.55 / 16.45, 16.6, 17.1; 15.6, of 32768 tokens 11.95, 11.9, 12.1; 11.45 / 11.4, 11.65, 12.2;
+// 10.55 / 11.2, 11.15, 11.3; 10.55; skv_select of 1400 buckets 6.25, 6.25, 6.4; 5.8 / 6.2, 6.6, 7.2; 5.45 / 6.05, 6.1, 6.25; 5.55, of 5200 8.2, 8.3, 8.45; 8.0 / 9.0, 10.6, 12.4; 7.6 /
+// 8.3, 8.3, 8.5; 7.95.  The last one, skv_select of more than 2048 buckets, takes the totals of 64 groups from the histogram, a wave four groups, with a barrier more (64 groups of
+// eight counters: 8.2, 8.5, 8.7; 7.75); the steps, whose blocks have more to do, would lose by that (131072 tokens, normal scores 15.75 -> 16.0).  Not kept: 64 groups of four
+// counters (131072 tokens 16.8, 17.2, 17.8; 15.75), of eight (16.5, 16.7, 17.15; 15.7), of sixteen (17.1, 17.3, 17.8; 16.35), neighbouring buckets of a thread added up first (18.1, 18.1, 18.6; 17.5).  The three
 // histograms are zeroed up front.  The search stops as soon as the crossing digit holds a single bucket
 // (typically after one pass); buckets with exactly the cut's score are resolved in id order by a scan.
 //
@@ -499,12 +498,11 @@ hipError_t launch_score(Ctx* c, const void* q, const void* semvec_layer, const S
 
 constexpr int kSelKreg = 6;                                   // 1024 threads x 6 buckets in registers: S <= 6144
 constexpr int kBins = 2048;                                   // 11-bit digits (the last pass uses 1024)
-constexpr int kGroupBins = kBins / kWave;                     // digits of a group: 64 groups, a lane each
-constexpr int kGroupCounters = 8;                             // counters of a group, at most
+constexpr int kGroupCounters = 8;                             // counters of a group's total: lane l adds to l % 8
 
 struct SelectShared {
     __attribute__((aligned(16))) unsigned long long hist[3][kBins];           // packed (count << 32 | total length) per digit
-    __attribute__((aligned(16))) uint32_t group[3][kWave * kGroupCounters];   // total length per group of 32 digits, in parts
+    __attribute__((aligned(16))) uint32_t group[3][kWave / 2 * kGroupCounters];   // total length per group of digits, in parts
     uint32_t wave_tot[3][kBlockWaves];                        // one slot per block scan
     int32_t gave_up;                                          // tagged scores: set by a thread whose wait ran out
     __attribute__((aligned(16))) uint32_t wmax[kBlockWaves];  // largest key per wave
@@ -524,8 +522,8 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
                                              uint32_t tag = 0, int32_t wait_limit = 0, bool* ok_out = nullptr,
                                              uint32_t* __restrict__ key_lds = nullptr /* TAGGED: KREG * kBlockThreads words */) {
     constexpr bool kByHist = COUNT && KREG > 2;                // the groups' totals: from the histogram, else counted beside it
-    constexpr int kCounters = kByHist ? 1 : KREG > 2 ? kGroupCounters : 4;       // of a group: lane l adds to l % kCounters
-    static_assert(3 * kWave * kGroupCounters / 4 <= kBlockThreads, "zeroed by a store each");
+    constexpr int kGroupBins = kByHist ? kBins / kWave : 2 * kBins / kWave;      // digits of a group: a lane for each group, or two
+    static_assert(sizeof(sh.group) == 3 * kWave * 16, "16 bytes a lane and pass: half of a group's counters, or a group's total");
     const int tid = threadIdx.x;
     *n_sel_out = 0;
     *n_tok_out = 0;
@@ -576,7 +574,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
         unsigned long long* h = &sh.hist[0][0];
 #pragma unroll
         for (int i = 0; i < 3 * kBins / kBlockThreads; ++i) h[i * kBlockThreads + tid] = 0;
-        if (!kByHist && tid < 3 * kWave * kCounters / 4) *reinterpret_cast<uint4*>(&sh.group[tid / (kWave * kCounters / 4)][tid % (kWave * kCounters / 4) * 4]) = make_uint4(0, 0, 0, 0);
+        if (!kByHist && tid < 3 * kWave) reinterpret_cast<uint4*>(sh.group)[tid] = make_uint4(0, 0, 0, 0);
     };
     zero_hist();
     if (tid == 0) sh.gave_up = 0;
@@ -710,7 +708,7 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
             auto count = [&](uint32_t k, int32_t ln) {
                 const uint32_t digit = (k >> nshift) & (nbins - 1);
                 atomicAdd(&H[digit], (1ull << 32) | (unsigned long long)(uint32_t)ln);
-                if (!kByHist) atomicAdd(&sh.group[pass][digit / kGroupBins * kCounters + tid % kCounters], (uint32_t)ln);
+                if (!kByHist) atomicAdd(&sh.group[pass][digit / kGroupBins * kGroupCounters + tid % kGroupCounters], (uint32_t)ln);
             };
 #pragma unroll
             for (int i = 0; i < KREG; ++i)
@@ -743,13 +741,17 @@ __device__ __forceinline__ void select_block(const float* __restrict__ sc, const
                 carry = __builtin_amdgcn_readlane((int)above, l);
                 return l;
             };
-            uint32_t part[kCounters], in_group = 0;
-            __builtin_memcpy(part, __builtin_assume_aligned(&sh.group[pass][(kWave - 1 - lane) * kCounters], 4 * (kCounters < 4 ? kCounters : 4)), sizeof(part));
-#pragma unroll
-            for (int c = 0; c < kCounters; ++c) in_group += part[c];
-            const int grp = crossing(in_group);
-            if (grp < 0) { found_none = true; break; }             // the buckets of this attempt all fit (only possible in pass 0)
-            const int top = (kWave - 1 - grp) * kGroupBins + kGroupBins - 1;                  // the group's highest digit
+            uint32_t in_group;
+            if constexpr (kByHist) {
+                in_group = sh.group[pass][kWave - 1 - lane];
+            } else {                                               // the first of a group's two lanes stands for it
+                const uint4 x = *reinterpret_cast<const uint4*>(&sh.group[pass][4 * (kWave - 1 - lane)]);
+                in_group = dpp_add_u32<0xB1, 0xf>((x.x + x.y) + (x.z + x.w));
+                if (lane & 1) in_group = 0;
+            }
+            const int at = crossing(in_group);
+            if (at < 0) { found_none = true; break; }              // the buckets of this attempt all fit (only possible in pass 0)
+            const int grp = kByHist ? kWave - 1 - at : (kWave - 1 - at) / 2, top = (grp + 1) * kGroupBins - 1;      // its highest digit
             const unsigned long long v = lane < kGroupBins ? H[top - lane] : 0ull;
             const int sub = crossing((uint32_t)v);
             const int digit = top - sub;
